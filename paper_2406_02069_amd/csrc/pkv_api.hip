@@ -523,7 +523,7 @@ int pkv_decode_attention(const pkv_decode_desc* desc, const void* q, const void*
   if (need > 0 && (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need)) return PKV_ERR_WORKSPACE;
   DecodeArgs da;
   memset(&da, 0, sizeof(da));
-  da.S = decode_splits(d.B, d.Hkv, d.k_cap);
+  da.S = decode_splits_used(d.B, d.Hkv, d.d, d.k_cap);
   da.chunk = ((d.k_cap + da.S - 1) / da.S + 31) / 32 * 32;
   da.part_o = static_cast<float*>(workspace);
   da.part_mz = da.part_o ? da.part_o + (size_t)d.B * d.Hkv * da.S * 8 * d.d : nullptr;
@@ -536,6 +536,7 @@ int pkv_decode_attention(const pkv_decode_desc* desc, const void* q, const void*
   da.lse = lse_out;
   da.B = d.B; da.Hq = d.Hq; da.Hkv = d.Hkv; da.G = d.Hq / d.Hkv; da.d = d.d; da.k_cap = d.k_cap;
   da.page_size = d.page_size; da.num_pages = d.num_pages; da.max_pages = d.max_pages;
+  decode_page_division(d.page_size, &da.page_shift, &da.page_magic);
   da.c_sb = d.c_sb; da.c_sh = d.c_sh; da.c_st = d.c_st;
   da.scale_log2 = (float)(1.4426950408889634 / sqrt((double)d.d));
   return launch_decode_attention(da, static_cast<hipStream_t>(stream)) == hipSuccess ? PKV_OK : PKV_ERR_HIP;
@@ -544,8 +545,8 @@ int pkv_decode_attention(const pkv_decode_desc* desc, const void* q, const void*
 // How the layers of a decoding step are cut into key ranges (from the descriptors alone).
 namespace {
 struct DecodeLayersPlan {
-  int chunk_target;
-  int64_t records;  // partial-result records of the layers with more than one range
+  int chunk_target;  // keys per range
+  int64_t records;   // partial-result records that the workspace has room for
   bool ok;
 };
 DecodeLayersPlan decode_layers_plan(int32_t L, const pkv_decode_desc* descs) {
@@ -558,10 +559,11 @@ DecodeLayersPlan decode_layers_plan(int32_t L, const pkv_decode_desc* descs) {
     if (d.B != d0.B || d.Hq != d0.Hq || d.Hkv != d0.Hkv || d.d != d0.d || d.page_size != d0.page_size) return p;
     rows += (int64_t)d.B * d.Hkv * d.k_cap;
   }
-  p.chunk_target = decode_layers_chunk(rows);
+  p.chunk_target = decode_layers_chunk_used((int64_t)L * descs[0].B * descs[0].Hkv, rows);
+  const int chunk_room = decode_layers_chunk(rows);  // (never larger: the ranges used are no more than there is room for)
   for (int32_t l = 0; l < L; ++l) {
     int chunk;
-    const int S = decode_layers_splits(descs[l].k_cap, p.chunk_target, &chunk);
+    const int S = decode_layers_splits(descs[l].k_cap, chunk_room, &chunk);
     if (S > 1) p.records += (int64_t)descs[l].B * descs[l].Hkv * S;
   }
   p.ok = true;
@@ -608,7 +610,8 @@ int pkv_decode_attention_layers(int32_t L, const pkv_decode_desc* descs, const v
     a.part_mz = part_mz;
     a.L = nl; a.B = d0.B; a.Hq = d0.Hq; a.Hkv = d0.Hkv; a.G = d0.Hq / d0.Hkv; a.d = d0.d; a.page_size = d0.page_size;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)d0.d));
-    int64_t wg = 0;
+    decode_page_division(d0.page_size, &a.page_shift, &a.page_magic);
+    int64_t wg = 0, rows = 0;
     int max_chunk = 0;
     bool any_split = false;
     for (int32_t i = 0; i < nl; ++i) {
@@ -627,6 +630,7 @@ int pkv_decode_attention_layers(int32_t L, const pkv_decode_desc* descs, const v
       ly.wg0 = (int32_t)wg;
       ly.part0 = (int32_t)part0;
       wg += (int64_t)d.B * d.Hkv * ly.S;
+      rows += (int64_t)d.B * d.Hkv * d.k_cap;
       if (ly.S > 1) {
         part0 += (int64_t)d.B * d.Hkv * ly.S;
         any_split = true;
@@ -634,7 +638,7 @@ int pkv_decode_attention_layers(int32_t L, const pkv_decode_desc* descs, const v
       if (ly.chunk > max_chunk) max_chunk = ly.chunk;
     }
     if (wg > 0x7FFFFFFF || part0 > 0x7FFFFFFF) return PKV_ERR_UNSUPPORTED;
-    if (launch_decode_attention_layers(a, (int)wg, max_chunk, any_split, static_cast<hipStream_t>(stream)) != hipSuccess)
+    if (launch_decode_attention_layers(a, (int)wg, decode_waves(wg, rows, d0.d, a.G, max_chunk), any_split, static_cast<hipStream_t>(stream)) != hipSuccess)
       return PKV_ERR_HIP;
   }
   return PKV_OK;

@@ -4,259 +4,390 @@
 // embeddings); the cache is ragged (count_b rows per sequence) and may be paged with the layer's own block table
 // (appendix "PyramidKV Implementation at vLLM").
 //
-// Work split: (sequence, KV head) x S key ranges, one 512-thread workgroup each; the G <= 8 query heads of a KV head
-// share every key and value row.  S is chosen on the host so that a small batch still fills the chip; with S > 1
-// the workgroups leave un-normalised partial results (reference exponent, sum, weighted values) in a workspace and
-// a second small kernel merges them, with S = 1 the first kernel writes the result itself.
-//   A. logits: the G queries, padded to a 32-row tile, are the A operand of v_mfma_f32_32x32x16_bf16; every wave
-//      takes 32-key tiles, loaded from memory straight into the B-operand layout (one row per lane pair), the
-//      next tile while the current one is multiplied.  The useful rows of the product are elements 0..3 of both
-//      wave halves.  Logits go to LDS (log2 domain).
-//   B. per head: maximum and sum over the range's keys; 2^(x - max) stored in place.
-//   C. values: a lane moves 16 bytes of a value row per load (a wave: 4 rows at d = 128), eight loads in flight;
-//      every lane keeps G x 8 partial outputs, added up over the lanes that share columns and then over the
-//      waves through LDS, in a fixed order.
+// Work split: (sequence, KV head) x S key ranges, one workgroup of 4 .. 16 waves each; the G <= 8 query heads of a KV
+// head share every key and value row.  The waves of a workgroup take the 16-key tiles (32-key at d = 64) of its range
+// in turn, each on its own: K tile -> logits -> running softmax -> weighted V tile, the keys of the wave's next tile
+// requested as soon as this tile's are multiplied and its values as soon as these are added, so that a wave always
+// has loads in flight and no barrier separates the keys from the values.  One barrier at the end, when the waves'
+// (maximum, sum, weighted values) meet in LDS.  With S > 1 the ranges leave un-normalised partial results in a
+// workspace and a second small kernel merges them, with S = 1 the first kernel writes the result itself.
+//   logits  the G queries are rows 0 .. G-1 of the A operand of v_mfma_f32_16x16x32_bf16 (16-row tile, the other rows
+//           zero; queries straight from memory into operand layout), 16 keys its columns, loaded straight into the
+//           B-operand layout (16 rows x 64 bytes per load).  Lane (column l16, quad) ends with the logits of heads
+//           4 quad .. 4 quad + 3 for key l16.
+//   softmax a reference exponent per head and wave, moved to the exact maximum (and the sums rescaled) only when a
+//           logit exceeds it by a factor 2^16: a wave-uniform branch, taken on the first tile and rarely afterwards.
+//   values  a lane moves 16 bytes of a value row per load (a wave: 4 rows at d = 128), its weights come from a
+//           wave-private LDS tile; every lane keeps GP x 8 partial outputs (GP = G rounded up to 1, 2, 4, 8).  From
+//           GP = 4 on they are formed by v_mfma_f32_4x4x1_16b_f32 (fp32 products and sums): four neighbouring lanes
+//           share a row, so one instruction adds weight x value for four heads (8 clk in the matrix pipe, against four
+//           multiply-adds at 4 clk each in the vector pipe, which has the unpacking to do).
 // HBM-bound: every kept K and V row is read once (2 x count x d x 2 bytes per head), the rest stays on chip.
+#include <type_traits>
+
 #include "pkv_internal.h"
 
 namespace pkv {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kThreads = 512;
-constexpr int kWaves = kThreads / 64;
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
 
 constexpr int kMaxSplits = 16;     // key ranges per (sequence, KV head), at most
+// Waves of a workgroup, at most (always 4, 8 or 16): the outputs of eight heads need more than 128 registers.
+constexpr int max_waves(int gp) { return gp > 4 ? 8 : 16; }
 constexpr int kTabEntries = 1026;  // block-table entries of a key range kept in LDS (pages of 4 slots or more)
 
-// Row j of (sequence b, head g) of a cache, or null if its page number is out of range.  tab: the block-table
-// entries from page index q0 on (LDS), or null: read from the table in memory.
-template <int D>
-__device__ __forceinline__ const uint16_t* cache_row(const DecodeArgs& a, const uint16_t* base, int b, int g, int j,
-                                                     const int* tab, int q0) {
-  if (a.page_size > 0) {
-    const int q = j / a.page_size, slot = j - q * a.page_size;
-    const int pg = tab ? tab[q - q0] : a.table[(size_t)b * a.max_pages + q];
-    if ((uint32_t)pg >= (uint32_t)a.num_pages) return nullptr;
-    return base + (((size_t)pg * a.Hkv + g) * a.page_size + slot) * D;
-  }
-  return base + (size_t)b * a.c_sb + (size_t)g * a.c_sh + (size_t)j * a.c_st;
+// LDS traffic of one wave to its own region needs ordering only inside the wave.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// The value of the lane N places further round in the row of 16 lanes.
+template <int N>
+__device__ __forceinline__ float row_ror(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, row_ror<8>(x));
+  x = fmaxf(x, row_ror<4>(x));
+  x = fmaxf(x, row_ror<2>(x));
+  return fmaxf(x, row_ror<1>(x));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  return x + row_ror<1>(x);
+}
+__device__ __forceinline__ float read_lane(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+// Sum of x over the wave's halves in the lower half, of y in the upper half (and the same over neighbouring rows of 16).
+__device__ __forceinline__ float fold32(float x, float y) {
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false));
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float x, float y) {
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false));
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Key range sp of (sequence b, KV head g) of one layer's cache.
-// FINAL: S == 1, the result is written here; else partial results go to the workspace.
-template <int D, bool FINAL>
+template <int D, int GP, bool PAGED>
 __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g, int b, float* dsm) {
-  constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;
-  // dsm: [8][chunk] logits / weights | [32 * PITCH] Q tile (16-byte slots) | [4][8][D] partial outputs | [8][2]
-  // (max, sum) | [kTabEntries] block-table entries of this key range
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int cnt = a.count[b];
-  cnt = cnt < 0 ? 0 : (cnt > a.k_cap ? a.k_cap : cnt);
+  constexpr int KS = D / 32;             // matrix k-steps per dot product
+  constexpr int NG = D == 128 ? 1 : 2;   // groups of 16 keys per tile (4 KB of keys and of values either way)
+  constexpr int TK = 16 * NG;            // keys per tile
+  constexpr int LPR = D / 8;             // lanes per value row
+  constexpr int RPL = 64 / LPR;          // value rows per load of a wave
+  constexpr int NV = TK / RPL;           // value loads per tile
+  constexpr int QH = GP > 4 ? 2 : 1;     // quads that hold logits of real heads
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  const int l16 = lane & 15, quad = lane >> 4;
+  const int sub = lane / LPR, col = lane - sub * LPR;
+  // dsm: [nw][GP][D] outputs of the waves (before that, each wave's region holds its tile's weights) | [nw][GP][2]
+  // (max, sum) | [kTabEntries] block-table entries of this range
+  float* s_o = dsm + (size_t)wave * GP * D;
+  float* s_mz = dsm + (size_t)nw * GP * D;
+  int* s_tab = reinterpret_cast<int*>(s_mz + nw * GP * 2);
+  const int cnt_raw = a.count[b];
   const int j_lo = sp * a.chunk;
-  const int nloc = max(min(cnt - j_lo, a.chunk), 0);  // keys of this workgroup: j_lo .. j_lo + nloc - 1
-  float* s_p = dsm;
-  u32x4* s_q = reinterpret_cast<u32x4*>(dsm + 8 * a.chunk);
-  float* s_o = reinterpret_cast<float*>(s_q + 32 * PITCH);
-  float* s_mz = s_o + 4 * 8 * D;
-  int* s_tab = reinterpret_cast<int*>(s_mz + 16);
-  const size_t unit = (size_t)b * a.Hkv + g;
-  float* out = a.out + ((size_t)b * a.Hq + (size_t)g * a.G) * D;
-  float* part_o = a.part_o + (unit * a.S + sp) * 8 * D;
-  float* part_mz = a.part_mz + (unit * a.S + sp) * 16;
-  if (nloc == 0) {  // nothing here: a neutral partial result, or (FINAL) zero rows and lse = -inf
-    if (FINAL) {
-      for (int e = tid; e < a.G * D; e += kThreads) out[e] = 0.f;
-      if (a.lse && tid < a.G) a.lse[(size_t)b * a.Hq + g * a.G + tid] = -INFINITY;
-    } else {
-      for (int e = tid; e < a.G * D; e += kThreads) part_o[e] = 0.f;
-      if (tid < a.G) {
-        part_mz[2 * tid] = -INFINITY;
-        part_mz[2 * tid + 1] = 0.f;
-      }
-    }
-    return;
-  }
-  // paged cache: this range's block-table entries once into LDS, so that a row's address costs one memory access
-  const int* tab = nullptr;
+  const int nmax = min(a.k_cap - j_lo, a.chunk);  // rows the range can hold (<= 0: an empty last range)
+
+  const uint16_t* Kb = a.K;
+  const uint16_t* Vb = a.V;
   int q0 = 0;
-  if (a.page_size >= 4) {  // (at most chunk / 4 + 2 entries then)
-    q0 = j_lo / a.page_size;
-    const int n_ent = (j_lo + nloc - 1) / a.page_size - q0 + 1;
-    for (int e = tid; e < n_ent; e += kThreads) s_tab[e] = a.table[(size_t)b * a.max_pages + q0 + e];
-    tab = s_tab;
+  if constexpr (PAGED) {
+    Kb += (size_t)g * a.page_size * D;
+    Vb += (size_t)g * a.page_size * D;
+    // this range's block-table entries once into LDS, so that a row's address costs one memory access
+    if (a.page_size >= 4 && nmax > 0) {  // (at most chunk / 4 + 2 entries then)
+      q0 = j_lo / a.page_size;
+      const int n_ent = (j_lo + nmax - 1) / a.page_size - q0 + 1;
+      for (int e = tid; e < n_ent; e += blockDim.x) s_tab[e] = a.table[(size_t)b * a.max_pages + q0 + e];
+      __syncthreads();
+    }
+  } else {
+    Kb += (size_t)b * a.c_sb + (size_t)g * a.c_sh + (size_t)j_lo * a.c_st;
+    Vb += (size_t)b * a.c_sb + (size_t)g * a.c_sh + (size_t)j_lo * a.c_st;
   }
-  // ---- Q tile: rows 0..G-1 the group's queries, the rest zero ----
-  for (int e = tid; e < 32 * SEG; e += kThreads) {
-    const int r = e / SEG, seg = e - r * SEG;
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (r < a.G) v = *reinterpret_cast<const u32x4*>(a.q + ((size_t)b * a.Hq + (size_t)g * a.G + r) * D + seg * 8);
-    s_q[r * PITCH + seg] = v;
+  // Address of local row j (0 <= j < nmax) of Kb / Vb; paged: ok = its page number is in range (else the address is
+  // that of some readable row)
+  const uint64_t row_bytes = (uint64_t)a.c_st * 2u;
+  auto row_ptr = [&](const uint16_t* base, int j, bool& ok) -> const char* {
+    uint64_t off;
+    if constexpr (PAGED) {
+      j += j_lo;
+      const int q = a.page_shift >= 0 ? j >> a.page_shift : (int)__umulhi((uint32_t)j, a.page_magic);
+      const int slot = j - q * a.page_size;
+      int pg = a.page_size >= 4 ? s_tab[q - q0] : a.table[(size_t)b * a.max_pages + q];
+      ok = (uint32_t)pg < (uint32_t)a.num_pages;
+      pg = ok ? pg : 0;
+      off = (uint64_t)(uint32_t)pg * ((uint64_t)a.Hkv * a.page_size * (2 * D)) + (uint32_t)(slot * (2 * D));
+    } else {
+      ok = true;
+      off = (uint32_t)j * row_bytes;
+    }
+    return reinterpret_cast<const char*>(base) + off;
+  };
+  bf16x8 kf[NG][KS];
+  u32x4 vv[NV];
+  bool kok[NG], vok[NV];
+  // Keys / values of the wave's tile t; rows at or beyond lim are replaced by row lim - 1.  (The compiler may not move
+  // loads across the empty statement behind each: it would sink them to their use in the next iteration, and nothing
+  // would be in flight meanwhile.)
+  auto load_k = [&](int t, int lim) {
+#pragma unroll
+    for (int gr = 0; gr < NG; ++gr) {
+      const char* p = row_ptr(Kb, min(t * TK + 16 * gr + l16, lim - 1), kok[gr]) + 16 * quad;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[gr][ks] = as_frag(*reinterpret_cast<const u32x4*>(p + 64 * ks));
+    }
+    asm volatile("" ::: "memory");
+  };
+  auto load_v = [&](int t, int lim) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      vv[i] = *reinterpret_cast<const u32x4*>(row_ptr(Vb, min(t * TK + RPL * i + sub, lim - 1), vok[i]) + 16 * col);
+    asm volatile("" ::: "memory");
+  };
+
+  // m: reference exponent of each head (not necessarily the maximum so far, at most 2^kSlack below it), z: sum of
+  // this lane's weights.  Outputs of column 8 col + c: oc[c] over four (eight) heads, or of[h][c].
+  constexpr int NH = GP < 4 ? GP : 4;    // heads per quad
+  constexpr bool MF = GP >= 4;           // values by matrix instructions
+  constexpr float kSlack = 16.f;
+  float m[NH], z[NH], of[MF ? 1 : GP][8];
+  f32x4 oc[MF ? QH : 1][8];
+#pragma unroll
+  for (int v = 0; v < NH; ++v) {
+    m[v] = -INFINITY;
+    z[v] = 0.f;
   }
-  __syncthreads();
-  // ---- A. logits ----
-  const int l32 = lane & 31, hf = lane >> 5;
-  const int ntiles = (nloc + 31) / 32;
-  if (wave < ntiles) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+#pragma unroll
+    for (int q = 0; q < (MF ? QH : 1); ++q) oc[q][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int h = 0; h < (MF ? 1 : GP); ++h) of[h][c] = 0.f;
+  }
+
+  if (wave * TK < nmax) {
     bf16x8 qf[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = as_frag(s_q[l32 * PITCH + 2 * ks + hf]);
-    // fragments of local key tile t (keys at or beyond the range's end: its last row, masked below)
-    auto load_tile = [&](int t, bf16x8 (&kf)[KS], bool& ok) {
-      const int key = t * 32 + l32;
-      const uint16_t* row = cache_row<D>(a, a.K, b, g, j_lo + min(key, nloc - 1), tab, q0);
-      ok = key < nloc && row != nullptr;
-      if (row == nullptr) row = a.K;  // a bad page number: some readable row, masked
-      const char* rp = reinterpret_cast<const char*>(row) + 16 * hf;
+    for (int ks = 0; ks < KS; ++ks) {
+      u32x4 w = u32x4{0u, 0u, 0u, 0u};
+      if (l16 < a.G)
+        w = *reinterpret_cast<const u32x4*>(a.q + ((size_t)b * a.Hq + (size_t)g * a.G + l16) * D + 32 * ks + 8 * quad);
+      qf[ks] = as_frag(w);
+    }
+    // The first tile is requested before the count has arrived: every row below k_cap is readable, and what lies
+    // beyond the count is masked below.
+    load_k(wave, nmax);
+    load_v(wave, nmax);
+    const int cnt = min(max(cnt_raw, 0), a.k_cap);
+    const int nloc = min(max(cnt - j_lo, 0), a.chunk);
+    for (int t = wave; t * TK < nloc; t += nw) {
+      const bool partial = PAGED || (t + 1) * TK > nloc;  // rows to mask (beyond the count, or of a bad page)
+      f32x4 acc[NG];
+      bool have[NG];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kf[ks] = as_frag(*reinterpret_cast<const u32x4*>(rp + 32 * ks));
-    };
-    bf16x8 kf[KS], kn[KS];
-    bool ok = false, okn = false;
-    load_tile(wave, kf, ok);
-    for (int t = wave; t < ntiles; t += kWaves) {
-      const bool more = t + kWaves < ntiles;
-      if (more) load_tile(t + kWaves, kn, okn);
-      f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int gr = 0; gr < NG; ++gr) {
+        acc[gr] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[ks], kf[ks], acc, 0, 0, 0);
-      // element v (0..3) of this lane: query row v + 4 * hf, local key t * 32 + l32
-#pragma unroll
-      for (int v = 0; v < 4; ++v) s_p[(v + 4 * hf) * a.chunk + t * 32 + l32] = ok ? acc[v] * a.scale_log2 : -INFINITY;
-      if (more) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kf[ks] = kn[ks];
-        ok = okn;
+        for (int ks = 0; ks < KS; ++ks) acc[gr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks], kf[gr][ks], acc[gr], 0, 0, 0);
+        have[gr] = kok[gr] && t * TK + 16 * gr + l16 < nloc;
       }
-    }
-  }
-  __syncthreads();
-  // ---- B. per head: maximum, weights 2^(x - max) in place, their sum ----
-  for (int h = wave; h < a.G; h += kWaves) {
-    float* p = s_p + h * a.chunk;
-    float m = -INFINITY;
-    for (int j = lane; j < nloc; j += 64) m = fmaxf(m, p[j]);
+      // (behind the wave's last tile this fetches one row once more: under a condition the waits below would have to
+      // allow for either way in, and would wait for these keys as well)
+      load_k(t + nw, nloc);
+      // exponents relative to the heads' references; a reference is moved to the exact maximum only when some logit
+      // exceeds it by more than 2^kSlack (always on the first tile): weights stay far inside fp32's range
+      float y[NG][NH];
+      auto exponents = [&]() {
+        bool over = false;
 #pragma unroll
-    for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
-    const float ms = (m == -INFINITY) ? 0.f : m;  // every page number bad: all rows masked
-    float z = 0.f;
-    for (int j = lane; j < nloc; j += 64) {
-      const float e = __builtin_amdgcn_exp2f(p[j] - ms);
-      p[j] = e;
-      z += e;
-    }
+        for (int gr = 0; gr < NG; ++gr)
 #pragma unroll
-    for (int s = 32; s > 0; s >>= 1) z += __shfl_xor(z, s);
-    if (lane == 0) {
-      s_mz[2 * h] = m;
-      s_mz[2 * h + 1] = z;
-    }
-  }
-  __syncthreads();
-  // ---- C. values: o[h][c] = sum_j w[h][j] V[j][c] ----
-  // A lane moves 16 bytes (8 columns) of a value row per load, so a wave covers RPW rows per load and has UN of
-  // those in flight; every lane keeps G x 8 partial outputs for its columns and its share of the rows.
-  constexpr int LPR = D / 8;     // lanes per row
-  constexpr int RPW = 64 / LPR;  // rows per wave and load
-  constexpr int UN = 8;
-  const int sub = lane / LPR, col = lane - sub * LPR;
-  float o[8][8];
+          for (int v = 0; v < NH; ++v) {
+            y[gr][v] = __builtin_fmaf(acc[gr][v], a.scale_log2, -m[v]);
+            if (partial && !have[gr]) y[gr][v] = -INFINITY;
+            over = over || y[gr][v] > kSlack;
+          }
+        return over;
+      };
+      if (__any(exponents() && quad < QH)) {
+        float f[NH];
 #pragma unroll
-  for (int h = 0; h < 8; ++h)
+        for (int v = 0; v < NH; ++v) {
+          float tm = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) o[h][c] = 0.f;
-  for (int r0 = wave * RPW; r0 < nloc; r0 += UN * kWaves * RPW) {
-    u32x4 w[UN];
-    int rr[UN];
+          for (int gr = 0; gr < NG; ++gr) tm = fmaxf(tm, have[gr] ? acc[gr][v] * a.scale_log2 : -INFINITY);
+          const float mn = fmaxf(m[v], row_max(tm));
+          f[v] = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m[v] - mn);
+          z[v] *= f[v];
+          m[v] = mn;
+        }
 #pragma unroll
-    for (int i = 0; i < UN; ++i) {
-      const int r = r0 + i * kWaves * RPW + sub;
-      rr[i] = r < nloc ? r : -1;
-      const uint16_t* row = cache_row<D>(a, a.V, b, g, j_lo + min(r, nloc - 1), tab, q0);
-      if (row == nullptr) {  // a bad page number: the row counts as absent (its weight is zero as well)
-        row = a.V;
-        rr[i] = -1;
+        for (int c = 0; c < 8; ++c) {
+          if constexpr (MF) {
+#pragma unroll
+            for (int h = 0; h < GP; ++h) oc[h >> 2][c][h & 3] *= read_lane(f[h & 3], 16 * (h >> 2));
+          } else {
+#pragma unroll
+            for (int h = 0; h < GP; ++h) of[h][c] *= read_lane(f[h], 0);
+          }
+        }
+        (void)exponents();
       }
-      w[i] = *reinterpret_cast<const u32x4*>(row + 8 * col);
-    }
 #pragma unroll
-    for (int i = 0; i < UN; ++i) {
-      const bool have = rr[i] >= 0;
-      if (!have) w[i] = u32x4{0u, 0u, 0u, 0u};  // whatever was read there must not reach the sums
-      float v[8];
+      for (int gr = 0; gr < NG; ++gr) {
+        float p[NH];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        v[2 * c] = __uint_as_float(w[i][c] << 16);
-        v[2 * c + 1] = __uint_as_float(w[i][c] & 0xFFFF0000u);
-      }
-      const int rc = have ? rr[i] : 0;
-#pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        if (h < a.G) {
-          const float p = have ? s_p[h * a.chunk + rc] : 0.f;
-#pragma unroll
-          for (int c = 0; c < 8; ++c) o[h][c] = __builtin_fmaf(p, v[c], o[h][c]);
+        for (int v = 0; v < NH; ++v) {
+          p[v] = __builtin_amdgcn_exp2f(y[gr][v]);
+          z[v] += p[v];
+        }
+        if (quad < QH) {
+          float* dst = s_o + (16 * gr + l16) * GP + 4 * quad;
+          if constexpr (GP >= 4) *reinterpret_cast<f32x4*>(dst) = f32x4{p[0], p[1], p[2], p[3]};
+          else if constexpr (GP == 2) *reinterpret_cast<f32x2*>(dst) = f32x2{p[0], p[1]};
+          else *dst = p[0];
         }
       }
-    }
-  }
-  // over the RPW row shares of a wave (lanes LPR apart hold the same columns), in a fixed order
+      wave_lds_fence();
+      // rows beyond the count or of a bad page: their weights are zero, but what was read must not reach the sums
+      if (partial) {
 #pragma unroll
-  for (int h = 0; h < 8; ++h) {
-    if (h < a.G) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-#pragma unroll
-        for (int sft = 32; sft >= LPR; sft >>= 1) o[h][c] += __shfl_xor(o[h][c], sft);
+        for (int i = 0; i < NV; ++i)
+          if (!(vok[i] && t * TK + RPL * i + sub < nloc)) vv[i] = u32x4{0u, 0u, 0u, 0u};
       }
-    }
-  }
-  // over the waves: waves 0..3 store, then waves 4..7 add to slot (wave & 3)
-  for (int r = 0; r < kWaves / 4; ++r) {
-    if ((wave >> 2) == r && sub == 0) {
 #pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        if (h < a.G) {
+      for (int i = 0; i < NV; ++i) {
+        const float* src = s_o + (RPL * i + sub) * GP;
+        float pw[MF ? QH : GP];
+        if constexpr (MF) {
+          // one v_mfma_f32_4x4x1: four lanes of a row are a block, column block entry = the lane's value, row = head
 #pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            float* dst = &s_o[((wave & 3) * 8 + h) * D + 8 * col + c];
-            *dst = (r == 0 ? 0.f : *dst) + o[h][c];
+          for (int q = 0; q < QH; ++q) pw[q] = src[4 * q + (lane & 3)];
+        } else {
+#pragma unroll
+          for (int h = 0; h < GP; ++h) pw[h] = src[h];
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const uint32_t w = vv[i][c >> 1];
+          const float x = __uint_as_float((c & 1) ? w & 0xFFFF0000u : w << 16);
+          if constexpr (MF) {
+#pragma unroll
+            for (int q = 0; q < QH; ++q) oc[q][c] = __builtin_amdgcn_mfma_f32_4x4x1f32(pw[q], x, oc[q][c], 0, 0, 0);
+          } else {
+#pragma unroll
+            for (int h = 0; h < GP; ++h) of[h][c] = __builtin_fmaf(pw[h], x, of[h][c]);
           }
         }
       }
+      // (the sums are complete here: without this they move behind the requests below, whose registers then cannot be
+      // the ones just read)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        if constexpr (MF) {
+#pragma unroll
+          for (int q = 0; q < QH; ++q) asm volatile("" : "+v"(oc[q][c]));
+        } else {
+#pragma unroll
+          for (int h = 0; h < GP; ++h) asm volatile("" : "+v"(of[h][c]));
+        }
+      }
+      wave_lds_fence();
+      load_v(t + nw, nloc);
     }
-    __syncthreads();
   }
-  for (int e = tid; e < a.G * D; e += kThreads) {
-    const int h = e / D, c = e - h * D;
-    const float x = s_o[(0 * 8 + h) * D + c] + s_o[(1 * 8 + h) * D + c] + s_o[(2 * 8 + h) * D + c] + s_o[(3 * 8 + h) * D + c];
-    if (FINAL) {
-      const float z = s_mz[2 * h + 1];
-      out[e] = z > 0.f ? x / z : 0.f;
-    } else {
-      part_o[e] = x;
+  auto o = [&](int h, int c) -> float {
+    if constexpr (MF) return oc[h >> 2][c][h & 3];
+    else return of[h][c];
+  };
+
+  // ---- the wave's result to LDS: outputs summed over the lanes that share columns (each lane keeps its share of the
+  // heads as the sum proceeds), maxima and sums per head ----
+#pragma unroll
+  for (int v = 0; v < NH; ++v) {
+    z[v] = row_sum(z[v]);
+    if (l16 == 0 && quad < QH) {
+      s_mz[(wave * GP + 4 * quad + v) * 2] = m[v];
+      s_mz[(wave * GP + 4 * quad + v) * 2 + 1] = z[v];
     }
   }
-  if (tid < a.G) {
-    const float m = s_mz[2 * tid], z = s_mz[2 * tid + 1];
-    if (FINAL) {
-      if (a.lse) a.lse[(size_t)b * a.Hq + g * a.G + tid] = z > 0.f ? (m + __builtin_amdgcn_logf(z)) * 0.69314718055994530942f : -INFINITY;
+  const int upper = lane >> 5, odd = (lane >> 4) & 1;
+  constexpr int H1 = GP >= 2 ? GP / 2 : 1, H2 = GP >= 4 ? GP / 4 : 1;
+  float r1[H1][8], r2[H2][8];
+#pragma unroll
+  for (int h = 0; h < H1; ++h)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) r1[h][c] = GP >= 2 ? fold32(o(h, c), o((h + H1) % GP, c)) : fold32(o(0, c), o(0, c));
+#pragma unroll
+  for (int h = 0; h < H2; ++h)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      r2[h][c] = GP >= 4 ? fold16(r1[h][c], r1[(h + H2) % H1][c]) : fold16(r1[0][c], r1[0][c]);
+      if (D == 64) r2[h][c] += row_ror<8>(r2[h][c]);
+    }
+  const int h0 = (GP >= 2 ? upper * H1 : 0) + (GP >= 4 ? odd * H2 : 0);
+  const bool writes = (GP >= 2 || upper == 0) && (GP >= 4 || odd == 0) && (D == 128 || (lane & 8) == 0);
+  if (writes) {
+#pragma unroll
+    for (int h = 0; h < H2; ++h) {
+      float* dst = s_o + (h0 + h) * D + 8 * col;
+      *reinterpret_cast<f32x4*>(dst) = f32x4{r2[h][0], r2[h][1], r2[h][2], r2[h][3]};
+      *reinterpret_cast<f32x4*>(dst + 4) = f32x4{r2[h][4], r2[h][5], r2[h][6], r2[h][7]};
+    }
+  }
+  __syncthreads();
+  // ---- the waves' results meet, in wave order ----
+  const size_t unit = (size_t)b * a.Hkv + g;
+  for (int e = tid; e < a.G * D; e += blockDim.x) {
+    const int h = e / D;
+    float M = -INFINITY;
+    for (int w0 = 0; w0 < nw; w0 += 4)  // (nw is a multiple of 4)
+#pragma unroll
+      for (int w = w0; w < w0 + 4; ++w) M = fmaxf(M, s_mz[(w * GP + h) * 2]);
+    const float Ms = (M == -INFINITY) ? 0.f : M;  // nothing here: an empty range, or every page number bad
+    float zz = 0.f, xx = 0.f;
+    for (int w0 = 0; w0 < nw; w0 += 4)
+#pragma unroll
+      for (int w = w0; w < w0 + 4; ++w) {
+        const float f = __builtin_amdgcn_exp2f(s_mz[(w * GP + h) * 2] - Ms);
+        zz += f * s_mz[(w * GP + h) * 2 + 1];
+        xx += f * dsm[(size_t)w * GP * D + e];
+      }
+    const bool first = e == h * D;
+    if (a.S == 1) {
+      a.out[((size_t)b * a.Hq + (size_t)g * a.G) * D + e] = zz > 0.f ? xx / zz : 0.f;
+      if (first && a.lse)
+        a.lse[(size_t)b * a.Hq + g * a.G + h] = zz > 0.f ? (M + __builtin_amdgcn_logf(zz)) * 0.69314718055994530942f : -INFINITY;
     } else {
-      part_mz[2 * tid] = m;
-      part_mz[2 * tid + 1] = z;
+      a.part_o[(unit * a.S + sp) * 8 * D + e] = xx;
+      if (first) {
+        a.part_mz[(unit * a.S + sp) * 16 + 2 * h] = M;
+        a.part_mz[(unit * a.S + sp) * 16 + 2 * h + 1] = zz;
+      }
     }
   }
 }
 
-template <int D, bool FINAL>
-__global__ __launch_bounds__(kThreads) void decode_partial_kernel(const DecodeArgs a) {
+template <int D, int GP, bool PAGED>
+__global__ __launch_bounds__(64 * max_waves(GP)) void decode_partial_kernel(const DecodeArgs a) {
   extern __shared__ float dsm[];
-  decode_range<D, FINAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, dsm);
+  decode_range<D, GP, PAGED>(a, blockIdx.x, blockIdx.y, blockIdx.z, dsm);
 }
 
 // Merge of the S partial results of a (sequence, KV head): common reference exponent, sums, weighted values.
@@ -311,14 +442,15 @@ __device__ __forceinline__ DecodeArgs layer_args(const DecodeBatchArgs& a, int l
   d.part_mz = a.part_mz + (size_t)ly.part0 * 16;
   d.B = a.B; d.Hq = a.Hq; d.Hkv = a.Hkv; d.G = a.G; d.d = a.d; d.k_cap = ly.k_cap;
   d.page_size = a.page_size; d.num_pages = ly.num_pages; d.max_pages = ly.max_pages;
+  d.page_shift = a.page_shift; d.page_magic = a.page_magic;
   d.S = ly.S; d.chunk = ly.chunk;
   d.c_sb = ly.c_sb; d.c_sh = ly.c_sh; d.c_st = ly.c_st;
   d.scale_log2 = a.scale_log2;
   return d;
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) void decode_partial_layers_kernel(const DecodeBatchArgs a) {
+template <int D, int GP, bool PAGED>
+__global__ __launch_bounds__(64 * max_waves(GP)) void decode_partial_layers_kernel(const DecodeBatchArgs a) {
   extern __shared__ float dsm[];
   const int w = blockIdx.x;
   int l = 0;
@@ -327,8 +459,7 @@ __global__ __launch_bounds__(kThreads) void decode_partial_layers_kernel(const D
   const int rel = w - a.layer[l].wg0;          // [b][g][sp]
   const int sp = rel % d.S, bg = rel / d.S;
   const int g = bg % a.Hkv, b = bg / a.Hkv;
-  if (d.S == 1) decode_range<D, true>(d, sp, g, b, dsm);
-  else decode_range<D, false>(d, sp, g, b, dsm);
+  decode_range<D, GP, PAGED>(d, sp, g, b, dsm);
 }
 
 template <int D>
@@ -339,60 +470,59 @@ __global__ __launch_bounds__(256) void decode_merge_layers_kernel(const DecodeBa
   decode_merge<D>(d, blockIdx.x, blockIdx.y);
 }
 
-size_t lds_bytes(int d, int chunk) {
-  return (size_t)8 * chunk * sizeof(float) + (size_t)32 * (d / 8 + 1) * 16 + (size_t)4 * 8 * d * sizeof(float) + 64 +
-         kTabEntries * sizeof(int);
-}
-
-template <int D>
-hipError_t launch(const DecodeArgs& a, hipStream_t s) {
-  const size_t lds = lds_bytes(D, a.chunk);
-  static size_t granted_all[kMaxDevices][2];  // per device: the limit set so far for each of the two kernels
+// Raises a kernel's dynamic LDS limit to what any launch of it can need, once per device (no allocation).
+hipError_t grant_lds(const void* f, bool* granted, size_t lds_max) {
   const int dev = current_device_slot();
   if (dev < 0) return hipErrorInvalidDevice;
-  size_t* granted = granted_all[dev];
-  const int fin = a.S == 1 ? 1 : 0;
-  if (lds > granted[fin]) {  // raise the dynamic LDS limit when a larger cache comes along (no allocation)
-    const void* f = fin ? reinterpret_cast<const void*>(decode_partial_kernel<D, true>)
-                        : reinterpret_cast<const void*>(decode_partial_kernel<D, false>);
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    granted[fin] = lds;
-  }
-  const dim3 grid(a.S, a.Hkv, a.B);
-  if (fin) {
-    hipLaunchKernelGGL((decode_partial_kernel<D, true>), grid, dim3(kThreads), lds, s, a);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((decode_partial_kernel<D, false>), grid, dim3(kThreads), lds, s, a);
-  hipError_t e = hipGetLastError();
+  if (granted[dev]) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+  if (e == hipSuccess) granted[dev] = true;
+  return e;
+}
+constexpr size_t lds_bytes(int d, int gp, int nw, bool paged) {
+  return (size_t)nw * gp * (d + 2) * sizeof(float) + (paged ? kTabEntries * sizeof(int) : 0);
+}
+
+template <int D, int GP, bool PAGED>
+hipError_t launch_partial(const DecodeArgs& a, int nw, hipStream_t s) {
+  static bool granted[kMaxDevices];
+  const hipError_t e = grant_lds(reinterpret_cast<const void*>(decode_partial_kernel<D, GP, PAGED>), granted,
+                                 lds_bytes(D, GP, max_waves(GP), PAGED));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(decode_merge_kernel<D>, dim3(a.Hkv, a.B), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((decode_partial_kernel<D, GP, PAGED>), dim3(a.S, a.Hkv, a.B), dim3(64 * nw),
+                     lds_bytes(D, GP, nw, PAGED), s, a);
   return hipGetLastError();
 }
 
-template <int D>
-hipError_t launch_layers(const DecodeBatchArgs& a, int total_wgs, int max_chunk, bool any_split, hipStream_t s) {
-  const size_t lds = lds_bytes(D, max_chunk);
-  static size_t granted_all[kMaxDevices];
-  const int dev = current_device_slot();
-  if (dev < 0) return hipErrorInvalidDevice;
-  if (lds > granted_all[dev]) {  // raise the dynamic LDS limit when a larger range comes along (no allocation)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_layers_kernel<D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    granted_all[dev] = lds;
-  }
-  hipLaunchKernelGGL(decode_partial_layers_kernel<D>, dim3(total_wgs), dim3(kThreads), lds, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !any_split) return e;
-  hipLaunchKernelGGL(decode_merge_layers_kernel<D>, dim3(a.Hkv, a.B, a.L), dim3(256), 0, s, a);
+template <int D, int GP, bool PAGED>
+hipError_t launch_partial_layers(const DecodeBatchArgs& a, int total_wgs, int nw, hipStream_t s) {
+  static bool granted[kMaxDevices];
+  const hipError_t e = grant_lds(reinterpret_cast<const void*>(decode_partial_layers_kernel<D, GP, PAGED>), granted,
+                                 lds_bytes(D, GP, max_waves(GP), PAGED));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((decode_partial_layers_kernel<D, GP, PAGED>), dim3(total_wgs), dim3(64 * nw),
+                     lds_bytes(D, GP, nw, PAGED), s, a);
   return hipGetLastError();
+}
+
+// Calls fn with (head dimension, padded group size, paged) as compile-time constants.
+template <class Fn>
+hipError_t with_variant(int d, int G, bool paged, Fn fn) {
+  auto by_page = [&](auto D, auto GP) { return paged ? fn(D, GP, std::true_type{}) : fn(D, GP, std::false_type{}); };
+  auto by_group = [&](auto D) {
+    if (G == 1) return by_page(D, std::integral_constant<int, 1>{});
+    if (G == 2) return by_page(D, std::integral_constant<int, 2>{});
+    if (G <= 4) return by_page(D, std::integral_constant<int, 4>{});
+    return by_page(D, std::integral_constant<int, 8>{});
+  };
+  if (d == 128) return by_group(std::integral_constant<int, 128>{});
+  if (d == 64) return by_group(std::integral_constant<int, 64>{});
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// Key ranges per (sequence, KV head): enough workgroups to fill the chip, at least 128 keys each.
+// Key ranges per (sequence, KV head) that the workspace has room for.
 int decode_splits(int B, int Hkv, int k_cap) {
   int S = (512 + B * Hkv - 1) / (B * Hkv);
   if (S > kMaxSplits) S = kMaxSplits;
@@ -401,10 +531,31 @@ int decode_splits(int B, int Hkv, int k_cap) {
   return S < 1 ? 1 : S;
 }
 
-// All layers in one launch: keys per range so that the layers together give about 512 workgroups, between 256 and
-// 1024 keys (multiple of 32); a layer's cache is cut into at most 16 ranges of that size.  (Measured on caches of
-// 0.02 to 2 GB per step: 256 to 1024 workgroups are equally fast, more are slower (the merge grows); caches that fit
-// one range per head skip the merge launch, which is a third of the time of a small step.)
+// Key ranges actually used.  One compute unit fetches 57 - 59 bytes per ns from beyond its L2 however much it has in
+// flight, so the rows of a head are split over several when few heads leave the chip idle, but only where that saves
+// more than the merge launch costs (about 4 us: 990 rows of 8 heads take 15.9 us in one range each, 6 + 4 in four).
+int decode_splits_used(int B, int Hkv, int d, int k_cap) {
+  const int most = decode_splits(B, Hkv, k_cap), units = B * Hkv;
+  const int rows = d == 128 ? 256 : 512;  // per range
+  if (k_cap <= 3 * rows || units > 128) return 1;
+  int S = (k_cap + rows - 1) / rows;
+  if (S > 512 / units) S = 512 / units;
+  return S < most ? S : most;
+}
+
+// Waves per workgroup: sixteen (one workgroup per compute unit) up to 256 workgroups, four beyond 1024.  In between
+// eight, two workgroups per compute unit at a time, the next one starting where one is done (768 workgroups of 32 ..
+// 1368 rows: 60 us, with four waves, all of them resident from the start, 75 us), but four where they are short (1024
+// workgroups of 128 rows on average: 16 instead of 18 us).  Not many more than the longest range has tiles.
+int decode_waves(int64_t workgroups, int64_t rows_total, int d, int G, int chunk) {
+  int nw = workgroups <= 256 ? max_waves(G) : (workgroups <= 1024 && rows_total >= 256 * workgroups ? 8 : 4);
+  const int tiles = (chunk + (d == 128 ? 15 : 31)) / (d == 128 ? 16 : 32);
+  while (nw > 4 && nw / 2 >= tiles) nw /= 2;
+  return nw;
+}
+
+// All layers in one launch: keys per range that the workspace has room for (about 512 ranges in all, 256 to 1024
+// keys, at most 16 per head) ...
 int decode_layers_chunk(int64_t rows_total) {
   int64_t c = (rows_total + 511) / 512;
   c = c < 256 ? 256 : (c > 1024 ? 1024 : c);
@@ -416,18 +567,50 @@ int decode_layers_splits(int k_cap, int chunk_target, int* chunk) {
   *chunk = ((k_cap + S - 1) / S + 31) / 32 * 32;
   return S;
 }
+// ... and those used, never shorter than that.  With a head for every compute unit: one range per head (no partial
+// results, no merge launch: 768 heads of 32 .. 1368 rows 75 -> 60 us, 2048 heads of 133 .. 3963 rows 376 -> 355 us),
+// except for few long heads, where the longest would outlast the rest (256 heads of 133 .. 3963 rows: 63 -> 60 us).
+// With fewer heads: enough ranges for one per compute unit, of at least 256 keys.
+int decode_layers_chunk_used(int64_t units, int64_t rows_total) {
+  if (units >= 1024 || (units >= 256 && rows_total < 1536 * units)) return kDecodeMaxRows;
+  if (units >= 256) return decode_layers_chunk(rows_total);
+  int64_t c = (rows_total + 255) / 256;
+  c = c < 256 ? 256 : (c > kDecodeMaxRows ? kDecodeMaxRows : c);
+  return (int)((c + 31) / 32 * 32);
+}
 
-hipError_t launch_decode_attention_layers(const DecodeBatchArgs& a, int total_wgs, int max_chunk, bool any_split,
-                                          hipStream_t s) {
-  if (a.d == 128) return launch_layers<128>(a, total_wgs, max_chunk, any_split, s);
-  if (a.d == 64) return launch_layers<64>(a, total_wgs, max_chunk, any_split, s);
-  return hipErrorInvalidValue;
+// q = j / page_size for 0 <= j < 4096: a shift, or the high half of a product with ceil(2^32 / page_size) (exact
+// while j * page_size < 2^32; larger pages hold every row, so q = 0).
+void decode_page_division(int page_size, int32_t* shift, uint32_t* magic) {
+  *shift = -1;
+  *magic = 0;
+  if (page_size < 1) return;
+  if ((page_size & (page_size - 1)) == 0) {
+    *shift = __builtin_ctz((unsigned)page_size);
+  } else if (page_size < kDecodeMaxRows) {
+    *magic = (uint32_t)((((uint64_t)1 << 32) + page_size - 1) / page_size);
+  }
+}
+
+hipError_t launch_decode_attention_layers(const DecodeBatchArgs& a, int total_wgs, int nw, bool any_split, hipStream_t s) {
+  const hipError_t e = with_variant(a.d, a.G, a.page_size > 0, [&](auto D, auto GP, auto P) {
+    return launch_partial_layers<decltype(D)::value, decltype(GP)::value, decltype(P)::value>(a, total_wgs, nw, s);
+  });
+  if (e != hipSuccess || !any_split) return e;
+  if (a.d == 128) hipLaunchKernelGGL(decode_merge_layers_kernel<128>, dim3(a.Hkv, a.B, a.L), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(decode_merge_layers_kernel<64>, dim3(a.Hkv, a.B, a.L), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_decode_attention(const DecodeArgs& a, hipStream_t s) {
-  if (a.d == 128) return launch<128>(a, s);
-  if (a.d == 64) return launch<64>(a, s);
-  return hipErrorInvalidValue;
+  const int nw = decode_waves((int64_t)a.S * a.B * a.Hkv, (int64_t)a.B * a.Hkv * a.k_cap, a.d, a.G, a.chunk);
+  const hipError_t e = with_variant(a.d, a.G, a.page_size > 0, [&](auto D, auto GP, auto P) {
+    return launch_partial<decltype(D)::value, decltype(GP)::value, decltype(P)::value>(a, nw, s);
+  });
+  if (e != hipSuccess || a.S == 1) return e;
+  if (a.d == 128) hipLaunchKernelGGL(decode_merge_kernel<128>, dim3(a.Hkv, a.B), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(decode_merge_kernel<64>, dim3(a.Hkv, a.B), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace pkv

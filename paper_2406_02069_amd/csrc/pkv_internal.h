@@ -188,7 +188,7 @@ struct RecallArgs {
 };
 
 // ---- decoding attention over a compacted (possibly paged) cache ----
-constexpr int kDecodeMaxRows = 4096;  // kept rows per sequence the LDS probability table can hold
+constexpr int kDecodeMaxRows = 4096;  // kept rows per sequence
 struct DecodeArgs {
   const uint16_t* q;     // [B][Hq][d]
   const uint16_t* K;     // compact [B][Hkv][k_cap][d] (strides c_*) or pool [num_pages][Hkv][page_size][d]
@@ -200,11 +200,16 @@ struct DecodeArgs {
   float* part_o;         // [B][Hkv][S][8][d] un-normalised partial outputs (S > 1)
   float* part_mz;        // [B][Hkv][S][8][2] reference exponent and sum of the partial result
   int32_t B, Hq, Hkv, G, d, k_cap, page_size, num_pages, max_pages;
+  int32_t page_shift;    // log2(page_size), or -1: division by page_magic (decode_page_division)
+  uint32_t page_magic;
   int32_t S, chunk;      // key ranges per (sequence, head); keys per range (multiple of 32)
   int64_t c_sb, c_sh, c_st;
   float scale_log2;      // log2(e) / sqrt(d)
 };
 int decode_splits(int B, int Hkv, int k_cap);
+int decode_splits_used(int B, int Hkv, int d, int k_cap);
+int decode_waves(int64_t workgroups, int64_t rows_total, int d, int G, int chunk);
+void decode_page_division(int page_size, int32_t* shift, uint32_t* magic);
 hipError_t launch_decode_attention(const DecodeArgs& a, hipStream_t s);
 
 // The same over the caches of several layers in one launch (per-layer pointers and cache sizes; shape shared).
@@ -229,12 +234,14 @@ struct DecodeBatchArgs {
   float* part_o;   // [records][8][d]
   float* part_mz;  // [records][8][2]
   int32_t L, B, Hq, Hkv, G, d, page_size;
+  int32_t page_shift;
+  uint32_t page_magic;
   float scale_log2;
 };
 int decode_layers_chunk(int64_t rows_total);
+int decode_layers_chunk_used(int64_t units, int64_t rows_total);
 int decode_layers_splits(int k_cap, int chunk_target, int* chunk);
-hipError_t launch_decode_attention_layers(const DecodeBatchArgs& a, int total_wgs, int max_chunk, bool any_split,
-                                          hipStream_t s);
+hipError_t launch_decode_attention_layers(const DecodeBatchArgs& a, int total_wgs, int nw, bool any_split, hipStream_t s);
 
 // Index of the current device for per-device launch state (dynamic LDS limits are set per device), or -1.
 constexpr int kMaxDevices = 64;

@@ -1,0 +1,65 @@
+"""Decoding attention at the edges of its work split: group sizes of every padded width, row counts around the tiles of
+a wave and the ranges of a workgroup, page sizes that are no power of two, and logits that climb along the cache so that
+the running reference exponent has to be moved again and again."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_02069_amd import binding
+from tests.test_gpu_decode import DEV, _cmp, _rand
+
+pytestmark = pytest.mark.gpu
+
+
+def _climbing(q, Ks, Hq, Hkv, top):
+    """Adds to key j a share of the group's first query such that its logit climbs to about `top` at the last row."""
+    B, _, k_cap, d = Ks.shape
+    q0 = q.view(B, Hkv, Hq // Hkv, d)[:, :, 0].float()
+    step = top * np.sqrt(d) * torch.arange(k_cap, device=DEV) / max(k_cap - 1, 1)
+    return (Ks.float() + step[None, None, :, None] * (q0 / q0.square().sum(-1, keepdim=True))[:, :, None]).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,k_cap,top", [(1, 17, 0), (2, 15, 0), (3, 33, 0), (4, 16, 0), (5, 31, 0), (7, 257, 0), (8, 65, 0),
+                                          (4, 700, 90), (8, 700, 90), (1, 1025, 60), (2, 769, 60), (6, 1537, 90)])
+def test_groups_tiles_and_climbing_logits(d, G, k_cap, top):
+    B, Hkv = 2, 2
+    q, Ks, Vs = _rand(B, G * Hkv, Hkv, d, k_cap, seed=31 * G + k_cap + d)
+    if top:
+        Ks = _climbing(q, Ks, G * Hkv, Hkv, top)
+    count = np.array([k_cap, max(k_cap - 13, 1)], dtype=np.int32)
+    Ks[1, :, count[1]:] = float("nan")
+    Vs[1, :, count[1]:] = float("nan")
+    print("decode tiles", d, G, k_cap, top, flush=True)
+    out, lse = binding.decode_attention(q, Ks, Vs, torch.from_numpy(count).to(DEV), want_lse=True)
+    both = binding.decode_attention_layers([q, q], [Ks, Ks], [Vs, Vs], [torch.from_numpy(count).to(DEV)] * 2, want_lse=True)
+    torch.cuda.synchronize()
+    Kc, Vc = Ks.clone(), Vs.clone()
+    Kc[1, :, count[1]:] = 0
+    Vc[1, :, count[1]:] = 0
+    for o, s in ((out, lse), both[0], both[1]):
+        assert not torch.isnan(o).any()
+        _cmp(o, s, Kc, Vc, q, count)
+
+
+@pytest.mark.parametrize("page_size,k_cap", [(1, 40), (3, 100), (5, 333), (100, 999), (4095, 1300), (5000, 70)])
+def test_page_sizes(page_size, k_cap):
+    B, Hq, Hkv, d = 2, 8, 2, 128
+    q, Ks, Vs = _rand(B, Hq, Hkv, d, k_cap, seed=page_size)
+    per = (k_cap + page_size - 1) // page_size
+    table = torch.from_numpy(np.random.RandomState(page_size).permutation(B * per).astype(np.int32).reshape(B, per)).to(DEV)
+    pools = []
+    for x in (Ks, Vs):
+        p = torch.full((B * per, Hkv, page_size, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        for b in range(B):
+            for i in range(per):
+                rows = x[b, :, i * page_size:(i + 1) * page_size]
+                p[int(table[b, i]), :, :rows.shape[1]] = rows
+        pools.append(p)
+    count = np.array([k_cap, k_cap - 7], dtype=np.int32)
+    print("decode pages", page_size, k_cap, flush=True)
+    out, lse = binding.decode_attention(q, pools[0], pools[1], torch.from_numpy(count).to(DEV), block_table=table,
+                                        k_cap=k_cap, want_lse=True)
+    torch.cuda.synchronize()
+    assert not torch.isnan(out).any()
+    _cmp(out, lse, Ks, Vs, q, count)
