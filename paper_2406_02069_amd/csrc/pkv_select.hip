@@ -2,22 +2,28 @@
 // the k^l - alpha highest-scoring prefix tokens per head; the alpha instruction tokens are always kept).
 //
 // One 1024-thread workgroup per unit (layer x sequence x KV head); all layers of a call run in one
-// launch.
-//   A. pooled[i] = pool_w-wide max / average of the un-pooled scores, prefix only.  When the prefix fits in
-//      LDS (<= 32768 keys) all loads are issued at once, the scores are pooled out of LDS into registers
-//      (32 positions per thread, each wave owning a contiguous range of 2048 positions) and stay there; longer
-//      prefixes go through LDS in tiles of 16384 positions (all loads of a tile in flight at once) and keep their
-//      keys in the pooled array in global memory.  The
-//      fp32 bit patterns are the selection keys (scores are >= 0, so unsigned order = numeric order).
-//   B. the kk-th largest key T.  Keys in registers: binary search on T, one bit per round from the top; a
-//      round counts the keys >= the candidate (per lane, then per wave through ballots, then 16 wave counts
-//      through LDS: one barrier, no atomics).  As soon as at most 512 keys still agree with the decided
-//      bits, those keys move to a list and one wave decides the remaining bits on its own.
-//      Keys in global memory: radix select with LDS histograms, digits of up to 11 bits below the leading bits
-//      that all keys share (read off the largest and the smallest key).
-//   C. ordered emission: every wave owns a contiguous range of positions; ballots give each kept key
-//      its rank, so positions with key > T, and the lowest positions with key == T, come out in
-//      ascending order, followed by the window positions.
+// launch.  The fp32 bit patterns of the pooled scores are the selection keys (scores are >= 0, so unsigned order =
+// numeric order).
+//
+// Prefixes of up to 32768 keys (select_short): every thread holds PER keys in registers.
+//   A. pooled[i] = pool_w-wide max / average of the un-pooled scores, prefix only.  All loads are issued at once, four
+//      neighbouring positions per thread and load; the neighbours of a thread's four come out of an LDS copy.
+//   B. the kk-th largest key T.  (1) Of every group of up to PER / 4 keys of a thread the largest is counted in a
+//      histogram over the distance from a typical large key: the bin in which the count reaches kk bounds T from below (kk
+//      groups hold a key that large), with one LDS addition per group instead of one per key.  (2) The keys at or
+//      above the bound, a small multiple of kk, move to a list in LDS, in position order.  (3) A histogram of the list
+//      finds T's bin; (4) the few keys in that bin are ranked against each other.  Lists that do not fit (equal
+//      scores, a budget of nearly everything) take a plain binary search over all keys, one bit per round.
+//   C. ordered emission from the list: keys > T and the lowest positions with key == T, in ascending order, followed
+//      by the window positions.
+// What bounds it: the latency of some fifteen steps between barriers, 0.6 - 1.4 us each, beside the loads (5.8 of 19 us
+// for 256 units of 32k keys); the work over all keys (one maximum and one comparison each) is short.  Measured with the
+// copy of the kept rows, by the profiler, against a search of T over all keys one bit per round: one unit of 1k keys
+// 15.2 -> 9.0 us, 8 units of 8k 18.2 -> 11.4, 256 units of 8k 28 -> 19, of 32k 48 -> 27, 2048 units of 8k .. 16k
+// 215 -> 128 (its 0.55 GB of kept rows take 112 us at the rate of a large copy).
+// Longer prefixes (select_long) pool through LDS in tiles of 16384 positions (all loads of a tile in flight at once),
+// keep their keys in the pooled array in global memory and use a radix select with LDS histograms, digits of up to
+// 11 bits below the leading bits that all keys share (read off the largest and the smallest key).
 // All counters are integers and the emission is ordered, so the result does not depend on scheduling.
 #include <type_traits>
 
@@ -26,11 +32,16 @@
 namespace pkv {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_u __attribute__((aligned(4)));   // four floats at any 4-byte boundary
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int NT = kSelectThreads;
 constexpr int NW = NT / 64;
 constexpr int TL = 16384;          // pooling tile of long prefixes (outputs per iteration)
 constexpr int HIST = 2048;         // bins of the widest digit
-constexpr int kLdsKeys = 32768;    // prefix lengths up to this keep their keys in LDS
+constexpr int kLdsKeys = 32768;    // prefix lengths up to this keep their keys in registers
+constexpr int kPad = 32;           // neutral scores in LDS before the prefix and behind it (half a pooling window)
 
 // Workgroup barrier that orders LDS traffic only.  A full __syncthreads() carries fences over global memory too,
 // and the waits the compiler builds for them cover the global loads still in flight: a memory round trip per use,
@@ -56,14 +67,61 @@ __device__ __forceinline__ uint32_t wave_max_lane63(uint32_t v) {
   return v;
 }
 
+// Largest of a value over each row of 16 lanes, valid in its last lane.
+__device__ __forceinline__ uint32_t row_max_lane15(uint32_t v) {
+#define PKV_DPP_MAX(ctrl) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, false))
+  PKV_DPP_MAX(0x111);  // row_shr:1
+  PKV_DPP_MAX(0x112);  // row_shr:2
+  PKV_DPP_MAX(0x114);  // row_shr:4
+  PKV_DPP_MAX(0x118);  // row_shr:8
+#undef PKV_DPP_MAX
+  return v;
+}
+
+// Sum over the lanes up to and including each lane (the same row operations, additions).
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+#define PKV_DPP_ADD(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xF, false)
+  PKV_DPP_ADD(0x111, 0xF);
+  PKV_DPP_ADD(0x112, 0xF);
+  PKV_DPP_ADD(0x114, 0xF);
+  PKV_DPP_ADD(0x118, 0xF);
+  PKV_DPP_ADD(0x142, 0xA);
+  PKV_DPP_ADD(0x143, 0xC);
+#undef PKV_DPP_ADD
+  return v;
+}
+
+// A wave-uniform value the compiler must treat as new: the lane masks of comparisons with it are formed where they are
+// used instead of being kept (and spilled), 32 pairs of scalar registers, from an earlier use.
+__device__ __forceinline__ int fresh(int v) {
+  v = __builtin_amdgcn_readfirstlane(v);
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// The waves' 16 values in LDS, read one per lane: sum over the waves before `wave` (uniform), and over all of them.
+__device__ __forceinline__ uint32_t sum_before(const uint32_t* per_wave, int wave, uint32_t& total) {
+  uint32_t v = per_wave[threadIdx.x & 15];
+#define PKV_DPP_ADD(ctrl) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, false)
+  PKV_DPP_ADD(0x111);
+  PKV_DPP_ADD(0x112);
+  PKV_DPP_ADD(0x114);
+  PKV_DPP_ADD(0x118);
+#undef PKV_DPP_ADD
+  total = (uint32_t)__builtin_amdgcn_readlane((int)v, NW - 1);
+  const uint32_t incl = (uint32_t)__builtin_amdgcn_readlane((int)v, wave > 0 ? wave - 1 : 0);
+  return wave > 0 ? incl : 0u;
+}
+
+// Number of set bits of m below this lane.
+__device__ __forceinline__ uint32_t bits_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // Inclusive scan over the workgroup, thread order.  `scratch` holds NW entries.
 __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* scratch, uint32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t u = __shfl_up(v, o);
-    if (lane >= o) v += u;
-  }
+  v = wave_inclusive_sum(v);
   __syncthreads();  // scratch may still be read from a previous use
   if (lane == 63) scratch[wave] = v;
   __syncthreads();
@@ -79,12 +137,8 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* s
 }
 
 
-// PERT (prefix in LDS only): positions per thread, 1024 * PERT >= npre.  A short prefix is spread over all waves
-// (8 or 16 positions per thread) instead of filling the first few waves with 32 positions per thread and leaving
-// the others without keys: the rounds of the threshold search cost what the busiest wave needs.
-template <bool LDSKEYS, int PERT>
-__device__ __forceinline__ void select_unit(const float* raw, int nrb, size_t rb_stride, float inv_G, float* pooled,
-                                            bool write_pooled, int32_t* idx, int npre, int kk, int alpha, int pool,
+// A longer prefix.
+__device__ __forceinline__ void select_long(const float* raw, int nrb, size_t rb_stride, float inv_G, float* pooled, int32_t* idx, int npre, int kk, int alpha, int pool,
                                             int pool_w, uint32_t* lkeys, uint32_t* hist,
                                             uint32_t* scan32, uint32_t* sel) {
   const int tid = threadIdx.x;
@@ -92,23 +146,16 @@ __device__ __forceinline__ void select_unit(const float* raw, int nrb, size_t rb
   const uint32_t* gkeys = reinterpret_cast<const uint32_t*>(pooled);
 
   // ---- A. group mean + pooling ----
-  constexpr int PER = PERT;            // positions per thread when the prefix lives in LDS
-  constexpr int CW = 64 * PER;         // ... and per wave: wave w owns positions [w * CW, (w + 1) * CW)
-  uint32_t rkeys[PER];                 // pooled keys of positions wave * CW + 64 * j + lane (0: no such position)
   const int r = (pool == PKV_POOL_NONE) ? 0 : (pool_w - 1) / 2;
   const bool is_max = pool == PKV_POOL_MAX;
   const float inv_w = 1.0f / (float)pool_w;
-  const int pos0 = wave * CW + lane;   // the thread's first position; the others follow in steps of 64
-  // number of the thread's positions that exist (position pos0 + 64 * j exists iff j < nval): one register instead
-  // of 32 position registers kept alive for the comparisons
-  const int nval = min(max((npre - pos0 + 63) >> 6, 0), PER);
   uint32_t gmax = 0u, gmin = 0xFFFFFFFFu;  // long prefixes: largest and smallest key this thread has produced
   // long prefixes: largest key of every group of 64 positions, in LDS behind the pooling tile (if they fit)
   constexpr int kGrpOff = 16512, kGrpCap = kLdsKeys - kGrpOff;
   static_assert(kGrpOff >= TL + 2 * (kMaxPoolW / 2), "group maxima lie behind the tile");
   uint32_t* grp = lkeys + kGrpOff;
   const int ngrp = (npre + 63) >> 6;
-  const bool use_grp = !LDSKEYS && ngrp <= kGrpCap;
+  const bool use_grp = ngrp <= kGrpCap;
   // fn(gi) for every group gi of [g_lo, g_hi), ascending, whose largest key is at least `bound`: 64 groups are
   // tested at a time, one per lane, and the wave then walks the set bits (all arguments wave-uniform)
   auto for_groups_at_least = [&](int g_lo, int g_hi, uint32_t bound, auto fn) {
@@ -122,97 +169,7 @@ __device__ __forceinline__ void select_unit(const float* raw, int nrb, size_t rb
       }
     }
   };
-  if (LDSKEYS) {
-    // The whole prefix fits in LDS: every load of the un-pooled scores is in flight at once (one memory round
-    // trip), then each thread pools its positions out of LDS; the pooled values stay in registers, already in
-    // the order in which positions are emitted later (each wave owns a contiguous range).
-    float* lsc = reinterpret_cast<float*>(lkeys);
-    float v[PER];
-    if (nrb == 1) {
-      const float* rp = raw + pos0;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) v[j] = (j < nval) ? rp[64 * j] : 0.f;
-    } else {
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int i = pos0 + 64 * j;
-        float sacc = 0.f;
-        if (i < npre)
-          for (int q = 0; q < nrb; ++q) sacc += raw[q * rb_stride + i];
-        v[j] = sacc;
-      }
-    }
-    {
-      float* lp = lsc + pos0;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        v[j] *= inv_G;
-        if (j < nval) lp[64 * j] = v[j];
-      }
-    }
-    __syncthreads();
-    // window of half-width R around position i, summed (or maximised) in ascending position order.  A group of
-    // 64 positions whose windows lie inside the prefix reads with constant offsets and no predicates.
-    auto pool_fixed = [&](auto RR, auto MX) {
-      constexpr int R = decltype(RR)::value;
-      constexpr bool mx = decltype(MX)::value;
-      const float* lp = lsc + pos0;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int g0 = wave * CW + 64 * j;  // first position of the group (wave-uniform)
-        float acc;
-        if (g0 - R >= 0 && g0 + 63 + R < npre) {
-          acc = lp[64 * j - R];
-#pragma unroll
-          for (int u = -R + 1; u <= R; ++u) acc = mx ? fmaxf(acc, lp[64 * j + u]) : acc + lp[64 * j + u];
-          v[j] = mx ? acc : acc * inv_w;
-        } else if (g0 < npre) {
-          const int i = g0 + lane;
-          acc = mx ? -INFINITY : 0.f;
-#pragma unroll
-          for (int u = -R; u <= R; ++u) {
-            const int p = i + u;
-            const bool ok = p >= 0 && p < npre;
-            const float x = lsc[ok ? p : 0];
-            if (mx) acc = ok ? fmaxf(acc, x) : acc;
-            else acc += ok ? x : 0.f;
-          }
-          if (j < nval) v[j] = mx ? acc : acc * inv_w;
-        }
-      }
-    };
-    using std::integral_constant;
-    if (r >= 1 && r <= 3) {
-      if (is_max) {
-        if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::true_type{});
-        else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::true_type{});
-        else pool_fixed(integral_constant<int, 3>{}, std::true_type{});
-      } else {
-        if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::false_type{});
-        else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::false_type{});
-        else pool_fixed(integral_constant<int, 3>{}, std::false_type{});
-      }
-    }
-    else if (r > 3) {
-      for (int j = 0; j < PER; ++j) {
-        const int i = pos0 + 64 * j;
-        if (i < npre) {
-          const int lo = max(i - r, 0), hi = min(i + r, npre - 1);
-          float acc = is_max ? -INFINITY : 0.f;
-          for (int u = lo; u <= hi; ++u) acc = is_max ? fmaxf(acc, lsc[u]) : acc + lsc[u];
-          v[j] = is_max ? acc : acc * inv_w;
-        }
-      }
-    }
-    if (write_pooled) {
-      float* pp = pooled + pos0;
-#pragma unroll
-      for (int j = 0; j < PER; ++j)
-        if (j < nval) pp[64 * j] = v[j];
-    }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) rkeys[j] = (j < nval) ? __float_as_uint(v[j]) : 0u;
-  } else {
+  {
     // Long prefix: tiles of TL outputs go through LDS, every load of a tile in flight at once; the pooled values
     // are the keys, kept in global memory.  On the way the largest and the smallest key are noted, and the largest
     // key of every group of 64 consecutive positions (kept in LDS behind the tile): later passes skip the groups
@@ -313,115 +270,7 @@ __device__ __forceinline__ void select_unit(const float* raw, int nrb, size_t rb
     // ---- B. the kk-th largest key ----
     uint32_t prefix = 0;
     uint32_t remaining = (uint32_t)kk;
-    if (LDSKEYS) {
-      // Keys sit in registers: binary search for the largest T with count(key >= T) >= kk, one bit per round
-      // from the top.  Per round every wave counts its keys (ballots and scalar pop-counts: no LDS atomics,
-      // nothing that depends on timing) and the 16 wave counts meet in LDS: one barrier per bit.  All 32 bits are searched although scores are >= 0: whatever bit patterns the scores
-      // hold (NaN, negative zero), exactly kk positions are selected.  Positions that do not exist carry key 0
-      // and are never counted (T >= 1 in every comparison).
-      //
-      // Bookkeeping that comes for free: U = number of keys that still agree with the decided bits (the only
-      // ones whose comparison is open), G = number of keys above all of them.  Once U is at most 512
-      // the open keys are moved to a list in LDS and a single wave decides the remaining bits on its own.
-      uint32_t U = (uint32_t)npre, G = 0;
-      uint32_t* list = lkeys;  // the un-pooled scores are no longer needed
-      int bit = 31;
-      {
-        // The leading bits that all keys share (sign, the top of the exponent: scores span a few binades) are T's
-        // leading bits as well (count(key >= that prefix) = npre >= kk, and nothing lies above it): they are
-        // read off the largest and the smallest key instead of being searched, one round of counting each.
-        uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          if (j < nval) {
-            kmax = max(kmax, rkeys[j]);
-            kmin = min(kmin, rkeys[j]);
-          }
-        }
-#pragma unroll
-        for (int sft = 32; sft > 0; sft >>= 1) {
-          kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, sft));
-          kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, sft));
-        }
-        if (lane == 0) {
-          scan32[wave] = kmax;
-          scan32[NW + wave] = kmin;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          kmax = max(kmax, scan32[w]);
-          kmin = min(kmin, scan32[NW + w]);
-        }
-        __syncthreads();  // the slots are reused by the rounds below
-        const uint32_t diff = kmax ^ kmin;
-        if (diff == 0u) {  // all keys equal: T is that key
-          prefix = kmax;
-          bit = -1;
-        } else {
-          bit = 31 - __clz((int)diff);                      // the first bit in which keys differ
-          prefix = (bit == 31) ? 0u : (kmax >> (bit + 1)) << (bit + 1);
-        }
-      }
-      // rounds over all keys, until few enough are open
-      constexpr int kList = 512;  // open keys that the finishing wave can hold (8 per lane)
-      for (; bit >= 0 && U > (uint32_t)kList; --bit) {
-        const uint32_t cand = prefix | (1u << bit);
-        uint32_t wcount = 0;  // ballot + scalar pop-count per key: the scalar unit counts while the vector unit compares
-#pragma unroll
-        for (int j = 0; j < PER; ++j) wcount += __popcll(__ballot(rkeys[j] >= cand));
-        uint32_t* slot = scan32 + ((bit & 1) ? NW : 0);  // two sets of per-wave slots: one barrier per bit
-        if (lane == 0) slot[wave] = wcount;
-        __syncthreads();
-        uint32_t c = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) c += slot[w];
-        if (c >= (uint32_t)kk) {
-          prefix = cand;
-          U = c - G;
-        } else {
-          U -= c - G;
-          G = c;
-        }
-      }
-      if (bit >= 0) {
-        // the open keys (existing positions whose bits above `bit` equal the prefix's) move to a list in LDS ...
-        uint32_t my = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          const bool open = j < nval && (bit == 31 || (rkeys[j] >> (bit + 1)) == (prefix >> (bit + 1)));
-          my += open ? 1u : 0u;
-        }
-        uint32_t total;
-        uint32_t off = block_inclusive_scan(my, hist, &total) - my;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          const bool open = j < nval && (bit == 31 || (rkeys[j] >> (bit + 1)) == (prefix >> (bit + 1)));
-          if (open) list[off++] = rkeys[j];
-        }
-        __syncthreads();
-        // ... and one wave finishes the search on them alone: 8 keys per lane, no barrier between the rounds
-        if (wave == 0) {
-          constexpr int LK = kList / 64;
-          uint32_t lk[LK];
-#pragma unroll
-          for (int i = 0; i < LK; ++i) lk[i] = (uint32_t)(lane + 64 * i) < total ? list[lane + 64 * i] : 0u;
-          for (; bit >= 0; --bit) {
-            const uint32_t cand = prefix | (1u << bit);
-            uint32_t cnt = 0;
-#pragma unroll
-            for (int i = 0; i < LK; ++i) cnt += (lk[i] >= cand) ? 1u : 0u;
-            uint32_t c = G;  // keys above every key of the list
-#pragma unroll
-            for (int b = 0; b < 4; ++b) c += (uint32_t)__popcll(__ballot((cnt >> b) & 1u)) << b;  // cnt <= 8
-            if (c >= (uint32_t)kk) prefix = cand;
-          }
-          if (lane == 0) sel[0] = prefix;
-        }
-        __syncthreads();
-        prefix = sel[0];
-      }
-    } else {
+    {
       // Keys in global memory: radix select.  The leading bits that all keys share are T's as well and are read off
       // the largest and the smallest key; below them digits of up to 11 bits, most significant first, each with an
       // LDS histogram over the keys that agree with the digits decided so far.  (Starting at the first bit in which
@@ -505,54 +354,7 @@ __device__ __forceinline__ void select_unit(const float* raw, int nrb, size_t rb
     const uint32_t T = prefix;           // bit pattern of the kk-th largest pooled score
 
     // ---- C. ordered emission ----
-    if (LDSKEYS) {
-      // keys equal to T to take (lowest positions first) = kk - count(key > T); the counts per wave also give
-      // every wave the rank at which its range starts
-      uint32_t ngt = 0, neq = 0;  // per lane, at most 32 each
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const bool ok = j < nval;
-        ngt += (ok && rkeys[j] > T) ? 1u : 0u;
-        neq += (ok && rkeys[j] == T) ? 1u : 0u;
-      }
-      uint32_t cgt = 0, ceq = 0;
-#pragma unroll
-      for (int b = 0; b < 6; ++b) {
-        cgt += (uint32_t)__popcll(__ballot((ngt >> b) & 1u)) << b;
-        ceq += (uint32_t)__popcll(__ballot((neq >> b) & 1u)) << b;
-      }
-      if (lane == 0) {
-        hist[wave] = cgt;
-        hist[NW + wave] = ceq;
-      }
-      __syncthreads();
-      uint32_t gt_before = 0, eq_before = 0, gt_total = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const uint32_t g = hist[w], q = hist[NW + w];
-        gt_total += g;
-        if (w < wave) {
-          gt_before += g;
-          eq_before += q;
-        }
-      }
-      const uint32_t need_eq = (uint32_t)kk - gt_total;  // >= 1
-      const unsigned long long lt_mask = (1ull << lane) - 1ull;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const bool ok = j < nval;
-        const bool gt = ok && rkeys[j] > T, eq = ok && rkeys[j] == T;
-        const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
-        if ((bgt | beq) == 0) continue;  // nothing kept among these 64 positions (the usual case)
-        const uint32_t gtb = gt_before + __popcll(bgt & lt_mask);
-        const uint32_t eqb = eq_before + __popcll(beq & lt_mask);
-        const int i = pos0 + 64 * j;
-        if (gt) idx[gtb + min(eqb, need_eq)] = i;
-        if (eq && eqb < need_eq) idx[gtb + eqb] = i;
-        gt_before += __popcll(bgt);
-        eq_before += __popcll(beq);
-      }
-    } else {
+    {
       // every wave owns a contiguous range of positions; two passes over its keys (count, then emit).  With the
       // group maxima at hand only the groups that hold a key >= T are read; else eight groups of 64 positions per
       // round with their loads in flight together.
@@ -634,14 +436,452 @@ __device__ __forceinline__ void select_unit(const float* raw, int nrb, size_t rb
   for (int t = tid; t < alpha; t += NT) idx[kk + t] = npre + t;
 }
 
-// fuse_gather: once the unit's kept positions are written, the same workgroup copies the unit's K and V rows
-// (a7): for the few hundred rows of a small budget a launch of its own costs more than the copy.
-__global__ __launch_bounds__(NT) void pool_select_batch_kernel(const SelectBatchArgs a, const GatherBatchArgs ga,
-                                                               const int fuse_gather) {
-  extern __shared__ uint32_t lkeys[];  // kLdsKeys entries
-  __shared__ uint32_t hist[HIST];
+
+// The bin in which the count over ascending bins reaches kk: sel[0] = bin (untouched if there is none), sel[1] = count
+// before it, sel[2] = count in it.  Thread t owns bins 2t, 2t + 1 and leaves them cleared.  Every thread returns after
+// the answer is there.  (Bins 0 .. HIST - 1, `scan` holds NW entries.)
+__device__ __forceinline__ void find_bin(uint32_t* hist, uint32_t kk, uint32_t* scan, uint32_t* sel) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint2 h = reinterpret_cast<uint2*>(hist)[tid];
+  reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
+  const uint32_t incl = wave_inclusive_sum(h.x + h.y);
+  if (lane == 63) scan[wave] = incl;
+  lds_barrier();
+  uint32_t total;
+  const uint32_t before = sum_before(scan, wave, total) + incl - h.x - h.y;
+  const bool in0 = before < kk && before + h.x >= kk;
+  const bool in1 = before + h.x < kk && before + h.x + h.y >= kk;
+  if (in0 || in1) {
+    sel[0] = (uint32_t)(2 * tid + (in1 ? 1 : 0));
+    sel[1] = in1 ? before + h.x : before;
+    sel[2] = in1 ? h.y : h.x;
+  }
+  lds_barrier();
+}
+
+// A prefix of at most 1024 * PER keys.  Wave w owns positions [w * 64 * PER, (w + 1) * 64 * PER), lane l of it the four
+// from 256 * jj + 4 * l on, for every jj.  Returns true when the kept prefix positions are left in LDS (`keep`, kk
+// ascending entries), false when they have been written to idx instead.
+template <int PER, int PMAX>
+__device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const float* raw, size_t rb_stride, float* pooled,
+                                             int32_t* idx, int npre, int kk, uint32_t* area, uint32_t* hist,
+                                             uint32_t* scan, uint32_t* sel, uint16_t* keep) {
+  constexpr int NJ = PER / 4;
+  constexpr int CW = 64 * PER;
+  constexpr uint32_t kCap = PMAX * 512;  // entries of the list (key, position) and of `keep`: 8 bytes each of `area`
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w0 = wave * CW;
+  const int p0 = w0 + 4 * lane;
+  const int r = (a.pool == PKV_POOL_NONE) ? 0 : (a.pool_w - 1) / 2;
+  const bool is_max = a.pool == PKV_POOL_MAX;
+
+  // ---- A. group mean + pooling ----
+  f32x4 v[NJ];
+  int lim = npre - p0;  // the thread's position 256 * jj + c exists iff 256 * jj + c < lim
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj) {
+    const int g0 = w0 + 256 * jj, p = p0 + 256 * jj;  // first position of the wave's 256, of the thread's four
+    v[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (g0 + 256 <= npre) v[jj] = *reinterpret_cast<const f32x4_u*>(raw + p);
+    else if (g0 < npre) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (256 * jj + c < lim) v[jj][c] = raw[p + c];
+    }
+  }
+  for (int q = 1; q < a.nrb; ++q) {
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (256 * jj + c < lim) v[jj][c] += raw[q * rb_stride + p0 + 256 * jj + c];
+  }
+  reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
+  if (tid == 0) sel[0] = 0xFFFFFFFFu;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj) v[jj] *= a.inv_G;
+  if (r > 0) {
+    float* lsc = reinterpret_cast<float*>(area) + kPad;
+    lim = fresh(npre) - p0;
+    const float neutral = is_max ? -INFINITY : 0.f;
+    if (tid < kPad) {
+      lsc[tid - kPad] = neutral;
+      lsc[NT * PER + tid] = neutral;
+    }
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) {
+      const int g0 = w0 + 256 * jj, p = p0 + 256 * jj;
+      if (g0 < npre + kPad) {
+        f32x4 t = v[jj];
+        if (g0 + 256 > npre) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) t[c] = 256 * jj + c < lim ? t[c] : neutral;
+        }
+        *reinterpret_cast<f32x4*>(lsc + p) = t;
+      }
+    }
+    lds_barrier();
+    const float inv_w = 1.0f / (float)a.pool_w;
+    // windows summed (or maximised) in ascending position order
+    auto pool_fixed = [&](auto RR, auto MX) {
+      constexpr int R = decltype(RR)::value;
+      constexpr bool mx = decltype(MX)::value;
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) {
+        if (w0 + 256 * jj >= npre) continue;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj - 4);
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj + 4);
+        const f32x4 md = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj);
+        const float x[12] = {lo[0], lo[1], lo[2], lo[3], md[0], md[1], md[2], md[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float acc = x[4 + c - R];
+#pragma unroll
+          for (int u = -R + 1; u <= R; ++u) acc = mx ? fmaxf(acc, x[4 + c + u]) : acc + x[4 + c + u];
+          v[jj][c] = mx ? acc : acc * inv_w;
+        }
+      }
+    };
+    using std::integral_constant;
+    if (r <= 3) {
+      if (is_max) {
+        if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::true_type{});
+        else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::true_type{});
+        else pool_fixed(integral_constant<int, 3>{}, std::true_type{});
+      } else {
+        if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::false_type{});
+        else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::false_type{});
+        else pool_fixed(integral_constant<int, 3>{}, std::false_type{});
+      }
+    } else {
+      // wider windows: one new score per step for the thread's four outputs
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) {
+        if (w0 + 256 * jj >= npre) continue;
+        const float* lp = lsc + p0 + 256 * jj - r;
+        float x0 = lp[0], x1 = lp[1], x2 = lp[2];
+        f32x4 acc = is_max ? f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY} : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u <= 2 * r; ++u) {
+          const float x3 = lp[u + 3];
+          acc[0] = is_max ? fmaxf(acc[0], x0) : acc[0] + x0;
+          acc[1] = is_max ? fmaxf(acc[1], x1) : acc[1] + x1;
+          acc[2] = is_max ? fmaxf(acc[2], x2) : acc[2] + x2;
+          acc[3] = is_max ? fmaxf(acc[3], x3) : acc[3] + x3;
+          x0 = x1;
+          x1 = x2;
+          x2 = x3;
+        }
+        v[jj] = is_max ? acc : acc * inv_w;
+      }
+    }
+  }
+  uint32_t key[NJ][4];  // 0: no such position
+  lim = fresh(npre) - p0;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) key[jj][c] = 256 * jj + c < lim ? __float_as_uint(v[jj][c]) : 0u;
+  if (pooled) {
+    lim = fresh(npre) - p0;
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (256 * jj + c < lim) pooled[p0 + 256 * jj + c] = v[jj][c];
+  }
+  if (kk == 0) return true;
+
+  // ---- B. the kk-th largest key ----
+  uint32_t kmax = 0u;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) kmax = max(kmax, key[jj][c]);
+  // A reference below the few outstanding keys (an attention sink stands many binades above all others): in every wave
+  // the smallest of the largest keys of its four rows of 16 lanes, and the largest of these over the waves.
+  kmax = row_max_lane15(kmax);
+  {
+    const uint32_t m = min(min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 15), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 31)),
+                           min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 47), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 63)));
+    if (lane == 0) scan[wave] = m;
+  }
+  lds_barrier();  // (also: every thread is done with the scores in `area`)
+  const uint32_t ref = (uint32_t)__builtin_amdgcn_readlane((int)row_max_lane15(scan[lane & 15]), 15);
+
+  uint32_t* lkey = area;                                         // [kCap]
+  uint16_t* lpos = reinterpret_cast<uint16_t*>(area + kCap);      // [kCap]; `keep` lies behind it
+  // groups of gs keys (a power of two, at most NJ): at least twice as many groups as keys to select, so that the bound
+  // is not much below T.  A group's keys lie 256 positions apart: neighbours share a pooling window.
+  int gs = 1;
+  while (2 * gs <= NJ && 4 * gs * kk <= npre) gs *= 2;
+  // Bins, descending: 0 .. 1023 for keys from the reference up, 1/8 of a binade each (2^20 units of the bit pattern),
+  // 1024 .. 2047 for those below it, 2^shift each: 1/64 of a binade (16 binades) or, where T lies deeper, 1/8.
+  constexpr int kUp = 20;
+  constexpr uint32_t kMid = HIST / 2;
+  int shift = 17;
+  auto bin_of = [&](uint32_t k) -> uint32_t {
+    return k >= ref ? kMid - 1u - min((k - ref) >> kUp, kMid - 1u) : kMid + ((ref - 1u - k) >> shift);
+  };
+  // smallest key of a bin (0: there is no positive one)
+  auto lower_edge = [&](uint32_t bin) -> uint32_t {
+    if (bin < kMid) return ref + ((kMid - 1u - bin) << kUp);
+    const unsigned long long down = (unsigned long long)(bin - kMid + 1u) << shift;
+    return down < ref ? ref - (uint32_t)down : 0u;
+  };
+  uint32_t n_list = 0u, bound = 0u;
+  bool ok = false;
+  for (int attempt = 0; attempt < 2 && !ok; ++attempt) {
+    shift = attempt == 0 ? 17 : 20;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      uint32_t m = 0u;
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) {
+        m = max(m, key[jj][c]);
+        if (((jj + 1) & (gs - 1)) == 0) {  // uniform
+          const uint32_t bin = bin_of(m);
+          if (m != 0u && bin < (uint32_t)HIST) atomicAdd(&hist[bin], 1u);
+          m = 0u;
+        }
+      }
+    }
+    lds_barrier();
+    find_bin(hist, (uint32_t)kk, scan + NW, sel);
+    const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
+    if (bin == 0xFFFFFFFFu) continue;
+    bound = lower_edge(bin);
+    if (bound == 0u) continue;  // a key of zero would have to be told from none
+    // the keys at or above the bound: counted per wave, then listed in position order
+    uint32_t cnt = 0u;
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) cnt += (uint32_t)__popcll(__ballot(key[jj][c] >= bound));
+    if (lane == 0) scan[wave] = cnt;
+    lds_barrier();
+    uint32_t base = sum_before(scan, wave, n_list);
+    if (n_list > kCap) break;  // (uniform)
+    if (cnt != 0u) {
+      const uint32_t bnd = (uint32_t)fresh((int)bound);
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) {
+        unsigned long long b[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) b[c] = __ballot(key[jj][c] >= bnd);
+        if ((b[0] | b[1] | b[2] | b[3]) == 0ull) continue;
+        uint32_t at = base + bits_below(b[0]) + bits_below(b[1]) + bits_below(b[2]) + bits_below(b[3]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (key[jj][c] >= bnd) {
+            lkey[at] = key[jj][c];
+            lpos[at] = (uint16_t)(p0 + 256 * jj + c);
+            ++at;
+          }
+        }
+        base += (uint32_t)(__popcll(b[0]) + __popcll(b[1]) + __popcll(b[2]) + __popcll(b[3]));
+      }
+    }
+    ok = true;
+  }
+  uint32_t T = 0u;
+  if (ok) {
+    lds_barrier();  // the list is complete
+    for (uint32_t i = tid; i < n_list; i += NT) atomicAdd(&hist[bin_of(lkey[i])], 1u);
+    lds_barrier();
+    find_bin(hist, (uint32_t)kk, scan + NW, sel);  // (there is such a bin: the list holds at least kk keys)
+    const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
+    const uint32_t need = (uint32_t)kk - __builtin_amdgcn_readfirstlane(sel[1]);
+    const uint32_t n_open = __builtin_amdgcn_readfirstlane(sel[2]);
+    const uint32_t edge = lower_edge(bin);  // (>= bound >= 1)
+    constexpr int kOpen = 512;
+    if (need == n_open) {
+      T = edge - 1u;  // the whole bin is kept
+    } else if (n_open <= (uint32_t)kOpen) {
+      // the bin's keys, as distances from its edge, in hist (cleared by find_bin); their order does not matter
+      if (tid == 0) sel[0] = 0u;
+      lds_barrier();
+      for (uint32_t i = tid; i < n_list; i += NT) {
+        const uint32_t k = lkey[i];
+        if (bin_of(k) == bin) hist[atomicAdd(&sel[0], 1u)] = k - edge;
+      }
+      lds_barrier();
+      // the need-th largest: every key counts those above it and those not below it (entries behind the last are 0)
+      if ((uint32_t)tid < n_open) {
+        const uint32_t d = hist[tid];
+        uint32_t above = 0u, from = 0u;
+        for (uint32_t j = 0; j < n_open; j += 4) {
+          const u32x4 q = *reinterpret_cast<const u32x4*>(hist + j);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            above += q[c] > d ? 1u : 0u;
+            from += q[c] >= d ? 1u : 0u;
+          }
+        }
+        if (above < need && need <= from) sel[1] = edge + d;
+      }
+      lds_barrier();
+      T = __builtin_amdgcn_readfirstlane(sel[1]);
+    } else {
+      ok = false;
+    }
+  }
+  if (ok) {
+    // ---- C. ordered emission from the list, wave w its w-th stretch ----
+    const uint32_t seg = ((n_list + NW - 1) / NW + 63u) & ~63u;
+    const uint32_t e0 = min(wave * seg, n_list), e1 = min(e0 + seg, n_list);
+    uint32_t cgt = 0u, ceq = 0u;
+    for (uint32_t i0 = e0; i0 < e1; i0 += 64) {
+      const uint32_t k = i0 + lane < e1 ? lkey[i0 + lane] : 0u;
+      cgt += (uint32_t)__popcll(__ballot(k > T));
+      ceq += (uint32_t)__popcll(__ballot(k == T && i0 + lane < e1));
+    }
+    if (lane == 0) {
+      scan[wave] = cgt;
+      scan[NW + wave] = ceq;
+    }
+    lds_barrier();
+    uint32_t gt_total, eq_total;
+    uint32_t gt_before = sum_before(scan, wave, gt_total), eq_before = sum_before(scan + NW, wave, eq_total);
+    const uint32_t need_eq = (uint32_t)kk - gt_total;
+    for (uint32_t i0 = e0; i0 < e1; i0 += 64) {
+      const bool in = i0 + lane < e1;
+      const uint32_t k = in ? lkey[i0 + lane] : 0u;
+      const bool gt = k > T, eq = in && k == T;
+      const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
+      const uint32_t gtb = gt_before + bits_below(bgt), eqb = eq_before + bits_below(beq);
+      if (gt) keep[gtb + min(eqb, need_eq)] = lpos[i0 + lane];
+      if (eq && eqb < need_eq) keep[gtb + eqb] = lpos[i0 + lane];
+      gt_before += (uint32_t)__popcll(bgt);
+      eq_before += (uint32_t)__popcll(beq);
+    }
+    lds_barrier();
+    return true;
+  }
+
+  // ---- the plain way: binary search for T over all keys (all 32 bits, whatever bit patterns the scores hold; a
+  // position that does not exist carries key 0 and is never counted, T >= 1 in every comparison) ----
+  T = 0u;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = T | (1u << bit);
+    uint32_t cnt = 0u;
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) cnt += (uint32_t)__popcll(__ballot(key[jj][c] >= cand));
+    uint32_t* slot = scan + ((bit & 1) ? NW : 0);  // two sets of per-wave slots: one barrier per bit
+    if (lane == 0) slot[wave] = cnt;
+    __syncthreads();
+    uint32_t c = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) c += slot[w];
+    if (c >= (uint32_t)kk) T = cand;
+  }
+  uint32_t cgt = 0u, ceq = 0u;
+  lim = fresh(npre) - p0;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      cgt += (uint32_t)__popcll(__ballot(key[jj][c] > T));
+      ceq += (uint32_t)__popcll(__ballot(key[jj][c] == T && 256 * jj + c < lim));
+    }
+  __syncthreads();
+  if (lane == 0) {
+    scan[wave] = cgt;
+    scan[NW + wave] = ceq;
+  }
+  __syncthreads();
+  uint32_t gt_total, eq_total;
+  uint32_t gt_before = sum_before(scan, wave, gt_total), eq_before = sum_before(scan + NW, wave, eq_total);
+  const uint32_t need_eq = (uint32_t)kk - gt_total;  // keys equal to T to take, lowest positions first (>= 1)
+  lim = fresh(npre) - p0;
+  T = (uint32_t)fresh((int)T);
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj) {
+    unsigned long long bg[4], be[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      bg[c] = __ballot(key[jj][c] > T);
+      be[c] = __ballot(key[jj][c] == T && 256 * jj + c < lim);
+    }
+    uint32_t gtb = gt_before, eqb = eq_before;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      gtb += bits_below(bg[c]);
+      eqb += bits_below(be[c]);
+      gt_before += (uint32_t)__popcll(bg[c]);
+      eq_before += (uint32_t)__popcll(be[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int i = p0 + 256 * jj + c;
+      if (key[jj][c] > T) {
+        idx[gtb + min(eqb, need_eq)] = i;
+        ++gtb;
+      } else if (key[jj][c] == T && 256 * jj + c < lim) {
+        if (eqb < need_eq) idx[gtb + eqb] = i;
+        ++eqb;
+      }
+    }
+  }
+  return false;
+}
+
+// The kept rows' K and V of a unit, pos(j) the position of row j (-1: unused slot, the row is cleared).
+template <class Pos>
+__device__ __forceinline__ void gather_unit(const GatherBatchArgs& ga, const GatherLayer& gl, int b, int g, Pos pos) {
+  const int sh = ga.d == 128 ? 4 : 3;  // 16 or 8 lanes per row
+  const int total = gl.k_cap << sh;
+  // four row segments per thread and round, each stage (positions, rows, stores) issued for all four before the
+  // next one
+  constexpr int NB = 4;
+  const size_t head_off = (size_t)b * ga.kv_sb + (size_t)g * ga.kv_sh;
+  const size_t out_off = (size_t)b * gl.o_sb + (size_t)g * gl.o_sh;
+  for (int t0 = threadIdx.x; t0 < total; t0 += NB * NT) {
+    int src[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int t = t0 + u * NT;
+      src[u] = t < total ? pos(t >> sh) : -1;
+    }
+    u32x4 kv[NB], vv[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int seg = (t0 + u * NT) & ((1 << sh) - 1);
+      kv[u] = u32x4{0u, 0u, 0u, 0u};
+      vv[u] = kv[u];
+      if ((uint32_t)src[u] < (uint32_t)ga.N) {  // nothing outside [0, N) is dereferenced
+        const size_t off = head_off + (size_t)src[u] * ga.kv_st + seg * 8;
+        kv[u] = *reinterpret_cast<const u32x4*>(gl.K + off);
+        vv[u] = *reinterpret_cast<const u32x4*>(gl.V + off);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int t = t0 + u * NT;
+      if (t < total) {
+        const size_t o = out_off + (size_t)(t >> sh) * gl.o_st + (t & ((1 << sh) - 1)) * 8;
+        *reinterpret_cast<u32x4*>(gl.K_out + o) = kv[u];
+        *reinterpret_cast<u32x4*>(gl.V_out + o) = vv[u];
+      }
+    }
+  }
+}
+
+// PMAX: positions per thread that the launch's longest prefix needs (4 .. 32), LONG: prefixes beyond 32768.
+// fuse_gather: once the unit's kept positions are known, the same workgroup copies the unit's K and V rows (a7): for
+// the few hundred rows of a small budget a launch of its own costs more than the copy.
+template <int PMAX, bool LONG>
+__global__ __launch_bounds__(NT, PMAX <= 16 ? 8 : 4) void pool_select_batch_kernel(const SelectBatchArgs a,
+                                                                                   const GatherBatchArgs ga,
+                                                                                   const int fuse_gather) {
+  extern __shared__ uint32_t area[];  // select_area_words(PMAX) entries
+  __shared__ __attribute__((aligned(16))) uint32_t hist[HIST];
   __shared__ uint32_t scan32[2 * NW];
-  __shared__ uint32_t sel[2];
+  __shared__ uint32_t sel[4];
+  uint16_t* keep = reinterpret_cast<uint16_t*>(area + PMAX * 768);  // behind the list's keys and positions
 
   const int tid = threadIdx.x;
   const int BH = a.B * a.Hkv;
@@ -651,6 +891,7 @@ __global__ __launch_bounds__(NT) void pool_select_batch_kernel(const SelectBatch
   const int b = bg / a.Hkv;
   const int g = bg - b * a.Hkv;
   const SelectLayer& ly = a.layer[l];
+  const GatherLayer& gl = ga.layer[l];
   int n = a.N;
   if (a.seq_lens) {
     n = a.seq_lens[b];
@@ -660,51 +901,9 @@ __global__ __launch_bounds__(NT) void pool_select_batch_kernel(const SelectBatch
   // a scoring kernel that gave up a wait leaves meaningless scores: the caller learns it from the count
   if (g == 0 && tid == 0) ly.count_out[b] = (a.err && *a.err != 0) ? -1 : count;
   int32_t* idx = ly.idx_out + (size_t)bg * ly.k_cap;
-  auto gather_unit = [&]() {
-    if (!fuse_gather) return;
-    __syncthreads();  // the unit's kept positions are complete (all of them written by this workgroup)
-    const GatherLayer& gl = ga.layer[l];
-    const int sh = ga.d == 128 ? 4 : 3;  // 16 or 8 lanes per row
-    const int total = gl.k_cap << sh;
-    // four row segments per thread and round, each stage (positions, rows, stores) issued for all four before the
-    // next one: three memory round trips per round instead of twelve
-    constexpr int NB = 4;
-    const size_t head_off = (size_t)b * ga.kv_sb + (size_t)g * ga.kv_sh;
-    const size_t out_off = (size_t)b * gl.o_sb + (size_t)g * gl.o_sh;
-    const int32_t* pos = gl.idx + ((size_t)b * ga.Hkv + g) * gl.k_cap;
-    for (int t0 = tid; t0 < total; t0 += NB * NT) {
-      int src[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int t = t0 + u * NT;
-        src[u] = t < total ? pos[t >> sh] : -1;
-      }
-      uint4 kv[NB], vv[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int seg = (t0 + u * NT) & ((1 << sh) - 1);
-        kv[u] = make_uint4(0, 0, 0, 0);
-        vv[u] = kv[u];
-        if ((uint32_t)src[u] < (uint32_t)ga.N) {  // -1: unused slot; nothing outside [0, N) is dereferenced
-          const size_t off = head_off + (size_t)src[u] * ga.kv_st + seg * 8;
-          kv[u] = *reinterpret_cast<const uint4*>(gl.K + off);
-          vv[u] = *reinterpret_cast<const uint4*>(gl.V + off);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int t = t0 + u * NT;
-        if (t < total) {
-          const size_t o = out_off + (size_t)(t >> sh) * gl.o_st + (t & ((1 << sh) - 1)) * 8;
-          *reinterpret_cast<uint4*>(gl.K_out + o) = kv[u];
-          *reinterpret_cast<uint4*>(gl.V_out + o) = vv[u];
-        }
-      }
-    }
-  };
   if (ly.k_l >= n) {  // keep everything
     for (int j = tid; j < ly.k_cap; j += NT) idx[j] = j < n ? j : -1;
-    gather_unit();
+    if (fuse_gather) gather_unit(ga, gl, b, g, [&](int j) { return j < n ? j : -1; });
     return;
   }
   const int npre = n - a.alpha;
@@ -712,38 +911,59 @@ __global__ __launch_bounds__(NT) void pool_select_batch_kernel(const SelectBatch
   const size_t rb_stride = (size_t)BH * a.N;
   const float* raw = a.raw + ((size_t)l * a.nrb * BH + bg) * a.N;
   float* pooled = ly.pooled + (size_t)bg * a.N;
-  if (npre <= 8 * NT)
-    select_unit<true, 8>(raw, a.nrb, rb_stride, a.inv_G, pooled, ly.write_pooled != 0, idx, npre, kk, a.alpha, a.pool,
-                         a.pool_w, lkeys, hist, scan32, sel);
-  else if (npre <= 16 * NT)
-    select_unit<true, 16>(raw, a.nrb, rb_stride, a.inv_G, pooled, ly.write_pooled != 0, idx, npre, kk, a.alpha,
-                          a.pool, a.pool_w, lkeys, hist, scan32, sel);
-  else if (npre <= kLdsKeys)
-    select_unit<true, kLdsKeys / NT>(raw, a.nrb, rb_stride, a.inv_G, pooled, ly.write_pooled != 0, idx, npre, kk,
-                                     a.alpha, a.pool, a.pool_w, lkeys, hist, scan32, sel);
-  else
-    select_unit<false, kLdsKeys / NT>(raw, a.nrb, rb_stride, a.inv_G, pooled, true, idx, npre, kk, a.alpha, a.pool,
-                                      a.pool_w, lkeys, hist, scan32, sel);
-  gather_unit();
+  bool in_lds = false;
+  auto run = [&](auto P) {
+    if constexpr (decltype(P)::value <= PMAX)
+      in_lds = select_short<decltype(P)::value, PMAX>(a, raw, rb_stride, ly.write_pooled ? pooled : nullptr, idx, npre,
+                                                       kk, area, hist, scan32, sel, keep);
+  };
+  if (PMAX <= 8 && npre <= 4 * NT) run(std::integral_constant<int, 4>{});
+  else if (npre <= 8 * NT) run(std::integral_constant<int, 8>{});
+  else if (npre <= 16 * NT) run(std::integral_constant<int, 16>{});
+  else if (!LONG || npre <= kLdsKeys) run(std::integral_constant<int, 32>{});
+  else if constexpr (LONG)
+    select_long(raw, a.nrb, rb_stride, a.inv_G, pooled, idx, npre, kk, a.alpha, a.pool, a.pool_w, area, hist, scan32, sel);
+  if (in_lds) {
+    auto pos = [&](int j) { return j < kk ? (int)keep[j] : npre + j - kk; };
+    for (int j = tid; j < ly.k_l; j += NT) idx[j] = pos(j);
+    if (fuse_gather) gather_unit(ga, gl, b, g, pos);
+  } else {
+    for (int t = tid; t < a.alpha; t += NT) idx[kk + t] = npre + t;
+    if (fuse_gather) {
+      __syncthreads();  // the unit's kept positions are complete (all of them written by this workgroup)
+      gather_unit(ga, gl, b, g, [&](int j) { return idx[j]; });
+    }
+  }
+}
+
+constexpr size_t select_area_words(int pmax) { return (size_t)pmax * NT + 2 * kPad; }
+
+template <int PMAX, bool LONG>
+hipError_t launch_select(const SelectBatchArgs& a, const GatherBatchArgs& ga, bool fuse_gather, int nlayers, hipStream_t s) {
+  static bool attr_set[kMaxDevices];
+  const size_t dyn = select_area_words(PMAX) * sizeof(uint32_t);
+  const int dev = current_device_slot();
+  if (dev < 0) return hipErrorInvalidDevice;
+  if (!attr_set[dev]) {  // allow that much dynamic LDS, once per device (idempotent; no allocation)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pool_select_batch_kernel<PMAX, LONG>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    if (e != hipSuccess) return e;
+    attr_set[dev] = true;
+  }
+  hipLaunchKernelGGL((pool_select_batch_kernel<PMAX, LONG>), dim3(nlayers * a.B * a.Hkv), dim3(NT), dyn, s, a, ga,
+                     fuse_gather ? 1 : 0);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_pool_select_batch(const SelectBatchArgs& a, const GatherBatchArgs& ga, bool fuse_gather, int nlayers,
                                     hipStream_t s) {
-  static bool attr_set[kMaxDevices];
-  const size_t dyn = (size_t)kLdsKeys * sizeof(uint32_t);
-  const int dev = current_device_slot();
-  if (dev < 0) return hipErrorInvalidDevice;
-  if (!attr_set[dev]) {  // allow 128 KB of dynamic LDS, once per device (idempotent; no allocation)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pool_select_batch_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
-    if (e != hipSuccess) return e;
-    attr_set[dev] = true;
-  }
-  hipLaunchKernelGGL(pool_select_batch_kernel, dim3(nlayers * a.B * a.Hkv), dim3(NT), dyn, s, a, ga,
-                     fuse_gather ? 1 : 0);
-  return hipGetLastError();
+  const int npre = a.N - a.alpha;  // of the longest sequence
+  if (npre <= 8 * NT) return launch_select<8, false>(a, ga, fuse_gather, nlayers, s);
+  if (npre <= 16 * NT) return launch_select<16, false>(a, ga, fuse_gather, nlayers, s);
+  if (npre <= kLdsKeys) return launch_select<32, false>(a, ga, fuse_gather, nlayers, s);
+  return launch_select<32, true>(a, ga, fuse_gather, nlayers, s);
 }
 
 // ---- attention recall rate (appendix, "Attention Recall Rate Experiment") ----
