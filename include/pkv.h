@@ -31,7 +31,8 @@
  *  - Exclusive use of the device.  Whenever a device with at least 256
  *    compute units is given a shape the register-resident scoring kernel
  *    serves (G*alpha <= 512, N <= 262144) without supplied softmax
- *    denominators, that kernel's 512 workgroups exchange softmax statistics
+ *    denominators, that kernel's 512 workgroups (or, at few query rows, the
+ *    one-pass kernel's 256) exchange softmax statistics
  *    with each other and must all be resident on the device at the same
  *    time; they fill it completely (registers and LDS of every compute
  *    unit).  The caller must therefore not run other kernels on the device

@@ -170,6 +170,37 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
   return plan.resident_ok && (lse_mode || device_fits_resident());
 }
 
+// How the one-pass kernel for few query rows serves a call: layers per launch (0: it does not), workgroups, and
+// statistics kept per workgroup.  Whether it does is a matter of one layer's shape alone: a call over many layers gives
+// the same results as one call per layer.  (The statistics words lie in the part of the workspace that holds the pooled
+// scores later on.)
+struct StreamPlan {
+  int layers, grid, ring;
+};
+static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
+  StreamPlan p = {0, 0, 0};
+  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok || !device_fits_resident()) return p;
+  if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
+  const int64_t parts = (d.N + stream_item_keys(plan.R) - 1) / stream_item_keys(plan.R);
+  const int64_t per_layer = parts * plan.BH;
+  // Every item reads the statistics of all items of its unit: at 33 .. 64 rows and half as many keys per item that is
+  // half of the keys' own traffic at 128 items.  Measured against the resident kernel: 8 heads, 64 rows, d = 128:
+  // 24k keys 310 -> 227 us, 32k 327 -> 316, 64k 384 -> 456; d = 64: 10k 72.6 -> 72.3, 32k 124 -> 148.  (With 32 rows the
+  // one-pass kernel is ahead up to the longest context: 200k keys 595 -> 432 us.)
+  if (plan.R > 32 && parts > (d.d == 128 ? 64 : 20)) return p;
+  const int64_t by_items = (int64_t)kStreamItems * kStreamGrid / per_layer, by_units = kStreamUnits / d.B;
+  if (parts > kStreamGrid || by_items < 1 || by_units < 1) return p;
+  int64_t nl = by_items < by_units ? by_items : by_units;
+  if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;
+  if (nl > plan.L) nl = plan.L;
+  const int64_t items = nl * per_layer;
+  p.layers = (int)nl;
+  p.grid = items < kStreamGrid ? (int)items : kStreamGrid;
+  p.ring = 1;
+  while (p.ring < kStreamRing && (int64_t)p.ring * kStreamGrid < items) p.ring *= 2;
+  return p;
+}
+
 // Queue the kernels of L layers.  All arguments have been validated.
 static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, const LayerPtrs* ptrs,
                       const int32_t* seq_lens, void* workspace, hipStream_t stream, Recorder* rec,
@@ -186,7 +217,36 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   if (rec) rec->begin(stream);
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
-  if (any_scores && resident) {
+  StreamPlan sp = {0, 0, 0};
+  if (any_scores && resident) sp = stream_plan(plan, d, lse_mode);
+  if (sp.layers > 0) {
+    for (int32_t l0 = 0; l0 < L; l0 += sp.layers) {
+      const int32_t nl = L - l0 < sp.layers ? L - l0 : sp.layers;
+      StreamArgs sa;
+      memset(&sa, 0, sizeof(sa));
+      for (int32_t i = 0; i < nl; ++i) {
+        sa.layer[i].Q = static_cast<const uint16_t*>(ptrs[l0 + i].Q);
+        sa.layer[i].K = static_cast<const uint16_t*>(ptrs[l0 + i].K);
+        sa.layer[i].k_l = descs[l0 + i].k_l;
+      }
+      const int64_t rows = plan.R <= 32 ? 32 : 64;
+      sa.seq_lens = seq_lens;
+      sa.raw = raw + (size_t)l0 * plan.BH * d.N;
+      sa.stats = reinterpret_cast<unsigned long long*>(pooled_ws);
+      sa.dump = reinterpret_cast<float*>(sa.stats + (int64_t)sp.grid * sp.ring * rows);
+      sa.grid = sp.grid; sa.ring = sp.ring;
+      sa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
+      sa.L = nl; sa.B = d.B; sa.Hq = d.Hq; sa.Hkv = d.Hkv; sa.G = plan.G; sa.alpha = d.alpha; sa.N = d.N; sa.R = plan.R;
+      sa.d = d.d;
+      sa.wait_ticks = (d.flags & PKV_FLAG_NO_WAIT) ? 0 : kResidentWaitTicks;
+      sa.q_sb = d.q_sb; sa.q_sh = d.q_sh; sa.q_st = d.q_st;
+      sa.kv_sb = d.kv_sb; sa.kv_sh = d.kv_sh; sa.kv_st = d.kv_st;
+      sa.kappa = kappa;
+      sa.inv_G = 1.0f / (float)plan.G;
+      if (launch_score_stream(sa, l0 == 0, stream) != hipSuccess) return PKV_ERR_HIP;
+      if (rec) rec->after(PKV_KERNEL_SCORE_RESIDENT, stream);
+    }
+  } else if (any_scores && resident) {
     for (int32_t l0 = 0; l0 < L; l0 += kResidentMaxLayers) {
       const int32_t nl = L - l0 < kResidentMaxLayers ? L - l0 : kResidentMaxLayers;
       ResidentArgs ra;

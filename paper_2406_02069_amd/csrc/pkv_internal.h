@@ -99,6 +99,31 @@ struct ResidentArgs {
   float kappa, inv_kappa, inv_G;
 };
 
+// ---- one-pass scoring for few query rows, over many layers (pkv_stream.hip) ----
+constexpr int kStreamGrid = 256;    // persistent workgroups, one per compute unit
+constexpr int kStreamMaxRows = 64;  // G * alpha
+constexpr int kStreamItems = 272;   // items of a workgroup per launch, at most (table in LDS)
+constexpr int kStreamUnits = 2048;  // layers x sequences per launch, at most (prefix table in LDS)
+constexpr int kStreamRing = 8;      // a workgroup's statistics are kept for that many items (a power of two)
+
+struct StreamArgs {
+  ResidentLayer layer[kResidentMaxLayers];
+  const int32_t* seq_lens;
+  float* raw;                 // [U][N] un-pooled scores
+  unsigned long long* stats;  // [grid][ring][32 or 64] statistics of a workgroup's last items (log2 domain;
+                              // the sign bit of the sum carries a phase); cleared before the launch
+  float* dump;                // [grid][64] written, never read
+  int32_t* err;
+  int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
+  int32_t grid, ring;         // workgroups (kStreamGrid, fewer if there are fewer items); statistics kept per workgroup
+  int32_t wait_ticks;
+  int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
+  float kappa, inv_G;
+};
+int stream_item_keys(int R);
+// clear_err: the first launch of a call also clears the error word
+hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s);
+
 // ---- pooling + selection and gather over many layers ----
 constexpr int kBatchMaxLayers = 32;  // per launch (kernel-argument tables: selection + gather together < 4 KB)
 

@@ -1,0 +1,614 @@
+// Window scoring in one pass over K for few query rows per KV head (G * alpha <= 64; Sec. 4.2.2, Eq. Al and Eq.
+// att_score) on MI355X.
+//
+// The score of a key needs the softmax normaliser of every window query, which is known only after all keys of the
+// head have been seen.  With few query rows the un-normalised probabilities p = exp2(kappa q.k - m) of a key (m: a
+// reference exponent of the row) take less room than the key itself, so they, and not the keys, are what waits for
+// the normalisers:  s_i = sum_r p_ri exp2(m_r - c_r)  is one multiply-add per logit, K is multiplied once, and the
+// registers of a key are free for the next one as soon as it has been multiplied.
+//
+// Work split.  An item is KI = 256 * TPW keys of one unit (layer, sequence, KV head).  256 persistent workgroups of 512
+// threads, one per compute unit (all of its LDS, 256 registers per lane), take the items in turn: item j belongs to
+// workgroup j % 256.  Sequences of a ragged batch contribute the items they have, one after the other without gaps.
+//
+// Per item a workgroup
+//   1. multiplies its keys with the unit's queries (rows = queries in registers, columns = keys; wave w takes the 32-key
+//      tiles w, w + 8, ... of the item, loaded straight into operand layout, KB tiles ahead, across item boundaries),
+//      turns the logits into p relative to the logits of the unit's key 0 and keeps them in registers; sums over the keys give
+//      the item's statistics (reference, sum) per row, published for the unit's other items;
+//   2. finishes the item BEFORE: the statistics of all items of its unit, which have had nearly the time of a whole item
+//      to arrive, are read (8 bytes per row and item: a few per cent of the keys' traffic) and folded into the
+//      normalisers; its p, moved to LDS meanwhile, are weighted and summed over the rows; one score per key is written
+//      (already divided by G).
+// A word of statistics carries a phase bit and so announces itself (agent-scope relaxed atomics, cleared before the
+// launch).  They are requested a tile before they are used, in front of the keys requested at that place: a wave's
+// loads return in order, so a probe issued behind keys would hold the wave until those have arrived.  (For the same
+// reason there is one hop and not two, fold by one item and hand over: each hop costs a tile's time.)  A workgroup's
+// slot is written again eight items later; the phase bit keeps a late reader from taking the one for the other.
+// The reference is the same for all keys of a unit, so that equal keys get equal scores, bit for bit.
+// A row whose reference was too far below its logits (sum beyond 2^100) is recomputed by its wave with the exact
+// maximum, from memory (rare).
+//
+// What bounds it: HBM for many units.  Measured against the register-resident kernel, which keeps the keys and multiplies
+// them twice (one scoring launch, by the profiler): 256 units of 8k keys, 32 rows 146 -> 122 us; 256 of 32k, 8 rows 535
+// -> 398 us (5.4 TB/s); ragged batch, 2048 units of 8k .. 16k, 64 rows 2.20 -> 1.56 ms (4.4 TB/s; an item of 512 keys
+// takes 6 - 7 us, of which the hop between the workgroups is not always covered).  One unit or a few: the latency of the
+// keys, one hop and two barriers; one layer of 8 heads with 8k keys 17.9 -> 16.5 us.
+//
+// Every wait is bounded by wall-clock time (a workgroup that has waited too long raises the error word and carries on),
+// so the grid always drains.
+#include <type_traits>
+
+#include "pkv_internal.h"
+
+namespace pkv {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned long long u64;
+
+constexpr int kW = 8;             // waves per workgroup
+constexpr int kT = kW * 64;
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
+__device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
+// A value the compiler must treat as new: lane constants derived from it are recomputed where they are used instead of
+// being kept (and spilled) across the whole item loop.
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// LDS traffic of one wave to its own region needs ordering only inside the wave.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+__device__ __forceinline__ void st64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ u64 ld64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void merge_stats(float& m, float& z, float m2, float z2) {
+  const float M = fmaxf(m, m2);
+  const float Ms = (M == -INFINITY) ? 0.f : M;
+  z = z * fast_exp2(m - Ms) + z2 * fast_exp2(m2 - Ms);
+  m = M;
+}
+// Sum (maximum) over the 32 lanes of a wave half, valid in its last lane.
+template <bool MAX>
+__device__ __forceinline__ float half_reduce(float x) {
+#define PKV_STEP(ctrl, rows)                                                                                              \
+  {                                                                                                                       \
+    const float y = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(MAX ? -INFINITY : 0.f), __float_as_int(x), ctrl, rows, 0xF, false)); \
+    x = MAX ? fmaxf(x, y) : x + y;                                                                                        \
+  }
+  PKV_STEP(0x111, 0xF)  // row_shr:1, 2, 4, 8: the last lane of every row of 16 holds the row's result
+  PKV_STEP(0x112, 0xF)
+  PKV_STEP(0x114, 0xF)
+  PKV_STEP(0x118, 0xF)
+  PKV_STEP(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
+#undef PKV_STEP
+  return x;
+}
+// x summed over the two halves of the wave, in every lane.
+__device__ __forceinline__ float both_halves(float x) {
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// NV: registers of a 32x32 product that hold real rows (register v of half h: row 8 (v / 4) + 4 h + v % 4), 4 per 8
+// rows; RT: 32-row tiles of queries.
+template <int D, int NV, int RT>
+struct StreamShape {
+  static constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;  // (row pitch of Q in LDS: 16-byte slots, bank-free)
+  static constexpr int TPW = RT == 1 ? 4 : 2;                      // 32-key tiles of an item per wave
+  static constexpr int KI = 32 * kW * TPW;                         // keys per item
+  static constexpr int KB = D == 128 ? 2 : TPW;                    // tiles in flight per wave
+  static constexpr int ROWS = 32 * RT;
+  static constexpr int PPL = kT / (32 * RT);                       // items whose statistics one load per thread covers
+  static constexpr int NPL = 4;                                    // such loads made ahead
+  static constexpr int P_SLOTS = kW * TPW * RT * (NV / 4) * 64;    // 16-byte slots of the pending p
+  static constexpr int Q_SLOTS = ROWS * PITCH;
+  static constexpr size_t LDS = (size_t)(P_SLOTS + Q_SLOTS) * 16 + (size_t)kW * ROWS * 6 * 4 + (size_t)ROWS * 2 * 4 +
+                                (size_t)kStreamItems * 8;
+  static_assert(LDS <= 160 * 1024, "one workgroup per compute unit");
+  static_assert((size_t)(P_SLOTS + Q_SLOTS) * 16 >= (size_t)(kStreamUnits + 1 + kW) * 4, "prefix table fits");
+};
+
+template <int D, int NV, int RT>
+__global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a) {
+  using S = StreamShape<D, NV, RT>;
+  constexpr int KS = S::KS, SEG = S::SEG, PITCH = S::PITCH, TPW = S::TPW, KI = S::KI, KB = S::KB, ROWS = S::ROWS, PPL = S::PPL, NPL = S::NPL;
+  constexpr int NQ = ROWS * SEG / kT > 0 ? ROWS * SEG / kT : 1;  // 16-byte loads per thread for a unit's queries
+  constexpr int G4 = NV / 4;
+  extern __shared__ u32x4 smem[];
+  u32x4* s_q = smem + S::P_SLOTS;
+  float* s_m = reinterpret_cast<float*>(s_q + S::Q_SLOTS);  // [2][kW][ROWS] references by wave, of this item and the next
+  float* s_z = s_m + 2 * kW * ROWS;                         // [kW][ROWS] sums of this item
+  float* s_w = s_z + kW * ROWS;                             // [kW][ROWS] references, then weights of the pending item
+  float2* s_f = reinterpret_cast<float2*>(s_w + kW * ROWS); // [kW][ROWS] statistics of its unit, by wave
+  int* s_t = reinterpret_cast<int*>(s_f + kW * ROWS);       // [ROWS] window position of a row
+  int* s_off = s_t + ROWS;                                  // [ROWS] byte offset of a row of Q
+  uint2* s_item = reinterpret_cast<uint2*>(s_off + ROWS);   // [kStreamItems] (unit, part << 20 | keys)
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int BH = a.B * a.Hkv;
+
+  // ---- the items of this workgroup ----
+  int nmine;
+  {
+    int* pre = reinterpret_cast<int*>(smem);  // [E + 1] items before (layer, sequence) e
+    const int E = a.L * a.B;
+    int* wsum = pre + kStreamUnits + 1;
+    int run = 0;
+    for (int e0 = 0; e0 < E; e0 += kT) {
+      const int e = e0 + tid;
+      int c = 0;
+      if (e < E) {
+        const int l = e / a.B, b = e - l * a.B;
+        int n = a.N;
+        if (a.seq_lens) {
+          n = a.seq_lens[b];
+          n = n < 0 ? 0 : (n > a.N ? a.N : n);
+        }
+        c = a.layer[l].k_l < n ? a.Hkv * ((n + KI - 1) / KI) : 0;  // (whole sequence kept: no scores needed)
+      }
+      int v = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(v, o);
+        if (lane >= o) v += x;
+      }
+      __syncthreads();
+      if (lane == 63) wsum[wave] = v;
+      __syncthreads();
+      int before = run;
+#pragma unroll
+      for (int w = 0; w < kW; ++w) {
+        before += w < wave ? wsum[w] : 0;
+        run += wsum[w];
+      }
+      if (e < E) pre[e] = before + v - c;
+    }
+    if (tid == 0) pre[E] = run;
+    __syncthreads();
+    nmine = run > (int)blockIdx.x ? (run - (int)blockIdx.x + kStreamGrid - 1) / kStreamGrid : 0;
+    nmine = min(nmine, kStreamItems);  // (the host admits only launches that fit)
+    for (int k = tid; k < nmine; k += kT) {
+      const int j = k * kStreamGrid + (int)blockIdx.x;
+      int lo = 0, hi = E;  // pre[lo] <= j < pre[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pre[mid] <= j) lo = mid;
+        else hi = mid;
+      }
+      const int rem = j - pre[lo], parts = (pre[lo + 1] - pre[lo]) / a.Hkv;
+      const int g = rem / parts, part = rem - g * parts, b = lo % a.B;
+      int n = a.N;
+      if (a.seq_lens) {
+        n = a.seq_lens[b];
+        n = n < 0 ? 0 : (n > a.N ? a.N : n);
+      }
+      s_item[k] = make_uint2((uint32_t)(lo * a.Hkv + g), (uint32_t)part << 20 | (uint32_t)n);
+    }
+    if (tid < ROWS) {
+      const int r = min(tid, a.R - 1);  // (rows behind the last repeat it; their weights are zero)
+      const int hh = r / a.alpha, t = r - hh * a.alpha;
+      s_t[tid] = t;
+      s_off[tid] = (int)(hh * a.q_sh + t * a.q_st) * 2;
+    }
+    __syncthreads();
+  }
+  if (nmine == 0) return;
+
+  // One item as this workgroup sees it (all fields wave-uniform).
+  struct Item {
+    int u, part, n, start;
+    const uint16_t* Q;
+    const uint16_t* K;
+  };
+  auto item = [&](int i) {
+    const uint2 e = s_item[i];
+    Item d;
+    d.u = __builtin_amdgcn_readfirstlane((int)e.x);
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.y);
+    d.part = (int)(w >> 20);
+    d.n = (int)(w & 0xFFFFFu);
+    d.start = i * kStreamGrid + (int)blockIdx.x - d.part;  // the unit's first item
+    const int l = d.u / BH, bg = d.u - l * BH;
+    const int b = bg / a.Hkv, g = bg - b * a.Hkv;
+    d.Q = a.layer[l].Q + (size_t)b * a.q_sb + (size_t)(g * a.G) * a.q_sh;
+    d.K = a.layer[l].K + (size_t)b * a.kv_sb + (size_t)g * a.kv_sh;
+    return d;
+  };
+  auto tile_key = [&](const Item& d, int t) { return d.part * KI + (t * kW + wave) * 32; };
+  auto nparts = [&](const Item& d) { return (d.n + KI - 1) / KI; };
+
+  // Keys of the wave's tile t as matrix operand: lane (column l32, half hf) holds elements 16 ks + 8 hf of its key.
+  // Keys at or beyond n are replaced by the last one.
+  bf16x8 kf[KB][KS];
+  auto issue_k = [&](const Item& d, int t, bf16x8 (&f)[KS]) {
+    const int ln = fresh(lane);
+    const int key = min(tile_key(d, t) + (ln & 31), d.n - 1);
+    const char* rowp = reinterpret_cast<const char*>(d.K) + 16 * (ln >> 5) + (uint32_t)key * ((uint32_t)a.kv_st * 2u);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) f[ks] = as_frag(*reinterpret_cast<const u32x4*>(rowp + 32 * ks));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // A unit's queries and its key 0: requested into registers, written to LDS later.  The lanes that carry a row of Q
+  // carry the same segments of the key, so the row's logit of key 0, the reference, comes from them on the way.
+  u32x4 qv[NQ], kv0;
+  auto request_q = [&](const Item& d) {
+    const int td = fresh(tid);
+    kv0 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(d.K) + 16 * (td & (SEG - 1)));
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int c = td + kT * i, row = c / SEG, seg = c - row * SEG;
+      qv[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(d.Q) + seg * 16 + (uint32_t)s_off[min(row, ROWS - 1)]);
+    }
+  };
+  auto commit_q = [&](int mbuf) {
+    const int td = fresh(tid);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int c = td + kT * i, row = c / SEG, seg = c - row * SEG;
+      if (row < ROWS) s_q[row * PITCH + seg] = qv[i];
+      float dot = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        dot = __builtin_fmaf(__uint_as_float(qv[i][e] << 16), __uint_as_float(kv0[e] << 16), dot);
+        dot = __builtin_fmaf(__uint_as_float(qv[i][e] & 0xFFFF0000u), __uint_as_float(kv0[e] & 0xFFFF0000u), dot);
+      }
+      // over the row's 16 or 8 lanes, in all of them
+#define PKV_ADD(ctrl) dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), ctrl, 0xF, 0xF, true))
+      PKV_ADD(0xB1);                 // quad_perm 1,0,3,2
+      PKV_ADD(0x4E);                 // quad_perm 2,3,0,1
+      PKV_ADD(0x141);                // row_half_mirror: the other quad of 8 lanes
+      if (SEG == 16) PKV_ADD(0x140); // row_mirror: the other half of 16 lanes
+#undef PKV_ADD
+      if (row < ROWS && seg < kW) s_m[(mbuf * kW + seg) * ROWS + row] = dot * a.kappa;  // (one table per wave)
+    }
+  };
+  const u32x4* q_lane = s_q + l32 * PITCH + hf;
+  auto product = [&](const bf16x8 (&f)[KS], int rt) {
+    f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(q_lane[32 * rt * PITCH + 2 * ks]), f[ks], acc, 0, 0, 0);
+    return acc;
+  };
+
+  auto waited_too_long = [&](int& spins, long long& t0) -> bool {
+    if (a.wait_ticks == 0) return true;
+    if (spins++ == 0) {
+      t0 = wall_clock64();
+      return false;
+    }
+    if ((spins & 15) != 0) return false;
+    return wall_clock64() - t0 > (long long)a.wait_ticks ||
+           __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+  };
+  // statistics word of row r of item j, and the phase bit it carries
+  auto stat_word = [&](int j, int r) {
+    return a.stats + ((size_t)(j % kStreamGrid) * a.ring + ((j / kStreamGrid) & (a.ring - 1))) * ROWS + r;
+  };
+  auto stat_phase = [&](int j) { return ((uint32_t)(j / kStreamGrid) / (uint32_t)a.ring & 1u) ^ 1u; };
+
+  // Statistics of the items of a unit: thread = (row, every PPL-th item).
+  u64 sv[NPL];
+  auto request_stats = [&](const Item& d, int np) {
+    const int ln = fresh(lane);
+    const int srow = min(ln & (ROWS - 1), a.R - 1), sitem = wave * (64 / ROWS) + ln / ROWS;
+#pragma unroll
+    for (int k = 0; k < NPL; ++k) sv[k] = ld64(stat_word(d.start + min(sitem + k * PPL, np - 1), srow));
+  };
+  // ... folded over the thread's items (those not there yet are waited for) and left in LDS
+  auto fold_stats = [&](const Item& d, int np) {
+    const int ln = fresh(lane);
+    const int srow = min(ln & (ROWS - 1), a.R - 1), sitem = wave * (64 / ROWS) + ln / ROWS;
+    float m = -INFINITY, z = 0.f;
+    auto arrived = [&](int q, u64 w) -> u64 {
+      const uint32_t phase = stat_phase(d.start + q);
+      if ((uint32_t)(w >> 63) != phase) {
+        int spins = 0;
+        long long t0 = 0;
+        for (;;) {
+          w = ld64(stat_word(d.start + q, srow));
+          if ((uint32_t)(w >> 63) == phase) break;
+          __builtin_amdgcn_s_sleep(1);
+          if (waited_too_long(spins, t0)) {
+            __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+          }
+        }
+      }
+      return w;
+    };
+    // (the largest reference first, so that the exponentials do not wait for each other)
+#pragma unroll
+    for (int k = 0; k < NPL; ++k)
+      if (sitem + k * PPL < np) {
+        sv[k] = arrived(sitem + k * PPL, sv[k]);
+        m = fmaxf(m, __uint_as_float((uint32_t)sv[k]));
+      }
+    const float ms = (m == -INFINITY) ? 0.f : m;
+#pragma unroll
+    for (int k = 0; k < NPL; ++k)
+      if (sitem + k * PPL < np)
+        z = __builtin_fmaf(__uint_as_float((uint32_t)(sv[k] >> 32) & 0x7FFFFFFFu), fast_exp2(__uint_as_float((uint32_t)sv[k]) - ms), z);
+    for (int q = sitem + NPL * PPL; q < np; q += PPL) {
+      const u64 w = arrived(q, ld64(stat_word(d.start + q, srow)));
+      merge_stats(m, z, __uint_as_float((uint32_t)w), __uint_as_float((uint32_t)(w >> 32) & 0x7FFFFFFFu));
+    }
+    if (ROWS == 32) {
+      const float m2 = __shfl_xor(m, 32), z2 = __shfl_xor(z, 32);
+      merge_stats(m, z, m2, z2);
+    }
+    if (ln < ROWS) s_f[wave * ROWS + ln] = make_float2(m, z);
+  };
+
+  float* dump = a.dump + blockIdx.x * 64;
+
+  // Pending item (the one before): its p in LDS, waiting for normalisers.
+  Item pend;
+  pend.u = -1;
+  pend.part = 0; pend.n = 1; pend.start = 0; pend.Q = nullptr; pend.K = nullptr;
+  u32x4* p_wave = smem + (size_t)wave * (TPW * RT * G4 * 64);  // slot [t][rt][v / 4][lane]
+  // Scores of the pending item: weights exp2(m - c) / G per row, p weighted and summed over the rows.
+  auto finish = [&](const Item& d) {
+    const int lane = fresh(tid & 63), l32 = lane & 31, hf = lane >> 5;
+    const u32x4* p_lane = p_wave + lane;
+    if (lane < ROWS) {
+      float2 f[kW];
+      float mu = -INFINITY, zu = 0.f;
+#pragma unroll
+      for (int w = 0; w < kW; ++w) {
+        f[w] = s_f[w * ROWS + lane];
+        mu = fmaxf(mu, f[w].x);
+      }
+#pragma unroll
+      for (int w = 0; w < kW; ++w) zu = __builtin_fmaf(f[w].y, fast_exp2(f[w].x - mu), zu);
+      const float c = mu + fast_log2(zu);
+      const float m = s_w[wave * ROWS + lane];
+      s_w[wave * ROWS + lane] = lane < a.R ? fast_exp2(m - c) * a.inv_G : 0.f;
+    }
+    wave_lds_fence();
+    f32x4 w[RT][G4];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int q = 0; q < G4; ++q) w[rt][q] = *reinterpret_cast<const f32x4*>(s_w + wave * ROWS + 32 * rt + 8 * q + 4 * hf);
+    float* raw = a.raw + (size_t)d.u * a.N;
+    const int npre = d.n - a.alpha;
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int q = 0; q < G4; ++q) {
+          const f32x4 p = __builtin_bit_cast(f32x4, p_lane[((t * RT + rt) * G4 + q) * 64]);
+          s0 = __builtin_fmaf(p[0], w[rt][q][0], s0);
+          s1 = __builtin_fmaf(p[1], w[rt][q][1], s1);
+          s0 = __builtin_fmaf(p[2], w[rt][q][2], s0);
+          s1 = __builtin_fmaf(p[3], w[rt][q][3], s1);
+        }
+      const float s = both_halves(s0 + s1);
+      const int key = tile_key(d, t) + l32;
+      // (lanes without a score write to a spare line: a store under a condition would make the waits for keys that
+      // follow allow for either way in)
+      float* dst = (hf == 0 && key < npre) ? raw + key : dump + lane;
+      *dst = s;
+    }
+  };
+
+  Item cur = item(0);
+  request_q(cur);
+  commit_q(0);
+#pragma unroll
+  for (int t = 0; t < KB; ++t) issue_k(cur, t, kf[t]);
+  lds_barrier();
+
+  for (int i = 0; i < nmine; ++i) {
+    const Item nxt = item(i + 1 < nmine ? i + 1 : i);  // (behind the last item its own keys are fetched once more)
+    const int np_pend = nparts(pend);
+    const int npre = cur.n - a.alpha;
+    const int mbuf = i & 1;
+    float* m_tab = s_m + (mbuf * kW + wave) * ROWS;
+    f32x4 p[TPW][RT][G4];
+    // the row tile's references, from the wave's table in LDS (two row tiles' would not fit the registers)
+    auto load_m = [&](int rt, f32x4 (&m)[G4]) {
+#pragma unroll
+      for (int q = 0; q < G4; ++q) m[q] = *reinterpret_cast<const f32x4*>(m_tab + 32 * rt + 8 * q + 4 * hf);
+    };
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      const int key0 = tile_key(cur, t);
+      const bool masked = key0 + 32 > npre;         // the tile reaches into the causal window or beyond the end
+      f32x16 acc[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = product(kf[t % KB], rt);
+      // (these come before the keys requested here: loads return in order, and waits under conditions stay exact)
+      if (t == 0) request_q(nxt);
+      if (t == TPW - 2) request_stats(pend, np_pend);
+      if (t + KB < TPW) issue_k(cur, t + KB, kf[t % KB]);
+      else if (t < TPW - 1) issue_k(nxt, t + KB - TPW, kf[t % KB]);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        f32x4 m[G4];
+        load_m(rt, m);
+#pragma unroll
+        for (int q = 0; q < G4; ++q)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) p[t][rt][q][c] = fast_exp2(__builtin_fmaf(acc[rt][4 * q + c], a.kappa, -m[q][c]));
+      }
+      if (masked) {  // keys the row's query does not see
+        const int over = key0 + l32 - npre;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int q = 0; q < G4; ++q) {
+            const i32x4 tt = *reinterpret_cast<const i32x4*>(s_t + 32 * rt + 8 * q + 4 * hf);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) p[t][rt][q][c] = over > tt[c] ? 0.f : p[t][rt][q][c];
+          }
+      }
+    }
+    // ---- the item's statistics ----
+    f32x4 z[RT][G4];
+    auto sum_up = [&]() -> uint32_t {  // rows (bit 16 rt + 4 q + c, in the last lane of a half) whose reference does not fit
+      uint32_t bad = 0u;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int q = 0; q < G4; ++q) {
+          z[rt][q] = p[0][rt][q];
+#pragma unroll
+          for (int t = 1; t < TPW; ++t) z[rt][q] += p[t][rt][q];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            z[rt][q][c] = half_reduce<false>(z[rt][q][c]);
+            // (keys far below the reference vanish, as they should: key 0 alone contributes 1 to the unit's sum)
+            bad |= (l32 == 31 && !(z[rt][q][c] <= 0x1p100f)) ? 1u << (16 * rt + 4 * q + c) : 0u;
+          }
+        }
+      return bad;
+    };
+    const uint32_t bad = sum_up();
+    if (__any(bad != 0u) && tile_key(cur, 0) < cur.n) {
+      // rare: a reference that does not fit: for such a row the exact maximum over the wave's keys, then p once more
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        f32x4 mx[G4];
+#pragma unroll
+        for (int q = 0; q < G4; ++q) mx[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        for (int pass = 0; pass < 2; ++pass) {
+          f32x4 m[G4];
+          load_m(rt, m);
+#pragma unroll
+          for (int t = 0; t < TPW; ++t) {
+            bf16x8 f[KS];
+            issue_k(cur, t, f);
+            const f32x16 acc = product(f, rt);
+            const int over = tile_key(cur, t) + l32 - npre;
+#pragma unroll
+            for (int q = 0; q < G4; ++q) {
+              const i32x4 tt = *reinterpret_cast<const i32x4*>(s_t + 32 * rt + 8 * q + 4 * hf);
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                const float y = acc[4 * q + c];
+                if (pass == 0) mx[q][c] = fmaxf(mx[q][c], over > tt[c] ? -INFINITY : y * a.kappa);
+                else p[t][rt][q][c] = over > tt[c] ? 0.f : fast_exp2(__builtin_fmaf(y, a.kappa, -m[q][c]));
+              }
+            }
+          }
+          if (pass == 0) {
+#pragma unroll
+            for (int q = 0; q < G4; ++q)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                const float x = half_reduce<true>(mx[q][c]);
+                if (l32 == 31 && (bad >> (16 * rt + 4 * q + c) & 1u)) m_tab[32 * rt + 8 * q + 4 * hf + c] = x;
+              }
+            wave_lds_fence();
+          }
+        }
+      }
+      (void)sum_up();
+    }
+    if (pend.u >= 0) fold_stats(pend, np_pend);
+    if (l32 == 31) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int q = 0; q < G4; ++q) *reinterpret_cast<f32x4*>(s_z + wave * ROWS + 32 * rt + 8 * q + 4 * hf) = z[rt][q];
+    }
+    lds_barrier();  // every wave is done with this unit's queries; the waves' statistics are there
+    if (tid < ROWS) {
+      float mm = -INFINITY, zz = 0.f;
+#pragma unroll
+      for (int w = 0; w < kW; ++w) mm = fmaxf(mm, s_m[(mbuf * kW + w) * ROWS + tid]);
+#pragma unroll
+      for (int w = 0; w < kW; ++w)
+        zz = __builtin_fmaf(s_z[w * ROWS + tid], fast_exp2(s_m[(mbuf * kW + w) * ROWS + tid] - mm), zz);
+      const int j = cur.start + cur.part;
+      st64(stat_word(j, tid), ((u64)((__float_as_uint(zz) & 0x7FFFFFFFu) | (stat_phase(j) << 31)) << 32) | __float_as_uint(mm));
+    }
+    commit_q(mbuf ^ 1);
+    issue_k(nxt, KB - 1, kf[(TPW - 1) % KB]);  // (behind the statistics, which others wait for)
+    // ---- the item before ----
+    if (pend.u >= 0) finish(pend);
+    if (lane < ROWS) s_w[wave * ROWS + lane] = m_tab[lane];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int q = 0; q < G4; ++q) p_wave[((t * RT + rt) * G4 + q) * 64 + lane] = __builtin_bit_cast(u32x4, p[t][rt][q]);
+    pend = cur;
+    cur = nxt;
+    lds_barrier();  // the next unit's queries are in place
+  }
+  request_stats(pend, nparts(pend));
+  fold_stats(pend, nparts(pend));
+  lds_barrier();
+  finish(pend);
+}
+
+// Clears n 16-byte slots at p and the error word.
+__global__ __launch_bounds__(256) void clear_kernel(u32x4* p, int n, int32_t* err) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = u32x4{0u, 0u, 0u, 0u};
+  if (err && i < 2) err[i] = 0;
+}
+
+template <int D, int NV, int RT>
+hipError_t launch_stream(const StreamArgs& a, hipStream_t s) {
+  using S = StreamShape<D, NV, RT>;
+  static bool attr_set[kMaxDevices];
+  const int dev = current_device_slot();
+  if (dev < 0) return hipErrorInvalidDevice;
+  if (!attr_set[dev]) {  // raise the dynamic LDS limit once per device (idempotent; no allocation)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_stream_kernel<D, NV, RT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
+    if (e != hipSuccess) return e;
+    attr_set[dev] = true;
+  }
+  hipLaunchKernelGGL((score_stream_kernel<D, NV, RT>), dim3(a.grid), dim3(kT), S::LDS, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int stream_item_keys(int R) { return R <= 32 ? 1024 : 512; }
+
+hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s) {
+  const int n16 = a.grid * a.ring * (a.R <= 32 ? 32 : 64) / 2;  // 64-bit words, two per slot
+  hipLaunchKernelGGL(clear_kernel, dim3((n16 + 255) / 256), dim3(256), 0, s, reinterpret_cast<u32x4*>(a.stats), n16,
+                     clear_err ? a.err : nullptr);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+#define PKV_CASE(DD)                                            \
+  if (a.d == DD) {                                              \
+    if (a.R <= 8) return launch_stream<DD, 4, 1>(a, s);         \
+    if (a.R <= 16) return launch_stream<DD, 8, 1>(a, s);        \
+    if (a.R <= 32) return launch_stream<DD, 16, 1>(a, s);       \
+    if (a.R <= 64) return launch_stream<DD, 16, 2>(a, s);       \
+  }
+  PKV_CASE(128) PKV_CASE(64)
+#undef PKV_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace pkv

@@ -1,0 +1,92 @@
+"""One-pass scoring for few query rows (G * alpha <= 64) at the edges of its work split: rows around the register groups,
+lengths around the keys of an item, ragged batches whose sequences contribute unequal numbers of items, more items than
+a workgroup keeps statistics of, more sequences than one launch's table holds, references that do not fit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_02069_amd import binding, synth
+from tests.parity import compare_layer
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(B, Hq, Hkv, d, N, alpha, seed, scale=1.0):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    Q = (torch.randn(B, Hq, alpha, d, generator=g, device=DEV) * scale).to(torch.bfloat16)
+    K = torch.randn(B, Hkv, N, d, generator=g, device=DEV).to(torch.bfloat16)
+    V = torch.randn(B, Hkv, N, d, generator=g, device=DEV).to(torch.bfloat16)
+    return Q, K, V
+
+
+def _check(Q, K, V, k_l, lens=None, pool=synth.POOL_MAX, pw=7):
+    print("stream", tuple(Q.shape), tuple(K.shape), k_l, None if lens is None else lens.tolist()[:8], flush=True)
+    ld = None if lens is None else torch.from_numpy(lens).to(DEV)
+    out = binding.compress_layer(Q, K, V, k_l, pool, pw, seq_lens=ld, want_scores=True)
+    torch.cuda.synchronize()
+    return compare_layer(Q, K, V, k_l, Q.shape[2], pool, pw, lens, out)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,alpha", [(1, 1), (1, 5), (1, 8), (3, 3), (2, 8), (1, 17), (4, 8), (1, 33), (6, 8), (8, 8)])
+def test_rows(d, G, alpha):
+    Q, K, V = _inputs(1, 2 * G, 2, d, 2600, alpha, seed=G * 100 + alpha + d)
+    _check(Q, K, V, alpha + 60)
+
+
+@pytest.mark.parametrize("N", [9, 32, 33, 255, 511, 512, 513, 520, 1023, 1024, 1025, 1032, 2048, 2049, 4100])
+@pytest.mark.parametrize("G", [1, 8])
+def test_lengths_around_an_item(N, G):
+    alpha = 8
+    Q, K, V = _inputs(1, G, 1, 128, N, alpha, seed=N + G)
+    _check(Q, K, V, min(alpha + 40, N - 1))
+
+
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_ragged_batch(G):
+    alpha, N = 8, 5000
+    lens = np.array([5000, 0, 7, 8, 9, 40, 1032, 1033, 4097, 513], dtype=np.int32)
+    Q, K, V = _inputs(len(lens), 2 * G, 2, 128, N, alpha, seed=G)
+    for b, n in enumerate(lens):
+        K[b, :, n:] = float("nan")
+    _check(Q, K, V, 40, lens)
+
+
+def test_more_items_than_the_statistics_ring_holds():
+    # 40 layers x 16 heads x 4 items = 2560 items: ten per workgroup; equal to one call per layer, bit for bit
+    L, alpha, N = 40, 8, 4000
+    data = [_inputs(2, 8, 8, 64, N, alpha, seed=500 + l) for l in range(L)]
+    lens = torch.tensor([4000, 3100], dtype=torch.int32, device=DEV)
+    ks = [alpha + 3 + 5 * l for l in range(L)]
+    outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_MAX, 7,
+                                   seq_lens=lens, want_scores=True)
+    torch.cuda.synchronize()
+    for l in range(L):
+        one = binding.compress_layer(*data[l], ks[l], synth.POOL_MAX, 7, seq_lens=lens, want_scores=True)
+        torch.cuda.synchronize()
+        for x, y in zip(outs[l], one):
+            assert torch.equal(x, y), l
+
+
+def test_more_sequences_than_one_launch_holds():
+    L, B, alpha, N = 3, 1100, 4, 96                          # 2048 (layer, sequence) pairs per launch
+    data = [_inputs(B, 1, 1, 64, N, alpha, seed=40 + l) for l in range(L)]
+    lens = np.random.RandomState(3).randint(0, N + 1, size=B).astype(np.int32)
+    outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], [20, 12, 7],
+                                   synth.POOL_AVG, 3, seq_lens=torch.from_numpy(lens).to(DEV), want_scores=True)
+    torch.cuda.synchronize()
+    for l, k_l in enumerate((20, 12, 7)):
+        compare_layer(*data[l], k_l, alpha, synth.POOL_AVG, 3, lens, outs[l])
+
+
+@pytest.mark.parametrize("G", [2, 8])
+def test_references_that_do_not_fit(G):
+    # the first key of a wave's tiles lies hundreds of binades below a later one: its rows are recomputed
+    alpha, N = 8, 3000
+    Q, K, V = _inputs(1, G, 1, 128, N, alpha, seed=G, scale=0.5)
+    K[0, 0, 700] = 40 * Q[0, 0, 3]
+    K[0, 0, 0:2500:32] = -20 * Q[0, 0, 3]
+    out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
