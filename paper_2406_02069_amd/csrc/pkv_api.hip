@@ -228,6 +228,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         sa.layer[i].Q = static_cast<const uint16_t*>(ptrs[l0 + i].Q);
         sa.layer[i].K = static_cast<const uint16_t*>(ptrs[l0 + i].K);
         sa.layer[i].k_l = descs[l0 + i].k_l;
+        sa.uniform = (i == 0 || sa.uniform) && !seq_lens && descs[l0 + i].k_l < d.N ? 1 : 0;
       }
       const int64_t rows = plan.R <= 32 ? 32 : 64;
       sa.seq_lens = seq_lens;

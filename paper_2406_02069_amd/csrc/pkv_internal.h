@@ -115,6 +115,7 @@ struct StreamArgs {
   float* dump;                // [grid][64] written, never read
   int32_t* err;
   int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
+  int32_t uniform;            // 1: every unit has N keys and none is kept whole
   int32_t grid, ring;         // workgroups (kStreamGrid, fewer if there are fewer items); statistics kept per workgroup
   int32_t wait_ticks;
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;

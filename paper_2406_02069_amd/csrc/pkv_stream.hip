@@ -147,7 +147,21 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 
   // ---- the items of this workgroup ----
   int nmine;
-  {
+  if (tid < ROWS) {
+    const int r = min(tid, a.R - 1);  // (rows behind the last repeat it; their weights are zero)
+    const int hh = r / a.alpha, t = r - hh * a.alpha;
+    s_t[tid] = t;
+    s_off[tid] = (int)(hh * a.q_sh + t * a.q_st) * 2;
+  }
+  if (a.uniform) {  // every unit has N keys to score
+    const int parts = (a.N + KI - 1) / KI, total = a.L * BH * parts;
+    nmine = min((total - (int)blockIdx.x + kStreamGrid - 1) / kStreamGrid, kStreamItems);
+    if (tid < nmine) {
+      const int j = tid * kStreamGrid + (int)blockIdx.x, u = j / parts;
+      s_item[tid] = make_uint2((uint32_t)u, (uint32_t)(j - u * parts) << 20 | (uint32_t)a.N);
+    }
+    __syncthreads();
+  } else {
     int* pre = reinterpret_cast<int*>(smem);  // [E + 1] items before (layer, sequence) e
     const int E = a.L * a.B;
     int* wsum = pre + kStreamUnits + 1;
@@ -201,12 +215,6 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
         n = n < 0 ? 0 : (n > a.N ? a.N : n);
       }
       s_item[k] = make_uint2((uint32_t)(lo * a.Hkv + g), (uint32_t)part << 20 | (uint32_t)n);
-    }
-    if (tid < ROWS) {
-      const int r = min(tid, a.R - 1);  // (rows behind the last repeat it; their weights are zero)
-      const int hh = r / a.alpha, t = r - hh * a.alpha;
-      s_t[tid] = t;
-      s_off[tid] = (int)(hh * a.q_sh + t * a.q_st) * 2;
     }
     __syncthreads();
   }
@@ -415,13 +423,17 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 
   Item cur = item(0);
   request_q(cur);
-  commit_q(0);
 #pragma unroll
   for (int t = 0; t < KB; ++t) issue_k(cur, t, kf[t]);
+  commit_q(0);
   lds_barrier();
 
   for (int i = 0; i < nmine; ++i) {
-    const Item nxt = item(i + 1 < nmine ? i + 1 : i);  // (behind the last item its own keys are fetched once more)
+    Item nxt = item(i + 1 < nmine ? i + 1 : i);
+    if (i + 1 == nmine) {  // behind the last item: the requests go to the unit's key 0 alone, in the caches
+      nxt.part = 0;
+      nxt.n = 1;
+    }
     const int np_pend = nparts(pend);
     const int npre = cur.n - a.alpha;
     const int mbuf = i & 1;
