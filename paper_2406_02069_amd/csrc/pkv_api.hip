@@ -201,6 +201,38 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
   return p;
 }
 
+// How the two-launch kernel for many query rows serves a call: keys per chunk (0: it does not) and chunks per unit, from
+// one layer's shape alone.  A layer has about one chunk per workgroup.  (The statistics lie in the part of the workspace
+// that holds the pooled scores later on.)
+// Where the lines lie, against the resident kernel, whole calls (7 us and more of each gain are the selection's):
+//   80 layers of 8 heads x 32k keys, 512 rows 6439 -> 5542 us; 32 layers of 32k, 256 rows 1389 -> 1346, of 4k, 512 rows
+//   413 -> 313; one layer of 8k, 256 rows 58 -> 40.  At 128 rows K is read twice for nothing: 32 layers of 32k keys 801
+//   -> 908 us, of 128k 3371 -> 3551.  Few chunks leave compute units idle: one layer of 32 chunks 89.6 -> 76.5 us (8 x 4k
+//   keys, 512 rows) and 78.6 -> 71.3 (4 x 8k, 448 rows), which is even without the selection's share.
+// With supplied denominators there is one launch and nothing to read twice: 32 layers of 24k keys, 256 rows 570 -> 501 us,
+//   128 rows 394 -> 363, 64 rows 349 -> 340, 32 rows 345 -> 353; 8 layers of 32 heads x 32k, 8 rows 434 -> 461; one layer
+//   of 24k, 128 rows 54.5 -> 29.0.
+constexpr int kSweepMinRows = 129;
+constexpr int kSweepMinRowsLse = 33;
+constexpr int kSweepMinChunks = 32;
+struct SweepPlan {
+  int C, nchunk, Rs;
+};
+static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
+  SweepPlan p = {0, 0, 0};
+  if (plan.R < (lse_mode ? kSweepMinRowsLse : kSweepMinRows) || !plan.resident_ok) return p;
+  if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
+  p.Rs = (plan.R + 31) / 32 * 32;
+  const int64_t keys = ((int64_t)plan.BH * d.N + kSweepGrid - 1) / kSweepGrid;
+  const int64_t want = keys > 2 * p.Rs || lse_mode ? keys : 2 * p.Rs;  // (8 bytes per row and chunk in 4 bytes per key)
+  const int64_t C = (want + 511) / 512 * 512;
+  const int64_t nchunk = (d.N + C - 1) / C;
+  if (!lse_mode && (nchunk * plan.BH < kSweepMinChunks || nchunk * p.Rs * 8 > (int64_t)d.N * 4)) return p;
+  p.C = (int)C;
+  p.nchunk = (int)nchunk;
+  return p;
+}
+
 // Queue the kernels of L layers.  All arguments have been validated.
 static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, const LayerPtrs* ptrs,
                       const int32_t* seq_lens, void* workspace, hipStream_t stream, Recorder* rec,
@@ -218,8 +250,38 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
   StreamPlan sp = {0, 0, 0};
+  SweepPlan wp = {0, 0, 0};
   if (any_scores && resident) sp = stream_plan(plan, d, lse_mode);
-  if (sp.layers > 0) {
+  if (any_scores && resident) wp = sweep_plan(plan, d, lse_mode);
+  if (wp.C > 0) {
+    for (int32_t l0 = 0; l0 < L; l0 += kResidentMaxLayers) {
+      const int32_t nl = L - l0 < kResidentMaxLayers ? L - l0 : kResidentMaxLayers;
+      SweepArgs wa;
+      memset(&wa, 0, sizeof(wa));
+      for (int32_t i = 0; i < nl; ++i) {
+        wa.layer[i].Q = static_cast<const uint16_t*>(ptrs[l0 + i].Q);
+        wa.layer[i].K = static_cast<const uint16_t*>(ptrs[l0 + i].K);
+        wa.layer[i].lse = ptrs[l0 + i].lse;
+        wa.layer[i].k_l = descs[l0 + i].k_l;
+        wa.uniform = (i == 0 || wa.uniform) && !seq_lens && descs[l0 + i].k_l < d.N ? 1 : 0;
+      }
+      wa.seq_lens = seq_lens;
+      wa.raw = raw + (size_t)l0 * plan.BH * d.N;
+      wa.stats = reinterpret_cast<unsigned long long*>(pooled_ws);
+      wa.L = nl; wa.B = d.B; wa.Hq = d.Hq; wa.Hkv = d.Hkv; wa.G = plan.G; wa.alpha = d.alpha; wa.N = d.N;
+      wa.R = plan.R; wa.Rs = wp.Rs; wa.d = d.d; wa.C = wp.C; wa.nchunk = wp.nchunk;
+      const int64_t chunks = (int64_t)nl * plan.BH * wp.nchunk;
+      wa.grid = chunks < kSweepGrid ? (int32_t)chunks : kSweepGrid;
+      wa.lse_mode = lse_mode ? 1 : 0;
+      wa.q_sb = d.q_sb; wa.q_sh = d.q_sh; wa.q_st = d.q_st;
+      wa.kv_sb = d.kv_sb; wa.kv_sh = d.kv_sh; wa.kv_st = d.kv_st;
+      wa.kappa = kappa;
+      wa.inv_kappa = 1.0f / kappa;
+      wa.inv_G = 1.0f / (float)plan.G;
+      if (launch_score_sweep(wa, stream) != hipSuccess) return PKV_ERR_HIP;
+      if (rec) rec->after(PKV_KERNEL_SCORE_RESIDENT, stream);
+    }
+  } else if (sp.layers > 0) {
     for (int32_t l0 = 0; l0 < L; l0 += sp.layers) {
       const int32_t nl = L - l0 < sp.layers ? L - l0 : sp.layers;
       StreamArgs sa;
@@ -360,8 +422,8 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
     se.pool_w = d.pool_w;
     se.nrb = nrb;
     se.inv_G = resident ? 1.0f : 1.0f / (float)plan.G;
-    // the error word of this call's scoring launches
-    se.err = (any_scores && resident) ? reinterpret_cast<const int32_t*>(ws + plan.off_cnt) : nullptr;
+    // the error word of this call's scoring launches (the two-launch kernel waits for nobody and has none)
+    se.err = (any_scores && resident && wp.C == 0) ? reinterpret_cast<const int32_t*>(ws + plan.off_cnt) : nullptr;
     ga.L = nl; ga.B = d.B; ga.Hkv = d.Hkv; ga.d = d.d; ga.k_cap_max = k_cap_max; ga.N = d.N;
     ga.kv_sb = d.kv_sb; ga.kv_sh = d.kv_sh; ga.kv_st = d.kv_st;
     if (paged) {

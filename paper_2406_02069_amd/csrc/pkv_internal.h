@@ -125,6 +125,24 @@ int stream_item_keys(int R);
 // clear_err: the first launch of a call also clears the error word
 hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s);
 
+// ---- scoring in two streaming launches for many query rows, over many layers (pkv_sweep.hip) ----
+constexpr int kSweepGrid = 256;     // workgroups, one per compute unit
+
+struct SweepArgs {
+  ResidentLayer layer[kResidentMaxLayers];
+  const int32_t* seq_lens;
+  float* raw;                 // [U][N] un-pooled scores
+  unsigned long long* stats;  // [U][nchunk][Rs] (reference, sum) of a row over a chunk (log2 domain)
+  int32_t L, B, Hq, Hkv, G, alpha, N, R, Rs, d;  // Rs: rows padded to 32
+  int32_t C, nchunk;          // keys per chunk (a multiple of 512), chunks per unit
+  int32_t uniform;            // 1: every unit has N keys and none is kept whole
+  int32_t grid;
+  int32_t lse_mode;           // 1: every layer carries lse; no statistics
+  int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
+  float kappa, inv_kappa, inv_G;
+};
+hipError_t launch_score_sweep(const SweepArgs& a, hipStream_t s);
+
 // ---- pooling + selection and gather over many layers ----
 constexpr int kBatchMaxLayers = 32;  // per launch (kernel-argument tables: selection + gather together < 4 KB)
 

@@ -1,0 +1,550 @@
+// Window scoring in two streaming launches over K for many query rows per KV head (G * alpha > 128; Sec. 4.2.2, Eq. Al
+// and Eq. att_score) on MI355X; with supplied softmax denominators in one launch (G * alpha > 32).
+//
+// With many query rows the scoring is bound by its products and exponentials and not by the bandwidth of K, so that
+// reading K a second time is free, and what costs is everything that keeps the SIMDs from multiplying: waits for other
+// workgroups and staging of Q.  Here there is neither: one launch forms the softmax statistics, the next one the scores,
+// and no workgroup waits for another.  One workgroup of 512 threads per compute unit keeps ALL query rows of its unit
+// (layer, sequence, KV head) in LDS (512 rows of 128 elements: 136 of 160 KB) and streams keys past them, two waves per
+// SIMD that drift apart freely.
+//
+// Work split.  Units are cut into chunks of C keys (from one layer's shape, so that a call over many layers gives the
+// results of one call per layer); workgroup j of W takes the chunks [j T / W, (j + 1) T / W), so that it changes units,
+// and with them Q, a few times per launch.  In a chunk the workgroup takes 512 keys per pass: each wave holds two 32-key
+// tiles as matrix operands, multiplies them with all row tiles, and requests the next pass's keys meanwhile.
+//
+// Launch 1, per chunk and row: z = sum exp2(x - m) with the row's logit of the unit's key 0 as reference m, the same for
+// all keys, from which equal keys get equal sums.  Key 0 alone contributes 1 to the unit's sum, so vanishing terms are
+// as they should be; a sum beyond 2^100 makes the workgroup form its chunk again with the chunk's exact maxima (rare).
+// Launch 2, when it takes up a unit, folds the statistics of its chunks into the normalisers c_r (or takes the supplied
+// denominators: then it is the only launch) and writes s_i = sum_r exp2(x_ri - c_r) / G.
+//
+// Inner loops as in the register-resident kernel: one product's matrix instructions are issued between the exponentials
+// of the one before, in an order fixed in the source.
+//
+// What bounds it: the sweeps.  640 units of 32k keys, 512 rows: 3.04 + 2.80 ms (by the profiler, after 6.4 ms for the
+// register-resident kernel's one launch) against 2.2 ms per sweep for a bare loop of these instructions at the clock the
+// chip holds under them; 0.9 ms of that is what K takes to read.
+#include <type_traits>
+
+#include "pkv_internal.h"
+
+namespace pkv {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned long long u64;
+
+constexpr int kW = 8;              // waves per workgroup
+constexpr int kT = kW * 64;
+constexpr int kPassKeys = 64 * kW; // keys of a pass
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
+__device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
+#define PKV_MFMA32(A, B, C) __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, C, 0, 0, 0)
+// End of a hand-ordered chunk of instructions: nothing is scheduled across it, and the running sums are pinned here.
+#define PKV_CHUNK_END_SUMS(s0, s1)                 \
+  do {                                             \
+    asm volatile("" : "+v"(s0), "+v"(s1));         \
+    __builtin_amdgcn_sched_barrier(0);             \
+  } while (0)
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+template <bool MAX>
+__device__ __forceinline__ float both_halves(float x) {
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  const float p = __uint_as_float(r[0]), q = __uint_as_float(r[1]);
+  return MAX ? fmaxf(p, q) : p + q;
+}
+// c as three bf16 summands (to 2^-24): the first three k-elements of a matrix operand.  -inf stays -inf.
+__device__ __forceinline__ u64 split3(float c) {
+  const __bf16 hi = (__bf16)c;
+  float r = c - (float)hi;
+  if (c == -INFINITY) r = 0.f;
+  const __bf16 mid = (__bf16)r;
+  r -= (float)mid;
+  const __bf16 lo = (__bf16)r;
+  const uint32_t w0 = (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, mid) << 16);
+  return ((u64)__builtin_bit_cast(uint16_t, lo) << 32) | w0;
+}
+__device__ __forceinline__ constexpr int mrow0(int v) { return 8 * (v >> 2) + (v & 3); }
+
+template <int D, bool SCORE>
+constexpr size_t sweep_lds(int Rs) {
+  // Q with a row pitch of D / 8 + 1 sixteen-byte slots (bank-free); a zero slot; normalisers, or references (in use,
+  // original) and sums by wave, and the flag
+  return (size_t)Rs * (D / 8 + 1) * 16 + 16 + (SCORE ? (size_t)Rs * 8 : (size_t)Rs * 4 * (2 + kW) + 16);
+}
+static_assert(sweep_lds<128, false>(kResidentMaxRows) <= 160 * 1024, "one workgroup per compute unit");
+
+template <int D, bool SCORE>
+__global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
+  constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;
+  constexpr int TPM = 16 / KS;  // logits per lane handled between two matrix instructions
+  extern __shared__ u32x4 smem[];
+  u32x4* s_q = smem;
+  u32x4* s_zero = s_q + a.Rs * PITCH;
+  u64* s_c = reinterpret_cast<u64*>(s_zero + 1);      // [Rs] -c_r / kappa, split (SCORE)
+  float* s_m = reinterpret_cast<float*>(s_zero + 1);  // [Rs] references in use (else)
+  float* s_m0 = s_m + a.Rs;                           // [Rs] logits of key 0
+  float* s_z = s_m0 + a.Rs;                           // [kW][Rs] sums by wave
+  int* s_bad = reinterpret_cast<int*>(s_z + kW * a.Rs);  // [2] a chunk's reference does not fit; used in turn
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int BH = a.B * a.Hkv, C = a.C, nrt = a.Rs / 32;
+
+  auto length = [&](int b) {
+    int n = a.N;
+    if (a.seq_lens) {
+      n = a.seq_lens[b];
+      n = n < 0 ? 0 : (n > a.N ? a.N : n);
+    }
+    return n;
+  };
+
+  // One pass of the workgroup (all fields wave-uniform): 512 keys from `key` on of chunk `chunk` of unit u.
+  struct Pass {
+    int u, n, chunk, key, left;  // left: chunks of this workgroup behind this one
+    const uint16_t* Q;
+    const uint16_t* K;
+  };
+  auto open_unit = [&](Pass& p) {  // pointers and length of unit p.u; false: the unit needs no scores
+    const int l = p.u / BH, bg = p.u - l * BH;
+    const int b = bg / a.Hkv, g = bg - b * a.Hkv;
+    p.n = length(b);
+    p.Q = a.layer[l].Q + (size_t)b * a.q_sb + (size_t)(g * a.G) * a.q_sh;
+    p.K = a.layer[l].K + (size_t)b * a.kv_sb + (size_t)g * a.kv_sh;
+    return a.layer[l].k_l < p.n;
+  };
+  Pass cur;
+  {
+    // first chunk and number of chunks of this workgroup
+    int total, u0 = 0, c0 = 0;
+    if (a.uniform) {
+      total = a.L * BH * a.nchunk;
+      const int lo = (int)((int64_t)blockIdx.x * total / gridDim.x), hi = (int)((int64_t)(blockIdx.x + 1) * total / gridDim.x);
+      u0 = lo / a.nchunk;
+      c0 = lo - u0 * a.nchunk;
+      cur.left = hi - lo;
+    } else {
+      int* wsum = reinterpret_cast<int*>(smem);  // [kW] sums of the waves, [kW], [kW + 1] the first chunk's place
+      const int E = a.L * a.B;
+      int lo = 0, hi = 0;
+      for (int round = 0; round < 2; ++round) {  // how many chunks there are; then who owns the first one
+        int run = 0;
+        for (int e0 = 0; e0 < E; e0 += kT) {
+          const int e = e0 + tid;
+          int c = 0, parts = 0;
+          if (e < E) {
+            const int l = e / a.B, n = length(e - l * a.B);
+            parts = a.layer[l].k_l < n ? (n + C - 1) / C : 0;
+            c = a.Hkv * parts;
+          }
+          int v = c;
+#pragma unroll
+          for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(v, o);
+            if (lane >= o) v += x;
+          }
+          __syncthreads();
+          if (lane == 63) wsum[wave] = v;
+          __syncthreads();
+          int before = run;
+#pragma unroll
+          for (int w = 0; w < kW; ++w) {
+            before += w < wave ? wsum[w] : 0;
+            run += wsum[w];
+          }
+          before += v - c;
+          if (round == 1 && lo >= before && lo < before + c) {
+            const int rem = lo - before, g = rem / parts;
+            wsum[kW] = e * a.Hkv + g;
+            wsum[kW + 1] = rem - g * parts;
+          }
+        }
+        if (round == 0) {
+          lo = (int)((int64_t)blockIdx.x * run / gridDim.x);
+          hi = (int)((int64_t)(blockIdx.x + 1) * run / gridDim.x);
+        }
+      }
+      __syncthreads();
+      cur.left = hi - lo;
+      if (cur.left > 0) {
+        u0 = __builtin_amdgcn_readfirstlane(wsum[kW]);
+        c0 = __builtin_amdgcn_readfirstlane(wsum[kW + 1]);
+      }
+      __syncthreads();
+    }
+    if (cur.left == 0) return;
+    --cur.left;
+    cur.u = u0;
+    cur.chunk = c0;
+    cur.key = c0 * C;
+    (void)open_unit(cur);
+  }
+  // The pass after p; false if there is none (p is then a pass over the unit's first key alone).
+  auto advance = [&](Pass& p) {
+    p.key += kPassKeys;
+    if (p.key < min((p.chunk + 1) * C, p.n)) return true;
+    if (p.left == 0) {
+      p.key = 0;
+      p.n = 1;
+      return false;
+    }
+    --p.left;
+    ++p.chunk;
+    if (p.chunk * C >= p.n) {
+      p.chunk = 0;
+      do ++p.u;
+      while (!open_unit(p));  // (there is one: a chunk is left)
+    }
+    p.key = p.chunk * C;
+    return true;
+  };
+
+  // Queries of a unit into LDS with what belongs to them: the references, or the normalisers.  Barriers around it are
+  // the caller's.
+  auto stage = [&](const Pass& p) {
+    const int seg = tid & (SEG - 1);
+    u32x4 kv0 = u32x4{0u, 0u, 0u, 0u};
+    if (!SCORE) kv0 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.K) + 16 * seg);
+    const char* src = reinterpret_cast<const char*>(p.Q) + 16 * seg;
+    for (int row0 = tid / SEG; row0 < a.Rs; row0 += 4 * (kT / SEG)) {  // (uniform over a wave)
+      u32x4 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = row0 + j * (kT / SEG);
+        v[j] = u32x4{0u, 0u, 0u, 0u};
+        if (row < a.R) {
+          const int hh = row / a.alpha, t = row - hh * a.alpha;
+          v[j] = *reinterpret_cast<const u32x4*>(src + (uint32_t)((hh * a.q_sh + t * a.q_st) * 2));
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = row0 + j * (kT / SEG);
+        if (row < a.Rs) s_q[row * PITCH + seg] = v[j];
+        if (!SCORE) {
+          float dot = 0.f;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            dot = __builtin_fmaf(__uint_as_float(v[j][e] << 16), __uint_as_float(kv0[e] << 16), dot);
+            dot = __builtin_fmaf(__uint_as_float(v[j][e] & 0xFFFF0000u), __uint_as_float(kv0[e] & 0xFFFF0000u), dot);
+          }
+          // over the row's 16 or 8 lanes, in all of them
+#define PKV_ADD(ctrl) dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), ctrl, 0xF, 0xF, true))
+          PKV_ADD(0xB1);                 // quad_perm 1,0,3,2
+          PKV_ADD(0x4E);                 // quad_perm 2,3,0,1
+          PKV_ADD(0x141);                // row_half_mirror: the other quad of 8 lanes
+          if (SEG == 16) PKV_ADD(0x140); // row_mirror: the other half of 16 lanes
+#undef PKV_ADD
+          if (seg == 0 && row < a.Rs) s_m[row] = s_m0[row] = dot * a.kappa;
+        }
+      }
+    }
+    if (SCORE) {
+      if (tid < a.Rs) {
+        float c = INFINITY;  // padding rows contribute exp2(-inf) = 0
+        if (tid < a.R) {
+          if (a.lse_mode) {
+            const int l = p.u / BH, bg = p.u - l * BH, b = bg / a.Hkv, g = bg - b * a.Hkv;
+            c = a.layer[l].lse[((size_t)b * a.Hq + (size_t)g * a.G) * a.alpha + tid] * 1.44269504088896340736f;
+          } else {
+            const u64* st = a.stats + (size_t)p.u * a.nchunk * a.Rs + tid;
+            const int parts = (p.n + C - 1) / C;
+            float m = -INFINITY, z = 0.f;
+            for (int q0 = 0; q0 < parts; q0 += 8) {
+              u64 w[8];
+#pragma unroll
+              for (int k = 0; k < 8; ++k) w[k] = st[(size_t)min(q0 + k, parts - 1) * a.Rs];
+              float M = m;
+#pragma unroll
+              for (int k = 0; k < 8; ++k) M = fmaxf(M, __uint_as_float((uint32_t)w[k]));
+              const float Ms = (M == -INFINITY) ? 0.f : M;
+              z *= fast_exp2(m - Ms);
+#pragma unroll
+              for (int k = 0; k < 8; ++k)
+                if (q0 + k < parts)
+                  z = __builtin_fmaf(__uint_as_float((uint32_t)(w[k] >> 32)), fast_exp2(__uint_as_float((uint32_t)w[k]) - Ms), z);
+              m = M;
+            }
+            c = m + fast_log2(z);
+          }
+        }
+        s_c[tid] = split3(-c * a.inv_kappa);
+      }
+    }
+  };
+
+  // Keys of a wave's two tiles as matrix operands: lane (l32, hf) holds elements 16 ks + 8 hf of key 32 t + l32.  Keys
+  // at or beyond n are replaced by the last one.
+  bf16x8 kf[2][KS], kn[2][KS];
+  auto issue_k = [&](const Pass& p, int t, int lo, int hi, bf16x8 (&f)[2][KS]) {
+    const int ln = fresh(lane);
+    const int key = min(p.key + 64 * wave + 32 * t + (ln & 31), p.n - 1);
+    const char* rowp = reinterpret_cast<const char*>(p.K) + 16 * (ln >> 5) + (uint32_t)key * ((uint32_t)a.kv_st * 2u);
+#pragma unroll
+    for (int ks = lo; ks < hi; ++ks) f[t][ks] = as_frag(*reinterpret_cast<const u32x4*>(rowp + 32 * ks));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const u32x4* q_lane = s_q + l32 * PITCH + hf;
+  auto q_frag = [&](int rt, int ks) { return as_frag(q_lane[32 * rt * PITCH + 2 * ks]); };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using INONE = std::integral_constant<int, -1>;
+
+  if (tid == 0) {
+    *s_zero = u32x4{0u, 0u, 0u, 0u};
+    if (!SCORE) s_bad[0] = s_bad[1] = 0;
+  }
+  stage(cur);
+  issue_k(cur, 0, 0, KS, kf);
+  issue_k(cur, 1, 0, KS, kf);
+  lds_barrier();
+
+  bool first = true;  // first pass of a chunk
+  int turn = 0;       // of the flags
+  for (;;) {
+    Pass nxt = cur;
+    const bool has_next = advance(nxt);
+    const int wkey = cur.key + 64 * wave;
+    const int npre = cur.n - a.alpha;
+    bf16x8 qf[KS];
+    f32x16 fin, out;
+    // half a tile of the next pass's keys is requested at a time, at fixed places of the first two row tiles
+    auto refill = [&](auto RF, int half) {
+      if constexpr (decltype(RF)::value >= 0) issue_k(nxt, decltype(RF)::value, half * (KS / 2), half * (KS / 2) + KS / 2, kn);
+    };
+    if constexpr (!SCORE) {
+      // Product rows = keys (element v of a lane: key mrow0(v) + 4 hf of the tile), columns = query rows (l32).
+      float* z_lane = s_z + wave * a.Rs + l32;
+      const bool dirty = wkey + 64 > npre;  // a tile reaches into the causal window or beyond the end
+      bool bad = false;
+      auto pass = [&](auto MASKED) {
+        constexpr bool masked = decltype(MASKED)::value;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = q_frag(0, ks);
+        fin = zero16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) fin = PKV_MFMA32(kf[0][ks], qf[ks], fin);
+        // The product of tile TN goes into `nx` while `fi`, that of tile 1 - TN, turns into exponentials.
+        auto step = [&](auto TN, auto RF, int rt_next, float nref, int lim, const f32x16& fi, f32x16& nx, float& s0, float& s1) {
+          constexpr int tn = decltype(TN)::value, tc = 1 - tn;
+          const float kap = a.kappa;
+          nx = zero16;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            nx = PKV_MFMA32(kf[tn][ks], qf[ks], nx);
+            if (tn == 1) qf[ks] = q_frag(rt_next, ks);  // (last use of this row tile's fragment)
+            float x[TPM];
+#pragma unroll
+            for (int j = 0; j < TPM; ++j) {
+              x[j] = __builtin_fmaf(fi[TPM * ks + j], kap, nref);
+              if (masked && 32 * tc + mrow0(TPM * ks + j) > lim) x[j] = -INFINITY;
+            }
+#pragma unroll
+            for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
+#pragma unroll
+            for (int j = 0; j < TPM; ++j) {
+              if (j & 1) s1 += x[j]; else s0 += x[j];
+            }
+            PKV_CHUNK_END_SUMS(s0, s1);
+            if (ks == KS / 2 - 1) refill(RF, tn == 1 ? 0 : 1);
+          }
+        };
+        auto iter = [&](auto RF, int rt) {
+          const int rt_next = rt + 1 < nrt ? rt + 1 : 0;  // (the last product of the pass is not used)
+          const float nref = -s_m[32 * rt + l32];
+          int lim = 0;
+          if (masked) lim = npre + (32 * rt + l32) % a.alpha - wkey - 4 * hf;  // last key the lane's query sees
+          float s0 = 0.f, s1 = 0.f;
+          step(I1{}, RF, rt_next, nref, lim, fin, out, s0, s1);
+          step(I0{}, RF, rt_next, nref, lim, out, fin, s0, s1);
+          float z = both_halves<false>(s0 + s1);
+          bad = bad || !(z <= 0x1p100f);
+          if (!first) z += z_lane[32 * rt];
+          if (hf == 0) z_lane[32 * rt] = z;
+        };
+        iter(I0{}, 0);
+        if (nrt > 1) iter(I1{}, 1);
+        else issue_k(nxt, 1, 0, KS, kn);
+#pragma unroll 1
+        for (int rt = 2; rt < nrt; ++rt) iter(INONE{}, rt);
+      };
+      if (dirty) pass(std::true_type{});
+      else pass(std::false_type{});
+      if (__any(bad) && lane == 0) s_bad[turn] = 1;
+
+      const bool ends = !has_next || nxt.chunk != cur.chunk || nxt.u != cur.u;
+      if (ends) {
+        lds_barrier();
+        if (tid == 0) s_bad[turn ^ 1] = 0;
+        if (s_bad[turn] != 0) {
+          // rare: a reference that does not fit; round 0 finds the chunk's maxima, round 1 forms the sums with them
+          const int end = min((cur.chunk + 1) * C, cur.n);
+          for (int round = 0; round < 2; ++round) {
+            for (int r = lane; r < a.Rs; r += 64) s_z[wave * a.Rs + r] = round == 0 ? -INFINITY : 0.f;
+            lds_barrier();
+            Pass q = cur;
+            for (q.key = cur.chunk * C; q.key < end; q.key += kPassKeys) {
+              issue_k(q, 0, 0, KS, kf);
+              issue_k(q, 1, 0, KS, kf);
+#pragma unroll 1
+              for (int rt = 0; rt < nrt; ++rt) {
+                const float ref = s_m[32 * rt + l32];
+                const int lim = npre + (32 * rt + l32) % a.alpha - q.key - 64 * wave - 4 * hf;
+                float acc = round == 0 ? -INFINITY : 0.f;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                  f32x16 y = zero16;
+#pragma unroll
+                  for (int ks = 0; ks < KS; ++ks) y = PKV_MFMA32(kf[t][ks], q_frag(rt, ks), y);
+#pragma unroll
+                  for (int v = 0; v < 16; ++v) {
+                    const bool hidden = 32 * t + mrow0(v) > lim;
+                    if (round == 0) acc = fmaxf(acc, hidden ? -INFINITY : y[v] * a.kappa);
+                    else acc += hidden ? 0.f : fast_exp2(__builtin_fmaf(y[v], a.kappa, -ref));
+                  }
+                }
+                acc = round == 0 ? both_halves<true>(acc) : both_halves<false>(acc);
+                const float old = z_lane[32 * rt];
+                if (hf == 0) z_lane[32 * rt] = round == 0 ? fmaxf(old, acc) : old + acc;
+              }
+            }
+            lds_barrier();
+            if (round == 0) {
+              if (tid < a.Rs) {
+                float m = -INFINITY;
+#pragma unroll
+                for (int w = 0; w < kW; ++w) m = fmaxf(m, s_z[w * a.Rs + tid]);
+                s_m[tid] = m == -INFINITY ? 0.f : m;
+              }
+              lds_barrier();
+            }
+          }
+        }
+        if (tid < a.Rs) {
+          float z = 0.f;
+#pragma unroll
+          for (int w = 0; w < kW; ++w) z += s_z[w * a.Rs + tid];
+          a.stats[((size_t)cur.u * a.nchunk + cur.chunk) * a.Rs + tid] = ((u64)__float_as_uint(z) << 32) | __float_as_uint(s_m[tid]);
+          s_m[tid] = s_m0[tid];
+        }
+        lds_barrier();
+        turn ^= 1;
+      }
+      first = ends;
+    } else {
+      // Product rows = query rows (element v of a lane: row mrow0(v) + 4 hf), columns = keys (l32).  The normalisers
+      // enter through one more matrix instruction: (hi, mid, lo) of the lane's row times ones, in the first wave half.
+      const u32x4 ones_u = (hf == 0) ? u32x4{0x3F803F80u, 0x00003F80u, 0u, 0u} : u32x4{0u, 0u, 0u, 0u};
+      const bf16x8 ones = as_frag(ones_u);
+      const u64* c_lane = (hf == 0) ? s_c + l32 : reinterpret_cast<const u64*>(s_zero);
+      const int c_step = (hf == 0) ? 32 : 0;
+      bf16x8 bfr;
+      auto load_bias = [&](int rt) {
+        const u64 w = c_lane[c_step * rt];
+        bfr = as_frag(u32x4{(uint32_t)w, (uint32_t)(w >> 32), 0u, 0u});
+      };
+      float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) qf[ks] = q_frag(0, ks);
+      load_bias(0);
+      fin = PKV_MFMA32(bfr, ones, zero16);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) fin = PKV_MFMA32(qf[ks], kf[0][ks], fin);
+      auto step = [&](auto TN, auto RF, int rt_next, const f32x16& fi, f32x16& nx, float& e) {
+        constexpr int tn = decltype(TN)::value;
+        float s0 = 0.f, s1 = 0.f;
+        float kap = a.kappa;
+        asm volatile("" : "+s"(kap));
+        nx = PKV_MFMA32(bfr, ones, zero16);
+        if (tn == 1) load_bias(rt_next);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          nx = PKV_MFMA32(qf[ks], kf[tn][ks], nx);
+          if (tn == 1) qf[ks] = q_frag(rt_next, ks);
+          float x[TPM];
+#pragma unroll
+          for (int j = 0; j < TPM; ++j) x[j] = fi[TPM * ks + j] * kap;
+#pragma unroll
+          for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
+#pragma unroll
+          for (int j = 0; j < TPM; ++j) {
+            if (j & 1) s1 += x[j]; else s0 += x[j];
+          }
+          PKV_CHUNK_END_SUMS(s0, s1);
+          if (ks == KS / 2 - 1) refill(RF, tn == 1 ? 0 : 1);
+        }
+        e += s0 + s1;
+      };
+      auto iter = [&](auto RF, int rt) {
+        const int rt_next = rt + 1 < nrt ? rt + 1 : 0;
+        step(I1{}, RF, rt_next, fin, out, e0);
+        step(I0{}, RF, rt_next, out, fin, e1);
+      };
+      iter(I0{}, 0);
+      if (nrt > 1) iter(I1{}, 1);
+      else issue_k(nxt, 1, 0, KS, kn);
+#pragma unroll 1
+      for (int rt = 2; rt < nrt; ++rt) iter(INONE{}, rt);
+      const float s = both_halves<false>(e0), t = both_halves<false>(e1);
+      const int key = wkey + lane;
+      if (key < npre) a.raw[(size_t)cur.u * a.N + key] = (hf == 0 ? s : t) * a.inv_G;
+    }
+    if (!has_next) break;
+    if (nxt.u != cur.u) {
+      if (SCORE) lds_barrier();  // every wave is done with the unit's queries (else: the barrier behind the statistics)
+      stage(nxt);
+      lds_barrier();
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = kn[t][ks];
+    cur = nxt;
+  }
+}
+
+template <int D, bool SCORE>
+hipError_t launch_sweep(const SweepArgs& a, hipStream_t s) {
+  static bool attr_set[kMaxDevices];
+  const int dev = current_device_slot();
+  if (dev < 0) return hipErrorInvalidDevice;
+  if (!attr_set[dev]) {  // raise the dynamic LDS limit once per device (idempotent; no allocation)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sweep_kernel<D, SCORE>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sweep_lds<D, SCORE>(kResidentMaxRows));
+    if (e != hipSuccess) return e;
+    attr_set[dev] = true;
+  }
+  const size_t lds = sweep_lds<D, SCORE>(a.Rs);
+  hipLaunchKernelGGL((score_sweep_kernel<D, SCORE>), dim3(a.grid), dim3(kT), lds, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_score_sweep(const SweepArgs& a, hipStream_t s) {
+  if (a.d != 64 && a.d != 128) return hipErrorInvalidValue;
+  if (!a.lse_mode) {
+    const hipError_t e = a.d == 128 ? launch_sweep<128, false>(a, s) : launch_sweep<64, false>(a, s);
+    if (e != hipSuccess) return e;
+  }
+  return a.d == 128 ? launch_sweep<128, true>(a, s) : launch_sweep<64, true>(a, s);
+}
+
+}  // namespace pkv

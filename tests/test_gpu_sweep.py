@@ -1,0 +1,108 @@
+"""Scoring in two streaming launches for many query rows (G * alpha > 128) at the edges of its work split: rows around the
+32-row tiles and the limit, lengths around a pass and a chunk, ragged batches, chunk counts that the workgroups do not
+divide, references that do not fit, supplied denominators."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import pkv_oracle
+from paper_2406_02069_amd import binding, synth
+from tests import prefill_stub
+from tests.parity import compare_layer
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(B, Hq, Hkv, d, N, alpha, seed, scale=1.0):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    Q = (torch.randn(B, Hq, alpha, d, generator=g, device=DEV) * scale).to(torch.bfloat16)
+    K = torch.randn(B, Hkv, N, d, generator=g, device=DEV).to(torch.bfloat16)
+    V = torch.randn(B, Hkv, N, d, generator=g, device=DEV).to(torch.bfloat16)
+    return Q, K, V
+
+
+def _check(Q, K, V, k_l, lens=None, pool=synth.POOL_MAX, pw=7):
+    print("sweep", tuple(Q.shape), tuple(K.shape), k_l, None if lens is None else lens.tolist()[:8], flush=True)
+    ld = None if lens is None else torch.from_numpy(lens).to(DEV)
+    out = binding.compress_layer(Q, K, V, k_l, pool, pw, seq_lens=ld, want_scores=True)
+    torch.cuda.synchronize()
+    return compare_layer(Q, K, V, k_l, Q.shape[2], pool, pw, lens, out)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,alpha", [(3, 43), (4, 40), (7, 23), (5, 51), (8, 33), (7, 64), (8, 64)])
+def test_rows(d, G, alpha):
+    Hkv = 8
+    N = 4100 if G * alpha <= 256 else 8200
+    Q, K, V = _inputs(1, Hkv * G, Hkv, d, N, alpha, seed=G * 100 + alpha + d)
+    _check(Q, K, V, alpha + 60)
+
+
+@pytest.mark.parametrize("N", [3600, 3647, 4031, 4095, 4096, 4097, 4128, 4159, 4160, 4161])
+def test_lengths_around_a_pass(N):
+    Q, K, V = _inputs(1, 32, 8, 128, N, 33, seed=N)
+    _check(Q, K, V, 100)
+
+
+def test_one_chunk_per_unit():
+    Q, K, V = _inputs(8, 16, 8, 64, 1024, 64, seed=3)
+    _check(Q, K, V, 80)
+
+
+def test_ragged_batch():
+    alpha, N = 40, 4300
+    lens = np.array([4300, 0, 39, 40, 41, 100, 552, 553, 4096, 1037], dtype=np.int32)
+    Q, K, V = _inputs(len(lens), 8, 2, 128, N, alpha, seed=11)
+    for b, n in enumerate(lens):
+        K[b, :, n:] = float("nan")
+    _check(Q, K, V, 60, lens)
+
+
+def test_no_sequence_needs_scores():
+    alpha, N = 40, 4300
+    lens = np.full(4, 50, dtype=np.int32)
+    Q, K, V = _inputs(4, 8, 2, 128, N, alpha, seed=12)
+    _check(Q, K, V, 60, lens)
+
+
+def test_many_layers_equal_one_call_per_layer():
+    L, alpha, N = 7, 40, 4300
+    data = [_inputs(2, 16, 4, 64, N, alpha, seed=500 + l) for l in range(L)]
+    lens = torch.tensor([4300, 3100], dtype=torch.int32, device=DEV)
+    ks = [N + 5, 50, 60, 70, 3500, 90, N]                     # layers and sequences kept whole among them
+    outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_MAX, 7,
+                                   seq_lens=lens, want_scores=True)
+    torch.cuda.synchronize()
+    for l in range(L):
+        one = binding.compress_layer(*data[l], ks[l], synth.POOL_MAX, 7, seq_lens=lens, want_scores=True)
+        torch.cuda.synchronize()
+        for x, y in zip(outs[l], one):
+            assert torch.equal(x, y), l
+        if l in (1, 4):
+            compare_layer(*data[l], ks[l], alpha, synth.POOL_MAX, 7, lens.cpu().numpy(), outs[l])
+
+
+@pytest.mark.parametrize("G", [4, 8])
+def test_references_that_do_not_fit(G):
+    # some rows' logit of key 0 lies hundreds of binades below those of later keys: their chunks are formed again
+    alpha, N, Hkv = 40, 8200, 8
+    Q, K, V = _inputs(1, G * Hkv, Hkv, 128, N, alpha, seed=G, scale=0.5)
+    for g in (0, 5):
+        K[0, g, 700] = 40 * Q[0, g * G, 3]
+        K[0, g, 0] = -20 * Q[0, g * G, 3]
+    _check(Q, K, V, alpha + 30, pool=synth.POOL_NONE, pw=1)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,alpha,N", [(5, 27, 4099), (8, 64, 8200)])
+def test_supplied_denominators(d, G, alpha, N):
+    Q, K, V = _inputs(2, G * 4, 4, d, N, alpha, seed=G + N)
+    lens = np.array([N, N - 700], dtype=np.int32)
+    lse = prefill_stub.window_lse(Q, K, lens)
+    out = binding.compress_layers_lse([Q], [K], [V], [lse], [alpha + 50], synth.POOL_AVG, 5,
+                                      seq_lens=torch.from_numpy(lens).to(DEV), want_scores=True)[0]
+    torch.cuda.synchronize()
+    ref = pkv_oracle.compress_layer(Q, K, V, alpha + 50, alpha, synth.POOL_AVG, 5, seq_lens=lens,
+                                    lse=np.nan_to_num(lse.cpu().numpy(), nan=0.0))
+    compare_layer(Q, K, V, alpha + 50, alpha, synth.POOL_AVG, 5, lens, out, ref=ref)
