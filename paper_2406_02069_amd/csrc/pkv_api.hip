@@ -270,6 +270,13 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       wa.stats = reinterpret_cast<unsigned long long*>(pooled_ws);
       wa.L = nl; wa.B = d.B; wa.Hq = d.Hq; wa.Hkv = d.Hkv; wa.G = plan.G; wa.alpha = d.alpha; wa.N = d.N;
       wa.R = plan.R; wa.Rs = wp.Rs; wa.d = d.d; wa.C = wp.C; wa.nchunk = wp.nchunk;
+      // Sixteen waves write the scores where every workgroup has four passes of theirs and the products bind (the scores
+      // do not depend on the split): 80 layers x 32k keys, 512 rows 5593 -> 5448 us, 32 layers, 256 rows 1337 -> 1291, 161
+      // rows 565 -> 554.  K binds at 128 rows with supplied denominators, and fewer keys in flight cost: 354 -> 376 us.
+      const bool many = plan.R > 128 && (int64_t)nl * plan.BH * ((d.N + 1023) / 1024) >= 4 * kSweepGrid;
+      wa.score_waves = many ? 16 : 8;
+      wa.score_C = many ? (wp.C + 1023) / 1024 * 1024 : wp.C;
+      wa.score_nchunk = (d.N + wa.score_C - 1) / wa.score_C;
       const int64_t chunks = (int64_t)nl * plan.BH * wp.nchunk;
       wa.grid = chunks < kSweepGrid ? (int32_t)chunks : kSweepGrid;
       wa.lse_mode = lse_mode ? 1 : 0;

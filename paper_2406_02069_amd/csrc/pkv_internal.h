@@ -135,6 +135,8 @@ struct SweepArgs {
   unsigned long long* stats;  // [U][nchunk][Rs] (reference, sum) of a row over a chunk (log2 domain)
   int32_t L, B, Hq, Hkv, G, alpha, N, R, Rs, d;  // Rs: rows padded to 32
   int32_t C, nchunk;          // keys per chunk (a multiple of 512), chunks per unit
+  int32_t score_C, score_nchunk;  // the split of the launch that writes the scores (a multiple of 64 keys per wave)
+  int32_t score_waves;        // 8 or 16 per workgroup
   int32_t uniform;            // 1: every unit has N keys and none is kept whole
   int32_t grid;
   int32_t lse_mode;           // 1: every layer carries lse; no statistics

@@ -10,7 +10,7 @@
 //
 // Work split.  Units are cut into chunks of C keys (from one layer's shape, so that a call over many layers gives the
 // results of one call per layer); workgroup j of W takes the chunks [j T / W, (j + 1) T / W), so that it changes units,
-// and with them Q, a few times per launch.  In a chunk the workgroup takes 512 keys per pass: each wave holds two 32-key
+// and with them Q, a few times per launch.  In a chunk the workgroup takes 512 or 1024 keys per pass: each wave holds two 32-key
 // tiles as matrix operands, multiplies them with all row tiles, and requests the next pass's keys meanwhile.
 //
 // Launch 1, per chunk and row: z = sum exp2(x - m) with the row's logit of the unit's key 0 as reference m, the same for
@@ -22,9 +22,10 @@
 // Inner loops as in the register-resident kernel: one product's matrix instructions are issued between the exponentials
 // of the one before, in an order fixed in the source.
 //
-// What bounds it: the sweeps.  640 units of 32k keys, 512 rows: 3.04 + 2.80 ms (by the profiler, after 6.4 ms for the
+// What bounds it: the sweeps.  640 units of 32k keys, 512 rows: 3.04 + 2.62 ms (by the profiler, after 6.4 ms for the
 // register-resident kernel's one launch) against 2.2 ms per sweep for a bare loop of these instructions at the clock the
-// chip holds under them; 0.9 ms of that is what K takes to read.
+// chip holds under them; 0.9 ms of that is what K takes to read.  The scores took 2.80 ms with eight waves; for the
+// statistics sixteen do not help (3.04 -> 3.2 ms: their tables of sums do not fit beside 512 rows).
 #include <type_traits>
 
 #include "pkv_internal.h"
@@ -38,9 +39,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned long long u64;
 
-constexpr int kW = 8;              // waves per workgroup
-constexpr int kT = kW * 64;
-constexpr int kPassKeys = 64 * kW; // keys of a pass
+constexpr int kSums = 8;  // waves that form statistics
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
@@ -84,12 +83,15 @@ template <int D, bool SCORE>
 constexpr size_t sweep_lds(int Rs) {
   // Q with a row pitch of D / 8 + 1 sixteen-byte slots (bank-free); a zero slot; normalisers, or references (in use,
   // original) and sums by wave, and the flag
-  return (size_t)Rs * (D / 8 + 1) * 16 + 16 + (SCORE ? (size_t)Rs * 8 : (size_t)Rs * 4 * (2 + kW) + 16);
+  return (size_t)Rs * (D / 8 + 1) * 16 + 16 + (SCORE ? (size_t)Rs * 8 : (size_t)Rs * 4 * (2 + kSums) + 16);
 }
 static_assert(sweep_lds<128, false>(kResidentMaxRows) <= 160 * 1024, "one workgroup per compute unit");
 
-template <int D, bool SCORE>
-__global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
+// kW: waves per workgroup, 8, or 16 for the scores of launches with several passes per workgroup.
+template <int D, bool SCORE, int kW>
+__global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const SweepArgs a) {
+  static_assert(SCORE || kW == kSums, "a table of sums per wave");
+  constexpr int kT = kW * 64, kPassKeys = 64 * kW;  // threads; keys of a pass
   constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;
   constexpr int TPM = 16 / KS;  // logits per lane handled between two matrix instructions
   extern __shared__ u32x4 smem[];
@@ -104,7 +106,8 @@ __global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
-  const int BH = a.B * a.Hkv, C = a.C, nrt = a.Rs / 32;
+  const int BH = a.B * a.Hkv, nrt = a.Rs / 32;
+  const int C = SCORE ? a.score_C : a.C, nchunk = SCORE ? a.score_nchunk : a.nchunk;
 
   auto length = [&](int b) {
     int n = a.N;
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
     return n;
   };
 
-  // One pass of the workgroup (all fields wave-uniform): 512 keys from `key` on of chunk `chunk` of unit u.
+  // One pass of the workgroup (all fields wave-uniform): its keys from `key` on of chunk `chunk` of unit u.
   struct Pass {
     int u, n, chunk, key, left;  // left: chunks of this workgroup behind this one
     const uint16_t* Q;
@@ -134,10 +137,10 @@ __global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
     // first chunk and number of chunks of this workgroup
     int total, u0 = 0, c0 = 0;
     if (a.uniform) {
-      total = a.L * BH * a.nchunk;
+      total = a.L * BH * nchunk;
       const int lo = (int)((int64_t)blockIdx.x * total / gridDim.x), hi = (int)((int64_t)(blockIdx.x + 1) * total / gridDim.x);
-      u0 = lo / a.nchunk;
-      c0 = lo - u0 * a.nchunk;
+      u0 = lo / nchunk;
+      c0 = lo - u0 * nchunk;
       cur.left = hi - lo;
     } else {
       int* wsum = reinterpret_cast<int*>(smem);  // [kW] sums of the waves, [kW], [kW + 1] the first chunk's place
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
             c = a.layer[l].lse[((size_t)b * a.Hq + (size_t)g * a.G) * a.alpha + tid] * 1.44269504088896340736f;
           } else {
             const u64* st = a.stats + (size_t)p.u * a.nchunk * a.Rs + tid;
-            const int parts = (p.n + C - 1) / C;
+            const int parts = (p.n + a.C - 1) / a.C;
             float m = -INFINITY, z = 0.f;
             for (int q0 = 0; q0 < parts; q0 += 8) {
               u64 w[8];
@@ -461,47 +464,81 @@ __global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
         bfr = as_frag(u32x4{(uint32_t)w, (uint32_t)(w >> 32), 0u, 0u});
       };
       float e0 = 0.f, e1 = 0.f;
+      if constexpr (kW == 16) {
+        // Four waves per SIMD with half the registers each: a wave multiplies both tiles, then forms the exponentials,
+        // and the others fill the gaps.  Its keys are requested again as soon as they have been multiplied.
+        auto tile = [&](int rt, bool last) {
+          load_bias(rt);
+          f32x16 x0 = PKV_MFMA32(bfr, ones, zero16), x1 = PKV_MFMA32(bfr, ones, zero16);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) qf[ks] = q_frag(0, ks);
-      load_bias(0);
-      fin = PKV_MFMA32(bfr, ones, zero16);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) fin = PKV_MFMA32(qf[ks], kf[0][ks], fin);
-      auto step = [&](auto TN, auto RF, int rt_next, const f32x16& fi, f32x16& nx, float& e) {
-        constexpr int tn = decltype(TN)::value;
-        float s0 = 0.f, s1 = 0.f;
-        float kap = a.kappa;
-        asm volatile("" : "+s"(kap));
-        nx = PKV_MFMA32(bfr, ones, zero16);
-        if (tn == 1) load_bias(rt_next);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          nx = PKV_MFMA32(qf[ks], kf[tn][ks], nx);
-          if (tn == 1) qf[ks] = q_frag(rt_next, ks);
-          float x[TPM];
-#pragma unroll
-          for (int j = 0; j < TPM; ++j) x[j] = fi[TPM * ks + j] * kap;
-#pragma unroll
-          for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
-#pragma unroll
-          for (int j = 0; j < TPM; ++j) {
-            if (j & 1) s1 += x[j]; else s0 += x[j];
+          for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 q = q_frag(rt, ks);
+            x0 = PKV_MFMA32(q, kf[0][ks], x0);
+            x1 = PKV_MFMA32(q, kf[1][ks], x1);
           }
-          PKV_CHUNK_END_SUMS(s0, s1);
-          if (ks == KS / 2 - 1) refill(RF, tn == 1 ? 0 : 1);
-        }
-        e += s0 + s1;
-      };
-      auto iter = [&](auto RF, int rt) {
-        const int rt_next = rt + 1 < nrt ? rt + 1 : 0;
-        step(I1{}, RF, rt_next, fin, out, e0);
-        step(I0{}, RF, rt_next, out, fin, e1);
-      };
-      iter(I0{}, 0);
-      if (nrt > 1) iter(I1{}, 1);
-      else issue_k(nxt, 1, 0, KS, kn);
+          if (last) {
+            __builtin_amdgcn_sched_barrier(0);
+            issue_k(nxt, 0, 0, KS, kf);
+            issue_k(nxt, 1, 0, KS, kf);
+          }
+          // (the order of the sums is the eight waves': the scores do not depend on who writes them)
+          float s0 = 0.f, s1 = 0.f, t0 = 0.f, t1 = 0.f;
+#pragma unroll
+          for (int v = 0; v < 16; v += 2) {
+            s0 += fast_exp2(x0[v] * a.kappa);
+            s1 += fast_exp2(x0[v + 1] * a.kappa);
+            t0 += fast_exp2(x1[v] * a.kappa);
+            t1 += fast_exp2(x1[v + 1] * a.kappa);
+          }
+          e0 += s0 + s1;
+          e1 += t0 + t1;
+        };
 #pragma unroll 1
-      for (int rt = 2; rt < nrt; ++rt) iter(INONE{}, rt);
+        for (int rt = 0; rt + 1 < nrt; ++rt) tile(rt, false);
+        tile(nrt - 1, true);
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = q_frag(0, ks);
+        load_bias(0);
+        fin = PKV_MFMA32(bfr, ones, zero16);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) fin = PKV_MFMA32(qf[ks], kf[0][ks], fin);
+        auto step = [&](auto TN, auto RF, int rt_next, const f32x16& fi, f32x16& nx, float& e) {
+          constexpr int tn = decltype(TN)::value;
+          float s0 = 0.f, s1 = 0.f;
+          float kap = a.kappa;
+          asm volatile("" : "+s"(kap));
+          nx = PKV_MFMA32(bfr, ones, zero16);
+          if (tn == 1) load_bias(rt_next);
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            nx = PKV_MFMA32(qf[ks], kf[tn][ks], nx);
+            if (tn == 1) qf[ks] = q_frag(rt_next, ks);
+            float x[TPM];
+#pragma unroll
+            for (int j = 0; j < TPM; ++j) x[j] = fi[TPM * ks + j] * kap;
+#pragma unroll
+            for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
+#pragma unroll
+            for (int j = 0; j < TPM; ++j) {
+              if (j & 1) s1 += x[j]; else s0 += x[j];
+            }
+            PKV_CHUNK_END_SUMS(s0, s1);
+            if (ks == KS / 2 - 1) refill(RF, tn == 1 ? 0 : 1);
+          }
+          e += s0 + s1;
+        };
+        auto iter = [&](auto RF, int rt) {
+          const int rt_next = rt + 1 < nrt ? rt + 1 : 0;
+          step(I1{}, RF, rt_next, fin, out, e0);
+          step(I0{}, RF, rt_next, out, fin, e1);
+        };
+        iter(I0{}, 0);
+        if (nrt > 1) iter(I1{}, 1);
+        else issue_k(nxt, 1, 0, KS, kn);
+#pragma unroll 1
+        for (int rt = 2; rt < nrt; ++rt) iter(INONE{}, rt);
+      }
       const float s = both_halves<false>(e0), t = both_halves<false>(e1);
       const int key = wkey + lane;
       if (key < npre) a.raw[(size_t)cur.u * a.N + key] = (hf == 0 ? s : t) * a.inv_G;
@@ -512,27 +549,29 @@ __global__ __launch_bounds__(kT, 2) void score_sweep_kernel(const SweepArgs a) {
       stage(nxt);
       lds_barrier();
     }
+    if constexpr (kW == 8) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = kn[t][ks];
+        for (int ks = 0; ks < KS; ++ks) kf[t][ks] = kn[t][ks];
+    }
     cur = nxt;
   }
 }
 
-template <int D, bool SCORE>
+template <int D, bool SCORE, int kW>
 hipError_t launch_sweep(const SweepArgs& a, hipStream_t s) {
   static bool attr_set[kMaxDevices];
   const int dev = current_device_slot();
   if (dev < 0) return hipErrorInvalidDevice;
   if (!attr_set[dev]) {  // raise the dynamic LDS limit once per device (idempotent; no allocation)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sweep_kernel<D, SCORE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sweep_kernel<D, SCORE, kW>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sweep_lds<D, SCORE>(kResidentMaxRows));
     if (e != hipSuccess) return e;
     attr_set[dev] = true;
   }
   const size_t lds = sweep_lds<D, SCORE>(a.Rs);
-  hipLaunchKernelGGL((score_sweep_kernel<D, SCORE>), dim3(a.grid), dim3(kT), lds, s, a);
+  hipLaunchKernelGGL((score_sweep_kernel<D, SCORE, kW>), dim3(a.grid), dim3(64 * kW), lds, s, a);
   return hipGetLastError();
 }
 
@@ -541,10 +580,11 @@ hipError_t launch_sweep(const SweepArgs& a, hipStream_t s) {
 hipError_t launch_score_sweep(const SweepArgs& a, hipStream_t s) {
   if (a.d != 64 && a.d != 128) return hipErrorInvalidValue;
   if (!a.lse_mode) {
-    const hipError_t e = a.d == 128 ? launch_sweep<128, false>(a, s) : launch_sweep<64, false>(a, s);
+    const hipError_t e = a.d == 128 ? launch_sweep<128, false, 8>(a, s) : launch_sweep<64, false, 8>(a, s);
     if (e != hipSuccess) return e;
   }
-  return a.d == 128 ? launch_sweep<128, true>(a, s) : launch_sweep<64, true>(a, s);
+  if (a.score_waves == 16) return a.d == 128 ? launch_sweep<128, true, 16>(a, s) : launch_sweep<64, true, 16>(a, s);
+  return a.d == 128 ? launch_sweep<128, true, 8>(a, s) : launch_sweep<64, true, 8>(a, s);
 }
 
 }  // namespace pkv

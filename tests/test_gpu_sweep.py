@@ -106,3 +106,20 @@ def test_supplied_denominators(d, G, alpha, N):
     ref = pkv_oracle.compress_layer(Q, K, V, alpha + 50, alpha, synth.POOL_AVG, 5, seq_lens=lens,
                                     lse=np.nan_to_num(lse.cpu().numpy(), nan=0.0))
     compare_layer(Q, K, V, alpha + 50, alpha, synth.POOL_AVG, 5, lens, out, ref=ref)
+
+
+@pytest.mark.parametrize("d,G,alpha", [(64, 8, 17), (128, 8, 17), (128, 8, 64)])
+def test_sixteen_waves_write_the_scores(d, G, alpha):
+    # enough passes for sixteen waves, with chunks of which the last pass is partly empty; bit for bit what eight give
+    L, Hkv, N = 12, 8, 11300
+    data = [_inputs(1, G * Hkv, Hkv, d, N, alpha, seed=70 + l) for l in range(L)]
+    ks = [alpha + 20 + 9 * l for l in range(L)]
+    outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_AVG, 5,
+                                   want_scores=True)
+    torch.cuda.synchronize()
+    for l in range(L):
+        one = binding.compress_layer(*data[l], ks[l], synth.POOL_AVG, 5, want_scores=True)
+        torch.cuda.synchronize()
+        for x, y in zip(outs[l], one):
+            assert torch.equal(x, y), l
+    compare_layer(*data[3], ks[3], alpha, synth.POOL_AVG, 5, None, outs[3])
