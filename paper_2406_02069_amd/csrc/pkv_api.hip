@@ -202,7 +202,7 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
 }
 
 // How the two-launch kernel for many query rows serves a call: keys per chunk (0: it does not) and chunks per unit, from
-// one layer's shape alone.  A layer has about one chunk per workgroup.  (The statistics lie in the part of the workspace
+// one layer's shape alone but for the last rule.  A layer has about one chunk per workgroup.  (The statistics lie in the part of the workspace
 // that holds the pooled scores later on.)
 // Where the lines lie, against the resident kernel, whole calls (7 us and more of each gain are the selection's):
 //   80 layers of 8 heads x 32k keys, 512 rows 6439 -> 5542 us; 32 layers of 32k, 256 rows 1389 -> 1346, of 4k, 512 rows
@@ -211,16 +211,21 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
 //   keys, 512 rows) and 78.6 -> 71.3 (4 x 8k, 448 rows), which is even without the selection's share.
 // With supplied denominators there is one launch and nothing to read twice: 32 layers of 24k keys, 256 rows 570 -> 501 us,
 //   128 rows 394 -> 363, 64 rows 349 -> 340, 32 rows 345 -> 353; 8 layers of 32 heads x 32k, 8 rows 434 -> 461; one layer
-//   of 24k, 128 rows 54.5 -> 29.0.
+//   of 24k, 128 rows 54.5 -> 29.0.  Up to 32 rows it is ahead of the resident kernel, which hands its keys out from a
+//   counter that has to be cleared, until there are many of them: 32 rows, one layer of 8 x 2k keys 22.1 -> 16.3 us, of
+//   8 x 32k 41.3 -> 29.4, 4 such layers 83 -> 74, 8 (2.1 million keys) 131 -> 127; 6.1 million keys 345 -> 353.  (Both
+//   form the same sums in the same order: here the number of layers may count.)
 constexpr int kSweepMinRows = 129;
 constexpr int kSweepMinRowsLse = 33;
+constexpr int64_t kSweepMaxKeysLse = 4 << 20;
 constexpr int kSweepMinChunks = 32;
 struct SweepPlan {
   int C, nchunk, Rs;
 };
 static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
   SweepPlan p = {0, 0, 0};
-  if (plan.R < (lse_mode ? kSweepMinRowsLse : kSweepMinRows) || !plan.resident_ok) return p;
+  if (!plan.resident_ok) return p;
+  if (lse_mode ? plan.R < kSweepMinRowsLse && (int64_t)plan.L * plan.BH * d.N > kSweepMaxKeysLse : plan.R < kSweepMinRows) return p;
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
   p.Rs = (plan.R + 31) / 32 * 32;
   const int64_t keys = ((int64_t)plan.BH * d.N + kSweepGrid - 1) / kSweepGrid;

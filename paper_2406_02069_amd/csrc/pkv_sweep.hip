@@ -1,5 +1,5 @@
 // Window scoring in two streaming launches over K for many query rows per KV head (G * alpha > 128; Sec. 4.2.2, Eq. Al
-// and Eq. att_score) on MI355X; with supplied softmax denominators in one launch (G * alpha > 32).
+// and Eq. att_score) on MI355X; with supplied softmax denominators in one launch (G * alpha > 32, or few keys).
 //
 // With many query rows the scoring is bound by its products and exponentials and not by the bandwidth of K, so that
 // reading K a second time is free, and what costs is everything that keeps the SIMDs from multiplying: waits for other

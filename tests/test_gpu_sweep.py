@@ -123,3 +123,20 @@ def test_sixteen_waves_write_the_scores(d, G, alpha):
         for x, y in zip(outs[l], one):
             assert torch.equal(x, y), l
     compare_layer(*data[3], ks[3], alpha, synth.POOL_AVG, 5, None, outs[3])
+
+
+@pytest.mark.parametrize("d,G,alpha", [(64, 1, 5), (128, 4, 8), (128, 1, 32)])
+def test_supplied_denominators_few_rows(d, G, alpha):
+    # one layer against the oracle; a call with so many keys that another kernel takes it gives the same bits
+    Hkv, N, L = 8, 5003, 2 + (4 << 20) // (8 * 5003)
+    Q, K, V = _inputs(1, G * Hkv, Hkv, d, N, alpha, seed=G + alpha)
+    lse = prefill_stub.window_lse(Q, K, None)
+    one = binding.compress_layers_lse([Q], [K], [V], [lse], [alpha + 50], synth.POOL_MAX, 7, want_scores=True)[0]
+    many = binding.compress_layers_lse([Q] * L, [K] * L, [V] * L, [lse] * L, [alpha + 50] * L, synth.POOL_MAX, 7,
+                                       want_scores=True)
+    torch.cuda.synchronize()
+    ref = pkv_oracle.compress_layer(Q, K, V, alpha + 50, alpha, synth.POOL_MAX, 7, lse=lse.cpu().numpy())
+    compare_layer(Q, K, V, alpha + 50, alpha, synth.POOL_MAX, 7, None, one, ref=ref)
+    for l in (0, L // 2, L - 1):
+        for x, y in zip(many[l], one):
+            assert torch.equal(x, y), l
