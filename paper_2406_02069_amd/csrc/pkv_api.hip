@@ -205,10 +205,10 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
 // one layer's shape alone but for the last rule.  A layer has about one chunk per workgroup.  (The statistics lie in the part of the workspace
 // that holds the pooled scores later on.)
 // Where the lines lie, against the resident kernel, whole calls (7 us and more of each gain are the selection's):
-//   80 layers of 8 heads x 32k keys, 512 rows 6439 -> 5542 us; 32 layers of 32k, 256 rows 1389 -> 1346, of 4k, 512 rows
-//   413 -> 313; one layer of 8k, 256 rows 58 -> 40.  At 128 rows K is read twice for nothing: 32 layers of 32k keys 801
-//   -> 908 us, of 128k 3371 -> 3551.  Few chunks leave compute units idle: one layer of 32 chunks 89.6 -> 76.5 us (8 x 4k
-//   keys, 512 rows) and 78.6 -> 71.3 (4 x 8k, 448 rows), which is even without the selection's share.
+//   80 layers of 8 heads x 32k keys, 512 rows 6439 -> 5430 us; 32 layers of 32k, 256 rows 1389 -> 1300, of 4k, 512 rows
+//   413 -> 316; one layer of 8k, 256 rows 58 -> 45.  At 128 rows K is read twice for nothing: 32 layers of 32k keys 801
+//   -> 908 us, of 128k 3371 -> 3551.  Few chunks leave compute units idle: with 32 (8 heads x 4k keys, 512 rows) 32
+//   layers gain a quarter, one layer takes about as long as before (89.6 -> 82 us, 7 of it the selection's).
 // With supplied denominators there is one launch and nothing to read twice: 32 layers of 24k keys, 256 rows 570 -> 501 us,
 //   128 rows 394 -> 363, 64 rows 349 -> 340, 32 rows 345 -> 353; 8 layers of 32 heads x 32k, 8 rows 434 -> 461; one layer
 //   of 24k, 128 rows 54.5 -> 29.0.  Up to 32 rows it is ahead of the resident kernel, which hands its keys out from a

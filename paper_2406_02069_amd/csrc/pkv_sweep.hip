@@ -13,9 +13,11 @@
 // and with them Q, a few times per launch.  In a chunk the workgroup takes 512 or 1024 keys per pass: each wave holds two 32-key
 // tiles as matrix operands, multiplies them with all row tiles, and requests the next pass's keys meanwhile.
 //
-// Launch 1, per chunk and row: z = sum exp2(x - m) with the row's logit of the unit's key 0 as reference m, the same for
-// all keys, from which equal keys get equal sums.  Key 0 alone contributes 1 to the unit's sum, so vanishing terms are
-// as they should be; a sum beyond 2^100 makes the workgroup form its chunk again with the chunk's exact maxima (rare).
+// Launch 1, per chunk and row: z = sum exp2(x - m) with the largest of the row's logits of 64 sampled keys, key 0 among
+// them, as reference m: near the terms that count, so that x - m loses nothing to its rounding (with key 0's logit alone
+// the scores were 1.0e-6 off those of 64 bits at 512 rows, the register-resident kernel's 0.6e-6), and the same for all
+// keys.  The sampled keys alone contribute 1 to the unit's sum, so vanishing terms are as they should be; a sum beyond
+// 2^100 makes the workgroup form its chunk again with the chunk's exact maxima (rare).
 // Launch 2, when it takes up a unit, folds the statistics of its chunks into the normalisers c_r (or takes the supplied
 // denominators: then it is the only launch) and writes s_i = sum_r exp2(x_ri - c_r) / G.
 //
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
   u32x4* s_zero = s_q + a.Rs * PITCH;
   u64* s_c = reinterpret_cast<u64*>(s_zero + 1);      // [Rs] -c_r / kappa, split (SCORE)
   float* s_m = reinterpret_cast<float*>(s_zero + 1);  // [Rs] references in use (else)
-  float* s_m0 = s_m + a.Rs;                           // [Rs] logits of key 0
+  float* s_m0 = s_m + a.Rs;                           // [Rs] references of the unit
   float* s_z = s_m0 + a.Rs;                           // [kW][Rs] sums by wave
   int* s_bad = reinterpret_cast<int*>(s_z + kW * a.Rs);  // [2] a chunk's reference does not fit; used in turn
 
@@ -218,12 +220,9 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
     return true;
   };
 
-  // Queries of a unit into LDS with what belongs to them: the references, or the normalisers.  Barriers around it are
-  // the caller's.
+  // Queries of a unit into LDS, and the normalisers (SCORE).  Barriers around it are the caller's.
   auto stage = [&](const Pass& p) {
     const int seg = tid & (SEG - 1);
-    u32x4 kv0 = u32x4{0u, 0u, 0u, 0u};
-    if (!SCORE) kv0 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.K) + 16 * seg);
     const char* src = reinterpret_cast<const char*>(p.Q) + 16 * seg;
     for (int row0 = tid / SEG; row0 < a.Rs; row0 += 4 * (kT / SEG)) {  // (uniform over a wave)
       u32x4 v[4];
@@ -240,22 +239,6 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
       for (int j = 0; j < 4; ++j) {
         const int row = row0 + j * (kT / SEG);
         if (row < a.Rs) s_q[row * PITCH + seg] = v[j];
-        if (!SCORE) {
-          float dot = 0.f;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            dot = __builtin_fmaf(__uint_as_float(v[j][e] << 16), __uint_as_float(kv0[e] << 16), dot);
-            dot = __builtin_fmaf(__uint_as_float(v[j][e] & 0xFFFF0000u), __uint_as_float(kv0[e] & 0xFFFF0000u), dot);
-          }
-          // over the row's 16 or 8 lanes, in all of them
-#define PKV_ADD(ctrl) dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), ctrl, 0xF, 0xF, true))
-          PKV_ADD(0xB1);                 // quad_perm 1,0,3,2
-          PKV_ADD(0x4E);                 // quad_perm 2,3,0,1
-          PKV_ADD(0x141);                // row_half_mirror: the other quad of 8 lanes
-          if (SEG == 16) PKV_ADD(0x140); // row_mirror: the other half of 16 lanes
-#undef PKV_ADD
-          if (seg == 0 && row < a.Rs) s_m[row] = s_m0[row] = dot * a.kappa;
-        }
       }
     }
     if (SCORE) {
@@ -306,6 +289,33 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const u32x4* q_lane = s_q + l32 * PITCH + hf;
   auto q_frag = [&](int rt, int ks) { return as_frag(q_lane[32 * rt * PITCH + 2 * ks]); };
+  // References of a unit's rows: the largest logit over 64 keys spread evenly over the prefix, key 0 among them.  The keys
+  // are requested before the queries are staged (into kf, free at that time); wave w takes the row tiles w, w + 8, ...
+  auto sample_keys = [&](const Pass& p) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int ln = fresh(lane), key = (int)((int64_t)(32 * t + (ln & 31)) * (p.n - a.alpha) >> 6);
+      const char* rowp = reinterpret_cast<const char*>(p.K) + 16 * (ln >> 5) + (uint32_t)key * ((uint32_t)a.kv_st * 2u);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = as_frag(*reinterpret_cast<const u32x4*>(rowp + 32 * ks));
+    }
+  };
+  auto set_references = [&]() {
+#pragma unroll 1
+    for (int rt = wave; rt < nrt; rt += kW) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x16 y = zero16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) y = PKV_MFMA32(kf[t][ks], q_frag(rt, ks), y);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) m = fmaxf(m, y[v]);
+      }
+      m = both_halves<true>(m) * a.kappa;
+      if (hf == 0) s_m[32 * rt + l32] = s_m0[32 * rt + l32] = m;
+    }
+  };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   using INONE = std::integral_constant<int, -1>;
@@ -314,10 +324,24 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
     *s_zero = u32x4{0u, 0u, 0u, 0u};
     if (!SCORE) s_bad[0] = s_bad[1] = 0;
   }
-  stage(cur);
-  issue_k(cur, 0, 0, KS, kf);
-  issue_k(cur, 1, 0, KS, kf);
-  lds_barrier();
+  if constexpr (SCORE) {
+    stage(cur);
+    issue_k(cur, 0, 0, KS, kf);
+    issue_k(cur, 1, 0, KS, kf);
+    lds_barrier();
+  } else {
+    sample_keys(cur);
+    issue_k(cur, 0, 0, KS, kn);
+    issue_k(cur, 1, 0, KS, kn);
+    stage(cur);
+    lds_barrier();
+    set_references();
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = kn[t][ks];
+    lds_barrier();
+  }
 
   bool first = true;  // first pass of a chunk
   int turn = 0;       // of the flags
@@ -546,8 +570,13 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
     if (!has_next) break;
     if (nxt.u != cur.u) {
       if (SCORE) lds_barrier();  // every wave is done with the unit's queries (else: the barrier behind the statistics)
+      if constexpr (!SCORE) sample_keys(nxt);
       stage(nxt);
       lds_barrier();
+      if constexpr (!SCORE) {
+        set_references();
+        lds_barrier();
+      }
     }
     if constexpr (kW == 8) {
 #pragma unroll
