@@ -55,7 +55,10 @@ typedef enum {
   PKV_KERNEL_SCORE_ACCUM = 2, /* sweep 2 over K: per-key window scores      */
   PKV_KERNEL_POOL_SELECT = 3,
   PKV_KERNEL_GATHER = 4,
-  PKV_KERNEL_SCORE_RESIDENT = 5 /* both sweeps, K held in registers (all layers) */
+  PKV_KERNEL_SCORE_RESIDENT = 5, /* both sweeps, K held in registers (all layers) */
+  PKV_KERNEL_SCORE_STREAM = 6,   /* one pass over K, few query rows (all layers) */
+  PKV_KERNEL_SCORE_SWEEP = 7     /* streaming sweeps over K, many query rows or
+                                    supplied denominators (all layers)       */
 } pkv_kernel_id;
 
 int pkv_compress_layers_profiled(
@@ -85,6 +88,23 @@ int pkv_compress_layers_profiled(
  */
 int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
                    void* stream);
+
+/*
+ * Test aid, HOST only (no device is touched): which kernel scores a call over
+ * L layers of desc's shape on a device of 256 compute units or more, and what
+ * it keeps in the last region of the workspace, where the pooled scores lie
+ * later on.
+ *
+ * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _SWEEP, _RESIDENT, or
+ *                _ACCUM for the per-layer kernels.
+ * scratch_bytes  written: bytes a launch addresses in that region.
+ * scratch_room   written: bytes from the region's start to the end of the
+ *                pkv_workspace_bytes(desc, L) bytes.
+ * Returns PKV_OK, PKV_ERR_INVALID_ARG or PKV_ERR_UNSUPPORTED.
+ */
+int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L,
+                      int32_t lse_supplied, int32_t* kernel_id,
+                      size_t* scratch_bytes, size_t* scratch_room);
 
 #ifdef __cplusplus
 }

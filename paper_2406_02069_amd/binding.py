@@ -28,7 +28,7 @@ DESC_FLAGS = 0
 EXPORTS = ["pkv_budgets", "pkv_workspace_bytes", "pkv_compress_layer", "pkv_compress_layer_noalloc", "pkv_compress_layers",
            "pkv_compress_layers_lse", "pkv_compress_layers_paged", "pkv_compress_layers_profiled",
            "pkv_budgets_schedule", "pkv_attention_recall", "pkv_decode_attention", "pkv_decode_workspace_bytes", "pkv_decode_attention_layers",
-           "pkv_decode_layers_workspace_bytes", "pkv_probe_read", "pkv_status_string"]
+           "pkv_decode_layers_workspace_bytes", "pkv_probe_read", "pkv_scoring_route", "pkv_status_string"]
 
 
 class PkvError(RuntimeError):
@@ -420,7 +420,21 @@ def probe_read(buf: torch.Tensor, sink: torch.Tensor) -> None:
         raise PkvError(rc, "pkv_probe_read")
 
 
-KERNEL_NAMES = ["score_stats", "score_finalize", "score_accum", "pool_select", "gather", "score_resident"]
+KERNEL_NAMES = ["score_stats", "score_finalize", "score_accum", "pool_select", "gather", "score_resident", "score_stream",
+                "score_sweep"]
+
+
+def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False):
+    """pkv_scoring_route: (kernel name, scratch bytes, room for them) of a call over L layers.  Touches no device."""
+    lib = load()
+    lib.pkv_scoring_route.argtypes = [ctypes.POINTER(LayerDesc), ctypes.c_int32, ctypes.c_int32] + [ctypes.c_void_p] * 3
+    lib.pkv_scoring_route.restype = ctypes.c_int
+    kernel, used, room = ctypes.c_int32(), ctypes.c_size_t(), ctypes.c_size_t()
+    rc = lib.pkv_scoring_route(ctypes.byref(desc), L, int(lse_supplied), ctypes.byref(kernel), ctypes.byref(used),
+                               ctypes.byref(room))
+    if rc != OK:
+        raise PkvError(rc, "pkv_scoring_route")
+    return KERNEL_NAMES[kernel.value], used.value, room.value
 
 
 class HipEvents:

@@ -172,14 +172,17 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
 
 // How the one-pass kernel for few query rows serves a call: layers per launch (0: it does not), workgroups, and
 // statistics kept per workgroup.  Whether it does is a matter of one layer's shape alone: a call over many layers gives
-// the same results as one call per layer.  (The statistics words lie in the part of the workspace that holds the pooled
-// scores later on.)
+// the same results as one call per layer.
+// The statistics words lie in the part of the workspace that holds the pooled scores later on: rows * 8 bytes in less
+// than twice as many slots as there are items, in the place of 4 bytes per key.  From N = 4 * rows on (128 keys, 256 at
+// 33 .. 64 rows) that fits whatever the number of layers and heads; shorter prompts go to the resident kernel.
 struct StreamPlan {
-  int layers, grid, ring;
+  int layers, grid, ring, rows;  // rows: padded to 32 or 64
+  size_t stats_bytes() const { return (size_t)grid * ring * rows * 8; }
 };
 static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
-  StreamPlan p = {0, 0, 0};
-  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok || !device_fits_resident()) return p;
+  StreamPlan p = {0, 0, 0, plan.R <= 32 ? 32 : 64};
+  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok || d.N < 4 * p.rows) return p;
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
   const int64_t parts = (d.N + stream_item_keys(plan.R) - 1) / stream_item_keys(plan.R);
   const int64_t per_layer = parts * plan.BH;
@@ -221,6 +224,9 @@ constexpr int64_t kSweepMaxKeysLse = 4 << 20;
 constexpr int kSweepMinChunks = 32;
 struct SweepPlan {
   int C, nchunk, Rs;
+  size_t stats_bytes(const Plan& plan, bool lse_mode) const {
+    return lse_mode ? 0 : (size_t)plan.L * plan.BH * nchunk * Rs * 8;
+  }
 };
 static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
   SweepPlan p = {0, 0, 0};
@@ -254,7 +260,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   if (rec) rec->begin(stream);
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
-  StreamPlan sp = {0, 0, 0};
+  StreamPlan sp = {0, 0, 0, 0};
   SweepPlan wp = {0, 0, 0};
   if (any_scores && resident) sp = stream_plan(plan, d, lse_mode);
   if (any_scores && resident) wp = sweep_plan(plan, d, lse_mode);
@@ -304,11 +310,9 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         sa.layer[i].k_l = descs[l0 + i].k_l;
         sa.uniform = (i == 0 || sa.uniform) && !seq_lens && descs[l0 + i].k_l < d.N ? 1 : 0;
       }
-      const int64_t rows = plan.R <= 32 ? 32 : 64;
       sa.seq_lens = seq_lens;
       sa.raw = raw + (size_t)l0 * plan.BH * d.N;
       sa.stats = reinterpret_cast<unsigned long long*>(pooled_ws);
-      sa.dump = reinterpret_cast<float*>(sa.stats + (int64_t)sp.grid * sp.ring * rows);
       sa.grid = sp.grid; sa.ring = sp.ring;
       sa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       sa.L = nl; sa.B = d.B; sa.Hq = d.Hq; sa.Hkv = d.Hkv; sa.G = plan.G; sa.alpha = d.alpha; sa.N = d.N; sa.R = plan.R;
@@ -870,6 +874,24 @@ int pkv_compress_layers_profiled(int32_t L, const pkv_layer_desc* descs, const v
                                       paged, block_tables);
   *n_used = rec.used;
   return rc;
+}
+
+int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t lse_supplied, int32_t* kernel_id,
+                      size_t* scratch_bytes, size_t* scratch_room) {
+  const int rc = check_desc(desc);
+  if (rc != PKV_OK) return rc;
+  if (L < 1 || L > kMaxLayers || !kernel_id || !scratch_bytes || !scratch_room) return PKV_ERR_INVALID_ARG;
+  const Plan plan = make_plan(*desc, L);
+  const bool lse_mode = lse_supplied != 0;
+  *kernel_id = PKV_KERNEL_SCORE_ACCUM;
+  *scratch_bytes = 0;
+  *scratch_room = plan.total - plan.off_pooled;
+  if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return PKV_OK;
+  const SweepPlan wp = sweep_plan(plan, *desc, lse_mode);
+  const StreamPlan sp = stream_plan(plan, *desc, lse_mode);
+  *kernel_id = wp.C > 0 ? PKV_KERNEL_SCORE_SWEEP : (sp.layers > 0 ? PKV_KERNEL_SCORE_STREAM : PKV_KERNEL_SCORE_RESIDENT);
+  *scratch_bytes = wp.C > 0 ? wp.stats_bytes(plan, lse_mode) : (sp.layers > 0 ? sp.stats_bytes() : 0);
+  return PKV_OK;
 }
 
 int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink, void* stream) {

@@ -112,7 +112,6 @@ struct StreamArgs {
   float* raw;                 // [U][N] un-pooled scores
   unsigned long long* stats;  // [grid][ring][32 or 64] statistics of a workgroup's last items (log2 domain;
                               // the sign bit of the sum carries a phase); cleared before the launch
-  float* dump;                // [grid][64] written, never read
   int32_t* err;
   int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
   int32_t uniform;            // 1: every unit has N keys and none is kept whole

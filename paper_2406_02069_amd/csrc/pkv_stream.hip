@@ -366,8 +366,6 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     if (ln < ROWS) s_f[wave * ROWS + ln] = make_float2(m, z);
   };
 
-  float* dump = a.dump + blockIdx.x * 64;
-
   // Pending item (the one before): its p in LDS, waiting for normalisers.
   Item pend;
   pend.u = -1;
@@ -413,11 +411,9 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
           s1 = __builtin_fmaf(p[3], w[rt][q][3], s1);
         }
       const float s = both_halves(s0 + s1);
-      const int key = tile_key(d, t) + l32;
-      // (lanes without a score write to a spare line: a store under a condition would make the waits for keys that
-      // follow allow for either way in)
-      float* dst = (hf == 0 && key < npre) ? raw + key : dump + lane;
-      *dst = s;
+      // (both halves of the wave hold the score; keys without one write into the unit's first place behind the prefix,
+      // which nobody reads: a store under a condition would make the waits for keys that follow allow for either way in)
+      raw[min(tile_key(d, t) + l32, npre)] = s;
     }
   };
 

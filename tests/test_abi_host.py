@@ -302,3 +302,34 @@ def test_decode_attention_layers_rejects_bad_arguments():
     one = (binding.DecodeDesc * 1)(desc(k_cap=100, c_sb=8 * 100 * 128, c_sh=100 * 128))
     assert lib.pkv_decode_layers_workspace_bytes(1, one) == 0                   # a single range per head: no partials
     assert lib.pkv_decode_layers_workspace_bytes(2, (binding.DecodeDesc * 2)(desc(), desc(Hq=16))) == 0
+
+
+def _shape(B, Hq, Hkv, d, N, alpha, flags=0):
+    return _desc(B=B, Hq=Hq, Hkv=Hkv, d=d, N=N, alpha=alpha, k_l=alpha, flags=flags, q_sb=Hq * alpha * d, q_sh=alpha * d,
+                 q_st=d, kv_sb=Hkv * N * d, kv_sh=N * d, kv_st=d, o_sb=Hkv * alpha * d, o_sh=alpha * d, o_st=d)
+
+
+def test_statistics_of_the_scoring_kernels_fit_the_workspace():
+    # short prompts on many units, item and chunk edges, launches of many layers: what a scoring kernel keeps beside its
+    # scores ends inside the workspace, and the kernel that takes a call does not depend on the number of layers
+    taken = set()
+    for Hkv, G, alpha in ((1, 1, 8), (8, 4, 8), (8, 8, 8), (8, 2, 32), (32, 1, 8), (1, 8, 4), (300, 1, 1), (8, 8, 32), (8, 8, 64)):
+        for d in (64, 128):
+            for B in (1, 3, 40):
+                for N in (9, 32, 40, 64, 100, 127, 128, 190, 250, 255, 256, 300, 511, 513, 1023, 1025, 4097, 20000, 131072):
+                    if N <= alpha:
+                        continue
+                    desc = _shape(B, G * Hkv, Hkv, d, N, alpha)
+                    kernels = set()
+                    for L in (1, 2, 32, 33, 126):
+                        kernel, used, room = binding.scoring_route(desc, L)
+                        assert used <= room, (kernel, B, Hkv, G, alpha, d, N, L, used, room)
+                        kernels.add(kernel)
+                        _, used, room = binding.scoring_route(desc, L, lse_supplied=True)
+                        assert used <= room
+                    assert len(kernels) == 1, (B, Hkv, G, alpha, d, N, kernels)
+                    taken |= kernels
+    assert taken == {"score_resident", "score_stream", "score_sweep"}
+    assert binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8, flags=binding.FLAG_STREAM_SCORING))[0] == "score_accum"
+    with pytest.raises(binding.PkvError):
+        binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8), 0)

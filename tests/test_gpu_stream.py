@@ -90,3 +90,19 @@ def test_references_that_do_not_fit(G):
     out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
     torch.cuda.synchronize()
     compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+
+
+@pytest.mark.parametrize("L,B,Hkv,G,alpha,N", [(1, 1, 1, 1, 8, 40), (1, 1, 8, 4, 8, 100), (32, 1, 8, 4, 8, 100), (40, 1, 8, 4, 8, 127),
+                                               (40, 1, 8, 4, 8, 128), (33, 1, 8, 8, 8, 250), (33, 1, 8, 8, 8, 256), (3, 2, 8, 8, 8, 600)])
+def test_nothing_is_written_behind_the_workspace(L, B, Hkv, G, alpha, N):
+    data = [_inputs(B, G * Hkv, Hkv, 128, N, alpha, seed=900 + l) for l in range(L)]
+    print("guard", L, B, Hkv, G, alpha, N, flush=True)
+    call = binding.LayersCall([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], [alpha + 5] * L, synth.POOL_MAX, 7,
+                              want_scores=True)
+    need = binding.workspace_bytes(call.descs[0], L)
+    guarded = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device=DEV)   # (the guard is this test's own memory)
+    call.workspace = guarded[:need]
+    outs = call.run()
+    torch.cuda.synchronize()
+    assert bool((guarded[need:] == 0x5A).all())
+    compare_layer(*data[-1], alpha + 5, alpha, synth.POOL_MAX, 7, None, outs[-1])
