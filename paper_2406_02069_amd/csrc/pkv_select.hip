@@ -499,7 +499,10 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
         if (256 * jj + c < lim) v[jj][c] += raw[q * rb_stride + p0 + 256 * jj + c];
   }
   reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
-  if (tid == 0) sel[0] = 0xFFFFFFFFu;
+  if (tid == 0) {
+    sel[0] = 0xFFFFFFFFu;
+    sel[3] = 0u;
+  }
 #pragma unroll
   for (int jj = 0; jj < NJ; ++jj) v[jj] *= a.inv_G;
   if (r > 0) {
@@ -699,12 +702,11 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
     if (need == n_open) {
       T = edge - 1u;  // the whole bin is kept
     } else if (n_open <= (uint32_t)kOpen) {
-      // the bin's keys, as distances from its edge, in hist (cleared by find_bin); their order does not matter
-      if (tid == 0) sel[0] = 0u;
-      lds_barrier();
+      // the bin's keys, as distances from its edge, in hist (cleared by find_bin); their order does not matter.  They are
+      // counted in sel[3], which nothing else uses: other waves may still be reading the bin from sel[0].
       for (uint32_t i = tid; i < n_list; i += NT) {
         const uint32_t k = lkey[i];
-        if (bin_of(k) == bin) hist[atomicAdd(&sel[0], 1u)] = k - edge;
+        if (bin_of(k) == bin) hist[atomicAdd(&sel[3], 1u)] = k - edge;
       }
       lds_barrier();
       // the need-th largest: every key counts those above it and those not below it (entries behind the last are 0)

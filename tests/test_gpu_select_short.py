@@ -74,3 +74,16 @@ def test_many_units_of_ragged_lengths():
     Q, K, V = _inputs(N, alpha, seed=5, B=6)
     lens = np.array([20000, 8200, 8201, 4104, 300, 40], dtype=np.int32)
     _check(Q, K, V, 200, synth.POOL_MAX, 7, lens)
+
+
+@pytest.mark.parametrize("N,kk,scale", [(520, 40, 0.02), (520, 200, 0.004), (4000, 300, 0.02), (1500, 90, 0.1)])
+def test_many_units_rank_the_keys_of_one_bin(N, kk, scale):
+    # scores so close together that the cut falls into a bin of up to some hundred keys, which are ranked against each other:
+    # the waves read the bin while its keys are being counted
+    alpha, B, Hkv = 8, 128, 16
+    Q, K, V = _inputs(N, alpha, seed=N + kk, scale=scale, B=B, Hq=Hkv, Hkv=Hkv)
+    print("select bins", N, kk, scale, flush=True)
+    out = binding.compress_layer(Q, K, V, alpha + kk, synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    order = torch.sort(out[4][:, :, :N - alpha], dim=2, descending=True, stable=True)[1][:, :, :kk]
+    assert torch.equal(out[2][:, :, :kk].long(), order.sort(dim=2)[0])
