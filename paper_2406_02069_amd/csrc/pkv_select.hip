@@ -12,9 +12,10 @@
 //      histogram over the distance from a typical large key: the bin in which the count reaches kk bounds T from below (kk
 //      groups hold a key that large), with one LDS addition per group instead of one per key.  (2) The keys at or
 //      above the bound, a small multiple of kk, move to a list in LDS, in position order.  (3) A histogram of the list
-//      finds T's bin; (4) the few keys in that bin are ranked against each other.  Lists that do not fit (equal
-//      scores, a budget of nearly everything) take a plain binary search over all keys, one bit per round.
-//   C. ordered emission from the list: keys > T and the lowest positions with key == T, in ascending order, followed
+//      finds T's bin; (4) the few keys in that bin are ranked against each other.  For more than a quarter of the
+//      prefix, where the list does not fit (many equal scores) or there are not enough groups with a positive key, the
+//      histograms go over all keys.
+//   C. ordered emission, from the list where there is one: keys > T and the lowest positions with key == T, in ascending order, followed
 //      by the window positions.
 // What bounds it: the latency of some fifteen steps between barriers, 0.6 - 1.4 us each, beside the loads (5.8 of 19 us
 // for 256 units of 32k keys); the work over all keys (one maximum and one comparison each) is short.  Measured with the
@@ -437,10 +438,10 @@ __device__ __forceinline__ void select_long(const float* raw, int nrb, size_t rb
 }
 
 
-// The bin in which the count over ascending bins reaches kk: sel[0] = bin (untouched if there is none), sel[1] = count
-// before it, sel[2] = count in it.  Thread t owns bins 2t, 2t + 1 and leaves them cleared.  Every thread returns after
-// the answer is there.  (Bins 0 .. HIST - 1, `scan` holds NW entries.)
-__device__ __forceinline__ void find_bin(uint32_t* hist, uint32_t kk, uint32_t* scan, uint32_t* sel) {
+// The bin in which the count over ascending bins reaches kk: sel[0] = bin, sel[1] = count before it, sel[2] = count in it
+// (untouched if there is none).  Returns the count over all bins.  Thread t owns bins 2t, 2t + 1 and leaves them cleared.
+// Every thread returns after the answer is there.  (Bins 0 .. HIST - 1, `scan` holds NW entries.)
+__device__ __forceinline__ uint32_t find_bin(uint32_t* hist, uint32_t kk, uint32_t* scan, uint32_t* sel) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint2 h = reinterpret_cast<uint2*>(hist)[tid];
@@ -458,6 +459,7 @@ __device__ __forceinline__ void find_bin(uint32_t* hist, uint32_t kk, uint32_t* 
     sel[2] = in1 ? h.y : h.x;
   }
   lds_barrier();
+  return total;
 }
 
 // A prefix of at most 1024 * PER keys.  Wave w owns positions [w * 64 * PER, (w + 1) * 64 * PER), lane l of it the four
@@ -499,10 +501,7 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
         if (256 * jj + c < lim) v[jj][c] += raw[q * rb_stride + p0 + 256 * jj + c];
   }
   reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
-  if (tid == 0) {
-    sel[0] = 0xFFFFFFFFu;
-    sel[3] = 0u;
-  }
+  if (tid == 0) sel[3] = 0u;
 #pragma unroll
   for (int jj = 0; jj < NJ; ++jj) v[jj] *= a.inv_G;
   if (r > 0) {
@@ -620,23 +619,51 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
   int gs = 1;
   while (2 * gs <= NJ && 4 * gs * kk <= npre) gs *= 2;
   // Bins, descending: 0 .. 1023 for keys from the reference up, 1/8 of a binade each (2^20 units of the bit pattern),
-  // 1024 .. 2047 for those below it, 2^shift each: 1/64 of a binade (16 binades) or, where T lies deeper, 1/8.
-  constexpr int kUp = 20;
+  // 1024 .. 2047 for those below it, 1/64 of a binade each (2^17 units, 16 binades in all); the first and the last bin
+  // are open to the outside.
+  constexpr int kUp = 20, kDown = 17;
   constexpr uint32_t kMid = HIST / 2;
-  int shift = 17;
   auto bin_of = [&](uint32_t k) -> uint32_t {
-    return k >= ref ? kMid - 1u - min((k - ref) >> kUp, kMid - 1u) : kMid + ((ref - 1u - k) >> shift);
+    return k >= ref ? kMid - 1u - min((k - ref) >> kUp, kMid - 1u) : kMid + min((ref - 1u - k) >> kDown, kMid - 1u);
   };
-  // smallest key of a bin (0: there is no positive one)
+  // smallest and largest key of a bin that holds one (never 0, the mark of a position that does not exist)
   auto lower_edge = [&](uint32_t bin) -> uint32_t {
-    if (bin < kMid) return ref + ((kMid - 1u - bin) << kUp);
-    const unsigned long long down = (unsigned long long)(bin - kMid + 1u) << shift;
-    return down < ref ? ref - (uint32_t)down : 0u;
+    if (bin < kMid) return max(ref + ((kMid - 1u - bin) << kUp), 1u);
+    const uint32_t down = (bin - kMid + 1u) << kDown;
+    return bin < HIST - 1u && down < ref ? ref - down : 1u;
   };
-  uint32_t n_list = 0u, bound = 0u;
-  bool ok = false;
-  for (int attempt = 0; attempt < 2 && !ok; ++attempt) {
-    shift = attempt == 0 ? 17 : 20;
+  auto upper_edge = [&](uint32_t bin) -> uint32_t {
+    if (bin >= kMid) return ref - 1u - ((bin - kMid) << kDown);
+    const uint32_t up = ref + ((kMid - bin) << kUp) - 1u;
+    return bin > 0u && up >= ref ? up : 0xFFFFFFFFu;
+  };
+  constexpr uint32_t kOpen = 512u;  // keys of a bin that are ranked against each other
+  uint32_t n_list = 0u, T = 0u, lo = 0u, hi = 0u, need = (uint32_t)kk, n_open = 0u;  // (T's bin: edges, rank in it, keys)
+  bool ok = false, have_bin = false;
+  // the need-th largest of the n_open distances in hist (entries behind the last are 0): every key counts those above it
+  // and those not below it
+  auto rank_open = [&]() {
+    lds_barrier();
+    if ((uint32_t)tid < n_open) {
+      const uint32_t d = hist[tid];
+      uint32_t above = 0u, from = 0u;
+      for (uint32_t j = 0; j < n_open; j += 4) {
+        const u32x4 q = *reinterpret_cast<const u32x4*>(hist + j);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          above += q[c] > d ? 1u : 0u;
+          from += q[c] >= d ? 1u : 0u;
+        }
+      }
+      if (above < need && need <= from) sel[1] = lo + d;
+    }
+    lds_barrier();
+    T = __builtin_amdgcn_readfirstlane(sel[1]);
+  };
+  // The list pays for small shares of the prefix.  256 units of 32k keys, with and without it: kk = 0.02 of the prefix 22 and
+  // 30 us, 0.1 27 and 32, 0.2 32 and 34, 0.3 38 and 37, 0.5 42 and 39; of 8k keys 15 and 16, 13 and 14, 14 and 14, 16 and 15,
+  // 17 and 15.
+  if (4 * kk <= npre) {  // (uniform)
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       uint32_t m = 0u;
@@ -644,88 +671,68 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
       for (int jj = 0; jj < NJ; ++jj) {
         m = max(m, key[jj][c]);
         if (((jj + 1) & (gs - 1)) == 0) {  // uniform
-          const uint32_t bin = bin_of(m);
-          if (m != 0u && bin < (uint32_t)HIST) atomicAdd(&hist[bin], 1u);
+          if (m != 0u) atomicAdd(&hist[bin_of(m)], 1u);
           m = 0u;
         }
       }
     }
     lds_barrier();
-    find_bin(hist, (uint32_t)kk, scan + NW, sel);
-    const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
-    if (bin == 0xFFFFFFFFu) continue;
-    bound = lower_edge(bin);
-    if (bound == 0u) continue;  // a key of zero would have to be told from none
-    // the keys at or above the bound: counted per wave, then listed in position order
-    uint32_t cnt = 0u;
+    if (find_bin(hist, (uint32_t)kk, scan + NW, sel) >= (uint32_t)kk) {
+      // the keys at or above the bound: counted per wave, then listed in position order
+      const uint32_t bound = lower_edge(__builtin_amdgcn_readfirstlane(sel[0]));
+      uint32_t cnt = 0u;
 #pragma unroll
-    for (int jj = 0; jj < NJ; ++jj)
+      for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) cnt += (uint32_t)__popcll(__ballot(key[jj][c] >= bound));
-    if (lane == 0) scan[wave] = cnt;
-    lds_barrier();
-    uint32_t base = sum_before(scan, wave, n_list);
-    if (n_list > kCap) break;  // (uniform)
-    if (cnt != 0u) {
-      const uint32_t bnd = (uint32_t)fresh((int)bound);
+        for (int c = 0; c < 4; ++c) cnt += (uint32_t)__popcll(__ballot(key[jj][c] >= bound));
+      if (lane == 0) scan[wave] = cnt;
+      lds_barrier();
+      uint32_t base = sum_before(scan, wave, n_list);
+      ok = n_list <= kCap;  // (uniform)
+      if (ok && cnt != 0u) {
+        const uint32_t bnd = (uint32_t)fresh((int)bound);
 #pragma unroll
-      for (int jj = 0; jj < NJ; ++jj) {
-        unsigned long long b[4];
+        for (int jj = 0; jj < NJ; ++jj) {
+          unsigned long long b[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) b[c] = __ballot(key[jj][c] >= bnd);
-        if ((b[0] | b[1] | b[2] | b[3]) == 0ull) continue;
-        uint32_t at = base + bits_below(b[0]) + bits_below(b[1]) + bits_below(b[2]) + bits_below(b[3]);
+          for (int c = 0; c < 4; ++c) b[c] = __ballot(key[jj][c] >= bnd);
+          if ((b[0] | b[1] | b[2] | b[3]) == 0ull) continue;
+          uint32_t at = base + bits_below(b[0]) + bits_below(b[1]) + bits_below(b[2]) + bits_below(b[3]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (key[jj][c] >= bnd) {
-            lkey[at] = key[jj][c];
-            lpos[at] = (uint16_t)(p0 + 256 * jj + c);
-            ++at;
+          for (int c = 0; c < 4; ++c) {
+            if (key[jj][c] >= bnd) {
+              lkey[at] = key[jj][c];
+              lpos[at] = (uint16_t)(p0 + 256 * jj + c);
+              ++at;
+            }
           }
+          base += (uint32_t)(__popcll(b[0]) + __popcll(b[1]) + __popcll(b[2]) + __popcll(b[3]));
         }
-        base += (uint32_t)(__popcll(b[0]) + __popcll(b[1]) + __popcll(b[2]) + __popcll(b[3]));
       }
     }
-    ok = true;
   }
-  uint32_t T = 0u;
   if (ok) {
     lds_barrier();  // the list is complete
     for (uint32_t i = tid; i < n_list; i += NT) atomicAdd(&hist[bin_of(lkey[i])], 1u);
     lds_barrier();
-    find_bin(hist, (uint32_t)kk, scan + NW, sel);  // (there is such a bin: the list holds at least kk keys)
+    (void)find_bin(hist, (uint32_t)kk, scan + NW, sel);  // (there is such a bin: the list holds at least kk keys)
     const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
-    const uint32_t need = (uint32_t)kk - __builtin_amdgcn_readfirstlane(sel[1]);
-    const uint32_t n_open = __builtin_amdgcn_readfirstlane(sel[2]);
-    const uint32_t edge = lower_edge(bin);  // (>= bound >= 1)
-    constexpr int kOpen = 512;
+    need = (uint32_t)kk - __builtin_amdgcn_readfirstlane(sel[1]);
+    n_open = __builtin_amdgcn_readfirstlane(sel[2]);
+    lo = lower_edge(bin);
     if (need == n_open) {
-      T = edge - 1u;  // the whole bin is kept
-    } else if (n_open <= (uint32_t)kOpen) {
+      T = lo - 1u;  // the whole bin is kept
+    } else if (n_open <= kOpen) {
       // the bin's keys, as distances from its edge, in hist (cleared by find_bin); their order does not matter.  They are
       // counted in sel[3], which nothing else uses: other waves may still be reading the bin from sel[0].
       for (uint32_t i = tid; i < n_list; i += NT) {
         const uint32_t k = lkey[i];
-        if (bin_of(k) == bin) hist[atomicAdd(&sel[3], 1u)] = k - edge;
+        if (bin_of(k) == bin) hist[atomicAdd(&sel[3], 1u)] = k - lo;
       }
-      lds_barrier();
-      // the need-th largest: every key counts those above it and those not below it (entries behind the last are 0)
-      if ((uint32_t)tid < n_open) {
-        const uint32_t d = hist[tid];
-        uint32_t above = 0u, from = 0u;
-        for (uint32_t j = 0; j < n_open; j += 4) {
-          const u32x4 q = *reinterpret_cast<const u32x4*>(hist + j);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            above += q[c] > d ? 1u : 0u;
-            from += q[c] >= d ? 1u : 0u;
-          }
-        }
-        if (above < need && need <= from) sel[1] = edge + d;
-      }
-      lds_barrier();
-      T = __builtin_amdgcn_readfirstlane(sel[1]);
+      rank_open();
     } else {
+      hi = upper_edge(bin);
+      have_bin = true;
       ok = false;
     }
   }
@@ -762,23 +769,65 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
     return true;
   }
 
-  // ---- the plain way: binary search for T over all keys (all 32 bits, whatever bit patterns the scores hold; a
-  // position that does not exist carries key 0 and is never counted, T >= 1 in every comparison) ----
-  T = 0u;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = T | (1u << bit);
-    uint32_t cnt = 0u;
+  // ---- without a list: histograms over all keys, the first one as above, the next ones over the keys of the bin found, in
+  // 2048 parts, until few keys are left in it or all of them are equal.  A thread adds up runs of keys of one bin (pooling
+  // windows share their largest score) before it touches the histogram.  Keys of 0 are counted nowhere: if the others are
+  // fewer than kk, T is 0.  Measured against a search of T over all keys, one bit per round: 256 units of 32k keys, kk = 0.6
+  // or 0.95 of the prefix, 58 - 61 -> 40 us; 7 / 8 of the scores exact zeros, kk = 0.6, 77 -> 37 us ----
+  auto count_keys = [&](auto is_open, auto bin_fn) {
+    uint32_t run_bin = 0u, run = 0u;
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) cnt += (uint32_t)__popcll(__ballot(key[jj][c] >= cand));
-    uint32_t* slot = scan + ((bit & 1) ? NW : 0);  // two sets of per-wave slots: one barrier per bit
-    if (lane == 0) slot[wave] = cnt;
-    __syncthreads();
-    uint32_t c = 0u;
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t k = key[jj][c];
+        if (is_open(k)) {
+          const uint32_t bin = bin_fn(k);
+          if (bin != run_bin) {
+            if (run != 0u) atomicAdd(&hist[run_bin], run);
+            run_bin = bin;
+            run = 0u;
+          }
+          ++run;
+        }
+      }
+    if (run != 0u) atomicAdd(&hist[run_bin], run);
+    lds_barrier();
+  };
+  if (!have_bin) {
+    count_keys([](uint32_t k) { return k != 0u; }, bin_of);
+    have_bin = find_bin(hist, need, scan + NW, sel) >= need;
+    if (have_bin) {
+      const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
+      need -= __builtin_amdgcn_readfirstlane(sel[1]);
+      n_open = __builtin_amdgcn_readfirstlane(sel[2]);
+      lo = lower_edge(bin);
+      hi = upper_edge(bin);
+    }
+  }
+  if (have_bin) {
+    while (need != n_open && n_open > kOpen && lo != hi) {
+      const int bits = 32 - __clz((int)(hi - lo)), part = bits > 11 ? bits - 11 : 0;
+      count_keys([&](uint32_t k) { return k >= lo && k <= hi; }, [&](uint32_t k) { return (hi - k) >> part; });
+      (void)find_bin(hist, need, scan + NW, sel);
+      const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
+      need -= __builtin_amdgcn_readfirstlane(sel[1]);
+      n_open = __builtin_amdgcn_readfirstlane(sel[2]);
+      hi -= bin << part;
+      if (((hi - lo) >> part) != 0u) lo = hi - (1u << part) + 1u;
+    }
+    if (need == n_open) {
+      T = lo - 1u;
+    } else if (lo == hi) {
+      T = lo;
+    } else {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) c += slot[w];
-    if (c >= (uint32_t)kk) T = cand;
+      for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (key[jj][c] >= lo && key[jj][c] <= hi) hist[atomicAdd(&sel[3], 1u)] = key[jj][c] - lo;
+      rank_open();
+    }
   }
   uint32_t cgt = 0u, ceq = 0u;
   lim = fresh(npre) - p0;
@@ -797,7 +846,7 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
   __syncthreads();
   uint32_t gt_total, eq_total;
   uint32_t gt_before = sum_before(scan, wave, gt_total), eq_before = sum_before(scan + NW, wave, eq_total);
-  const uint32_t need_eq = (uint32_t)kk - gt_total;  // keys equal to T to take, lowest positions first (>= 1)
+  const uint32_t need_eq = (uint32_t)kk - gt_total;  // keys equal to T to take, lowest positions first
   lim = fresh(npre) - p0;
   T = (uint32_t)fresh((int)T);
 #pragma unroll

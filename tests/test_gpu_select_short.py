@@ -87,3 +87,30 @@ def test_many_units_rank_the_keys_of_one_bin(N, kk, scale):
     torch.cuda.synchronize()
     order = torch.sort(out[4][:, :, :N - alpha], dim=2, descending=True, stable=True)[1][:, :, :kk]
     assert torch.equal(out[2][:, :, :kk].long(), order.sort(dim=2)[0])
+
+
+@pytest.mark.parametrize("N", [520, 4000, 7900, 16100, 32500])
+@pytest.mark.parametrize("share", [0.02, 0.3, 0.55, 0.97])
+@pytest.mark.parametrize("kind", ["spread", "sharp", "flat", "zeros behind", "zeros between", "two values", "equal"])
+def test_budgets_of_every_share_of_the_prefix(N, share, kind):
+    # lists that do not fit, positive keys that are fewer than the budget or sit in few groups, cuts in the last bin,
+    # bins of equal keys
+    alpha, B, Hkv = 4, 2, 8
+    Q, K, V = _inputs(N, alpha, seed=N, scale={"sharp": 8.0, "flat": 0.002}.get(kind, 1.0), B=B, Hq=Hkv, Hkv=Hkv)
+    far = -30 * Q[:, :, :1]                                   # exact zeros
+    if kind == "zeros behind":
+        K[:, :, N // 8:] = far
+    if kind == "zeros between":
+        K[:, :, torch.arange(N, device=DEV) % 3 != 0] = far
+    if kind == "two values":
+        K[:, :, ::2] = K[:, :, :1]
+        K[:, :, 1::2] = K[:, :, 1:2]
+    if kind == "equal":
+        K[:] = K[:, :, :1]
+    kk = max(int(share * (N - alpha)), 1)
+    print("select share", N, share, kind, flush=True)
+    for pool, pw in ((synth.POOL_NONE, 1), (synth.POOL_MAX, 7)):
+        out = binding.compress_layer(Q, K, V, alpha + kk, pool, pw, want_scores=True)
+        torch.cuda.synchronize()
+        order = torch.sort(out[4][:, :, :N - alpha], dim=2, descending=True, stable=True)[1][:, :, :kk]
+        assert torch.equal(out[2][:, :, :kk].long(), order.sort(dim=2)[0])
