@@ -170,19 +170,19 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
   return plan.resident_ok && (lse_mode || device_fits_resident());
 }
 
-// How the one-pass kernel for few query rows serves a call: layers per launch (0: it does not), workgroups, and
-// statistics kept per workgroup.  Whether it does is a matter of one layer's shape alone: a call over many layers gives
+// How the one-pass kernel for few query rows serves a call: layers per launch (0: it does not), workgroups, and items of a
+// launch at most.  Whether it does is a matter of one layer's shape alone: a call over many layers gives
 // the same results as one call per layer.
-// The statistics words lie in the part of the workspace that holds the pooled scores later on: rows * 8 bytes in less
-// than twice as many slots as there are items, in the place of 4 bytes per key.  From N = 4 * rows on (128 keys, 256 at
-// 33 .. 64 rows) that fits whatever the number of layers and heads; shorter prompts go to the resident kernel.
+// The statistics words lie in the part of the workspace that holds the pooled scores later on: rows * 8 bytes
+// per item in the place of 4 bytes per key.  From N = 2 * rows on (64 keys, 128 at 33 .. 64 rows) that fits whatever the
+// number of layers and heads; shorter prompts go to the resident kernel.
 struct StreamPlan {
-  int layers, grid, ring, rows;  // rows: padded to 32 or 64
-  size_t stats_bytes() const { return (size_t)grid * ring * rows * 8; }
+  int layers, grid, items, rows;  // rows: padded to 32 or 64
+  size_t stats_bytes() const { return (size_t)items * rows * 8; }
 };
 static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
   StreamPlan p = {0, 0, 0, plan.R <= 32 ? 32 : 64};
-  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok || d.N < 4 * p.rows) return p;
+  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok || d.N < 2 * p.rows) return p;
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
   const int64_t parts = (d.N + stream_item_keys(plan.R) - 1) / stream_item_keys(plan.R);
   const int64_t per_layer = parts * plan.BH;
@@ -199,8 +199,7 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
   const int64_t items = nl * per_layer;
   p.layers = (int)nl;
   p.grid = items < kStreamGrid ? (int)items : kStreamGrid;
-  p.ring = 1;
-  while (p.ring < kStreamRing && (int64_t)p.ring * kStreamGrid < items) p.ring *= 2;
+  p.items = (int)items;
   return p;
 }
 
@@ -313,7 +312,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       sa.seq_lens = seq_lens;
       sa.raw = raw + (size_t)l0 * plan.BH * d.N;
       sa.stats = reinterpret_cast<unsigned long long*>(pooled_ws);
-      sa.grid = sp.grid; sa.ring = sp.ring;
+      sa.grid = sp.grid; sa.items = sp.items;
       sa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       sa.L = nl; sa.B = d.B; sa.Hq = d.Hq; sa.Hkv = d.Hkv; sa.G = plan.G; sa.alpha = d.alpha; sa.N = d.N; sa.R = plan.R;
       sa.d = d.d;

@@ -104,18 +104,17 @@ constexpr int kStreamGrid = 256;    // persistent workgroups, one per compute un
 constexpr int kStreamMaxRows = 64;  // G * alpha
 constexpr int kStreamItems = 272;   // items of a workgroup per launch, at most (table in LDS)
 constexpr int kStreamUnits = 2048;  // layers x sequences per launch, at most (prefix table in LDS)
-constexpr int kStreamRing = 8;      // a workgroup's statistics are kept for that many items (a power of two)
 
 struct StreamArgs {
   ResidentLayer layer[kResidentMaxLayers];
   const int32_t* seq_lens;
   float* raw;                 // [U][N] un-pooled scores
-  unsigned long long* stats;  // [grid][ring][32 or 64] statistics of a workgroup's last items (log2 domain;
-                              // the sign bit of the sum carries a phase); cleared before the launch
+  unsigned long long* stats;  // [items][32 or 64] statistics of the items (log2 domain; the sign bit of the sum marks a
+                              // word as there); cleared before the launch
   int32_t* err;
   int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
   int32_t uniform;            // 1: every unit has N keys and none is kept whole
-  int32_t grid, ring;         // workgroups (kStreamGrid, fewer if there are fewer items); statistics kept per workgroup
+  int32_t grid, items;        // workgroups (kStreamGrid, fewer if there are fewer items); items, if every unit has N keys
   int32_t wait_ticks;
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;

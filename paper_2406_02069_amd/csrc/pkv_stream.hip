@@ -20,11 +20,11 @@
 //      to arrive, are read (8 bytes per row and item: a few per cent of the keys' traffic) and folded into the
 //      normalisers; its p, moved to LDS meanwhile, are weighted and summed over the rows; one score per key is written
 //      (already divided by G).
-// A word of statistics carries a phase bit and so announces itself (agent-scope relaxed atomics, cleared before the
-// launch).  They are requested a tile before they are used, in front of the keys requested at that place: a wave's
-// loads return in order, so a probe issued behind keys would hold the wave until those have arrived.  (For the same
-// reason there is one hop and not two, fold by one item and hand over: each hop costs a tile's time.)  A workgroup's
-// slot is written again eight items later; the phase bit keeps a late reader from taking the one for the other.
+// A word of statistics carries a mark, the sign bit of the sum, and so announces itself (agent-scope relaxed atomics, cleared
+// before the launch).  Every item has words of its own, written once: a workgroup that starts late or falls behind, however
+// far, finds what it waits for.  They are requested a tile before they are used, in front of the keys requested at that
+// place: a wave's loads return in order, so a probe issued behind keys would hold the wave until those have arrived.  (For
+// the same reason there is one hop and not two, fold by one item and hand over: each hop costs a tile's time.)
 // The reference is the same for all keys of a unit, so that equal keys get equal scores, bit for bit.
 // A row whose reference was too far below its logits (sum beyond 2^100) is recomputed by its wave with the exact
 // maximum, from memory (rare).
@@ -307,11 +307,9 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     return wall_clock64() - t0 > (long long)a.wait_ticks ||
            __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
   };
-  // statistics word of row r of item j, and the phase bit it carries
-  auto stat_word = [&](int j, int r) {
-    return a.stats + ((size_t)(j % kStreamGrid) * a.ring + ((j / kStreamGrid) & (a.ring - 1))) * ROWS + r;
-  };
-  auto stat_phase = [&](int j) { return ((uint32_t)(j / kStreamGrid) / (uint32_t)a.ring & 1u) ^ 1u; };
+  // statistics word of row r of item j; the mark that it is there
+  auto stat_word = [&](int j, int r) { return a.stats + (uint32_t)(j * ROWS + r); };
+  constexpr u64 kThere = 1ull << 63;
 
   // Statistics of the items of a unit: thread = (row, every PPL-th item).
   u64 sv[NPL];
@@ -327,13 +325,12 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     const int srow = min(ln & (ROWS - 1), a.R - 1), sitem = wave * (64 / ROWS) + ln / ROWS;
     float m = -INFINITY, z = 0.f;
     auto arrived = [&](int q, u64 w) -> u64 {
-      const uint32_t phase = stat_phase(d.start + q);
-      if ((uint32_t)(w >> 63) != phase) {
+      if ((w & kThere) == 0) {
         int spins = 0;
         long long t0 = 0;
         for (;;) {
           w = ld64(stat_word(d.start + q, srow));
-          if ((uint32_t)(w >> 63) == phase) break;
+          if ((w & kThere) != 0) break;
           __builtin_amdgcn_s_sleep(1);
           if (waited_too_long(spins, t0)) {
             __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -550,8 +547,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 #pragma unroll
       for (int w = 0; w < kW; ++w)
         zz = __builtin_fmaf(s_z[w * ROWS + tid], fast_exp2(s_m[(mbuf * kW + w) * ROWS + tid] - mm), zz);
-      const int j = cur.start + cur.part;
-      st64(stat_word(j, tid), ((u64)((__float_as_uint(zz) & 0x7FFFFFFFu) | (stat_phase(j) << 31)) << 32) | __float_as_uint(mm));
+      st64(stat_word(cur.start + cur.part, tid), kThere | (u64)__float_as_uint(zz) << 32 | __float_as_uint(mm));
     }
     commit_q(mbuf ^ 1);
     issue_k(nxt, KB - 1, kf[(TPW - 1) % KB]);  // (behind the statistics, which others wait for)
@@ -602,7 +598,7 @@ hipError_t launch_stream(const StreamArgs& a, hipStream_t s) {
 int stream_item_keys(int R) { return R <= 32 ? 1024 : 512; }
 
 hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s) {
-  const int n16 = a.grid * a.ring * (a.R <= 32 ? 32 : 64) / 2;  // 64-bit words, two per slot
+  const int n16 = a.items * (a.R <= 32 ? 32 : 64) / 2;  // 64-bit words, two per slot
   hipLaunchKernelGGL(clear_kernel, dim3((n16 + 255) / 256), dim3(256), 0, s, reinterpret_cast<u32x4*>(a.stats), n16,
                      clear_err ? a.err : nullptr);
   hipError_t e = hipGetLastError();
