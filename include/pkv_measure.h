@@ -92,14 +92,12 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
 /*
  * Test aid, HOST only (no device is touched): which kernel scores a call over
  * L layers of desc's shape on a device of 256 compute units or more, and what
- * it keeps in the last region of the workspace, where the pooled scores lie
- * later on.
+ * it keeps of its statistics in the workspace.
  *
  * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _SWEEP, _RESIDENT, or
  *                _ACCUM for the per-layer kernels.
- * scratch_bytes  written: bytes a launch addresses in that region.
- * scratch_room   written: bytes from the region's start to the end of the
- *                pkv_workspace_bytes(desc, L) bytes.
+ * scratch_bytes  written: bytes of statistics that a launch addresses.
+ * scratch_room   written: bytes of the workspace region that holds them.
  * Returns PKV_OK, PKV_ERR_INVALID_ARG or PKV_ERR_UNSUPPORTED.
  */
 int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L,

@@ -170,19 +170,26 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
   return plan.resident_ok && (lse_mode || device_fits_resident());
 }
 
-// How the one-pass kernel for few query rows serves a call: layers per launch (0: it does not), workgroups, and items of a
-// launch at most.  Whether it does is a matter of one layer's shape alone: a call over many layers gives
-// the same results as one call per layer.
-// The statistics words lie in the part of the workspace that holds the pooled scores later on: rows * 8 bytes
-// per item in the place of 4 bytes per key.  From N = 2 * rows on (64 keys, 128 at 33 .. 64 rows) that fits whatever the
-// number of layers and heads; shorter prompts go to the resident kernel.
+// How the one-pass kernel for few query rows serves a call: layers per launch (0: it does not), workgroups, items of a
+// launch at most, and the workspace region (offset, size) that holds their statistics words.  Whether it does is a matter
+// of one layer's shape alone: a call over many layers gives the same results as one call per layer.
+// The words lie where the pooled scores lie later on: rows * 8 bytes per item in the place of 4 bytes per key, which fits
+// whatever the number of layers and heads from N = 2 * rows on (64 keys, 128 at 33 .. 64 rows).  Those of shorter prompts lie
+// in the region of the other kernels' partial statistics, which has room for the items of one layer at least (one per
+// unit), and for 512 KB.  (There the resident kernel is slower: one layer of 8 heads x 50 keys, 32 rows 19.8 -> 21.8 us, of
+// 8 x 100, 64 rows 20.7 -> 24.2.)
 struct StreamPlan {
   int layers, grid, items, rows;  // rows: padded to 32 or 64
+  size_t off, room;
   size_t stats_bytes() const { return (size_t)items * rows * 8; }
 };
 static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
-  StreamPlan p = {0, 0, 0, plan.R <= 32 ? 32 : 64};
-  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok || d.N < 2 * p.rows) return p;
+  StreamPlan p = {0, 0, 0, plan.R <= 32 ? 32 : 64, plan.off_pooled, plan.total - plan.off_pooled};
+  if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok) return p;
+  if (d.N < 2 * p.rows) {
+    p.off = plan.off_part;
+    p.room = plan.off_cfin - plan.off_part;
+  }
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
   const int64_t parts = (d.N + stream_item_keys(plan.R) - 1) / stream_item_keys(plan.R);
   const int64_t per_layer = parts * plan.BH;
@@ -194,6 +201,8 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
   const int64_t by_items = (int64_t)kStreamItems * kStreamGrid / per_layer, by_units = kStreamUnits / d.B;
   if (parts > kStreamGrid || by_items < 1 || by_units < 1) return p;
   int64_t nl = by_items < by_units ? by_items : by_units;
+  const int64_t by_room = (int64_t)(p.room / ((size_t)per_layer * p.rows * 8));
+  if (nl > by_room) nl = by_room;
   if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;
   if (nl > plan.L) nl = plan.L;
   const int64_t items = nl * per_layer;
@@ -259,7 +268,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   if (rec) rec->begin(stream);
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
-  StreamPlan sp = {0, 0, 0, 0};
+  StreamPlan sp = {0, 0, 0, 0, 0, 0};
   SweepPlan wp = {0, 0, 0};
   if (any_scores && resident) sp = stream_plan(plan, d, lse_mode);
   if (any_scores && resident) wp = sweep_plan(plan, d, lse_mode);
@@ -311,7 +320,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       }
       sa.seq_lens = seq_lens;
       sa.raw = raw + (size_t)l0 * plan.BH * d.N;
-      sa.stats = reinterpret_cast<unsigned long long*>(pooled_ws);
+      sa.stats = reinterpret_cast<unsigned long long*>(ws + sp.off);
       sa.grid = sp.grid; sa.items = sp.items;
       sa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       sa.L = nl; sa.B = d.B; sa.Hq = d.Hq; sa.Hkv = d.Hkv; sa.G = plan.G; sa.alpha = d.alpha; sa.N = d.N; sa.R = plan.R;
@@ -889,6 +898,7 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t lse_supplie
   const SweepPlan wp = sweep_plan(plan, *desc, lse_mode);
   const StreamPlan sp = stream_plan(plan, *desc, lse_mode);
   *kernel_id = wp.C > 0 ? PKV_KERNEL_SCORE_SWEEP : (sp.layers > 0 ? PKV_KERNEL_SCORE_STREAM : PKV_KERNEL_SCORE_RESIDENT);
+  if (wp.C == 0 && sp.layers > 0) *scratch_room = sp.room;
   *scratch_bytes = wp.C > 0 ? wp.stats_bytes(plan, lse_mode) : (sp.layers > 0 ? sp.stats_bytes() : 0);
   return PKV_OK;
 }

@@ -330,6 +330,8 @@ def test_statistics_of_the_scoring_kernels_fit_the_workspace():
                     assert len(kernels) == 1, (B, Hkv, G, alpha, d, N, kernels)
                     taken |= kernels
     assert taken == {"score_resident", "score_stream", "score_sweep"}
+    for N in (9, 63, 64, 127, 128):
+        assert binding.scoring_route(_shape(1, 64, 8, 128, N, 8), 126)[0] == "score_stream"
     assert binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8, flags=binding.FLAG_STREAM_SCORING))[0] == "score_accum"
     with pytest.raises(binding.PkvError):
         binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8), 0)

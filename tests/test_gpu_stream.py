@@ -93,7 +93,8 @@ def test_references_that_do_not_fit(G):
 
 
 @pytest.mark.parametrize("L,B,Hkv,G,alpha,N", [(1, 1, 1, 1, 8, 40), (1, 1, 8, 4, 8, 100), (32, 1, 8, 4, 8, 100), (40, 1, 8, 4, 8, 127),
-                                               (40, 1, 8, 4, 8, 128), (33, 1, 8, 8, 8, 250), (33, 1, 8, 8, 8, 256), (3, 2, 8, 8, 8, 600)])
+                                               (40, 1, 8, 4, 8, 128), (33, 1, 8, 8, 8, 250), (33, 1, 8, 8, 8, 256), (3, 2, 8, 8, 8, 600),
+                                               (33, 4, 16, 8, 8, 100), (2, 150, 16, 1, 8, 60)])
 def test_nothing_is_written_behind_the_workspace(L, B, Hkv, G, alpha, N):
     data = [_inputs(B, G * Hkv, Hkv, 128, N, alpha, seed=900 + l) for l in range(L)]
     print("guard", L, B, Hkv, G, alpha, N, flush=True)
