@@ -14,7 +14,7 @@
 // Per item a workgroup
 //   1. multiplies its keys with the unit's queries (rows = queries in registers, columns = keys; wave w takes the 32-key
 //      tiles w, w + 8, ... of the item, loaded straight into operand layout, KB tiles ahead, across item boundaries),
-//      turns the logits into p relative to the logits of the unit's key 0 and keeps them in registers; sums over the keys give
+//      turns the logits into p relative to the row's reference and keeps them in registers; sums over the keys give
 //      the item's statistics (reference, sum) per row, published for the unit's other items;
 //   2. finishes the item BEFORE: the statistics of all items of its unit, which have had nearly the time of a whole item
 //      to arrive, are read (8 bytes per row and item: a few per cent of the keys' traffic) and folded into the
@@ -25,7 +25,11 @@
 // far, finds what it waits for.  They are requested a tile before they are used, in front of the keys requested at that
 // place: a wave's loads return in order, so a probe issued behind keys would hold the wave until those have arrived.  (For
 // the same reason there is one hop and not two, fold by one item and hand over: each hop costs a tile's time.)
-// The reference is the same for all keys of a unit, so that equal keys get equal scores, bit for bit.
+// The reference of a row is its largest logit of four keys of the unit, the sink at position 0 among them: the same for all
+// keys, so that equal keys get equal scores, bit for bit, and near enough to the terms that count, so that x - m loses little
+// to its rounding.  (With key 0 alone the scores of a head whose key 0 lies 30 binades below the others were 2.2e-6 off those
+// of 64 bits, now 0.1e-6; with the normaliser's own rounding taken out of the weights too, usual heads 0.5e-6 -> 0.1e-6,
+// the register-resident kernel 0.6e-6.)
 // A row whose reference was too far below its logits (sum beyond 2^100) is recomputed by its wave with the exact
 // maximum, from memory (rare).
 //
@@ -44,6 +48,7 @@
 namespace pkv {
 namespace {
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -56,7 +61,7 @@ constexpr int kW = 8;             // waves per workgroup
 constexpr int kT = kW * 64;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
+__device__ __forceinline__ bf16x2 as_pair(uint32_t u) { return __builtin_bit_cast(bf16x2, u); }
 __device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
 // A value the compiler must treat as new: lane constants derived from it are recomputed where they are used instead of
 // being kept (and spilled) across the whole item loop.
@@ -254,12 +259,14 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     for (int ks = 0; ks < KS; ++ks) f[ks] = as_frag(*reinterpret_cast<const u32x4*>(rowp + 32 * ks));
     __builtin_amdgcn_sched_barrier(0);
   };
-  // A unit's queries and its key 0: requested into registers, written to LDS later.  The lanes that carry a row of Q
-  // carry the same segments of the key, so the row's logit of key 0, the reference, comes from them on the way.
-  u32x4 qv[NQ], kv0;
+  // A unit's queries and four sampled keys (spread evenly over the prefix, key 0 among them; sixteen lanes carry one):
+  // requested into registers, written to LDS later.  The lanes that carry a row of Q come to see the same segments of each
+  // key, so the row's logits of these keys, and with them its reference, are formed on the way.
+  u32x4 qv[NQ], kv;
   auto request_q = [&](const Item& d) {
     const int td = fresh(tid);
-    kv0 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(d.K) + 16 * (td & (SEG - 1)));
+    const uint32_t key = (uint32_t)max(d.n - a.alpha, 0) * (uint32_t)((td & 63) >> 4) >> 2;
+    kv = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(d.K) + 16 * (td & (SEG - 1)) + key * ((uint32_t)a.kv_st * 2u));
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int c = td + kT * i, row = c / SEG, seg = c - row * SEG;
@@ -268,24 +275,40 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
   };
   auto commit_q = [&](int mbuf) {
     const int td = fresh(tid);
+    float ref[NQ][4];  // [row][key]
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ref[i][j] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // the key of each row of sixteen lanes, in all lanes
+      const u32x2 h = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(kv[e], kv[e], false, false));
+      const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false));
+      const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false));
+      const uint32_t k[4] = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+      for (int i = 0; i < NQ; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ref[i][j] = __builtin_amdgcn_fdot2_f32_bf16(as_pair(qv[i][e]), as_pair(k[j]), ref[i][j], false);
+    }
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int c = td + kT * i, row = c / SEG, seg = c - row * SEG;
       if (row < ROWS) s_q[row * PITCH + seg] = qv[i];
-      float dot = 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        dot = __builtin_fmaf(__uint_as_float(qv[i][e] << 16), __uint_as_float(kv0[e] << 16), dot);
-        dot = __builtin_fmaf(__uint_as_float(qv[i][e] & 0xFFFF0000u), __uint_as_float(kv0[e] & 0xFFFF0000u), dot);
-      }
-      // over the row's 16 or 8 lanes, in all of them
+      for (int j = 0; j < 4; ++j) {
+        float& dot = ref[i][j];
+        // over the row's 16 or 8 lanes, in all of them
 #define PKV_ADD(ctrl) dot += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(dot), ctrl, 0xF, 0xF, true))
-      PKV_ADD(0xB1);                 // quad_perm 1,0,3,2
-      PKV_ADD(0x4E);                 // quad_perm 2,3,0,1
-      PKV_ADD(0x141);                // row_half_mirror: the other quad of 8 lanes
-      if (SEG == 16) PKV_ADD(0x140); // row_mirror: the other half of 16 lanes
+        PKV_ADD(0xB1);                 // quad_perm 1,0,3,2
+        PKV_ADD(0x4E);                 // quad_perm 2,3,0,1
+        PKV_ADD(0x141);                // row_half_mirror: the other quad of 8 lanes
+        if (SEG == 16) PKV_ADD(0x140); // row_mirror: the other half of 16 lanes
 #undef PKV_ADD
-      if (row < ROWS && seg < kW) s_m[(mbuf * kW + seg) * ROWS + row] = dot * a.kappa;  // (one table per wave)
+      }
+      const float m = fmaxf(fmaxf(ref[i][0], ref[i][1]), fmaxf(ref[i][2], ref[i][3])) * a.kappa;
+      if (row < ROWS && seg < kW) s_m[(mbuf * kW + seg) * ROWS + row] = m;  // (one table per wave)
     }
   };
   const u32x4* q_lane = s_q + l32 * PITCH + hf;
@@ -382,9 +405,9 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
       }
 #pragma unroll
       for (int w = 0; w < kW; ++w) zu = __builtin_fmaf(f[w].y, fast_exp2(f[w].x - mu), zu);
-      const float c = mu + fast_log2(zu);
       const float m = s_w[wave * ROWS + lane];
-      s_w[wave * ROWS + lane] = lane < a.R ? fast_exp2(m - c) * a.inv_G : 0.f;
+      // (exp2(m - c) without c: nothing is lost to its rounding)
+      s_w[wave * ROWS + lane] = lane < a.R ? fast_exp2(m - mu) * __builtin_amdgcn_rcpf(zu) * a.inv_G : 0.f;
     }
     wave_lds_fence();
     f32x4 w[RT][G4];
@@ -423,7 +446,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 
   for (int i = 0; i < nmine; ++i) {
     Item nxt = item(i + 1 < nmine ? i + 1 : i);
-    if (i + 1 == nmine) {  // behind the last item: the requests go to the unit's key 0 alone, in the caches
+    if (i + 1 == nmine) {  // behind the last item: the requests go to the unit's key 0 alone
       nxt.part = 0;
       nxt.n = 1;
     }
@@ -484,7 +507,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             z[rt][q][c] = half_reduce<false>(z[rt][q][c]);
-            // (keys far below the reference vanish, as they should: key 0 alone contributes 1 to the unit's sum)
+            // (keys far below the reference vanish, as they should: a sampled key alone contributes 1 to the unit's sum)
             bad |= (l32 == 31 && !(z[rt][q][c] <= 0x1p100f)) ? 1u << (16 * rt + 4 * q + c) : 0u;
           }
         }
