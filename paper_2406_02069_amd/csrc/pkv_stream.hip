@@ -30,8 +30,9 @@
 // to its rounding.  (With key 0 alone the scores of a head whose key 0 lies 30 binades below the others were 2.2e-6 off those
 // of 64 bits, now 0.1e-6; with the normaliser's own rounding taken out of the weights too, usual heads 0.5e-6 -> 0.1e-6,
 // the register-resident kernel 0.6e-6.)
-// A row whose reference was too far below its logits (sum beyond 2^100) is recomputed by its wave with the exact
-// maximum, from memory (rare).
+// A row whose reference was too far below its logits (sum beyond 2^100) is summed up once more by its wave with the exact
+// maximum, from memory, and the items of such a unit are scored again at the end of the launch (rare: a key that stands 93
+// binades above the four; such a launch takes up to three times as long).
 //
 // What bounds it: HBM for many units.  Measured against the register-resident kernel, which keeps the keys and multiplies
 // them twice (one scoring launch, by the profiler): 256 units of 8k keys, 32 rows 146 -> 122 us; 256 of 32k, 8 rows 535
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
   float2* s_f = reinterpret_cast<float2*>(s_w + kW * ROWS); // [kW][ROWS] statistics of its unit, by wave
   int* s_t = reinterpret_cast<int*>(s_f + kW * ROWS);       // [ROWS] window position of a row
   int* s_off = s_t + ROWS;                                  // [ROWS] byte offset of a row of Q
-  uint2* s_item = reinterpret_cast<uint2*>(s_off + ROWS);   // [kStreamItems] (unit, part << 20 | keys)
+  uint2* s_item = reinterpret_cast<uint2*>(s_off + ROWS);   // [kStreamItems] (waves to score it again << 24 | unit, part << 20 | keys)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
   auto item = [&](int i) {
     const uint2 e = s_item[i];
     Item d;
-    d.u = __builtin_amdgcn_readfirstlane((int)e.x);
+    d.u = __builtin_amdgcn_readfirstlane((int)e.x) & 0xFFFFFF;
     const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.y);
     d.part = (int)(w >> 20);
     d.n = (int)(w & 0xFFFFFu);
@@ -391,10 +392,15 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
   pend.u = -1;
   pend.part = 0; pend.n = 1; pend.start = 0; pend.Q = nullptr; pend.K = nullptr;
   u32x4* p_wave = smem + (size_t)wave * (TPW * RT * G4 * 64);  // slot [t][rt][v / 4][lane]
-  // Scores of the pending item: weights exp2(m - c) / G per row, p weighted and summed over the rows.
-  auto finish = [&](const Item& d) {
+  // Scores of the pending item (the workgroup's item i): weights exp2(m - mu) / (G zu) per row, p weighted and summed over
+  // the rows.  Where some wave of the unit had to take a reference of its own (mu > m; in that wave s_w holds -inf),
+  // exp2(m - mu) may vanish before the products do, and equal keys of different waves would get different scores: every wave
+  // of the unit scores the item again at the end.
+  bool again = false;
+  auto finish = [&](const Item& d, int i) {
     const int lane = fresh(tid & 63), l32 = lane & 31, hf = lane >> 5;
     const u32x4* p_lane = p_wave + lane;
+    bool differ = false;
     if (lane < ROWS) {
       float2 f[kW];
       float mu = -INFINITY, zu = 0.f;
@@ -406,8 +412,13 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 #pragma unroll
       for (int w = 0; w < kW; ++w) zu = __builtin_fmaf(f[w].y, fast_exp2(f[w].x - mu), zu);
       const float m = s_w[wave * ROWS + lane];
-      // (exp2(m - c) without c: nothing is lost to its rounding)
+      // (not exp2(m - c), c = mu + log2 zu: nothing is lost to the rounding of c)
       s_w[wave * ROWS + lane] = lane < a.R ? fast_exp2(m - mu) * __builtin_amdgcn_rcpf(zu) * a.inv_G : 0.f;
+      differ = lane < a.R && !(m == mu);
+    }
+    if (__builtin_expect(__any(differ), 0)) {
+      again = true;
+      if (lane == 0) atomicOr(&s_item[i].x, 0x1000000u << wave);
     }
     wave_lds_fence();
     f32x4 w[RT][G4];
@@ -514,7 +525,9 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
       return bad;
     };
     const uint32_t bad = sum_up();
-    if (__any(bad != 0u) && tile_key(cur, 0) < cur.n) {
+    bool own = false;  // (lane = row) the wave has a reference of its own
+    if (__builtin_expect(__any(bad != 0u) && tile_key(cur, 0) < cur.n, 0)) {
+      const float unit_ref = m_tab[lane & (ROWS - 1)];
       // rare: a reference that does not fit: for such a row the exact maximum over the wave's keys, then p once more
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -554,6 +567,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
         }
       }
       (void)sum_up();
+      own = m_tab[lane & (ROWS - 1)] != unit_ref;
     }
     if (pend.u >= 0) fold_stats(pend, np_pend);
     if (l32 == 31) {
@@ -575,8 +589,8 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     commit_q(mbuf ^ 1);
     issue_k(nxt, KB - 1, kf[(TPW - 1) % KB]);  // (behind the statistics, which others wait for)
     // ---- the item before ----
-    if (pend.u >= 0) finish(pend);
-    if (lane < ROWS) s_w[wave * ROWS + lane] = m_tab[lane];
+    if (pend.u >= 0) finish(pend, i - 1);
+    if (lane < ROWS) s_w[wave * ROWS + lane] = own ? -INFINITY : m_tab[lane];
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
 #pragma unroll
@@ -590,7 +604,56 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
   request_stats(pend, nparts(pend));
   fold_stats(pend, nparts(pend));
   lds_barrier();
-  finish(pend);
+  finish(pend, nmine - 1);
+
+  // ---- rare: items to score again, from memory and relative to the largest reference of the unit; every wave its own
+  // tiles ----
+  if (__builtin_expect(!again, 1)) return;
+  float* ref_tab = reinterpret_cast<float*>(p_wave);  // [ROWS] references, [ROWS] weights
+  static_assert((size_t)TPW * RT * G4 * 64 * 16 >= (size_t)ROWS * 8, "tables fit");
+#pragma unroll 1
+  for (int i = 0; i < nmine; ++i) {
+    if ((__builtin_amdgcn_readfirstlane((int)s_item[i].x) >> (24 + wave) & 1) == 0) continue;
+    const Item d = item(i);
+    const int np = nparts(d), npre = d.n - a.alpha;
+    if (lane < ROWS) {
+      float m = -INFINITY, z = 0.f;
+      for (int q = 0; q < np; ++q) {  // (all there: the item has been finished before)
+        const u64 w = ld64(stat_word(d.start + q, lane));
+        merge_stats(m, z, __uint_as_float((uint32_t)w), __uint_as_float((uint32_t)(w >> 32) & 0x7FFFFFFFu));
+      }
+      ref_tab[lane] = m;
+      ref_tab[ROWS + lane] = lane < a.R ? __builtin_amdgcn_rcpf(z) * a.inv_G : 0.f;
+    }
+    wave_lds_fence();
+    float* raw = a.raw + (size_t)d.u * a.N;
+#pragma unroll 1
+    for (int t = 0; t < TPW; ++t) {
+      bf16x8 f[KS];
+      issue_k(d, t, f);
+      const int over = tile_key(d, t) + l32 - npre;
+      float s = 0.f;
+#pragma unroll 1
+      for (int rt = 0; rt < RT; ++rt) {
+        const char* q_row = reinterpret_cast<const char*>(d.Q) + 16 * hf + (uint32_t)s_off[32 * rt + l32];
+        f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(*reinterpret_cast<const u32x4*>(q_row + 32 * ks)), f[ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < G4; ++q) {
+          const i32x4 tt = *reinterpret_cast<const i32x4*>(s_t + 32 * rt + 8 * q + 4 * hf);
+          const f32x4 m = *reinterpret_cast<const f32x4*>(ref_tab + 32 * rt + 8 * q + 4 * hf);
+          const f32x4 w = *reinterpret_cast<const f32x4*>(ref_tab + ROWS + 32 * rt + 8 * q + 4 * hf);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            s = __builtin_fmaf(over > tt[e] ? 0.f : fast_exp2(__builtin_fmaf(acc[4 * q + e], a.kappa, -m[e])), w[e], s);
+        }
+      }
+      raw[min(tile_key(d, t) + l32, npre)] = both_halves(s);
+    }
+    wave_lds_fence();
+  }
 }
 
 // Clears n 16-byte slots at p and the error word.

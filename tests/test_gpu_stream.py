@@ -115,6 +115,36 @@ def test_precision_with_a_sink_above_or_below_the_other_keys(Hq, Hkv, d, N, alph
         assert err < 1.3e-6, (h, float(err))
 
 
+def _along(G, alpha, binades, d, seed):
+    """One KV head whose query rows all point the same way; key j's logit for each of them is about binades[j] ln 2."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    base = torch.randn(d, generator=g, device=DEV)
+    base *= d ** 0.5 / base.norm()
+    Q = (base + 0.02 * torch.randn(1, G, alpha, d, generator=g, device=DEV)).to(torch.bfloat16)
+    x = torch.tensor(binades, device=DEV, dtype=torch.float32) * np.log(2)
+    noise = 0.3 * torch.randn(len(binades), d, generator=g, device=DEV)
+    K = ((x / d ** 0.5)[:, None] * base + noise).to(torch.bfloat16)[None, None].contiguous()
+    return Q, K, torch.randn(1, 1, len(binades), d, generator=g, device=DEV).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,alpha", [(1, 8), (3, 5), (4, 8), (8, 8)])
+@pytest.mark.parametrize("first,top", [(-70, 75), (-20, 50), (-5, 75), (-30, 90), (-60, 20)])
+def test_normalisers_far_above_the_references(d, G, alpha, first, top):
+    # in every row one key stands far above the others and above key 0: the scores of the other keys, down to 2^-100 of
+    # it, are ordinary fp32 numbers, and equal keys in different waves and items get equal ones
+    binades = np.random.RandomState(G + d).uniform(-25, 25, 4100)
+    binades[0], binades[700] = first, top
+    Q, K, V = _along(G, alpha, binades, d, seed=G)
+    equal = [100, 701, 1500, 1800, 3999]
+    K[0, 0, equal] = K[0, 0, 1500].clone()
+    print("far", d, G, alpha, first, top, flush=True)
+    out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+    assert len(set(out[4][0, 0, equal].tolist())) == 1
+
+
 @pytest.mark.parametrize("L,B,Hkv,G,alpha,N", [(1, 1, 1, 1, 8, 40), (1, 1, 8, 4, 8, 100), (32, 1, 8, 4, 8, 100), (40, 1, 8, 4, 8, 127),
                                                (40, 1, 8, 4, 8, 128), (33, 1, 8, 8, 8, 250), (33, 1, 8, 8, 8, 256), (3, 2, 8, 8, 8, 600),
                                                (33, 4, 16, 8, 8, 100), (2, 150, 16, 1, 8, 60)])
