@@ -161,16 +161,17 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
     asm volatile("" ::: "memory");
   };
 
-  // m: reference exponent of each head (not necessarily the maximum so far, at most 2^kSlack below it), z: sum of
-  // this lane's weights.  Outputs of column 8 col + c: oc[c] over four (eight) heads, or of[h][c].
+  // m: reference exponent of each head (not necessarily the maximum so far, at most 2^kSlack below it; kNone, below every
+  // finite logit and finite itself, so that logits of -inf have weight 0, before the first finite one), z: sum of this
+  // lane's weights.  Outputs of column 8 col + c: oc[c] over four (eight) heads, or of[h][c].
   constexpr int NH = GP < 4 ? GP : 4;    // heads per quad
   constexpr bool MF = GP >= 4;           // values by matrix instructions
-  constexpr float kSlack = 16.f;
+  constexpr float kSlack = 16.f, kNone = -3e38f;
   float m[NH], z[NH], of[MF ? 1 : GP][8];
   f32x4 oc[MF ? QH : 1][8];
 #pragma unroll
   for (int v = 0; v < NH; ++v) {
-    m[v] = -INFINITY;
+    m[v] = kNone;
     z[v] = 0.f;
   }
 #pragma unroll
@@ -233,7 +234,7 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
 #pragma unroll
           for (int gr = 0; gr < NG; ++gr) tm = fmaxf(tm, have[gr] ? acc[gr][v] * a.scale_log2 : -INFINITY);
           const float mn = fmaxf(m[v], row_max(tm));
-          f[v] = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m[v] - mn);
+          f[v] = __builtin_amdgcn_exp2f(m[v] - mn);
           z[v] *= f[v];
           m[v] = mn;
         }
@@ -360,12 +361,11 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
     for (int w0 = 0; w0 < nw; w0 += 4)  // (nw is a multiple of 4)
 #pragma unroll
       for (int w = w0; w < w0 + 4; ++w) M = fmaxf(M, s_mz[(w * GP + h) * 2]);
-    const float Ms = (M == -INFINITY) ? 0.f : M;  // nothing here: an empty range, or every page number bad
     float zz = 0.f, xx = 0.f;
     for (int w0 = 0; w0 < nw; w0 += 4)
 #pragma unroll
       for (int w = w0; w < w0 + 4; ++w) {
-        const float f = __builtin_amdgcn_exp2f(s_mz[(w * GP + h) * 2] - Ms);
+        const float f = __builtin_amdgcn_exp2f(s_mz[(w * GP + h) * 2] - M);  // (nothing here, M = kNone: zz and xx are 0)
         zz += f * s_mz[(w * GP + h) * 2 + 1];
         xx += f * dsm[(size_t)w * GP * D + e];
       }
@@ -411,11 +411,10 @@ __device__ __forceinline__ void decode_merge(const DecodeArgs& a, int g, int b) 
     float M = -INFINITY;
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s) M = fmaxf(M, pm[s]);
-    const float Ms = (M == -INFINITY) ? 0.f : M;
     float z = 0.f, x = 0.f;
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s) {
-      const float f = __builtin_amdgcn_exp2f(pm[s] - Ms);
+      const float f = __builtin_amdgcn_exp2f(pm[s] - M);
       z += pz[s] * f;
       x += px[s] * f;
     }

@@ -42,6 +42,21 @@ def test_groups_tiles_and_climbing_logits(d, G, k_cap, top):
         _cmp(o, s, Kc, Vc, q, count)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,lo,hi", [(1, 0, 32), (2, 0, 40), (4, 0, 300), (8, 0, 700), (4, 100, 600), (8, 0, 1499)])
+def test_logits_of_minus_infinity(d, G, lo, hi):
+    # products that overflow to -inf in the first tiles of a wave, of a whole range, and in all rows but the last ones
+    B, Hkv, k_cap = 2, 2, 1600
+    q, Ks, Vs = _rand(B, G * Hkv, Hkv, d, k_cap, seed=G + hi)
+    q = q.abs()
+    Ks[:, 0, lo:hi] = -3e38
+    count = np.array([k_cap, 1500], dtype=np.int32)
+    print("decode -inf", d, G, lo, hi, flush=True)
+    out, lse = binding.decode_attention(q, Ks, Vs, torch.from_numpy(count).to(DEV), want_lse=True)
+    torch.cuda.synchronize()
+    _cmp(out, lse, Ks, Vs, q, count)
+
+
 @pytest.mark.parametrize("page_size,k_cap", [(1, 40), (3, 100), (5, 333), (100, 999), (4095, 1300), (5000, 70)])
 def test_page_sizes(page_size, k_cap):
     B, Hq, Hkv, d = 2, 8, 2, 128
