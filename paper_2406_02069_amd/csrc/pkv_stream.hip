@@ -528,7 +528,8 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     bool own = false;  // (lane = row) the wave has a reference of its own
     if (__builtin_expect(__any(bad != 0u) && tile_key(cur, 0) < cur.n, 0)) {
       const float unit_ref = m_tab[lane & (ROWS - 1)];
-      // rare: a reference that does not fit: for such a row the exact maximum over the wave's keys, then p once more
+      // rare: a reference that does not fit (the sum is beyond 2^100 or, with one of -inf, undefined): for such a row the
+      // exact maximum over the wave's keys (-inf if there is nothing to add up), then p once more
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         f32x4 mx[G4];
@@ -537,6 +538,10 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
         for (int pass = 0; pass < 2; ++pass) {
           f32x4 m[G4];
           load_m(rt, m);
+#pragma unroll
+          for (int q = 0; q < G4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) m[q][c] = m[q][c] == -INFINITY ? 0.f : m[q][c];
 #pragma unroll
           for (int t = 0; t < TPW; ++t) {
             bf16x8 f[KS];
@@ -581,9 +586,10 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
       float mm = -INFINITY, zz = 0.f;
 #pragma unroll
       for (int w = 0; w < kW; ++w) mm = fmaxf(mm, s_m[(mbuf * kW + w) * ROWS + tid]);
+      const float ms = mm == -INFINITY ? 0.f : mm;
 #pragma unroll
       for (int w = 0; w < kW; ++w)
-        zz = __builtin_fmaf(s_z[w * ROWS + tid], fast_exp2(s_m[(mbuf * kW + w) * ROWS + tid] - mm), zz);
+        zz = __builtin_fmaf(s_z[w * ROWS + tid], fast_exp2(s_m[(mbuf * kW + w) * ROWS + tid] - ms), zz);
       st64(stat_word(cur.start + cur.part, tid), kThere | (u64)__float_as_uint(zz) << 32 | __float_as_uint(mm));
     }
     commit_q(mbuf ^ 1);

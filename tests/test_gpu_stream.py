@@ -145,6 +145,17 @@ def test_normalisers_far_above_the_references(d, G, alpha, first, top):
     assert len(set(out[4][0, 0, equal].tolist())) == 1
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,alpha", [(1, 8), (2, 8), (4, 8), (8, 8)])
+@pytest.mark.parametrize("lo,hi", [(0, 1), (32, 64), (0, 600), (1024, 2048), (0, 3500), (500, 4000)])
+def test_logits_of_minus_infinity(d, G, alpha, lo, hi):
+    # products that overflow to -inf: single keys, whole waves and items of them, and all keys that the references come from
+    Q, K, V = _inputs(1, G, 1, d, 4100, alpha, seed=G + hi)
+    Q = Q.abs()
+    K[:, :, lo:hi] = -3e38
+    _check(Q, K, V, alpha + 30, pool=synth.POOL_NONE, pw=1)
+
+
 @pytest.mark.parametrize("L,B,Hkv,G,alpha,N", [(1, 1, 1, 1, 8, 40), (1, 1, 8, 4, 8, 100), (32, 1, 8, 4, 8, 100), (40, 1, 8, 4, 8, 127),
                                                (40, 1, 8, 4, 8, 128), (33, 1, 8, 8, 8, 250), (33, 1, 8, 8, 8, 256), (3, 2, 8, 8, 8, 600),
                                                (33, 4, 16, 8, 8, 100), (2, 150, 16, 1, 8, 60)])
