@@ -18,8 +18,9 @@
 // the scores were 1.0e-6 off those of 64 bits at 512 rows, the register-resident kernel's 0.6e-6), and the same for all
 // keys.  The sampled keys alone contribute 1 to the unit's sum, so vanishing terms are as they should be; a sum beyond
 // 2^100 makes the workgroup form its chunk again with the chunk's exact maxima (rare).
-// Launch 2, when it takes up a unit, folds the statistics of its chunks into the normalisers c_r (or takes the supplied
-// denominators: then it is the only launch) and writes s_i = sum_r exp2(x_ri - c_r) / G.
+// Launch 2, when it takes up a unit, folds the statistics of its chunks into the normalisers c_r, rounded once (scores of 512
+// rows 6.2e-7 -> 1.3e-7 off those of 64 bits, of 256 rows at d = 64 4.5e-7 -> 0.8e-7; the register-resident kernel 5.9e-7 and
+// 4.2e-7), or takes the supplied denominators (then it is the only launch), and writes s_i = sum_r exp2(x_ri - c_r) / G.
 //
 // Inner loops as in the register-resident kernel: one product's matrix instructions are issued between the exponentials
 // of the one before, in an order fixed in the source.
@@ -243,11 +244,12 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
     }
     if (SCORE) {
       if (tid < a.Rs) {
-        float c = INFINITY;  // padding rows contribute exp2(-inf) = 0
+        u64 w3 = split3(-INFINITY);  // -c / kappa; padding rows contribute exp2(-inf) = 0
         if (tid < a.R) {
           if (a.lse_mode) {
             const int l = p.u / BH, bg = p.u - l * BH, b = bg / a.Hkv, g = bg - b * a.Hkv;
-            c = a.layer[l].lse[((size_t)b * a.Hq + (size_t)g * a.G) * a.alpha + tid] * 1.44269504088896340736f;
+            const float c = a.layer[l].lse[((size_t)b * a.Hq + (size_t)g * a.G) * a.alpha + tid] * 1.44269504088896340736f;
+            w3 = split3(-c * a.inv_kappa);
           } else {
             const u64* st = a.stats + (size_t)p.u * a.nchunk * a.Rs + tid;
             const int parts = (p.n + a.C - 1) / a.C;
@@ -267,10 +269,16 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
                   z = __builtin_fmaf(__uint_as_float((uint32_t)(w[k] >> 32)), fast_exp2(__uint_as_float((uint32_t)w[k]) - Ms), z);
               m = M;
             }
-            c = m + fast_log2(z);
+            // c = m + log2 z, divided by kappa and rounded once: the logarithm of the mantissa alone (between 0 and 1, its
+            // error is below 2^-24; that of log2 z, not centred on 0, showed in all scores of a row), the sum's rounding
+            // error and the quotient's remainder are carried along
+            const float e = (float)(__builtin_amdgcn_frexp_expf(z) - 1), lf = fast_log2(__builtin_amdgcn_frexp_mantf(z) * 2.f);
+            const float t = m + e, t1 = t - m, err = (m - (t - t1)) + (e - t1);
+            const float q = -t * a.inv_kappa, rem = __builtin_fmaf(q, a.kappa, t);
+            w3 = split3(__builtin_fmaf(-(rem + (err + lf)), a.inv_kappa, q));
           }
         }
-        s_c[tid] = split3(-c * a.inv_kappa);
+        s_c[tid] = w3;
       }
     }
   };

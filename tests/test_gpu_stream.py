@@ -92,11 +92,9 @@ def test_references_that_do_not_fit(G):
     compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,N,alpha", [(32, 8, 128, 8192, 16), (32, 8, 128, 30000, 8), (8, 8, 64, 1024, 8), (16, 4, 64, 5000, 16)])
-@pytest.mark.parametrize("sink", [None, 3, -4])
-def test_precision_with_a_sink_above_or_below_the_other_keys(Hq, Hkv, d, N, alpha, sink):
-    # against 64 bits on the GPU, over the whole prefix in the 2-norm.  Bound: a logit of up to 2^5 binades carries half a unit in
-    # the last place, 2^-20, and so does its distance from the reference; together 2^-19 ln 2 = 1.3e-6 in a score
+def precision_of_scores(Hq, Hkv, d, N, alpha, sink):
+    """Largest error of a KV head's un-pooled scores against 64 bits, 2-norm over the prefix, for queries that point largely
+    the same way.  sink: key 0 as a multiple of that direction, None for a key like the others."""
     g = torch.Generator(device=DEV).manual_seed(N + alpha)
     base = torch.randn(1, Hkv, 1, d, generator=g, device=DEV)
     Q = 1.2 * base + 0.9 * torch.randn(1, Hkv, Hq // Hkv * alpha, d, generator=g, device=DEV)
@@ -107,12 +105,22 @@ def test_precision_with_a_sink_above_or_below_the_other_keys(Hq, Hkv, d, N, alph
     out = binding.compress_layer(Q, K, K, alpha + 100, synth.POOL_NONE, 1, want_scores=True)
     torch.cuda.synchronize()
     hidden = torch.ones(alpha, alpha, dtype=torch.bool, device=DEV).triu(1)
+    worst = 0.0
     for h in range(Hkv):
         x = Q[0].view(Hkv, -1, d)[h].double() @ K[0, h].double().t().contiguous() / d ** 0.5
         x.view(-1, alpha, N)[:, :, N - alpha:].masked_fill_(hidden, -np.inf)
         want = x.softmax(dim=1).sum(dim=0)[:N - alpha] / (Hq // Hkv)
-        err = (out[4][0, h, :N - alpha].double() - want).norm() / want.norm()
-        assert err < 1.3e-6, (h, float(err))
+        worst = max(worst, float((out[4][0, h, :N - alpha].double() - want).norm() / want.norm()))
+    return worst
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,N,alpha", [(32, 8, 128, 8192, 16), (32, 8, 128, 30000, 8), (8, 8, 64, 1024, 8), (16, 4, 64, 5000, 16)])
+@pytest.mark.parametrize("sink", [None, 3, -4])
+def test_precision_with_a_sink_above_or_below_the_other_keys(Hq, Hkv, d, N, alpha, sink):
+    # bound: a logit of up to 2^5 binades carries half a unit in the last place, 2^-20, and so does its distance from the
+    # reference; together 2^-19 ln 2 = 1.3e-6 in a score
+    assert precision_of_scores(Hq, Hkv, d, N, alpha, sink) < 1.3e-6
+
 
 
 def _along(G, alpha, binades, d, seed):

@@ -9,6 +9,7 @@ from oracle import pkv_oracle
 from paper_2406_02069_amd import binding, synth
 from tests import prefill_stub
 from tests.parity import compare_layer
+from tests.test_gpu_stream import precision_of_scores
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -140,3 +141,10 @@ def test_supplied_denominators_few_rows(d, G, alpha):
     for l in (0, L // 2, L - 1):
         for x, y in zip(many[l], one):
             assert torch.equal(x, y), l
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,N,alpha", [(64, 8, 128, 8192, 32), (28, 4, 128, 20001, 40), (16, 4, 64, 16384, 64), (64, 8, 128, 16384, 64)])
+def test_precision_of_the_normalisers(Hq, Hkv, d, N, alpha):
+    # errors of single rows average out over this many; what is left is common to all rows: the rounding of kappa, 2^-25 of a
+    # logit up to 10 binades from the mean, 10 ln 2 / 2^25 = 2.1e-7, and as much again for the normalisers
+    assert precision_of_scores(Hq, Hkv, d, N, alpha, None) < 4.2e-7
