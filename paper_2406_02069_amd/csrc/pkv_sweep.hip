@@ -476,7 +476,9 @@ __global__ __launch_bounds__(64 * kW, kW / 4) void score_sweep_kernel(const Swee
           float z = 0.f;
 #pragma unroll
           for (int w = 0; w < kW; ++w) z += s_z[w * a.Rs + tid];
-          a.stats[((size_t)cur.u * a.nchunk + cur.chunk) * a.Rs + tid] = ((u64)__float_as_uint(z) << 32) | __float_as_uint(s_m[tid]);
+          // (nothing to add up: no reference either, lest the stand-in for one of -inf outweighs the other chunks')
+          const float m = z == 0.f ? -INFINITY : s_m[tid];
+          a.stats[((size_t)cur.u * a.nchunk + cur.chunk) * a.Rs + tid] = ((u64)__float_as_uint(z) << 32) | __float_as_uint(m);
           s_m[tid] = s_m0[tid];
         }
         lds_barrier();

@@ -148,3 +148,16 @@ def test_precision_of_the_normalisers(Hq, Hkv, d, N, alpha):
     # errors of single rows average out over this many; what is left is common to all rows: the rounding of kappa, 2^-25 of a
     # logit up to 10 binades from the mean, 10 ln 2 / 2^25 = 2.1e-7, and as much again for the normalisers
     assert precision_of_scores(Hq, Hkv, d, N, alpha, None) < 4.2e-7
+
+
+@pytest.mark.parametrize("finite", [[1, 700, 701, 2500, 4000], list(range(3000, 3200))])
+def test_logits_of_minus_infinity(finite):
+    # products that overflow to -inf but for a few keys whose logits are two hundred binades below 0
+    G, alpha, Hkv, N, d = 4, 40, 8, 4300, 128
+    Q, K, V = _inputs(1, G * Hkv, Hkv, d, N, alpha, seed=7)
+    Q = Q.abs()
+    low = (-15 - 0.05 * K[:, :, finite].float()).to(torch.bfloat16)
+    K[:] = -3e38
+    K[:, :, finite] = low
+    K[:, :, N - alpha:] = -3e38
+    _check(Q, K, V, alpha + 3, pool=synth.POOL_NONE, pw=1)
