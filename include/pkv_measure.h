@@ -42,7 +42,9 @@ typedef enum {
  *            with timing enabled.  events[0] is recorded on `stream` before
  *            the first kernel, events[i] after the i-th kernel launched.
  * kernel_ids HOST int32[n_events - 1], written: kernel_ids[i-1] is the
- *            pkv_kernel_id of the kernel between events[i-1] and events[i].
+ *            pkv_kernel_id of the kernel between events[i-1] and events[i]
+ *            (a scoring kernel together with the small kernel that clears
+ *            its scratch; SCORE_SWEEP with both of its launches).
  * n_used     HOST int32, written: number of events recorded (kernels + 1).
  * The call does not synchronise; the caller synchronises the stream and
  * reads hipEventElapsedTime(events[i-1], events[i]).

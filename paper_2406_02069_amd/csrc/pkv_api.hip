@@ -216,7 +216,7 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
 // one layer's shape alone but for the last rule.  A layer has about one chunk per workgroup.  (The statistics lie in the part of the workspace
 // that holds the pooled scores later on.)
 // Where the lines lie, against the resident kernel, whole calls (7 us and more of each gain are the selection's):
-//   80 layers of 8 heads x 32k keys, 512 rows 6439 -> 5430 us; 32 layers of 32k, 256 rows 1389 -> 1300, of 4k, 512 rows
+//   80 layers of 8 heads x 32k keys, 512 rows 6270 -> 5460 us; 32 layers of 32k, 256 rows 1389 -> 1300, of 4k, 512 rows
 //   413 -> 316; one layer of 8k, 256 rows 58 -> 45.  At 128 rows K is read twice for nothing: 32 layers of 32k keys 801
 //   -> 908 us, of 128k 3371 -> 3551.  Few chunks leave compute units idle: with 32 (8 heads x 4k keys, 512 rows) 32
 //   layers gain a quarter, one layer takes about as long as before (89.6 -> 82 us, 7 of it the selection's).
@@ -305,7 +305,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       wa.inv_kappa = 1.0f / kappa;
       wa.inv_G = 1.0f / (float)plan.G;
       if (launch_score_sweep(wa, stream) != hipSuccess) return PKV_ERR_HIP;
-      if (rec) rec->after(PKV_KERNEL_SCORE_RESIDENT, stream);
+      if (rec) rec->after(PKV_KERNEL_SCORE_SWEEP, stream);
     }
   } else if (sp.layers > 0) {
     for (int32_t l0 = 0; l0 < L; l0 += sp.layers) {
@@ -331,7 +331,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       sa.kappa = kappa;
       sa.inv_G = 1.0f / (float)plan.G;
       if (launch_score_stream(sa, l0 == 0, stream) != hipSuccess) return PKV_ERR_HIP;
-      if (rec) rec->after(PKV_KERNEL_SCORE_RESIDENT, stream);
+      if (rec) rec->after(PKV_KERNEL_SCORE_STREAM, stream);
     }
   } else if (any_scores && resident) {
     for (int32_t l0 = 0; l0 < L; l0 += kResidentMaxLayers) {

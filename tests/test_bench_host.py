@@ -22,6 +22,8 @@ def test_algorithmic_bytes_of_the_headline_workload():
     w = synth.WORKLOADS[2]
     per_layer = 8 * 32768 * 128 * 2 + 32 * 32 * 128 * 2
     assert bench.kernel_bytes("score_resident", w, [128] * w.L, w.N) == per_layer * 32 == 2155872256
+    for name in ("score_stream", "score_sweep"):
+        assert bench.kernel_bytes(name, w, [128] * w.L, w.N) == per_layer * 32
     # one layer: K, Q_win, kept K and V rows read and written, kept indices
     k = 100
     assert bench.layer_bytes(w, k, w.N) == per_layer + 4 * 8 * k * 128 * 2 + 8 * k * 4
