@@ -35,9 +35,9 @@
 // binades above the four; such a launch takes up to three times as long).
 //
 // What bounds it: HBM for many units.  Measured against the register-resident kernel, which keeps the keys and multiplies
-// them twice (one scoring launch, by the profiler): 256 units of 8k keys, 32 rows 146 -> 122 us; 256 of 32k, 8 rows 535
-// -> 398 us (5.4 TB/s); ragged batch, 2048 units of 8k .. 16k, 64 rows 2.20 -> 1.56 ms (4.4 TB/s; an item of 512 keys
-// takes 6 - 7 us, of which the hop between the workgroups is not always covered).  One unit or a few: the latency of the
+// them twice (one scoring launch, by the profiler): 256 units of 8k keys, 32 rows 146 -> 112 us; 256 of 32k, 8 rows 535
+// -> 389 us (5.5 TB/s); ragged batch, 2048 units of 8k .. 16k, 64 rows 2.22 -> 1.67 ms (4.2 TB/s; an item of 512 keys
+// takes 6 - 8 us, of which the hop between the workgroups is not always covered).  One unit or a few: the latency of the
 // keys, one hop and two barriers; one layer of 8 heads with 8k keys 17.9 -> 16.5 us.
 //
 // Every wait is bounded by wall-clock time (a workgroup that has waited too long raises the error word and carries on),

@@ -332,6 +332,9 @@ def test_statistics_of_the_scoring_kernels_fit_the_workspace():
     assert taken == {"score_resident", "score_stream", "score_sweep"}
     for N in (9, 63, 64, 127, 128):
         assert binding.scoring_route(_shape(1, 64, 8, 128, N, 8), 126)[0] == "score_stream"
+    # the one-pass kernel keeps statistics words for every item of a launch (1024 keys of a unit; 512 at 33 .. 64 rows)
+    assert binding.scoring_route(_shape(2, 8, 8, 64, 4000, 8), 40)[:2] == ("score_stream", 40 * 16 * 4 * 32 * 8)
+    assert binding.scoring_route(_shape(2, 64, 8, 128, 4000, 8), 20)[:2] == ("score_stream", 20 * 16 * 8 * 64 * 8)
     assert binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8, flags=binding.FLAG_STREAM_SCORING))[0] == "score_accum"
     with pytest.raises(binding.PkvError):
         binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8), 0)

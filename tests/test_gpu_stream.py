@@ -1,6 +1,7 @@
 """One-pass scoring for few query rows (G * alpha <= 64) at the edges of its work split: rows around the register groups,
-lengths around the keys of an item, ragged batches whose sequences contribute unequal numbers of items, more items than
-a workgroup keeps statistics of, more sequences than one launch's table holds, references that do not fit."""
+lengths around the keys of an item, ragged batches whose sequences contribute unequal numbers of items, many items per
+workgroup, more sequences than one launch's table holds, references that do not fit or overflow, precision, the end of the
+workspace."""
 import numpy as np
 import pytest
 import torch
@@ -53,7 +54,7 @@ def test_ragged_batch(G):
     _check(Q, K, V, 40, lens)
 
 
-def test_more_items_than_the_statistics_ring_holds():
+def test_many_items_per_workgroup():
     # 40 layers x 16 heads x 4 items = 2560 items: ten per workgroup; equal to one call per layer, bit for bit
     L, alpha, N = 40, 8, 4000
     data = [_inputs(2, 8, 8, 64, N, alpha, seed=500 + l) for l in range(L)]
