@@ -227,7 +227,7 @@ def measure(w, avg, steps, warmup, dev, lse=False, page_size=0, host_layers=(), 
     launches_per_step = len(per_kernel[binding.KERNEL_NAMES.index(dominant)]) / n_prof
     if dominant.startswith("score") and fl / dom_bytes / max(launches_per_step, 1) > MFMA_BF16_PEAK_TFLOPS / HBM_PEAK_GBPS * 1e3:
         tf = fl / (sum_ms[dominant] * 1e-3) / 1e12
-        sweeps = 1 if lse or dominant == "score_stream" else 2
+        sweeps = binding.scoring_sweeps(call.descs[0], lse)
         res["roofline"].update({"bound": "mfma", "achieved": tf, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                                 "frac": tf / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                                 "executed_TFLOPs": tf * sweeps, "executed_frac": tf * sweeps / MFMA_BF16_PEAK_TFLOPS,

@@ -57,10 +57,15 @@ typedef enum {
   PKV_KERNEL_SCORE_ACCUM = 2, /* sweep 2 over K: per-key window scores      */
   PKV_KERNEL_POOL_SELECT = 3,
   PKV_KERNEL_GATHER = 4,
-  PKV_KERNEL_SCORE_RESIDENT = 5, /* both sweeps, K held in registers (all layers) */
-  PKV_KERNEL_SCORE_STREAM = 6,   /* one pass over K, few query rows (all layers) */
+  /* All layers in one launch or a few.  The lagging one-pass kernel, which
+     serves calls of 33 to 512 query rows per KV head from some size on, is
+     counted under the kernel that serves these rows elsewhere: SCORE_STREAM up
+     to 64 rows, SCORE_RESIDENT up to 128, SCORE_SWEEP beyond
+     (pkv_scoring_sweeps tells them apart).                                  */
+  PKV_KERNEL_SCORE_RESIDENT = 5, /* both sweeps, K held in registers         */
+  PKV_KERNEL_SCORE_STREAM = 6,   /* one pass over K, few query rows          */
   PKV_KERNEL_SCORE_SWEEP = 7     /* streaming sweeps over K, many query rows or
-                                    supplied denominators (all layers)       */
+                                    supplied denominators                    */
 } pkv_kernel_id;
 
 int pkv_compress_layers_profiled(
@@ -105,6 +110,12 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
 int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L,
                       int32_t lse_supplied, int32_t* kernel_id,
                       size_t* scratch_bytes, size_t* scratch_room);
+
+/*
+ * Measurement aid, HOST only: how many times the scoring of a layer of desc's
+ * shape forms each window logit (1 or 2), or 0 where desc is not accepted.
+ */
+int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t lse_supplied);
 
 #ifdef __cplusplus
 }

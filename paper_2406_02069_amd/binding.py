@@ -28,7 +28,7 @@ DESC_FLAGS = 0
 EXPORTS = ["pkv_budgets", "pkv_workspace_bytes", "pkv_compress_layer", "pkv_compress_layer_noalloc", "pkv_compress_layers",
            "pkv_compress_layers_lse", "pkv_compress_layers_paged", "pkv_compress_layers_profiled",
            "pkv_budgets_schedule", "pkv_attention_recall", "pkv_decode_attention", "pkv_decode_workspace_bytes", "pkv_decode_attention_layers",
-           "pkv_decode_layers_workspace_bytes", "pkv_probe_read", "pkv_scoring_route", "pkv_status_string"]
+           "pkv_decode_layers_workspace_bytes", "pkv_probe_read", "pkv_scoring_route", "pkv_scoring_sweeps", "pkv_status_string"]
 
 
 class PkvError(RuntimeError):
@@ -435,6 +435,14 @@ def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False):
     if rc != OK:
         raise PkvError(rc, "pkv_scoring_route")
     return KERNEL_NAMES[kernel.value], used.value, room.value
+
+
+def scoring_sweeps(desc: LayerDesc, lse_supplied: bool = False) -> int:
+    """pkv_scoring_sweeps: how many times the scoring forms each window logit.  Touches no device."""
+    lib = load()
+    lib.pkv_scoring_sweeps.argtypes = [ctypes.POINTER(LayerDesc), ctypes.c_int32]
+    lib.pkv_scoring_sweeps.restype = ctypes.c_int
+    return lib.pkv_scoring_sweeps(ctypes.byref(desc), int(lse_supplied))
 
 
 class HipEvents:

@@ -252,6 +252,50 @@ static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_
   return p;
 }
 
+// How the lagging one-pass kernel serves a call: items of a unit of N keys, groups of query rows, layers per launch (0: it
+// does not).  From one layer's shape alone, so that a call over many layers gives the results of one call per layer.  A unit's
+// words lie where its pooled scores lie later on.
+// Where the lines lie, whole calls of 8 layers (of one) with 8 heads, before -> with this kernel, us:
+//   33 .. 64 rows, against the other one-pass kernel, whose start is 4 us shorter: 8k keys 53 -> 48 (27 -> 32), 32k keys
+//     181 -> 155 (45 -> 49), 64k keys 375 -> 303 (99 -> 90), 128k keys 767 -> 565 (168 -> 154): from 768 items per layer on.
+//   65 .. 128 rows, against the register-resident one: 1500 keys 39 -> 32 (36 -> 28), 8k keys 78 -> 59 (40 -> 31), 20k keys
+//     208 -> 158 (52 -> 47), 64k keys 462 -> 419 (116 -> 102), 128k keys 931 -> 904 (196 -> 189).
+//   more rows, against the two-launch one: 192 rows, 32k keys 321 -> 258 (70 -> 59); 256 rows, 8k keys 108 -> 87 (47 -> 37);
+//     512 rows, 8k keys 185 -> 142 (86 -> 49), 64k keys 1164 -> 945 (209 -> 179); 512 rows, 128k keys 2282 -> 2249.
+//   Units of more than 128 items keep all workgroups in step: 136 rows, 128k keys 1030 -> 1372, 72 rows 848 -> 877, 256 rows
+//     1349 -> 1443; only where the rows fill one or two groups does it stay ahead.
+constexpr int kLagMinRows = 33;
+constexpr int kLagMinItems = 768;   // per layer, at 64 rows and less
+constexpr int kLagMaxParts = 128;
+struct LagPlan {
+  int parts, groups, layers;
+};
+static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
+  LagPlan p = {0, 0, 0};
+  if (lse_mode || plan.R < kLagMinRows || plan.R > kResidentMaxRows || !plan.resident_ok) return p;
+  if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
+  if (d.q_sh >= 1 << 24 || d.q_st >= 1 << 24) return p;  // (offsets of query rows by 24-bit multiplication)
+  const int groups = (plan.R + 63) / 64;
+  if ((size_t)groups * kLagGroupBytes > (size_t)d.N * 4) return p;
+  const int64_t parts = (d.N + kLagKeys - 1) / kLagKeys;
+  if (groups == 1 && parts * plan.BH < kLagMinItems) return p;
+  // (an item is finished two steps later, when its unit's other items, dealt one after the other, are at most one item ahead)
+  if (parts > (groups == 1 || (groups == 2 && plan.R > 112) ? kStreamGrid : kLagMaxParts)) return p;
+  const int64_t by_items = (int64_t)kLagItems * kStreamGrid / (parts * plan.BH), by_units = kStreamUnits / d.B;
+  int64_t nl = by_items < by_units ? by_items : by_units;
+  if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;
+  if (nl < 1) return p;
+  p.parts = (int)parts;
+  p.groups = groups;
+  p.layers = (int)nl;
+  return p;
+}
+
+// What the recorder calls the lagging kernel: the kernel that serves calls of these query rows elsewhere.
+static int lag_kernel_id(const Plan& plan) {
+  return plan.R <= kStreamMaxRows ? PKV_KERNEL_SCORE_STREAM : (plan.R < kSweepMinRows ? PKV_KERNEL_SCORE_RESIDENT : PKV_KERNEL_SCORE_SWEEP);
+}
+
 // Queue the kernels of L layers.  All arguments have been validated.
 static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, const LayerPtrs* ptrs,
                       const int32_t* seq_lens, void* workspace, hipStream_t stream, Recorder* rec,
@@ -268,10 +312,14 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   if (rec) rec->begin(stream);
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
+  LagPlan gp = {0, 0, 0};
   StreamPlan sp = {0, 0, 0, 0, 0, 0};
   SweepPlan wp = {0, 0, 0};
-  if (any_scores && resident) sp = stream_plan(plan, d, lse_mode);
-  if (any_scores && resident) wp = sweep_plan(plan, d, lse_mode);
+  if (any_scores && resident) gp = lag_plan(plan, d, lse_mode);
+  if (any_scores && resident && gp.layers == 0) {
+    sp = stream_plan(plan, d, lse_mode);
+    wp = sweep_plan(plan, d, lse_mode);
+  }
   if (wp.C > 0) {
     for (int32_t l0 = 0; l0 < L; l0 += kResidentMaxLayers) {
       const int32_t nl = L - l0 < kResidentMaxLayers ? L - l0 : kResidentMaxLayers;
@@ -306,6 +354,43 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       wa.inv_G = 1.0f / (float)plan.G;
       if (launch_score_sweep(wa, stream) != hipSuccess) return PKV_ERR_HIP;
       if (rec) rec->after(PKV_KERNEL_SCORE_SWEEP, stream);
+    }
+  } else if (gp.layers > 0) {
+    // (layers that are kept whole take no part)
+    bool first = true;
+    for (int32_t l = 0; l < L;) {
+      LagArgs ga;
+      memset(&ga, 0, sizeof(ga));
+      const int32_t l0 = l;
+      for (; l < L && ga.L < gp.layers; ++l) {
+        if (descs[l].k_l >= d.N) continue;
+        ga.layer[ga.L].Q = static_cast<const uint16_t*>(ptrs[l].Q);
+        ga.layer[ga.L].K = static_cast<const uint16_t*>(ptrs[l].K);
+        ga.layer[ga.L].k_l = descs[l].k_l;
+        ga.layer[ga.L++].slot = l - l0;
+      }
+      if (ga.L == 0) break;
+      ga.seq_lens = seq_lens;
+      ga.raw = raw + (size_t)l0 * plan.BH * d.N;
+      ga.words = reinterpret_cast<unsigned long long*>(pooled_ws);
+      ga.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
+      ga.B = d.B; ga.Hq = d.Hq; ga.Hkv = d.Hkv; ga.G = plan.G; ga.alpha = d.alpha; ga.N = d.N; ga.R = plan.R; ga.d = d.d;
+      ga.uniform = seq_lens ? 0 : 1;
+      ga.parts = gp.parts;
+      ga.groups = gp.groups;
+      ga.alpha_magic = (65536u + (uint32_t)d.alpha - 1) / (uint32_t)d.alpha;
+      ga.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;
+      ga.hkv_magic = 0xFFFFFFFFu / (uint32_t)d.Hkv;
+      const int64_t items = (int64_t)ga.L * plan.BH * gp.parts;
+      ga.grid = items < kStreamGrid ? (int32_t)items : kStreamGrid;
+      ga.wait_ticks = (d.flags & PKV_FLAG_NO_WAIT) ? 0 : kResidentWaitTicks;
+      ga.q_sb = d.q_sb; ga.q_sh = d.q_sh; ga.q_st = d.q_st;
+      ga.kv_sb = d.kv_sb; ga.kv_sh = d.kv_sh; ga.kv_st = d.kv_st;
+      ga.kappa = kappa;
+      ga.inv_G = 1.0f / (float)plan.G;
+      if (launch_score_lag(ga, first, stream) != hipSuccess) return PKV_ERR_HIP;
+      first = false;
+      if (rec) rec->after(lag_kernel_id(plan), stream);
     }
   } else if (sp.layers > 0) {
     for (int32_t l0 = 0; l0 < L; l0 += sp.layers) {
@@ -895,6 +980,12 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t lse_supplie
   *scratch_bytes = 0;
   *scratch_room = plan.total - plan.off_pooled;
   if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return PKV_OK;
+  const LagPlan gp = lag_plan(plan, *desc, lse_mode);
+  if (gp.layers > 0) {
+    *kernel_id = lag_kernel_id(plan);
+    *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.groups * kLagGroupBytes;
+    return PKV_OK;
+  }
   const SweepPlan wp = sweep_plan(plan, *desc, lse_mode);
   const StreamPlan sp = stream_plan(plan, *desc, lse_mode);
   *kernel_id = wp.C > 0 ? PKV_KERNEL_SCORE_SWEEP : (sp.layers > 0 ? PKV_KERNEL_SCORE_STREAM : PKV_KERNEL_SCORE_RESIDENT);
@@ -906,6 +997,14 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t lse_supplie
 int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink, void* stream) {
   if (!buf || !sink || bytes == 0 || bytes % 16 != 0 || ((uintptr_t)buf & 15) || ((uintptr_t)sink & 3)) return PKV_ERR_INVALID_ARG;
   return launch_probe_read(buf, bytes, sink, static_cast<hipStream_t>(stream)) == hipSuccess ? PKV_OK : PKV_ERR_HIP;
+}
+
+int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t lse_supplied) {
+  if (check_desc(desc) != PKV_OK) return 0;
+  const Plan plan = make_plan(*desc, 1);
+  if (lse_supplied) return 1;
+  if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return 2;
+  return lag_plan(plan, *desc, false).layers > 0 || stream_plan(plan, *desc, false).layers > 0 ? 1 : 2;
 }
 
 const char* pkv_status_string(int status) {

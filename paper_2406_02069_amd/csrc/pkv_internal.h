@@ -72,7 +72,7 @@ struct ResidentLayer {
   const uint16_t* K;
   const float* lse;  // [B][Hq][alpha] supplied natural-log softmax denominators, or null (two-sweep scoring)
   int32_t k_l;
-  int32_t pad;
+  int32_t slot;  // (lagging kernel) the layer's place among the score arrays
 };
 
 struct ResidentArgs {
@@ -122,6 +122,30 @@ struct StreamArgs {
 int stream_item_keys(int R);
 // clear_err: the first launch of a call also clears the error word
 hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s);
+
+// ---- one-pass scoring, probabilities waiting on the chip two items long, over many layers (pkv_lag.hip) ----
+constexpr int kLagItems = 255;      // items of a workgroup per launch, at most (table in LDS)
+constexpr int kLagKeys = 512;       // keys of an item
+constexpr int kLagGroupBytes = 2048;  // of the workspace, per unit and group of 64 query rows
+
+struct LagArgs {
+  ResidentLayer layer[kResidentMaxLayers];
+  const int32_t* seq_lens;
+  float* raw;                 // [layer slot][B][Hkv][N] un-pooled scores
+  unsigned long long* words;  // [units][groups][256] sums, references, maxima; cleared by the first of the two kernels
+  int32_t* err;
+  int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
+  int32_t uniform;            // 1: every unit has N keys and none is kept whole
+  int32_t parts;              // uniform: items of a unit (those beyond its end are empty)
+  int32_t grid;               // workgroups (kStreamGrid, fewer if there are fewer items)
+  int32_t wait_ticks;
+  int32_t groups;             // of 64 query rows
+  uint32_t alpha_magic;       // ceil(2^16 / alpha): row / alpha = (row alpha_magic) >> 16 for rows below 512
+  uint32_t bh_magic, hkv_magic;  // floor((2^32 - 1) / x) of B Hkv and Hkv: u / x = ((u + 1) magic) >> 32 while (u + 1) x <= 2^32
+  int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
+  float kappa, inv_G;
+};
+hipError_t launch_score_lag(const LagArgs& a, bool clear_err, hipStream_t s);
 
 // ---- scoring in two streaming launches for many query rows, over many layers (pkv_sweep.hip) ----
 constexpr int kSweepGrid = 256;     // workgroups, one per compute unit

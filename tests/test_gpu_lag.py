@@ -1,0 +1,147 @@
+"""One-pass scoring, 64 rows at a time, probabilities two steps behind (33 .. 512 query rows) at the edges of its work split:
+rows around the groups, lengths around the items, ragged batches, odd and even numbers of items and steps, layers kept whole,
+references that do not fit or are -inf, precision, the end of the workspace, waits that are given up."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_02069_amd import binding, synth
+from tests.parity import compare_layer
+from tests.test_gpu_stream import _along, _check, _inputs, precision_of_scores
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _taken(Q, K, k_l):
+    """The kernel under test takes the call: every logit formed once, and not the kernel for few rows."""
+    desc = binding.make_desc(Q, K, k_l, synth.POOL_MAX, 7, None)
+    R = Q.shape[1] // K.shape[1] * Q.shape[2]
+    groups = (R + 63) // 64
+    return binding.scoring_sweeps(desc) == 1 and binding.scoring_route(desc)[1] == K.shape[0] * K.shape[1] * groups * 2048
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,alpha", [(5, 13), (3, 32), (127, 1), (8, 16), (3, 43), (4, 48), (1, 64), (7, 28), (5, 51), (8, 32), (7, 37),
+                                     (8, 40), (6, 64), (7, 56), (8, 64)])
+def test_rows(d, G, alpha):
+    # one to eight groups of rows, the last of them full or with a single row
+    Hkv = 2 if G * alpha > 64 else 128
+    Q, K, V = _inputs(1, Hkv * G, Hkv, d, 4111, alpha, seed=G * 100 + alpha + d)
+    assert _taken(Q, K, alpha + 60)
+    _check(Q, K, V, alpha + 60)
+
+
+@pytest.mark.parametrize("N", [1024, 1025, 1055, 1056, 1057, 1535, 1536, 1537, 1567, 1568, 2047, 2048, 2049, 2560])
+@pytest.mark.parametrize("G,alpha", [(4, 32), (2, 64)])
+def test_lengths_around_an_item(N, G, alpha):
+    Q, K, V = _inputs(1, 3 * G, 3, 128, N, alpha, seed=N + G)
+    assert _taken(Q, K, alpha + 40)
+    _check(Q, K, V, alpha + 40)
+
+
+@pytest.mark.parametrize("d,G,alpha", [(64, 3, 40), (128, 4, 32), (128, 3, 51), (128, 8, 32), (64, 5, 64)])
+def test_ragged_batch(d, G, alpha):
+    # sequences without scores, of one key more than the window, and items that units share a workgroup's round with
+    N = 6000
+    lens = np.array([6000, 0, 7, alpha, alpha + 1, 100, 512, 513, 4097, 1037, 2048 + alpha, 2047 + alpha], dtype=np.int32)
+    Q, K, V = _inputs(len(lens), 2 * G, 2, d, N, alpha, seed=G)
+    for b, n in enumerate(lens):
+        K[b, :, n:] = float("nan")
+    assert _taken(Q, K, alpha + 20)
+    _check(Q, K, V, alpha + 20, lens)
+
+
+@pytest.mark.parametrize("d,Hkv,G,alpha,L,N", [(64, 16, 8, 8, 5, 33000), (128, 16, 4, 32, 9, 5000), (64, 16, 3, 50, 7, 6000), (128, 4, 8, 33, 6, 9000), (64, 40, 4, 64, 11, 4100)])
+def test_many_items_per_workgroup_equal_one_call_per_layer(d, Hkv, G, alpha, L, N):
+    # several rounds of items, units that straddle them, odd and even numbers of steps; layers kept whole among them
+    data = [_inputs(1, G * Hkv, Hkv, d, N, alpha, seed=500 + l) for l in range(L)]
+    ks = [alpha + 3 + 5 * l for l in range(L)]
+    ks[1] = N
+    ks[L - 1] = N + 7
+    assert _taken(data[0][0], data[0][1], ks[0])
+    outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_MAX, 7,
+                                   want_scores=True)
+    full = torch.full((1,), N, dtype=torch.int32, device=DEV)
+    torch.cuda.synchronize()
+    for l in range(L):
+        one = binding.compress_layer(*data[l], ks[l], synth.POOL_MAX, 7, seq_lens=full, want_scores=True)
+        torch.cuda.synchronize()
+        for x, y in zip(outs[l], one):
+            assert torch.equal(x, y), l
+    compare_layer(*data[0], ks[0], alpha, synth.POOL_MAX, 7, None, outs[0])
+
+
+@pytest.mark.parametrize("G,alpha", [(4, 32), (8, 24), (8, 64)])
+@pytest.mark.parametrize("first,top", [(-70, 75), (-20, 50), (-5, 75), (-30, 90), (-60, 20)])
+def test_normalisers_far_above_the_references(G, alpha, first, top):
+    # in every row one key stands far above the others and above key 0, and above the keys the references come from: the unit
+    # is scored again, and equal keys in different waves and items get equal scores
+    binades = np.random.RandomState(G + alpha).uniform(-25, 25, 4100)
+    binades[0], binades[700] = first, top
+    Q, K, V = _along(G, alpha, binades, 128, seed=G)
+    equal = [100, 701, 1500, 1800, 3999]
+    K[0, 0, equal] = K[0, 0, 1500].clone()
+    print("far", G, alpha, first, top, flush=True)
+    out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+    assert len(set(out[4][0, 0, equal].tolist())) == 1
+
+
+def test_some_units_of_many_are_scored_again():
+    # two of forty-eight heads in three of nine layers, in a launch whose workgroups have several items
+    L, Hkv, G, alpha, N = 9, 16, 4, 32, 5000
+    data = [_inputs(1, G * Hkv, Hkv, 128, N, alpha, seed=70 + l, scale=0.5) for l in range(L)]
+    for l in (0, 4, 8):
+        for g in (3, 15):
+            data[l][1][0, g, 1234 + l] = 40 * data[l][0][0, g * G, 3]
+    outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], [alpha + 30] * L,
+                                   synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    for l in (0, 3, 8):
+        compare_layer(*data[l], alpha + 30, alpha, synth.POOL_NONE, 1, None, outs[l])
+
+
+@pytest.mark.parametrize("d,G,alpha", [(64, 4, 32), (128, 4, 32), (128, 5, 51)])
+@pytest.mark.parametrize("lo,hi", [(0, 1), (0, 600), (1024, 2048), (0, 4000), (500, 5000)])
+def test_logits_of_minus_infinity(d, G, alpha, lo, hi):
+    # products that overflow to -inf: single keys, whole items, and all keys that the references come from
+    Q, K, V = _inputs(1, G, 1, d, 5100, alpha, seed=G + hi)
+    Q = Q.abs()
+    K[:, :, lo:hi] = -3e38
+    _check(Q, K, V, alpha + 30, pool=synth.POOL_NONE, pw=1)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,N,alpha", [(64, 64, 128, 8192, 40), (32, 8, 128, 30000, 32), (16, 4, 64, 5000, 32), (64, 8, 128, 8192, 64)])
+@pytest.mark.parametrize("sink", [None, 3, -4])
+def test_precision_of_the_scores(Hq, Hkv, d, N, alpha, sink):
+    # errors of single rows average out over this many; what is left is common to all rows: the rounding of kappa, 2^-25 of a
+    # logit up to 10 binades from the mean, 10 ln 2 / 2^25 = 2.1e-7
+    assert precision_of_scores(Hq, Hkv, d, N, alpha, sink) < 2.1e-7
+
+
+@pytest.mark.parametrize("L,B,Hkv,G,alpha,N", [(1, 1, 1, 4, 32, 1024), (33, 1, 8, 2, 64, 1024), (3, 2, 8, 8, 24, 1537), (7, 1, 4, 8, 64, 4096)])
+def test_nothing_is_written_behind_the_workspace(L, B, Hkv, G, alpha, N):
+    data = [_inputs(B, G * Hkv, Hkv, 128, N, alpha, seed=900 + l) for l in range(L)]
+    assert _taken(data[0][0], data[0][1], alpha + 5)
+    call = binding.LayersCall([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], [alpha + 5] * L, synth.POOL_MAX, 7,
+                              want_scores=True)
+    need = binding.workspace_bytes(call.descs[0], L)
+    guarded = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device=DEV)   # (the guard is this test's own memory)
+    call.workspace = guarded[:need]
+    outs = call.run()
+    torch.cuda.synchronize()
+    assert bool((guarded[need:] == 0x5A).all())
+    compare_layer(*data[-1], alpha + 5, alpha, synth.POOL_MAX, 7, None, outs[-1])
+
+
+def test_given_up_waits_are_reported(monkeypatch):
+    # forced from the host: no wait for other workgroups; the kernel runs to its end and the counts say so
+    Q, K, V = _inputs(2, 16, 4, 128, 5000, 32, seed=1)
+    monkeypatch.setattr(binding, "DESC_FLAGS", binding.FLAG_NO_WAIT)
+    out = binding.compress_layer(Q, K, V, 80, synth.POOL_MAX, 7)
+    torch.cuda.synchronize()
+    assert out[3].tolist() == [-1, -1]
+    monkeypatch.setattr(binding, "DESC_FLAGS", 0)
+    _check(Q, K, V, 80)
