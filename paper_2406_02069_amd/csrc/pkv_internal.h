@@ -187,6 +187,7 @@ struct SelectBatchArgs {
   int32_t nrb;         // partial score arrays to add per layer
   float inv_G;         // factor applied to the sum of the partials
   const int32_t* err;  // error word of the scoring kernel (non-zero: a wait was given up), or null
+  int32_t listed;      // a launch before this one has listed the candidates of long prefixes
 };
 
 struct GatherLayer {
@@ -322,7 +323,7 @@ inline int current_device_slot() {
 hipError_t launch_score_resident(const ResidentArgs& a, hipStream_t s);
 hipError_t launch_recall(const RecallArgs& a, int nlayers, hipStream_t s);
 // fuse_gather: the selection workgroup of a unit also copies the unit's kept rows (compact output only)
-hipError_t launch_pool_select_batch(const SelectBatchArgs& a, const GatherBatchArgs& ga, bool fuse_gather, int nlayers,
+hipError_t launch_pool_select_batch(SelectBatchArgs& a, const GatherBatchArgs& ga, bool fuse_gather, int nlayers,
                                     hipStream_t s);
 hipError_t launch_gather_batch(const GatherBatchArgs& a, hipStream_t s);
 hipError_t launch_probe_read(const void* buf, size_t bytes, uint32_t* sink, hipStream_t s);

@@ -22,8 +22,11 @@
 // copy of the kept rows, by the profiler, against a search of T over all keys one bit per round: one unit of 1k keys
 // 15.2 -> 9.0 us, 8 units of 8k 18.2 -> 11.4, 256 units of 8k 28 -> 19, of 32k 48 -> 27, 2048 units of 8k .. 16k
 // 215 -> 128 (its 0.55 GB of kept rows take 112 us at the rate of a large copy).
-// Longer prefixes (select_long) pool through LDS in tiles of 16384 positions (all loads of a tile in flight at once),
-// keep their keys in the pooled array in global memory and use a radix select with LDS histograms, digits of up to
+// Longer prefixes are cut into stretches of up to 16384 keys, a workgroup each, which list the keys that can be among the
+// largest (select_stretch_kernel); the unit's workgroup finds the kept ones among the listed (select_merge).  Where a
+// stretch cannot list them (more than a quarter of it kept, very many equal scores) or pooled scores are asked for, one workgroup
+// does it alone (select_long): it pools through LDS in tiles of 16384 positions (all loads of a tile in flight at once),
+// keeps its keys in the pooled array in global memory and uses a radix select with LDS histograms, digits of up to
 // 11 bits below the leading bits that all keys share (read off the largest and the smallest key).
 // All counters are integers and the emission is ordered, so the result does not depend on scheduling.
 #include <type_traits>
@@ -42,6 +45,7 @@ constexpr int NW = NT / 64;
 constexpr int TL = 16384;          // pooling tile of long prefixes (outputs per iteration)
 constexpr int HIST = 2048;         // bins of the widest digit
 constexpr int kLdsKeys = 32768;    // prefix lengths up to this keep their keys in registers
+constexpr uint32_t kOpen = 512u;   // keys of a bin that are ranked against each other
 constexpr int kPad = 32;           // neutral scores in LDS before the prefix and behind it (half a pooling window)
 
 // Workgroup barrier that orders LDS traffic only.  A full __syncthreads() carries fences over global memory too,
@@ -138,7 +142,7 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* s
 }
 
 
-// A longer prefix.
+// A longer prefix, by one workgroup.
 __device__ __forceinline__ void select_long(const float* raw, int nrb, size_t rb_stride, float inv_G, float* pooled, int32_t* idx, int npre, int kk, int alpha, int pool,
                                             int pool_w, uint32_t* lkeys, uint32_t* hist,
                                             uint32_t* scan32, uint32_t* sel) {
@@ -462,6 +466,118 @@ __device__ __forceinline__ uint32_t find_bin(uint32_t* hist, uint32_t kk, uint32
   return total;
 }
 
+template <int NJ>
+struct Scores {
+  f32x4 v[NJ];
+};
+
+// Pooled scores of a thread's positions p0 + 256 * jj + c out of an LDS copy of the scores (half a window of them, or of
+// neutral values, on both sides); v holds the scores on entry.  w0: first position of the wave, n: positions in all.
+template <int NJ>
+__device__ __forceinline__ Scores<NJ> pool_lds(const float* lsc, int p0, int w0, int n, int r, bool is_max, int pool_w,
+                                               Scores<NJ> s) {
+  f32x4* v = s.v;
+  const float inv_w = 1.0f / (float)pool_w;
+  // windows summed (or maximised) in ascending position order
+  auto pool_fixed = [&](auto RR, auto MX) __attribute__((always_inline)) {
+    constexpr int R = decltype(RR)::value;
+    constexpr bool mx = decltype(MX)::value;
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) {
+      if (w0 + 256 * jj >= n) continue;
+      const f32x4 lo = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj - 4);
+      const f32x4 hi = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj + 4);
+      const f32x4 md = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj);
+      const float x[12] = {lo[0], lo[1], lo[2], lo[3], md[0], md[1], md[2], md[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float acc = x[4 + c - R];
+#pragma unroll
+        for (int u = -R + 1; u <= R; ++u) acc = mx ? fmaxf(acc, x[4 + c + u]) : acc + x[4 + c + u];
+        v[jj][c] = mx ? acc : acc * inv_w;
+      }
+    }
+  };
+  using std::integral_constant;
+  if (r <= 3) {
+    if (is_max) {
+      if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::true_type{});
+      else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::true_type{});
+      else pool_fixed(integral_constant<int, 3>{}, std::true_type{});
+    } else {
+      if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::false_type{});
+      else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::false_type{});
+      else pool_fixed(integral_constant<int, 3>{}, std::false_type{});
+    }
+  } else {
+    // wider windows: one new score per step for the thread's four outputs
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) {
+      if (w0 + 256 * jj >= n) continue;
+      const float* lp = lsc + p0 + 256 * jj - r;
+      float x0 = lp[0], x1 = lp[1], x2 = lp[2];
+      f32x4 acc = is_max ? f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY} : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int u = 0; u <= 2 * r; ++u) {
+        const float x3 = lp[u + 3];
+        acc[0] = is_max ? fmaxf(acc[0], x0) : acc[0] + x0;
+        acc[1] = is_max ? fmaxf(acc[1], x1) : acc[1] + x1;
+        acc[2] = is_max ? fmaxf(acc[2], x2) : acc[2] + x2;
+        acc[3] = is_max ? fmaxf(acc[3], x3) : acc[3] + x3;
+        x0 = x1;
+        x1 = x2;
+        x2 = x3;
+      }
+      v[jj] = is_max ? acc : acc * inv_w;
+    }
+  }
+  return s;
+}
+
+// The need-th largest of the n_open distances in hist (entries behind the last are 0), plus lo: every distance counts those
+// above it and those not below it.  Needs n_open <= NT.
+__device__ __forceinline__ uint32_t rank_open(const uint32_t* hist, uint32_t n_open, uint32_t need, uint32_t lo, uint32_t* sel) {
+  lds_barrier();
+  if (threadIdx.x < n_open) {
+    const uint32_t d = hist[threadIdx.x];
+    uint32_t above = 0u, from = 0u;
+    for (uint32_t j = 0; j < n_open; j += 4) {
+      const u32x4 q = *reinterpret_cast<const u32x4*>(hist + j);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        above += q[c] > d ? 1u : 0u;
+        from += q[c] >= d ? 1u : 0u;
+      }
+    }
+    if (above < need && need <= from) sel[1] = lo + d;
+  }
+  lds_barrier();
+  return __builtin_amdgcn_readfirstlane(sel[1]);
+}
+
+// Bins of the distance from a reference key, descending: the first half for keys from the reference up, 1/8 of a binade
+// each (2^20 units of the bit pattern), the second half for those below it, 1/64 of a binade each (2^17 units; 16 binades in
+// 1024 bins); the first and the last bin are open to the outside.
+template <int BINS>
+struct KeyBins {
+  static constexpr int kUp = 20, kDown = 17;
+  static constexpr uint32_t kMid = BINS / 2;
+  uint32_t ref;
+  __device__ __forceinline__ uint32_t of(uint32_t k) const {
+    return k >= ref ? kMid - 1u - min((k - ref) >> kUp, kMid - 1u) : kMid + min((ref - 1u - k) >> kDown, kMid - 1u);
+  }
+  // smallest and largest key of a bin that holds one (never 0, the mark of a position that does not exist)
+  __device__ __forceinline__ uint32_t lower_edge(uint32_t bin) const {
+    if (bin < kMid) return max(ref + ((kMid - 1u - bin) << kUp), 1u);
+    const uint32_t down = (bin - kMid + 1u) << kDown;
+    return bin < BINS - 1u && down < ref ? ref - down : 1u;
+  }
+  __device__ __forceinline__ uint32_t upper_edge(uint32_t bin) const {
+    if (bin >= kMid) return ref - 1u - ((bin - kMid) << kDown);
+    const uint32_t up = ref + ((kMid - bin) << kUp) - 1u;
+    return bin > 0u && up >= ref ? up : 0xFFFFFFFFu;
+  }
+};
+
 // A prefix of at most 1024 * PER keys.  Wave w owns positions [w * 64 * PER, (w + 1) * 64 * PER), lane l of it the four
 // from 256 * jj + 4 * l on, for every jj.  Returns true when the kept prefix positions are left in LDS (`keep`, kk
 // ascending entries), false when they have been written to idx instead.
@@ -480,7 +596,8 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
   const bool is_max = a.pool == PKV_POOL_MAX;
 
   // ---- A. group mean + pooling ----
-  f32x4 v[NJ];
+  Scores<NJ> s;
+  f32x4* v = s.v;
   int lim = npre - p0;  // the thread's position 256 * jj + c exists iff 256 * jj + c < lim
 #pragma unroll
   for (int jj = 0; jj < NJ; ++jj) {
@@ -525,59 +642,7 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
       }
     }
     lds_barrier();
-    const float inv_w = 1.0f / (float)a.pool_w;
-    // windows summed (or maximised) in ascending position order
-    auto pool_fixed = [&](auto RR, auto MX) {
-      constexpr int R = decltype(RR)::value;
-      constexpr bool mx = decltype(MX)::value;
-#pragma unroll
-      for (int jj = 0; jj < NJ; ++jj) {
-        if (w0 + 256 * jj >= npre) continue;
-        const f32x4 lo = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj - 4);
-        const f32x4 hi = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj + 4);
-        const f32x4 md = *reinterpret_cast<const f32x4*>(lsc + p0 + 256 * jj);
-        const float x[12] = {lo[0], lo[1], lo[2], lo[3], md[0], md[1], md[2], md[3], hi[0], hi[1], hi[2], hi[3]};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          float acc = x[4 + c - R];
-#pragma unroll
-          for (int u = -R + 1; u <= R; ++u) acc = mx ? fmaxf(acc, x[4 + c + u]) : acc + x[4 + c + u];
-          v[jj][c] = mx ? acc : acc * inv_w;
-        }
-      }
-    };
-    using std::integral_constant;
-    if (r <= 3) {
-      if (is_max) {
-        if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::true_type{});
-        else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::true_type{});
-        else pool_fixed(integral_constant<int, 3>{}, std::true_type{});
-      } else {
-        if (r == 1) pool_fixed(integral_constant<int, 1>{}, std::false_type{});
-        else if (r == 2) pool_fixed(integral_constant<int, 2>{}, std::false_type{});
-        else pool_fixed(integral_constant<int, 3>{}, std::false_type{});
-      }
-    } else {
-      // wider windows: one new score per step for the thread's four outputs
-#pragma unroll
-      for (int jj = 0; jj < NJ; ++jj) {
-        if (w0 + 256 * jj >= npre) continue;
-        const float* lp = lsc + p0 + 256 * jj - r;
-        float x0 = lp[0], x1 = lp[1], x2 = lp[2];
-        f32x4 acc = is_max ? f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY} : f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int u = 0; u <= 2 * r; ++u) {
-          const float x3 = lp[u + 3];
-          acc[0] = is_max ? fmaxf(acc[0], x0) : acc[0] + x0;
-          acc[1] = is_max ? fmaxf(acc[1], x1) : acc[1] + x1;
-          acc[2] = is_max ? fmaxf(acc[2], x2) : acc[2] + x2;
-          acc[3] = is_max ? fmaxf(acc[3], x3) : acc[3] + x3;
-          x0 = x1;
-          x1 = x2;
-          x2 = x3;
-        }
-        v[jj] = is_max ? acc : acc * inv_w;
-      }
-    }
+    s = pool_lds(lsc, p0, w0, npre, r, is_max, a.pool_w, s);
   }
   uint32_t key[NJ][4];  // 0: no such position
   lim = fresh(npre) - p0;
@@ -618,48 +683,12 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
   // is not much below T.  A group's keys lie 256 positions apart: neighbours share a pooling window.
   int gs = 1;
   while (2 * gs <= NJ && 4 * gs * kk <= npre) gs *= 2;
-  // Bins, descending: 0 .. 1023 for keys from the reference up, 1/8 of a binade each (2^20 units of the bit pattern),
-  // 1024 .. 2047 for those below it, 1/64 of a binade each (2^17 units, 16 binades in all); the first and the last bin
-  // are open to the outside.
-  constexpr int kUp = 20, kDown = 17;
-  constexpr uint32_t kMid = HIST / 2;
-  auto bin_of = [&](uint32_t k) -> uint32_t {
-    return k >= ref ? kMid - 1u - min((k - ref) >> kUp, kMid - 1u) : kMid + min((ref - 1u - k) >> kDown, kMid - 1u);
-  };
-  // smallest and largest key of a bin that holds one (never 0, the mark of a position that does not exist)
-  auto lower_edge = [&](uint32_t bin) -> uint32_t {
-    if (bin < kMid) return max(ref + ((kMid - 1u - bin) << kUp), 1u);
-    const uint32_t down = (bin - kMid + 1u) << kDown;
-    return bin < HIST - 1u && down < ref ? ref - down : 1u;
-  };
-  auto upper_edge = [&](uint32_t bin) -> uint32_t {
-    if (bin >= kMid) return ref - 1u - ((bin - kMid) << kDown);
-    const uint32_t up = ref + ((kMid - bin) << kUp) - 1u;
-    return bin > 0u && up >= ref ? up : 0xFFFFFFFFu;
-  };
-  constexpr uint32_t kOpen = 512u;  // keys of a bin that are ranked against each other
+  const KeyBins<HIST> bins{ref};
+  auto bin_of = [&](uint32_t k) { return bins.of(k); };
+  auto lower_edge = [&](uint32_t bin) { return bins.lower_edge(bin); };
+  auto upper_edge = [&](uint32_t bin) { return bins.upper_edge(bin); };
   uint32_t n_list = 0u, T = 0u, lo = 0u, hi = 0u, need = (uint32_t)kk, n_open = 0u;  // (T's bin: edges, rank in it, keys)
   bool ok = false, have_bin = false;
-  // the need-th largest of the n_open distances in hist (entries behind the last are 0): every key counts those above it
-  // and those not below it
-  auto rank_open = [&]() {
-    lds_barrier();
-    if ((uint32_t)tid < n_open) {
-      const uint32_t d = hist[tid];
-      uint32_t above = 0u, from = 0u;
-      for (uint32_t j = 0; j < n_open; j += 4) {
-        const u32x4 q = *reinterpret_cast<const u32x4*>(hist + j);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          above += q[c] > d ? 1u : 0u;
-          from += q[c] >= d ? 1u : 0u;
-        }
-      }
-      if (above < need && need <= from) sel[1] = lo + d;
-    }
-    lds_barrier();
-    T = __builtin_amdgcn_readfirstlane(sel[1]);
-  };
   // The list pays for small shares of the prefix.  256 units of 32k keys, with and without it: kk = 0.02 of the prefix 22 and
   // 30 us, 0.1 27 and 32, 0.2 32 and 34, 0.3 38 and 37, 0.5 42 and 39; of 8k keys 15 and 16, 13 and 14, 14 and 14, 16 and 15,
   // 17 and 15.
@@ -729,7 +758,7 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
         const uint32_t k = lkey[i];
         if (bin_of(k) == bin) hist[atomicAdd(&sel[3], 1u)] = k - lo;
       }
-      rank_open();
+      T = rank_open(hist, n_open, need, lo, sel);
     } else {
       hi = upper_edge(bin);
       have_bin = true;
@@ -826,7 +855,7 @@ __device__ __forceinline__ bool select_short(const SelectBatchArgs& a, const flo
 #pragma unroll
         for (int c = 0; c < 4; ++c)
           if (key[jj][c] >= lo && key[jj][c] <= hi) hist[atomicAdd(&sel[3], 1u)] = key[jj][c] - lo;
-      rank_open();
+      T = rank_open(hist, n_open, need, lo, sel);
     }
   }
   uint32_t cgt = 0u, ceq = 0u;
@@ -921,6 +950,347 @@ __device__ __forceinline__ void gather_unit(const GatherBatchArgs& ga, const Gat
   }
 }
 
+// ---- prefixes beyond 32768 keys, first step: candidates ----
+// The prefix is cut into stretches of nearly equal length, a workgroup each.  A workgroup pools its stretch and lists the
+// keys that can be among the unit's kk largest: those at or above a bound that at least kk keys of the stretch reach.  The
+// lists (keys, positions within the stretch, their number, the bound and the reference of the bins) lie in the unit's
+// array for pooled scores, at the stretch's own place.  The kk largest of the unit are found among the listed keys then
+// (select_merge).  What bounds it: for few units the latency of a dozen steps between barriers, twice (17 and 14 us); for
+// many some 25 vector operations per key beside the read of the scores (256 units of 128k keys: 80 us, 26 of them the read
+// alone).  Measured against one workgroup per unit, whole calls: one layer of 8 units of 128k keys 190 -> 138 us, of 50k
+// 119 -> 88, 4 layers of 100k keys, 1024 kept, 441 -> 386, 32 layers of 128k 3222 -> 3207.  Stretches of 8192 keys by 256
+// threads: 137, 88, 386; 16 layers of 60k keys 442 instead of 436, 8 of 40k 376 instead of 369.
+constexpr int kMaxStretches = 64;       // a lane of a wave each
+constexpr int kStretchThreads = 512;
+constexpr int kStretch = 16384;         // keys a workgroup holds in registers
+constexpr int kStretchWords = kStretch + 2 * kPad;
+constexpr int kStretchBins = 1024;
+constexpr uint32_t kNoList = 0xFFFFFFFFu;
+struct Stretches {
+  int count, len;  // count 0: the unit is left to select_long; the last stretch may be shorter
+};
+// A stretch must hold four keys per key to select, for the bound to be worth its while, and no pooled scores may be asked
+// for (they would lie where the lists do).
+__host__ __device__ inline int stretch_count(int npre) { return (npre + kStretch - 1) / kStretch; }
+__device__ __forceinline__ Stretches stretches(int npre, int kk, bool listed, bool write_pooled) {
+  if (!listed || write_pooled || kk <= 0 || npre <= kLdsKeys) return {0, 0};
+  const int p = stretch_count(npre);
+  if (p > kMaxStretches) return {0, 0};
+  const int len = ((npre + p - 1) / p + 63) & ~63;
+  const int last = npre - (p - 1) * len;
+  return {last >= 64 && 4 * kk <= last ? p : 0, len};
+}
+
+__global__ __launch_bounds__(kStretchThreads, 4) void select_stretch_kernel(const SelectBatchArgs a) {
+  constexpr int NTA = kStretchThreads, NJ = kStretch / (4 * NTA), CW = 64 * 4 * NJ, NWA = NTA / 64, OWN = kStretchBins / NTA;
+  extern __shared__ uint32_t area[];  // kStretchWords entries
+  __shared__ uint32_t hist[kStretchBins];
+  __shared__ uint32_t scan[2 * NWA];
+  __shared__ uint32_t sel[1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int BH = a.B * a.Hkv;
+  const int l = (int)blockIdx.y / BH;
+  const int bg = (int)blockIdx.y - l * BH;
+  const SelectLayer& ly = a.layer[l];
+  int n = a.N;
+  if (a.seq_lens) {
+    n = a.seq_lens[bg / a.Hkv];
+    n = n < 0 ? 0 : (n > a.N ? a.N : n);
+  }
+  if (ly.k_l >= n) return;
+  const int npre = n - a.alpha, kk = ly.k_l - a.alpha;
+  const Stretches st = stretches(npre, kk, a.listed != 0, ly.write_pooled != 0);
+  if ((int)blockIdx.x >= st.count) return;
+  const int t0 = (int)blockIdx.x * st.len;
+  const int len = min(st.len, npre - t0);       // keys of the stretch
+  const int have = min(len + kPad, npre - t0);  // scores behind its first one that are looked at
+  const size_t rb_stride = (size_t)BH * a.N;
+  const float* raw = a.raw + ((size_t)l * a.nrb * BH + bg) * a.N + t0;
+  uint32_t* out = reinterpret_cast<uint32_t*>(ly.pooled) + (size_t)bg * a.N + t0;
+
+  // ---- group mean + pooling (as select_short has it) ----
+  const int w0 = wave * CW, p0 = w0 + 4 * lane;
+  const int r = (a.pool == PKV_POOL_NONE) ? 0 : (a.pool_w - 1) / 2;
+  const bool is_max = a.pool == PKV_POOL_MAX;
+  Scores<NJ> s;
+  f32x4* v = s.v;
+  int lim = have - p0;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj) {
+    const int g0 = w0 + 256 * jj, p = p0 + 256 * jj;
+    v[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (g0 + 256 <= have) v[jj] = *reinterpret_cast<const f32x4_u*>(raw + p);
+    else if (g0 < have) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (256 * jj + c < lim) v[jj][c] = raw[p + c];
+    }
+  }
+  // the scores around them: 32 before the stretch, 32 behind the last position of any thread
+  const float neutral = is_max ? -INFINITY : 0.f;
+  const int pe = tid < kPad ? tid - kPad : kStretch + tid - kPad;
+  const bool edge = tid < 2 * kPad && t0 + pe >= 0 && pe < have;
+  float ve = edge ? raw[pe] : 0.f;
+  for (int q = 1; q < a.nrb; ++q) {
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (256 * jj + c < lim) v[jj][c] += raw[q * rb_stride + p0 + 256 * jj + c];
+    if (edge) ve += raw[q * rb_stride + pe];
+  }
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) hist[tid + NTA * u] = 0u;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj) v[jj] *= a.inv_G;
+  if (r > 0) {
+    float* lsc = reinterpret_cast<float*>(area) + kPad;
+    if (tid < 2 * kPad) lsc[pe] = edge ? ve * a.inv_G : neutral;
+    lim = fresh(have) - p0;
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) {
+      const int g0 = w0 + 256 * jj, p = p0 + 256 * jj;
+      if (g0 < len + kPad) {
+        f32x4 t = v[jj];
+        if (g0 + 256 > have) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) t[c] = 256 * jj + c < lim ? t[c] : neutral;
+        }
+        *reinterpret_cast<f32x4*>(lsc + p) = t;
+      }
+    }
+    lds_barrier();
+    s = pool_lds(lsc, p0, w0, len, r, is_max, a.pool_w, s);
+  }
+  uint32_t key[NJ][4];  // 0: no such position
+  lim = fresh(len) - p0;
+  uint32_t kmax = 0u;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      key[jj][c] = 256 * jj + c < lim ? __float_as_uint(v[jj][c]) : 0u;
+      kmax = max(kmax, key[jj][c]);
+    }
+
+  // ---- the bound: reference, histogram over the largest of every group, the bin in which kk is reached ----
+  kmax = row_max_lane15(kmax);
+  {
+    const uint32_t m = min(min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 15), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 31)),
+                           min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 47), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 63)));
+    if (lane == 0) scan[wave] = m;
+  }
+  if (tid == 0) sel[0] = kNoList;
+  lds_barrier();  // (also: the histogram is cleared)
+  KeyBins<kStretchBins> bins{0u};
+#pragma unroll
+  for (int w = 0; w < NWA; ++w) bins.ref = max(bins.ref, scan[w]);
+  bins.ref = __builtin_amdgcn_readfirstlane(bins.ref);
+  // groups of gs of a thread's keys, at least twice as many as keys to select
+  int gs = 1;
+  while (gs < 4 * NJ && 4 * gs * kk <= len) gs *= 2;
+  uint32_t m = 0u;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) {
+      m = max(m, key[jj][c]);
+      if (((NJ * c + jj + 1) & (gs - 1)) == 0) {  // uniform
+        if (m != 0u) atomicAdd(&hist[bins.of(m)], 1u);
+        m = 0u;
+      }
+    }
+  lds_barrier();
+  {
+    uint32_t h[OWN], sum = 0u;  // thread t owns bins OWN * t ..
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) {
+      h[u] = hist[OWN * tid + u];
+      sum += h[u];
+    }
+    const uint32_t incl = wave_inclusive_sum(sum);
+    if (lane == 63) scan[NWA + wave] = incl;
+    lds_barrier();
+    uint32_t at = incl - sum;
+    for (int w = 0; w < wave; ++w) at += scan[NWA + w];
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) {
+      if (at < (uint32_t)kk && at + h[u] >= (uint32_t)kk) sel[0] = (uint32_t)(OWN * tid + u);
+      at += h[u];
+    }
+  }
+  lds_barrier();
+  const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
+  const uint32_t bound = bin == kNoList ? kNoList : bins.lower_edge(bin);
+
+  // ---- the list, in position order ----
+  uint32_t cnt = 0u;
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cnt += (uint32_t)__popcll(__ballot(key[jj][c] >= bound));
+  if (lane == 0) scan[wave] = cnt;
+  lds_barrier();
+  uint32_t base = 0u, total = 0u;
+#pragma unroll
+  for (int w = 0; w < NWA; ++w) {
+    base += w < wave ? scan[w] : 0u;
+    total += scan[w];
+  }
+  base = __builtin_amdgcn_readfirstlane(base);
+  total = __builtin_amdgcn_readfirstlane(total);
+  const int cap = len / 2;  // keys, behind them half as many words of positions, at the end three words about the list
+  const bool fits = bin != kNoList && total <= (uint32_t)cap && (len - cap - (cap + 1) / 2) >= 3;
+  if (tid == 0) {
+    out[len - 3] = fits ? total : kNoList;
+    out[len - 2] = bound;
+    out[len - 1] = bins.ref;
+  }
+  if (!fits || cnt == 0u) return;
+  uint16_t* pos = reinterpret_cast<uint16_t*>(out + cap);
+#pragma unroll
+  for (int jj = 0; jj < NJ; ++jj) {
+    unsigned long long b[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) b[c] = __ballot(key[jj][c] >= bound);
+    if ((b[0] | b[1] | b[2] | b[3]) == 0ull) continue;
+    uint32_t at = base + bits_below(b[0]) + bits_below(b[1]) + bits_below(b[2]) + bits_below(b[3]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (key[jj][c] >= bound) {
+        out[at] = key[jj][c];
+        pos[at] = (uint16_t)(p0 + 256 * jj + c);
+        ++at;
+      }
+    }
+    base += (uint32_t)(__popcll(b[0]) + __popcll(b[1]) + __popcll(b[2]) + __popcll(b[3]));
+  }
+}
+
+// The second step: the kk largest of the listed keys, their positions in ascending order in `keep` (LDS).  False, and nothing
+// left behind, if a stretch has no list or more than kOpen keys share the bin of the kk-th largest.  The largest bound of
+// any stretch is a bound for the unit: its own stretch holds kk keys that reach it.  Wave w takes the w-th of 16 parts of
+// the lists; the keys are read again in every pass (they are few, and near).
+__device__ __forceinline__ bool select_merge(const uint32_t* lists, const Stretches st, int npre, int kk, uint32_t* keep,
+                                             uint32_t* tab, uint32_t* hist, uint32_t* scan, uint32_t* sel) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t cnt = 0u, bound = 0u, ref = 0u;
+  if (lane < st.count) {
+    const uint32_t* foot = lists + min((lane + 1) * st.len, npre) - 3;
+    cnt = foot[0];
+    bound = foot[1];
+    ref = foot[2];
+  }
+  reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
+  if (tid == 0) sel[3] = 0u;
+  if (__ballot(cnt == kNoList) != 0ull) return false;  // (the same in every wave)
+  bound = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_lane63(bound), 63);
+  const KeyBins<HIST> bins{(uint32_t)__builtin_amdgcn_readlane((int)wave_max_lane63(ref), 63)};
+  const int psh = st.count <= 4 ? 2 : st.count <= 8 ? 1 : 0;  // parts per stretch
+  const int pieces = st.count << psh;
+  // fn(keys of a chunk, lane l those 64 u + l from its first entry on (0 behind the last), piece, first chunk of the piece,
+  // first position of the stretch, positions of the chunk) for the wave's pieces; a wave whose one piece is one chunk reads it
+  // once and for all
+  constexpr int U = 8;
+  struct Chunk {
+    uint32_t x[U];
+  };
+  auto load = [&](const uint32_t* k, int left) {
+    Chunk c;
+#pragma unroll
+    for (int u = 0; u < U; ++u) c.x[u] = 64 * u + lane < left ? k[64 * u + lane] : 0u;
+    return c;
+  };
+  struct Piece {
+    int t0, e0, e1, cap;
+  };
+  auto piece = [&](int p) -> Piece {
+    const int s = p >> psh, part = p & ((1 << psh) - 1);
+    const int t0 = s * st.len, c = __builtin_amdgcn_readlane((int)cnt, s);
+    const int seg = (((c + (1 << psh) - 1) >> psh) + 63) & ~63;
+    const int e0 = min(part * seg, c);
+    return {t0, e0, min(e0 + seg, c), min(st.len, npre - t0) / 2};
+  };
+  const Piece first = piece(min(wave, pieces - 1));
+  const bool one = pieces <= NW && first.e1 - first.e0 <= 64 * U;  // (uniform within the wave)
+  const Chunk kept = load(lists + first.t0 + first.e0, one ? first.e1 - first.e0 : 0);
+  auto for_chunks = [&](auto fn) {
+    if (one) {
+      if (wave < pieces)
+        fn(kept, wave, true, first.t0, reinterpret_cast<const uint16_t*>(lists + first.t0 + first.cap) + first.e0);
+    } else {
+      for (int p = wave; p < pieces; p += NW) {
+        const Piece q = piece(p);
+        for (int i0 = q.e0; i0 < q.e1 || i0 == q.e0; i0 += 64 * U)
+          fn(load(lists + q.t0 + i0, q.e1 - i0), p, i0 == q.e0, q.t0, reinterpret_cast<const uint16_t*>(lists + q.t0 + q.cap) + i0);
+      }
+    }
+  };
+  lds_barrier();
+  for_chunks([&](const Chunk& c, int, bool, int, const uint16_t*) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c.x[u] >= bound) atomicAdd(&hist[bins.of(c.x[u])], 1u);
+  });
+  lds_barrier();
+  (void)find_bin(hist, (uint32_t)kk, scan, sel);  // (there is such a bin: at least kk keys reach the bound)
+  const uint32_t bin = __builtin_amdgcn_readfirstlane(sel[0]);
+  const uint32_t need = (uint32_t)kk - __builtin_amdgcn_readfirstlane(sel[1]);
+  const uint32_t n_open = __builtin_amdgcn_readfirstlane(sel[2]);
+  const uint32_t lo = max(bins.lower_edge(bin), bound);
+  uint32_t T = lo - 1u;  // the whole bin is kept
+  if (need != n_open) {
+    if (n_open > kOpen) return false;
+    for_chunks([&](const Chunk& c, int, bool, int, const uint16_t*) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c.x[u] >= bound && bins.of(c.x[u]) == bin) hist[atomicAdd(&sel[3], 1u)] = c.x[u] - lo;
+    });
+    T = rank_open(hist, n_open, need, lo, sel);
+  }
+  uint32_t cgt = 0u, ceq = 0u;  // (T >= 1 wherever the equal ones matter: an entry that does not exist is none of them)
+  for_chunks([&](const Chunk& c, int p, bool start, int, const uint16_t*) {
+    if (start) cgt = ceq = 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      cgt += (uint32_t)__popcll(__ballot(c.x[u] > T));
+      ceq += (uint32_t)__popcll(__ballot(c.x[u] == T));
+    }
+    if (lane == 0) {
+      tab[p] = cgt;
+      tab[kMaxStretches + p] = ceq;
+    }
+  });
+  lds_barrier();
+  const uint32_t ngt = lane < pieces ? tab[lane] : 0u, neq = lane < pieces ? tab[kMaxStretches + lane] : 0u;
+  const uint32_t gt_incl = wave_inclusive_sum(ngt), eq_incl = wave_inclusive_sum(neq);
+  const uint32_t need_eq = (uint32_t)kk - (uint32_t)__builtin_amdgcn_readlane((int)gt_incl, 63);
+  uint32_t gt_before = 0u, eq_before = 0u;
+  for_chunks([&](const Chunk& c, int p, bool start, int t0, const uint16_t* pos) {
+    if (start) {
+      gt_before = (uint32_t)__builtin_amdgcn_readlane((int)(gt_incl - ngt), p);
+      eq_before = (uint32_t)__builtin_amdgcn_readlane((int)(eq_incl - neq), p);
+    }
+    uint32_t at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) at[u] = c.x[u] >= max(T, 1u) ? (uint32_t)t0 + pos[64 * u + lane] : 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool gt = c.x[u] > T, eq = c.x[u] == T;
+      const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
+      const uint32_t gtb = gt_before + bits_below(bgt), eqb = eq_before + bits_below(beq);
+      if (gt) keep[gtb + min(eqb, need_eq)] = at[u];
+      if (eq && eqb < need_eq) keep[gtb + eqb] = at[u];
+      gt_before += (uint32_t)__popcll(bgt);
+      eq_before += (uint32_t)__popcll(beq);
+    }
+  });
+  lds_barrier();
+  return true;
+}
+
 // PMAX: positions per thread that the launch's longest prefix needs (4 .. 32), LONG: prefixes beyond 32768.
 // fuse_gather: once the unit's kept positions are known, the same workgroup copies the unit's K and V rows (a7): for
 // the few hundred rows of a small budget a launch of its own costs more than the copy.
@@ -962,7 +1332,7 @@ __global__ __launch_bounds__(NT, PMAX <= 16 ? 8 : 4) void pool_select_batch_kern
   const size_t rb_stride = (size_t)BH * a.N;
   const float* raw = a.raw + ((size_t)l * a.nrb * BH + bg) * a.N;
   float* pooled = ly.pooled + (size_t)bg * a.N;
-  bool in_lds = false;
+  bool in_lds = false, merged = false;
   auto run = [&](auto P) {
     if constexpr (decltype(P)::value <= PMAX)
       in_lds = select_short<decltype(P)::value, PMAX>(a, raw, rb_stride, ly.write_pooled ? pooled : nullptr, idx, npre,
@@ -972,10 +1342,15 @@ __global__ __launch_bounds__(NT, PMAX <= 16 ? 8 : 4) void pool_select_batch_kern
   else if (npre <= 8 * NT) run(std::integral_constant<int, 8>{});
   else if (npre <= 16 * NT) run(std::integral_constant<int, 16>{});
   else if (!LONG || npre <= kLdsKeys) run(std::integral_constant<int, 32>{});
-  else if constexpr (LONG)
-    select_long(raw, a.nrb, rb_stride, a.inv_G, pooled, idx, npre, kk, a.alpha, a.pool, a.pool_w, area, hist, scan32, sel);
-  if (in_lds) {
-    auto pos = [&](int j) { return j < kk ? (int)keep[j] : npre + j - kk; };
+  else if constexpr (LONG) {
+    const Stretches st = stretches(npre, kk, a.listed != 0, ly.write_pooled != 0);
+    if (st.count != 0)
+      merged = select_merge(reinterpret_cast<const uint32_t*>(pooled), st, npre, kk, area, area + PMAX * 512, hist, scan32, sel);
+    if (!merged)
+      select_long(raw, a.nrb, rb_stride, a.inv_G, pooled, idx, npre, kk, a.alpha, a.pool, a.pool_w, area, hist, scan32, sel);
+  }
+  if (in_lds || merged) {
+    auto pos = [&](int j) { return j >= kk ? npre + j - kk : merged ? (int)area[j] : (int)keep[j]; };
     for (int j = tid; j < ly.k_l; j += NT) idx[j] = pos(j);
     if (fuse_gather) gather_unit(ga, gl, b, g, pos);
   } else {
@@ -1006,14 +1381,39 @@ hipError_t launch_select(const SelectBatchArgs& a, const GatherBatchArgs& ga, bo
   return hipGetLastError();
 }
 
+// Candidates of the prefixes beyond 32768 keys, a workgroup per stretch.
+hipError_t launch_stretches(SelectBatchArgs& a, int nlayers, hipStream_t s) {
+  const int most = stretch_count(a.N - a.alpha);
+  const int64_t units = (int64_t)nlayers * a.B * a.Hkv;
+  bool wanted = false;
+  for (int l = 0; l < nlayers; ++l) wanted = wanted || (!a.layer[l].write_pooled && a.layer[l].k_l > a.alpha);
+  // (65535: the second dimension of a grid)
+  if (!wanted || most > kMaxStretches || units > 65535) return hipSuccess;  // select_long takes all
+  a.listed = 1;
+  static bool attr_set[kMaxDevices];
+  const size_t dyn = kStretchWords * sizeof(uint32_t);
+  const int dev = current_device_slot();
+  if (dev < 0) return hipErrorInvalidDevice;
+  if (!attr_set[dev]) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_stretch_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    if (e != hipSuccess) return e;
+    attr_set[dev] = true;
+  }
+  hipLaunchKernelGGL(select_stretch_kernel, dim3(most, (unsigned)units), dim3(kStretchThreads), dyn, s, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_pool_select_batch(const SelectBatchArgs& a, const GatherBatchArgs& ga, bool fuse_gather, int nlayers,
+hipError_t launch_pool_select_batch(SelectBatchArgs& a, const GatherBatchArgs& ga, bool fuse_gather, int nlayers,
                                     hipStream_t s) {
   const int npre = a.N - a.alpha;  // of the longest sequence
   if (npre <= 8 * NT) return launch_select<8, false>(a, ga, fuse_gather, nlayers, s);
   if (npre <= 16 * NT) return launch_select<16, false>(a, ga, fuse_gather, nlayers, s);
   if (npre <= kLdsKeys) return launch_select<32, false>(a, ga, fuse_gather, nlayers, s);
+  const hipError_t e = launch_stretches(a, nlayers, s);
+  if (e != hipSuccess) return e;
   return launch_select<32, true>(a, ga, fuse_gather, nlayers, s);
 }
 
