@@ -178,20 +178,36 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
 // in the region of the other kernels' partial statistics, which has room for the items of one layer at least (one per
 // unit), and for 512 KB.  (There the resident kernel is slower: one layer of 8 heads x 50 keys, 32 rows 19.8 -> 21.8 us, of
 // 8 x 100, 64 rows 20.7 -> 24.2.)
+// Up to 32 rows an item is 1024 keys.  Where all items of a call find a workgroup each, items of 512 keys have twice as many
+// at work: one layer of 8 heads x 8k keys, 32 rows 26.6 -> 23.0 us, x 1k 24.2 -> 20.0, of 8 x 1k, d = 64, 8 rows 20.0 -> 17.2;
+// in larger calls they are 3 - 9 % slower (32 layers of 8 x 16k 232 -> 241).  Whether a call is large depends on its number of
+// layers, and the scores must not: up to N = 8192, where one layer would take the small items, a word of statistics stands for
+// 512 keys in either case, and an item of 1024 keys has two of them.  (All items of a unit read them: 32 layers of 8 x 16000
+// keys 228 -> 234, of 24000 keys 334 -> 343, and so not beyond.)
 struct StreamPlan {
-  int layers, grid, items, rows;  // rows: padded to 32 or 64
+  int layers, grid, items;
+  int item_keys, words_per_item, word_rows;
   size_t off, room;
-  size_t stats_bytes() const { return (size_t)items * rows * 8; }
+  size_t item_bytes() const { return (size_t)words_per_item * word_rows * 8; }
+  size_t stats_bytes() const { return items * item_bytes(); }
 };
+constexpr int kStreamSplitKeys = 8192;
 static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
-  StreamPlan p = {0, 0, 0, plan.R <= 32 ? 32 : 64, plan.off_pooled, plan.total - plan.off_pooled};
+  StreamPlan p = {0, 0, 0, 512, 1, plan.R <= 16 ? 16 : plan.R <= 32 ? 32 : 64, plan.off_pooled, plan.total - plan.off_pooled};
   if (lse_mode || plan.R > kStreamMaxRows || !plan.resident_ok) return p;
-  if (d.N < 2 * p.rows) {
+  if (plan.R <= 32 && d.N > 512) {
+    if (d.N > kStreamSplitKeys) p.item_keys = 1024;
+    else if ((int64_t)plan.L * plan.BH * ((d.N + 511) / 512) > kStreamGrid) {
+      p.item_keys = 1024;
+      if ((int64_t)plan.BH * ((d.N + 511) / 512) <= kStreamGrid) p.words_per_item = 2;  // (one layer would take the small items)
+    }
+  }
+  if (d.N < 2 * p.word_rows) {
     p.off = plan.off_part;
     p.room = plan.off_cfin - plan.off_part;
   }
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
-  const int64_t parts = (d.N + stream_item_keys(plan.R) - 1) / stream_item_keys(plan.R);
+  const int64_t parts = (d.N + p.item_keys - 1) / p.item_keys;
   const int64_t per_layer = parts * plan.BH;
   // Every item reads the statistics of all items of its unit: at 33 .. 64 rows and half as many keys per item that is
   // half of the keys' own traffic at 128 items.  Measured against the resident kernel: 8 heads, 64 rows, d = 128:
@@ -201,7 +217,7 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
   const int64_t by_items = (int64_t)kStreamItems * kStreamGrid / per_layer, by_units = kStreamUnits / d.B;
   if (parts > kStreamGrid || by_items < 1 || by_units < 1) return p;
   int64_t nl = by_items < by_units ? by_items : by_units;
-  const int64_t by_room = (int64_t)(p.room / ((size_t)per_layer * p.rows * 8));
+  const int64_t by_room = (int64_t)(p.room / ((size_t)per_layer * p.item_bytes()));
   if (nl > by_room) nl = by_room;
   if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;
   if (nl > plan.L) nl = plan.L;
@@ -313,7 +329,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
   LagPlan gp = {0, 0, 0};
-  StreamPlan sp = {0, 0, 0, 0, 0, 0};
+  StreamPlan sp = {0, 0, 0, 0, 0, 0, 0, 0};
   SweepPlan wp = {0, 0, 0};
   if (any_scores && resident) gp = lag_plan(plan, d, lse_mode);
   if (any_scores && resident && gp.layers == 0) {
@@ -407,6 +423,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       sa.raw = raw + (size_t)l0 * plan.BH * d.N;
       sa.stats = reinterpret_cast<unsigned long long*>(ws + sp.off);
       sa.grid = sp.grid; sa.items = sp.items;
+      sa.item_keys = sp.item_keys; sa.words_per_item = sp.words_per_item; sa.word_rows = sp.word_rows;
       sa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       sa.L = nl; sa.B = d.B; sa.Hq = d.Hq; sa.Hkv = d.Hkv; sa.G = plan.G; sa.alpha = d.alpha; sa.N = d.N; sa.R = plan.R;
       sa.d = d.d;

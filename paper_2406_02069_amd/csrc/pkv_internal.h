@@ -109,17 +109,17 @@ struct StreamArgs {
   ResidentLayer layer[kResidentMaxLayers];
   const int32_t* seq_lens;
   float* raw;                 // [U][N] un-pooled scores
-  unsigned long long* stats;  // [items][32 or 64] statistics of the items (log2 domain; the sign bit of the sum marks a
-                              // word as there); cleared before the launch
+  unsigned long long* stats;  // [words][word_rows] statistics (log2 domain; the sign bit of the sum marks a word as there);
+                              // cleared before the launch
   int32_t* err;
   int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
   int32_t uniform;            // 1: every unit has N keys and none is kept whole
   int32_t grid, items;        // workgroups (kStreamGrid, fewer if there are fewer items); items, if every unit has N keys
+  int32_t item_keys, words_per_item, word_rows;  // keys of an item; its statistics words; rows of a word's place
   int32_t wait_ticks;
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;
 };
-int stream_item_keys(int R);
 // clear_err: the first launch of a call also clears the error word
 hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s);
 

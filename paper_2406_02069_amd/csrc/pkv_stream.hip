@@ -7,7 +7,7 @@
 // the normalisers:  s_i = sum_r p_ri exp2(m_r - c_r)  is one multiply-add per logit, K is multiplied once, and the
 // registers of a key are free for the next one as soon as it has been multiplied.
 //
-// Work split.  An item is KI = 256 * TPW keys of one unit (layer, sequence, KV head).  256 persistent workgroups of 512
+// Work split.  An item is KI = 256 * TPW keys of one unit (layer, sequence, KV head): 512, or 1024 for up to 32 rows.  256 persistent workgroups of 512
 // threads, one per compute unit (all of its LDS, 256 registers per lane), take the items in turn: item j belongs to
 // workgroup j % 256.  Sequences of a ragged batch contribute the items they have, one after the other without gaps.
 //
@@ -15,7 +15,8 @@
 //   1. multiplies its keys with the unit's queries (rows = queries in registers, columns = keys; wave w takes the 32-key
 //      tiles w, w + 8, ... of the item, loaded straight into operand layout, KB tiles ahead, across item boundaries),
 //      turns the logits into p relative to the row's reference and keeps them in registers; sums over the keys give
-//      the item's statistics (reference, sum) per row, published for the unit's other items;
+//      the item's statistics (reference, sum) per row, published for the unit's other items (a word per row, or one for each of
+//      the item's halves, so that items of 512 and of 1024 keys publish the same);
 //   2. finishes the item BEFORE: the statistics of all items of its unit, which have had nearly the time of a whole item
 //      to arrive, are read (8 bytes per row and item: a few per cent of the keys' traffic) and folded into the
 //      normalisers; its p, moved to LDS meanwhile, are weighted and summed over the rows; one score per key is written
@@ -38,7 +39,8 @@
 // them twice (one scoring launch, by the profiler): 256 units of 8k keys, 32 rows 146 -> 112 us; 256 of 32k, 8 rows 535
 // -> 389 us (5.5 TB/s); ragged batch, 2048 units of 8k .. 16k, 64 rows 2.22 -> 1.67 ms (4.2 TB/s; an item of 512 keys
 // takes 6 - 8 us, of which the hop between the workgroups is not always covered).  One unit or a few: the latency of the
-// keys, one hop and two barriers; one layer of 8 heads with 8k keys 17.9 -> 16.5 us.
+// keys, one hop and two barriers; one layer of 8 heads with 8k keys 17.9 -> 16.5 us,
+// with items of half the size and no more statistics requested than there are, whole calls 26.6 -> 23.0.
 //
 // Every wait is bounded by wall-clock time (a workgroup that has waited too long raises the error word and carries on),
 // so the grid always drains.
@@ -89,19 +91,27 @@ __device__ __forceinline__ void merge_stats(float& m, float& z, float m2, float 
   z = z * fast_exp2(m - Ms) + z2 * fast_exp2(m2 - Ms);
   m = M;
 }
-// Sum (maximum) over the 32 lanes of a wave half, valid in its last lane.
-template <bool MAX>
-__device__ __forceinline__ float half_reduce(float x) {
-#define PKV_STEP(ctrl, rows)                                                                                              \
-  {                                                                                                                       \
-    const float y = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(MAX ? -INFINITY : 0.f), __float_as_int(x), ctrl, rows, 0xF, false)); \
-    x = MAX ? fmaxf(x, y) : x + y;                                                                                        \
-  }
+// Maximum over the 32 lanes of a wave half, valid in its last lane.
+__device__ __forceinline__ float half_max(float x) {
+#define PKV_STEP(ctrl, rows) \
+  x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(-INFINITY), __float_as_int(x), ctrl, rows, 0xF, false)));
   PKV_STEP(0x111, 0xF)  // row_shr:1, 2, 4, 8: the last lane of every row of 16 holds the row's result
   PKV_STEP(0x112, 0xF)
   PKV_STEP(0x114, 0xF)
   PKV_STEP(0x118, 0xF)
   PKV_STEP(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
+#undef PKV_STEP
+  return x;
+}
+// Sums of a and of b over the 32 lanes of a wave half: a's in the last lane of the half's first row of 16, b's of its second.
+__device__ __forceinline__ float half_sums(float a, float b) {
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+  float x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+#define PKV_STEP(ctrl) x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xF, 0xF, true))
+  PKV_STEP(0x111);  // row_shr:1, 2, 4, 8
+  PKV_STEP(0x112);
+  PKV_STEP(0x114);
+  PKV_STEP(0x118);
 #undef PKV_STEP
   return x;
 }
@@ -112,36 +122,38 @@ __device__ __forceinline__ float both_halves(float x) {
 }
 
 // NV: registers of a 32x32 product that hold real rows (register v of half h: row 8 (v / 4) + 4 h + v % 4), 4 per 8
-// rows; RT: 32-row tiles of queries.
-template <int D, int NV, int RT>
+// rows; RT: 32-row tiles of queries; TPW: 32-key tiles of an item per wave, summed up in SUB parts, a word of statistics
+// each; NPL: loads of
+// statistics made ahead per thread.
+template <int D, int NV, int RT, int TPW, int SUB, int NPL>
 struct StreamShape {
   static constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;  // (row pitch of Q in LDS: 16-byte slots, bank-free)
-  static constexpr int TPW = RT == 1 ? 4 : 2;                      // 32-key tiles of an item per wave
   static constexpr int KI = 32 * kW * TPW;                         // keys per item
+  static constexpr int WR = NV == 16 ? 32 * RT : 16;               // rows of a statistics word's place
   static constexpr int KB = D == 128 ? 2 : TPW;                    // tiles in flight per wave
   static constexpr int ROWS = 32 * RT;
   static constexpr int PPL = kT / (32 * RT);                       // items whose statistics one load per thread covers
-  static constexpr int NPL = 4;                                    // such loads made ahead
   static constexpr int P_SLOTS = kW * TPW * RT * (NV / 4) * 64;    // 16-byte slots of the pending p
   static constexpr int Q_SLOTS = ROWS * PITCH;
-  static constexpr size_t LDS = (size_t)(P_SLOTS + Q_SLOTS) * 16 + (size_t)kW * ROWS * 6 * 4 + (size_t)ROWS * 2 * 4 +
+  static constexpr size_t LDS = (size_t)(P_SLOTS + Q_SLOTS) * 16 + (size_t)kW * ROWS * (3 * SUB + 3) * 4 + (size_t)ROWS * 2 * 4 +
                                 (size_t)kStreamItems * 8;
   static_assert(LDS <= 160 * 1024, "one workgroup per compute unit");
   static_assert((size_t)(P_SLOTS + Q_SLOTS) * 16 >= (size_t)(kStreamUnits + 1 + kW) * 4, "prefix table fits");
 };
 
-template <int D, int NV, int RT>
+template <int D, int NV, int RT, int TPW, int SUB, int NPL>
 __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a) {
-  using S = StreamShape<D, NV, RT>;
-  constexpr int KS = S::KS, SEG = S::SEG, PITCH = S::PITCH, TPW = S::TPW, KI = S::KI, KB = S::KB, ROWS = S::ROWS, PPL = S::PPL, NPL = S::NPL;
+  using S = StreamShape<D, NV, RT, TPW, SUB, NPL>;
+  constexpr int TPS = TPW / SUB, WR = S::WR;
+  constexpr int KS = S::KS, SEG = S::SEG, PITCH = S::PITCH, KI = S::KI, KB = S::KB, ROWS = S::ROWS, PPL = S::PPL;
   constexpr int NQ = ROWS * SEG / kT > 0 ? ROWS * SEG / kT : 1;  // 16-byte loads per thread for a unit's queries
   constexpr int G4 = NV / 4;
   extern __shared__ u32x4 smem[];
   u32x4* s_q = smem + S::P_SLOTS;
-  float* s_m = reinterpret_cast<float*>(s_q + S::Q_SLOTS);  // [2][kW][ROWS] references by wave, of this item and the next
-  float* s_z = s_m + 2 * kW * ROWS;                         // [kW][ROWS] sums of this item
-  float* s_w = s_z + kW * ROWS;                             // [kW][ROWS] references, then weights of the pending item
-  float2* s_f = reinterpret_cast<float2*>(s_w + kW * ROWS); // [kW][ROWS] statistics of its unit, by wave
+  float* s_m = reinterpret_cast<float*>(s_q + S::Q_SLOTS);  // [2][SUB][kW][ROWS] references by wave, of this item and the next
+  float* s_z = s_m + 2 * SUB * kW * ROWS;                   // [SUB][kW][ROWS] sums of this item
+  float* s_w = s_z + SUB * kW * ROWS;                       // [kW][ROWS] references, then weights of the pending item
+  float2* s_f = reinterpret_cast<float2*>(s_w + kW * ROWS);  // [kW][ROWS] statistics of its unit, by wave
   int* s_t = reinterpret_cast<int*>(s_f + kW * ROWS);       // [ROWS] window position of a row
   int* s_off = s_t + ROWS;                                  // [ROWS] byte offset of a row of Q
   uint2* s_item = reinterpret_cast<uint2*>(s_off + ROWS);   // [kStreamItems] (waves to score it again << 24 | unit, part << 20 | keys)
@@ -247,7 +259,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     return d;
   };
   auto tile_key = [&](const Item& d, int t) { return d.part * KI + (t * kW + wave) * 32; };
-  auto nparts = [&](const Item& d) { return (d.n + KI - 1) / KI; };
+  auto nwords = [&](const Item& d) { return (d.n + KI / SUB - 1) / (KI / SUB); };  // of a unit, per row
 
   // Keys of the wave's tile t as matrix operand: lane (column l32, half hf) holds elements 16 ks + 8 hf of its key.
   // Keys at or beyond n are replaced by the last one.
@@ -309,7 +321,9 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 #undef PKV_ADD
       }
       const float m = fmaxf(fmaxf(ref[i][0], ref[i][1]), fmaxf(ref[i][2], ref[i][3])) * a.kappa;
-      if (row < ROWS && seg < kW) s_m[(mbuf * kW + seg) * ROWS + row] = m;  // (one table per wave)
+#pragma unroll
+      for (int sb = 0; sb < SUB; ++sb)
+        if (row < ROWS && seg < kW) s_m[((mbuf * SUB + sb) * kW + seg) * ROWS + row] = m;  // (a table per wave and word)
     }
   };
   const u32x4* q_lane = s_q + l32 * PITCH + hf;
@@ -331,17 +345,17 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     return wall_clock64() - t0 > (long long)a.wait_ticks ||
            __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
   };
-  // statistics word of row r of item j; the mark that it is there
-  auto stat_word = [&](int j, int r) { return a.stats + (uint32_t)(j * ROWS + r); };
+  // row r of statistics word j; the mark that it is there
+  auto stat_word = [&](int j, int r) { return a.stats + (uint32_t)(j * WR + r); };
   constexpr u64 kThere = 1ull << 63;
 
-  // Statistics of the items of a unit: thread = (row, every PPL-th item).
+  // Statistics of a unit: thread = (row, every PPL-th word).
   u64 sv[NPL];
   auto request_stats = [&](const Item& d, int np) {
     const int ln = fresh(lane);
     const int srow = min(ln & (ROWS - 1), a.R - 1), sitem = wave * (64 / ROWS) + ln / ROWS;
 #pragma unroll
-    for (int k = 0; k < NPL; ++k) sv[k] = ld64(stat_word(d.start + min(sitem + k * PPL, np - 1), srow));
+    for (int k = 0; k < NPL; ++k) sv[k] = ld64(stat_word(d.start * SUB + min(sitem + k * PPL, np - 1), srow));
   };
   // ... folded over the thread's items (those not there yet are waited for) and left in LDS
   auto fold_stats = [&](const Item& d, int np) {
@@ -353,7 +367,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
         int spins = 0;
         long long t0 = 0;
         for (;;) {
-          w = ld64(stat_word(d.start + q, srow));
+          w = ld64(stat_word(d.start * SUB + q, srow));
           if ((w & kThere) != 0) break;
           __builtin_amdgcn_s_sleep(1);
           if (waited_too_long(spins, t0)) {
@@ -377,7 +391,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
       if (sitem + k * PPL < np)
         z = __builtin_fmaf(__uint_as_float((uint32_t)(sv[k] >> 32) & 0x7FFFFFFFu), fast_exp2(__uint_as_float((uint32_t)sv[k]) - ms), z);
     for (int q = sitem + NPL * PPL; q < np; q += PPL) {
-      const u64 w = arrived(q, ld64(stat_word(d.start + q, srow)));
+      const u64 w = arrived(q, ld64(stat_word(d.start * SUB + q, srow)));
       merge_stats(m, z, __uint_as_float((uint32_t)w), __uint_as_float((uint32_t)(w >> 32) & 0x7FFFFFFFu));
     }
     if (ROWS == 32) {
@@ -461,15 +475,15 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
       nxt.part = 0;
       nxt.n = 1;
     }
-    const int np_pend = nparts(pend);
+    const int np_pend = nwords(pend);
     const int npre = cur.n - a.alpha;
     const int mbuf = i & 1;
-    float* m_tab = s_m + (mbuf * kW + wave) * ROWS;
+    float* m_tab = s_m + (mbuf * SUB * kW + wave) * ROWS;  // (a word's: kW * ROWS further)
     f32x4 p[TPW][RT][G4];
     // the row tile's references, from the wave's table in LDS (two row tiles' would not fit the registers)
-    auto load_m = [&](int rt, f32x4 (&m)[G4]) {
+    auto load_m = [&](int sb, int rt, f32x4 (&m)[G4]) {
 #pragma unroll
-      for (int q = 0; q < G4; ++q) m[q] = *reinterpret_cast<const f32x4*>(m_tab + 32 * rt + 8 * q + 4 * hf);
+      for (int q = 0; q < G4; ++q) m[q] = *reinterpret_cast<const f32x4*>(m_tab + sb * kW * ROWS + 32 * rt + 8 * q + 4 * hf);
     };
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -486,7 +500,7 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         f32x4 m[G4];
-        load_m(rt, m);
+        load_m(0, rt, m);  // (both parts' are the unit's so far)
 #pragma unroll
         for (int q = 0; q < G4; ++q)
 #pragma unroll
@@ -505,92 +519,110 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
       }
     }
     // ---- the item's statistics ----
-    f32x4 z[RT][G4];
-    auto sum_up = [&]() -> uint32_t {  // rows (bit 16 rt + 4 q + c, in the last lane of a half) whose reference does not fit
+    // (two sums share a register: those of the two parts, or of neighbouring rows of four)
+    constexpr int NZ = SUB == 2 ? G4 : (G4 + 1) / 2;
+    static_assert(SUB == 1 || SUB == 2, "pairs");
+    f32x4 z[RT][NZ];
+    auto sum_up = [&]() -> uint32_t {  // sums (bit 4 (NZ rt + q) + c, in the lane that holds it) whose reference does not fit
       uint32_t bad = 0u;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int q = 0; q < G4; ++q) {
-          z[rt][q] = p[0][rt][q];
+        for (int q = 0; q < NZ; ++q) {
+          const int qa = SUB == 2 ? q : 2 * q, qb = SUB == 2 ? q : (2 * q + 1 < G4 ? 2 * q + 1 : 2 * q), tb = SUB == 2 ? TPS : 0;
+          f32x4 za = p[0][rt][qa], zb = p[tb][rt][qb];
 #pragma unroll
-          for (int t = 1; t < TPW; ++t) z[rt][q] += p[t][rt][q];
+          for (int t = 1; t < TPS; ++t) {
+            za += p[t][rt][qa];
+            zb += p[tb + t][rt][qb];
+          }
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            z[rt][q][c] = half_reduce<false>(z[rt][q][c]);
+            z[rt][q][c] = half_sums(za[c], zb[c]);
             // (keys far below the reference vanish, as they should: a sampled key alone contributes 1 to the unit's sum)
-            bad |= (l32 == 31 && !(z[rt][q][c] <= 0x1p100f)) ? 1u << (16 * rt + 4 * q + c) : 0u;
+            bad |= ((lane & 15) == 15 && !(z[rt][q][c] <= 0x1p100f)) ? 1u << (4 * (NZ * rt + q) + c) : 0u;
           }
         }
       return bad;
     };
-    const uint32_t bad = sum_up();
+    uint32_t bad = sum_up();
     bool own = false;  // (lane = row) the wave has a reference of its own
     if (__builtin_expect(__any(bad != 0u) && tile_key(cur, 0) < cur.n, 0)) {
-      const float unit_ref = m_tab[lane & (ROWS - 1)];
-      // rare: a reference that does not fit (the sum is beyond 2^100 or, with one of -inf, undefined): for such a row the
-      // exact maximum over the wave's keys (-inf if there is nothing to add up), then p once more
+      const uint32_t bad_before = __shfl_xor(bad, 16);  // (in the last lane of a half: of the half's first row of lanes)
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        f32x4 mx[G4];
+      for (int sb = 0; sb < SUB; ++sb) {
+        if (tile_key(cur, TPS * sb) >= cur.n) continue;
+        const float unit_ref = m_tab[sb * kW * ROWS + (lane & (ROWS - 1))];
+        // rare: a reference that does not fit (the sum is beyond 2^100 or, with one of -inf, undefined): for such a row the
+        // exact maximum over the wave's keys (-inf if there is nothing to add up), then p once more
 #pragma unroll
-        for (int q = 0; q < G4; ++q) mx[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        for (int pass = 0; pass < 2; ++pass) {
-          f32x4 m[G4];
-          load_m(rt, m);
+        for (int rt = 0; rt < RT; ++rt) {
+          f32x4 mx[G4];
 #pragma unroll
-          for (int q = 0; q < G4; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) m[q][c] = m[q][c] == -INFINITY ? 0.f : m[q][c];
-#pragma unroll
-          for (int t = 0; t < TPW; ++t) {
-            bf16x8 f[KS];
-            issue_k(cur, t, f);
-            const f32x16 acc = product(f, rt);
-            const int over = tile_key(cur, t) + l32 - npre;
-#pragma unroll
-            for (int q = 0; q < G4; ++q) {
-              const i32x4 tt = *reinterpret_cast<const i32x4*>(s_t + 32 * rt + 8 * q + 4 * hf);
-#pragma unroll
-              for (int c = 0; c < 4; ++c) {
-                const float y = acc[4 * q + c];
-                if (pass == 0) mx[q][c] = fmaxf(mx[q][c], over > tt[c] ? -INFINITY : y * a.kappa);
-                else p[t][rt][q][c] = over > tt[c] ? 0.f : fast_exp2(__builtin_fmaf(y, a.kappa, -m[q][c]));
-              }
-            }
-          }
-          if (pass == 0) {
+          for (int q = 0; q < G4; ++q) mx[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+          for (int pass = 0; pass < 2; ++pass) {
+            f32x4 m[G4];
+            load_m(sb, rt, m);
 #pragma unroll
             for (int q = 0; q < G4; ++q)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) {
-                const float x = half_reduce<true>(mx[q][c]);
-                if (l32 == 31 && (bad >> (16 * rt + 4 * q + c) & 1u)) m_tab[32 * rt + 8 * q + 4 * hf + c] = x;
+              for (int c = 0; c < 4; ++c) m[q][c] = m[q][c] == -INFINITY ? 0.f : m[q][c];
+#pragma unroll
+            for (int t = TPS * sb; t < TPS * (sb + 1); ++t) {
+              bf16x8 f[KS];
+              issue_k(cur, t, f);
+              const f32x16 acc = product(f, rt);
+              const int over = tile_key(cur, t) + l32 - npre;
+#pragma unroll
+              for (int q = 0; q < G4; ++q) {
+                const i32x4 tt = *reinterpret_cast<const i32x4*>(s_t + 32 * rt + 8 * q + 4 * hf);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                  const float y = acc[4 * q + c];
+                  if (pass == 0) mx[q][c] = fmaxf(mx[q][c], over > tt[c] ? -INFINITY : y * a.kappa);
+                  else p[t][rt][q][c] = over > tt[c] ? 0.f : fast_exp2(__builtin_fmaf(y, a.kappa, -m[q][c]));
+                }
               }
-            wave_lds_fence();
+            }
+            if (pass == 0) {
+#pragma unroll
+              for (int q = 0; q < G4; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                  const float x = half_max(mx[q][c]);
+                  const bool second = SUB == 2 ? sb == 1 : (q & 1) == 1 || G4 == 1;
+                  if (l32 == 31 && ((second ? bad : bad_before) >> (4 * (NZ * rt + (SUB == 2 ? q : q / 2)) + c) & 1u)) m_tab[sb * kW * ROWS + 32 * rt + 8 * q + 4 * hf + c] = x;
+                }
+              wave_lds_fence();
+            }
           }
         }
+        own = own || m_tab[sb * kW * ROWS + (lane & (ROWS - 1))] != unit_ref;
       }
       (void)sum_up();
-      own = m_tab[lane & (ROWS - 1)] != unit_ref;
     }
     if (pend.u >= 0) fold_stats(pend, np_pend);
-    if (l32 == 31) {
+    if ((lane & 15) == 15) {
+      const int second = lane >> 4 & 1;
+      float* zt = s_z + wave * ROWS + 4 * hf + second * (SUB == 2 ? kW * ROWS : G4 == 1 ? 0 : 8);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int q = 0; q < G4; ++q) *reinterpret_cast<f32x4*>(s_z + wave * ROWS + 32 * rt + 8 * q + 4 * hf) = z[rt][q];
+        for (int q = 0; q < NZ; ++q) *reinterpret_cast<f32x4*>(zt + 32 * rt + (SUB == 2 ? 8 : 16) * q) = z[rt][q];
     }
     lds_barrier();  // every wave is done with this unit's queries; the waves' statistics are there
-    if (tid < ROWS) {
+    if (tid < ROWS * SUB) {
+      const int sb = tid / ROWS, row = tid & (ROWS - 1);
+      const float* mt = s_m + ((mbuf * SUB + sb) * kW) * ROWS + row;
+      const float* zt = s_z + sb * kW * ROWS + row;
       float mm = -INFINITY, zz = 0.f;
 #pragma unroll
-      for (int w = 0; w < kW; ++w) mm = fmaxf(mm, s_m[(mbuf * kW + w) * ROWS + tid]);
+      for (int w = 0; w < kW; ++w) mm = fmaxf(mm, mt[w * ROWS]);
       const float ms = mm == -INFINITY ? 0.f : mm;
 #pragma unroll
-      for (int w = 0; w < kW; ++w)
-        zz = __builtin_fmaf(s_z[w * ROWS + tid], fast_exp2(s_m[(mbuf * kW + w) * ROWS + tid] - ms), zz);
-      st64(stat_word(cur.start + cur.part, tid), kThere | (u64)__float_as_uint(zz) << 32 | __float_as_uint(mm));
+      for (int w = 0; w < kW; ++w) zz = __builtin_fmaf(zt[w * ROWS], fast_exp2(mt[w * ROWS] - ms), zz);
+      if (WR == ROWS || row < WR)
+        st64(stat_word((cur.start + cur.part) * SUB + sb, row), kThere | (u64)__float_as_uint(zz) << 32 | __float_as_uint(mm));
     }
     commit_q(mbuf ^ 1);
     issue_k(nxt, KB - 1, kf[(TPW - 1) % KB]);  // (behind the statistics, which others wait for)
@@ -607,8 +639,8 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
     cur = nxt;
     lds_barrier();  // the next unit's queries are in place
   }
-  request_stats(pend, nparts(pend));
-  fold_stats(pend, nparts(pend));
+  request_stats(pend, nwords(pend));
+  fold_stats(pend, nwords(pend));
   lds_barrier();
   finish(pend, nmine - 1);
 
@@ -621,11 +653,11 @@ __global__ __launch_bounds__(kT, 2) void score_stream_kernel(const StreamArgs a)
   for (int i = 0; i < nmine; ++i) {
     if ((__builtin_amdgcn_readfirstlane((int)s_item[i].x) >> (24 + wave) & 1) == 0) continue;
     const Item d = item(i);
-    const int np = nparts(d), npre = d.n - a.alpha;
+    const int np = nwords(d), npre = d.n - a.alpha;
     if (lane < ROWS) {
       float m = -INFINITY, z = 0.f;
       for (int q = 0; q < np; ++q) {  // (all there: the item has been finished before)
-        const u64 w = ld64(stat_word(d.start + q, lane));
+        const u64 w = ld64(stat_word(d.start * SUB + q, min(lane, a.R - 1)));
         merge_stats(m, z, __uint_as_float((uint32_t)w), __uint_as_float((uint32_t)(w >> 32) & 0x7FFFFFFFu));
       }
       ref_tab[lane] = m;
@@ -669,38 +701,51 @@ __global__ __launch_bounds__(256) void clear_kernel(u32x4* p, int n, int32_t* er
   if (err && i < 2) err[i] = 0;
 }
 
-template <int D, int NV, int RT>
+template <int D, int NV, int RT, int TPW, int SUB, int NPL>
 hipError_t launch_stream(const StreamArgs& a, hipStream_t s) {
-  using S = StreamShape<D, NV, RT>;
+  using S = StreamShape<D, NV, RT, TPW, SUB, NPL>;
   static bool attr_set[kMaxDevices];
   const int dev = current_device_slot();
   if (dev < 0) return hipErrorInvalidDevice;
   if (!attr_set[dev]) {  // raise the dynamic LDS limit once per device (idempotent; no allocation)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_stream_kernel<D, NV, RT>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_stream_kernel<D, NV, RT, TPW, SUB, NPL>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
     if (e != hipSuccess) return e;
     attr_set[dev] = true;
   }
-  hipLaunchKernelGGL((score_stream_kernel<D, NV, RT>), dim3(a.grid), dim3(kT), S::LDS, s, a);
+  hipLaunchKernelGGL((score_stream_kernel<D, NV, RT, TPW, SUB, NPL>), dim3(a.grid), dim3(kT), S::LDS, s, a);
   return hipGetLastError();
+}
+
+// A thread loads no more words of statistics ahead than the unit's number calls for: the loads pass the caches by, and four,
+// most of them of the unit's last word again, cost a launch of 32 layers of 8 x 8k keys, 32 rows, 2 %, of one layer 6 %.
+template <int D, int NV>
+hipError_t launch_rows32(const StreamArgs& a, hipStream_t s) {
+  if (a.item_keys == 512) return launch_stream<D, NV, 1, 2, 1, 1>(a, s);          // (up to 8192 keys: 16 words)
+  if (a.words_per_item == 2) return launch_stream<D, NV, 1, 4, 2, 1>(a, s);       // (likewise)
+  if (a.N <= 16384) return launch_stream<D, NV, 1, 4, 1, 1>(a, s);
+  return a.N <= 32768 ? launch_stream<D, NV, 1, 4, 1, 2>(a, s) : launch_stream<D, NV, 1, 4, 1, 4>(a, s);
+}
+template <int D>
+hipError_t launch_rows64(const StreamArgs& a, hipStream_t s) {
+  if (a.N <= 4096) return launch_stream<D, 16, 2, 2, 1, 1>(a, s);
+  return a.N <= 8192 ? launch_stream<D, 16, 2, 2, 1, 2>(a, s) : launch_stream<D, 16, 2, 2, 1, 4>(a, s);
 }
 
 }  // namespace
 
-int stream_item_keys(int R) { return R <= 32 ? 1024 : 512; }
-
 hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s) {
-  const int n16 = a.items * (a.R <= 32 ? 32 : 64) / 2;  // 64-bit words, two per slot
+  const int n16 = a.items * a.words_per_item * a.word_rows / 2;  // 64-bit words, two per slot
   hipLaunchKernelGGL(clear_kernel, dim3((n16 + 255) / 256), dim3(256), 0, s, reinterpret_cast<u32x4*>(a.stats), n16,
                      clear_err ? a.err : nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-#define PKV_CASE(DD)                                            \
-  if (a.d == DD) {                                              \
-    if (a.R <= 8) return launch_stream<DD, 4, 1>(a, s);         \
-    if (a.R <= 16) return launch_stream<DD, 8, 1>(a, s);        \
-    if (a.R <= 32) return launch_stream<DD, 16, 1>(a, s);       \
-    if (a.R <= 64) return launch_stream<DD, 16, 2>(a, s);       \
+#define PKV_CASE(DD)                                             \
+  if (a.d == DD) {                                               \
+    if (a.R <= 8) return launch_rows32<DD, 4>(a, s);             \
+    if (a.R <= 16) return launch_rows32<DD, 8>(a, s);            \
+    if (a.R <= 32) return launch_rows32<DD, 16>(a, s);           \
+    if (a.R <= 64) return launch_rows64<DD>(a, s);             \
   }
   PKV_CASE(128) PKV_CASE(64)
 #undef PKV_CASE
