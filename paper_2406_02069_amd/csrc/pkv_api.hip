@@ -273,16 +273,28 @@ static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_
 // words lie where its pooled scores lie later on.
 // Where the lines lie, whole calls of 8 layers (of one) with 8 heads, before -> with this kernel, us:
 //   33 .. 64 rows, against the other one-pass kernel, whose start is 4 us shorter: 8k keys 53 -> 48 (27 -> 32), 32k keys
-//     181 -> 155 (45 -> 49), 64k keys 375 -> 303 (99 -> 90), 128k keys 767 -> 565 (168 -> 154): from 768 items per layer on.
+//     181 -> 155 (45 -> 49), 64k keys 375 -> 303 (99 -> 90), 128k keys 767 -> 565 (168 -> 154).
 //   65 .. 128 rows, against the register-resident one: 1500 keys 39 -> 32 (36 -> 28), 8k keys 78 -> 59 (40 -> 31), 20k keys
 //     208 -> 158 (52 -> 47), 64k keys 462 -> 419 (116 -> 102), 128k keys 931 -> 904 (196 -> 189).
 //   more rows, against the two-launch one: 192 rows, 32k keys 321 -> 258 (70 -> 59); 256 rows, 8k keys 108 -> 87 (47 -> 37);
 //     512 rows, 8k keys 185 -> 142 (86 -> 49), 64k keys 1164 -> 945 (209 -> 179); 512 rows, 128k keys 2282 -> 2249.
-//   Units of more than 128 items keep all workgroups in step: 136 rows, 128k keys 1030 -> 1372, 72 rows 848 -> 877, 256 rows
-//     1349 -> 1443; only where the rows fill one or two groups does it stay ahead.
+//   33 .. 64 rows of other head counts: 16 heads, 25k keys (784 items) 54 -> 58 for one layer, 134 -> 138 for 4; 32 heads,
+//     19k keys (1216) 62 -> 63 and 188 -> 180, 24k keys (1504) 70 -> 70 and 229 -> 209: from 1280 items per layer on.  Units of
+//     more than 64 items, which the register-resident kernel takes otherwise: 8 heads, 52k keys (816) 76 -> 74 and 191 -> 160.
+//   Long units that do not divide the 256 workgroups: the ends of a unit are dealt a round apart, and with some numbers of
+//     items the workgroups wait for each other in a ring.  4 layers of 8 heads, 64 rows: 102 items 191 -> 160, 118 items 198 ->
+//     213, 127 .. 157 items 205 -> 181 and 348 -> 238, 235 items 372 -> 550, 256 items 450 -> 331; 128 rows: 86 items 231 ->
+//     165, 94 items about equal, 118 items 266 -> 313, 128 items 281 -> 230, 167 items and more 445 -> 506, 470 -> 662, 256
+//     items 523 -> 465; 96 rows, 256 items 848 -> 877 (8 layers); 256 rows: 88 items 298 -> 277, 94 items 300 -> 316, 128
+//     items 384 -> 307, 256 items 1349 -> 1443 (8 layers).
 constexpr int kLagMinRows = 33;
-constexpr int kLagMinItems = 768;   // per layer, at 64 rows and less
-constexpr int kLagMaxParts = 128;
+constexpr int kLagMinItems = 1280;      // per layer, at 64 rows and less
+constexpr int kLagMinItemsLong = 768;   // ... of units of more than 64 items
+static bool lag_parts_ok(int64_t parts, int groups, int R) {
+  if (parts <= 88 || parts == 128) return true;
+  if (parts == kStreamGrid) return groups == 1 || (groups == 2 && R > 112);
+  return groups == 1 && (parts <= 102 || (parts > 125 && parts <= 176));
+}
 struct LagPlan {
   int parts, groups, layers;
 };
@@ -294,9 +306,8 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
   const int groups = (plan.R + 63) / 64;
   if ((size_t)groups * kLagGroupBytes > (size_t)d.N * 4) return p;
   const int64_t parts = (d.N + kLagKeys - 1) / kLagKeys;
-  if (groups == 1 && parts * plan.BH < kLagMinItems) return p;
-  // (an item is finished two steps later, when its unit's other items, dealt one after the other, are at most one item ahead)
-  if (parts > (groups == 1 || (groups == 2 && plan.R > 112) ? kStreamGrid : kLagMaxParts)) return p;
+  if (groups == 1 && parts * plan.BH < (parts > 64 ? kLagMinItemsLong : kLagMinItems)) return p;
+  if (!lag_parts_ok(parts, groups, plan.R)) return p;
   const int64_t by_items = (int64_t)kLagItems * kStreamGrid / (parts * plan.BH), by_units = kStreamUnits / d.B;
   int64_t nl = by_items < by_units ? by_items : by_units;
   if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;

@@ -26,7 +26,7 @@ def _taken(Q, K, k_l):
                                      (8, 40), (6, 64), (7, 56), (8, 64)])
 def test_rows(d, G, alpha):
     # one to eight groups of rows, the last of them full or with a single row
-    Hkv = 2 if G * alpha > 64 else 128
+    Hkv = 2 if G * alpha > 64 else 144
     Q, K, V = _inputs(1, Hkv * G, Hkv, d, 4111, alpha, seed=G * 100 + alpha + d)
     assert _taken(Q, K, alpha + 60)
     _check(Q, K, V, alpha + 60)
