@@ -24,7 +24,7 @@
 // keys this takes half the time of storing the sums, folding and storing the normalisers (3.3 against 5.4 us per round with one
 // round's slack, 2.7 against 3.8 with two).
 //
-// A sum beyond 2^20 times its reference (or undefined) does not fit: the unit is scored again at the launch's end, from memory
+// A sum beyond 2^50 times its reference (or undefined) does not fit: the unit is scored again at the launch's end, from memory
 // and with exact maxima (a key some twenty binades above the 64 that the references come from).
 //
 // What bounds it: at 64 rows HBM (32 layers of 32k keys 599 -> 487 us whole call, against the one-pass kernel that waits for an
@@ -110,23 +110,29 @@ __device__ __forceinline__ float transpose_sum(const f32x16& t, int lane) {
 // among 128 workgroups takes 2.3 us with eight rows' sums to 256 bytes and 4.3 us with the sums in one piece: the adds to a
 // memory channel come one after the other.)
 // A sum is a 64-bit integer that the items add to: bits 0 .. 52 the sum of p in units of 2^-24 (2^-34 at the second
-// attempt), bits 53 .. 62 the items that have been added, bit 63 an item whose sum does not fit.
+// attempt), bits 53 .. 61 the items that have been added, bit 62 an item whose sum does not fit, bit 63 one that is counted in
+// the row's word for the second attempt, in units of 2^-4: a sum beyond 2^20 (a key some twenty binades above the sampled ones),
+// up to 2^50, which is rare but has to cost little: planted keys of that kind in every unit, the 32k workload 10.1 -> 0.66 ms.
 constexpr int kSums = 0, kSums2 = 8, kRefs = 16, kMax = 20, kArrived = 24;  // places in a block, in 64-bit words
 __device__ __forceinline__ uint32_t word_of(int which, int row) { return (uint32_t)(which + (row >> 3) * 32 + (row & 7)); }
 __device__ __forceinline__ uint32_t half_word_of(int which, int row) { return (uint32_t)(2 * which + (row >> 3) * 64 + (row & 7)); }
-constexpr u64 kOne = 1ull << 53, kBad = 1ull << 63;
-constexpr float kLimit = 0x1p20f;  // of an item's sum (512 of them fit 53 bits)
+constexpr u64 kOne = 1ull << 53, kBad = 1ull << 62, kBig = 1ull << 63;
+constexpr float kLimit = 0x1p20f, kBigLimit = 0x1p50f;  // of an item's sum (256 of them fit 53 and 63 bits)
 
 __device__ __forceinline__ u64 fixed_point(float z, float scale) {
   const float y = rintf(z * scale);
   const float hi = floorf(y * 0x1p-32f);
   return (u64)(uint32_t)hi << 32 | (uint32_t)__builtin_fmaf(hi, -0x1p32f, y);
 }
-__device__ __forceinline__ void add_sum(u64* word, float z, float limit, float scale) {
+__device__ __forceinline__ void add_sum(u64* word, float z, float limit, float scale, bool first) {
   u64 add = kOne;
   if (__builtin_expect(!(z <= limit), 0)) {
-    // (the mark is there before the item counts)
-    u64 seen = __hip_atomic_fetch_or(word, kBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (the mark and the sum are there before the item counts)
+    const bool big = first && z <= kBigLimit;
+    u64 seen = 0;
+    if (big) seen = __hip_atomic_fetch_add(word + (kSums2 - kSums), fixed_point(z, 0x1p4f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" : "+v"(seen));
+    seen = __hip_atomic_fetch_or(word, big ? kBig : kBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" : "+v"(seen));
   } else {
     add += fixed_point(z, scale);
@@ -320,7 +326,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
   // sum did not fit (the same in all waves and workgroups).
   auto weights = [&](int u, int h, int np, int which, float scale, float (&w)[2], bool armed) -> bool {
     auto missing = [&]() {
-      const int m = (a.wait_ticks == 0 ? np - 1 : 0) | ((int)((uint32_t)(sum >> 53) & 0x3FFu) ^ np);
+      const int m = (a.wait_ticks == 0 ? np - 1 : 0) | ((int)((uint32_t)(sum >> 53) & 0x1FFu) ^ np);
       return armed & (m != 0);
     };
     if (__builtin_expect(__any(missing()), 0)) {  // (a test of its own: inside a loop it would wait for all that is under way)
@@ -334,12 +340,20 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
         request_sum(u, h, which);
       } while (__any(missing()));
     }
-    const float x = (int)(sum >> 32) < 0 ? __builtin_nanf("") : inverse(sum, scale);
+    const int top = (int)(sum >> 32);
+    float x = inverse(sum, scale);
+    if (__builtin_expect(which == kSums && __any(armed & (top < 0)), 0)) {
+      const u64 big = ld64(a.words + (size_t)u * unit_words + word_of(kSums2, 64 * h + lane));
+      const float z = __builtin_fmaf((float)((uint32_t)top & 0x1FFFFFu), 0x1p32f, (float)(uint32_t)sum);
+      const float zb = __builtin_fmaf((float)(uint32_t)(big >> 32), 0x1p32f, (float)(uint32_t)big);
+      if (top < 0) x = __builtin_amdgcn_rcpf(__builtin_fmaf(zb, 0x1p20f, z)) * scale;
+    }
+    if ((top & 0x40000000) != 0) x = __builtin_nanf("");
     const uint32_t mine = __float_as_uint(64 * h + lane < a.R ? x : 0.f);
     const u32x2 both = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(mine, mine, false, false));
     w[0] = __uint_as_float(both[0]);
     w[1] = __uint_as_float(both[1]);
-    return armed & __any((int)(sum >> 32) < 0);
+    return armed & __any((top & 0x40000000) != 0);
   };
 
   // Where p waits: groups with an even number in registers, the others in LDS (but for four registers).
@@ -411,7 +425,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false));
     const float z = both_halves<false>(__uint_as_float(r[0]) + __uint_as_float(r[1]));
     if (ln < ROWS / kW && armed)
-      add_sum(a.words + (size_t)u * unit_words + word_of(kSums, 64 * h + wave * (ROWS / kW) + ln), z, kLimit, 0x1p24f);
+      add_sum(a.words + (size_t)u * unit_words + word_of(kSums, 64 * h + wave * (ROWS / kW) + ln), z, kLimit, 0x1p24f, true);
   };
   f32x16 t[2] = {};  // scores of the item that has waited: a lane's rows of the groups so far, by key
 
@@ -602,7 +616,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     finish(P0{}, old);
   }
 
-  // ---- rare: units with an item whose sum did not fit (a key some twenty binades above the sampled ones, or a reference of
+  // ---- rare: units with an item whose sum did not fit (a key some fifty binades above the sampled ones, or a reference of
   // -inf) are scored again, from memory and relative to the exact maxima, which their items exchange first ----
   lds_barrier();
   float ps[2] = {0.f, 0.f};  // scores over the groups so far
@@ -690,9 +704,13 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
             (void)__hip_atomic_fetch_max(reinterpret_cast<uint32_t*>(words) + half_word_of(kMax, 64 * h + tid), (o & 0x80000000u) ? ~o : o | 0x80000000u,
                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           } else {
-            add_sum(words + word_of(kSums2, 64 * h + tid), r, 0x1p10f, 0x1p34f);
+            add_sum(words + word_of(kSums2, 64 * h + tid), r, 0x1p10f, 0x1p34f, false);
           }
         }
+        // (the words for these sums may hold what the first attempt put there; every item has been counted, and so has its
+        // part of that.  Who still reads it has seen the mark and scores its item again.)
+        if (round == 0 && d.part == 0 && tid < ROWS)
+          __hip_atomic_store(words + word_of(kSums2, 64 * h + tid), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (round == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // (the maxima before the count)
         __syncthreads();
         if (round == 0 && tid == 0) add64(words + h * (ROWS / 8 * 32) + kArrived, 1);

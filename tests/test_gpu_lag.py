@@ -145,3 +145,16 @@ def test_given_up_waits_are_reported(monkeypatch):
     assert out[3].tolist() == [-1, -1]
     monkeypatch.setattr(binding, "DESC_FLAGS", 0)
     _check(Q, K, V, 80)
+
+
+@pytest.mark.parametrize("G,alpha", [(4, 32), (8, 24), (8, 64)])
+@pytest.mark.parametrize("top", [19, 22, 35, 48, 52])
+def test_sums_that_are_counted_apart(G, alpha, top):
+    # a key that many binades above all others, in one item or in every third: its sum is kept in a word of its own up to 2^50
+    for step in (5000, 1500):
+        binades = np.random.RandomState(top).uniform(-6, 0, 5000)
+        binades[700::step] = top
+        Q, K, V = _along(G, alpha, binades, 128, seed=top)
+        out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
+        torch.cuda.synchronize()
+        compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
