@@ -24,8 +24,8 @@
 // keys this takes half the time of storing the sums, folding and storing the normalisers (3.3 against 5.4 us per round with one
 // round's slack, 2.7 against 3.8 with two).
 //
-// A sum beyond 2^50 times its reference (or undefined) does not fit: the unit is scored again at the launch's end, from memory
-// and with exact maxima (a key some twenty binades above the 64 that the references come from).
+// A sum beyond 2^44 times its reference (or undefined) does not fit: the unit is scored again at the launch's end, from memory
+// and with exact maxima.
 //
 // What bounds it: at 64 rows HBM (32 layers of 32k keys 599 -> 487 us whole call, against the one-pass kernel that waits for an
 // exchange of all items' statistics), beyond them the issue of vector instructions around the products: a step takes 7600 clk
@@ -109,15 +109,19 @@ __device__ __forceinline__ float transpose_sum(const f32x16& t, int lane) {
 // (floats), exact maxima (ordered integers), and in the first block the number of items whose maxima are in.  (An exchange
 // among 128 workgroups takes 2.3 us with eight rows' sums to 256 bytes and 4.3 us with the sums in one piece: the adds to a
 // memory channel come one after the other.)
-// A sum is a 64-bit integer that the items add to: bits 0 .. 52 the sum of p in units of 2^-24 (2^-34 at the second
+// A sum is a 64-bit integer that the items add to: bits 0 .. 52 the sum of p in units of 2^-30 (2^-34 at the second
 // attempt), bits 53 .. 61 the items that have been added, bit 62 an item whose sum does not fit, bit 63 one that is counted in
-// the row's word for the second attempt, in units of 2^-4: a sum beyond 2^20 (a key some twenty binades above the sampled ones),
-// up to 2^50, which is rare but has to cost little: planted keys of that kind in every unit, the 32k workload 10.1 -> 0.66 ms.
+// the row's word for the second attempt, in units of 2^-10: a sum beyond 2^14 (a key some binades above the sampled ones), up to
+// 2^44, which is rare but has to cost little: planted keys of that kind in every unit, the 32k workload 10.1 -> 0.66 ms.
+// (One key alone adds 1 to a row's sum, so half a unit of each of 256 items is at most 2^-23 of it: as much as two roundings of
+// a float.  In units of 2^-24 the sums of items far below the reference were lost: 64 items of 2^-26 each 9.5e-7 of the
+// normaliser, 256 items 3.8e-6.)
 constexpr int kSums = 0, kSums2 = 8, kRefs = 16, kMax = 20, kArrived = 24;  // places in a block, in 64-bit words
 __device__ __forceinline__ uint32_t word_of(int which, int row) { return (uint32_t)(which + (row >> 3) * 32 + (row & 7)); }
 __device__ __forceinline__ uint32_t half_word_of(int which, int row) { return (uint32_t)(2 * which + (row >> 3) * 64 + (row & 7)); }
 constexpr u64 kOne = 1ull << 53, kBad = 1ull << 62, kBig = 1ull << 63;
-constexpr float kLimit = 0x1p20f, kBigLimit = 0x1p50f;  // of an item's sum (256 of them fit 53 and 63 bits)
+constexpr float kLimit = 0x1p14f, kBigLimit = 0x1p44f;  // of an item's sum (256 of them fit 53 and 63 bits)
+constexpr float kUnits = 0x1p30f, kBigUnits = 0x1p10f;  // to the 1
 
 __device__ __forceinline__ u64 fixed_point(float z, float scale) {
   const float y = rintf(z * scale);
@@ -130,7 +134,7 @@ __device__ __forceinline__ void add_sum(u64* word, float z, float limit, float s
     // (the mark and the sum are there before the item counts)
     const bool big = first && z <= kBigLimit;
     u64 seen = 0;
-    if (big) seen = __hip_atomic_fetch_add(word + (kSums2 - kSums), fixed_point(z, 0x1p4f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (big) seen = __hip_atomic_fetch_add(word + (kSums2 - kSums), fixed_point(z, kBigUnits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" : "+v"(seen));
     seen = __hip_atomic_fetch_or(word, big ? kBig : kBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" : "+v"(seen));
@@ -346,7 +350,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
       const u64 big = ld64(a.words + (size_t)u * unit_words + word_of(kSums2, 64 * h + lane));
       const float z = __builtin_fmaf((float)((uint32_t)top & 0x1FFFFFu), 0x1p32f, (float)(uint32_t)sum);
       const float zb = __builtin_fmaf((float)(uint32_t)(big >> 32), 0x1p32f, (float)(uint32_t)big);
-      if (top < 0) x = __builtin_amdgcn_rcpf(__builtin_fmaf(zb, 0x1p20f, z)) * scale;
+      if (top < 0) x = __builtin_amdgcn_rcpf(__builtin_fmaf(zb, kUnits / kBigUnits, z)) * scale;
     }
     if ((top & 0x40000000) != 0) x = __builtin_nanf("");
     const uint32_t mine = __float_as_uint(64 * h + lane < a.R ? x : 0.f);
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false));
     const float z = both_halves<false>(__uint_as_float(r[0]) + __uint_as_float(r[1]));
     if (ln < ROWS / kW && armed)
-      add_sum(a.words + (size_t)u * unit_words + word_of(kSums, 64 * h + wave * (ROWS / kW) + ln), z, kLimit, 0x1p24f, true);
+      add_sum(a.words + (size_t)u * unit_words + word_of(kSums, 64 * h + wave * (ROWS / kW) + ln), z, kLimit, kUnits, true);
   };
   f32x16 t[2] = {};  // scores of the item that has waited: a lane's rows of the groups so far, by key
 
@@ -545,7 +549,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     products(I0{});
     publish(par ^ 1, old1.d.u, old1.h, n > 0);
     // (in front of the first two steps there is nothing: their scores are written later, over what is written here)
-    mark(weights(old.d.u, old.h, nparts(old.d), kSums, 0x1p24f * a.inv_G, w, n >= 2), old.i);
+    mark(weights(old.d.u, old.h, nparts(old.d), kSums, kUnits * a.inv_G, w, n >= 2), old.i);
     products(I1{});
     commit_q(par ^ 1);
     request_q(nx2.d, nx2.h);
@@ -589,7 +593,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     constexpr int par = decltype(PAR)::value;
     float w[2];
     request_sum(s.d.u, s.h, kSums);
-    mark(weights(s.d.u, s.h, nparts(s.d), kSums, 0x1p24f * a.inv_G, w, true), s.i);
+    mark(weights(s.d.u, s.h, nparts(s.d), kSums, kUnits * a.inv_G, w, true), s.i);
 #pragma unroll
     for (int tc = 0; tc < 2; ++tc) {
       if (s.h == 0) t[tc] = f32x16{};

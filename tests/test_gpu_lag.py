@@ -150,7 +150,7 @@ def test_given_up_waits_are_reported(monkeypatch):
 @pytest.mark.parametrize("G,alpha", [(4, 32), (8, 24), (8, 64)])
 @pytest.mark.parametrize("top", [19, 22, 35, 48, 52])
 def test_sums_that_are_counted_apart(G, alpha, top):
-    # a key that many binades above all others, in one item or in every third: its sum is kept in a word of its own up to 2^50
+    # a key that many binades above all others, in one item or in every third: its sum is kept in a word of its own up to 2^44
     for step in (5000, 1500):
         binades = np.random.RandomState(top).uniform(-6, 0, 5000)
         binades[700::step] = top
@@ -158,3 +158,27 @@ def test_sums_that_are_counted_apart(G, alpha, top):
         out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
         torch.cuda.synchronize()
         compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+
+
+@pytest.mark.parametrize("Hkv,G,alpha,N", [(1, 4, 32, 32768), (1, 8, 64, 32768), (6, 4, 16, 65536), (1, 4, 32, 131072)])
+def test_sums_far_below_the_reference_count(Hkv, G, alpha, N):
+    # key 0 alone is the reference; every item of the others adds 2^-26 of it to the normaliser, 64 items 2^-20 = 9.5e-7, and
+    # nobody's sum may be rounded away.  Bound of key 0's score: roundings of the normaliser, its reciprocal (1 ulp), the weight,
+    # the sums over the rows (two per group of 64, five across the lanes), half an ulp each where not said otherwise;
+    # and below 8e-7, half of what would be lost here (1.6e-6 and more)
+    heads = [_along(G, alpha, np.where(np.arange(N) > 0, -35.0, 0.0), 128, seed=h) for h in range(Hkv)]
+    Q, K, V = (torch.cat([x[i] for x in heads], dim=1).contiguous() for i in range(3))
+    assert _taken(Q, K, alpha + 30)
+    out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    hidden = torch.ones(alpha, alpha, dtype=torch.bool, device=DEV).triu(1)
+    bound = (1 + 2 + 1 + 2 * ((G * alpha + 63) // 64) + 5) * 2.0 ** -24
+    for h in range(Hkv):
+        x = Q[0].view(Hkv, -1, 128)[h].double() @ K[0, h].double().t().contiguous() / 128 ** 0.5
+        x.view(-1, alpha, N)[:, :, N - alpha:].masked_fill_(hidden, -np.inf)
+        rest = x[:, 1:].sub(x[:, :1]).exp().sum(dim=1)
+        assert 0.5 * N / 512 * 2.0 ** -26 < float(rest.mean()) < 1.9 * N / 512 * 2.0 ** -26   # (else the inputs miss the point)
+        want = float((1 / (1 + rest)).sum() / G)
+        got = float(out[4][0, h, 0])
+        print("sink", Hkv, G, alpha, N, (got - want) / want, bound, flush=True)
+        assert abs(got - want) < min(bound, 8e-7) * want
