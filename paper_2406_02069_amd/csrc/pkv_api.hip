@@ -297,14 +297,17 @@ static bool lag_parts_ok(int64_t parts, int groups, int R) {
 }
 struct LagPlan {
   int parts, groups, layers;
+  bool words4;
+  size_t unit_bytes() const { return (size_t)groups * (kLagGroupBytes + (words4 ? kLagGroupBytes4 : 0)); }
 };
 static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
-  LagPlan p = {0, 0, 0};
+  LagPlan p = {0, 0, 0, false};
   if (lse_mode || plan.R < kLagMinRows || plan.R > kResidentMaxRows || !plan.resident_ok) return p;
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
   if (d.q_sh >= 1 << 24 || d.q_st >= 1 << 24) return p;  // (offsets of query rows by 24-bit multiplication)
   const int groups = (plan.R + 63) / 64;
-  if ((size_t)groups * kLagGroupBytes > (size_t)d.N * 4) return p;
+  if ((int64_t)groups * kLagGroupBytes > (int64_t)d.N * 4) return p;
+  p.words4 = (int64_t)groups * (kLagGroupBytes + kLagGroupBytes4) <= (int64_t)d.N * 4;
   const int64_t parts = (d.N + kLagKeys - 1) / kLagKeys;
   if (groups == 1 && parts * plan.BH < (parts > 64 ? kLagMinItemsLong : kLagMinItems)) return p;
   if (!lag_parts_ok(parts, groups, plan.R)) return p;
@@ -339,7 +342,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   if (rec) rec->begin(stream);
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
-  LagPlan gp = {0, 0, 0};
+  LagPlan gp = {0, 0, 0, false};
   StreamPlan sp = {0, 0, 0, 0, 0, 0, 0, 0};
   SweepPlan wp = {0, 0, 0};
   if (any_scores && resident) gp = lag_plan(plan, d, lse_mode);
@@ -400,6 +403,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       ga.seq_lens = seq_lens;
       ga.raw = raw + (size_t)l0 * plan.BH * d.N;
       ga.words = reinterpret_cast<unsigned long long*>(pooled_ws);
+      if (gp.words4) ga.words4 = ga.words + (size_t)ga.L * plan.BH * gp.groups * (kLagGroupBytes / 8);
       ga.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       ga.B = d.B; ga.Hq = d.Hq; ga.Hkv = d.Hkv; ga.G = plan.G; ga.alpha = d.alpha; ga.N = d.N; ga.R = plan.R; ga.d = d.d;
       ga.uniform = seq_lens ? 0 : 1;
@@ -1011,7 +1015,7 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t lse_supplie
   const LagPlan gp = lag_plan(plan, *desc, lse_mode);
   if (gp.layers > 0) {
     *kernel_id = lag_kernel_id(plan);
-    *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.groups * kLagGroupBytes;
+    *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.unit_bytes();
     return PKV_OK;
   }
   const SweepPlan wp = sweep_plan(plan, *desc, lse_mode);

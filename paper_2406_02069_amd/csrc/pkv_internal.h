@@ -126,13 +126,15 @@ hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t 
 // ---- one-pass scoring, probabilities waiting on the chip two items long, over many layers (pkv_lag.hip) ----
 constexpr int kLagItems = 255;      // items of a workgroup per launch, at most (table in LDS)
 constexpr int kLagKeys = 512;       // keys of an item
-constexpr int kLagGroupBytes = 2048;  // of the workspace, per unit and group of 64 query rows
+constexpr int kLagGroupBytes = 2048;   // of the workspace, per unit and group of 64 query rows
+constexpr int kLagGroupBytes4 = 512;   // ... and of the last words for large sums, where there is room
 
 struct LagArgs {
   ResidentLayer layer[kResidentMaxLayers];
   const int32_t* seq_lens;
   float* raw;                 // [layer slot][B][Hkv][N] un-pooled scores
   unsigned long long* words;  // [units][groups][256] sums, references, maxima; cleared by the first of the two kernels
+  unsigned long long* words4; // [units][groups][64] last words for large sums, or null; likewise
   int32_t* err;
   int32_t L, B, Hq, Hkv, G, alpha, N, R, d;
   int32_t uniform;            // 1: every unit has N keys and none is kept whole

@@ -24,8 +24,8 @@
 // keys this takes half the time of storing the sums, folding and storing the normalisers (3.3 against 5.4 us per round with one
 // round's slack, 2.7 against 3.8 with two).
 //
-// A sum beyond 2^44 times its reference (or undefined) does not fit: the unit is scored again at the launch's end, from memory
-// and with exact maxima.
+// A sum beyond 2^103 times its reference (2^73 in units of less than 640 keys per group of rows; or undefined) does not fit: the unit is scored again at the
+// launch's end, from memory and with exact maxima, which is slow.
 //
 // What bounds it: at 64 rows HBM (32 layers of 32k keys 599 -> 487 us whole call, against the one-pass kernel that waits for an
 // exchange of all items' statistics), beyond them the issue of vector instructions around the products: a step takes 7600 clk
@@ -105,49 +105,63 @@ __device__ __forceinline__ float transpose_sum(const f32x16& t, int lane) {
   return s + dpp<0xB1>(s);                  // quad_perm 1,0,3,2
 }
 
-// Words of a unit in the workspace, 256 bytes for eight rows: their sums, their sums at the second attempt, references
-// (floats), exact maxima (ordered integers), and in the first block the number of items whose maxima are in.  (An exchange
-// among 128 workgroups takes 2.3 us with eight rows' sums to 256 bytes and 4.3 us with the sums in one piece: the adds to a
-// memory channel come one after the other.)
-// A sum is a 64-bit integer that the items add to: bits 0 .. 52 the sum of p in units of 2^-30 (2^-34 at the second
-// attempt), bits 53 .. 61 the items that have been added, bit 62 an item whose sum does not fit, bit 63 one that is counted in
-// the row's word for the second attempt, in units of 2^-10: a sum beyond 2^14 (a key some binades above the sampled ones), up to
-// 2^44, which is rare but has to cost little: planted keys of that kind in every unit, the 32k workload 10.1 -> 0.66 ms.
+// Words of a unit in the workspace, 256 bytes for eight rows: their sums, two further words each for large sums, references
+// (floats) and exact maxima (ordered integers).  (An exchange among 128 workgroups takes 2.3 us with eight rows' sums to 256
+// bytes and 4.3 us with the sums in one piece: the adds to a memory channel come one after the other.)  A third word for large
+// sums per row lies behind the words of all units, where there is room for it (from 640 keys per group of 64 rows on).
+// A sum is a 64-bit integer that the items add to: bits 0 .. 51 the sum of p in units of 2^-30 (2^-34 at the second
+// attempt, which uses the first word for large sums), bits 52 .. 61 the items that have been added (in the group's first row
+// also those whose maxima are in), bit 62 an item whose sum does not fit, bit 63 one that is counted in a word for large sums: up
+// to 2^13, 2^43, 2^73 and 2^103, in units 2^-24 of what the word before holds.  That is rare but has to cost little.  A key
+// far above the sampled ones for every row of every unit, 32 layers of 32k keys, 128 rows: 660 us without, 739 with one 20 binades
+// above, 774 at 55 (10 100 where the unit is scored again); 8 layers, 512 rows: 540, 633 and 654 (10 250).  What remains is one
+// read of these words per step, for which everything under way is waited for.
 // (One key alone adds 1 to a row's sum, so half a unit of each of 256 items is at most 2^-23 of it: as much as two roundings of
 // a float.  In units of 2^-24 the sums of items far below the reference were lost: 64 items of 2^-26 each 9.5e-7 of the
 // normaliser, 256 items 3.8e-6.)
-constexpr int kSums = 0, kSums2 = 8, kRefs = 16, kMax = 20, kArrived = 24;  // places in a block, in 64-bit words
+constexpr int kSums = 0, kSums2 = 8, kSums3 = 16, kRefs = 24, kMax = 28;  // places in a block, in 64-bit words
 __device__ __forceinline__ uint32_t word_of(int which, int row) { return (uint32_t)(which + (row >> 3) * 32 + (row & 7)); }
 __device__ __forceinline__ uint32_t half_word_of(int which, int row) { return (uint32_t)(2 * which + (row >> 3) * 64 + (row & 7)); }
-constexpr u64 kOne = 1ull << 53, kBad = 1ull << 62, kBig = 1ull << 63;
-constexpr float kLimit = 0x1p14f, kBigLimit = 0x1p44f;  // of an item's sum (256 of them fit 53 and 63 bits)
-constexpr float kUnits = 0x1p30f, kBigUnits = 0x1p10f;  // to the 1
+constexpr u64 kOne = 1ull << 52, kBad = 1ull << 62, kBig = 1ull << 63;
+constexpr float kUnits = 0x1p30f, kUnits2 = 0x1p11f, kUnits3 = 0x1p-19f, kUnits4 = 0x1p-49f;  // to the 1
+constexpr float kLimit = 0x1p13f, kLimit2 = 0x1p43f, kLimit3 = 0x1p73f, kLimit4 = 0x1p103f;   // of an item's sum (256 fit)
 
 __device__ __forceinline__ u64 fixed_point(float z, float scale) {
   const float y = rintf(z * scale);
   const float hi = floorf(y * 0x1p-32f);
   return (u64)(uint32_t)hi << 32 | (uint32_t)__builtin_fmaf(hi, -0x1p32f, y);
 }
-__device__ __forceinline__ void add_sum(u64* word, float z, float limit, float scale, bool first) {
+__device__ __forceinline__ float as_float(u64 w) { return __builtin_fmaf((float)(uint32_t)(w >> 32), 0x1p32f, (float)(uint32_t)w); }
+// An item's sum of a row, at the first and at the second attempt.  What does not fit is marked first, so that whoever finds
+// the item counted sees it.  word4(): the row's last word for large sums, or null.
+template <class F>
+__device__ __forceinline__ void add_sum(u64* word, float z, F word4) {
   u64 add = kOne;
-  if (__builtin_expect(!(z <= limit), 0)) {
-    // (the mark and the sum are there before the item counts)
-    const bool big = first && z <= kBigLimit;
+  if (__builtin_expect(!(z <= kLimit), 0)) {
+    u64* big = z <= kLimit2 ? word + (kSums2 - kSums) : z <= kLimit3 ? word + (kSums3 - kSums) : z <= kLimit4 ? word4() : nullptr;
     u64 seen = 0;
-    if (big) seen = __hip_atomic_fetch_add(word + (kSums2 - kSums), fixed_point(z, kBigUnits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (big) seen = __hip_atomic_fetch_add(big, fixed_point(z, z <= kLimit2 ? kUnits2 : z <= kLimit3 ? kUnits3 : kUnits4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" : "+v"(seen));
     seen = __hip_atomic_fetch_or(word, big ? kBig : kBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" : "+v"(seen));
   } else {
-    add += fixed_point(z, scale);
+    add += fixed_point(z, kUnits);
   }
   add64(word, add);
 }
-// 1 / sum, times scale
-__device__ __forceinline__ float inverse(u64 w, float scale) {
-  const uint32_t hi = (uint32_t)(w >> 32) & 0x1FFFFFu;
-  return __builtin_amdgcn_rcpf(__builtin_fmaf((float)hi, 0x1p32f, (float)(uint32_t)w)) * scale;
+__device__ __forceinline__ void add_sum_again(u64* word, float z) {
+  u64 add = kOne;
+  if (z <= 0x1p10f) {
+    add += fixed_point(z, 0x1p34f);
+  } else {
+    u64 seen = __hip_atomic_fetch_or(word, kBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" : "+v"(seen));
+  }
+  add64(word, add);
 }
+// sum, and 1 / sum, times scale
+__device__ __forceinline__ float sum_of(u64 w) { return as_float(w & (kOne - 1)); }
+__device__ __forceinline__ float inverse(u64 w, float scale) { return __builtin_amdgcn_rcpf(sum_of(w)) * scale; }
 
 // A step handles 64 query rows (a group: two row tiles) of an item's 512 keys (two key tiles per wave).
 template <int D>
@@ -157,7 +171,7 @@ struct LagShape {
   static constexpr int PQ = 15;          // 16-byte slots per lane of a group that waits in LDS (of 16, one does not fit)
   static constexpr int P_SLOTS = kW * PQ * 64, Q_SLOTS = ROWS * PITCH;
   static constexpr int NQ = ROWS * SEG / kT;  // 16-byte loads per thread for a group's queries
-  static constexpr size_t LDS = (size_t)(P_SLOTS + 2 * Q_SLOTS) * 16 + (size_t)2 * kW * ROWS * 4 + (size_t)kLagItems * 8;
+  static constexpr size_t LDS = (size_t)(P_SLOTS + 2 * Q_SLOTS) * 16 + (size_t)2 * kW * ROWS * 4 + (size_t)kLagItems * 8 + 8;
   static_assert(LDS <= 160 * 1024, "one workgroup per compute unit");
   static_assert((size_t)P_SLOTS * 16 >= (size_t)(kStreamUnits + 1 + kW) * 4, "prefix table fits");
 };
@@ -172,6 +186,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
   u32x4* s_q = smem + S::P_SLOTS;                                 // [2][ROWS][PITCH] queries of a group, used in turn
   float* s_z = reinterpret_cast<float*>(s_q + 2 * S::Q_SLOTS);    // [2][kW][ROWS] sums by wave, used in turn
   uint2* s_item = reinterpret_cast<uint2*>(s_z + 2 * kW * ROWS);  // [kLagItems] (unit, part << 20 | keys)
+  u64** s_words4 = reinterpret_cast<u64**>(s_item + kLagItems);   // a.words4 (kept in a register it would cost the loop one)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -181,6 +196,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
   // head and window position of a unit's row
   auto head_of = [&](int row) { return (int)(__umul24((uint32_t)row, a.alpha_magic) >> 16); };
 
+  if (tid == 0) *s_words4 = a.words4;
   // ---- the items of this workgroup ----
   int nmine;
   if (a.uniform) {  // every unit has N keys to score
@@ -323,16 +339,18 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
   };
   auto give_up = [&]() { __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
 
+  auto word4_of = [&](int u, int h, int row) {
+    u64* w = *s_words4;
+    return w ? w + ((uint32_t)(u * NG + h) * ROWS + (uint32_t)row) : nullptr;
+  };
   // Sum of a lane's row of a group, as it is now.
   u64 sum;
   auto request_sum = [&](int u, int h, int which) { sum = ld64(a.words + (size_t)u * unit_words + word_of(which, 64 * h + lane)); };
   // ... when all items have been added: the rows' weights 1 / (G z), of rows l32 and 32 + l32.  Returns whether some item's
   // sum did not fit (the same in all waves and workgroups).
   auto weights = [&](int u, int h, int np, int which, float scale, float (&w)[2], bool armed) -> bool {
-    auto missing = [&]() {
-      const int m = (a.wait_ticks == 0 ? np - 1 : 0) | ((int)((uint32_t)(sum >> 53) & 0x1FFu) ^ np);
-      return armed & (m != 0);
-    };
+    const uint32_t need = a.wait_ticks == 0 && np > 1 ? 0x400u : (uint32_t)np;
+    auto missing = [&]() { return armed & (((uint32_t)(sum >> 52) & 0x3FFu) < need); };
     if (__builtin_expect(__any(missing()), 0)) {  // (a test of its own: inside a loop it would wait for all that is under way)
       int spins = 0;
       long long t0 = 0;
@@ -347,10 +365,11 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     const int top = (int)(sum >> 32);
     float x = inverse(sum, scale);
     if (__builtin_expect(which == kSums && __any(armed & (top < 0)), 0)) {
-      const u64 big = ld64(a.words + (size_t)u * unit_words + word_of(kSums2, 64 * h + lane));
-      const float z = __builtin_fmaf((float)((uint32_t)top & 0x1FFFFFu), 0x1p32f, (float)(uint32_t)sum);
-      const float zb = __builtin_fmaf((float)(uint32_t)(big >> 32), 0x1p32f, (float)(uint32_t)big);
-      if (top < 0) x = __builtin_amdgcn_rcpf(__builtin_fmaf(zb, kUnits / kBigUnits, z)) * scale;
+      const u64* w2 = a.words + (size_t)u * unit_words + word_of(kSums2, 64 * h + lane);
+      const u64 b2 = ld64(w2), b3 = ld64(w2 + (kSums3 - kSums2)), b4 = *s_words4 ? ld64(word4_of(u, h, lane)) : 0ull;
+      float z = __builtin_fmaf(as_float(b2), 1.f / kUnits2, sum_of(sum) * (1.f / kUnits));
+      z = __builtin_fmaf(as_float(b4), 1.f / kUnits4, __builtin_fmaf(as_float(b3), 1.f / kUnits3, z));
+      if (top < 0) x = __builtin_amdgcn_rcpf(z) * (scale * (1.f / kUnits));
     }
     if ((top & 0x40000000) != 0) x = __builtin_nanf("");
     const uint32_t mine = __float_as_uint(64 * h + lane < a.R ? x : 0.f);
@@ -429,7 +448,8 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false));
     const float z = both_halves<false>(__uint_as_float(r[0]) + __uint_as_float(r[1]));
     if (ln < ROWS / kW && armed)
-      add_sum(a.words + (size_t)u * unit_words + word_of(kSums, 64 * h + wave * (ROWS / kW) + ln), z, kLimit, kUnits, true);
+      add_sum(a.words + (size_t)u * unit_words + word_of(kSums, 64 * h + wave * (ROWS / kW) + ln), z,
+              [&]() { return word4_of(u, h, wave * (ROWS / kW) + ln); });
   };
   f32x16 t[2] = {};  // scores of the item that has waited: a lane's rows of the groups so far, by key
 
@@ -620,7 +640,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     finish(P0{}, old);
   }
 
-  // ---- rare: units with an item whose sum did not fit (a key some fifty binades above the sampled ones, or a reference of
+  // ---- rare: units with an item whose sum did not fit (a key a hundred binades above the sampled ones, or a reference of
   // -inf) are scored again, from memory and relative to the exact maxima, which their items exchange first ----
   lds_barrier();
   float ps[2] = {0.f, 0.f};  // scores over the groups so far
@@ -656,7 +676,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
         if (round == 1) {
           int spins = 0;
           long long t0 = 0;
-          while (a.wait_ticks == 0 || (int)ld64(words + h * (ROWS / 8 * 32) + kArrived) < np)
+          while (a.wait_ticks == 0 || (int)((uint32_t)(ld64(words + word_of(kSums, 64 * h)) >> 52) & 0x3FFu) < 2 * np)
             if (waited_too_long(spins, t0)) {
               give_up();
               break;
@@ -708,7 +728,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
             (void)__hip_atomic_fetch_max(reinterpret_cast<uint32_t*>(words) + half_word_of(kMax, 64 * h + tid), (o & 0x80000000u) ? ~o : o | 0x80000000u,
                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           } else {
-            add_sum(words + word_of(kSums2, 64 * h + tid), r, 0x1p10f, 0x1p34f, false);
+            add_sum_again(words + word_of(kSums2, 64 * h + tid), r);
           }
         }
         // (the words for these sums may hold what the first attempt put there; every item has been counted, and so has its
@@ -717,7 +737,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
           __hip_atomic_store(words + word_of(kSums2, 64 * h + tid), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (round == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // (the maxima before the count)
         __syncthreads();
-        if (round == 0 && tid == 0) add64(words + h * (ROWS / 8 * 32) + kArrived, 1);
+        if (round == 0 && tid == 0) add64(words + word_of(kSums, 64 * h), kOne);
       }
   }
 }
@@ -734,6 +754,7 @@ __global__ __launch_bounds__(256) void lag_prepare_kernel(const LagArgs a, int c
   if (blockIdx.x == 0 && clear_err && tid < 2) a.err[tid] = 0;
   u64* words = a.words + (size_t)blockIdx.x * 256;
   if ((tid & 31) < kRefs || (tid & 31) >= kMax) words[tid] = 0;
+  if (a.words4 && tid < 64) a.words4[(size_t)blockIdx.x * 64 + tid] = 0;
   int n = a.N;
   if (a.seq_lens) {
     n = a.seq_lens[b];

@@ -18,7 +18,8 @@ def _taken(Q, K, k_l):
     desc = binding.make_desc(Q, K, k_l, synth.POOL_MAX, 7, None)
     R = Q.shape[1] // K.shape[1] * Q.shape[2]
     groups = (R + 63) // 64
-    return binding.scoring_sweeps(desc) == 1 and binding.scoring_route(desc)[1] == K.shape[0] * K.shape[1] * groups * 2048
+    per_group = 2560 if K.shape[2] >= 640 * groups else 2048
+    return binding.scoring_sweeps(desc) == 1 and binding.scoring_route(desc)[1] == K.shape[0] * K.shape[1] * groups * per_group
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -148,16 +149,65 @@ def test_given_up_waits_are_reported(monkeypatch):
 
 
 @pytest.mark.parametrize("G,alpha", [(4, 32), (8, 24), (8, 64)])
-@pytest.mark.parametrize("top", [19, 22, 35, 48, 52])
-def test_sums_that_are_counted_apart(G, alpha, top):
-    # a key that many binades above all others, in one item or in every third: its sum is kept in a word of its own up to 2^44
-    for step in (5000, 1500):
-        binades = np.random.RandomState(top).uniform(-6, 0, 5000)
+@pytest.mark.parametrize("N", [2600, 5200])
+@pytest.mark.parametrize("top", [12, 14, 22, 35, 42, 45, 60, 72, 75, 90, 101, 106])
+def test_sums_that_are_counted_apart(G, alpha, top, N):
+    # a key that many binades above all others, in one item or in several: sums beyond 2^13, 2^43 and 2^73 are kept in words of
+    # their own (at 512 rows the shorter prompts have no third one), beyond 2^103 the unit is scored again
+    for step in (N, 1100):
+        binades = np.random.RandomState(top).uniform(-6, 0, N)
         binades[700::step] = top
         Q, K, V = _along(G, alpha, binades, 128, seed=top)
+        assert N < 512 * ((G * alpha + 63) // 64) or _taken(Q, K, alpha + 30)
         out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
         torch.cuda.synchronize()
         compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+
+
+@pytest.mark.parametrize("G,alpha", [(4, 32), (8, 64)])
+@pytest.mark.parametrize("tops", [(10, 43, 73, 103), (30, 45, 44), (60, 74, 73.5), (99, 100, 70, 40, 10)])
+def test_sums_in_several_words_add_up(G, alpha, tops):
+    # items whose sums go to different words, about as large as each other at the borders between them
+    binades = np.random.RandomState(len(tops)).uniform(-6, 0, 5200)
+    for i, top in enumerate(tops):
+        binades[300 + 900 * i] = top
+    Q, K, V = _along(G, alpha, binades, 128, seed=7)
+    assert _taken(Q, K, alpha + 30)
+    out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
+    torch.cuda.synchronize()
+    compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+
+
+@pytest.mark.parametrize("binades", [55, 88])
+def test_a_key_far_above_the_others_in_every_unit_costs_little(binades):
+    # (scoring such units again takes some fifteen times as long; reading the words for large sums a few per cent)
+    G, alpha, N, Hkv, L = 4, 32, 16384, 8, 8
+    data = [_inputs(1, G * Hkv, Hkv, 128, N, alpha, seed=l) for l in range(L)]
+    for Q, _, _ in data:
+        Q += 1.5 * torch.randn(1, Hkv, 1, 1, 128, device=DEV).expand(1, Hkv, G, 1, 128).reshape(1, Hkv * G, 1, 128).to(torch.bfloat16)
+
+    def best(call):
+        took = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call.run()
+            b.record()
+            torch.cuda.synchronize()
+            took.append(a.elapsed_time(b))
+        return min(took)
+
+    def call():
+        return binding.LayersCall([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], [alpha + 60] * L, synth.POOL_MAX, 7)
+
+    assert _taken(data[0][0], data[0][1], alpha + 60)
+    plain = best(call())
+    for Q, K, _ in data:
+        q = Q.view(1, Hkv, G * alpha, 128).float().mean(dim=2)
+        K[:, :, 9000] = (q * (binades * np.log(2) * 128 ** 0.5 / q.square().sum(dim=2, keepdim=True))).to(torch.bfloat16)
+    far = best(call())
+    print("far", binades, plain, far, flush=True)
+    assert far < 3 * plain
 
 
 @pytest.mark.parametrize("Hkv,G,alpha,N", [(1, 4, 32, 32768), (1, 8, 64, 32768), (6, 4, 16, 65536), (1, 4, 32, 131072)])
