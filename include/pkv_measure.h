@@ -101,21 +101,26 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
  * L layers of desc's shape on a device of 256 compute units or more, and what
  * it keeps of its statistics in the workspace.
  *
+ * variant        0, or PKV_ROUTE_LSE where softmax denominators are supplied,
+ *                plus PKV_ROUTE_SEQ_LENS where seq_lens is not NULL.
  * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _SWEEP, _RESIDENT, or
  *                _ACCUM for the per-layer kernels.
  * scratch_bytes  written: bytes of statistics that a launch addresses.
  * scratch_room   written: bytes of the workspace region that holds them.
  * Returns PKV_OK, PKV_ERR_INVALID_ARG or PKV_ERR_UNSUPPORTED.
  */
+enum { PKV_ROUTE_LSE = 1, PKV_ROUTE_SEQ_LENS = 2 };
+
 int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L,
-                      int32_t lse_supplied, int32_t* kernel_id,
+                      int32_t variant, int32_t* kernel_id,
                       size_t* scratch_bytes, size_t* scratch_room);
 
 /*
  * Measurement aid, HOST only: how many times the scoring of a layer of desc's
  * shape forms each window logit (1 or 2), or 0 where desc is not accepted.
+ * variant as above.
  */
-int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t lse_supplied);
+int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t variant);
 
 #ifdef __cplusplus
 }

@@ -424,25 +424,25 @@ KERNEL_NAMES = ["score_stats", "score_finalize", "score_accum", "pool_select", "
                 "score_sweep"]
 
 
-def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False):
+def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False, seq_lens: bool = False):
     """pkv_scoring_route: (kernel name, scratch bytes, room for them) of a call over L layers.  Touches no device."""
     lib = load()
     lib.pkv_scoring_route.argtypes = [ctypes.POINTER(LayerDesc), ctypes.c_int32, ctypes.c_int32] + [ctypes.c_void_p] * 3
     lib.pkv_scoring_route.restype = ctypes.c_int
     kernel, used, room = ctypes.c_int32(), ctypes.c_size_t(), ctypes.c_size_t()
-    rc = lib.pkv_scoring_route(ctypes.byref(desc), L, int(lse_supplied), ctypes.byref(kernel), ctypes.byref(used),
+    rc = lib.pkv_scoring_route(ctypes.byref(desc), L, int(lse_supplied) + 2 * int(seq_lens), ctypes.byref(kernel), ctypes.byref(used),
                                ctypes.byref(room))
     if rc != OK:
         raise PkvError(rc, "pkv_scoring_route")
     return KERNEL_NAMES[kernel.value], used.value, room.value
 
 
-def scoring_sweeps(desc: LayerDesc, lse_supplied: bool = False) -> int:
+def scoring_sweeps(desc: LayerDesc, lse_supplied: bool = False, seq_lens: bool = False) -> int:
     """pkv_scoring_sweeps: how many times the scoring forms each window logit.  Touches no device."""
     lib = load()
     lib.pkv_scoring_sweeps.argtypes = [ctypes.POINTER(LayerDesc), ctypes.c_int32]
     lib.pkv_scoring_sweeps.restype = ctypes.c_int
-    return lib.pkv_scoring_sweeps(ctypes.byref(desc), int(lse_supplied))
+    return lib.pkv_scoring_sweeps(ctypes.byref(desc), int(lse_supplied) + 2 * int(seq_lens))
 
 
 class HipEvents:

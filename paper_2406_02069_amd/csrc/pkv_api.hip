@@ -269,8 +269,8 @@ static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_
 }
 
 // How the lagging one-pass kernel serves a call: items of a unit of N keys, groups of query rows, layers per launch (0: it
-// does not).  From one layer's shape alone, so that a call over many layers gives the results of one call per layer.  A unit's
-// words lie where its pooled scores lie later on.
+// does not).  From one layer's shape and whether there are sequence lengths, so that a call over many layers gives the results of
+// one call per layer.  A unit's words lie where its pooled scores lie later on.
 // Where the lines lie, whole calls of 8 layers (of one) with 8 heads, before -> with this kernel, us:
 //   33 .. 64 rows, against the other one-pass kernel, whose start is 4 us shorter: 8k keys 53 -> 48 (27 -> 32), 32k keys
 //     181 -> 155 (45 -> 49), 64k keys 375 -> 303 (99 -> 90), 128k keys 767 -> 565 (168 -> 154).
@@ -287,12 +287,19 @@ static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_
 //     165, 94 items about equal, 118 items 266 -> 313, 128 items 281 -> 230, 167 items and more 445 -> 506, 470 -> 662, 256
 //     items 523 -> 465; 96 rows, 256 items 848 -> 877 (8 layers); 256 rows: 88 items 298 -> 277, 94 items 300 -> 316, 128
 //     items 384 -> 307, 256 items 1349 -> 1443 (8 layers).
+//   With sequence lengths the items are those of the sequences, not of N, and the host does not know them: 128 and 256 items say
+//     nothing.  Beyond 88 items per unit, buffers of 64k keys, sequences of 53k .. 64k, 4 of them x 2 layers: 96 rows 419 -> 516,
+//     128 rows 453 -> 540, 256 rows 666 -> 758, 512 rows 1119 -> 1180; of 128k keys, 85k .. 120k: 128 rows 501 -> 661.  64 rows,
+//     units of 90 .. 126 items in 64k buffers 0.62 .. 0.97 of the time before, of 103 .. 170 in 88k buffers 0.38 .. 0.61; in 128k
+//     buffers 130 items 701 -> 300 but 215 items 777 -> 847, 235 items 799 -> 991.  (Sequences that fill less than a tenth of
+//     their buffer: 8 of 600 keys in 16k, 64 rows, one layer 25.5 -> 29.8, 32 layers 191 -> 207; of 4000 keys 604 -> 569.)
 constexpr int kLagMinRows = 33;
 constexpr int kLagMinItems = 1280;      // per layer, at 64 rows and less
 constexpr int kLagMinItemsLong = 768;   // ... of units of more than 64 items
-static bool lag_parts_ok(int64_t parts, int groups, int R) {
-  if (parts <= 88 || parts == 128) return true;
-  if (parts == kStreamGrid) return groups == 1 || (groups == 2 && R > 112);
+static bool lag_parts_ok(int64_t parts, int groups, int R, bool ragged) {
+  if (parts <= 88) return true;
+  if (parts == 128 && !ragged) return true;
+  if (parts == kStreamGrid && !ragged) return groups == 1 || (groups == 2 && R > 112);
   return groups == 1 && (parts <= 102 || (parts > 125 && parts <= 176));
 }
 struct LagPlan {
@@ -300,7 +307,7 @@ struct LagPlan {
   bool words4;
   size_t unit_bytes() const { return (size_t)groups * (kLagGroupBytes + (words4 ? kLagGroupBytes4 : 0)); }
 };
-static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode) {
+static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged) {
   LagPlan p = {0, 0, 0, false};
   if (lse_mode || plan.R < kLagMinRows || plan.R > kResidentMaxRows || !plan.resident_ok) return p;
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
@@ -310,7 +317,7 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
   p.words4 = (int64_t)groups * (kLagGroupBytes + kLagGroupBytes4) <= (int64_t)d.N * 4;
   const int64_t parts = (d.N + kLagKeys - 1) / kLagKeys;
   if (groups == 1 && parts * plan.BH < (parts > 64 ? kLagMinItemsLong : kLagMinItems)) return p;
-  if (!lag_parts_ok(parts, groups, plan.R)) return p;
+  if (!lag_parts_ok(parts, groups, plan.R, ragged)) return p;
   const int64_t by_items = (int64_t)kLagItems * kStreamGrid / (parts * plan.BH), by_units = kStreamUnits / d.B;
   int64_t nl = by_items < by_units ? by_items : by_units;
   if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;
@@ -345,7 +352,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   LagPlan gp = {0, 0, 0, false};
   StreamPlan sp = {0, 0, 0, 0, 0, 0, 0, 0};
   SweepPlan wp = {0, 0, 0};
-  if (any_scores && resident) gp = lag_plan(plan, d, lse_mode);
+  if (any_scores && resident) gp = lag_plan(plan, d, lse_mode, seq_lens != nullptr);
   if (any_scores && resident && gp.layers == 0) {
     sp = stream_plan(plan, d, lse_mode);
     wp = sweep_plan(plan, d, lse_mode);
@@ -1001,18 +1008,18 @@ int pkv_compress_layers_profiled(int32_t L, const pkv_layer_desc* descs, const v
   return rc;
 }
 
-int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t lse_supplied, int32_t* kernel_id,
+int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t variant, int32_t* kernel_id,
                       size_t* scratch_bytes, size_t* scratch_room) {
   const int rc = check_desc(desc);
   if (rc != PKV_OK) return rc;
   if (L < 1 || L > kMaxLayers || !kernel_id || !scratch_bytes || !scratch_room) return PKV_ERR_INVALID_ARG;
   const Plan plan = make_plan(*desc, L);
-  const bool lse_mode = lse_supplied != 0;
+  const bool lse_mode = (variant & ~PKV_ROUTE_SEQ_LENS) != 0, ragged = (variant & PKV_ROUTE_SEQ_LENS) != 0;
   *kernel_id = PKV_KERNEL_SCORE_ACCUM;
   *scratch_bytes = 0;
   *scratch_room = plan.total - plan.off_pooled;
   if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return PKV_OK;
-  const LagPlan gp = lag_plan(plan, *desc, lse_mode);
+  const LagPlan gp = lag_plan(plan, *desc, lse_mode, ragged);
   if (gp.layers > 0) {
     *kernel_id = lag_kernel_id(plan);
     *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.unit_bytes();
@@ -1031,12 +1038,12 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink, void* stream) 
   return launch_probe_read(buf, bytes, sink, static_cast<hipStream_t>(stream)) == hipSuccess ? PKV_OK : PKV_ERR_HIP;
 }
 
-int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t lse_supplied) {
+int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t variant) {
   if (check_desc(desc) != PKV_OK) return 0;
   const Plan plan = make_plan(*desc, 1);
-  if (lse_supplied) return 1;
+  if ((variant & ~PKV_ROUTE_SEQ_LENS) != 0) return 1;
   if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return 2;
-  return lag_plan(plan, *desc, false).layers > 0 || stream_plan(plan, *desc, false).layers > 0 ? 1 : 2;
+  return lag_plan(plan, *desc, false, (variant & PKV_ROUTE_SEQ_LENS) != 0).layers > 0 || stream_plan(plan, *desc, false).layers > 0 ? 1 : 2;
 }
 
 const char* pkv_status_string(int status) {

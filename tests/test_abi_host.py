@@ -309,6 +309,21 @@ def _shape(B, Hq, Hkv, d, N, alpha, flags=0):
                  q_st=d, kv_sb=Hkv * N * d, kv_sh=N * d, kv_st=d, o_sb=Hkv * alpha * d, o_sh=alpha * d, o_st=d)
 
 
+def test_long_buffers_with_sequence_lengths_are_not_judged_by_their_own_length():
+    # one pass over K at 33 rows and more pays at up to 88 items of 512 keys per head, and where the heads' items deal out evenly
+    # over 256 workgroups; with sequence lengths the host does not know a head's items, only that there are no more than N has
+    for Hq, alpha in ((32, 24), (32, 32), (64, 32), (64, 64)):
+        for N in (20000, 45056):
+            assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, N, alpha), seq_lens=True) == 1
+        assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, 65536, alpha)) == 1
+        for N in (45057, 60000, 65536, 131072):
+            assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, N, alpha), seq_lens=True) == 2
+    for N in (40000, 52224, 65536, 90112):
+        assert binding.scoring_sweeps(_shape(4, 32, 8, 128, N, 16), seq_lens=True) == 1
+    assert binding.scoring_sweeps(_shape(4, 32, 8, 128, 131072, 16)) == 1
+    assert binding.scoring_sweeps(_shape(4, 32, 8, 128, 131072, 16), seq_lens=True) == 2
+
+
 def test_statistics_of_the_scoring_kernels_fit_the_workspace():
     # short prompts on many units, item and chunk edges, launches of many layers: what a scoring kernel keeps beside its
     # scores ends inside the workspace, and the kernel that takes a call does not depend on the number of layers
