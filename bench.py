@@ -39,7 +39,7 @@ def layer_bytes(w, k_l, sum_n):
 def kernel_bytes(name, w, ks, sum_n):
     """Algorithmic bytes of ONE launch of a kernel (same accounting as layer_bytes, split per kernel)."""
     kq = w.Hkv * sum_n * w.d * 2 + w.B * w.Hq * w.alpha * w.d * 2          # K once + Q_win, one layer
-    if name in ("score_resident", "score_stream", "score_sweep"):            # one launch covers all layers
+    if name in ("score_resident", "score_stream", "score_sweep", "score_lag"):   # one launch covers all layers
         return kq * w.L
     if name in ("score_stats", "score_accum"):                               # one launch per layer and sweep
         return kq
@@ -227,7 +227,7 @@ def measure(w, avg, steps, warmup, dev, lse=False, page_size=0, host_layers=(), 
     launches_per_step = len(per_kernel[binding.KERNEL_NAMES.index(dominant)]) / n_prof
     if dominant.startswith("score") and fl / dom_bytes / max(launches_per_step, 1) > MFMA_BF16_PEAK_TFLOPS / HBM_PEAK_GBPS * 1e3:
         tf = fl / (sum_ms[dominant] * 1e-3) / 1e12
-        sweeps = binding.scoring_sweeps(call.descs[0], lse)
+        sweeps = binding.scoring_sweeps(call.descs[0], lse, lens is not None)
         res["roofline"].update({"bound": "mfma", "achieved": tf, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                                 "frac": tf / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                                 "executed_TFLOPs": tf * sweeps, "executed_frac": tf * sweeps / MFMA_BF16_PEAK_TFLOPS,

@@ -57,15 +57,12 @@ typedef enum {
   PKV_KERNEL_SCORE_ACCUM = 2, /* sweep 2 over K: per-key window scores      */
   PKV_KERNEL_POOL_SELECT = 3,
   PKV_KERNEL_GATHER = 4,
-  /* All layers in one launch or a few.  The lagging one-pass kernel, which
-     serves calls of 33 to 512 query rows per KV head from some size on, is
-     counted under the kernel that serves these rows elsewhere: SCORE_STREAM up
-     to 64 rows, SCORE_RESIDENT up to 128, SCORE_SWEEP beyond
-     (pkv_scoring_sweeps tells them apart).                                  */
+  /* all layers in one launch or a few:                                      */
   PKV_KERNEL_SCORE_RESIDENT = 5, /* both sweeps, K held in registers         */
   PKV_KERNEL_SCORE_STREAM = 6,   /* one pass over K, few query rows          */
-  PKV_KERNEL_SCORE_SWEEP = 7     /* streaming sweeps over K, many query rows or
+  PKV_KERNEL_SCORE_SWEEP = 7,    /* streaming sweeps over K, many query rows or
                                     supplied denominators                    */
+  PKV_KERNEL_SCORE_LAG = 8       /* one pass over K, 64 query rows at a time */
 } pkv_kernel_id;
 
 int pkv_compress_layers_profiled(
@@ -103,7 +100,7 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
  *
  * variant        0, or PKV_ROUTE_LSE where softmax denominators are supplied,
  *                plus PKV_ROUTE_SEQ_LENS where seq_lens is not NULL.
- * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _SWEEP, _RESIDENT, or
+ * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _LAG, _SWEEP, _RESIDENT, or
  *                _ACCUM for the per-layer kernels.
  * scratch_bytes  written: bytes of statistics that a launch addresses.
  * scratch_room   written: bytes of the workspace region that holds them.

@@ -328,11 +328,6 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
   return p;
 }
 
-// What the recorder calls the lagging kernel: the kernel that serves calls of these query rows elsewhere.
-static int lag_kernel_id(const Plan& plan) {
-  return plan.R <= kStreamMaxRows ? PKV_KERNEL_SCORE_STREAM : (plan.R < kSweepMinRows ? PKV_KERNEL_SCORE_RESIDENT : PKV_KERNEL_SCORE_SWEEP);
-}
-
 // Queue the kernels of L layers.  All arguments have been validated.
 static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, const LayerPtrs* ptrs,
                       const int32_t* seq_lens, void* workspace, hipStream_t stream, Recorder* rec,
@@ -428,7 +423,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       ga.inv_G = 1.0f / (float)plan.G;
       if (launch_score_lag(ga, first, stream) != hipSuccess) return PKV_ERR_HIP;
       first = false;
-      if (rec) rec->after(lag_kernel_id(plan), stream);
+      if (rec) rec->after(PKV_KERNEL_SCORE_LAG, stream);
     }
   } else if (sp.layers > 0) {
     for (int32_t l0 = 0; l0 < L; l0 += sp.layers) {
@@ -1021,7 +1016,7 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t variant, in
   if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return PKV_OK;
   const LagPlan gp = lag_plan(plan, *desc, lse_mode, ragged);
   if (gp.layers > 0) {
-    *kernel_id = lag_kernel_id(plan);
+    *kernel_id = PKV_KERNEL_SCORE_LAG;
     *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.unit_bytes();
     return PKV_OK;
   }

@@ -344,7 +344,7 @@ def test_statistics_of_the_scoring_kernels_fit_the_workspace():
                         assert used <= room
                     assert len(kernels) == 1, (B, Hkv, G, alpha, d, N, kernels)
                     taken |= kernels
-    assert taken == {"score_resident", "score_stream", "score_sweep"}
+    assert taken == {"score_lag", "score_resident", "score_stream", "score_sweep"}
     for N in (9, 63, 64, 127, 128):
         assert binding.scoring_route(_shape(1, 64, 8, 128, N, 8), 126)[0] == "score_stream"
     # the one-pass kernel keeps statistics words for every item of a launch (1024 keys of a unit; 512 at 33 .. 64 rows)

