@@ -37,9 +37,10 @@ def layer_bytes(w, k_l, sum_n):
 
 
 def kernel_bytes(name, w, ks, sum_n):
-    """Algorithmic bytes of ONE launch of a kernel (same accounting as layer_bytes, split per kernel)."""
+    """Algorithmic bytes of a kernel, same accounting as layer_bytes: over all layers, or over one layer where every layer
+    has a launch of its own."""
     kq = w.Hkv * sum_n * w.d * 2 + w.B * w.Hq * w.alpha * w.d * 2          # K once + Q_win, one layer
-    if name in ("score_resident", "score_stream", "score_sweep", "score_lag"):   # one launch covers all layers
+    if name in ("score_resident", "score_stream", "score_sweep", "score_lag"):   # all layers, in one launch or a few
         return kq * w.L
     if name in ("score_stats", "score_accum"):                               # one launch per layer and sweep
         return kq
@@ -48,6 +49,11 @@ def kernel_bytes(name, w, ks, sum_n):
     if name == "pool_select":
         return sum(w.B * w.Hkv * k * 4 for k in ks)
     return 0
+
+
+def step_bytes(name, w, ks, sum_n, launches_per_step):
+    """Algorithmic bytes of a kernel over a whole step."""
+    return kernel_bytes(name, w, ks, sum_n) * (launches_per_step if name in ("score_stats", "score_accum") else 1)
 
 
 def score_flops(w, sum_n):
@@ -196,8 +202,9 @@ def measure(w, avg, steps, warmup, dev, lse=False, page_size=0, host_layers=(), 
                                "the timed steps did not produce valid results")
 
     total_bytes = sum(layer_bytes(w, k, sum_n) for k in ks)
-    dom_bytes = kernel_bytes(dominant, w, ks, sum_n)
-    achieved = dom_bytes / (avg_ms[dominant] * 1e-3) / 1e9
+    launches_per_step = len(per_kernel[binding.KERNEL_NAMES.index(dominant)]) / n_prof
+    dom_bytes = step_bytes(dominant, w, ks, sum_n, launches_per_step)
+    achieved = dom_bytes / (sum_ms[dominant] * 1e-3) / 1e9
     kname = dominant + ("_lse" if lse else "")
     res = {
         "value": sum_n / (ms_per_step * 1e-3),
@@ -214,7 +221,7 @@ def measure(w, avg, steps, warmup, dev, lse=False, page_size=0, host_layers=(), 
         "roofline": {"kernel": dominant, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS,
                      "traffic": tracked("traffic_bytes.txt", kname, w.name, avg, int),
-                     "algorithmic_bytes_per_launch": dom_bytes, "avg_launch_ms": avg_ms[dominant],
+                     "algorithmic_bytes_per_launch": dom_bytes / launches_per_step, "avg_launch_ms": avg_ms[dominant],
                      "launches_timed": len(per_kernel[binding.KERNEL_NAMES.index(dominant)]),
                      "mfma_busy_frac": tracked("pipe_busy.txt", kname + ":mfma", w.name, avg, float),
                      "valu_busy_frac": tracked("pipe_busy.txt", kname + ":valu", w.name, avg, float)},
@@ -224,8 +231,7 @@ def measure(w, avg, steps, warmup, dev, lse=False, page_size=0, host_layers=(), 
     # matrix pipe, not by HBM: its roofline is stated in flops (each logit formed once; the two-sweep kernels
     # execute twice that, reported beside it).
     fl = score_flops(w, sum_n)
-    launches_per_step = len(per_kernel[binding.KERNEL_NAMES.index(dominant)]) / n_prof
-    if dominant.startswith("score") and fl / dom_bytes / max(launches_per_step, 1) > MFMA_BF16_PEAK_TFLOPS / HBM_PEAK_GBPS * 1e3:
+    if dominant.startswith("score") and fl / dom_bytes > MFMA_BF16_PEAK_TFLOPS / HBM_PEAK_GBPS * 1e3:
         tf = fl / (sum_ms[dominant] * 1e-3) / 1e12
         sweeps = binding.scoring_sweeps(call.descs[0], lse, lens is not None)
         res["roofline"].update({"bound": "mfma", "achieved": tf, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",

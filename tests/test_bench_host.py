@@ -25,6 +25,9 @@ def test_algorithmic_bytes_of_the_headline_workload():
     assert bench.kernel_bytes("score_resident", w, [128] * w.L, w.N) == per_layer * 32 == 2155872256
     for name in ("score_stream", "score_sweep", "score_lag"):
         assert bench.kernel_bytes(name, w, [128] * w.L, w.N) == per_layer * 32
+        # ... in one launch or in two: a step reads the same
+        assert bench.step_bytes(name, w, [128] * w.L, w.N, 1) == bench.step_bytes(name, w, [128] * w.L, w.N, 2) == per_layer * 32
+    assert bench.step_bytes("score_stats", w, [128] * w.L, w.N, 32) == per_layer * 32   # a launch per layer
     # one layer: K, Q_win, kept K and V rows read and written, kept indices
     k = 100
     assert bench.layer_bytes(w, k, w.N) == per_layer + 4 * 8 * k * 128 * 2 + 8 * k * 4
