@@ -28,6 +28,14 @@ def bits(t: torch.Tensor) -> np.ndarray:
     return t.detach().cpu().contiguous().view(torch.int16).numpy().view(np.uint16)
 
 
+def spread_queries(Q: torch.Tensor) -> torch.Tensor:
+    """The same window queries as a view into all queries of a long prefill: 2^24 elements from head to head.  The one-pass
+    kernel for 33 rows and more does not take such a view; the kernels that also serve its rows do."""
+    B, H, alpha, d = Q.shape
+    view = torch.empty(B * H << 24, dtype=Q.dtype, device=Q.device).as_strided((B, H, alpha, d), (H << 24, 1 << 24, d, 1))
+    return view.copy_(Q)
+
+
 def compare_layer(Q, K, V, k_l, alpha, pool, pool_w, lens, gpu, ref=None, check_scores=True):
     """gpu = (K_out, V_out, idx, count, scores) torch tensors from the library.  Returns a stats dict."""
     Kb, Vb = bits(K), bits(V)

@@ -21,8 +21,9 @@ def _inputs(B, Hq, Hkv, d, N, alpha, seed, scale=1.0):
     return Q, K, V
 
 
-def _check(Q, K, V, k_l, lens=None, pool=synth.POOL_MAX, pw=7):
-    print("stream", tuple(Q.shape), tuple(K.shape), k_l, None if lens is None else lens.tolist()[:8], flush=True)
+def _check(Q, K, V, k_l, lens=None, pool=synth.POOL_MAX, pw=7, kernel="score_stream"):
+    assert binding.scoring_route(binding.make_desc(Q, K, k_l, pool, pw), seq_lens=lens is not None)[0] == kernel
+    print(kernel, tuple(Q.shape), tuple(K.shape), k_l, None if lens is None else lens.tolist()[:8], flush=True)
     ld = None if lens is None else torch.from_numpy(lens).to(DEV)
     out = binding.compress_layer(Q, K, V, k_l, pool, pw, seq_lens=ld, want_scores=True)
     torch.cuda.synchronize()
@@ -88,12 +89,10 @@ def test_references_that_do_not_fit(G):
     Q, K, V = _inputs(1, G, 1, 128, N, alpha, seed=G, scale=0.5)
     K[0, 0, 700] = 40 * Q[0, 0, 3]
     K[0, 0, 0:2500:32] = -20 * Q[0, 0, 3]
-    out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
-    torch.cuda.synchronize()
-    compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
+    _check(Q, K, V, alpha + 30, pool=synth.POOL_NONE, pw=1)
 
 
-def precision_of_scores(Hq, Hkv, d, N, alpha, sink):
+def precision_of_scores(Hq, Hkv, d, N, alpha, sink, kernel, layout=lambda Q: Q):
     """Largest error of a KV head's un-pooled scores against 64 bits, 2-norm over the prefix, for queries that point largely
     the same way.  sink: key 0 as a multiple of that direction, None for a key like the others."""
     g = torch.Generator(device=DEV).manual_seed(N + alpha)
@@ -103,12 +102,14 @@ def precision_of_scores(Hq, Hkv, d, N, alpha, sink):
     K = torch.randn(1, Hkv, N, d, generator=g, device=DEV).to(torch.bfloat16)
     if sink is not None:
         K[:, :, 0] = (sink * base[:, :, 0]).to(torch.bfloat16)
+    Q = layout(Q)
+    assert binding.scoring_route(binding.make_desc(Q, K, alpha + 100, synth.POOL_NONE, 1))[0] == kernel
     out = binding.compress_layer(Q, K, K, alpha + 100, synth.POOL_NONE, 1, want_scores=True)
     torch.cuda.synchronize()
     hidden = torch.ones(alpha, alpha, dtype=torch.bool, device=DEV).triu(1)
     worst = 0.0
     for h in range(Hkv):
-        x = Q[0].view(Hkv, -1, d)[h].double() @ K[0, h].double().t().contiguous() / d ** 0.5
+        x = Q[0].reshape(Hkv, -1, d)[h].double() @ K[0, h].double().t().contiguous() / d ** 0.5
         x.view(-1, alpha, N)[:, :, N - alpha:].masked_fill_(hidden, -np.inf)
         want = x.softmax(dim=1).sum(dim=0)[:N - alpha] / (Hq // Hkv)
         worst = max(worst, float((out[4][0, h, :N - alpha].double() - want).norm() / want.norm()))
@@ -120,7 +121,7 @@ def precision_of_scores(Hq, Hkv, d, N, alpha, sink):
 def test_precision_with_a_sink_above_or_below_the_other_keys(Hq, Hkv, d, N, alpha, sink):
     # bound: a logit of up to 2^5 binades carries half a unit in the last place, 2^-20, and so does its distance from the
     # reference; together 2^-19 ln 2 = 1.3e-6 in a score
-    assert precision_of_scores(Hq, Hkv, d, N, alpha, sink) < 1.3e-6
+    assert precision_of_scores(Hq, Hkv, d, N, alpha, sink, "score_stream") < 1.3e-6
 
 
 

@@ -1,6 +1,7 @@
 """Scoring in two streaming launches for many query rows (G * alpha > 128) at the edges of its work split: rows around the
 32-row tiles and the limit, lengths around a pass and a chunk, ragged batches, chunk counts that the workgroups do not
-divide, references that do not fit, supplied denominators."""
+divide, references that do not fit, supplied denominators.  (Own denominators: the queries lie so far apart that the one-pass
+kernel, which serves most of these shapes otherwise, does not take them; and lengths that it leaves to this one anyway.)"""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +9,7 @@ import torch
 from oracle import pkv_oracle
 from paper_2406_02069_amd import binding, synth
 from tests import prefill_stub
-from tests.parity import compare_layer
+from tests.parity import compare_layer, spread_queries
 from tests.test_gpu_stream import precision_of_scores
 
 pytestmark = pytest.mark.gpu
@@ -23,7 +24,14 @@ def _inputs(B, Hq, Hkv, d, N, alpha, seed, scale=1.0):
     return Q, K, V
 
 
+def _taken(Q, K, k_l, seq_lens=False):
+    """The kernel under test takes the call."""
+    return binding.scoring_route(binding.make_desc(Q, K, k_l, synth.POOL_MAX, 7), seq_lens=seq_lens)[0] == "score_sweep"
+
+
 def _check(Q, K, V, k_l, lens=None, pool=synth.POOL_MAX, pw=7):
+    Q = spread_queries(Q)
+    assert _taken(Q, K, k_l, lens is not None)
     print("sweep", tuple(Q.shape), tuple(K.shape), k_l, None if lens is None else lens.tolist()[:8], flush=True)
     ld = None if lens is None else torch.from_numpy(lens).to(DEV)
     out = binding.compress_layer(Q, K, V, k_l, pool, pw, seq_lens=ld, want_scores=True)
@@ -35,7 +43,7 @@ def _check(Q, K, V, k_l, lens=None, pool=synth.POOL_MAX, pw=7):
 @pytest.mark.parametrize("G,alpha", [(3, 43), (4, 40), (7, 23), (5, 51), (8, 33), (7, 64), (8, 64)])
 def test_rows(d, G, alpha):
     Hkv = 8
-    N = 4100 if G * alpha <= 256 else 8200
+    N = 4100 if G * alpha <= 224 else 4096 if G * alpha <= 256 else 8192 if G * alpha == 512 else 8200   # (room for the statistics of the last chunk)
     Q, K, V = _inputs(1, Hkv * G, Hkv, d, N, alpha, seed=G * 100 + alpha + d)
     _check(Q, K, V, alpha + 60)
 
@@ -47,8 +55,17 @@ def test_lengths_around_a_pass(N):
 
 
 def test_one_chunk_per_unit():
-    Q, K, V = _inputs(8, 16, 8, 64, 1024, 64, seed=3)
+    Q, K, V = _inputs(8, 24, 8, 64, 512, 64, seed=3)
     _check(Q, K, V, 80)
+
+
+@pytest.mark.parametrize("G,alpha,N", [(4, 40, 45057), (8, 32, 59000), (8, 64, 46100)])
+def test_lengths_that_the_one_pass_kernel_leaves(G, alpha, N):
+    Q, K, V = _inputs(1, 8 * G, 8, 128, N, alpha, seed=N)
+    assert _taken(Q, K, alpha + 60)
+    out = binding.compress_layer(Q, K, V, alpha + 60, synth.POOL_MAX, 7, want_scores=True)
+    torch.cuda.synchronize()
+    compare_layer(Q, K, V, alpha + 60, alpha, synth.POOL_MAX, 7, None, out)
 
 
 def test_ragged_batch():
@@ -70,6 +87,8 @@ def test_no_sequence_needs_scores():
 def test_many_layers_equal_one_call_per_layer():
     L, alpha, N = 7, 40, 4300
     data = [_inputs(2, 16, 4, 64, N, alpha, seed=500 + l) for l in range(L)]
+    data = [(spread_queries(x[0]), x[1], x[2]) for x in data]
+    assert _taken(data[0][0], data[0][1], 50, seq_lens=True)
     lens = torch.tensor([4300, 3100], dtype=torch.int32, device=DEV)
     ks = [N + 5, 50, 60, 70, 3500, 90, N]                     # layers and sequences kept whole among them
     outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_MAX, 7,
@@ -109,11 +128,13 @@ def test_supplied_denominators(d, G, alpha, N):
     compare_layer(Q, K, V, alpha + 50, alpha, synth.POOL_AVG, 5, lens, out, ref=ref)
 
 
-@pytest.mark.parametrize("d,G,alpha", [(64, 8, 17), (128, 8, 17), (128, 8, 64)])
-def test_sixteen_waves_write_the_scores(d, G, alpha):
+@pytest.mark.parametrize("d,G,alpha,N", [(64, 8, 17, 11300), (128, 8, 17, 11300), (128, 8, 64, 36000)])
+def test_sixteen_waves_write_the_scores(d, G, alpha, N):
     # enough passes for sixteen waves, with chunks of which the last pass is partly empty; bit for bit what eight give
-    L, Hkv, N = 12, 8, 11300
+    L, Hkv = 12, 8
     data = [_inputs(1, G * Hkv, Hkv, d, N, alpha, seed=70 + l) for l in range(L)]
+    data = [(spread_queries(x[0]), x[1], x[2]) for x in data]
+    assert _taken(data[0][0], data[0][1], alpha + 20)
     ks = [alpha + 20 + 9 * l for l in range(L)]
     outs = binding.compress_layers([x[0] for x in data], [x[1] for x in data], [x[2] for x in data], ks, synth.POOL_AVG, 5,
                                    want_scores=True)
@@ -147,7 +168,7 @@ def test_supplied_denominators_few_rows(d, G, alpha):
 def test_precision_of_the_normalisers(Hq, Hkv, d, N, alpha):
     # errors of single rows average out over this many; what is left is common to all rows: the rounding of kappa, 2^-25 of a
     # logit up to 10 binades from the mean, 10 ln 2 / 2^25 = 2.1e-7, and as much again for the normalisers
-    assert precision_of_scores(Hq, Hkv, d, N, alpha, None) < 4.2e-7
+    assert precision_of_scores(Hq, Hkv, d, N, alpha, None, "score_sweep", spread_queries) < 4.2e-7
 
 
 @pytest.mark.parametrize("finite", [[1, 700, 701, 2500, 4000], list(range(3000, 3200))])
