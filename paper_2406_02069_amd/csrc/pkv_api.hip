@@ -181,7 +181,7 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
 // Up to 32 rows an item is 1024 keys.  Where all items of a call find a workgroup each, items of 512 keys have twice as many
 // at work: one layer of 8 heads x 8k keys, 32 rows 26.6 -> 23.0 us, x 1k 24.2 -> 20.0, of 8 x 1k, d = 64, 8 rows 20.0 -> 17.2;
 // in larger calls they are 3 - 9 % slower (32 layers of 8 x 16k 232 -> 241).  Whether a call is large depends on its number of
-// layers, and the scores must not: up to N = 8192, where one layer would take the small items, a word of statistics stands for
+// layers and sequences, and the scores must not: up to N = 8192, where the small items pay, a word of statistics stands for
 // 512 keys in either case, and an item of 1024 keys has two of them.  (All items of a unit read them: 32 layers of 8 x 16000
 // keys 228 -> 234, of 24000 keys 334 -> 343, and so not beyond.)
 struct StreamPlan {
@@ -199,7 +199,7 @@ static StreamPlan stream_plan(const Plan& plan, const pkv_layer_desc& d, bool ls
     if (d.N > kStreamSplitKeys) p.item_keys = 1024;
     else if ((int64_t)plan.L * plan.BH * ((d.N + 511) / 512) > kStreamGrid) {
       p.item_keys = 1024;
-      if ((int64_t)plan.BH * ((d.N + 511) / 512) <= kStreamGrid) p.words_per_item = 2;  // (one layer would take the small items)
+      p.words_per_item = 2;
     }
   }
   if (d.N < 2 * p.word_rows) {

@@ -59,3 +59,18 @@ def test_items_with_references_that_do_not_fit(G, alpha):
         Q, K = _inputs(1, G, 1, 64, 4100, alpha, at)
         K[0, 0, at] = (Q[0, 0, 3].float() * 12).to(torch.bfloat16)
         _same(Q, K, alpha + 20)
+
+
+# (16 sequences: a layer of them has more items than there are workgroups, a layer of one has not)
+@pytest.mark.parametrize("G,alpha", [(1, 8), (2, 8), (4, 8)])
+@pytest.mark.parametrize("N", [513, 2300, 8192])
+def test_scores_do_not_depend_on_the_number_of_sequences(G, alpha, N):
+    B, k = 16, alpha + 20
+    Q, K = _inputs(B, 8 * G, 8, 128, N, alpha, N % 89)
+    batch = binding.compress_layers([Q], [K], [K], [k], synth.POOL_NONE, 1, want_scores=True)[0]
+    for b in (0, B - 1):
+        one = binding.compress_layers([Q[b:b + 1]], [K[b:b + 1]], [K[b:b + 1]], [k], synth.POOL_NONE, 1, want_scores=True)[0]
+        torch.cuda.synchronize()
+        assert torch.equal(batch[4][b, :, :N - alpha], one[4][0, :, :N - alpha])
+        assert torch.equal(batch[2][b], one[2][0])
+    print("sequences", tuple(Q.shape), tuple(K.shape), flush=True)
