@@ -171,7 +171,7 @@ def test_given_up_waits_are_reported(Hq, Hkv, alpha, monkeypatch):
 
 
 @pytest.mark.parametrize("G,alpha", [(2, 32), (4, 32), (8, 24), (8, 64)])
-@pytest.mark.parametrize("N", [2600, 5200])
+@pytest.mark.parametrize("N", [4500, 5200])
 @pytest.mark.parametrize("top", [12, 14, 22, 35, 42, 45, 60, 72, 75, 90, 101, 106])
 def test_sums_that_are_counted_apart(G, alpha, top, N):
     # a key that many binades above all others, in one item or in several: sums beyond 2^13, 2^43 and 2^73 are kept in words of
@@ -181,7 +181,7 @@ def test_sums_that_are_counted_apart(G, alpha, top, N):
         binades[700::step] = top
         Q, K, V = _along(G, alpha, binades, 128, seed=top)
         Q, K, V = _enough_heads(Q, K, V)
-        assert N < 512 * ((G * alpha + 63) // 64) or _taken(Q, K, alpha + 30)
+        assert _taken(Q, K, alpha + 30)
         out = binding.compress_layer(Q, K, V, alpha + 30, synth.POOL_NONE, 1, want_scores=True)
         torch.cuda.synchronize()
         compare_layer(Q, K, V, alpha + 30, alpha, synth.POOL_NONE, 1, None, out)
