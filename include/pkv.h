@@ -22,20 +22,22 @@
  *  - Launching calls are asynchronous on `stream` (a hipStream_t passed as
  *    void*; NULL = the default stream).  They never synchronise and never
  *    allocate or free memory.  Results are deterministic: the same inputs
- *    give bit-identical outputs.
+ *    give bit-identical outputs.  A layer's do not depend on the number of
+ *    layers in the call; the last bits of a sequence's scores can depend on
+ *    the number of sequences and heads in it.
  *  - Inputs are never modified.
  *  - The library keeps no state between calls and reads no environment
  *    variables.  (The per-device attributes of its kernels are set on first
  *    use; pkv_compress_layer_noalloc has a built-in scratch buffer per device,
  *    see there.)
  *  - Exclusive use of the device.  Whenever a device with at least 256
- *    compute units is given a shape the register-resident scoring kernel
- *    serves (G*alpha <= 512, N <= 262144) without supplied softmax
- *    denominators, that kernel's 512 workgroups (or, at few query rows, the
- *    one-pass kernel's 256) exchange softmax statistics
- *    with each other and must all be resident on the device at the same
- *    time; they fill it completely (registers and LDS of every compute
- *    unit).  The caller must therefore not run other kernels on the device
+ *    compute units is given a shape of G*alpha <= 512 and N <= 262144 without
+ *    supplied softmax denominators, the workgroups of the scoring kernel
+ *    (256 of a one-pass kernel, 512 of the register-resident one) exchange
+ *    softmax sums with each other and must all be resident on the device at
+ *    the same time; they fill it completely (registers and LDS of every
+ *    compute unit).  (Some shapes of more than 128 query rows take a kernel
+ *    without such waits; which ones is not part of the contract.)  The caller must therefore not run other kernels on the device
  *    while such a call executes: no second compress call on another stream,
  *    no other tenant.  Work queued behind it on the same stream is fine.
  *    If the workgroups cannot all be resident, the waits between them are

@@ -183,7 +183,7 @@ static bool use_resident(const Plan& plan, bool lse_mode, int32_t flags) {
 // in larger calls they are 3 - 9 % slower (32 layers of 8 x 16k 232 -> 241).  Whether a call is large depends on its number of
 // layers and sequences, and the scores must not: up to N = 8192, where the small items pay, a word of statistics stands for
 // 512 keys in either case, and an item of 1024 keys has two of them.  (All items of a unit read them: 32 layers of 8 x 16000
-// keys 228 -> 234, of 24000 keys 334 -> 343, and so not beyond.)
+// keys 228 -> 234, of 24000 keys 334 -> 343, and so not beyond.  8 sequences of 8 heads x 8k keys, 32 layers, 836 -> 849.)
 struct StreamPlan {
   int layers, grid, items;
   int item_keys, words_per_item, word_rows;

@@ -123,7 +123,7 @@ struct StreamArgs {
 // clear_err: the first launch of a call also clears the error word
 hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t s);
 
-// ---- one-pass scoring, probabilities waiting on the chip two items long, over many layers (pkv_lag.hip) ----
+// ---- one-pass scoring, probabilities waiting on the chip for two steps of 64 rows, over many layers (pkv_lag.hip) ----
 constexpr int kLagItems = 255;      // items of a workgroup per launch, at most (table in LDS)
 constexpr int kLagKeys = 512;       // keys of an item
 constexpr int kLagGroupBytes = 2048;   // of the workspace, per unit and group of 64 query rows

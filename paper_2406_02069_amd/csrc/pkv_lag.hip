@@ -24,13 +24,14 @@
 // keys this takes half the time of storing the sums, folding and storing the normalisers (3.3 against 5.4 us per round with one
 // round's slack, 2.7 against 3.8 with two).
 //
-// A sum beyond 2^103 times its reference (2^73 in units of less than 640 keys per group of rows; or undefined) does not fit: the unit is scored again at the
-// launch's end, from memory and with exact maxima, which is slow.
+// A sum beyond 2^103 times its reference (2^73 in units of less than 640 keys per group of rows; or undefined) does not fit:
+// the unit is scored again at the launch's end, from memory and with exact maxima, which is slow.
 //
 // What bounds it: at 64 rows HBM (32 layers of 32k keys 599 -> 487 us whole call, against the one-pass kernel that waits for an
-// exchange of all items' statistics), beyond them the issue of vector instructions around the products: a step takes 7600 clk
-// with keys from the cache, of which vector instructions issue for 4000 and the matrix pipe is busy for 2050.  128 rows, 32
-// layers of 32k keys 773 -> 672 us, 512 rows, 80 layers 5435 -> 4385, against the kernels that form everything twice.
+// exchange of all items' statistics), beyond them no pipe alone: at 128 rows a step takes 11 350 clk (5.1 us), in which vector
+// instructions issue for 4 570, the LDS is busy for 2 350 and the matrix pipe for 2 050, one after the other for the most part
+// with two waves per SIMD, and waves wait for 43 % of the time; its keys alone take 2.8 us from HBM.  128 rows, 32 layers of
+// 32k keys 773 -> 672 us, 512 rows, 80 layers 5435 -> 4385, against the kernels that form everything twice.
 //
 // Every wait is bounded by wall-clock time (a workgroup that has waited too long raises the error word and carries on), so the
 // grid always drains.
