@@ -287,20 +287,26 @@ static SweepPlan sweep_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_
 //     165, 94 items about equal, 118 items 266 -> 313, 128 items 281 -> 230, 167 items and more 445 -> 506, 470 -> 662, 256
 //     items 523 -> 465; 96 rows, 256 items 848 -> 877 (8 layers); 256 rows: 88 items 298 -> 277, 94 items 300 -> 316, 128
 //     items 384 -> 307, 256 items 1349 -> 1443 (8 layers).
-//   With sequence lengths the items are those of the sequences, not of N, and the host does not know them: 128 and 256 items say
-//     nothing.  Beyond 88 items per unit, buffers of 64k keys, sequences of 53k .. 64k, 4 of them x 2 layers: 96 rows 419 -> 516,
-//     128 rows 453 -> 540, 256 rows 666 -> 758, 512 rows 1119 -> 1180; of 128k keys, 85k .. 120k: 128 rows 501 -> 661.  64 rows,
-//     units of 90 .. 126 items in 64k buffers 0.62 .. 0.97 of the time before, of 103 .. 170 in 88k buffers 0.38 .. 0.61; in 128k
-//     buffers 130 items 701 -> 300 but 215 items 777 -> 847, 235 items 799 -> 991.  (Sequences that fill less than a tenth of
-//     their buffer: 8 of 600 keys in 16k, 64 rows, one layer 25.5 -> 29.8, 32 layers 191 -> 207; of 4000 keys 604 -> 569.)
+//   With sequence lengths the items are those of the sequences, not of N, and the host does not know them.  The kernel deals units
+//     for which the ring was measured so that none lies in two rounds (lag_unit_straddles; rounds are not filled then), and the
+//     register-resident kernel's time goes with N, whatever the lengths.  4 sequences x 2 layers, lengths of 0.8 .. 1 of N, of
+//     0.3 .. 1, of a tenth and less, before -> with this kernel: 96 rows, 47k keys 390 -> 352, 378 -> 282, 284 -> 46; 59k 414 ->
+//     403, 395 -> 344, 278 -> 47; 64k 430 -> 432, 406 -> 353, 283 -> 48; 100k 819 -> 748, 773 -> 609, 555 -> 57; 128k 848 -> 865,
+//     810 -> 726, 561 -> 69; 128 rows, 64k 461 -> 446, 429 -> 351, 335 -> 49; 128k 910 -> 922, 863 -> 712, 686 -> 67; 64 rows,
+//     59k 378 -> 292, 366 -> 234, 251 -> 41; 128k 797 -> 584, 765 -> 469, 523 -> 56.  The two-launch kernel's time goes with the
+//     lengths: 256 rows, 59k 648 -> 597, 574 -> 502, 196 -> 63; 75k 902 -> 954, 716 -> 761; 512 rows, 47k 854 -> 870 (8 x 4
+//     layers 3078 -> 3356), 798 -> 636; 51k 936 -> 936, 876 -> 750; 64k 1108 -> 1037, 1057 -> 832; 75k 1363 -> 1632, 1240 -> 1256;
+//     100k 1754 -> 1968, 1619 -> 1586: there only where two units fill four fifths of a round and more.
+//     (Sequences that fill less than a tenth of a short buffer: 8 of 600 keys in 16k, 64 rows, one layer 25.5 -> 29.8, 32 layers
+//     191 -> 207; of 4000 keys 604 -> 569.)
 constexpr int kLagMinRows = 33;
 constexpr int kLagMinItems = 1280;      // per layer, at 64 rows and less
 constexpr int kLagMinItemsLong = 768;   // ... of units of more than 64 items
 static bool lag_parts_ok(int64_t parts, int groups, int R, bool ragged) {
-  if (parts <= 88) return true;
-  if (parts == 128 && !ragged) return true;
-  if (parts == kStreamGrid && !ragged) return groups == 1 || (groups == 2 && R > 112);
-  return groups == 1 && (parts <= 102 || (parts > 125 && parts <= 176));
+  if (ragged && parts > 88) return groups <= 2 ? parts <= kStreamGrid : parts >= 102 && parts <= kStreamGrid / 2;
+  if (parts == 128) return true;
+  if (parts == kStreamGrid) return groups == 1 || (groups == 2 && R > 112);
+  return lag_unit_straddles(parts, groups);
 }
 struct LagPlan {
   int parts, groups, layers;
@@ -318,7 +324,16 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
   const int64_t parts = (d.N + kLagKeys - 1) / kLagKeys;
   if (groups == 1 && parts * plan.BH < (parts > 64 ? kLagMinItemsLong : kLagMinItems)) return p;
   if (!lag_parts_ok(parts, groups, plan.R, ragged)) return p;
-  const int64_t by_items = (int64_t)kLagItems * kStreamGrid / (parts * plan.BH), by_units = kStreamUnits / d.B;
+  // Rounds of a launch: a sequence's units one after the other or, where none may lie in two rounds, one or two to a round,
+  // whichever of the lengths up to N takes the most; and a round that is begun.
+  int64_t room = (int64_t)kLagItems * kStreamGrid, places = parts * d.Hkv;
+  for (int64_t p = 1; ragged && p <= parts; ++p) {
+    if (lag_unit_straddles(p, groups)) continue;
+    places = std::max<int64_t>(places, (p > kStreamGrid / 2 ? d.Hkv : (d.Hkv + 1) / 2) * kStreamGrid);
+    room = (int64_t)(kLagItems - 1) * kStreamGrid + 1;
+  }
+  const int64_t by_items = room / (places * d.B);
+  const int64_t by_units = kStreamUnits / d.B;
   int64_t nl = by_items < by_units ? by_items : by_units;
   if (nl > kResidentMaxLayers) nl = kResidentMaxLayers;
   if (nl < 1) return p;

@@ -126,6 +126,11 @@ hipError_t launch_score_stream(const StreamArgs& a, bool clear_err, hipStream_t 
 // ---- one-pass scoring, probabilities waiting on the chip for two steps of 64 rows, over many layers (pkv_lag.hip) ----
 constexpr int kLagItems = 255;      // items of a workgroup per launch, at most (table in LDS)
 constexpr int kLagKeys = 512;       // keys of an item
+// Whether a unit of that many items may lie in two rounds of the workgroups, 256 items each, without the workgroups waiting for
+// each other in a ring: not where its ends, a round apart, wait for what lies between (measured beside the host's rule).
+__host__ __device__ constexpr bool lag_unit_straddles(int64_t parts, int groups) {
+  return parts <= 88 || (groups == 1 && (parts <= 102 || (parts > 125 && parts <= 176)));
+}
 constexpr int kLagGroupBytes = 2048;   // of the workspace, per unit and group of 64 query rows
 constexpr int kLagGroupBytes4 = 512;   // ... and of the last words for large sums, where there is room
 

@@ -309,19 +309,21 @@ def _shape(B, Hq, Hkv, d, N, alpha, flags=0):
                  q_st=d, kv_sb=Hkv * N * d, kv_sh=N * d, kv_st=d, o_sb=Hkv * alpha * d, o_sh=alpha * d, o_st=d)
 
 
-def test_long_buffers_with_sequence_lengths_are_not_judged_by_their_own_length():
+def test_long_buffers_with_sequence_lengths():
     # one pass over K at 33 rows and more pays at up to 88 items of 512 keys per head, and where the heads' items deal out evenly
-    # over 256 workgroups; with sequence lengths the host does not know a head's items, only that there are no more than N has
-    for Hq, alpha in ((32, 24), (32, 32), (64, 32), (64, 64)):
-        for N in (20000, 45056):
+    # over 256 workgroups; with sequence lengths the host does not know a head's items, only that there are no more than N has,
+    # and the kernel deals long heads apart: up to 256 items at 128 rows and less, up to 128 beyond
+    for Hq, alpha in ((32, 16), (32, 24), (32, 32), (64, 32), (64, 64)):
+        for N in (20000, 45056, 52224, 60000, 65536):
             assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, N, alpha), seq_lens=True) == 1
         assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, 65536, alpha)) == 1
-        for N in (45057, 60000, 65536, 131072):
-            assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, N, alpha), seq_lens=True) == 2
-    for N in (40000, 52224, 65536, 90112):
-        assert binding.scoring_sweeps(_shape(4, 32, 8, 128, N, 16), seq_lens=True) == 1
-    assert binding.scoring_sweeps(_shape(4, 32, 8, 128, 131072, 16)) == 1
-    assert binding.scoring_sweeps(_shape(4, 32, 8, 128, 131072, 16), seq_lens=True) == 2
+        assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, 60000, alpha)) == 2
+        for N in (65537, 100000, 131072):
+            assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, N, alpha), seq_lens=True) == (1 if Hq // 8 * alpha <= 128 else 2)
+        assert binding.scoring_sweeps(_shape(4, Hq, 8, 128, 131073, alpha), seq_lens=True) == 2
+    # a round of the workgroups for every head at 256 items: 255 of them, less one that is begun
+    assert binding.scoring_sweeps(_shape(31, 32, 8, 128, 131072, 32), seq_lens=True) == 1
+    assert binding.scoring_sweeps(_shape(32, 32, 8, 128, 131072, 32), seq_lens=True) == 2
 
 
 def test_statistics_of_the_scoring_kernels_fit_the_workspace():

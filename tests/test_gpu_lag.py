@@ -91,6 +91,33 @@ def test_ragged_batch_of_one_group(d, B, Hkv, G, alpha, N):
     _check(Q, K, V, alpha + 20, lens)
 
 
+@pytest.mark.parametrize("G,alpha", [(1, 40), (4, 10), (4, 32), (4, 36)])
+@pytest.mark.parametrize("Hkv", [3, 4])
+def test_ragged_batch_of_long_sequences(Hkv, G, alpha):
+    # units that may not lie in two rounds of the workgroups, two of them to a round (an odd one out among three), one to a round,
+    # behind units that may; more layers than a launch has room for
+    N = 131072 if G * alpha <= 128 else 65536
+    lens = np.array([n for n in (45056, 45057, 7, 52224, 52225, 64513, 65536, 65537, 90113, 0, 600, 131072) if n <= N], dtype=np.int32)
+    B, k, d = len(lens), alpha + 20, 64
+    Q, K, V = _inputs(B, Hkv * G, Hkv, d, N, alpha, seed=G + Hkv)
+    for b, n in enumerate(lens):
+        K[b, :, n:] = float("nan")
+    assert _taken(Q, K, k, seq_lens=True)
+    L = 10
+    outs = binding.compress_layers([Q] * L, [K] * L, [V] * L, [k] * L, synth.POOL_MAX, 7, seq_lens=torch.from_numpy(lens).to(DEV),
+                                   want_scores=True)
+    torch.cuda.synchronize()
+    print("long", Hkv, G, alpha, flush=True)
+    for out in outs[1:]:
+        assert torch.equal(out[3], outs[0][3])
+        for b, n in enumerate(lens):
+            if n > k:
+                assert torch.equal(out[4][b, :, :n - alpha], outs[0][4][b, :, :n - alpha])
+                assert torch.equal(out[2][b], outs[0][2][b])
+    some = [b for b in range(B) if lens[b] in (45057, 7, 65536, 90113)]
+    compare_layer(Q[some], K[some], V[some], k, alpha, synth.POOL_MAX, 7, lens[some], tuple(x[some] for x in outs[0]))
+
+
 @pytest.mark.parametrize("G,alpha", [(2, 32), (4, 32), (8, 24), (8, 64)])
 @pytest.mark.parametrize("first,top", [(-70, 75), (-20, 50), (-5, 75), (-30, 90), (-60, 20)])
 def test_normalisers_far_above_the_references(G, alpha, first, top):

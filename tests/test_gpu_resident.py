@@ -41,7 +41,7 @@ def test_ragged_batch():
     _check(spread_queries(Q), K, V, 50, lens)
 
 
-@pytest.mark.parametrize("G,alpha,N,ragged", [(4, 32, 60000, False), (3, 32, 131072, False), (4, 32, 65536, True)])
+@pytest.mark.parametrize("G,alpha,N,ragged", [(4, 32, 60000, False), (3, 32, 131072, False), (4, 32, 140000, True)])
 def test_lengths_that_the_one_pass_kernel_leaves(G, alpha, N, ragged):
     Q, K, V = _inputs(1, 2 * G, 2, 128, N, alpha, seed=N)
     _check(Q, K, V, alpha + 60, np.array([N - 3000], dtype=np.int32) if ragged else None)
