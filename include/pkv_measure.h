@@ -62,7 +62,9 @@ typedef enum {
   PKV_KERNEL_SCORE_STREAM = 6,   /* one pass over K, few query rows          */
   PKV_KERNEL_SCORE_SWEEP = 7,    /* streaming sweeps over K, many query rows or
                                     supplied denominators                    */
-  PKV_KERNEL_SCORE_LAG = 8       /* one pass over K, 64 query rows at a time */
+  PKV_KERNEL_SCORE_LAG = 8,      /* one pass over K, 64 query rows at a time */
+  PKV_KERNEL_SCORE_SIFT = 9      /* estimated scores of all keys, exact ones of
+                                    those that can be kept                   */
 } pkv_kernel_id;
 
 int pkv_compress_layers_profiled(

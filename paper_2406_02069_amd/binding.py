@@ -421,7 +421,7 @@ def probe_read(buf: torch.Tensor, sink: torch.Tensor) -> None:
 
 
 KERNEL_NAMES = ["score_stats", "score_finalize", "score_accum", "pool_select", "gather", "score_resident", "score_stream",
-                "score_sweep", "score_lag"]
+                "score_sweep", "score_lag", "score_sift"]
 
 
 def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False, seq_lens: bool = False):

@@ -313,7 +313,7 @@ struct LagPlan {
   bool words4;
   size_t unit_bytes() const { return (size_t)groups * (kLagGroupBytes + (words4 ? kLagGroupBytes4 : 0)); }
 };
-static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged) {
+static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged, bool dealt = false) {
   LagPlan p = {0, 0, 0, false};
   if (lse_mode || plan.R < kLagMinRows || plan.R > kResidentMaxRows || !plan.resident_ok) return p;
   if (d.flags & (PKV_FLAG_STREAM_SCORING | PKV_FLAG_COUNTER_EXCHANGE)) return p;
@@ -327,7 +327,7 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
   // Rounds of a launch: a sequence's units one after the other or, where none may lie in two rounds, one or two to a round,
   // whichever of the lengths up to N takes the most; and a round that is begun.
   int64_t room = (int64_t)kLagItems * kStreamGrid, places = parts * d.Hkv;
-  for (int64_t p = 1; ragged && p <= parts; ++p) {
+  for (int64_t p = ragged ? 1 : parts; (ragged || dealt) && p <= parts; ++p) {
     if (lag_unit_straddles(p, groups)) continue;
     places = std::max<int64_t>(places, (p > kStreamGrid / 2 ? d.Hkv : (d.Hkv + 1) / 2) * kStreamGrid);
     room = (int64_t)(kLagItems - 1) * kStreamGrid + 1;
@@ -341,6 +341,29 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
   p.groups = groups;
   p.layers = (int)nl;
   return p;
+}
+
+// How the sifting kernels serve a call whose shape the lagging kernel takes: padded rows (0: they do not).  The two give the
+// same kept sets to the bit (the scores that decide them are the same to the bit), so that here the number of layers may count.
+// Where the lines lie, whole calls, before -> with these kernels, us: five launches instead of two cost about 100 us where
+//   keys are few, and a key costs less by a quarter at 128 rows and a fifth at 512.  32 layers of 8 heads x 32k keys, 128 rows
+//   674 -> 604; x 128k 3360 -> 2080; 80 layers x 32k, 512 rows 4400 -> 3750; 2.1 million keys, 128 rows, 159 -> 173.
+//   Uncorrelated queries (32 layers x 32k, 128 rows), whose layers are all handed on: 665 -> 705.
+// The statistics, lists and jobs lie where the pooled scores lie later on, behind the words of the lagging kernel.
+constexpr int kSiftMinRows = 65;     // (64 rows: K's read binds either way)
+constexpr int kSiftMinLen = 16384;
+constexpr int64_t kSiftMinTotal = 6 << 20;  // keys of a call
+struct SiftPlan {
+  int Rs;
+  // the other kernel's words, sums, jobs, list, estimates, count of jobs
+  size_t unit_bytes(const LagPlan& gp, int N) const { return gp.unit_bytes() + (size_t)Rs * 12 + sift_list(N) / kSiftJob * 16 + sift_list(N) * 4 + 4; }
+};
+static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, const LagPlan& gp, int scoring_layers) {
+  SiftPlan p = {0};
+  if (gp.layers == 0 || d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return p;
+  if ((int64_t)scoring_layers * plan.BH * d.N < kSiftMinTotal) return p;
+  const SiftPlan q = {(plan.R + 63) / 64 * 64};
+  return q.unit_bytes(gp, d.N) <= (size_t)d.N * 4 - 4 ? q : p;
 }
 
 // Queue the kernels of L layers.  All arguments have been validated.
@@ -405,6 +428,76 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   } else if (gp.layers > 0) {
     // (layers that are kept whole take no part)
     bool first = true;
+    unsigned long long* const words = reinterpret_cast<unsigned long long*>(pooled_ws);
+    const size_t unit_words = (size_t)gp.groups * (kLagGroupBytes / 8), unit_words4 = (size_t)gp.groups * (kLagGroupBytes4 / 8);
+    const uint32_t alpha_magic = (65536u + (uint32_t)d.alpha - 1) / (uint32_t)d.alpha;
+    int32_t scoring = 0, unscored = 0;  // layers that take part; those of them without scores_out
+    for (int32_t l = 0; l < L; ++l) {
+      if (descs[l].k_l >= d.N) continue;
+      ++scoring;
+      unscored += ptrs[l].scores_out ? 0 : 1;
+    }
+    const SiftPlan may = sift_plan(plan, d, gp, scoring), fp = unscored > 0 ? may : SiftPlan{0};
+    unsigned long long* const words4 = words + scoring * plan.BH * unit_words;
+    int32_t* const flags = reinterpret_cast<int32_t*>(ws + plan.off_cnt) + 2;
+    if (fp.Rs > 0) {
+      // (parts of 16 bytes first, then of 8 and of 4)
+      const size_t units = (size_t)scoring * plan.BH;
+      unsigned long long* const zsum = words4 + (gp.words4 ? units * unit_words4 : 0);
+      int4* const jobs = reinterpret_cast<int4*>(zsum + units * fp.Rs);
+      uint32_t* const list = reinterpret_cast<uint32_t*>(jobs + units * (sift_list(d.N) / kSiftJob));
+      float* const omega = reinterpret_cast<float*>(list + units * sift_list(d.N));
+      int32_t* const done_jobs = reinterpret_cast<int32_t*>(omega + units * fp.Rs);
+      int32_t done = 0;
+      for (int32_t l = 0; l < L;) {
+        SiftArgs fa;
+        memset(&fa, 0, sizeof(fa));
+        const int32_t l0 = l;
+        for (; l < L && fa.L < kResidentMaxLayers; ++l) {
+          if (descs[l].k_l >= d.N) continue;
+          fa.layer[fa.L].Q = static_cast<const uint16_t*>(ptrs[l].Q);
+          fa.layer[fa.L].K = static_cast<const uint16_t*>(ptrs[l].K);
+          fa.layer[fa.L].k_l = descs[l].k_l;
+          if (ptrs[l].scores_out) fa.scored[fa.L >> 5] |= 1u << (fa.L & 31);
+          fa.layer[fa.L++].slot = l - l0;
+        }
+        if (fa.L == 0) break;
+        fa.seq_lens = seq_lens;
+        fa.raw = raw + (size_t)l0 * plan.BH * d.N;
+        fa.flags = flags + (size_t)l0 * plan.BH;
+        const size_t u0 = (size_t)done * plan.BH;
+        fa.words = words + u0 * unit_words;
+        if (gp.words4) fa.words4 = words4 + u0 * unit_words4;
+        fa.zsum = zsum + u0 * fp.Rs;
+        fa.omega = omega + u0 * fp.Rs;
+        fa.jobs = jobs;
+        fa.list = list + u0 * sift_list(d.N);
+        fa.done = done_jobs + u0;
+        fa.njobs = done_jobs + units;
+        fa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
+        fa.B = d.B; fa.Hq = d.Hq; fa.Hkv = d.Hkv; fa.G = plan.G; fa.alpha = d.alpha; fa.N = d.N; fa.R = plan.R; fa.Rs = fp.Rs; fa.d = d.d;
+        const int64_t items = (int64_t)fa.L * plan.BH * gp.parts;
+        fa.grid = items < kSweepGrid ? (int32_t)items : kSweepGrid;
+        fa.groups = gp.groups;
+        fa.pool = (d.pool_w == 1) ? PKV_POOL_NONE : d.pool;
+        fa.pool_w = d.pool_w;
+        fa.zbufs = sift_zbufs(fp.Rs);
+        fa.sample_tiles = fa.pool == PKV_POOL_AVG ? 4 : 2;
+        // (so that the list fits an eighth of the keys: it holds about 4 keys per key to keep, with average pooling 2.5 + w)
+        fa.min_share = fa.pool == PKV_POOL_AVG ? 27 + 11 * d.pool_w : 43;
+        fa.alpha_magic = alpha_magic;
+        fa.q_sb = d.q_sb; fa.q_sh = d.q_sh; fa.q_st = d.q_st;
+        fa.kv_sb = d.kv_sb; fa.kv_sh = d.kv_sh; fa.kv_st = d.kv_st;
+        fa.kappa = kappa;
+        fa.inv_G = 1.0f / (float)plan.G;
+        if (launch_score_sift(fa, first, stream) != hipSuccess) return PKV_ERR_HIP;
+        first = false;
+        if (rec) rec->after(PKV_KERNEL_SCORE_SIFT, stream);
+        done += fa.L;
+      }
+      gp = lag_plan(plan, d, lse_mode, seq_lens != nullptr, true);
+    }
+    int32_t done = 0;
     for (int32_t l = 0; l < L;) {
       LagArgs ga;
       memset(&ga, 0, sizeof(ga));
@@ -419,14 +512,15 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       if (ga.L == 0) break;
       ga.seq_lens = seq_lens;
       ga.raw = raw + (size_t)l0 * plan.BH * d.N;
-      ga.words = reinterpret_cast<unsigned long long*>(pooled_ws);
-      if (gp.words4) ga.words4 = ga.words + (size_t)ga.L * plan.BH * gp.groups * (kLagGroupBytes / 8);
+      ga.words = words + (size_t)done * plan.BH * unit_words;
+      if (gp.words4) ga.words4 = words4 + (size_t)done * plan.BH * unit_words4;
+      if (may.Rs > 0) ga.flags = flags + (size_t)l0 * plan.BH;
       ga.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       ga.B = d.B; ga.Hq = d.Hq; ga.Hkv = d.Hkv; ga.G = plan.G; ga.alpha = d.alpha; ga.N = d.N; ga.R = plan.R; ga.d = d.d;
-      ga.uniform = seq_lens ? 0 : 1;
+      ga.uniform = seq_lens || fp.Rs > 0 ? 0 : 1;
       ga.parts = gp.parts;
       ga.groups = gp.groups;
-      ga.alpha_magic = (65536u + (uint32_t)d.alpha - 1) / (uint32_t)d.alpha;
+      ga.alpha_magic = alpha_magic;
       ga.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;
       ga.hkv_magic = 0xFFFFFFFFu / (uint32_t)d.Hkv;
       const int64_t items = (int64_t)ga.L * plan.BH * gp.parts;
@@ -436,8 +530,9 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       ga.kv_sb = d.kv_sb; ga.kv_sh = d.kv_sh; ga.kv_st = d.kv_st;
       ga.kappa = kappa;
       ga.inv_G = 1.0f / (float)plan.G;
-      if (launch_score_lag(ga, first, stream) != hipSuccess) return PKV_ERR_HIP;
+      if (launch_score_lag(ga, first, fp.Rs > 0, stream) != hipSuccess) return PKV_ERR_HIP;
       first = false;
+      done += ga.L;
       if (rec) rec->after(PKV_KERNEL_SCORE_LAG, stream);
     }
   } else if (sp.layers > 0) {
@@ -982,6 +1077,10 @@ int pkv_attention_recall(int32_t L, const pkv_layer_desc* descs, int32_t lse_sup
   const bool resident = use_resident(plan, lse_supplied != 0, d.flags);
   const int nrb = resident ? 1 : plan.nrb;
   const float* raw = reinterpret_cast<const float*>(static_cast<const char*>(workspace) + plan.off_raw);
+  int32_t scoring = 0;
+  for (int32_t l = 0; l < L; ++l) scoring += descs[l].k_l < d.N ? 1 : 0;
+  const bool sifted = resident && sift_plan(plan, d, lag_plan(plan, d, lse_supplied != 0, seq_lens != nullptr), scoring).Rs > 0;
+  const int32_t* flags = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + plan.off_cnt) + 2;
   for (int32_t l0 = 0; l0 < L; l0 += kBatchMaxLayers) {
     const int32_t nl = L - l0 < kBatchMaxLayers ? L - l0 : kBatchMaxLayers;
     RecallArgs ra;
@@ -993,6 +1092,7 @@ int pkv_attention_recall(int32_t L, const pkv_layer_desc* descs, int32_t lse_sup
       ra.layer[i].k_cap = descs[l0 + i].k_l < d.N ? descs[l0 + i].k_l : d.N;
     }
     ra.raw = raw + (size_t)l0 * nrb * plan.BH * d.N;
+    ra.flags = sifted ? flags + (size_t)l0 * plan.BH : nullptr;
     ra.seq_lens = seq_lens;
     ra.B = d.B; ra.Hkv = d.Hkv; ra.N = d.N; ra.alpha = d.alpha; ra.nrb = nrb;
     ra.inv_G = resident ? 1.0f : 1.0f / (float)plan.G;

@@ -134,9 +134,13 @@ __host__ __device__ constexpr bool lag_unit_straddles(int64_t parts, int groups)
 constexpr int kLagGroupBytes = 2048;   // of the workspace, per unit and group of 64 query rows
 constexpr int kLagGroupBytes4 = 512;   // ... and of the last words for large sums, where there is room
 
+constexpr int kLagRefs = 24, kLagMax = 28;  // places of the references and of the maxima in a block of 32 words (8 rows)
+__device__ __forceinline__ uint32_t lag_half_word(int which, int row) { return (uint32_t)(2 * which + (row >> 3) * 64 + (row & 7)); }
+
 struct LagArgs {
   ResidentLayer layer[kResidentMaxLayers];
   const int32_t* seq_lens;
+  int32_t* flags;             // [layer slot][B][Hkv] of the sifting kernels: only what they have not scored, or null: all
   float* raw;                 // [layer slot][B][Hkv][N] un-pooled scores
   unsigned long long* words;  // [units][groups][256] sums, references, maxima; cleared by the first of the two kernels
   unsigned long long* words4; // [units][groups][64] last words for large sums, or null; likewise
@@ -152,7 +156,78 @@ struct LagArgs {
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;
 };
-hipError_t launch_score_lag(const LagArgs& a, bool clear_err, hipStream_t s);
+// prepared: the references and words are there
+hipError_t launch_score_lag(const LagArgs& a, bool clear_err, bool prepared, hipStream_t s);
+
+// ---- estimated scores of all keys, exact ones of those that can be kept, over many layers (pkv_sift.hip) ----
+constexpr int kSiftMaxKeys = 131072;  // of a prefix
+constexpr int kSiftJob = 256;         // keys scored exactly by a workgroup
+// ... of a unit, at most: an eighth of its keys
+__host__ __device__ constexpr int sift_list(int N) { return N / 8 / kSiftJob * kSiftJob; }
+constexpr int kSiftMinKeys = 4096;    // of a prefix
+// Estimates are no use where more than 12 of 256 sampled keys lie between half the cut's estimate and the cut.
+constexpr float kSiftNear = 0.5f;
+constexpr int kSiftMaxNear = 12;
+// The guess of tau: the estimate that kSiftRank times the groups that the kept keys are thought to fill reach, times what the mean
+// ratio of weight to estimate is below the largest, times kSiftSlack (0.95 and 1: one head in a hundred fails the check).
+constexpr float kSiftSlack = 0.9f, kSiftRank = 1.2f;
+constexpr int kSiftMaxPoolW = 17;
+
+// (two where they fit the LDS beside the queries)
+__host__ __device__ constexpr int sift_zbufs(int Rs) { return Rs <= 384 ? 2 : 1; }
+
+struct SiftArgs {
+  ResidentLayer layer[kResidentMaxLayers];
+  const int32_t* seq_lens;
+  float* raw;                 // [layer slot][B][Hkv][N] scores
+  float* omega;               // [units][Rs] estimated weights of the rows: 1 / (G z)
+  unsigned long long* zsum;   // [units][Rs] their sums, as the other kernel's words hold them (bit 63: one that does not fit)
+  int32_t* flags;             // [layer slot][B][Hkv] bit 0: not worth it; bit 1: not scored exactly
+  int32_t* done;              // [units] jobs done
+  uint32_t* list;             // [units][sift_list(N)] positions of keys that can be kept, ascending
+  int4* jobs;                 // [units * sift_list(N) / kSiftJob] unit, part of its list, keys listed, bound
+  int32_t* njobs;
+  unsigned long long *words, *words4;  // of the kernel that takes the rest, prepared by the way
+  int32_t* err;
+  uint32_t scored[(kResidentMaxLayers + 31) / 32];  // layers whose scores are asked for: left to that kernel
+  int32_t L, B, Hq, Hkv, G, alpha, N, R, Rs, d;     // Rs: rows padded to 64
+  int32_t grid, groups;       // workgroups of the pass over K; groups of 64 rows
+  int32_t zbufs;              // tables of sums by wave, used in turn
+  int32_t pool, pool_w;
+  int32_t sample_tiles;       // of 32 keys, per wave (8 waves; even)
+  int32_t min_share;          // keys of a prefix per key to keep, at least
+  uint32_t alpha_magic;       // as LagArgs
+  int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
+  float kappa, inv_G;
+};
+hipError_t launch_score_sift(const SiftArgs& a, bool clear_err, hipStream_t s);
+// Whether the heads' flags of a (layer, sequence) have it sifted: a quarter of the heads at most object.  And whether its
+// scores are there then.
+__device__ __forceinline__ bool sift_takes(const int32_t* flags, int Hkv) {
+  int bad = 0;
+  for (int g0 = 0; g0 < Hkv; g0 += 8) {
+    int f[8];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) f[g] = flags[g0 + g < Hkv ? g0 + g : 0];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) bad += g0 + g < Hkv ? f[g] & 1 : 0;
+  }
+  return 4 * bad <= Hkv;
+}
+__device__ __forceinline__ bool sift_done(const int32_t* flags, int Hkv) {
+  int bad = 0, failed = 0;
+  for (int g0 = 0; g0 < Hkv; g0 += 8) {
+    int f[8];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) f[g] = flags[g0 + g < Hkv ? g0 + g : 0];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      bad += g0 + g < Hkv ? f[g] & 1 : 0;
+      failed |= f[g] & 2;
+    }
+  }
+  return 4 * bad <= Hkv && failed == 0;
+}
 
 // ---- scoring in two streaming launches for many query rows, over many layers (pkv_sweep.hip) ----
 constexpr int kSweepGrid = 256;     // workgroups, one per compute unit
@@ -162,7 +237,7 @@ struct SweepArgs {
   const int32_t* seq_lens;
   float* raw;                 // [U][N] un-pooled scores
   unsigned long long* stats;  // [U][nchunk][Rs] (reference, sum) of a row over a chunk (log2 domain)
-  int32_t L, B, Hq, Hkv, G, alpha, N, R, Rs, d;  // Rs: rows padded to 32
+  int32_t L, B, Hq, Hkv, G, alpha, N, R, Rs, d;  // Rs: rows padded to 64
   int32_t C, nchunk;          // keys per chunk (a multiple of 512), chunks per unit
   int32_t score_C, score_nchunk;  // the split of the launch that writes the scores (a multiple of 64 keys per wave)
   int32_t score_waves;        // 8 or 16 per workgroup
@@ -261,6 +336,8 @@ struct RecallArgs {
   const int32_t* seq_lens;
   int32_t B, Hkv, N, alpha, nrb;
   float inv_G;         // factor applied to the sum of the partials
+  const int32_t* flags;  // [layer][B][Hkv] of the sifting kernels, first layer of this launch: where they scored a sequence,
+                         // the sum over all keys lies behind its scores; or null
 };
 
 // ---- decoding attention over a compacted (possibly paged) cache ----

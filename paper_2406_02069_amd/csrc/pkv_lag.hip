@@ -38,74 +38,17 @@
 #include <type_traits>
 
 #include "pkv_internal.h"
+#include "pkv_tile.h"
 
 namespace pkv {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned long long u64;
-
 constexpr int kW = 8;  // waves per workgroup
 constexpr int kT = kW * 64;
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
-#define PKV_MFMA32(A, B, C) __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, C, 0, 0, 0)
-// A value the compiler must treat as new: lane constants derived from it are recomputed where they are used instead of
-// being kept (and spilled) across the whole item loop.
-__device__ __forceinline__ int fresh(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 __device__ __forceinline__ u64 ld64(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ uint32_t ld32(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void add64(u64* p, u64 v) { (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <bool MAX>
-__device__ __forceinline__ float both_halves(float x) {
-  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
-  const float p = __uint_as_float(r[0]), q = __uint_as_float(r[1]);
-  return MAX ? fmaxf(p, q) : p + q;
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-__device__ __forceinline__ constexpr int mrow0(int v) { return 8 * (v >> 2) + (v & 3); }
-
-// Sums of 16 registers over the 32 lanes of a wave half: the sum of register 8 b4 + 4 b3 + 2 b2 + b1 arrives in the lanes
-// whose number has these bits.
-__device__ __forceinline__ float transpose_sum(const f32x16& t, int lane) {
-  float u[8];
-#pragma unroll
-  for (int v = 0; v < 8; ++v) {
-    const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(t[v]), __float_as_uint(t[v + 8]), false, false));
-    u[v] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const float mine = b3 ? u[v + 4] : u[v], other = b3 ? u[v] : u[v + 4];
-    u[v] = mine + dpp<0x128>(other);  // row_ror:8
-  }
-#pragma unroll
-  for (int v = 0; v < 2; ++v) {
-    const float mine = b2 ? u[v + 2] : u[v], other = b2 ? u[v] : u[v + 2];
-    u[v] = mine + dpp<0x141>(other);  // row_half_mirror
-  }
-  const float mine = b1 ? u[1] : u[0], other = b1 ? u[0] : u[1];
-  const float s = mine + dpp<0x4E>(other);  // quad_perm 2,3,0,1
-  return s + dpp<0xB1>(s);                  // quad_perm 1,0,3,2
-}
-
 // Words of a unit in the workspace, 256 bytes for eight rows: their sums, two further words each for large sums, references
 // (floats) and exact maxima (ordered integers).  (An exchange among 128 workgroups takes 2.3 us with eight rows' sums to 256
 // bytes and 4.3 us with the sums in one piece: the adds to a memory channel come one after the other.)  A third word for large
@@ -120,19 +63,13 @@ __device__ __forceinline__ float transpose_sum(const f32x16& t, int lane) {
 // (One key alone adds 1 to a row's sum, so half a unit of each of 256 items is at most 2^-23 of it: as much as two roundings of
 // a float.  In units of 2^-24 the sums of items far below the reference were lost: 64 items of 2^-26 each 9.5e-7 of the
 // normaliser, 256 items 3.8e-6.)
-constexpr int kSums = 0, kSums2 = 8, kSums3 = 16, kRefs = 24, kMax = 28;  // places in a block, in 64-bit words
+constexpr int kSums = 0, kSums2 = 8, kSums3 = 16, kRefs = kLagRefs, kMax = kLagMax;  // places in a block, in 64-bit words
 __device__ __forceinline__ uint32_t word_of(int which, int row) { return (uint32_t)(which + (row >> 3) * 32 + (row & 7)); }
-__device__ __forceinline__ uint32_t half_word_of(int which, int row) { return (uint32_t)(2 * which + (row >> 3) * 64 + (row & 7)); }
+__device__ __forceinline__ uint32_t half_word_of(int which, int row) { return lag_half_word(which, row); }
 constexpr u64 kOne = 1ull << 52, kBad = 1ull << 62, kBig = 1ull << 63;
-constexpr float kUnits = 0x1p30f, kUnits2 = 0x1p11f, kUnits3 = 0x1p-19f, kUnits4 = 0x1p-49f;  // to the 1
-constexpr float kLimit = 0x1p13f, kLimit2 = 0x1p43f, kLimit3 = 0x1p73f, kLimit4 = 0x1p103f;   // of an item's sum (256 fit)
+constexpr float kUnits = kSumUnits, kUnits2 = 0x1p11f, kUnits3 = 0x1p-19f, kUnits4 = 0x1p-49f;  // to the 1
+constexpr float kLimit = kSumLimit, kLimit2 = 0x1p43f, kLimit3 = 0x1p73f, kLimit4 = 0x1p103f;   // of an item's sum (256 fit)
 
-__device__ __forceinline__ u64 fixed_point(float z, float scale) {
-  const float y = rintf(z * scale);
-  const float hi = floorf(y * 0x1p-32f);
-  return (u64)(uint32_t)hi << 32 | (uint32_t)__builtin_fmaf(hi, -0x1p32f, y);
-}
-__device__ __forceinline__ float as_float(u64 w) { return __builtin_fmaf((float)(uint32_t)(w >> 32), 0x1p32f, (float)(uint32_t)w); }
 // An item's sum of a row, at the first and at the second attempt.  What does not fit is marked first, so that whoever finds
 // the item counted sees it.  word4(): the row's last word for large sums, or null.
 template <class F>
@@ -229,7 +166,9 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
       int c = 0;
       if (e < E) {
         const int l = e / a.B, n = length(e - l * a.B), parts = (n + KI - 1) / KI;
-        if (a.layer[l].k_l < n) {  // (whole sequence kept: no scores needed)
+        // (whole sequence kept: no scores needed; or they are there)
+        const int32_t* flags = a.flags ? a.flags + ((size_t)a.layer[l].slot * a.B + (e - l * a.B)) * a.Hkv : nullptr;
+        if (a.layer[l].k_l < n && (!flags || !sift_done(flags, a.Hkv))) {
           if (lag_unit_straddles(parts, MODE)) c = a.Hkv * parts;
           else {
             const int q = kStreamGrid / parts;  // (the host admits no unit of more items than workgroups)
@@ -423,8 +362,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
   // would make the waits for keys that follow allow for either way.)
   auto write_score = [&](const Item& d, int t, float s) {
     const int ln = fresh(lane);
-    const int key = (ln & 24) + 4 * (ln >> 5) + ((ln & 6) >> 1);
-    d.raw[min(tile_key(d, t) + key, d.n - a.alpha)] = s;
+    d.raw[min(tile_key(d, t) + transpose_key(ln), d.n - a.alpha)] = s;
   };
   auto mark = [&](bool bad, int i) {
     if (__builtin_expect(bad, 0) && lane == 0) atomicOr(&s_item[i].x, 0x80000000u);
@@ -787,6 +725,7 @@ __global__ __launch_bounds__(256) void lag_prepare_kernel(const LagArgs a, int c
   u64* words = a.words + (size_t)blockIdx.x * 256;
   if ((tid & 31) < kRefs || (tid & 31) >= kMax) words[tid] = 0;
   if (a.words4 && tid < 64) a.words4[(size_t)blockIdx.x * 64 + tid] = 0;
+  if (a.flags && h == 0 && tid == 0) a.flags[(size_t)a.layer[l].slot * BH + bg] = 1;  // (not sifted)
   int n = a.N;
   if (a.seq_lens) {
     n = a.seq_lens[b];
@@ -817,7 +756,7 @@ __global__ __launch_bounds__(256) void lag_prepare_kernel(const LagArgs a, int c
 }
 
 template <int D, int MODE>
-hipError_t launch_lag(const LagArgs& a, bool clear_err, hipStream_t s) {
+hipError_t launch_lag(const LagArgs& a, bool clear_err, bool prepared, hipStream_t s) {
   using S = LagShape<D>;
   static bool attr_set[kMaxDevices];
   const int dev = current_device_slot();
@@ -828,22 +767,24 @@ hipError_t launch_lag(const LagArgs& a, bool clear_err, hipStream_t s) {
     if (e != hipSuccess) return e;
     attr_set[dev] = true;
   }
-  hipLaunchKernelGGL((lag_prepare_kernel<D>), dim3(a.L * a.B * a.Hkv * a.groups), dim3(256), 0, s, a, clear_err ? 1 : 0);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!prepared) {
+    hipLaunchKernelGGL((lag_prepare_kernel<D>), dim3(a.L * a.B * a.Hkv * a.groups), dim3(256), 0, s, a, clear_err ? 1 : 0);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((score_lag_kernel<D, MODE>), dim3(a.grid), dim3(kT), S::LDS, s, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_score_lag(const LagArgs& a, bool clear_err, hipStream_t s) {
+hipError_t launch_score_lag(const LagArgs& a, bool clear_err, bool prepared, hipStream_t s) {
 #define PKV_CASE(DD)                                                   \
   if (a.d == DD) {                                                     \
-    if (a.groups == 1) return launch_lag<DD, 1>(a, clear_err, s);      \
-    if (a.groups == 2) return launch_lag<DD, 2>(a, clear_err, s);      \
-    if (a.groups % 2 == 0) return launch_lag<DD, 4>(a, clear_err, s);  \
-    return launch_lag<DD, 3>(a, clear_err, s);                         \
+    if (a.groups == 1) return launch_lag<DD, 1>(a, clear_err, prepared, s);      \
+    if (a.groups == 2) return launch_lag<DD, 2>(a, clear_err, prepared, s);      \
+    if (a.groups % 2 == 0) return launch_lag<DD, 4>(a, clear_err, prepared, s);  \
+    return launch_lag<DD, 3>(a, clear_err, prepared, s);                         \
   }
   PKV_CASE(128) PKV_CASE(64)
 #undef PKV_CASE

@@ -1,0 +1,937 @@
+// Window scoring for more than 64 query rows per KV head where only the kept set is asked for (Sec. 4.2.2, Eq. Al, Eq. att_score
+// and the top-k behind it) on MI355X: estimated scores of all keys, exact ones of the few that can be kept.
+//
+// A key's score s_i = sum_r w_r p_ri (p: un-normalised probabilities, w_r = 1 / (G z_r)) needs the normalisers z_r, which are known only
+// after all keys of the head have been seen.  The other kernels wait for them, with the keys or the probabilities on the chip, or form
+// everything twice.  Here nothing waits: K streams through once, and with it go the normalisers and the estimates
+// e_i = sum_r o_r p_ri with weights o_r from a sample of the keys.  Behind it the largest ratio rho = max_r w_r / o_r is known,
+// and s_i <= rho e_i for every key.  So the keys (with pooling: the windows) with e_i >= tau are listed and scored exactly, and
+// where the kept number of them reaches rho tau, no other key can be among the kept: the estimates of the others stay where they
+// are, all below, and the selection finds the kept set among all of them.  tau is a guess (from the largest estimates, less what
+// the weights differ); whether it was low enough is checked, never assumed.
+//
+// Handed on to the lagging one-pass kernel, which scores all keys of a sequence: heads whose estimates are no use (seen in the sample
+// beforehand: the cut lies where keys are many, as with queries that have no common direction), whose sums do not fit, whose list
+// does not fit an eighth of the keys, or that fail the check.  Sums and scores come about exactly as in that kernel (same
+// references, same order of additions), so that the kept sets are the same to the bit whoever scores.
+//
+// Four launches: sift_prepare_kernel (references, weights o_r from 512 or 1024 keys: the median of eight groups' sums, so that a rare
+// large key does not spoil them), score_sift_kernel (the pass over K), sift_list_kernel (a workgroup per head: tau and the list),
+// sift_exact_kernel (256 listed keys at a time, from a common list of jobs; a head's last job makes the check).
+//
+// score_sift_kernel: 256 persistent workgroups of 512 threads, all query rows of a unit in LDS, a wave holds 32 keys as matrix
+// operands and passes over all rows with them, the next two tiles of keys under way; one product's matrix instructions are issued
+// between the exponentials of the one before.  A barrier per 512 keys, for the sums.  Workgroups take stretches of items of equal
+// length; no workgroup waits for another.
+//
+// What bounds it: HBM and the clock the chip holds under this load at 128 rows (32 layers x 8 heads x 32k keys 470 us, 4.6 TB/s, at
+// 2.0 GHz; the lagging kernel 620), vector instructions at 512 rows (80 layers 3.39 ms at 1.8 GHz; 4.3).  A launch begins with
+// 12 us until the first product.
+#include <type_traits>
+
+#include "pkv_internal.h"
+#include "pkv_select_parts.h"
+#include "pkv_tile.h"
+
+namespace pkv {
+namespace {
+
+constexpr int kW = 8, kT = kW * 64;   // waves and threads of the kernel that reads K
+constexpr int kPass = 32 * kW;        // keys of a pass
+constexpr u64 kZBad = 1ull << 63;     // an item's sum does not fit
+constexpr int kBlockRows = 128, kBlockTiles = kBlockRows / 32;  // query rows that lie in LDS at a time where keys are scored exactly
+constexpr int kSiftExactGrid = 512;
+
+// A unit's place: layer entry, sequence, head, valid length.
+struct Unit {
+  int l, b, g, n;
+};
+__device__ __forceinline__ int valid_length(const SiftArgs& a, int b) {
+  if (!a.seq_lens) return a.N;
+  const int n = a.seq_lens[b];
+  return n < 0 ? 0 : (n > a.N ? a.N : n);
+}
+__device__ __forceinline__ Unit unit_of(const SiftArgs& a, int u) {
+  const int BH = a.B * a.Hkv, l = u / BH, bg = u - l * BH, b = bg / a.Hkv;
+  return {l, b, bg - b * a.Hkv, valid_length(a, b)};
+}
+__device__ __forceinline__ const int32_t* flags_of(const SiftArgs& a, int l, int b) {
+  return a.flags + (size_t)a.layer[l].slot * a.B * a.Hkv + (size_t)b * a.Hkv;
+}
+__device__ __forceinline__ const uint16_t* keys_of(const SiftArgs& a, const Unit& p) {
+  return a.layer[p.l].K + (size_t)p.b * a.kv_sb + (size_t)p.g * a.kv_sh;
+}
+__device__ __forceinline__ const uint16_t* queries_of(const SiftArgs& a, const Unit& p) {
+  return a.layer[p.l].Q + (size_t)p.b * a.q_sb + (size_t)(p.g * a.G) * a.q_sh;
+}
+// Row r of 32 as matrix operand, from memory: lane (l32, hf) holds elements 16 ks + 8 hf of its row.
+template <int KS>
+__device__ __forceinline__ void load_rows(bf16x8 (&f)[KS], const uint16_t* row, int hf) {
+  const char* p = reinterpret_cast<const char*>(row) + 16 * hf;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) f[ks] = as_frag(*reinterpret_cast<const u32x4*>(p + 32 * ks));
+}
+
+// Queries of ROWS rows in LDS: rows of D / 8 + 1 sixteen-byte slots (bank-free).
+template <int D, int ROWS>
+struct QueryBlock {
+  static constexpr int SEG = D / 8, PITCH = SEG + 1, PER = ROWS * SEG / kT, SLOTS = ROWS * PITCH;
+  u32x4 v[PER];
+  template <class Row>
+  __device__ __forceinline__ void request(int row0, Row row) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int j = (int)threadIdx.x + i * kT;
+      v[i] = *reinterpret_cast<const u32x4*>(row(row0 + j / SEG) + 8 * (j % SEG));
+    }
+  }
+  __device__ __forceinline__ void commit(u32x4* s_q) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int j = (int)threadIdx.x + i * kT;
+      s_q[j / SEG * PITCH + j % SEG] = v[i];
+    }
+  }
+};
+__device__ __forceinline__ const uint16_t* query_row_of(const SiftArgs& a, const uint16_t* Q, int row) {  // (rows behind the last repeat it)
+  row = min(row, a.R - 1);
+  const int hh = (int)(__umul24(row, a.alpha_magic) >> 16);
+  return Q + (uint32_t)(hh * (int)a.q_sh + (row - hh * a.alpha) * (int)a.q_st);
+}
+// Logits of 32 keys (rows) and the 32 queries from `row` on of such a block.
+template <int KS>
+__device__ __forceinline__ f32x16 product(const bf16x8 (&k)[KS], const u32x4* s_q, int row, int hf) {
+  const u32x4* q = s_q + row * (2 * KS + 1) + hf;
+  f32x16 x = {};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) x = PKV_MFMA32(k[ks], as_frag(q[2 * ks]), x);
+  __builtin_amdgcn_sched_barrier(0);  // (one product's operands at a time)
+  return x;
+}
+
+// ---- estimates of the normalisers of 64 rows of a unit; with its first rows, whether it is worth it ----
+template <int D>
+__global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, int clear_err) {
+  constexpr int KS = D / 16;
+  using QB = QueryBlock<D, 64>;
+  __shared__ u32x4 s_q[QB::SLOTS];
+  __shared__ float s_m[64], s_x0[64], s_o[64], s_part[kW][64], s_win[2][64], s_score[32 * kW];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int u = blockIdx.x / a.groups, row0 = 64 * (blockIdx.x - u * a.groups);
+  if (blockIdx.x == 0 && tid == 0) {
+    if (clear_err) a.err[0] = a.err[1] = 0;
+    *a.njobs = 0;
+  }
+  const Unit p = unit_of(a, u);
+  const bool whole = a.layer[p.l].k_l >= p.n;
+  const int npre = whole ? 1 : p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
+  const uint16_t* Q = queries_of(a, p);
+  const uint16_t* K = keys_of(a, p);
+  const int half = wave & 1, rt = (wave >> 1) & 1;  // of the reference and window keys: the tile; of the rows
+  bf16x8 kf[2][KS], kx[KS];
+  QB qb;
+  // The sample: wave w's group of keys is spread evenly over the prefix in runs of eight neighbours, four to a tile.
+  auto sample = [&](int tile, bf16x8 (&f)[KS]) {
+    const uint32_t run = (uint32_t)((4 * tile + (l32 >> 3)) * kW + wave), runs = (uint32_t)(4 * a.sample_tiles * kW);
+    load_rows(f, K + (size_t)min((int)((u64)(uint32_t)npre * run / runs) + (l32 & 7), npre - 1) * a.kv_st, hf);
+  };
+  if (!whole) {
+    qb.request(row0, [&](int row) { return query_row_of(a, Q, row); });
+    // references: the largest logit of 64 keys, eight neighbours each at eight places, key 0 among them
+    if (wave < 4) load_rows(kx, K + (size_t)min((int)((uint32_t)npre * (uint32_t)(4 * half + (l32 >> 3)) >> 3) + (l32 & 7), npre - 1) * a.kv_st, hf);
+    else load_rows(kx, K + (size_t)min(npre + 32 * half + l32, p.n - 1) * a.kv_st, hf);  // window keys
+    sample(0, kf[0]);
+    sample(1, kf[1]);
+  }
+  // the words of the kernel that takes the other sequences
+  u64* words = a.words + (size_t)blockIdx.x * (kLagGroupBytes / 8);
+  if (tid < kLagGroupBytes / 8 && ((tid & 31) < kLagRefs || (tid & 31) >= kLagMax)) words[tid] = 0;
+  if (a.words4 && tid < kLagGroupBytes4 / 8) a.words4[(size_t)blockIdx.x * (kLagGroupBytes4 / 8) + tid] = 0;
+  int32_t* flag = a.flags + (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
+  if (row0 == 0 && tid == 0) a.done[u] = 0;
+  if (whole) {
+    if (row0 == 0 && tid == 0) *flag = 0;
+    return;
+  }
+  qb.commit(s_q);
+  __syncthreads();
+  f32x16 xw;  // logits of the wave's reference or window keys
+  {
+    xw = product(kx, s_q, 32 * rt + l32, hf);
+    if (wave < 4) {
+      float m = xw[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) m = fmaxf(m, xw[v]);
+      m = both_halves<true>(m) * a.kappa;
+      if (hf == 0) {
+        s_part[half][32 * rt + l32] = m;
+        if (half == 0) s_x0[32 * rt + l32] = xw[0] * a.kappa;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const float m = fmaxf(s_part[0][tid], s_part[1][tid]);
+    s_m[tid] = m;
+    reinterpret_cast<float*>(words)[lag_half_word(kLagRefs, tid)] = m;
+  }
+  __syncthreads();
+  if (wave >= 4) {
+    const int lim = min(row0 + 32 * rt + l32, a.R - 1) % a.alpha - 32 * half - 4 * hf;  // last window key the lane's query sees
+    const float nm = -s_m[32 * rt + l32];
+    float y = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) y += mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(xw[v], a.kappa, nm));
+    y = both_halves<false>(y);
+    if (hf == 0) s_win[half][32 * rt + l32] = y;
+  }
+  float z[2] = {0.f, 0.f};
+#pragma unroll 1
+  for (int tile = 0; tile < a.sample_tiles; tile += 2) {
+    if (tile > 0) {
+      sample(tile, kf[0]);
+      sample(tile + 1, kf[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float nm = -s_m[32 * q + l32];
+      float z0 = 0.f, z1 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const f32x16 x = product(kf[i], s_q, 32 * q + l32, hf);
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          z0 += fast_exp2(__builtin_fmaf(x[v], a.kappa, nm));
+          z1 += fast_exp2(__builtin_fmaf(x[v + 1], a.kappa, nm));
+        }
+      }
+      z[q] += z0 + z1;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float y = both_halves<false>(z[q]);
+    if (hf == 0) s_part[wave][32 * q + l32] = y;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    // half the sum of the two middle ones of the groups: a rare large key does not count
+    float v[kW], mid = 0.f;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) v[w] = s_part[w][tid];
+#pragma unroll
+    for (int w = 0; w < kW; ++w) {
+      int rank = 0;
+#pragma unroll
+      for (int x = 0; x < kW; ++x) rank += (v[x] < v[w] || (v[x] == v[w] && x < w)) ? 1 : 0;
+      if (rank == kW / 2 - 1 || rank == kW / 2) mid += v[w];
+    }
+    const float m = s_m[tid];
+    const float sum = __builtin_fmaf(mid, (float)(npre - 1) / (float)(64 * a.sample_tiles), fast_exp2(s_x0[tid] - m)) + (s_win[0][tid] + s_win[1][tid]);
+    const float o = row0 + tid < a.R ? a.inv_G / sum : 0.f;
+    s_o[tid] = o;
+    a.omega[(size_t)u * a.Rs + row0 + tid] = o;
+    a.zsum[(size_t)u * a.Rs + row0 + tid] = 0;
+  }
+  if (row0 != 0) return;
+  __syncthreads();
+  // estimated scores (of these rows) of a part of the sample
+  f32x16 t = {};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float nm = -s_m[32 * q + l32], o = s_o[32 * q + l32];
+    const f32x16 x = product(kf[0], s_q, 32 * q + l32, hf);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t[v] = __builtin_fmaf(o, fast_exp2(__builtin_fmaf(x[v], a.kappa, nm)), t[v]);
+  }
+  s_score[32 * wave + transpose_key(lane)] = transpose_sum(t, lane);
+  __syncthreads();
+  if (wave == 0) {
+    // the cut's place in it, and how many of its keys lie near the cut or above
+    uint32_t v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = __float_as_uint(s_score[64 * j + lane]);
+    const int at = (int)((int64_t)32 * kW * kk / npre);
+    uint32_t cut = 0x7FFFFFFFu;
+    for (int above = 0; above <= at;) {  // the next smaller score, until enough have been passed (each round passes one at least)
+      uint32_t m = 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) m = max(m, v[j] < cut ? v[j] : 0u);
+      m = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_lane63(m), 63);
+      if (m == 0u) break;
+      cut = m;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) above += __popcll(__ballot(v[j] == cut));
+    }
+    int near = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) near += __popcll(__ballot(__uint_as_float(v[j]) >= __uint_as_float(cut) * kSiftNear));
+    const bool skip = (a.scored[p.l >> 5] >> (p.l & 31) & 1) != 0 || npre < kSiftMinKeys || (int64_t)kk * a.min_share > npre || near > at + kSiftMaxNear;
+    if (lane == 0) *flag = skip ? 1 : 0;
+  }
+}
+
+template <int D>
+constexpr size_t sift_lds(int Rs) {
+  // queries with a row pitch of D / 8 + 1 sixteen-byte slots (bank-free), references and estimates, sums by wave
+  return (size_t)Rs * ((D / 8 + 1) * 16 + 8 + 4 * kW * sift_zbufs(Rs));
+}
+static_assert(sift_lds<128>(kResidentMaxRows) <= 160 * 1024 && sift_lds<128>(384) <= 160 * 1024, "one workgroup per compute unit");
+
+// ---- the pass over K ----
+template <int D>
+__global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
+  constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;
+  constexpr int TPM = 16 / KS;  // logits per lane handled between two matrix instructions
+  extern __shared__ u32x4 smem[];
+  u32x4* s_q = smem;
+  float2* s_r = reinterpret_cast<float2*>(s_q + a.Rs * PITCH);  // [Rs] minus the reference, estimated weight
+  float* s_z = reinterpret_cast<float*>(s_r + a.Rs);            // [zbufs][kW][Rs]
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int nrt = a.Rs / 32;
+
+  // One pass of the workgroup (all fields wave-uniform): its keys from `key` on of unit u.
+  struct Pass {
+    int u, n, key, left;  // left: items of this workgroup behind this one
+    const uint16_t* Q;
+    const uint16_t* K;
+    float* raw;
+  };
+  auto open_unit = [&](Pass& p, bool known) {  // pointers and length of unit p.u; false: the unit is not sifted
+    const Unit x = unit_of(a, p.u);
+    p.n = x.n;
+    p.Q = queries_of(a, x);
+    p.K = keys_of(a, x);
+    p.raw = a.raw + ((size_t)a.layer[x.l].slot * a.B * a.Hkv + (size_t)x.b * a.Hkv + x.g) * a.N;
+    return known || (a.layer[x.l].k_l < x.n && sift_takes(flags_of(a, x.l, x.b), a.Hkv));
+  };
+  Pass cur;
+  {
+    // first item and number of items of this workgroup
+    int* wsum = reinterpret_cast<int*>(smem);  // [kW] sums of the waves, [kW], [kW + 1] the first item's place
+    const int E = a.L * a.B;
+    int lo = 0, hi = 0, u0 = 0, c0 = 0;
+    int c = 0, parts = 0, before = 0;
+    for (int round = 0; round < 2; ++round) {  // how many items there are; then who owns the first one
+      int run = 0;
+      for (int e0 = 0; e0 < E; e0 += kT) {
+        const int e = e0 + tid;
+        if (round == 0 || E > kT) {  // (else the first round's are still there)
+          c = parts = 0;
+          if (e < E) {
+            const int l = e / a.B, b = e - l * a.B, n = valid_length(a, b);
+            parts = a.layer[l].k_l < n && sift_takes(flags_of(a, l, b), a.Hkv) ? (n + kLagKeys - 1) / kLagKeys : 0;
+            c = a.Hkv * parts;
+          }
+          int v = c;
+#pragma unroll
+          for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(v, o);
+            if (lane >= o) v += x;
+          }
+          lds_barrier();
+          if (lane == 63) wsum[wave] = v;
+          lds_barrier();
+          before = run + v - c;
+#pragma unroll
+          for (int w = 0; w < kW; ++w) {
+            before += w < wave ? wsum[w] : 0;
+            run += wsum[w];
+          }
+        }
+        if (round == 1 && lo >= before && lo < before + c) {
+          const int rem = lo - before, g = rem / parts;
+          wsum[kW] = e * a.Hkv + g;
+          wsum[kW + 1] = rem - g * parts;
+        }
+      }
+      if (round == 0) {
+        if (run == 0) return;
+        lo = (int)((int64_t)blockIdx.x * run / gridDim.x);
+        hi = (int)((int64_t)(blockIdx.x + 1) * run / gridDim.x);
+      }
+    }
+    lds_barrier();
+    cur.left = hi - lo;
+    if (cur.left == 0) return;
+    u0 = __builtin_amdgcn_readfirstlane(wsum[kW]);
+    c0 = __builtin_amdgcn_readfirstlane(wsum[kW + 1]);
+    --cur.left;
+    cur.u = u0;
+    cur.key = c0 * kLagKeys;
+    (void)open_unit(cur, true);
+  }
+  // The pass after p; false if there is none (p is then a pass over the unit's first key alone).
+  auto advance = [&](Pass& p) {
+    p.key += kPass;
+    if (p.key % kLagKeys != 0 && p.key < p.n) return true;
+    if (p.left == 0) {
+      p.key = 0;
+      p.n = 1;
+      return false;
+    }
+    --p.left;
+    if (p.key >= p.n) {
+      do ++p.u;
+      while (!open_unit(p, false));  // (there is one: an item is left)
+      p.key = 0;
+    }
+    return true;
+  };
+  // Queries, references and estimates of a unit into LDS.  Barriers around it are the caller's.
+  auto stage = [&](const Pass& p) {
+    const int seg = tid & (SEG - 1);
+    float2 ref = make_float2(0.f, 0.f);
+    if (tid < a.Rs) {
+      ref.x = -reinterpret_cast<const float*>(a.words + (size_t)p.u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)];
+      ref.y = a.omega[(size_t)p.u * a.Rs + tid];
+    }
+    for (int row0 = tid / SEG; row0 < a.Rs; row0 += 4 * (kT / SEG)) {
+      u32x4 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4*>(query_row_of(a, p.Q, row0 + j * (kT / SEG)) + 8 * seg);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = row0 + j * (kT / SEG);
+        if (row < a.Rs) s_q[row * PITCH + seg] = v[j];
+      }
+    }
+    if (tid < a.Rs) s_r[tid] = ref;
+  };
+  // Keys of a wave's tile as matrix operand.  Keys at or beyond n are replaced by the last one.
+  bf16x8 b0[KS], b1[KS], b2[KS];
+  auto issue_k = [&](const Pass& p, bf16x8 (&f)[KS]) {
+    const int ln = fresh(lane);
+    const int key = min(p.key + 32 * wave + (ln & 31), p.n - 1);
+    const char* rowp = reinterpret_cast<const char*>(p.K) + 16 * (ln >> 5) + (uint32_t)key * ((uint32_t)a.kv_st * 2u);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) f[ks] = as_frag(*reinterpret_cast<const u32x4*>(rowp + 32 * ks));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const u32x4* q_lane = s_q + l32 * PITCH + hf;
+  auto q_frag = [&](int rt, int ks) { return as_frag(q_lane[32 * rt * PITCH + 2 * ks]); };
+  float* z_lane = s_z + wave * a.Rs + l32;
+
+  bf16x8 qf[4];
+  f32x16 fin, out;  // products of even and of odd row tiles
+  bool first = true;  // pass of an item
+  int zbuf = 0;       // table in use
+  u64 sum = 0;        // of the thread's row over the unit's items so far
+  auto prime = [&](const bf16x8 (&kc)[KS]) {  // the first product of a pass
+    fin = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fin = PKV_MFMA32(kc[ks], q_frag(0, ks), fin);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) qf[s] = q_frag(1, s);
+  };
+  Pass nxt = cur;
+  bool has_next = advance(nxt);
+  // One pass over the keys in kc; those of the next pass are in kn, those of the one after it are requested into kp.
+  auto pass = [&](bf16x8 (&kc)[KS], bf16x8 (&kn)[KS], bf16x8 (&kp)[KS]) {
+    Pass nx2 = nxt;
+    const bool has_nx2 = has_next && advance(nx2);
+    issue_k(nx2, kp);
+    const int wkey = cur.key + 32 * wave, npre = cur.n - a.alpha;
+    f32x16 t = {};
+    float* zp = z_lane + zbuf * kW * a.Rs;
+    auto add_z = [&](int rt, float z) {  // (the sums of an item come about as in the kernel that scores the other sequences)
+      z = both_halves<false>(z);
+      if (!first) z += zp[32 * rt];
+      if (hf == 0) zp[32 * rt] = z;
+    };
+    if (__builtin_expect(wkey + 32 > npre, 0)) {
+      // the tile reaches into the causal window or beyond the end
+#pragma unroll 1
+      for (int rt = 0; rt < nrt; ++rt) {
+        const float2 ref = s_r[32 * rt + l32];
+        const int lim = npre + (32 * rt + l32) % a.alpha - wkey - 4 * hf;  // last key the lane's query sees
+        float z0 = 0.f, z1 = 0.f;
+        f32x16 x = {};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) x = PKV_MFMA32(kc[ks], q_frag(rt, ks), x);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float y = mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(x[v], a.kappa, ref.x));
+          if (v & 1) z1 += y;
+          else z0 += y;
+          t[v] = __builtin_fmaf(y, ref.y, t[v]);
+        }
+        add_z(rt, z0 + z1);
+      }
+      if (has_next && nxt.u == cur.u) prime(kn);
+    } else {
+      // Product of row tile rt + 1 (LAST: of the next pass's keys and row tile 0) goes into `nx` while `fi`, that of row
+      // tile rt, turns into exponentials.
+      auto step = [&](auto LAST, int rt, const f32x16& fi, f32x16& nx) {
+        constexpr bool last = decltype(LAST)::value;
+        const int mul = last ? 0 : rt + 1, then = last ? 1 : rt + 2 < nrt ? rt + 2 : 0;
+        const float2 ref = s_r[32 * rt + l32];
+        float z0 = 0.f, z1 = 0.f;
+        nx = f32x16{};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          // fragment 3 ahead: of this product, or of the next one
+          if (ks + 3 < KS) qf[(ks + 3) & 3] = q_frag(mul, ks + 3);
+          else qf[(ks + 3) & 3] = q_frag(then, ks + 3 - KS);
+          nx = PKV_MFMA32(last ? kn[ks] : kc[ks], qf[ks & 3], nx);
+          float x[TPM];
+#pragma unroll
+          for (int j = 0; j < TPM; ++j) x[j] = __builtin_fmaf(fi[TPM * ks + j], a.kappa, ref.x);
+#pragma unroll
+          for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
+#pragma unroll
+          for (int j = 0; j < TPM; ++j) {
+            t[TPM * ks + j] = __builtin_fmaf(x[j], ref.y, t[TPM * ks + j]);
+            if (j & 1) z1 += x[j];
+            else z0 += x[j];
+            asm volatile("" : "+v"(t[TPM * ks + j]));
+          }
+          asm volatile("" : "+v"(z0), "+v"(z1));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        add_z(rt, z0 + z1);
+      };
+#pragma unroll 1
+      for (int rt = 0; rt + 2 < nrt; rt += 2) {
+        step(std::false_type{}, rt, fin, out);
+        step(std::false_type{}, rt + 1, out, fin);
+      }
+      step(std::false_type{}, nrt - 2, fin, out);
+      step(std::true_type{}, nrt - 1, out, fin);
+    }
+    {
+      const int ln = fresh(lane), key = wkey + transpose_key(ln);
+      const float s = transpose_sum(t, ln);
+      if (key < npre && (ln & 1) == 0) cur.raw[key] = s;
+    }
+    const bool unit_ends = !has_next || nxt.u != cur.u;
+    first = unit_ends || nxt.key % kLagKeys == 0;
+    if (first) {  // the item's sums
+      lds_barrier();
+      if (tid < a.R) {
+        const float* z8 = s_z + zbuf * kW * a.Rs + tid;
+        float z[kW];
+#pragma unroll
+        for (int w = 0; w < kW; ++w) z[w] = z8[w * a.Rs];
+        const float all = ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
+        if (all <= kSumLimit) sum += fixed_point(all, kSumUnits);
+        else sum |= kZBad;
+      }
+      if (a.zbufs == 2) zbuf ^= 1;  // (the table is written again behind the next item's barrier)
+      else lds_barrier();
+    }
+    if (unit_ends) {
+      if (tid < a.R) {
+        u64* z = a.zsum + (size_t)cur.u * a.Rs + tid;
+        if (sum & kZBad) (void)__hip_atomic_fetch_or(z, kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        (void)__hip_atomic_fetch_add(z, sum & ~kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sum = 0;
+      }
+      if (has_next) {  // (every wave is done with the unit's queries: the barrier above)
+        stage(nxt);
+        lds_barrier();
+        prime(kn);
+      }
+    }
+    const bool more = has_next;
+    cur = nxt;
+    nxt = nx2;
+    has_next = has_nx2;
+    return more;
+  };
+  issue_k(cur, b0);
+  issue_k(nxt, b1);
+  lds_barrier();  // (the first item's place has been read)
+  stage(cur);
+  lds_barrier();
+  prime(b0);
+#pragma unroll 1
+  for (;;) {
+    if (!pass(b0, b1, b2)) break;
+    if (!pass(b1, b2, b0)) break;
+    if (!pass(b2, b0, b1)) break;
+  }
+}
+
+// ---- the keys that can be kept ----
+// The row's weight 1 / (G z), the other kernel's to the bit; 0 where its sum is not usable.
+__device__ __forceinline__ float weight_of(const SiftArgs& a, u64 w) {
+  return (w >> 63) != 0 || w < 1024ull ? 0.f : __builtin_amdgcn_rcpf(as_float(w)) * (kSumUnits * a.inv_G);
+}
+
+__global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
+  extern __shared__ uint32_t smem_u[];  // [N / 8] the largest of every four, upper 16 bits | [N / 32] a bit per key
+  __shared__ __attribute__((aligned(16))) uint32_t hist[HIST];
+  __shared__ uint32_t scan[2 * NW], sel[4];
+  __shared__ float s_red[3][NW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int u = blockIdx.x;
+  const Unit p = unit_of(a, u);
+  if (a.layer[p.l].k_l >= p.n || !sift_takes(flags_of(a, p.l, p.b), a.Hkv)) return;
+  const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
+  const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
+  const float* raw = a.raw + place * a.N;
+  const int ngroup4 = (npre + 3) / 4, nwords = (npre + 31) / 32;
+  uint16_t* gmax = reinterpret_cast<uint16_t*>(smem_u);
+  uint32_t* bitmap = smem_u + (a.N + 7) / 8;
+  const bool is_avg = a.pool == PKV_POOL_AVG;
+  const int r = a.pool == PKV_POOL_NONE ? 0 : (a.pool_w - 1) / 2;
+  const float inv_w = 1.f / (float)a.pool_w;
+  // no list: the kernel behind the next one scores the sequence
+  auto fail = [&]() {
+    if (tid == 0) a.flags[place] |= 2;
+  };
+
+  // rows: the largest and the mean ratio of the weight to its estimate
+  const u64 word = tid < a.R ? a.zsum[(size_t)u * a.Rs + tid] : 0ull;
+  const float omega = tid < a.R ? a.omega[(size_t)u * a.Rs + tid] : 1.f;
+  // the pooled scores of positions q .. q + 3, from the scores around them (P: 4-score pieces on each side)
+  auto pooled4 = [&](auto PP, int q) __attribute__((always_inline)) {
+    constexpr int P = decltype(PP)::value;
+    float x[4 + 8 * P];
+    if (q >= 4 * P && q + 4 + 4 * P <= npre) {
+#pragma unroll
+      for (int i = 0; i < 1 + 2 * P; ++i) {
+        const f32x4 v = *reinterpret_cast<const f32x4_u*>(raw + q + 4 * (i - P));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[4 * i + c] = v[c];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4 + 8 * P; ++i) x[i] = q + i - 4 * P >= 0 && q + i - 4 * P < npre ? raw[q + i - 4 * P] : 0.f;
+    }
+    f32x4 y;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float acc = x[4 * P + c];
+#pragma unroll
+      for (int o = 1; o <= 4 * P; ++o) {
+        if (o > r) break;  // (uniform)
+        const float lo = x[4 * P + c - o], hi = x[4 * P + c + o];
+        acc = is_avg ? acc + (lo + hi) : fmaxf(acc, fmaxf(lo, hi));
+      }
+      y[c] = is_avg && P > 0 ? acc * inv_w : acc;
+    }
+    return y;
+  };
+  reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
+  for (int i = tid; i < nwords; i += NT) bitmap[i] = 0u;
+  // ---- A. the largest estimated pooled score of every four neighbours ----
+  uint32_t kmax = 0u;
+  auto scan_groups = [&](auto PP) __attribute__((always_inline)) {
+#pragma unroll 2
+    for (int i = tid; i < ngroup4; i += NT) {
+      const f32x4 y = pooled4(PP, 4 * i);
+      uint32_t m = 0u;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) m = max(m, 4 * i + c < npre ? __float_as_uint(y[c]) : 0u);
+      kmax = max(kmax, m);
+      gmax[i] = (uint16_t)(m >> 16);
+    }
+  };
+  if (r == 0) scan_groups(std::integral_constant<int, 0>{});
+  else if (r <= 4) scan_groups(std::integral_constant<int, 1>{});
+  else scan_groups(std::integral_constant<int, 2>{});
+  {
+    const float ratio = tid < a.R ? weight_of(a, word) / omega : 0.f;
+    float mx = ratio, sm = ratio;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      mx = fmaxf(mx, __shfl_xor(mx, o));
+      sm += __shfl_xor(sm, o);
+    }
+    const bool bad = __any(tid < a.R && !(ratio > 0.f && ratio < INFINITY));
+    kmax = row_max_lane15(kmax);
+    const uint32_t m = min(min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 15), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 31)),
+                           min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 47), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 63)));
+    if (lane == 0) {
+      s_red[0][wave] = mx;
+      s_red[1][wave] = sm;
+      s_red[2][wave] = bad ? 1.f : 0.f;
+      scan[wave] = m;
+    }
+  }
+  __syncthreads();
+  float rmax = 1.f, mean = 0.f, anybad = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    rmax = fmaxf(rmax, s_red[0][w]);
+    mean += s_red[1][w];
+    anybad += s_red[2][w];
+  }
+  mean /= (float)a.R;
+  if (anybad != 0.f) {
+    fail();
+    return;
+  }
+  uint32_t total = 0u;
+  float bound = 0.f;
+  if (kk > 0) {  // (uniform)
+    // ---- B. what about kk positions reach, and the estimates down to which a key can be kept then ----
+    const KeyBins<HIST> bins{(uint32_t)__builtin_amdgcn_readlane((int)row_max_lane15(scan[lane & 15]), 15)};
+    for (int i = tid; i < ngroup4; i += NT) {
+      const uint32_t m = (uint32_t)gmax[i] << 16;
+      if (m != 0u) atomicAdd(&hist[bins.of(m)], 1u);
+    }
+    __syncthreads();
+    // (a pooling window's largest score fills 4 w / (w + 3) places of a group it reaches, on average; whether this was enough
+    // is seen at the end)
+    const uint32_t want = min((uint32_t)kk, (uint32_t)((float)(kk * (2 * r + 4)) * (kSiftRank / (float)(8 * r + 4))) + 4u);
+    if (find_bin(hist, want, scan + NW, sel) < want) {
+      fail();
+      return;
+    }
+    const float edge = __uint_as_float(bins.lower_edge(__builtin_amdgcn_readfirstlane(sel[0])));
+    const float tau = edge * fminf(1.f, kSiftSlack * mean / rmax);
+    bound = tau * rmax * (1.f + 0x1p-9f);
+    if (!(tau > 0x1p-60f) || !(bound < 0x1p100f)) {
+      fail();
+      return;
+    }
+    // ---- C. the positions whose scores can matter: the windows of the pooled scores from tau on ----
+    const uint32_t tau16 = __float_as_uint(tau) >> 16;
+    for (int i = tid; i < ngroup4; i += NT) {
+      if (gmax[i] < tau16) continue;
+      const int q = 4 * i;
+      // from the first to the last of the four that reaches it (max: by its own score)
+      const f32x4 y = !is_avg || r == 0 ? pooled4(std::integral_constant<int, 0>{}, q) : r <= 4 ? pooled4(std::integral_constant<int, 1>{}, q) : pooled4(std::integral_constant<int, 2>{}, q);
+      int first = 4, last = -1;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (q + c < npre && __float_as_uint(y[c]) >> 16 >= tau16) {
+          first = min(first, c);
+          last = c;
+        }
+      if (last < 0) continue;  // (its window's largest lies in another group)
+      const int lo = q + first - r;
+      int hi = q + last + 1 + r;
+      hi = min(hi, npre);
+      for (int x = max(lo, 0); x < hi;) {
+        const int e = min((x | 31) + 1, hi);
+        atomicOr(&bitmap[x >> 5], (e - x == 32 ? 0xFFFFFFFFu : ((1u << (e - x)) - 1u)) << (x & 31));
+        x = e;
+      }
+    }
+    __syncthreads();
+    uint32_t bits[kSiftMaxKeys / 32 / NT], cnt = 0u;
+#pragma unroll
+    for (int j = 0; j < kSiftMaxKeys / 32 / NT; ++j) {
+      const int w = tid * (kSiftMaxKeys / 32 / NT) + j;
+      bits[j] = w < nwords ? bitmap[w] : 0u;
+      cnt += (uint32_t)__popc(bits[j]);
+    }
+    const uint32_t incl = wave_inclusive_sum(cnt);
+    if (lane == 63) scan[wave] = incl;
+    __syncthreads();
+    uint32_t at = sum_before(scan, wave, total) + incl - cnt;
+    if (total > (uint32_t)sift_list(a.N)) {
+      fail();
+      return;
+    }
+    uint32_t* list = a.list + (size_t)u * sift_list(a.N);
+#pragma unroll
+    for (int j = 0; j < kSiftMaxKeys / 32 / NT; ++j)
+      for (uint32_t b = bits[j]; b != 0u; b &= b - 1u) list[at++] = 32u * (uint32_t)(tid * (kSiftMaxKeys / 32 / NT) + j) + (uint32_t)__ffs((int)b) - 1u;
+  }
+  // a job per kSiftJob listed keys, one at least
+  if (wave == 0) {
+    const int n = max(((int)total + kSiftJob - 1) / kSiftJob, 1);
+    int at = 0;
+    if (lane == 0) at = atomicAdd(a.njobs, n);
+    at = __builtin_amdgcn_readfirstlane(at);
+    for (int j = lane; j < n; j += 64) a.jobs[at + j] = make_int4(u, j, (int)total, __float_as_int(bound));
+  }
+}
+
+// ---- their exact scores; and the attention to the prefix, for the recall of the kept set ----
+template <int D>
+__global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a) {
+  constexpr int KS = D / 16;
+  using QB = QueryBlock<D, kBlockRows>;
+  static_assert(kSiftJob == 32 * kW, "a tile per wave");
+  constexpr int kView = 2048, kEdge = 32;  // keys of the list that are looked at at a time, and around them
+  static_assert(sizeof(u32x4) * QueryBlock<64, kBlockRows>::SLOTS >= 8 * (kView + 2 * kEdge), "the list and its scores take the queries' place");
+  __shared__ u32x4 s_q[QB::SLOTS];
+  __shared__ float s_m[kResidentMaxRows], s_w[kResidentMaxRows], s_win[2][kResidentMaxRows], s_red[kW];
+  __shared__ int s_count[kW], s_last;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int njobs = *a.njobs;
+#pragma unroll 1
+  for (int job = blockIdx.x; job < njobs; job += gridDim.x) {
+    const int4 jb = a.jobs[job];
+    const int u = __builtin_amdgcn_readfirstlane(jb.x), part = __builtin_amdgcn_readfirstlane(jb.y), total = __builtin_amdgcn_readfirstlane(jb.z);
+    const float bound = __int_as_float(__builtin_amdgcn_readfirstlane(jb.w));
+    const Unit p = unit_of(a, u);
+    const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
+    const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
+    float* raw = a.raw + place * a.N;
+    const uint16_t* Q = queries_of(a, p);
+    const uint16_t* K = keys_of(a, p);
+    const uint32_t* list = a.list + (size_t)u * sift_list(a.N);
+    QB qb;
+    auto row_at = [&](int row) { return query_row_of(a, Q, row); };
+    qb.request(0, row_at);
+    const int e = part * kSiftJob + 32 * wave + l32;
+    const bool mine = part * kSiftJob + 32 * wave < total;  // (uniform within the wave)
+    const int pos = mine ? (int)list[min(e, total - 1)] : 0;
+    bf16x8 kf[KS];
+    load_rows(kf, K + (size_t)pos * a.kv_st, hf);
+    if (tid < a.Rs) {
+      s_m[tid] = reinterpret_cast<const float*>(a.words + (size_t)u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)];
+      s_w[tid] = tid < a.R ? weight_of(a, a.zsum[(size_t)u * a.Rs + tid]) : 0.f;
+    }
+    f32x16 t = {};
+#pragma unroll 1
+    for (int row0 = 0; row0 < a.Rs; row0 += kBlockRows) {
+      const int ntile = min(kBlockTiles, (a.Rs - row0) / 32);
+      qb.commit(s_q);
+      __syncthreads();
+      if (row0 + kBlockRows < a.Rs) qb.request(row0 + kBlockRows, row_at);
+      if (part == 0 && wave < 2 * ntile) {  // the window: a row tile and half of its keys each
+        const int wrt = wave >> 1, whalf = wave & 1, row = row0 + 32 * wrt + l32;
+        load_rows(kf, K + (size_t)min(npre + 32 * whalf + l32, p.n - 1) * a.kv_st, hf);
+        const f32x16 x = product(kf, s_q, 32 * wrt + l32, hf);
+        const int lim = min(row, a.R - 1) % a.alpha - 32 * whalf - 4 * hf;
+        const float nm = -s_m[row];
+        float y = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) y += mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(x[v], a.kappa, nm));
+        y = both_halves<false>(y);
+        if (hf == 0) s_win[whalf][row] = y;
+        load_rows(kf, K + (size_t)pos * a.kv_st, hf);
+      }
+      if (mine) {
+        // (products, exponentials and sums as in the kernel that scores every key, so that the scores are its to the bit)
+#pragma unroll 1
+        for (int rt = 0; rt < ntile; ++rt) {
+          const f32x16 x = product(kf, s_q, 32 * rt + l32, hf);
+          const float nm = -s_m[row0 + 32 * rt + l32], w = s_w[row0 + 32 * rt + l32];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) t[v] = __builtin_fmaf(fast_exp2(__builtin_fmaf(x[v], a.kappa, nm)), w, t[v]);
+        }
+      }
+      __syncthreads();
+    }
+    const float s = transpose_sum(t, lane);
+    const int es = part * kSiftJob + 32 * wave + transpose_key(lane);
+    const int ps = __shfl(pos, transpose_key(lane));
+    if ((lane & 1) == 0 && es < total)  // (another workgroup may look at it before the kernel ends)
+      __hip_atomic_store(raw + ps, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);  // the scores are on their way no more when the job counts as done
+    if (part == 0) {
+      float w = tid < a.R ? (s_win[0][tid] + s_win[1][tid]) * s_w[tid] : 0.f;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o);
+      if (lane == 0) s_red[wave] = w;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      if (part == 0) {
+        float w = 0.f;
+#pragma unroll
+        for (int i = 0; i < kW; ++i) w += s_red[i];
+        raw[npre] = (float)a.alpha - w;  // (behind the scores)
+      }
+      const int jobs = max((total + kSiftJob - 1) / kSiftJob, 1);
+      s_last = __hip_atomic_fetch_add(a.done + u, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == jobs - 1 ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_last == 0) continue;
+    // ---- the unit's last job: do enough positions reach the bound?  Then nothing outside the list can be kept ----
+    uint32_t* lpos = reinterpret_cast<uint32_t*>(s_q) + kEdge;  // [-kEdge, kView + kEdge)
+    float* exact = reinterpret_cast<float*>(lpos + kView + 2 * kEdge);
+    const bool is_avg = a.pool == PKV_POOL_AVG;
+    const int r = a.pool == PKV_POOL_NONE ? 0 : (a.pool_w - 1) / 2;
+    bool odd = false;
+    int reach = 0;
+#pragma unroll 1
+    for (int i0 = 0; i0 < total; i0 += kView) {
+      const int first = max(-i0, -kEdge), last = min(total - i0, kView + kEdge);
+      for (int i = first + tid; i < last; i += kT) {
+        const uint32_t q = list[i0 + i];
+        lpos[i] = q;
+        exact[i] = __hip_atomic_load(raw + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        odd = odd || !(exact[i] < INFINITY);
+      }
+      __syncthreads();
+      for (int i = tid; i < min(last, kView); i += kT) {
+        const int q = (int)lpos[i];
+        const int lo = min(r, q), hi = min(r, npre - 1 - q);
+        if (is_avg) {  // the window is listed whole
+          if (i - lo >= first && i + hi < last && (int)lpos[i - lo] == q - lo && (int)lpos[i + hi] == q + hi) {
+            float w = 0.f;
+            for (int x = -lo; x <= hi; ++x) w += exact[i + x];
+            reach += w >= bound * (float)a.pool_w ? 1 : 0;
+          }
+        } else if (exact[i] >= bound) {  // the places of its window that the one before it has not reached
+          int from = q - lo;
+          for (int j = i - 1; j >= first && (int)lpos[j] + r >= from; --j)
+            if (exact[j] >= bound) {
+              from = (int)lpos[j] + r + 1;
+              break;
+            }
+          reach += max(q + hi + 1 - from, 0);
+        }
+      }
+      __syncthreads();
+    }
+    if (odd) reach = -(1 << 20);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) reach += __shfl_xor(reach, o);
+    if (lane == 0) s_count[wave] = reach;
+    __syncthreads();
+    if (tid == 0) {
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < kW; ++i) n += s_count[i];
+      if (n < kk) a.flags[place] |= 2;
+    }
+    __syncthreads();
+  }
+}
+
+template <int D>
+hipError_t launch_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
+  static bool attr_set[kMaxDevices];
+  constexpr size_t list_lds = (size_t)(kSiftMaxKeys + kMaxAlpha) / 2 + kSiftMaxKeys / 8 + 64;
+  const int dev = current_device_slot();
+  if (dev < 0) return hipErrorInvalidDevice;
+  if (!attr_set[dev]) {  // raise the dynamic LDS limits once per device (idempotent; no allocation)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_kernel<D>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sift_lds<D>(kResidentMaxRows));
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(sift_list_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
+    if (e != hipSuccess) return e;
+    attr_set[dev] = true;
+  }
+  const int units = a.L * a.B * a.Hkv;
+  hipLaunchKernelGGL((sift_prepare_kernel<D>), dim3(units * a.groups), dim3(kT), 0, s, a, clear_err ? 1 : 0);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((score_sift_kernel<D>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t lds = (size_t)((a.N + 7) / 8 + (a.N + 31) / 32) * 4;
+  hipLaunchKernelGGL(sift_list_kernel, dim3(units), dim3(NT), lds, s, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t jobs = (int64_t)units * (sift_list(a.N) / kSiftJob);
+  hipLaunchKernelGGL((sift_exact_kernel<D>), dim3(jobs < kSiftExactGrid ? (unsigned)jobs : kSiftExactGrid), dim3(kT), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_score_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
+  if (a.d == 128) return launch_sift<128>(a, clear_err, s);
+  if (a.d == 64) return launch_sift<64>(a, clear_err, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace pkv

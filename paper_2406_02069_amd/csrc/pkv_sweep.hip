@@ -32,43 +32,19 @@
 #include <type_traits>
 
 #include "pkv_internal.h"
+#include "pkv_tile.h"
 
 namespace pkv {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned long long u64;
-
 constexpr int kSums = 8;  // waves that form statistics
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
-__device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
-#define PKV_MFMA32(A, B, C) __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, C, 0, 0, 0)
 // End of a hand-ordered chunk of instructions: nothing is scheduled across it, and the running sums are pinned here.
 #define PKV_CHUNK_END_SUMS(s0, s1)                 \
   do {                                             \
     asm volatile("" : "+v"(s0), "+v"(s1));         \
     __builtin_amdgcn_sched_barrier(0);             \
   } while (0)
-__device__ __forceinline__ int fresh(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-template <bool MAX>
-__device__ __forceinline__ float both_halves(float x) {
-  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
-  const float p = __uint_as_float(r[0]), q = __uint_as_float(r[1]);
-  return MAX ? fmaxf(p, q) : p + q;
-}
 // c as three bf16 summands (to 2^-24): the first three k-elements of a matrix operand.  -inf stays -inf.
 __device__ __forceinline__ u64 split3(float c) {
   const __bf16 hi = (__bf16)c;
@@ -80,7 +56,6 @@ __device__ __forceinline__ u64 split3(float c) {
   const uint32_t w0 = (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, mid) << 16);
   return ((u64)__builtin_bit_cast(uint16_t, lo) << 32) | w0;
 }
-__device__ __forceinline__ constexpr int mrow0(int v) { return 8 * (v >> 2) + (v & 3); }
 
 template <int D, bool SCORE>
 constexpr size_t sweep_lds(int Rs) {

@@ -1,0 +1,122 @@
+"""Scoring by estimates (G * alpha > 64, 16k keys and more, 6 million in the call, no scores asked for): kept sets against the CPU oracle and against
+the kernel that scores every key, at the edges of the work split; and the calls that are handed on to that kernel: estimates
+that are no use, sums that do not fit, more keys near the cut than there is room for, layers whose scores are asked for."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import pkv_oracle
+from paper_2406_02069_amd import binding, synth
+from tests.parity import compare_layer
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+NONE, MAX, AVG = synth.POOL_NONE, synth.POOL_MAX, synth.POOL_AVG
+
+
+def _inputs(B, G, Hkv, d, N, alpha, seed, spread=0.9):
+    """Window queries that point largely the same way, key 0 an attention sink."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    base = torch.randn(B, Hkv, 1, 1, d, generator=g, device=DEV)
+    Q = (1.2 * base + spread * torch.randn(B, Hkv, G, alpha, d, generator=g, device=DEV)).reshape(B, Hkv * G, alpha, d)
+    K, V = (torch.randn(B, Hkv, N, d, generator=g, device=DEV) for _ in range(2))
+    K[:, :, 0] *= 6
+    return Q.to(torch.bfloat16), K.to(torch.bfloat16), V.to(torch.bfloat16)
+
+
+def _run(Qs, Ks, Vs, ks, pool, pw, lens=None, scores=False):
+    """The call over the layers, repeated until it is large enough to be taken; and of the first ones, per layer, sequence and
+    head, what became of it: 0 scored by estimates, 1 not tried, 2 handed on."""
+    L = len(Ks)
+    n = -(-(6 << 20) // (L * Ks[0].shape[0] * Ks[0].shape[1] * Ks[0].shape[2]))
+    Qs, Ks, Vs, ks = Qs * n, Ks * n, Vs * n, ks * n
+    ld = None if lens is None else torch.from_numpy(np.asarray(lens, np.int32)).to(DEV)
+    call = binding.LayersCall(Qs, Ks, Vs, ks, pool, pw, seq_lens=ld, want_scores=scores)
+    call.run()
+    torch.cuda.synchronize()
+    B, Hkv = Ks[0].shape[:2]
+    flags = call.workspace[8:8 + 4 * len(Ks) * B * Hkv].view(torch.int32).cpu().numpy().reshape(len(Ks), B, Hkv)
+    for l in range(L, len(Ks)):
+        assert np.array_equal(flags[l], flags[l % L])
+        for i in range(4):
+            assert torch.equal(call.outputs[l][i], call.outputs[l % L][i])
+    return call, flags[:L]
+
+
+def _sifted(flags):
+    """Per layer and sequence: tried (no more than a quarter of the heads object), and scored."""
+    return (4 * (flags & 1).sum(-1) <= flags.shape[-1]) & ((flags & 2) == 0).all(-1)
+
+
+def _same(a, b):
+    """Same kept sets and rows, ties and all: the scores of the two kernels are the same to the bit."""
+    for x, y in zip(a[:4], b[:4]):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d,G,alpha,N,pool,pw,k", [
+    (128, 4, 17, 16384, AVG, 5, 17 + 60),      # a third row tile; the shortest buffer
+    (128, 4, 32, 16417, MAX, 7, 32 + 1),       # one key to keep; a last pass of one key
+    (128, 8, 64, 16640, NONE, 1, 64 + 120),    # all rows that fit, many kept
+    (64, 8, 16, 16500, AVG, 17, 16 + 60),      # the widest pooling window
+    (64, 7, 37, 16500, MAX, 3, 37),            # nothing to choose; rows that fill no tile
+    (128, 5, 33, 17000, AVG, 3, 33 + 120),
+])
+def test_against_the_oracle(d, G, alpha, N, pool, pw, k):
+    print("sift", d, G, alpha, N, pool, pw, k, flush=True)
+    Q, K, V = _inputs(1, G, 8, d, N, alpha, seed=N + G)
+    call, flags = _run([Q], [K], [V], [k], pool, pw)
+    assert _sifted(flags).all()
+    compare_layer(Q, K, V, k, alpha, pool, pw, None, call.outputs[0])
+    rec = binding.attention_recall(call)[0].cpu().numpy()
+    idx = call.outputs[0][2].cpu().numpy()
+    for g in (0, 7):
+        want = pkv_oracle.attention_recall(Q[0, g * G:(g + 1) * G], K[0, g], idx[0, g])
+        assert abs(rec[0, g] - want) <= 1e-5  # (sums of 16k fp32 terms of at most 1)
+
+
+@pytest.mark.parametrize("N", [32768, 33000, 65536, 131072])
+@pytest.mark.parametrize("pool,pw", [(AVG, 5), (MAX, 13)])
+def test_against_every_key_scored(N, pool, pw):
+    print("sift", N, pool, pw, flush=True)
+    alpha, G, ks = 32, 4, [32 + 20, 32 + 250]
+    data = [_inputs(1, G, 8, 128, N, alpha, seed=N + l) for l in range(2)]
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, ks, pool, pw)
+    assert _sifted(flags).all()
+    full, other = _run(Qs, Ks, Vs, ks, pool, pw, scores=True)
+    assert np.all(other == 1)
+    for l in range(2):
+        _same(call.outputs[l], full.outputs[l])
+
+
+def test_ragged_batch():
+    B, G, alpha, N, k = 5, 4, 32, 20000, 100
+    lens = [20000, 4000, 90, 16401, 12289]   # two that are too short for it, one of them kept whole
+    Q, K, V = _inputs(B, G, 8, 128, N, alpha, seed=5)
+    for b in range(B):
+        K[b, :, lens[b]:] = float("nan")
+        V[b, :, lens[b]:] = float("nan")
+    call, flags = _run([Q], [K], [V], [k], AVG, 5, lens)
+    print(flags[0], flush=True)
+    assert _sifted(flags)[0].tolist() == [True, False, True, True, True]
+    compare_layer(Q, K, V, k, alpha, AVG, 5, np.asarray(lens, np.int32), call.outputs[0])
+
+
+def test_handed_on():
+    """Queries without a common direction (any key may be kept), keys far above the estimates, many keys at the cut, scores
+    asked for: the kernel that scores every key takes these, among others that it does not."""
+    alpha, G, N, k, L = 32, 4, 16384, 100, 5
+    data = [list(_inputs(1, G, 8, 128, N, alpha, seed=50 + l)) for l in range(L)]
+    data[1][0] = torch.randn_like(data[1][0].float()).to(torch.bfloat16)
+    data[2][1][0, 3, 7001] = 4 * data[2][0][0, 13, 5]           # one head's normaliser is far above its estimate
+    data[3][1][0, 2, 9000:15000] = data[3][1][0, 2, 9000] * 0 + 0.9 * data[3][0][0, 9, 0]  # 6000 equal keys at the top
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, [k] * L, MAX, 7)
+    print(flags[:, 0], flush=True)
+    assert _sifted(flags)[:, 0].tolist() == [True, False, False, False, True] and flags[2, 0, 3] & 2 and flags[3, 0, 2] & 2
+    full, _ = _run(Qs, Ks, Vs, [k] * L, MAX, 7, scores=True)
+    for l in range(L):
+        _same(call.outputs[l], full.outputs[l])
+    a, b = (torch.stack(binding.attention_recall(c)).cpu().numpy() for c in (call, full))
+    assert np.abs(a - b).max() <= 1e-5
