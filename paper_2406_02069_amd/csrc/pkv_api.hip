@@ -355,15 +355,15 @@ constexpr int kSiftMinLen = 16384;
 constexpr int64_t kSiftMinTotal = 6 << 20;  // keys of a call
 struct SiftPlan {
   int Rs;
-  // the other kernel's words, sums, jobs, list, estimates, count of jobs
-  size_t unit_bytes(const LagPlan& gp, int N) const { return gp.unit_bytes() + (size_t)Rs * 12 + sift_list(N) / kSiftJob * 16 + sift_list(N) * 4 + 4; }
+  // the other kernel's words; sums, estimates, sums over the window; list and three words about it
+  size_t unit_bytes(const LagPlan& gp, int N) const { return gp.unit_bytes() + (size_t)Rs * 16 + sift_list(N) * 4 + 12; }
 };
 static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, const LagPlan& gp, int scoring_layers) {
   SiftPlan p = {0};
   if (gp.layers == 0 || d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return p;
   if ((int64_t)scoring_layers * plan.BH * d.N < kSiftMinTotal) return p;
   const SiftPlan q = {(plan.R + 63) / 64 * 64};
-  return q.unit_bytes(gp, d.N) <= (size_t)d.N * 4 - 4 ? q : p;
+  return q.unit_bytes(gp, d.N) <= (size_t)d.N * 4 ? q : p;
 }
 
 // Queue the kernels of L layers.  All arguments have been validated.
@@ -380,6 +380,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
   bool any_scores = false;
   for (int32_t l = 0; l < L; ++l) any_scores = any_scores || descs[l].k_l < d.N;
   if (rec) rec->begin(stream);
+  const int32_t* sifted = nullptr;
 
   // ---- scoring: un-pooled group-mean scores of every prefix key -> raw ----
   LagPlan gp = {0, 0, 0, false};
@@ -441,13 +442,12 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
     unsigned long long* const words4 = words + scoring * plan.BH * unit_words;
     int32_t* const flags = reinterpret_cast<int32_t*>(ws + plan.off_cnt) + 2;
     if (fp.Rs > 0) {
-      // (parts of 16 bytes first, then of 8 and of 4)
       const size_t units = (size_t)scoring * plan.BH;
       unsigned long long* const zsum = words4 + (gp.words4 ? units * unit_words4 : 0);
-      int4* const jobs = reinterpret_cast<int4*>(zsum + units * fp.Rs);
-      uint32_t* const list = reinterpret_cast<uint32_t*>(jobs + units * (sift_list(d.N) / kSiftJob));
-      float* const omega = reinterpret_cast<float*>(list + units * sift_list(d.N));
-      int32_t* const done_jobs = reinterpret_cast<int32_t*>(omega + units * fp.Rs);
+      float* const omega = reinterpret_cast<float*>(zsum + units * fp.Rs);
+      float* const window = omega + units * fp.Rs;
+      uint32_t* const list = reinterpret_cast<uint32_t*>(window + units * fp.Rs);
+      int32_t* const about = reinterpret_cast<int32_t*>(list + units * sift_list(d.N));
       int32_t done = 0;
       for (int32_t l = 0; l < L;) {
         SiftArgs fa;
@@ -458,6 +458,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
           fa.layer[fa.L].Q = static_cast<const uint16_t*>(ptrs[l].Q);
           fa.layer[fa.L].K = static_cast<const uint16_t*>(ptrs[l].K);
           fa.layer[fa.L].k_l = descs[l].k_l;
+          fa.layer[fa.L].idx = ptrs[l].idx_out;
           if (ptrs[l].scores_out) fa.scored[fa.L >> 5] |= 1u << (fa.L & 31);
           fa.layer[fa.L++].slot = l - l0;
         }
@@ -470,10 +471,11 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         if (gp.words4) fa.words4 = words4 + u0 * unit_words4;
         fa.zsum = zsum + u0 * fp.Rs;
         fa.omega = omega + u0 * fp.Rs;
-        fa.jobs = jobs;
+        fa.window = window + u0 * fp.Rs;
         fa.list = list + u0 * sift_list(d.N);
-        fa.done = done_jobs + u0;
-        fa.njobs = done_jobs + units;
+        fa.done = about + u0;
+        fa.total = about + units + u0;
+        fa.bound = reinterpret_cast<float*>(about + 2 * units + u0);
         fa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
         fa.B = d.B; fa.Hq = d.Hq; fa.Hkv = d.Hkv; fa.G = plan.G; fa.alpha = d.alpha; fa.N = d.N; fa.R = plan.R; fa.Rs = fp.Rs; fa.d = d.d;
         const int64_t items = (int64_t)fa.L * plan.BH * gp.parts;
@@ -482,10 +484,13 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         fa.pool = (d.pool_w == 1) ? PKV_POOL_NONE : d.pool;
         fa.pool_w = d.pool_w;
         fa.zbufs = sift_zbufs(fp.Rs);
-        fa.sample_tiles = fa.pool == PKV_POOL_AVG ? 4 : 2;
+        fa.sample_tiles = fa.pool == PKV_POOL_AVG ? 4 : 2;  // (its lists are longer)
+        fa.sample_shift = fa.sample_tiles == 4 ? 7 : 6;
         // (so that the list fits an eighth of the keys: it holds about 4 keys per key to keep, with average pooling 2.5 + w)
         fa.min_share = fa.pool == PKV_POOL_AVG ? 27 + 11 * d.pool_w : 43;
         fa.alpha_magic = alpha_magic;
+        fa.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;
+        fa.hkv_magic = 0xFFFFFFFFu / (uint32_t)d.Hkv;
         fa.q_sb = d.q_sb; fa.q_sh = d.q_sh; fa.q_st = d.q_st;
         fa.kv_sb = d.kv_sb; fa.kv_sh = d.kv_sh; fa.kv_st = d.kv_st;
         fa.kappa = kappa;
@@ -496,6 +501,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         done += fa.L;
       }
       gp = lag_plan(plan, d, lse_mode, seq_lens != nullptr, true);
+      sifted = flags;
     }
     int32_t done = 0;
     for (int32_t l = 0; l < L;) {
@@ -677,6 +683,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
     se.inv_G = resident ? 1.0f : 1.0f / (float)plan.G;
     // the error word of this call's scoring launches (the two-launch kernel waits for nobody and has none)
     se.err = (any_scores && resident && wp.C == 0) ? reinterpret_cast<const int32_t*>(ws + plan.off_cnt) : nullptr;
+    se.flags = sifted ? sifted + (size_t)l0 * plan.BH : nullptr;
     ga.L = nl; ga.B = d.B; ga.Hkv = d.Hkv; ga.d = d.d; ga.k_cap_max = k_cap_max; ga.N = d.N;
     ga.kv_sb = d.kv_sb; ga.kv_sh = d.kv_sh; ga.kv_st = d.kv_st;
     if (paged) {

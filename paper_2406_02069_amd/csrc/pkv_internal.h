@@ -176,17 +176,26 @@ constexpr int kSiftMaxPoolW = 17;
 // (two where they fit the LDS beside the queries)
 __host__ __device__ constexpr int sift_zbufs(int Rs) { return Rs <= 384 ? 2 : 1; }
 
+struct SiftLayer {
+  const uint16_t* Q;
+  const uint16_t* K;
+  int32_t* idx;   // [BH][k_l] kept positions
+  int32_t k_l;
+  int32_t slot;   // as ResidentLayer
+};
+
 struct SiftArgs {
-  ResidentLayer layer[kResidentMaxLayers];
+  SiftLayer layer[kResidentMaxLayers];
   const int32_t* seq_lens;
   float* raw;                 // [layer slot][B][Hkv][N] scores
   float* omega;               // [units][Rs] estimated weights of the rows: 1 / (G z)
   unsigned long long* zsum;   // [units][Rs] their sums, as the other kernel's words hold them (bit 63: one that does not fit)
   int32_t* flags;             // [layer slot][B][Hkv] bit 0: not worth it; bit 1: not scored exactly
+  float* window;              // [units][Rs] sums of the rows over the window keys
   int32_t* done;              // [units] jobs done
+  int32_t* total;             // [units] keys listed
+  float* bound;               // [units] what the kept number of them has to reach
   uint32_t* list;             // [units][sift_list(N)] positions of keys that can be kept, ascending
-  int4* jobs;                 // [units * sift_list(N) / kSiftJob] unit, part of its list, keys listed, bound
-  int32_t* njobs;
   unsigned long long *words, *words4;  // of the kernel that takes the rest, prepared by the way
   int32_t* err;
   uint32_t scored[(kResidentMaxLayers + 31) / 32];  // layers whose scores are asked for: left to that kernel
@@ -194,9 +203,10 @@ struct SiftArgs {
   int32_t grid, groups;       // workgroups of the pass over K; groups of 64 rows
   int32_t zbufs;              // tables of sums by wave, used in turn
   int32_t pool, pool_w;
-  int32_t sample_tiles;       // of 32 keys, per wave (8 waves; even)
+  int32_t sample_tiles;       // of 32 keys, per wave (8 waves): 2 or 4
+  int32_t sample_shift;       // log2 of the sample's runs of eight keys
   int32_t min_share;          // keys of a prefix per key to keep, at least
-  uint32_t alpha_magic;       // as LagArgs
+  uint32_t alpha_magic, bh_magic, hkv_magic;  // as LagArgs
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;
 };
@@ -269,6 +279,7 @@ struct SelectBatchArgs {
   int32_t nrb;         // partial score arrays to add per layer
   float inv_G;         // factor applied to the sum of the partials
   const int32_t* err;  // error word of the scoring kernel (non-zero: a wait was given up), or null
+  const int32_t* flags;  // [layer][B][Hkv] of the sifting kernels: where they scored a sequence, its kept positions are there; or null
   int32_t listed;      // a launch before this one has listed the candidates of long prefixes
 };
 

@@ -816,6 +816,7 @@ __global__ __launch_bounds__(kStretchThreads, 4) void select_stretch_kernel(cons
     n = n < 0 ? 0 : (n > a.N ? a.N : n);
   }
   if (ly.k_l >= n) return;
+  if (a.flags && sift_done(a.flags + (size_t)l * BH + (size_t)(bg / a.Hkv) * a.Hkv, a.Hkv)) return;  // (the kept set is there)
   const int npre = n - a.alpha, kk = ly.k_l - a.alpha;
   const Stretches st = stretches(npre, kk, a.listed != 0, ly.write_pooled != 0);
   if ((int)blockIdx.x >= st.count) return;
@@ -1142,6 +1143,10 @@ __global__ __launch_bounds__(NT, PMAX <= 16 ? 8 : 4) void pool_select_batch_kern
   if (ly.k_l >= n) {  // keep everything
     for (int j = tid; j < ly.k_cap; j += NT) idx[j] = j < n ? j : -1;
     if (fuse_gather) gather_unit(ga, gl, b, g, [&](int j) { return j < n ? j : -1; });
+    return;
+  }
+  if (a.flags && sift_done(a.flags + (size_t)l * BH + (size_t)b * a.Hkv, a.Hkv)) {  // the kept set is there
+    if (fuse_gather) gather_unit(ga, gl, b, g, [&](int j) { return idx[j]; });
     return;
   }
   const int npre = n - a.alpha;

@@ -17,16 +17,18 @@
 //
 // Four launches: sift_prepare_kernel (references, weights o_r from 512 or 1024 keys: the median of eight groups' sums, so that a rare
 // large key does not spoil them), score_sift_kernel (the pass over K), sift_list_kernel (a workgroup per head: tau and the list),
-// sift_exact_kernel (256 listed keys at a time, from a common list of jobs; a head's last job makes the check).
+// sift_exact_kernel (256 listed keys at a time; the last workgroup of a head makes the check and selects the kept set among the few
+// places that reach the bound, so that the selection kernel only copies their rows).
 //
 // score_sift_kernel: 256 persistent workgroups of 512 threads, all query rows of a unit in LDS, a wave holds 32 keys as matrix
 // operands and passes over all rows with them, the next two tiles of keys under way; one product's matrix instructions are issued
 // between the exponentials of the one before.  A barrier per 512 keys, for the sums.  Workgroups take stretches of items of equal
 // length; no workgroup waits for another.
 //
-// What bounds it: HBM and the clock the chip holds under this load at 128 rows (32 layers x 8 heads x 32k keys 470 us, 4.6 TB/s, at
-// 2.0 GHz; the lagging kernel 620), vector instructions at 512 rows (80 layers 3.39 ms at 1.8 GHz; 4.3).  A launch begins with
-// 12 us until the first product.
+// What bounds it: vector instructions and HBM, and the clock the chip holds under this load, at 128 rows (32 layers x 8 heads x 32k
+// keys 465 us, 4.6 TB/s, at 2.0 GHz; with the keys in the caches 438; the lagging kernel 620), vector instructions at 512 rows (80
+// layers 3.34 ms at 1.8 GHz; 4.3).  A launch begins with 12 us until the first product.  The kernels around it are chains of latencies:
+// 31, 26 and 38 us for 256 heads of 32k keys (the selection kernel, which takes 27 otherwise, is left with 10).
 #include <type_traits>
 
 #include "pkv_internal.h"
@@ -40,7 +42,7 @@ constexpr int kW = 8, kT = kW * 64;   // waves and threads of the kernel that re
 constexpr int kPass = 32 * kW;        // keys of a pass
 constexpr u64 kZBad = 1ull << 63;     // an item's sum does not fit
 constexpr int kBlockRows = 128, kBlockTiles = kBlockRows / 32;  // query rows that lie in LDS at a time where keys are scored exactly
-constexpr int kSiftExactGrid = 512;
+constexpr int kSiftParts = 8;  // workgroups per unit there
 
 // A unit's place: layer entry, sequence, head, valid length.
 struct Unit {
@@ -52,7 +54,7 @@ __device__ __forceinline__ int valid_length(const SiftArgs& a, int b) {
   return n < 0 ? 0 : (n > a.N ? a.N : n);
 }
 __device__ __forceinline__ Unit unit_of(const SiftArgs& a, int u) {
-  const int BH = a.B * a.Hkv, l = u / BH, bg = u - l * BH, b = bg / a.Hkv;
+  const int BH = a.B * a.Hkv, l = (int)((u64)(uint32_t)(u + 1) * a.bh_magic >> 32), bg = u - l * BH, b = (int)((u64)(uint32_t)(bg + 1) * a.hkv_magic >> 32);
   return {l, b, bg - b * a.Hkv, valid_length(a, b)};
 }
 __device__ __forceinline__ const int32_t* flags_of(const SiftArgs& a, int l, int b) {
@@ -119,10 +121,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = blockIdx.x / a.groups, row0 = 64 * (blockIdx.x - u * a.groups);
-  if (blockIdx.x == 0 && tid == 0) {
-    if (clear_err) a.err[0] = a.err[1] = 0;
-    *a.njobs = 0;
-  }
+  if (blockIdx.x == 0 && tid == 0 && clear_err) a.err[0] = a.err[1] = 0;
   const Unit p = unit_of(a, u);
   const bool whole = a.layer[p.l].k_l >= p.n;
   const int npre = whole ? 1 : p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
@@ -133,8 +132,8 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   QB qb;
   // The sample: wave w's group of keys is spread evenly over the prefix in runs of eight neighbours, four to a tile.
   auto sample = [&](int tile, bf16x8 (&f)[KS]) {
-    const uint32_t run = (uint32_t)((4 * tile + (l32 >> 3)) * kW + wave), runs = (uint32_t)(4 * a.sample_tiles * kW);
-    load_rows(f, K + (size_t)min((int)((u64)(uint32_t)npre * run / runs) + (l32 & 7), npre - 1) * a.kv_st, hf);
+    const uint32_t run = (uint32_t)((4 * tile + (l32 >> 3)) * kW + wave);
+    load_rows(f, K + (size_t)min((int)((uint32_t)npre * run >> a.sample_shift) + (l32 & 7), npre - 1) * a.kv_st, hf);
   };
   if (!whole) {
     qb.request(row0, [&](int row) { return query_row_of(a, Q, row); });
@@ -149,7 +148,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   if (tid < kLagGroupBytes / 8 && ((tid & 31) < kLagRefs || (tid & 31) >= kLagMax)) words[tid] = 0;
   if (a.words4 && tid < kLagGroupBytes4 / 8) a.words4[(size_t)blockIdx.x * (kLagGroupBytes4 / 8) + tid] = 0;
   int32_t* flag = a.flags + (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
-  if (row0 == 0 && tid == 0) a.done[u] = 0;
+  if (row0 == 0 && tid == 0) a.done[u] = a.total[u] = 0;
   if (whole) {
     if (row0 == 0 && tid == 0) *flag = 0;
     return;
@@ -228,7 +227,9 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
       if (rank == kW / 2 - 1 || rank == kW / 2) mid += v[w];
     }
     const float m = s_m[tid];
-    const float sum = __builtin_fmaf(mid, (float)(npre - 1) / (float)(64 * a.sample_tiles), fast_exp2(s_x0[tid] - m)) + (s_win[0][tid] + s_win[1][tid]);
+    const float window = s_win[0][tid] + s_win[1][tid];
+    const float sum = __builtin_fmaf(mid, (float)(npre - 1) / (float)(64 * a.sample_tiles), fast_exp2(s_x0[tid] - m)) + window;
+    a.window[(size_t)u * a.Rs + row0 + tid] = window;
     const float o = row0 + tid < a.R ? a.inv_G / sum : 0.f;
     s_o[tid] = o;
     a.omega[(size_t)u * a.Rs + row0 + tid] = o;
@@ -280,7 +281,8 @@ constexpr size_t sift_lds(int Rs) {
 static_assert(sift_lds<128>(kResidentMaxRows) <= 160 * 1024 && sift_lds<128>(384) <= 160 * 1024, "one workgroup per compute unit");
 
 // ---- the pass over K ----
-template <int D>
+// FOUR: four row tiles (65 .. 128 rows), no loop over them: entering and leaving one costs 40 register copies a pass.
+template <int D, bool FOUR>
 __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;
   constexpr int TPM = 16 / KS;  // logits per lane handled between two matrix instructions
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
-  const int nrt = a.Rs / 32;
+  const int nrt = FOUR ? 4 : a.Rs / 32;  // (even, four at least)
 
   // One pass of the workgroup (all fields wave-uniform): its keys from `key` on of unit u.
   struct Pass {
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     const bool has_nx2 = has_next && advance(nx2);
     issue_k(nx2, kp);
     const int wkey = cur.key + 32 * wave, npre = cur.n - a.alpha;
-    f32x16 t = {};
+    f32x16 t;
     float* zp = z_lane + zbuf * kW * a.Rs;
     auto add_z = [&](int rt, float z) {  // (the sums of an item come about as in the kernel that scores the other sequences)
       z = both_halves<false>(z);
@@ -445,6 +447,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     };
     if (__builtin_expect(wkey + 32 > npre, 0)) {
       // the tile reaches into the causal window or beyond the end
+      t = f32x16{};
 #pragma unroll 1
       for (int rt = 0; rt < nrt; ++rt) {
         const float2 ref = s_r[32 * rt + l32];
@@ -466,8 +469,8 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     } else {
       // Product of row tile rt + 1 (LAST: of the next pass's keys and row tile 0) goes into `nx` while `fi`, that of row
       // tile rt, turns into exponentials.
-      auto step = [&](auto LAST, int rt, const f32x16& fi, f32x16& nx) {
-        constexpr bool last = decltype(LAST)::value;
+      auto step = [&](auto FIRST, auto LAST, int rt, const f32x16& fi, f32x16& nx) {
+        constexpr bool start = decltype(FIRST)::value, last = decltype(LAST)::value;
         const int mul = last ? 0 : rt + 1, then = last ? 1 : rt + 2 < nrt ? rt + 2 : 0;
         const float2 ref = s_r[32 * rt + l32];
         float z0 = 0.f, z1 = 0.f;
@@ -485,7 +488,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
           for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
 #pragma unroll
           for (int j = 0; j < TPM; ++j) {
-            t[TPM * ks + j] = __builtin_fmaf(x[j], ref.y, t[TPM * ks + j]);
+            t[TPM * ks + j] = start ? x[j] * ref.y : __builtin_fmaf(x[j], ref.y, t[TPM * ks + j]);
             if (j & 1) z1 += x[j];
             else z0 += x[j];
             asm volatile("" : "+v"(t[TPM * ks + j]));
@@ -495,13 +498,19 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
         }
         add_z(rt, z0 + z1);
       };
+      using Y = std::true_type;
+      using N = std::false_type;
+      step(Y{}, N{}, 0, fin, out);
+      step(N{}, N{}, 1, out, fin);
+      if constexpr (!FOUR) {
 #pragma unroll 1
-      for (int rt = 0; rt + 2 < nrt; rt += 2) {
-        step(std::false_type{}, rt, fin, out);
-        step(std::false_type{}, rt + 1, out, fin);
+        for (int rt = 2; rt + 2 < nrt; rt += 2) {
+          step(N{}, N{}, rt, fin, out);
+          step(N{}, N{}, rt + 1, out, fin);
+        }
       }
-      step(std::false_type{}, nrt - 2, fin, out);
-      step(std::true_type{}, nrt - 1, out, fin);
+      step(N{}, N{}, nrt - 2, fin, out);
+      step(N{}, Y{}, nrt - 1, out, fin);
     }
     {
       const int ln = fresh(lane), key = wkey + transpose_key(ln);
@@ -567,7 +576,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   extern __shared__ uint32_t smem_u[];  // [N / 8] the largest of every four, upper 16 bits | [N / 32] a bit per key
   __shared__ __attribute__((aligned(16))) uint32_t hist[HIST];
   __shared__ uint32_t scan[2 * NW], sel[4];
-  __shared__ float s_red[3][NW];
+  __shared__ float s_red[4][NW];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = blockIdx.x;
@@ -575,7 +584,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   if (a.layer[p.l].k_l >= p.n || !sift_takes(flags_of(a, p.l, p.b), a.Hkv)) return;
   const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
   const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
-  const float* raw = a.raw + place * a.N;
+  float* raw = a.raw + place * a.N;
   const int ngroup4 = (npre + 3) / 4, nwords = (npre + 31) / 32;
   uint16_t* gmax = reinterpret_cast<uint16_t*>(smem_u);
   uint32_t* bitmap = smem_u + (a.N + 7) / 8;
@@ -590,6 +599,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   // rows: the largest and the mean ratio of the weight to its estimate
   const u64 word = tid < a.R ? a.zsum[(size_t)u * a.Rs + tid] : 0ull;
   const float omega = tid < a.R ? a.omega[(size_t)u * a.Rs + tid] : 1.f;
+  const float row_window = tid < a.R ? a.window[(size_t)u * a.Rs + tid] : 0.f;
   // the pooled scores of positions q .. q + 3, from the scores around them (P: 4-score pieces on each side)
   auto pooled4 = [&](auto PP, int q) __attribute__((always_inline)) {
     constexpr int P = decltype(PP)::value;
@@ -639,11 +649,12 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   else scan_groups(std::integral_constant<int, 2>{});
   {
     const float ratio = tid < a.R ? weight_of(a, word) / omega : 0.f;
-    float mx = ratio, sm = ratio;
+    float mx = ratio, sm = ratio, wn = row_window * weight_of(a, word);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       mx = fmaxf(mx, __shfl_xor(mx, o));
       sm += __shfl_xor(sm, o);
+      wn += __shfl_xor(wn, o);
     }
     const bool bad = __any(tid < a.R && !(ratio > 0.f && ratio < INFINITY));
     kmax = row_max_lane15(kmax);
@@ -653,16 +664,18 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
       s_red[0][wave] = mx;
       s_red[1][wave] = sm;
       s_red[2][wave] = bad ? 1.f : 0.f;
+      s_red[3][wave] = wn;
       scan[wave] = m;
     }
   }
   __syncthreads();
-  float rmax = 1.f, mean = 0.f, anybad = 0.f;
+  float rmax = 1.f, mean = 0.f, anybad = 0.f, window = 0.f;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     rmax = fmaxf(rmax, s_red[0][w]);
     mean += s_red[1][w];
     anybad += s_red[2][w];
+    window += s_red[3][w];
   }
   mean /= (float)a.R;
   if (anybad != 0.f) {
@@ -738,85 +751,81 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
     for (int j = 0; j < kSiftMaxKeys / 32 / NT; ++j)
       for (uint32_t b = bits[j]; b != 0u; b &= b - 1u) list[at++] = 32u * (uint32_t)(tid * (kSiftMaxKeys / 32 / NT) + j) + (uint32_t)__ffs((int)b) - 1u;
   }
-  // a job per kSiftJob listed keys, one at least
-  if (wave == 0) {
-    const int n = max(((int)total + kSiftJob - 1) / kSiftJob, 1);
-    int at = 0;
-    if (lane == 0) at = atomicAdd(a.njobs, n);
-    at = __builtin_amdgcn_readfirstlane(at);
-    for (int j = lane; j < n; j += 64) a.jobs[at + j] = make_int4(u, j, (int)total, __float_as_int(bound));
+  if (kk == 0) {
+    for (int t = tid; t < a.alpha; t += NT) a.layer[p.l].idx[((size_t)p.b * a.Hkv + p.g) * a.alpha + t] = npre + t;
+  }
+  if (tid == 0) {
+    a.total[u] = (int)total;
+    a.bound[u] = bound;
+    raw[npre] = (float)a.alpha - window;  // the attention to the prefix, behind the scores: for the recall of the kept set
   }
 }
 
-// ---- their exact scores; and the attention to the prefix, for the recall of the kept set ----
+// ---- their exact scores ----
+// Workgroup x takes the parts x / units, x / units + kSiftParts, ... of unit x % units.
 template <int D>
-__global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a) {
+__global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a, int units) {
   constexpr int KS = D / 16;
   using QB = QueryBlock<D, kBlockRows>;
   static_assert(kSiftJob == 32 * kW, "a tile per wave");
-  constexpr int kView = 2048, kEdge = 32;  // keys of the list that are looked at at a time, and around them
-  static_assert(sizeof(u32x4) * QueryBlock<64, kBlockRows>::SLOTS >= 8 * (kView + 2 * kEdge), "the list and its scores take the queries' place");
-  __shared__ u32x4 s_q[QB::SLOTS];
-  __shared__ float s_m[kResidentMaxRows], s_w[kResidentMaxRows], s_win[2][kResidentMaxRows], s_red[kW];
-  __shared__ int s_count[kW], s_last;
+  constexpr int kView = 4 * kT, kEdge = 32;  // keys of the list that are looked at at a time, and around them
+  constexpr int kReach = 6144;               // places that reach the bound, at most
+  constexpr int kWords = 2 * (kView + 2 * kEdge) + 2 * kReach;
+  constexpr int kSlots = 2 * QB::SLOTS > kWords / 4 ? 2 * QB::SLOTS : kWords / 4;
+  static_assert(kSiftMaxPoolW <= 17, "eight keys on each side");
+  static_assert(kWords % 4 == 0 && kEdge % 4 == 0 && kSlots * 16 + 6 * 1024 <= 80 * 1024, "two workgroups per compute unit");
+  __shared__ u32x4 s_q[kSlots];
+  __shared__ float2 s_r[kResidentMaxRows];  // minus the reference, weight
+  __shared__ uint32_t s_scan[2 * kW], s_sel[4];
+  __shared__ int s_last;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int njobs = *a.njobs;
+  const int part0 = blockIdx.x / units, u = blockIdx.x - part0 * units;
+  const uint32_t* list = a.list + (size_t)u * sift_list(a.N);
+  uint32_t q = list[min(part0 * kSiftJob + 32 * wave + l32, sift_list(a.N) - 1)];  // (not one of the list's, perhaps)
+  const int total = a.total[u];
+  const float bound = a.bound[u];
+  if (part0 * kSiftJob >= total) return;
+  const Unit p = unit_of(a, u);
+  const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
+  const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
+  float* raw = a.raw + place * a.N;
+  const uint16_t* Q = queries_of(a, p);
+  const uint16_t* K = keys_of(a, p);
+  const int jobs = (total + kSiftJob - 1) / kSiftJob;
+  QB qb;
+  auto row_at = [&](int row) { return query_row_of(a, Q, row); };
+  if (tid < a.Rs) {
+    const float m = reinterpret_cast<const float*>(a.words + (size_t)u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)];
+    s_r[tid] = make_float2(-m, tid < a.R ? weight_of(a, a.zsum[(size_t)u * a.Rs + tid]) : 0.f);
+  }
 #pragma unroll 1
-  for (int job = blockIdx.x; job < njobs; job += gridDim.x) {
-    const int4 jb = a.jobs[job];
-    const int u = __builtin_amdgcn_readfirstlane(jb.x), part = __builtin_amdgcn_readfirstlane(jb.y), total = __builtin_amdgcn_readfirstlane(jb.z);
-    const float bound = __int_as_float(__builtin_amdgcn_readfirstlane(jb.w));
-    const Unit p = unit_of(a, u);
-    const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
-    const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
-    float* raw = a.raw + place * a.N;
-    const uint16_t* Q = queries_of(a, p);
-    const uint16_t* K = keys_of(a, p);
-    const uint32_t* list = a.list + (size_t)u * sift_list(a.N);
-    QB qb;
-    auto row_at = [&](int row) { return query_row_of(a, Q, row); };
+  for (int part = part0; part < jobs; part += kSiftParts) {
     qb.request(0, row_at);
     const int e = part * kSiftJob + 32 * wave + l32;
     const bool mine = part * kSiftJob + 32 * wave < total;  // (uniform within the wave)
-    const int pos = mine ? (int)list[min(e, total - 1)] : 0;
+    if (part != part0) q = list[min(e, total - 1)];
+    const int pos = e < total ? (int)q : 0;
     bf16x8 kf[KS];
     load_rows(kf, K + (size_t)pos * a.kv_st, hf);
-    if (tid < a.Rs) {
-      s_m[tid] = reinterpret_cast<const float*>(a.words + (size_t)u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)];
-      s_w[tid] = tid < a.R ? weight_of(a, a.zsum[(size_t)u * a.Rs + tid]) : 0.f;
-    }
     f32x16 t = {};
+    int buf = 0;
 #pragma unroll 1
-    for (int row0 = 0; row0 < a.Rs; row0 += kBlockRows) {
+    for (int row0 = 0; row0 < a.Rs; row0 += kBlockRows, buf ^= 1) {
       const int ntile = min(kBlockTiles, (a.Rs - row0) / 32);
-      qb.commit(s_q);
+      qb.commit(s_q + buf * QB::SLOTS);
       __syncthreads();
       if (row0 + kBlockRows < a.Rs) qb.request(row0 + kBlockRows, row_at);
-      if (part == 0 && wave < 2 * ntile) {  // the window: a row tile and half of its keys each
-        const int wrt = wave >> 1, whalf = wave & 1, row = row0 + 32 * wrt + l32;
-        load_rows(kf, K + (size_t)min(npre + 32 * whalf + l32, p.n - 1) * a.kv_st, hf);
-        const f32x16 x = product(kf, s_q, 32 * wrt + l32, hf);
-        const int lim = min(row, a.R - 1) % a.alpha - 32 * whalf - 4 * hf;
-        const float nm = -s_m[row];
-        float y = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) y += mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(x[v], a.kappa, nm));
-        y = both_halves<false>(y);
-        if (hf == 0) s_win[whalf][row] = y;
-        load_rows(kf, K + (size_t)pos * a.kv_st, hf);
-      }
       if (mine) {
         // (products, exponentials and sums as in the kernel that scores every key, so that the scores are its to the bit)
 #pragma unroll 1
         for (int rt = 0; rt < ntile; ++rt) {
-          const f32x16 x = product(kf, s_q, 32 * rt + l32, hf);
-          const float nm = -s_m[row0 + 32 * rt + l32], w = s_w[row0 + 32 * rt + l32];
+          const f32x16 x = product(kf, s_q + buf * QB::SLOTS, 32 * rt + l32, hf);
+          const float2 ref = s_r[row0 + 32 * rt + l32];
 #pragma unroll
-          for (int v = 0; v < 16; ++v) t[v] = __builtin_fmaf(fast_exp2(__builtin_fmaf(x[v], a.kappa, nm)), w, t[v]);
+          for (int v = 0; v < 16; ++v) t[v] = __builtin_fmaf(fast_exp2(__builtin_fmaf(x[v], a.kappa, ref.x)), ref.y, t[v]);
         }
       }
-      __syncthreads();
     }
     const float s = transpose_sum(t, lane);
     const int es = part * kSiftJob + 32 * wave + transpose_key(lane);
@@ -824,75 +833,179 @@ __global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a) {
     if ((lane & 1) == 0 && es < total)  // (another workgroup may look at it before the kernel ends)
       __hip_atomic_store(raw + ps, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_waitcnt(0);  // the scores are on their way no more when the job counts as done
-    if (part == 0) {
-      float w = tid < a.R ? (s_win[0][tid] + s_win[1][tid]) * s_w[tid] : 0.f;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o);
-      if (lane == 0) s_red[wave] = w;
-    }
     __syncthreads();
-    if (tid == 0) {
-      if (part == 0) {
-        float w = 0.f;
-#pragma unroll
-        for (int i = 0; i < kW; ++i) w += s_red[i];
-        raw[npre] = (float)a.alpha - w;  // (behind the scores)
-      }
-      const int jobs = max((total + kSiftJob - 1) / kSiftJob, 1);
-      s_last = __hip_atomic_fetch_add(a.done + u, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == jobs - 1 ? 1 : 0;
-    }
+    if (tid == 0) s_last = __hip_atomic_fetch_add(a.done + u, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == jobs - 1 ? 1 : 0;
     __syncthreads();
     if (s_last == 0) continue;
-    // ---- the unit's last job: do enough positions reach the bound?  Then nothing outside the list can be kept ----
+    // ---- the unit's last job: the places whose pooled score reaches the bound, in order.  If they are enough, the kept ones
+    // are among them, and nothing outside the list is ----
     uint32_t* lpos = reinterpret_cast<uint32_t*>(s_q) + kEdge;  // [-kEdge, kView + kEdge)
     float* exact = reinterpret_cast<float*>(lpos + kView + 2 * kEdge);
+    uint32_t* qpos = reinterpret_cast<uint32_t*>(s_q) + 2 * (kView + 2 * kEdge);
+    uint32_t* qkey = qpos + kReach;
     const bool is_avg = a.pool == PKV_POOL_AVG;
     const int r = a.pool == PKV_POOL_NONE ? 0 : (a.pool_w - 1) / 2;
+    const float inv_w = 1.f / (float)a.pool_w;
+    // sums over the threads before a thread and over all of them (x: the thread's, ends with the scratch free)
+    auto scan = [&](uint32_t x, uint32_t& total) {
+      const uint32_t incl = wave_inclusive_sum(x);
+      if (lane == 63) s_scan[wave] = incl;
+      lds_barrier();
+      uint32_t before = incl - x;
+      total = 0u;
+#pragma unroll
+      for (int w = 0; w < kW; ++w) {
+        before += w < wave ? s_scan[w] : 0u;
+        total += s_scan[w];
+      }
+      lds_barrier();
+      return before;
+    };
+    uint32_t reach = 0u;
     bool odd = false;
-    int reach = 0;
 #pragma unroll 1
     for (int i0 = 0; i0 < total; i0 += kView) {
-      const int first = max(-i0, -kEdge), last = min(total - i0, kView + kEdge);
-      for (int i = first + tid; i < last; i += kT) {
-        const uint32_t q = list[i0 + i];
-        lpos[i] = q;
-        exact[i] = __hip_atomic_load(raw + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        odd = odd || !(exact[i] < INFINITY);
+      for (int i = tid - kEdge; i < kView + kEdge; i += kT) {  // (what is not there lies far away)
+        const bool there = i0 + i >= 0 && i0 + i < total;
+        const uint32_t at = there ? list[i0 + i] : i < 0 ? 0u - 1024u : 1u << 30;
+        float y = 0.f;
+        if (there) y = __hip_atomic_load(raw + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        lpos[i] = at;
+        exact[i] = y;
+        odd = odd || !(y < INFINITY);
       }
-      __syncthreads();
-      for (int i = tid; i < min(last, kView); i += kT) {
-        const int q = (int)lpos[i];
-        const int lo = min(r, q), hi = min(r, npre - 1 - q);
-        if (is_avg) {  // the window is listed whole
-          if (i - lo >= first && i + hi < last && (int)lpos[i - lo] == q - lo && (int)lpos[i + hi] == q + hi) {
-            float w = 0.f;
-            for (int x = -lo; x <= hi; ++x) w += exact[i + x];
-            reach += w >= bound * (float)a.pool_w ? 1 : 0;
-          }
-        } else if (exact[i] >= bound) {  // the places of its window that the one before it has not reached
-          int from = q - lo;
-          for (int j = i - 1; j >= first && (int)lpos[j] + r >= from; --j)
-            if (exact[j] >= bound) {
-              from = (int)lpos[j] + r + 1;
-              break;
-            }
-          reach += max(q + hi + 1 - from, 0);
+      lds_barrier();
+      // a thread takes four neighbours and what is listed around them
+      int P[20];
+      float E[20];
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        const u32x4 x = *reinterpret_cast<const u32x4*>(lpos + 4 * tid - 8 + 4 * i);
+        const f32x4 y = *reinterpret_cast<const f32x4*>(exact + 4 * tid - 8 + 4 * i);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          P[4 * i + c] = (int)x[c];
+          E[4 * i + c] = y[c];
         }
       }
-      __syncthreads();
-    }
-    if (odd) reach = -(1 << 20);
+      uint32_t key[4], mine4 = 0u;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) reach += __shfl_xor(reach, o);
-    if (lane == 0) s_count[wave] = reach;
-    __syncthreads();
-    if (tid == 0) {
-      int n = 0;
+      for (int c = 0; c < 4; ++c) {
+        const int at = P[8 + c];
+        float y = is_avg ? 0.f : E[8 + c];
+        int found = 0;
 #pragma unroll
-      for (int i = 0; i < kW; ++i) n += s_count[i];
-      if (n < kk) a.flags[place] |= 2;
+        for (int d = -8; d <= 8; ++d) {
+          if (d < -r || d > r) continue;  // (uniform)
+          const int o = P[8 + c + d] - at;
+          const bool in = o >= -r && o <= r;
+          found += in ? 1 : 0;
+          y = is_avg ? y + (in ? E[8 + c + d] : 0.f) : in ? fmaxf(y, E[8 + c + d]) : y;
+        }
+        y = is_avg ? y * inv_w : y;
+        const bool whole = !is_avg || found == min(r, at) + min(r, npre - 1 - at) + 1;  // (else the window is not listed whole)
+        key[c] = i0 + 4 * tid + c < total && whole && y >= bound ? __float_as_uint(y) : 0u;
+        mine4 += key[c] != 0u ? 1u : 0u;
+      }
+      uint32_t all;
+      uint32_t to = reach + scan(mine4, all);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (key[c] != 0u) {
+          if (to < (uint32_t)kReach) {
+            qpos[to] = (uint32_t)P[8 + c];
+            qkey[to] = key[c];
+          }
+          ++to;
+        }
+      reach += all;
+      lds_barrier();
     }
-    __syncthreads();
+    if (__any(odd) && lane == 0) s_scan[kW + wave] = 1u;
+    else if (lane == 0) s_scan[kW + wave] = 0u;
+    lds_barrier();
+    uint32_t bad = reach < (uint32_t)kk || reach > (uint32_t)kReach ? 1u : 0u;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) bad |= s_scan[kW + w];
+    if (bad != 0u) {
+      if (tid == 0) a.flags[place] |= 2;
+      return;  // (no part of the unit is left)
+    }
+    // ---- the kk-th largest of them: bins of equal width between the smallest and the largest, as long as more than 64 are in its bin ----
+    uint32_t* hist = reinterpret_cast<uint32_t*>(s_q);  // [1024] (the list is done with)
+    uint32_t lo = __float_as_uint(bound), hi = 0u, need = (uint32_t)kk, open = reach;
+    for (uint32_t i = tid; i < reach; i += kT) hi = max(hi, qkey[i]);
+    hi = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_lane63(hi), 63);
+    if (lane == 0) s_scan[wave] = hi;
+    lds_barrier();
+#pragma unroll
+    for (int w = 0; w < kW; ++w) hi = max(hi, s_scan[w]);
+    lds_barrier();
+    while (need != open && open > 64u && lo != hi) {
+      const int bits = 32 - __clz((int)(hi - lo)), sh = bits > 10 ? bits - 10 : 0;
+      reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
+      lds_barrier();
+      for (uint32_t i = tid; i < reach; i += kT)
+        if (qkey[i] >= lo && qkey[i] <= hi) atomicAdd(&hist[(hi - qkey[i]) >> sh], 1u);
+      lds_barrier();
+      const uint2 h = reinterpret_cast<uint2*>(hist)[tid];
+      uint32_t all;
+      const uint32_t before = scan(h.x + h.y, all);
+      const bool in0 = before < need && before + h.x >= need, in1 = before + h.x < need && before + h.x + h.y >= need;
+      if (in0 || in1) {
+        s_sel[0] = (uint32_t)(2 * tid + (in1 ? 1 : 0));
+        s_sel[1] = in1 ? before + h.x : before;
+        s_sel[2] = in1 ? h.y : h.x;
+      }
+      lds_barrier();
+      need -= s_sel[1];
+      open = s_sel[2];
+      hi -= s_sel[0] << sh;
+      if (((hi - lo) >> sh) != 0u) lo = hi - (1u << sh) + 1u;
+      lds_barrier();
+    }
+    uint32_t T = need == open ? lo - 1u : lo;  // (all of the bin are kept, or all are equal)
+    if (need != open && lo != hi) {
+      if (tid == 0) s_sel[3] = 0u;
+      lds_barrier();
+      for (uint32_t i = tid; i < reach; i += kT)
+        if (qkey[i] >= lo && qkey[i] <= hi) hist[atomicAdd(&s_sel[3], 1u)] = qkey[i];
+      lds_barrier();
+      if (wave == 0) {
+        const uint32_t d = lane < (int)open ? hist[lane] : 0u;
+        uint32_t above = 0u, from = 0u;
+        for (int j = 0; j < (int)open; ++j) {
+          const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)d, j);
+          above += x > d ? 1u : 0u;
+          from += x >= d ? 1u : 0u;
+        }
+        if (lane < (int)open && above < need && need <= from) s_sel[0] = d;
+      }
+      lds_barrier();
+      T = s_sel[0];
+    }
+    // ---- the kept positions in order, equal ones the lowest first; behind them the window ----
+    int32_t* idx = a.layer[p.l].idx + ((size_t)p.b * a.Hkv + p.g) * (size_t)(kk + a.alpha);
+    const uint32_t run = (reach + kT - 1) / kT, i0 = min(tid * run, reach), i1 = min(i0 + run, reach);
+    uint32_t gt = 0u, eq = 0u, all_gt, all_eq;
+    for (uint32_t i = i0; i < i1; ++i) {
+      gt += qkey[i] > T ? 1u : 0u;
+      eq += qkey[i] == T ? 1u : 0u;
+    }
+    gt = scan(gt, all_gt);
+    eq = scan(eq, all_eq);
+    const uint32_t need_eq = (uint32_t)kk - all_gt;
+    for (uint32_t i = i0; i < i1; ++i) {
+      if (qkey[i] > T) {
+        idx[gt + min(eq, need_eq)] = (int)qpos[i];
+        ++gt;
+      } else if (qkey[i] == T) {
+        if (eq < need_eq) idx[gt + eq] = (int)qpos[i];
+        ++eq;
+      }
+    }
+    for (int t = tid; t < a.alpha; t += kT) idx[kk + t] = npre + t;
+    return;
   }
 }
 
@@ -903,8 +1016,11 @@ hipError_t launch_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
   const int dev = current_device_slot();
   if (dev < 0) return hipErrorInvalidDevice;
   if (!attr_set[dev]) {  // raise the dynamic LDS limits once per device (idempotent; no allocation)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_kernel<D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sift_lds<D>(kResidentMaxRows));
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_kernel<D, true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sift_lds<D>(128));
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_kernel<D, false>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sift_lds<D>(kResidentMaxRows));
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(sift_list_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
     if (e != hipSuccess) return e;
@@ -914,15 +1030,15 @@ hipError_t launch_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
   hipLaunchKernelGGL((sift_prepare_kernel<D>), dim3(units * a.groups), dim3(kT), 0, s, a, clear_err ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((score_sift_kernel<D>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
+  if (a.Rs == 128) hipLaunchKernelGGL((score_sift_kernel<D, true>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
+  else hipLaunchKernelGGL((score_sift_kernel<D, false>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = (size_t)((a.N + 7) / 8 + (a.N + 31) / 32) * 4;
   hipLaunchKernelGGL(sift_list_kernel, dim3(units), dim3(NT), lds, s, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t jobs = (int64_t)units * (sift_list(a.N) / kSiftJob);
-  hipLaunchKernelGGL((sift_exact_kernel<D>), dim3(jobs < kSiftExactGrid ? (unsigned)jobs : kSiftExactGrid), dim3(kT), 0, s, a);
+  hipLaunchKernelGGL((sift_exact_kernel<D>), dim3(units * kSiftParts), dim3(kT), 0, s, a, units);
   return hipGetLastError();
 }
 
