@@ -41,7 +41,7 @@ namespace {
 constexpr int kW = 8, kT = kW * 64;   // waves and threads of the kernel that reads K
 constexpr int kPass = 32 * kW;        // keys of a pass
 constexpr u64 kZBad = 1ull << 63;     // an item's sum does not fit
-constexpr int kBlockRows = 128, kBlockTiles = kBlockRows / 32;  // query rows that lie in LDS at a time where keys are scored exactly
+constexpr int kBlockRows = 128, kBlockTiles = kBlockRows / 32;  // query rows that lie in LDS at a time, but for the pass over K
 constexpr int kSiftParts = 8;  // workgroups per unit there
 
 // A unit's place: layer entry, sequence, head, valid length.
@@ -74,9 +74,9 @@ __device__ __forceinline__ void load_rows(bf16x8 (&f)[KS], const uint16_t* row, 
   for (int ks = 0; ks < KS; ++ks) f[ks] = as_frag(*reinterpret_cast<const u32x4*>(p + 32 * ks));
 }
 
-// Queries of ROWS rows in LDS: rows of D / 8 + 1 sixteen-byte slots (bank-free).
+// ROWS rows of D elements on their way into LDS: rows of D / 8 + 1 sixteen-byte slots there (bank-free).
 template <int D, int ROWS>
-struct QueryBlock {
+struct RowBlock {
   static constexpr int SEG = D / 8, PITCH = SEG + 1, PER = ROWS * SEG / kT, SLOTS = ROWS * PITCH;
   u32x4 v[PER];
   template <class Row>
@@ -102,6 +102,15 @@ __device__ __forceinline__ const uint16_t* query_row_of(const SiftArgs& a, const
 }
 // Logits of 32 keys (rows) and the 32 queries from `row` on of such a block.
 template <int KS>
+__device__ __forceinline__ f32x16 product_of(const u32x4* s_k, int key, const u32x4* s_q, int row, int hf) {
+  const u32x4 *k = s_k + key * (2 * KS + 1) + hf, *q = s_q + row * (2 * KS + 1) + hf;
+  f32x16 x = {};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) x = PKV_MFMA32(as_frag(k[2 * ks]), as_frag(q[2 * ks]), x);
+  __builtin_amdgcn_sched_barrier(0);  // (one product's operands at a time)
+  return x;
+}
+template <int KS>
 __device__ __forceinline__ f32x16 product(const bf16x8 (&k)[KS], const u32x4* s_q, int row, int hf) {
   const u32x4* q = s_q + row * (2 * KS + 1) + hf;
   f32x16 x = {};
@@ -111,72 +120,76 @@ __device__ __forceinline__ f32x16 product(const bf16x8 (&k)[KS], const u32x4* s_
   return x;
 }
 
-// ---- estimates of the normalisers of 64 rows of a unit; with its first rows, whether it is worth it ----
+// ---- estimates of the normalisers of 128 rows of a unit; with its first rows, whether it is worth it ----
+// What bounds it: latencies, and the address units, which take a fragment's 32 rows one by one.  So queries and the keys that
+// several waves multiply come through LDS (256 units of 128 rows 31 -> 26 us, 640 of 512 rows 154 -> 98, against 64 rows per
+// workgroup and every key as fragments from memory).
 template <int D>
 __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, int clear_err) {
   constexpr int KS = D / 16;
-  using QB = QueryBlock<D, 64>;
-  __shared__ u32x4 s_q[QB::SLOTS];
-  __shared__ float s_m[64], s_x0[64], s_o[64], s_part[kW][64], s_win[2][64], s_score[32 * kW];
+  using QB = RowBlock<D, kBlockRows>;
+  __shared__ u32x4 s_q[QB::SLOTS], s_k[QB::SLOTS];  // queries; 64 keys for the references and 64 of the window
+  __shared__ float s_m[kBlockRows], s_x0[kBlockRows], s_o[kBlockRows], s_part[kW][kBlockRows], s_win[2][kBlockRows], s_score[32 * kW];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int u = blockIdx.x / a.groups, row0 = 64 * (blockIdx.x - u * a.groups);
+  const int blocks = (a.Rs + kBlockRows - 1) / kBlockRows, u = blockIdx.x / blocks, row0 = kBlockRows * (blockIdx.x - u * blocks);
+  const int rows = min(kBlockRows, a.Rs - row0), ntile = rows / 32;
   if (blockIdx.x == 0 && tid == 0 && clear_err) a.err[0] = a.err[1] = 0;
   const Unit p = unit_of(a, u);
   const bool whole = a.layer[p.l].k_l >= p.n;
   const int npre = whole ? 1 : p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
   const uint16_t* Q = queries_of(a, p);
   const uint16_t* K = keys_of(a, p);
-  const int half = wave & 1, rt = (wave >> 1) & 1;  // of the reference and window keys: the tile; of the rows
-  bf16x8 kf[2][KS], kx[KS];
-  QB qb;
+  bf16x8 kf[2][KS];
+  QB qb, kb;
   // The sample: wave w's group of keys is spread evenly over the prefix in runs of eight neighbours, four to a tile.
   auto sample = [&](int tile, bf16x8 (&f)[KS]) {
     const uint32_t run = (uint32_t)((4 * tile + (l32 >> 3)) * kW + wave);
     load_rows(f, K + (size_t)min((int)((uint32_t)npre * run >> a.sample_shift) + (l32 & 7), npre - 1) * a.kv_st, hf);
   };
   if (!whole) {
-    qb.request(row0, [&](int row) { return query_row_of(a, Q, row); });
     // references: the largest logit of 64 keys, eight neighbours each at eight places, key 0 among them
-    if (wave < 4) load_rows(kx, K + (size_t)min((int)((uint32_t)npre * (uint32_t)(4 * half + (l32 >> 3)) >> 3) + (l32 & 7), npre - 1) * a.kv_st, hf);
-    else load_rows(kx, K + (size_t)min(npre + 32 * half + l32, p.n - 1) * a.kv_st, hf);  // window keys
+    kb.request(0, [&](int i) { return K + (size_t)(i < 64 ? min((int)((uint32_t)npre * (uint32_t)(i >> 3) >> 3) + (i & 7), npre - 1) : min(npre + i - 64, p.n - 1)) * a.kv_st; });
+    qb.request(row0, [&](int row) { return query_row_of(a, Q, row); });
     sample(0, kf[0]);
     sample(1, kf[1]);
   }
   // the words of the kernel that takes the other sequences
-  u64* words = a.words + (size_t)blockIdx.x * (kLagGroupBytes / 8);
-  if (tid < kLagGroupBytes / 8 && ((tid & 31) < kLagRefs || (tid & 31) >= kLagMax)) words[tid] = 0;
-  if (a.words4 && tid < kLagGroupBytes4 / 8) a.words4[(size_t)blockIdx.x * (kLagGroupBytes4 / 8) + tid] = 0;
+  const size_t group0 = (size_t)u * a.groups + row0 / 64;
+  u64* words = a.words + group0 * (kLagGroupBytes / 8);
+  if (tid < rows * (kLagGroupBytes / 512) && ((tid & 31) < kLagRefs || (tid & 31) >= kLagMax)) words[tid] = 0;
+  if (a.words4 && tid < rows) a.words4[group0 * (kLagGroupBytes4 / 8) + tid] = 0;
   int32_t* flag = a.flags + (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
   if (row0 == 0 && tid == 0) a.done[u] = a.total[u] = 0;
   if (whole) {
     if (row0 == 0 && tid == 0) *flag = 0;
     return;
   }
+  kb.commit(s_k);
   qb.commit(s_q);
   __syncthreads();
-  f32x16 xw;  // logits of the wave's reference or window keys
-  {
-    xw = product(kx, s_q, 32 * rt + l32, hf);
-    if (wave < 4) {
-      float m = xw[0];
+  const int half = wave & 1, rt = wave >> 1;  // of the reference and window keys: the tile; of the rows
+  f32x16 xw;  // logits of the wave's window keys
+  if (rt < ntile) {
+    const f32x16 x = product_of<KS>(s_k, 32 * half + l32, s_q, 32 * rt + l32, hf);
+    float m = x[0];
 #pragma unroll
-      for (int v = 1; v < 16; ++v) m = fmaxf(m, xw[v]);
-      m = both_halves<true>(m) * a.kappa;
-      if (hf == 0) {
-        s_part[half][32 * rt + l32] = m;
-        if (half == 0) s_x0[32 * rt + l32] = xw[0] * a.kappa;
-      }
+    for (int v = 1; v < 16; ++v) m = fmaxf(m, x[v]);
+    m = both_halves<true>(m) * a.kappa;
+    if (hf == 0) {
+      s_part[half][32 * rt + l32] = m;
+      if (half == 0) s_x0[32 * rt + l32] = x[0] * a.kappa;
     }
+    xw = product_of<KS>(s_k, 64 + 32 * half + l32, s_q, 32 * rt + l32, hf);
   }
   __syncthreads();
-  if (tid < 64) {
+  if (tid < rows) {
     const float m = fmaxf(s_part[0][tid], s_part[1][tid]);
     s_m[tid] = m;
     reinterpret_cast<float*>(words)[lag_half_word(kLagRefs, tid)] = m;
   }
   __syncthreads();
-  if (wave >= 4) {
+  if (rt < ntile) {
     const int lim = min(row0 + 32 * rt + l32, a.R - 1) % a.alpha - 32 * half - 4 * hf;  // last window key the lane's query sees
     const float nm = -s_m[32 * rt + l32];
     float y = 0.f;
@@ -185,7 +198,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     y = both_halves<false>(y);
     if (hf == 0) s_win[half][32 * rt + l32] = y;
   }
-  float z[2] = {0.f, 0.f};
+  float z[kBlockTiles] = {};
 #pragma unroll 1
   for (int tile = 0; tile < a.sample_tiles; tile += 2) {
     if (tile > 0) {
@@ -193,7 +206,8 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
       sample(tile + 1, kf[1]);
     }
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < kBlockTiles; ++q) {
+      if (q >= ntile) continue;  // (uniform)
       const float nm = -s_m[32 * q + l32];
       float z0 = 0.f, z1 = 0.f;
 #pragma unroll
@@ -209,12 +223,12 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     }
   }
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < kBlockTiles; ++q) {
     const float y = both_halves<false>(z[q]);
     if (hf == 0) s_part[wave][32 * q + l32] = y;
   }
   __syncthreads();
-  if (tid < 64) {
+  if (tid < rows) {
     // half the sum of the two middle ones of the groups: a rare large key does not count
     float v[kW], mid = 0.f;
 #pragma unroll
@@ -423,6 +437,15 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   bool first = true;  // pass of an item
   int zbuf = 0;       // table in use
   u64 sum = 0;        // of the thread's row over the unit's items so far
+  // With four row tiles a lane's references and estimates, and its sums over an item, stay in registers.
+  float2 ref4[4];
+  float z4[4] = {0.f, 0.f, 0.f, 0.f};
+  auto load_refs = [&]() {
+    if constexpr (FOUR) {
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt) ref4[rt] = s_r[32 * rt + l32];
+    }
+  };
   auto prime = [&](const bf16x8 (&kc)[KS]) {  // the first product of a pass
     fin = f32x16{};
 #pragma unroll
@@ -440,9 +463,9 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     const int wkey = cur.key + 32 * wave, npre = cur.n - a.alpha;
     f32x16 t;
     float* zp = z_lane + zbuf * kW * a.Rs;
-    auto add_z = [&](int rt, float z) {  // (the sums of an item come about as in the kernel that scores the other sequences)
-      z = both_halves<false>(z);
-      if (!first) z += zp[32 * rt];
+    // (the sums of an item come about as in the kernel that scores the other sequences)
+    auto z_before = [&](int rt) { return first ? 0.f : zp[32 * rt]; };
+    auto set_z = [&](int rt, float z) {
       if (hf == 0) zp[32 * rt] = z;
     };
     if (__builtin_expect(wkey + 32 > npre, 0)) {
@@ -451,6 +474,13 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
 #pragma unroll 1
       for (int rt = 0; rt < nrt; ++rt) {
         const float2 ref = s_r[32 * rt + l32];
+        float before = 0.f;
+        if constexpr (FOUR) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) before = rt == i ? z4[i] : before;
+        } else {
+          before = z_before(rt);
+        }
         const int lim = npre + (32 * rt + l32) % a.alpha - wkey - 4 * hf;  // last key the lane's query sees
         float z0 = 0.f, z1 = 0.f;
         f32x16 x = {};
@@ -463,16 +493,32 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
           else z0 += y;
           t[v] = __builtin_fmaf(y, ref.y, t[v]);
         }
-        add_z(rt, z0 + z1);
+        const float z = both_halves<false>(z0 + z1) + before;
+        if constexpr (FOUR) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) z4[i] = rt == i ? z : z4[i];
+        } else {
+          set_z(rt, z);
+        }
       }
       if (has_next && nxt.u == cur.u) prime(kn);
     } else {
       // Product of row tile rt + 1 (LAST: of the next pass's keys and row tile 0) goes into `nx` while `fi`, that of row
       // tile rt, turns into exponentials.
+      float2 ref_next = make_float2(0.f, 0.f);
+      if constexpr (!FOUR) ref_next = s_r[l32];
       auto step = [&](auto FIRST, auto LAST, int rt, const f32x16& fi, f32x16& nx) {
         constexpr bool start = decltype(FIRST)::value, last = decltype(LAST)::value;
         const int mul = last ? 0 : rt + 1, then = last ? 1 : rt + 2 < nrt ? rt + 2 : 0;
-        const float2 ref = s_r[32 * rt + l32];
+        float2 ref;
+        float before = 0.f;
+        if constexpr (FOUR) {
+          ref = ref4[rt];
+        } else {  // (what the next step needs at its beginning, and this one at its end)
+          ref = ref_next;
+          if (!last) ref_next = s_r[32 * (rt + 1) + l32];
+          before = z_before(rt);
+        }
         float z0 = 0.f, z1 = 0.f;
         nx = f32x16{};
 #pragma unroll
@@ -496,7 +542,9 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
           asm volatile("" : "+v"(z0), "+v"(z1));
           __builtin_amdgcn_sched_barrier(0);
         }
-        add_z(rt, z0 + z1);
+        const float z = both_halves<false>(z0 + z1);
+        if constexpr (FOUR) z4[rt] += z;
+        else set_z(rt, before + z);
       };
       using Y = std::true_type;
       using N = std::false_type;
@@ -520,6 +568,13 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     const bool unit_ends = !has_next || nxt.u != cur.u;
     first = unit_ends || nxt.key % kLagKeys == 0;
     if (first) {  // the item's sums
+      if constexpr (FOUR) {
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+          if (hf == 0) zp[32 * rt] = z4[rt];
+          z4[rt] = 0.f;
+        }
+      }
       lds_barrier();
       if (tid < a.R) {
         const float* z8 = s_z + zbuf * kW * a.Rs + tid;
@@ -543,6 +598,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
       if (has_next) {  // (every wave is done with the unit's queries: the barrier above)
         stage(nxt);
         lds_barrier();
+        load_refs();
         prime(kn);
       }
     }
@@ -557,6 +613,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   lds_barrier();  // (the first item's place has been read)
   stage(cur);
   lds_barrier();
+  load_refs();
   prime(b0);
 #pragma unroll 1
   for (;;) {
@@ -600,6 +657,16 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   const u64 word = tid < a.R ? a.zsum[(size_t)u * a.Rs + tid] : 0ull;
   const float omega = tid < a.R ? a.omega[(size_t)u * a.Rs + tid] : 1.f;
   const float row_window = tid < a.R ? a.window[(size_t)u * a.Rs + tid] : 0.f;
+  // the pooled score of the middle one, M scores on each side at hand
+  auto pooled_of = [&](const float* x, int at, auto M) __attribute__((always_inline)) {
+    float acc = x[at];
+#pragma unroll
+    for (int o = 1; o <= decltype(M)::value; ++o) {
+      if (o > r) break;  // (uniform)
+      acc = is_avg ? acc + (x[at - o] + x[at + o]) : fmaxf(acc, fmaxf(x[at - o], x[at + o]));
+    }
+    return is_avg ? acc * inv_w : acc;
+  };
   // the pooled scores of positions q .. q + 3, from the scores around them (P: 4-score pieces on each side)
   auto pooled4 = [&](auto PP, int q) __attribute__((always_inline)) {
     constexpr int P = decltype(PP)::value;
@@ -617,36 +684,76 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
     }
     f32x4 y;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float acc = x[4 * P + c];
-#pragma unroll
-      for (int o = 1; o <= 4 * P; ++o) {
-        if (o > r) break;  // (uniform)
-        const float lo = x[4 * P + c - o], hi = x[4 * P + c + o];
-        acc = is_avg ? acc + (lo + hi) : fmaxf(acc, fmaxf(lo, hi));
-      }
-      y[c] = is_avg && P > 0 ? acc * inv_w : acc;
-    }
+    for (int c = 0; c < 4; ++c) y[c] = P > 0 ? pooled_of(x, 4 * P + c, std::integral_constant<int, 4 * P>{}) : x[c];
     return y;
   };
   reinterpret_cast<uint2*>(hist)[tid] = make_uint2(0u, 0u);
   for (int i = tid; i < nwords; i += NT) bitmap[i] = 0u;
   // ---- A. the largest estimated pooled score of every four neighbours ----
   uint32_t kmax = 0u;
-  auto scan_groups = [&](auto PP) __attribute__((always_inline)) {
-#pragma unroll 2
-    for (int i = tid; i < ngroup4; i += NT) {
-      const f32x4 y = pooled4(PP, 4 * i);
-      uint32_t m = 0u;
+  auto note = [&](int i, const f32x4& y) {
+    uint32_t m = 0u;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) m = max(m, 4 * i + c < npre ? __float_as_uint(y[c]) : 0u);
-      kmax = max(kmax, m);
-      gmax[i] = (uint16_t)(m >> 16);
-    }
+    for (int c = 0; c < 4; ++c) m = max(m, 4 * i + c < npre ? __float_as_uint(y[c]) : 0u);
+    kmax = max(kmax, m);
+    gmax[i] = (uint16_t)(m >> 16);
   };
-  if (r == 0) scan_groups(std::integral_constant<int, 0>{});
-  else if (r <= 4) scan_groups(std::integral_constant<int, 1>{});
-  else scan_groups(std::integral_constant<int, 2>{});
+  if (r <= 4) {
+    // A wave takes 256 neighbouring groups at a time, lane l those from l on, 64 apart: what lies beside a lane's four scores is
+    // with its neighbours, but for the first and the last lane's.  The next 256 are under way.
+    auto quad = [&](int q) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (q >= 0 && q + 4 <= npre) v = *reinterpret_cast<const f32x4_u*>(raw + q);
+      else if (q >= 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (q + c < npre) v[c] = raw[q + c];
+      }
+      return v;
+    };
+    struct Batch {
+      f32x4 v[4], e;
+    };
+    auto load = [&](int g0) {
+      Batch x;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x.v[j] = quad(4 * (g0 + 64 * j + lane));
+      x.e = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (r > 0 && (lane == 0 || lane == 63)) x.e = quad(lane == 0 ? 4 * g0 - 4 : 4 * (g0 + 256));
+      return x;
+    };
+#define PKV_DPP(old, src, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), ctrl, 0xF, 0xF, false))
+    auto work = [&](int g0, const Batch& x) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f32x4 y = x.v[j];
+        if (r > 0) {
+          float at[12];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const float first = j == 0 ? x.e[c] : PKV_DPP(0.f, x.v[j == 0 ? 0 : j - 1][c], 0x13C);  // wave_ror:1
+            const float last = j == 3 ? x.e[c] : PKV_DPP(0.f, x.v[j == 3 ? 3 : j + 1][c], 0x134);   // wave_rol:1
+            at[c] = PKV_DPP(first, x.v[j][c], 0x138);     // wave_shr:1
+            at[4 + c] = x.v[j][c];
+            at[8 + c] = PKV_DPP(last, x.v[j][c], 0x130);  // wave_shl:1
+          }
+#pragma unroll
+          for (int c = 0; c < 4; ++c) y[c] = pooled_of(at, 4 + c, std::integral_constant<int, 4>{});
+        }
+        if (g0 + 64 * j + lane < ngroup4) note(g0 + 64 * j + lane, y);
+      }
+    };
+#undef PKV_DPP
+    Batch one = load(256 * wave), two;
+    for (int g0 = 256 * wave; g0 < ngroup4; g0 += 512 * NW) {  // (uniform within the wave)
+      two = load(g0 + 256 * NW);
+      work(g0, one);
+      one = load(g0 + 512 * NW);
+      work(g0 + 256 * NW, two);
+    }
+  } else {
+    for (int i = tid; i < ngroup4; i += NT) note(i, pooled4(std::integral_constant<int, 2>{}, 4 * i));
+  }
   {
     const float ratio = tid < a.R ? weight_of(a, word) / omega : 0.f;
     float mx = ratio, sm = ratio, wn = row_window * weight_of(a, word);
@@ -687,17 +794,26 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   if (kk > 0) {  // (uniform)
     // ---- B. what about kk positions reach, and the estimates down to which a key can be kept then ----
     const KeyBins<HIST> bins{(uint32_t)__builtin_amdgcn_readlane((int)row_max_lane15(scan[lane & 15]), 15)};
+    // (those four binades and more below the reference, nearly all, only if the others are not enough)
+    const uint32_t low = bins.ref > (4u << 23) ? bins.ref - (4u << 23) : 0u;
     for (int i = tid; i < ngroup4; i += NT) {
       const uint32_t m = (uint32_t)gmax[i] << 16;
-      if (m != 0u) atomicAdd(&hist[bins.of(m)], 1u);
+      if (m != 0u && m >= low) atomicAdd(&hist[bins.of(m)], 1u);
     }
     __syncthreads();
     // (a pooling window's largest score fills 4 w / (w + 3) places of a group it reaches, on average; whether this was enough
     // is seen at the end)
     const uint32_t want = min((uint32_t)kk, (uint32_t)((float)(kk * (2 * r + 4)) * (kSiftRank / (float)(8 * r + 4))) + 4u);
-    if (find_bin(hist, want, scan + NW, sel) < want) {
-      fail();
-      return;
+    if (find_bin(hist, want, scan + NW, sel) < want) {  // (uniform; it leaves the bins cleared)
+      for (int i = tid; i < ngroup4; i += NT) {
+        const uint32_t m = (uint32_t)gmax[i] << 16;
+        if (m != 0u) atomicAdd(&hist[bins.of(m)], 1u);
+      }
+      __syncthreads();
+      if (find_bin(hist, want, scan + NW, sel) < want) {
+        fail();
+        return;
+      }
     }
     const float edge = __uint_as_float(bins.lower_edge(__builtin_amdgcn_readfirstlane(sel[0])));
     const float tau = edge * fminf(1.f, kSiftSlack * mean / rmax);
@@ -708,9 +824,22 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
     }
     // ---- C. the positions whose scores can matter: the windows of the pooled scores from tau on ----
     const uint32_t tau16 = __float_as_uint(tau) >> 16;
-    for (int i = tid; i < ngroup4; i += NT) {
-      if (gmax[i] < tau16) continue;
-      const int q = 4 * i;
+    uint16_t* hit = reinterpret_cast<uint16_t*>(hist);  // groups that reach it, in any order
+    if (tid == 0) sel[3] = 0u;
+    __syncthreads();
+    for (int i = tid; i < ngroup4; i += NT)
+      if (gmax[i] >= tau16) {
+        const uint32_t at = atomicAdd(&sel[3], 1u);
+        if (at < 2u * HIST) hit[at] = (uint16_t)i;
+      }
+    __syncthreads();
+    const int hits = (int)sel[3];
+    if (hits > 2 * HIST) {
+      fail();
+      return;
+    }
+    for (int h = tid; h < hits; h += NT) {
+      const int q = 4 * (int)hit[h];
       // from the first to the last of the four that reaches it (max: by its own score)
       const f32x4 y = !is_avg || r == 0 ? pooled4(std::integral_constant<int, 0>{}, q) : r <= 4 ? pooled4(std::integral_constant<int, 1>{}, q) : pooled4(std::integral_constant<int, 2>{}, q);
       int first = 4, last = -1;
@@ -766,7 +895,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
 template <int D>
 __global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a, int units) {
   constexpr int KS = D / 16;
-  using QB = QueryBlock<D, kBlockRows>;
+  using QB = RowBlock<D, kBlockRows>;
   static_assert(kSiftJob == 32 * kW, "a tile per wave");
   constexpr int kView = 4 * kT, kEdge = 32;  // keys of the list that are looked at at a time, and around them
   constexpr int kReach = 6144;               // places that reach the bound, at most
@@ -1027,7 +1156,7 @@ hipError_t launch_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
     attr_set[dev] = true;
   }
   const int units = a.L * a.B * a.Hkv;
-  hipLaunchKernelGGL((sift_prepare_kernel<D>), dim3(units * a.groups), dim3(kT), 0, s, a, clear_err ? 1 : 0);
+  hipLaunchKernelGGL((sift_prepare_kernel<D>), dim3(units * ((a.Rs + kBlockRows - 1) / kBlockRows)), dim3(kT), 0, s, a, clear_err ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.Rs == 128) hipLaunchKernelGGL((score_sift_kernel<D, true>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
