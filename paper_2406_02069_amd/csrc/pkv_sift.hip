@@ -287,6 +287,358 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   }
 }
 
+// ---- the pass over K ----
+// A pass of a workgroup (all fields wave-uniform): keys from `key` on of unit u.
+struct Pass {
+  int u, n, key, left;  // left: items of this workgroup behind this one
+  const uint16_t* K;
+};
+__device__ __forceinline__ float* scores_of(const SiftArgs& a, int u) {
+  const Unit x = unit_of(a, u);
+  return a.raw + ((size_t)a.layer[x.l].slot * a.B * a.Hkv + (size_t)x.b * a.Hkv + x.g) * a.N;
+}
+// Keys and length of unit p.u; false: the unit is not sifted.
+__device__ __forceinline__ bool open_unit(const SiftArgs& a, Pass& p, bool known) {
+  const Unit x = unit_of(a, p.u);
+  p.n = x.n;
+  p.K = keys_of(a, x);
+  return known || (a.layer[x.l].k_l < x.n && sift_takes(flags_of(a, x.l, x.b), a.Hkv));
+}
+// The pass after p, of KEYS keys; false if there is none (p is then a pass over the unit's first key alone).
+template <int KEYS>
+__device__ __forceinline__ bool advance(const SiftArgs& a, Pass& p) {
+  p.key += KEYS;
+  if (p.key % kLagKeys != 0 && p.key < p.n) return true;
+  if (p.left == 0) {
+    p.key = 0;
+    p.n = 1;
+    return false;
+  }
+  --p.left;
+  if (p.key >= p.n) {
+    do ++p.u;
+    while (!open_unit(a, p, false));  // (there is one: an item is left)
+    p.key = 0;
+  }
+  return true;
+}
+// The workgroup's first pass; false if it has none.  wsum: kW + 2 words of LDS, read before the next barrier.
+__device__ __forceinline__ bool first_pass(const SiftArgs& a, Pass& p, int* wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // wsum: [kW] sums of the waves, [kW], [kW + 1] the first item's place
+  const int E = a.L * a.B;
+  int lo = 0, hi = 0, u0 = 0, c0 = 0;
+  int c = 0, parts = 0, before = 0;
+  for (int round = 0; round < 2; ++round) {  // how many items there are; then who owns the first one
+    int run = 0;
+    for (int e0 = 0; e0 < E; e0 += kT) {
+      const int e = e0 + tid;
+      if (round == 0 || E > kT) {  // (else the first round's are still there)
+        c = parts = 0;
+        if (e < E) {
+          const int l = e / a.B, b = e - l * a.B, n = valid_length(a, b);
+          parts = a.layer[l].k_l < n && sift_takes(flags_of(a, l, b), a.Hkv) ? (n + kLagKeys - 1) / kLagKeys : 0;
+          c = a.Hkv * parts;
+        }
+        int v = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int x = __shfl_up(v, o);
+          if (lane >= o) v += x;
+        }
+        lds_barrier();
+        if (lane == 63) wsum[wave] = v;
+        lds_barrier();
+        before = run + v - c;
+#pragma unroll
+        for (int w = 0; w < kW; ++w) {
+          before += w < wave ? wsum[w] : 0;
+          run += wsum[w];
+        }
+      }
+      if (round == 1 && lo >= before && lo < before + c) {
+        const int rem = lo - before, g = rem / parts;
+        wsum[kW] = e * a.Hkv + g;
+        wsum[kW + 1] = rem - g * parts;
+      }
+    }
+    if (round == 0) {
+      if (run == 0) return false;
+      lo = (int)((int64_t)blockIdx.x * run / gridDim.x);
+      hi = (int)((int64_t)(blockIdx.x + 1) * run / gridDim.x);
+    }
+  }
+  lds_barrier();
+  p.left = hi - lo;
+  if (p.left == 0) return false;
+  u0 = __builtin_amdgcn_readfirstlane(wsum[kW]);
+  c0 = __builtin_amdgcn_readfirstlane(wsum[kW + 1]);
+  --p.left;
+  p.u = u0;
+  p.key = c0 * kLagKeys;
+  (void)open_unit(a, p, true);
+  return true;
+}
+
+// A row's sum over a workgroup's items of a unit.
+__device__ __forceinline__ void add_sum(const SiftArgs& a, int u, int row, u64 sum) {
+  u64* z = a.zsum + (size_t)u * a.Rs + row;
+  if (sum & kZBad) (void)__hip_atomic_fetch_or(z, kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  (void)__hip_atomic_fetch_add(z, sum & ~kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// 65 to 128 rows: they lie in the registers of every wave as matrix operands, and K comes through LDS.  A wave requests its tile two
+// passes ahead, whole rows at a time and past the registers, and reads each fragment once, behind the last product that needs its
+// predecessor: a pass reads 8 KB of LDS per wave instead of 32 for the queries, and a request of 64 lanes touches 4 rows instead of 32.
+template <int D>
+struct FewRows {
+  static constexpr int ROWS = 128, TILES = ROWS / 32;
+  static constexpr int SEG = D / 8, TILE = 32 * SEG;   // sixteen-byte slots of a key and of a wave's tile
+  static constexpr int PER = 64 / SEG, LOADS = TILE / 64;  // keys of a request, requests of a tile
+  static constexpr int QROWS = 64, QPITCH = SEG + 1;   // queries on their way into the registers
+  static constexpr size_t kLds = (size_t)(2 * kW * TILE + QROWS * QPITCH) * 16 + ROWS * 8 + 3 * kW * ROWS * 4;
+};
+static_assert(FewRows<128>::kLds <= 160 * 1024, "one workgroup per compute unit");
+
+template <int D>
+__global__ __launch_bounds__(kT, 2) void score_sift_few_kernel(const SiftArgs a) {
+  using F = FewRows<D>;
+  constexpr int KS = D / 16, SEG = F::SEG, NRT = F::TILES;
+  constexpr int TPM = 16 / KS;  // logits per lane handled between two matrix instructions
+  extern __shared__ u32x4 smem[];
+  u32x4* s_q = smem + 2 * kW * F::TILE;
+  float2* s_r = reinterpret_cast<float2*>(s_q + F::QROWS * F::QPITCH);  // [ROWS] minus the reference, estimated weight
+  float* s_z = reinterpret_cast<float*>(s_r + F::ROWS);                  // [2][kW][ROWS] sums by wave, in turn
+
+  float* s_end = s_z + 2 * kW * F::ROWS;                                 // [kW][ROWS] a wave's sums behind a unit's end
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    u32x4* s_k = smem + wave * 2 * F::TILE;  // [2][32] keys, slot s of key i at s ^ (i % SEG) (bank-free)
+  const uint32_t s_k_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_k);
+
+  Pass cur;
+  if (!first_pass(a, cur, reinterpret_cast<int*>(s_z))) return;
+
+  // Requests the wave's tile of a pass.  Keys at or beyond n are replaced by the last one.  Nothing of the buffer is being read.
+  auto request = [&](const Pass& p, auto BUF) __attribute__((always_inline)) {
+    const uint32_t stride = (uint32_t)a.kv_st * 2u;
+    const int ln = fresh(lane), row = ln / SEG;
+    const uint32_t seg16 = (uint32_t)((ln % SEG) ^ row) * 16u;
+    const int key0 = min(p.key + 32 * wave, p.n - 1), last = p.n - 1 - key0;
+    const char* base = reinterpret_cast<const char*>(p.K) + (uint64_t)(uint32_t)key0 * stride;
+    uint32_t to0 = s_k_at;
+    asm volatile("" : "+s"(to0));  // (not one register for each request all through the loop)
+    auto go = [&](int j, const char* from, uint32_t row_at) __attribute__((always_inline)) {
+      const uint32_t to = to0 + (uint32_t)(decltype(BUF)::value * F::TILE + 64 * j) * 16u;
+      const uint32_t at = row_at + (seg16 ^ (F::PER * j & (SEG - 1)) * 16u);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(at), "s"(from) : "memory");
+    };
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (__builtin_expect(last >= 31, 1)) {
+      const uint32_t row_at = __umul24(row, stride);
+#pragma unroll
+      for (int j = 0; j < F::LOADS; ++j) go(j, base + (uint64_t)(F::PER * j) * stride, row_at);
+    } else {
+#pragma unroll
+      for (int j = 0; j < F::LOADS; ++j) go(j, base, __umul24((uint32_t)min(F::PER * j + row, last), stride));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the tile before the one requested last is there
+  auto arrived = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(F::LOADS) : "memory");
+  };
+  typedef const __attribute__((address_space(3))) u32x4* lds_slots;
+  const uint32_t k_lane = s_k_at + (uint32_t)((lane & 31) * SEG + ((lane >> 5) ^ (lane & (SEG - 1)))) * 16u;
+  auto key_frag = [&](auto BUF, int ks) __attribute__((always_inline)) {
+    return as_frag(reinterpret_cast<lds_slots>((uint32_t)fresh((int)k_lane) ^ (32u * ks))[decltype(BUF)::value * F::TILE]);
+  };
+
+  bf16x8 q[NRT - 1][KS], ql[3], kc[KS];  // queries but for the last row tile's, and a part of those
+  float2 ref[NRT];
+  float z[NRT] = {};
+  f32x16 fin, out;  // products of even and of odd row tiles
+  float* raw;  // the unit's scores
+  // Queries, references and estimates of a unit.
+  auto stage = [&](const Pass& p) __attribute__((always_inline)) {
+    const uint16_t* Q = queries_of(a, unit_of(a, p.u));
+    raw = scores_of(a, p.u);
+    constexpr int N = F::QROWS * SEG / kT;
+    const int tid = fresh(threadIdx.x), l32 = tid & 31, hf = tid >> 5 & 1;
+    if (tid < F::ROWS)
+      s_r[tid] = make_float2(-reinterpret_cast<const float*>(a.words + (size_t)p.u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)],
+                             a.omega[(size_t)p.u * a.Rs + tid]);
+#pragma unroll
+    for (int h = 0; h < F::ROWS / F::QROWS; ++h) {
+      u32x4 v[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int j = tid + i * kT;
+        v[i] = *reinterpret_cast<const u32x4*>(query_row_of(a, Q, F::QROWS * h + j / SEG) + 8 * (j % SEG));
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int j = tid + i * kT;
+        s_q[j / SEG * F::QPITCH + j % SEG] = v[i];
+      }
+      lds_barrier();
+#pragma unroll
+      for (int rt = 0; rt < F::QROWS / 32; ++rt)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          if (F::QROWS / 32 * h + rt < NRT - 1) q[F::QROWS / 32 * h + rt][ks] = as_frag(s_q[(32 * rt + l32) * F::QPITCH + 2 * ks + hf]);
+      if (h == 0)
+#pragma unroll
+        for (int rt = 0; rt < NRT; ++rt) ref[rt] = s_r[32 * rt + l32];
+      if (h == 0) lds_barrier();
+    }
+  };
+  const u32x4* q_lane = s_q + (F::QROWS - 32 + (lane & 31)) * F::QPITCH + (lane >> 5);
+  auto last_q = [&](int ks) __attribute__((always_inline)) {
+    return as_frag(q_lane[2 * ks]);
+  };
+  auto prime = [&]() __attribute__((always_inline)) {  // the first product of a pass
+    fin = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fin = PKV_MFMA32(kc[ks], q[0][ks], fin);
+  };
+
+  int zbuf = 0;  // table in use
+  u64 sum = 0;   // of the thread's row over the unit's items so far
+  Pass nxt = cur;
+  bool has_next = advance<kPass>(a, nxt);
+  // One pass over the keys in kc; those of the next pass are on their way into the other buffer, those of the one after it are
+  // requested into this one, which has been read.
+  auto pass = [&](auto BUF) __attribute__((always_inline)) {
+    using Other = std::integral_constant<int, 1 - decltype(BUF)::value>;
+    Pass nx2 = nxt;
+    const bool has_nx2 = has_next && advance<kPass>(a, nx2);
+    request(nx2, BUF);
+    const int wkey = cur.key + 32 * wave, npre = cur.n - a.alpha;
+    f32x16 t;
+    const bool ends = wkey + 32 > npre;  // the tile reaches into the causal window or beyond the end
+    if (__builtin_expect(ends, 0)) {
+      // sums without what a query does not see
+      const int ln = fresh(lane), l32 = ln & 31, hf = ln >> 5;
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) {
+        const int lim = npre + (32 * rt + l32) % a.alpha - wkey - 4 * hf;  // last key the lane's query sees
+        float z0 = 0.f, z1 = 0.f;
+        f32x16 x = {};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) x = PKV_MFMA32(kc[ks], rt < NRT - 1 ? q[min(rt, NRT - 2)][ks] : last_q(ks), x);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float y = mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(x[v], a.kappa, ref[rt].x));
+          if (v & 1) z1 += y;
+          else z0 += y;
+        }
+        s_end[wave * F::ROWS + 32 * rt + l32] = z[rt] + both_halves<false>(z0 + z1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // Product of row tile rt + 1 (behind the last one: of the next pass's keys and row tile 0) goes into `nx` while `fi`, that of row
+    // tile rt, turns into exponentials.
+    auto step = [&](auto RT, const f32x16& fi, f32x16& nx) __attribute__((always_inline)) {
+      constexpr int rt = decltype(RT)::value;
+      if constexpr (rt == NRT - 2) arrived();
+      float z0 = 0.f, z1 = 0.f;
+      nx = f32x16{};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if constexpr (rt == NRT - 2) {
+          nx = PKV_MFMA32(kc[ks], ql[ks % 3], nx);
+          if (ks + 2 < KS) ql[(ks + 2) % 3] = last_q(ks + 2);
+          kc[ks] = key_frag(Other{}, ks);
+        } else {
+          nx = PKV_MFMA32(kc[ks], q[(rt + 1) % NRT][ks], nx);
+          if (rt == NRT - 3 && ks >= KS - 2) ql[ks - KS + 2] = last_q(ks - KS + 2);
+        }
+        float x[TPM];
+#pragma unroll
+        for (int j = 0; j < TPM; ++j) x[j] = __builtin_fmaf(fi[TPM * ks + j], a.kappa, ref[rt].x);
+#pragma unroll
+        for (int j = 0; j < TPM; ++j) x[j] = fast_exp2(x[j]);
+#pragma unroll
+        for (int j = 0; j < TPM; ++j) {
+          t[TPM * ks + j] = rt == 0 ? x[j] * ref[rt].y : __builtin_fmaf(x[j], ref[rt].y, t[TPM * ks + j]);
+          if (j & 1) z1 += x[j];
+          else z0 += x[j];
+          asm volatile("" : "+v"(t[TPM * ks + j]));
+        }
+        asm volatile("" : "+v"(z0), "+v"(z1));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      z[rt] += both_halves<false>(z0 + z1);  // (the sums of an item come about as in the kernel that scores the other sequences)
+    };
+    step(std::integral_constant<int, 0>{}, fin, out);
+    step(std::integral_constant<int, 1>{}, out, fin);
+    step(std::integral_constant<int, 2>{}, fin, out);
+    step(std::integral_constant<int, 3>{}, out, fin);
+    if (__builtin_expect(ends, 0)) {
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) z[rt] = s_end[wave * F::ROWS + 32 * rt + (fresh(lane) & 31)];
+    }
+    {
+      const int ln = fresh(lane), key = wkey + transpose_key(ln);
+      const float s = transpose_sum(t, ln);
+      if (key < npre && (ln & 1) == 0) raw[key] = s;
+    }
+    const bool unit_ends = !has_next || nxt.u != cur.u;
+    if (unit_ends || nxt.key % kLagKeys == 0) {  // the item's sums
+      const int tid = fresh(threadIdx.x), l32 = tid & 31, hf = tid >> 5 & 1;
+      float* z_lane = s_z + (zbuf * kW + wave) * F::ROWS + l32;
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) {
+        if (hf == 0) z_lane[32 * rt] = z[rt];
+        z[rt] = 0.f;
+      }
+      lds_barrier();
+      if (tid < a.R) {
+        const float* z8 = s_z + zbuf * kW * F::ROWS + tid;
+        float w[kW];
+#pragma unroll
+        for (int i = 0; i < kW; ++i) w[i] = z8[i * F::ROWS];
+        const float all = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
+        if (all <= kSumLimit) sum += fixed_point(all, kSumUnits);
+        else sum |= kZBad;
+      }
+      zbuf ^= 1;  // (the table is written again behind the next item's barrier)
+    }
+    if (unit_ends) {
+      const int tid = fresh(threadIdx.x);
+      if (tid < a.R) add_sum(a, cur.u, tid, sum);
+      sum = 0;
+      if (has_next) {
+        stage(nxt);
+        prime();
+      }
+    }
+    const bool more = has_next;
+    cur = nxt;
+    nxt = nx2;
+    has_next = has_nx2;
+    return more;
+  };
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  request(cur, B0{});
+  request(nxt, B1{});
+  stage(cur);
+  arrived();
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) kc[ks] = key_frag(B0{}, ks);
+  prime();
+#pragma unroll 1
+  for (;;) {
+    if (!pass(B0{})) break;
+    if (!pass(B1{})) break;
+  }
+  // (requests of the pass that is not there: LDS belongs to the workgroup until they are through)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 template <int D>
 constexpr size_t sift_lds(int Rs) {
   // queries with a row pitch of D / 8 + 1 sixteen-byte slots (bank-free), references and estimates, sums by wave
@@ -294,10 +646,9 @@ constexpr size_t sift_lds(int Rs) {
 }
 static_assert(sift_lds<128>(kResidentMaxRows) <= 160 * 1024 && sift_lds<128>(384) <= 160 * 1024, "one workgroup per compute unit");
 
-// ---- the pass over K ----
-// FOUR: four row tiles (65 .. 128 rows), no loop over them: entering and leaving one costs 40 register copies a pass.
-template <int D, bool FOUR>
-__global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
+// More than 128 rows: they lie in LDS.
+template <int D>
+__global__ __launch_bounds__(kT, 2) void score_sift_many_kernel(const SiftArgs a) {
   constexpr int KS = D / 16, SEG = D / 8, PITCH = SEG + 1;
   constexpr int TPM = 16 / KS;  // logits per lane handled between two matrix instructions
   extern __shared__ u32x4 smem[];
@@ -308,98 +659,15 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
-  const int nrt = FOUR ? 4 : a.Rs / 32;  // (even, four at least)
+  const int nrt = a.Rs / 32;  // (even, six at least)
 
-  // One pass of the workgroup (all fields wave-uniform): its keys from `key` on of unit u.
-  struct Pass {
-    int u, n, key, left;  // left: items of this workgroup behind this one
-    const uint16_t* Q;
-    const uint16_t* K;
-    float* raw;
-  };
-  auto open_unit = [&](Pass& p, bool known) {  // pointers and length of unit p.u; false: the unit is not sifted
-    const Unit x = unit_of(a, p.u);
-    p.n = x.n;
-    p.Q = queries_of(a, x);
-    p.K = keys_of(a, x);
-    p.raw = a.raw + ((size_t)a.layer[x.l].slot * a.B * a.Hkv + (size_t)x.b * a.Hkv + x.g) * a.N;
-    return known || (a.layer[x.l].k_l < x.n && sift_takes(flags_of(a, x.l, x.b), a.Hkv));
-  };
   Pass cur;
-  {
-    // first item and number of items of this workgroup
-    int* wsum = reinterpret_cast<int*>(smem);  // [kW] sums of the waves, [kW], [kW + 1] the first item's place
-    const int E = a.L * a.B;
-    int lo = 0, hi = 0, u0 = 0, c0 = 0;
-    int c = 0, parts = 0, before = 0;
-    for (int round = 0; round < 2; ++round) {  // how many items there are; then who owns the first one
-      int run = 0;
-      for (int e0 = 0; e0 < E; e0 += kT) {
-        const int e = e0 + tid;
-        if (round == 0 || E > kT) {  // (else the first round's are still there)
-          c = parts = 0;
-          if (e < E) {
-            const int l = e / a.B, b = e - l * a.B, n = valid_length(a, b);
-            parts = a.layer[l].k_l < n && sift_takes(flags_of(a, l, b), a.Hkv) ? (n + kLagKeys - 1) / kLagKeys : 0;
-            c = a.Hkv * parts;
-          }
-          int v = c;
-#pragma unroll
-          for (int o = 1; o < 64; o <<= 1) {
-            const int x = __shfl_up(v, o);
-            if (lane >= o) v += x;
-          }
-          lds_barrier();
-          if (lane == 63) wsum[wave] = v;
-          lds_barrier();
-          before = run + v - c;
-#pragma unroll
-          for (int w = 0; w < kW; ++w) {
-            before += w < wave ? wsum[w] : 0;
-            run += wsum[w];
-          }
-        }
-        if (round == 1 && lo >= before && lo < before + c) {
-          const int rem = lo - before, g = rem / parts;
-          wsum[kW] = e * a.Hkv + g;
-          wsum[kW + 1] = rem - g * parts;
-        }
-      }
-      if (round == 0) {
-        if (run == 0) return;
-        lo = (int)((int64_t)blockIdx.x * run / gridDim.x);
-        hi = (int)((int64_t)(blockIdx.x + 1) * run / gridDim.x);
-      }
-    }
-    lds_barrier();
-    cur.left = hi - lo;
-    if (cur.left == 0) return;
-    u0 = __builtin_amdgcn_readfirstlane(wsum[kW]);
-    c0 = __builtin_amdgcn_readfirstlane(wsum[kW + 1]);
-    --cur.left;
-    cur.u = u0;
-    cur.key = c0 * kLagKeys;
-    (void)open_unit(cur, true);
-  }
-  // The pass after p; false if there is none (p is then a pass over the unit's first key alone).
-  auto advance = [&](Pass& p) {
-    p.key += kPass;
-    if (p.key % kLagKeys != 0 && p.key < p.n) return true;
-    if (p.left == 0) {
-      p.key = 0;
-      p.n = 1;
-      return false;
-    }
-    --p.left;
-    if (p.key >= p.n) {
-      do ++p.u;
-      while (!open_unit(p, false));  // (there is one: an item is left)
-      p.key = 0;
-    }
-    return true;
-  };
+  if (!first_pass(a, cur, reinterpret_cast<int*>(smem))) return;
+  float* raw;  // the unit's scores
   // Queries, references and estimates of a unit into LDS.  Barriers around it are the caller's.
   auto stage = [&](const Pass& p) {
+    const uint16_t* Q = queries_of(a, unit_of(a, p.u));
+    raw = scores_of(a, p.u);
     const int seg = tid & (SEG - 1);
     float2 ref = make_float2(0.f, 0.f);
     if (tid < a.Rs) {
@@ -409,7 +677,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     for (int row0 = tid / SEG; row0 < a.Rs; row0 += 4 * (kT / SEG)) {
       u32x4 v[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4*>(query_row_of(a, p.Q, row0 + j * (kT / SEG)) + 8 * seg);
+      for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4*>(query_row_of(a, Q, row0 + j * (kT / SEG)) + 8 * seg);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int row = row0 + j * (kT / SEG);
@@ -437,15 +705,6 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   bool first = true;  // pass of an item
   int zbuf = 0;       // table in use
   u64 sum = 0;        // of the thread's row over the unit's items so far
-  // With four row tiles a lane's references and estimates, and its sums over an item, stay in registers.
-  float2 ref4[4];
-  float z4[4] = {0.f, 0.f, 0.f, 0.f};
-  auto load_refs = [&]() {
-    if constexpr (FOUR) {
-#pragma unroll
-      for (int rt = 0; rt < 4; ++rt) ref4[rt] = s_r[32 * rt + l32];
-    }
-  };
   auto prime = [&](const bf16x8 (&kc)[KS]) {  // the first product of a pass
     fin = f32x16{};
 #pragma unroll
@@ -454,11 +713,11 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     for (int s = 0; s < 3; ++s) qf[s] = q_frag(1, s);
   };
   Pass nxt = cur;
-  bool has_next = advance(nxt);
+  bool has_next = advance<kPass>(a, nxt);
   // One pass over the keys in kc; those of the next pass are in kn, those of the one after it are requested into kp.
   auto pass = [&](bf16x8 (&kc)[KS], bf16x8 (&kn)[KS], bf16x8 (&kp)[KS]) {
     Pass nx2 = nxt;
-    const bool has_nx2 = has_next && advance(nx2);
+    const bool has_nx2 = has_next && advance<kPass>(a, nx2);
     issue_k(nx2, kp);
     const int wkey = cur.key + 32 * wave, npre = cur.n - a.alpha;
     f32x16 t;
@@ -474,13 +733,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
 #pragma unroll 1
       for (int rt = 0; rt < nrt; ++rt) {
         const float2 ref = s_r[32 * rt + l32];
-        float before = 0.f;
-        if constexpr (FOUR) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) before = rt == i ? z4[i] : before;
-        } else {
-          before = z_before(rt);
-        }
+        const float before = z_before(rt);
         const int lim = npre + (32 * rt + l32) % a.alpha - wkey - 4 * hf;  // last key the lane's query sees
         float z0 = 0.f, z1 = 0.f;
         f32x16 x = {};
@@ -493,32 +746,20 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
           else z0 += y;
           t[v] = __builtin_fmaf(y, ref.y, t[v]);
         }
-        const float z = both_halves<false>(z0 + z1) + before;
-        if constexpr (FOUR) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) z4[i] = rt == i ? z : z4[i];
-        } else {
-          set_z(rt, z);
-        }
+        set_z(rt, both_halves<false>(z0 + z1) + before);
       }
       if (has_next && nxt.u == cur.u) prime(kn);
     } else {
       // Product of row tile rt + 1 (LAST: of the next pass's keys and row tile 0) goes into `nx` while `fi`, that of row
       // tile rt, turns into exponentials.
-      float2 ref_next = make_float2(0.f, 0.f);
-      if constexpr (!FOUR) ref_next = s_r[l32];
+      float2 ref_next = s_r[l32];
       auto step = [&](auto FIRST, auto LAST, int rt, const f32x16& fi, f32x16& nx) {
         constexpr bool start = decltype(FIRST)::value, last = decltype(LAST)::value;
         const int mul = last ? 0 : rt + 1, then = last ? 1 : rt + 2 < nrt ? rt + 2 : 0;
-        float2 ref;
-        float before = 0.f;
-        if constexpr (FOUR) {
-          ref = ref4[rt];
-        } else {  // (what the next step needs at its beginning, and this one at its end)
-          ref = ref_next;
-          if (!last) ref_next = s_r[32 * (rt + 1) + l32];
-          before = z_before(rt);
-        }
+        // (what the next step needs at its beginning, and this one at its end)
+        const float2 ref = ref_next;
+        if (!last) ref_next = s_r[32 * (rt + 1) + l32];
+        const float before = z_before(rt);
         float z0 = 0.f, z1 = 0.f;
         nx = f32x16{};
 #pragma unroll
@@ -542,20 +783,16 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
           asm volatile("" : "+v"(z0), "+v"(z1));
           __builtin_amdgcn_sched_barrier(0);
         }
-        const float z = both_halves<false>(z0 + z1);
-        if constexpr (FOUR) z4[rt] += z;
-        else set_z(rt, before + z);
+        set_z(rt, before + both_halves<false>(z0 + z1));
       };
       using Y = std::true_type;
       using N = std::false_type;
       step(Y{}, N{}, 0, fin, out);
       step(N{}, N{}, 1, out, fin);
-      if constexpr (!FOUR) {
 #pragma unroll 1
-        for (int rt = 2; rt + 2 < nrt; rt += 2) {
-          step(N{}, N{}, rt, fin, out);
-          step(N{}, N{}, rt + 1, out, fin);
-        }
+      for (int rt = 2; rt + 2 < nrt; rt += 2) {
+        step(N{}, N{}, rt, fin, out);
+        step(N{}, N{}, rt + 1, out, fin);
       }
       step(N{}, N{}, nrt - 2, fin, out);
       step(N{}, Y{}, nrt - 1, out, fin);
@@ -563,18 +800,11 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
     {
       const int ln = fresh(lane), key = wkey + transpose_key(ln);
       const float s = transpose_sum(t, ln);
-      if (key < npre && (ln & 1) == 0) cur.raw[key] = s;
+      if (key < npre && (ln & 1) == 0) raw[key] = s;
     }
     const bool unit_ends = !has_next || nxt.u != cur.u;
     first = unit_ends || nxt.key % kLagKeys == 0;
     if (first) {  // the item's sums
-      if constexpr (FOUR) {
-#pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-          if (hf == 0) zp[32 * rt] = z4[rt];
-          z4[rt] = 0.f;
-        }
-      }
       lds_barrier();
       if (tid < a.R) {
         const float* z8 = s_z + zbuf * kW * a.Rs + tid;
@@ -589,16 +819,11 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
       else lds_barrier();
     }
     if (unit_ends) {
-      if (tid < a.R) {
-        u64* z = a.zsum + (size_t)cur.u * a.Rs + tid;
-        if (sum & kZBad) (void)__hip_atomic_fetch_or(z, kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        (void)__hip_atomic_fetch_add(z, sum & ~kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sum = 0;
-      }
+      if (tid < a.R) add_sum(a, cur.u, tid, sum);
+      sum = 0;
       if (has_next) {  // (every wave is done with the unit's queries: the barrier above)
         stage(nxt);
         lds_barrier();
-        load_refs();
         prime(kn);
       }
     }
@@ -613,7 +838,6 @@ __global__ __launch_bounds__(kT, 2) void score_sift_kernel(const SiftArgs a) {
   lds_barrier();  // (the first item's place has been read)
   stage(cur);
   lds_barrier();
-  load_refs();
   prime(b0);
 #pragma unroll 1
   for (;;) {
@@ -1145,10 +1369,10 @@ hipError_t launch_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
   const int dev = current_device_slot();
   if (dev < 0) return hipErrorInvalidDevice;
   if (!attr_set[dev]) {  // raise the dynamic LDS limits once per device (idempotent; no allocation)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_kernel<D, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sift_lds<D>(128));
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_few_kernel<D>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)FewRows<D>::kLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_kernel<D, false>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_sift_many_kernel<D>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sift_lds<D>(kResidentMaxRows));
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(sift_list_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
@@ -1159,8 +1383,8 @@ hipError_t launch_sift(const SiftArgs& a, bool clear_err, hipStream_t s) {
   hipLaunchKernelGGL((sift_prepare_kernel<D>), dim3(units * ((a.Rs + kBlockRows - 1) / kBlockRows)), dim3(kT), 0, s, a, clear_err ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.Rs == 128) hipLaunchKernelGGL((score_sift_kernel<D, true>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
-  else hipLaunchKernelGGL((score_sift_kernel<D, false>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
+  if (a.Rs == FewRows<D>::ROWS) hipLaunchKernelGGL((score_sift_few_kernel<D>), dim3(a.grid), dim3(kT), FewRows<D>::kLds, s, a);
+  else hipLaunchKernelGGL((score_sift_many_kernel<D>), dim3(a.grid), dim3(kT), sift_lds<D>(a.Rs), s, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = (size_t)((a.N + 7) / 8 + (a.N + 31) / 32) * 4;
