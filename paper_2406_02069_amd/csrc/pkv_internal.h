@@ -165,9 +165,12 @@ constexpr int kSiftJob = 256;         // keys scored exactly by a workgroup
 // ... of a unit, at most: an eighth of its keys
 __host__ __device__ constexpr int sift_list(int N) { return N / 8 / kSiftJob * kSiftJob; }
 constexpr int kSiftMinKeys = 4096;    // of a prefix
-// Estimates are no use where more than 12 of 256 sampled keys lie between half the cut's estimate and the cut.
+// Estimates are no use where more than 16 of 256 sampled keys lie between half the cut's estimate and the cut.  Whole calls of 32
+// layers x 8 heads x 32k keys, 128 rows, us, with 12 and with 16 (where nothing is tried: 705), by the strength of the queries' common
+// direction (the rest: 0.9): 1.0 568 and 555, 0.9 582 and 553, 0.8 620 and 557, 0.7 685 and 596, 0.6 695 and 645, 0.5 788 and 728, 0.4
+// 706 and 751 (two layers in vain; with 20 837), 0.2 706 and 677.
 constexpr float kSiftNear = 0.5f;
-constexpr int kSiftMaxNear = 12;
+constexpr int kSiftMaxNear = 16;
 // The guess of tau: the estimate that kSiftRank times the groups that the kept keys are thought to fill reach, times what the mean
 // ratio of weight to estimate is below the largest, times kSiftSlack (0.95 and 1: one head in a hundred fails the check).
 constexpr float kSiftSlack = 0.9f, kSiftRank = 1.2f;

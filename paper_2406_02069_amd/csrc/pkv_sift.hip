@@ -26,8 +26,9 @@
 // length; no workgroup waits for another.
 //
 // What bounds it: vector instructions and HBM, and the clock the chip holds under this load, at 128 rows (32 layers x 8 heads x 32k
-// keys 465 us, 4.6 TB/s, at 2.0 GHz; with the keys in the caches 438; the lagging kernel 620), vector instructions at 512 rows (80
-// layers 3.34 ms at 1.8 GHz; 4.3).  A launch begins with 12 us until the first product.  The kernels around it are chains of latencies:
+// keys 412 us, 5.2 TB/s, at 2.1 GHz; the lagging kernel 620), power at 512 rows (80 layers 3.25 ms at 1.8 GHz; 4.3: two key tiles per
+// query fragment, sixteen waves, or products and exponentials of two waves in turn by barriers change the clock, 1.80 .. 1.94 GHz, and
+// the time to 3.2 .. 3.5).  A launch begins with 12 us until the first product.  The kernels around it are chains of latencies:
 // 31, 26 and 38 us for 256 heads of 32k keys (the selection kernel, which takes 27 otherwise, is left with 10).
 #include <type_traits>
 
@@ -387,9 +388,11 @@ __device__ __forceinline__ void add_sum(const SiftArgs& a, int u, int row, u64 s
   (void)__hip_atomic_fetch_add(z, sum & ~kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// 65 to 128 rows: they lie in the registers of every wave as matrix operands, and K comes through LDS.  A wave requests its tile two
-// passes ahead, whole rows at a time and past the registers, and reads each fragment once, behind the last product that needs its
-// predecessor: a pass reads 8 KB of LDS per wave instead of 32 for the queries, and a request of 64 lanes touches 4 rows instead of 32.
+// 65 to 128 rows: they lie in the registers of every wave as matrix operands (but for the last row tile's, for which there are none
+// left), and K comes through LDS.  A wave requests its tile two passes ahead, whole rows at a time and past the registers, and reads
+// each fragment once, behind the last product that needs its predecessor.  Against queries in LDS and keys requested as operands a
+// pass reads 16 KB of LDS per wave instead of 32 and has 390 vector instructions instead of 508: 32 layers x 8 heads x 32k keys 450 ->
+// 412 us, x 128k 1853 -> 1700.
 template <int D>
 struct FewRows {
   static constexpr int ROWS = 128, TILES = ROWS / 32;
