@@ -80,24 +80,25 @@ __device__ __forceinline__ float fold16(float x, float y) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Key range sp of (sequence b, KV head g) of one layer's cache.
-template <int D, int GP, bool PAGED>
-__device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g, int b, float* dsm) {
+// Key range sp of (sequence b, KV head g) of one layer's cache; output columns part * DV .. part * DV + DV - 1 of D.
+template <int D, int GP, bool PAGED, int DV = D>
+__device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g, int b, float* dsm, int part = 0) {
   constexpr int KS = D / 32;             // matrix k-steps per dot product
   constexpr int NG = D == 128 ? 1 : 2;   // groups of 16 keys per tile (4 KB of keys and of values either way)
   constexpr int TK = 16 * NG;            // keys per tile
-  constexpr int LPR = D / 8;             // lanes per value row
+  constexpr int LPR = DV / 8;            // lanes per value row
   constexpr int RPL = 64 / LPR;          // value rows per load of a wave
   constexpr int NV = TK / RPL;           // value loads per tile
   constexpr int QH = GP > 4 ? 2 : 1;     // quads that hold logits of real heads
+  static_assert(LPR >= 4 && DV >= TK, "lanes of a matrix block share a row; a wave's weights fit its outputs' place");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
   const int l16 = lane & 15, quad = lane >> 4;
   const int sub = lane / LPR, col = lane - sub * LPR;
-  // dsm: [nw][GP][D] outputs of the waves (before that, each wave's region holds its tile's weights) | [nw][GP][2]
+  // dsm: [nw][GP][DV] outputs of the waves (before that, each wave's region holds its tile's weights) | [nw][GP][2]
   // (max, sum) | [kTabEntries] block-table entries of this range
-  float* s_o = dsm + (size_t)wave * GP * D;
-  float* s_mz = dsm + (size_t)nw * GP * D;
+  float* s_o = dsm + (size_t)wave * GP * DV;
+  float* s_mz = dsm + (size_t)nw * GP * DV;
   int* s_tab = reinterpret_cast<int*>(s_mz + nw * GP * 2);
   const int cnt_raw = a.count[b];
   const int j_lo = sp * a.chunk;
@@ -120,6 +121,7 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
     Kb += (size_t)b * a.c_sb + (size_t)g * a.c_sh + (size_t)j_lo * a.c_st;
     Vb += (size_t)b * a.c_sb + (size_t)g * a.c_sh + (size_t)j_lo * a.c_st;
   }
+  Vb += part * DV;
   // Address of local row j (0 <= j < nmax) of Kb / Vb; paged: ok = its page number is in range (else the address is
   // that of some readable row)
   const uint64_t row_bytes = (uint64_t)a.c_st * 2u;
@@ -340,14 +342,15 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       r2[h][c] = GP >= 4 ? fold16(r1[h][c], r1[(h + H2) % H1][c]) : fold16(r1[0][c], r1[0][c]);
-      if (D == 64) r2[h][c] += row_ror<8>(r2[h][c]);
+      if (LPR <= 8) r2[h][c] += row_ror<8>(r2[h][c]);
+      if (LPR <= 4) r2[h][c] += row_ror<4>(r2[h][c]);
     }
   const int h0 = (GP >= 2 ? upper * H1 : 0) + (GP >= 4 ? odd * H2 : 0);
-  const bool writes = (GP >= 2 || upper == 0) && (GP >= 4 || odd == 0) && (D == 128 || (lane & 8) == 0);
+  const bool writes = (GP >= 2 || upper == 0) && (GP >= 4 || odd == 0) && (lane & (16 - LPR)) == 0;
   if (writes) {
 #pragma unroll
     for (int h = 0; h < H2; ++h) {
-      float* dst = s_o + (h0 + h) * D + 8 * col;
+      float* dst = s_o + (h0 + h) * DV + 8 * col;
       *reinterpret_cast<f32x4*>(dst) = f32x4{r2[h][0], r2[h][1], r2[h][2], r2[h][3]};
       *reinterpret_cast<f32x4*>(dst + 4) = f32x4{r2[h][4], r2[h][5], r2[h][6], r2[h][7]};
     }
@@ -355,8 +358,8 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
   __syncthreads();
   // ---- the waves' results meet, in wave order ----
   const size_t unit = (size_t)b * a.Hkv + g;
-  for (int e = tid; e < a.G * D; e += blockDim.x) {
-    const int h = e / D;
+  for (int e = tid; e < a.G * DV; e += blockDim.x) {
+    const int h = e / DV;
     float M = -INFINITY;
     for (int w0 = 0; w0 < nw; w0 += 4)  // (nw is a multiple of 4)
 #pragma unroll
@@ -367,11 +370,12 @@ __device__ __forceinline__ void decode_range(const DecodeArgs& a, int sp, int g,
       for (int w = w0; w < w0 + 4; ++w) {
         const float f = __builtin_amdgcn_exp2f(s_mz[(w * GP + h) * 2] - M);  // (nothing here, M = kNone: zz and xx are 0)
         zz += f * s_mz[(w * GP + h) * 2 + 1];
-        xx += f * dsm[(size_t)w * GP * D + e];
+        xx += f * dsm[(size_t)w * GP * DV + e];
       }
-    const bool first = e == h * D;
+    const bool first = e == h * DV && part == 0;
+    const int at = DV == D ? e : h * D + part * DV + (e - h * DV);
     if (a.S == 1) {
-      a.out[((size_t)b * a.Hq + (size_t)g * a.G) * D + e] = zz > 0.f ? xx / zz : 0.f;
+      a.out[((size_t)b * a.Hq + (size_t)g * a.G) * D + at] = zz > 0.f ? xx / zz : 0.f;
       if (first && a.lse)
         a.lse[(size_t)b * a.Hq + g * a.G + h] = zz > 0.f ? (M + __builtin_amdgcn_logf(zz)) * 0.69314718055994530942f : -INFINITY;
     } else {
@@ -388,6 +392,15 @@ template <int D, int GP, bool PAGED>
 __global__ __launch_bounds__(64 * max_waves(GP)) void decode_partial_kernel(const DecodeArgs a) {
   extern __shared__ float dsm[];
   decode_range<D, GP, PAGED>(a, blockIdx.x, blockIdx.y, blockIdx.z, dsm);
+}
+
+// Few heads, one range each: a head's output columns over several workgroups.  Each forms all logits, so the keys are read D / 32
+// times, but a compute unit has 5/8 (d = 64: 3/4) of the bytes to fetch, and nothing has to be merged.
+constexpr int kColumns = 32;
+template <int D, int GP, bool PAGED>
+__global__ __launch_bounds__(64 * max_waves(GP)) void decode_columns_kernel(const DecodeArgs a) {
+  extern __shared__ float dsm[];
+  decode_range<D, GP, PAGED, kColumns>(a, 0, blockIdx.y, blockIdx.z, dsm, blockIdx.x);
 }
 
 // Merge of the S partial results of a (sequence, KV head): common reference exponent, sums, weighted values.
@@ -494,6 +507,17 @@ hipError_t launch_partial(const DecodeArgs& a, int nw, hipStream_t s) {
 }
 
 template <int D, int GP, bool PAGED>
+hipError_t launch_columns(const DecodeArgs& a, int nw, hipStream_t s) {
+  static bool granted[kMaxDevices];
+  const hipError_t e = grant_lds(reinterpret_cast<const void*>(decode_columns_kernel<D, GP, PAGED>), granted,
+                                 lds_bytes(kColumns, GP, max_waves(GP), PAGED));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((decode_columns_kernel<D, GP, PAGED>), dim3(D / kColumns, a.Hkv, a.B), dim3(64 * nw),
+                     lds_bytes(kColumns, GP, nw, PAGED), s, a);
+  return hipGetLastError();
+}
+
+template <int D, int GP, bool PAGED>
 hipError_t launch_partial_layers(const DecodeBatchArgs& a, int total_wgs, int nw, hipStream_t s) {
   static bool granted[kMaxDevices];
   const hipError_t e = grant_lds(reinterpret_cast<const void*>(decode_partial_layers_kernel<D, GP, PAGED>), granted,
@@ -540,6 +564,16 @@ int decode_splits_used(int B, int Hkv, int d, int k_cap) {
   int S = (k_cap + rows - 1) / rows;
   if (S > 512 / units) S = 512 / units;
   return S < most ? S : most;
+}
+
+// One range per head, but its output columns over several workgroups: up to 128 of them, where there is something to fetch.  Launches
+// behind one another, us each, before -> with it: 8 heads of 4 queries, d = 128, 64 rows 4.1 -> 3.6, 256 rows 7.3 -> 6.6, 512 rows 9.6 ->
+// 8.4, 768 rows 11.8 -> 10.0; of 8 queries, 512 rows 9.9 -> 8.0; 32 heads of one query, 64 rows 3.3 -> 3.8, 128 rows 4.3 -> 4.3, 512
+// rows 8.6 -> 7.9; d = 64, 8 heads of 4 queries, 512 rows 6.9 -> 6.6.  256 workgroups: 64 heads of one query, 128 rows 4.4 -> 5.1, of
+// 4 queries 5.4 -> 5.5, 512 rows 10.7 -> 10.7.
+constexpr int kColumnsMaxWorkgroups = 128;
+static bool decode_by_columns(const DecodeArgs& a) {
+  return a.S == 1 && a.B * a.Hkv * (a.d / kColumns) <= kColumnsMaxWorkgroups && a.k_cap >= (a.G > 1 ? 64 : 128);
 }
 
 // Waves per workgroup: sixteen (one workgroup per compute unit) up to 256 workgroups, four beyond 1024.  In between
@@ -602,6 +636,12 @@ hipError_t launch_decode_attention_layers(const DecodeBatchArgs& a, int total_wg
 }
 
 hipError_t launch_decode_attention(const DecodeArgs& a, hipStream_t s) {
+  if (decode_by_columns(a)) {
+    const int nw = decode_waves((int64_t)a.B * a.Hkv * (a.d / kColumns), (int64_t)a.B * a.Hkv * a.k_cap, a.d, a.G, a.chunk);
+    return with_variant(a.d, a.G, a.page_size > 0, [&](auto D, auto GP, auto P) {
+      return launch_columns<decltype(D)::value, decltype(GP)::value, decltype(P)::value>(a, nw, s);
+    });
+  }
   const int nw = decode_waves((int64_t)a.S * a.B * a.Hkv, (int64_t)a.B * a.Hkv * a.k_cap, a.d, a.G, a.chunk);
   const hipError_t e = with_variant(a.d, a.G, a.page_size > 0, [&](auto D, auto GP, auto P) {
     return launch_partial<decltype(D)::value, decltype(GP)::value, decltype(P)::value>(a, nw, s);

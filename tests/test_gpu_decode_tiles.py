@@ -78,3 +78,31 @@ def test_page_sizes(page_size, k_cap):
     torch.cuda.synchronize()
     assert not torch.isnan(out).any()
     _cmp(out, lse, Ks, Vs, q, count)
+
+
+@pytest.mark.parametrize("page_size", [0, 7])
+@pytest.mark.parametrize("B,G,Hkv,d,k_cap", [
+    (4, 4, 8, 128, 64), (4, 4, 8, 128, 63),      # 128 workgroups for the columns, the fewest rows; one range each
+    (3, 3, 11, 128, 200),                        # a head too many
+    (2, 1, 16, 128, 128), (2, 1, 16, 128, 127),  # single queries need twice the rows
+    (1, 8, 2, 128, 768), (1, 8, 2, 128, 769),    # one range; several, merged
+    (4, 2, 16, 64, 65), (1, 5, 3, 64, 1536),
+])
+def test_columns_of_few_heads(B, G, Hkv, d, k_cap, page_size):
+    q, Ks, Vs = _rand(B, G * Hkv, Hkv, d, k_cap, seed=k_cap + B)
+    count = np.array([k_cap, k_cap - 1, 5, 0][:B], dtype=np.int32)
+    print("decode columns", B, G, Hkv, d, k_cap, page_size, flush=True)
+    K, V, kw = Ks, Vs, {}
+    if page_size:
+        per = (k_cap + page_size - 1) // page_size
+        table = np.random.RandomState(k_cap).permutation(B * per).astype(np.int32).reshape(B, per)
+        K, V = (torch.zeros(B * per, Hkv, page_size, d, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        for b in range(B):
+            for i in range(per):
+                n = min(page_size, k_cap - i * page_size)
+                for pool, x in ((K, Ks), (V, Vs)):
+                    pool[int(table[b, i]), :, :n] = x[b, :, i * page_size:i * page_size + n]
+        kw = {"block_table": torch.from_numpy(table).to(DEV), "k_cap": k_cap}
+    out, lse = binding.decode_attention(q, K, V, torch.from_numpy(count).to(DEV), want_lse=True, **kw)
+    torch.cuda.synchronize()
+    _cmp(out, lse, Ks, Vs, q, count)
