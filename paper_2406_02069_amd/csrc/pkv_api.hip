@@ -347,12 +347,15 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
 // same kept sets to the bit (the scores that decide them are the same to the bit), so that here the number of layers may count.
 // Where the lines lie, whole calls, before -> with these kernels, us: five launches instead of two cost about 100 us where
 //   keys are few, and a key costs less by a quarter at 128 rows and a fifth at 512.  32 layers of 8 heads x 32k keys, 128 rows
-//   674 -> 604; x 128k 3360 -> 2080; 80 layers x 32k, 512 rows 4400 -> 3750; 2.1 million keys, 128 rows, 159 -> 173.
-//   Uncorrelated queries (32 layers x 32k, 128 rows), whose layers are all handed on: 665 -> 705.
+//   673 -> 545; x 128k 3325 -> 1870; 80 layers x 32k, 512 rows 4390 -> 3500.  128 rows, 4 million keys of 32k 356 -> 302, of 16k 337 ->
+//   316, of 128k 458 -> 316; 3 million 272 -> 249, 259 -> 259; 2 million 193 -> 194, 181 -> 194, 258 -> 214; 1 million 106 -> 125.
+//   512 rows, of 32k keys, 3 million 700 -> 593, 2 million 480 -> 418, 1 million 250 -> 241; 256 rows, 4 million 522 -> 456, 2 million
+//   284 -> 271, 1 million 153 -> 173.  Uncorrelated queries (32 layers x 32k, 128 rows), whose layers are all handed on: 670 -> 705, and
+//   as much more at fewer keys, so that the lines lie where the gain is a sixth.
 // The statistics, lists and jobs lie where the pooled scores lie later on, behind the words of the lagging kernel.
 constexpr int kSiftMinRows = 65;     // (64 rows: K's read binds either way)
 constexpr int kSiftMinLen = 16384;
-constexpr int64_t kSiftMinTotal = 6 << 20;  // keys of a call
+constexpr int64_t kSiftMinTotal = 4 << 20, kSiftMinTotalMany = 3 << 20;  // keys of a call; with more than 128 rows
 struct SiftPlan {
   int Rs;
   // the other kernel's words; sums, estimates, sums over the window; list and three words about it
@@ -361,7 +364,7 @@ struct SiftPlan {
 static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, const LagPlan& gp, int scoring_layers) {
   SiftPlan p = {0};
   if (gp.layers == 0 || d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return p;
-  if ((int64_t)scoring_layers * plan.BH * d.N < kSiftMinTotal) return p;
+  if ((int64_t)scoring_layers * plan.BH * d.N < (plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal)) return p;
   const SiftPlan q = {(plan.R + 63) / 64 * 64};
   return q.unit_bytes(gp, d.N) <= (size_t)d.N * 4 ? q : p;
 }

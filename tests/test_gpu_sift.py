@@ -1,4 +1,4 @@
-"""Scoring by estimates (G * alpha > 64, 16k keys and more, 6 million in the call, no scores asked for): kept sets against the CPU oracle and against
+"""Scoring by estimates (G * alpha > 64, 16k keys and more, 3 or 4 million in the call, no scores asked for): kept sets against the CPU oracle and against
 the kernel that scores every key, at the edges of the work split; and the calls that are handed on to that kernel: estimates
 that are no use, sums that do not fit, more keys near the cut than there is room for, layers whose scores are asked for."""
 import numpy as np
@@ -88,6 +88,34 @@ def test_against_every_key_scored(N, pool, pw):
     assert np.all(other == 1)
     for l in range(2):
         _same(call.outputs[l], full.outputs[l])
+
+
+@pytest.mark.parametrize("G,million", [(4, 4), (5, 3)])
+def test_fewest_keys(G, million):
+    """From 4 million keys in a call on, 3 million with more than 128 rows: the same kept sets with a layer less."""
+    alpha, N = 32, 32768
+    Q, K, V = _inputs(1, G, 8, 128, N, alpha, seed=G)
+    L = (million << 20) // (8 * N)
+    print("sift fewest keys", G, L, flush=True)
+    outs = []
+    for n in (L, L - 1):
+        call = binding.LayersCall([Q] * n, [K] * n, [V] * n, [alpha + 60] * n, AVG, 5)
+        call.run()
+        torch.cuda.synchronize()
+        outs.append(call.outputs[n - 1])
+    _same(*outs)
+
+
+@pytest.mark.parametrize("d,G,alpha", [(128, 4, 32), (64, 4, 21), (128, 5, 40)])
+def test_token_major_layout(d, G, alpha):
+    """Keys and queries of a token beside one another, heads inside: rows d * heads apart."""
+    print("sift token-major", d, G, alpha, flush=True)
+    data = _inputs(2, G, 8, d, 16401, alpha, seed=d + G)
+    strided = [x.transpose(1, 2).contiguous().transpose(1, 2) for x in data]
+    assert strided[1].stride(2) == 8 * d
+    (a, flags), (b, same) = (_run([x[0]], [x[1]], [x[2]], [alpha + 40], AVG, 5) for x in (data, strided))
+    assert _sifted(flags).all() and np.array_equal(flags, same)
+    _same(a.outputs[0], b.outputs[0])
 
 
 def test_ragged_batch():
