@@ -131,6 +131,19 @@ def test_ragged_batch():
     compare_layer(Q, K, V, k, alpha, AVG, 5, np.asarray(lens, np.int32), call.outputs[0])
 
 
+@pytest.mark.parametrize("G,alpha,pool,pw", [(8, 64, MAX, 7), (4, 32, NONE, 1), (4, 32, AVG, 5)])
+def test_sink_does_not_hide_that_many_keys_lie_near_the_cut(G, alpha, pool, pw):
+    """Queries without a common direction and a sink that all of them see: no layer is tried."""
+    print("sift sink", G, alpha, pool, flush=True)
+    Q, K, V = _inputs(1, G, 8, 128, 16384, alpha, seed=G)
+    Q = torch.randn_like(Q.float()).to(torch.bfloat16)
+    K[0, :, 0] = 0.5 * Q.float().reshape(8, G * alpha, 128).sum(1).to(torch.bfloat16)
+    call, flags = _run([Q], [K], [V], [alpha + 60], pool, pw)
+    print(flags, flush=True)
+    assert not _sifted(flags).any() and (flags & 2 == 0).all()
+    compare_layer(Q, K, V, alpha + 60, alpha, pool, pw, None, call.outputs[0])
+
+
 def test_handed_on():
     """Queries without a common direction (any key may be kept), keys far above the estimates, many keys at the cut, scores
     asked for: the kernel that scores every key takes these, among others that it does not."""
