@@ -10,7 +10,8 @@
 // requested as soon as this tile's are multiplied and its values as soon as these are added, so that a wave always
 // has loads in flight and no barrier separates the keys from the values.  One barrier at the end, when the waves'
 // (maximum, sum, weighted values) meet in LDS.  With S > 1 the ranges leave un-normalised partial results in a
-// workspace and a second small kernel merges them, with S = 1 the first kernel writes the result itself.
+// workspace and a second small kernel merges them, with S = 1 the first kernel writes the result itself.  Few heads with S = 1 and a
+// launch of their own: a workgroup per 32 output columns, each of which forms all logits (decode_columns_kernel).
 //   logits  the G queries are rows 0 .. G-1 of the A operand of v_mfma_f32_16x16x32_bf16 (16-row tile, the other rows
 //           zero; queries straight from memory into operand layout), 16 keys its columns, loaded straight into the
 //           B-operand layout (16 rows x 64 bytes per load).  Lane (column l16, quad) ends with the logits of heads
