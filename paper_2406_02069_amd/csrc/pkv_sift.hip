@@ -16,14 +16,14 @@
 // references, same order of additions), so that the kept sets are the same to the bit whoever scores.
 //
 // Four launches: sift_prepare_kernel (references, weights o_r from 512 or 1024 keys: the median of eight groups' sums, so that a rare
-// large key does not spoil them), score_sift_kernel (the pass over K), sift_list_kernel (a workgroup per head: tau and the list),
+// large key does not spoil them), score_sift_few_kernel or score_sift_many_kernel (the pass over K), sift_list_kernel (a workgroup per head: tau and the list),
 // sift_exact_kernel (256 listed keys at a time; the last workgroup of a head makes the check and selects the kept set among the few
 // places that reach the bound, so that the selection kernel only copies their rows).
 //
-// score_sift_kernel: 256 persistent workgroups of 512 threads, all query rows of a unit in LDS, a wave holds 32 keys as matrix
-// operands and passes over all rows with them, the next two tiles of keys under way; one product's matrix instructions are issued
-// between the exponentials of the one before.  A barrier per 512 keys, for the sums.  Workgroups take stretches of items of equal
-// length; no workgroup waits for another.
+// The pass over K: 256 persistent workgroups of 512 threads.  A wave holds 32 keys as matrix operands and passes over all query rows with
+// them, the next two tiles of keys under way; up to 128 rows lie in the registers of every wave, more in LDS.  One product's matrix
+// instructions are issued between the exponentials of the one before.  A barrier per 512 keys, for the sums.  Workgroups take stretches
+// of items of equal length; no workgroup waits for another.
 //
 // What bounds it: vector instructions and HBM, and the clock the chip holds under this load, at 128 rows (32 layers x 8 heads x 32k
 // keys 412 us, 5.2 TB/s, at 2.1 GHz; the lagging kernel 620), power at 512 rows (80 layers 3.25 ms at 1.8 GHz; 4.3: two key tiles per
