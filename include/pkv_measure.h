@@ -101,14 +101,16 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
  * it keeps of its statistics in the workspace.
  *
  * variant        0, or PKV_ROUTE_LSE where softmax denominators are supplied,
- *                plus PKV_ROUTE_SEQ_LENS where seq_lens is not NULL.
+ *                plus PKV_ROUTE_SEQ_LENS where seq_lens is not NULL, plus
+ *                PKV_ROUTE_KEPT where some layer's scores_out is NULL.
  * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _LAG, _SWEEP, _RESIDENT, or
- *                _ACCUM for the per-layer kernels.
+ *                _ACCUM for the per-layer kernels; with PKV_ROUTE_KEPT also
+ *                _SIFT, which _LAG follows for what it does not take.
  * scratch_bytes  written: bytes of statistics that a launch addresses.
  * scratch_room   written: bytes of the workspace region that holds them.
  * Returns PKV_OK, PKV_ERR_INVALID_ARG or PKV_ERR_UNSUPPORTED.
  */
-enum { PKV_ROUTE_LSE = 1, PKV_ROUTE_SEQ_LENS = 2 };
+enum { PKV_ROUTE_LSE = 1, PKV_ROUTE_SEQ_LENS = 2, PKV_ROUTE_KEPT = 4 };
 
 int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L,
                       int32_t variant, int32_t* kernel_id,

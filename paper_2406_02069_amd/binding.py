@@ -424,14 +424,15 @@ KERNEL_NAMES = ["score_stats", "score_finalize", "score_accum", "pool_select", "
                 "score_sweep", "score_lag", "score_sift"]
 
 
-def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False, seq_lens: bool = False):
-    """pkv_scoring_route: (kernel name, scratch bytes, room for them) of a call over L layers.  Touches no device."""
+def scoring_route(desc: LayerDesc, L: int = 1, lse_supplied: bool = False, seq_lens: bool = False, kept_only: bool = False):
+    """pkv_scoring_route: (kernel name, scratch bytes, room for them) of a call over L layers; kept_only: without scores_out.
+    Touches no device."""
     lib = load()
     lib.pkv_scoring_route.argtypes = [ctypes.POINTER(LayerDesc), ctypes.c_int32, ctypes.c_int32] + [ctypes.c_void_p] * 3
     lib.pkv_scoring_route.restype = ctypes.c_int
     kernel, used, room = ctypes.c_int32(), ctypes.c_size_t(), ctypes.c_size_t()
-    rc = lib.pkv_scoring_route(ctypes.byref(desc), L, int(lse_supplied) + 2 * int(seq_lens), ctypes.byref(kernel), ctypes.byref(used),
-                               ctypes.byref(room))
+    rc = lib.pkv_scoring_route(ctypes.byref(desc), L, int(lse_supplied) + 2 * int(seq_lens) + 4 * int(kept_only),
+                               ctypes.byref(kernel), ctypes.byref(used), ctypes.byref(room))
     if rc != OK:
         raise PkvError(rc, "pkv_scoring_route")
     return KERNEL_NAMES[kernel.value], used.value, room.value

@@ -358,15 +358,19 @@ constexpr int kSiftMinLen = 16384;
 constexpr int64_t kSiftMinTotal = 4 << 20, kSiftMinTotalMany = 3 << 20;  // keys of a call; with more than 128 rows
 struct SiftPlan {
   int Rs;
+  LagPlan rest;  // of the sequences that are handed on: any of them, so they are dealt as with sequence lengths
   // the other kernel's words; sums, estimates, sums over the window; list and three words about it
-  size_t unit_bytes(const LagPlan& gp, int N) const { return gp.unit_bytes() + (size_t)Rs * 16 + sift_list(N) * 4 + 12; }
+  size_t unit_bytes(int N) const { return rest.unit_bytes() + (size_t)Rs * 16 + sift_list(N) * 4 + 12; }
 };
-static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, const LagPlan& gp, int scoring_layers) {
-  SiftPlan p = {0};
-  if (gp.layers == 0 || d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return p;
-  if ((int64_t)scoring_layers * plan.BH * d.N < (plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal)) return p;
-  const SiftPlan q = {(plan.R + 63) / 64 * 64};
-  return q.unit_bytes(gp, d.N) <= (size_t)d.N * 4 ? q : p;
+static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged, int scoring_layers) {
+  const SiftPlan none = {0, {0, 0, 0, false}};
+  if (d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return none;
+  if ((int64_t)scoring_layers * plan.BH * d.N < (plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal)) return none;
+  // (Dealing takes whole rounds for units of 128 items and more, so that a layer of many of them can be too much for a launch
+  // although it is not when all units are taken in order: 448 heads of 65 536 keys.)
+  const SiftPlan p = {(plan.R + 63) / 64 * 64, lag_plan(plan, d, lse_mode, ragged, true)};
+  if (p.rest.layers == 0 || lag_plan(plan, d, lse_mode, ragged).layers == 0) return none;
+  return p.unit_bytes(d.N) <= (size_t)d.N * 4 ? p : none;
 }
 
 // Queue the kernels of L layers.  All arguments have been validated.
@@ -441,15 +445,16 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       ++scoring;
       unscored += ptrs[l].scores_out ? 0 : 1;
     }
-    const SiftPlan may = sift_plan(plan, d, gp, scoring), fp = unscored > 0 ? may : SiftPlan{0};
+    const SiftPlan may = sift_plan(plan, d, lse_mode, seq_lens != nullptr, scoring);
+    const bool sift = may.Rs > 0 && unscored > 0;
     unsigned long long* const words4 = words + scoring * plan.BH * unit_words;
     int32_t* const flags = reinterpret_cast<int32_t*>(ws + plan.off_cnt) + 2;
-    if (fp.Rs > 0) {
+    if (sift) {
       const size_t units = (size_t)scoring * plan.BH;
       unsigned long long* const zsum = words4 + (gp.words4 ? units * unit_words4 : 0);
-      float* const omega = reinterpret_cast<float*>(zsum + units * fp.Rs);
-      float* const window = omega + units * fp.Rs;
-      uint32_t* const list = reinterpret_cast<uint32_t*>(window + units * fp.Rs);
+      float* const omega = reinterpret_cast<float*>(zsum + units * may.Rs);
+      float* const window = omega + units * may.Rs;
+      uint32_t* const list = reinterpret_cast<uint32_t*>(window + units * may.Rs);
       int32_t* const about = reinterpret_cast<int32_t*>(list + units * sift_list(d.N));
       int32_t done = 0;
       for (int32_t l = 0; l < L;) {
@@ -472,21 +477,21 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         const size_t u0 = (size_t)done * plan.BH;
         fa.words = words + u0 * unit_words;
         if (gp.words4) fa.words4 = words4 + u0 * unit_words4;
-        fa.zsum = zsum + u0 * fp.Rs;
-        fa.omega = omega + u0 * fp.Rs;
-        fa.window = window + u0 * fp.Rs;
+        fa.zsum = zsum + u0 * may.Rs;
+        fa.omega = omega + u0 * may.Rs;
+        fa.window = window + u0 * may.Rs;
         fa.list = list + u0 * sift_list(d.N);
         fa.done = about + u0;
         fa.total = about + units + u0;
         fa.bound = reinterpret_cast<float*>(about + 2 * units + u0);
         fa.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
-        fa.B = d.B; fa.Hq = d.Hq; fa.Hkv = d.Hkv; fa.G = plan.G; fa.alpha = d.alpha; fa.N = d.N; fa.R = plan.R; fa.Rs = fp.Rs; fa.d = d.d;
+        fa.B = d.B; fa.Hq = d.Hq; fa.Hkv = d.Hkv; fa.G = plan.G; fa.alpha = d.alpha; fa.N = d.N; fa.R = plan.R; fa.Rs = may.Rs; fa.d = d.d;
         const int64_t items = (int64_t)fa.L * plan.BH * gp.parts;
         fa.grid = items < kSweepGrid ? (int32_t)items : kSweepGrid;
         fa.groups = gp.groups;
         fa.pool = (d.pool_w == 1) ? PKV_POOL_NONE : d.pool;
         fa.pool_w = d.pool_w;
-        fa.zbufs = sift_zbufs(fp.Rs);
+        fa.zbufs = sift_zbufs(may.Rs);
         fa.sample_tiles = fa.pool == PKV_POOL_AVG ? 4 : 2;  // (its lists are longer)
         fa.sample_shift = fa.sample_tiles == 4 ? 7 : 6;
         // (so that the list fits an eighth of the keys: it holds about 4 keys per key to keep, with average pooling 2.5 + w)
@@ -503,7 +508,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         if (rec) rec->after(PKV_KERNEL_SCORE_SIFT, stream);
         done += fa.L;
       }
-      gp = lag_plan(plan, d, lse_mode, seq_lens != nullptr, true);
+      gp = may.rest;
       sifted = flags;
     }
     int32_t done = 0;
@@ -518,7 +523,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         ga.layer[ga.L].k_l = descs[l].k_l;
         ga.layer[ga.L++].slot = l - l0;
       }
-      if (ga.L == 0) break;
+      if (ga.L == 0) break;  // (the layers left are kept whole)
       ga.seq_lens = seq_lens;
       ga.raw = raw + (size_t)l0 * plan.BH * d.N;
       ga.words = words + (size_t)done * plan.BH * unit_words;
@@ -526,7 +531,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       if (may.Rs > 0) ga.flags = flags + (size_t)l0 * plan.BH;
       ga.err = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
       ga.B = d.B; ga.Hq = d.Hq; ga.Hkv = d.Hkv; ga.G = plan.G; ga.alpha = d.alpha; ga.N = d.N; ga.R = plan.R; ga.d = d.d;
-      ga.uniform = seq_lens || fp.Rs > 0 ? 0 : 1;
+      ga.uniform = seq_lens || sift ? 0 : 1;
       ga.parts = gp.parts;
       ga.groups = gp.groups;
       ga.alpha_magic = alpha_magic;
@@ -539,11 +544,12 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
       ga.kv_sb = d.kv_sb; ga.kv_sh = d.kv_sh; ga.kv_st = d.kv_st;
       ga.kappa = kappa;
       ga.inv_G = 1.0f / (float)plan.G;
-      if (launch_score_lag(ga, first, fp.Rs > 0, stream) != hipSuccess) return PKV_ERR_HIP;
+      if (launch_score_lag(ga, first, sift, stream) != hipSuccess) return PKV_ERR_HIP;
       first = false;
       done += ga.L;
       if (rec) rec->after(PKV_KERNEL_SCORE_LAG, stream);
     }
+    if (done != scoring) return PKV_ERR_UNSUPPORTED;  // (a plan without layers: never to pass for success)
   } else if (sp.layers > 0) {
     for (int32_t l0 = 0; l0 < L; l0 += sp.layers) {
       const int32_t nl = L - l0 < sp.layers ? L - l0 : sp.layers;
@@ -1089,7 +1095,7 @@ int pkv_attention_recall(int32_t L, const pkv_layer_desc* descs, int32_t lse_sup
   const float* raw = reinterpret_cast<const float*>(static_cast<const char*>(workspace) + plan.off_raw);
   int32_t scoring = 0;
   for (int32_t l = 0; l < L; ++l) scoring += descs[l].k_l < d.N ? 1 : 0;
-  const bool sifted = resident && sift_plan(plan, d, lag_plan(plan, d, lse_supplied != 0, seq_lens != nullptr), scoring).Rs > 0;
+  const bool sifted = resident && sift_plan(plan, d, lse_supplied != 0, seq_lens != nullptr, scoring).Rs > 0;
   const int32_t* flags = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + plan.off_cnt) + 2;
   for (int32_t l0 = 0; l0 < L; l0 += kBatchMaxLayers) {
     const int32_t nl = L - l0 < kBatchMaxLayers ? L - l0 : kBatchMaxLayers;
@@ -1134,7 +1140,7 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t variant, in
   if (rc != PKV_OK) return rc;
   if (L < 1 || L > kMaxLayers || !kernel_id || !scratch_bytes || !scratch_room) return PKV_ERR_INVALID_ARG;
   const Plan plan = make_plan(*desc, L);
-  const bool lse_mode = (variant & ~PKV_ROUTE_SEQ_LENS) != 0, ragged = (variant & PKV_ROUTE_SEQ_LENS) != 0;
+  const bool lse_mode = (variant & PKV_ROUTE_LSE) != 0, ragged = (variant & PKV_ROUTE_SEQ_LENS) != 0;
   *kernel_id = PKV_KERNEL_SCORE_ACCUM;
   *scratch_bytes = 0;
   *scratch_room = plan.total - plan.off_pooled;
@@ -1142,6 +1148,7 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t variant, in
   const LagPlan gp = lag_plan(plan, *desc, lse_mode, ragged);
   if (gp.layers > 0) {
     *kernel_id = PKV_KERNEL_SCORE_LAG;
+    if ((variant & PKV_ROUTE_KEPT) != 0 && sift_plan(plan, *desc, lse_mode, ragged, desc->k_l < desc->N ? L : 0).Rs > 0) *kernel_id = PKV_KERNEL_SCORE_SIFT;
     *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.unit_bytes();
     return PKV_OK;
   }
@@ -1161,7 +1168,7 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink, void* stream) 
 int pkv_scoring_sweeps(const pkv_layer_desc* desc, int32_t variant) {
   if (check_desc(desc) != PKV_OK) return 0;
   const Plan plan = make_plan(*desc, 1);
-  if ((variant & ~PKV_ROUTE_SEQ_LENS) != 0) return 1;
+  if ((variant & PKV_ROUTE_LSE) != 0) return 1;
   if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return 2;
   return lag_plan(plan, *desc, false, (variant & PKV_ROUTE_SEQ_LENS) != 0).layers > 0 || stream_plan(plan, *desc, false).layers > 0 ? 1 : 2;
 }

@@ -355,3 +355,29 @@ def test_statistics_of_the_scoring_kernels_fit_the_workspace():
     assert binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8, flags=binding.FLAG_STREAM_SCORING))[0] == "score_accum"
     with pytest.raises(binding.PkvError):
         binding.scoring_route(_shape(1, 8, 8, 64, 4096, 8), 0)
+
+
+def test_sifting_only_where_what_it_hands_on_fits_a_launch():
+    # Any sequence may be handed on to the one-pass kernel, which then deals each sequence whole rounds of the 256 workgroups where a
+    # head has 128 items of 512 keys or 256, and has 255 rounds, less one that is begun: a layer that needs more is not sifted, although the
+    # kernel takes it in order (the scoring of every key, kept_only=False).
+    def rounds(B, Hkv, N):
+        return B * -(-Hkv // (256 // -(-N // 512)))
+
+    def route(B, Hkv, N, R=128, L=1):
+        return binding.scoring_route(_shape(B, R // 32 * Hkv, Hkv, 64, N, 32), L, kept_only=True)[0]
+
+    for B, Hkv, N in ((255, 1, 65536), (510, 1, 65025), (128, 3, 65025), (85, 5, 65536), (64, 7, 65536), (51, 9, 65536), (16, 31, 65536),
+                      (15, 33, 65536), (255, 1, 131072), (85, 3, 130561), (51, 5, 131072)):
+        assert rounds(B, Hkv, N) > 254 and route(B, Hkv, N) == "score_lag"
+        assert route(B - 1, Hkv, N) == ("score_sift" if rounds(B - 1, Hkv, N) <= 254 else "score_lag")
+    sifted = 0
+    for N in (16384, 32768, 45056, 65025, 65536, 130561, 131072):
+        for Hkv in range(1, 65):
+            for B in (1, 2, 3, 5, 15, 16, 17, 31, 51, 63, 64, 72, 85, 102, 128, 170, 254, 255, 510):
+                for R in (96, 128, 160, 512):
+                    if route(B, Hkv, N, R, L=-(-(4 << 20) // (B * Hkv * N))) == "score_sift":
+                        sifted += 1
+                        assert N < 65025 or rounds(B, Hkv, N) <= 254, (B, Hkv, N, R)
+    assert sifted > 10000
+    assert binding.scoring_route(_shape(1, 32, 8, 128, 32768, 32), 32)[0] == "score_lag"  # (scores of every key are asked for)

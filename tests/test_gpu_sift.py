@@ -161,3 +161,28 @@ def test_handed_on():
         _same(call.outputs[l], full.outputs[l])
     a, b = (torch.stack(binding.attention_recall(c)).cpu().numpy() for c in (call, full))
     assert np.abs(a - b).max() <= 1e-5
+
+
+@pytest.mark.parametrize("B,Hkv,tried", [(64, 7, False), (255, 1, False), (51, 5, True), (254, 1, True)])
+def test_many_heads_of_128_items(B, Hkv, tried):
+    """A layer whose heads' rounds do not fit a launch of the kernel that takes what is handed on (rounds of 256 workgroups, two heads
+    of a sequence each: 254 fit) is scored by that kernel alone, every key; otherwise all of it may be handed on.  Queries without a
+    common direction; keys and values of all sequences are the same memory."""
+    N, alpha, G, k = 65536, 32, 4, 100
+    print("sift many heads", B, Hkv, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(B)
+    Q = torch.randn(B, Hkv * G, alpha, 64, generator=g, device=DEV).to(torch.bfloat16)
+    K, V = (torch.randn(1, Hkv, N, 64, generator=g, device=DEV).to(torch.bfloat16).expand(B, -1, -1, -1) for _ in range(2))
+    call = binding.LayersCall([Q], [K], [V], [k], MAX, 7)
+    assert binding.scoring_route(call.descs[0], kept_only=True)[0] == ("score_sift" if tried else "score_lag")
+    call.workspace.fill_(0x7F)  # (what an earlier call left there counts for nothing)
+    call.run()
+    torch.cuda.synchronize()
+    if tried:
+        flags = call.workspace[8:8 + 4 * B * Hkv].view(torch.int32).cpu().numpy().reshape(B, Hkv)
+        assert _sifted(flags).mean() < 0.1  # (nearly all are handed on)
+    for b in (0, B // 2, B - 1):  # one sequence alone: no estimates
+        alone = binding.compress_layer(Q[b:b + 1], K[b:b + 1], V[b:b + 1], k, MAX, 7)
+        for i in range(3):
+            assert torch.equal(call.outputs[0][i][b:b + 1], alone[i])
+    assert (call.outputs[0][3] == k).all()
