@@ -359,8 +359,8 @@ constexpr int64_t kSiftMinTotal = 4 << 20, kSiftMinTotalMany = 3 << 20;  // keys
 struct SiftPlan {
   int Rs;
   LagPlan rest;  // of the sequences that are handed on: any of them, so they are dealt as with sequence lengths
-  // the other kernel's words; sums, estimates, sums over the window; list and three words about it
-  size_t unit_bytes(int N) const { return rest.unit_bytes() + (size_t)Rs * 16 + sift_list(N) * 4 + 12; }
+  // the other kernel's words; sums in four words, estimates, sums over the window; list and three words about it
+  size_t unit_bytes(int N) const { return rest.unit_bytes() + (size_t)Rs * 40 + sift_list(N) * 4 + 12; }
 };
 static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged, int scoring_layers) {
   const SiftPlan none = {0, {0, 0, 0, false}};
@@ -452,7 +452,8 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
     if (sift) {
       const size_t units = (size_t)scoring * plan.BH;
       unsigned long long* const zsum = words4 + (gp.words4 ? units * unit_words4 : 0);
-      float* const omega = reinterpret_cast<float*>(zsum + units * may.Rs);
+      unsigned long long* const zlarge = zsum + units * may.Rs;
+      float* const omega = reinterpret_cast<float*>(zlarge + units * 3 * may.Rs);
       float* const window = omega + units * may.Rs;
       uint32_t* const list = reinterpret_cast<uint32_t*>(window + units * may.Rs);
       int32_t* const about = reinterpret_cast<int32_t*>(list + units * sift_list(d.N));
@@ -478,6 +479,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         fa.words = words + u0 * unit_words;
         if (gp.words4) fa.words4 = words4 + u0 * unit_words4;
         fa.zsum = zsum + u0 * may.Rs;
+        fa.zlarge = zlarge + u0 * 3 * may.Rs;
         fa.omega = omega + u0 * may.Rs;
         fa.window = window + u0 * may.Rs;
         fa.list = list + u0 * sift_list(d.N);

@@ -192,7 +192,8 @@ struct SiftArgs {
   const int32_t* seq_lens;
   float* raw;                 // [layer slot][B][Hkv][N] scores
   float* omega;               // [units][Rs] estimated weights of the rows: 1 / (G z)
-  unsigned long long* zsum;   // [units][Rs] their sums, as the other kernel's words hold them (bit 63: one that does not fit)
+  unsigned long long* zsum;   // [units][Rs] their sums, as the other kernel's words hold them (bit 63: large ones in further words; 62: beyond those)
+  unsigned long long* zlarge; // [units][3][Rs] the further words
   int32_t* flags;             // [layer slot][B][Hkv] bit 0: not worth it; bit 1: not scored exactly
   float* window;              // [units][Rs] sums of the rows over the window keys
   int32_t* done;              // [units] jobs done

@@ -67,8 +67,8 @@ constexpr int kSums = 0, kSums2 = 8, kSums3 = 16, kRefs = kLagRefs, kMax = kLagM
 __device__ __forceinline__ uint32_t word_of(int which, int row) { return (uint32_t)(which + (row >> 3) * 32 + (row & 7)); }
 __device__ __forceinline__ uint32_t half_word_of(int which, int row) { return lag_half_word(which, row); }
 constexpr u64 kOne = 1ull << 52, kBad = 1ull << 62, kBig = 1ull << 63;
-constexpr float kUnits = kSumUnits, kUnits2 = 0x1p11f, kUnits3 = 0x1p-19f, kUnits4 = 0x1p-49f;  // to the 1
-constexpr float kLimit = kSumLimit, kLimit2 = 0x1p43f, kLimit3 = 0x1p73f, kLimit4 = 0x1p103f;   // of an item's sum (256 fit)
+constexpr float kUnits = kSumUnits, kUnits2 = kSumUnits2, kUnits3 = kSumUnits3, kUnits4 = kSumUnits4;
+constexpr float kLimit = kSumLimit, kLimit2 = kSumLimit2, kLimit3 = kSumLimit3, kLimit4 = kSumLimit4;
 
 // An item's sum of a row, at the first and at the second attempt.  What does not fit is marked first, so that whoever finds
 // the item counted sees it.  word4(): the row's last word for large sums, or null.
@@ -338,8 +338,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     if (__builtin_expect(which == kSums && __any(armed & (top < 0)), 0)) {
       const u64* w2 = a.words + (size_t)u * unit_words + word_of(kSums2, 64 * h + lane);
       const u64 b2 = ld64(w2), b3 = ld64(w2 + (kSums3 - kSums2)), b4 = *s_words4 ? ld64(word4_of(u, h, lane)) : 0ull;
-      float z = __builtin_fmaf(as_float(b2), 1.f / kUnits2, sum_of(sum) * (1.f / kUnits));
-      z = __builtin_fmaf(as_float(b4), 1.f / kUnits4, __builtin_fmaf(as_float(b3), 1.f / kUnits3, z));
+      const float z = sum_of_words(sum_of(sum), b2, b3, b4);
       if (top < 0) x = __builtin_amdgcn_rcpf(z) * (scale * (1.f / kUnits));
     }
     if ((top & 0x40000000) != 0) x = __builtin_nanf("");

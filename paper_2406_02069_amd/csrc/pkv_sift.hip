@@ -41,7 +41,7 @@ namespace {
 
 constexpr int kW = 8, kT = kW * 64;   // waves and threads of the kernel that reads K
 constexpr int kPass = 32 * kW;        // keys of a pass
-constexpr u64 kZBad = 1ull << 63;     // an item's sum does not fit
+constexpr u64 kZLarge = 1ull << 63, kZBad = 1ull << 62;  // an item's sum lies in a further word; fits none
 constexpr int kBlockRows = 128, kBlockTiles = kBlockRows / 32;  // query rows that lie in LDS at a time, but for the pass over K
 constexpr int kSiftParts = 8;  // workgroups per unit there
 
@@ -249,6 +249,8 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     s_o[tid] = o;
     a.omega[(size_t)u * a.Rs + row0 + tid] = o;
     a.zsum[(size_t)u * a.Rs + row0 + tid] = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) a.zlarge[((size_t)u * 3 + i) * a.Rs + row0 + tid] = 0;
   }
   if (row0 != 0) return;
   __syncthreads();
@@ -383,11 +385,25 @@ __device__ __forceinline__ bool first_pass(const SiftArgs& a, Pass& p, int* wsum
   return true;
 }
 
-// A row's sum over a workgroup's items of a unit.
+// A row's sum over an item: into what the workgroup adds up of the unit, or, where it is large, into a further word.
+__device__ __forceinline__ void add_item(const SiftArgs& a, int u, int row, float z, u64& sum) {
+  if (__builtin_expect(z <= kSumLimit, 1)) {
+    sum += fixed_point(z, kSumUnits);
+  } else if (z <= kSumLimit4) {
+    const int i = z <= kSumLimit2 ? 0 : z <= kSumLimit3 ? 1 : 2;
+    const u64 y = fixed_point(z, z <= kSumLimit2 ? kSumUnits2 : z <= kSumLimit3 ? kSumUnits3 : kSumUnits4);
+    (void)__hip_atomic_fetch_add(a.zlarge + ((size_t)u * 3 + i) * a.Rs + row, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sum |= kZLarge;
+  } else {
+    sum |= kZBad;
+  }
+}
+// ... over a workgroup's items of the unit.
 __device__ __forceinline__ void add_sum(const SiftArgs& a, int u, int row, u64 sum) {
   u64* z = a.zsum + (size_t)u * a.Rs + row;
-  if (sum & kZBad) (void)__hip_atomic_fetch_or(z, kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  (void)__hip_atomic_fetch_add(z, sum & ~kZBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  constexpr u64 marks = kZLarge | kZBad;
+  if (sum & marks) (void)__hip_atomic_fetch_or(z, sum & marks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  (void)__hip_atomic_fetch_add(z, sum & ~marks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // 65 to 128 rows: they lie in the registers of every wave as matrix operands (but for the last row tile's, for which there are none
@@ -605,9 +621,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_few_kernel(const SiftArgs a)
         float w[kW];
 #pragma unroll
         for (int i = 0; i < kW; ++i) w[i] = z8[i * F::ROWS];
-        const float all = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
-        if (all <= kSumLimit) sum += fixed_point(all, kSumUnits);
-        else sum |= kZBad;
+        add_item(a, cur.u, tid, ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7])), sum);
       }
       zbuf ^= 1;  // (the table is written again behind the next item's barrier)
     }
@@ -816,9 +830,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_many_kernel(const SiftArgs a
         float z[kW];
 #pragma unroll
         for (int w = 0; w < kW; ++w) z[w] = z8[w * a.Rs];
-        const float all = ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
-        if (all <= kSumLimit) sum += fixed_point(all, kSumUnits);
-        else sum |= kZBad;
+        add_item(a, cur.u, tid, ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7])), sum);
       }
       if (a.zbufs == 2) zbuf ^= 1;  // (the table is written again behind the next item's barrier)
       else lds_barrier();
@@ -854,8 +866,13 @@ __global__ __launch_bounds__(kT, 2) void score_sift_many_kernel(const SiftArgs a
 
 // ---- the keys that can be kept ----
 // The row's weight 1 / (G z), the other kernel's to the bit; 0 where its sum is not usable.
-__device__ __forceinline__ float weight_of(const SiftArgs& a, u64 w) {
-  return (w >> 63) != 0 || w < 1024ull ? 0.f : __builtin_amdgcn_rcpf(as_float(w)) * (kSumUnits * a.inv_G);
+__device__ __forceinline__ float weight_of(const SiftArgs& a, int u, int row) {
+  const u64 w = a.zsum[(size_t)u * a.Rs + row];
+  if (__builtin_expect((w & kZLarge) != 0 && (w & kZBad) == 0, 0)) {
+    const u64* large = a.zlarge + (size_t)u * 3 * a.Rs + row;
+    return __builtin_amdgcn_rcpf(sum_of_words(as_float(w & ~kZLarge), large[0], large[a.Rs], large[2 * a.Rs])) * a.inv_G;
+  }
+  return (w & kZBad) != 0 || w < 1024ull ? 0.f : __builtin_amdgcn_rcpf(as_float(w)) * (kSumUnits * a.inv_G);
 }
 
 __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
@@ -883,7 +900,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   };
 
   // rows: the largest and the mean ratio of the weight to its estimate
-  const u64 word = tid < a.R ? a.zsum[(size_t)u * a.Rs + tid] : 0ull;
+  const float weight = tid < a.R ? weight_of(a, u, tid) : 0.f;
   const float omega = tid < a.R ? a.omega[(size_t)u * a.Rs + tid] : 1.f;
   const float row_window = tid < a.R ? a.window[(size_t)u * a.Rs + tid] : 0.f;
   // the pooled score of the middle one, M scores on each side at hand
@@ -984,8 +1001,8 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
     for (int i = tid; i < ngroup4; i += NT) note(i, pooled4(std::integral_constant<int, 2>{}, 4 * i));
   }
   {
-    const float ratio = tid < a.R ? weight_of(a, word) / omega : 0.f;
-    float mx = ratio, sm = ratio, wn = row_window * weight_of(a, word);
+    const float ratio = tid < a.R ? weight / omega : 0.f;
+    float mx = ratio, sm = ratio, wn = row_window * weight;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -1155,7 +1172,7 @@ __global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a, int
   auto row_at = [&](int row) { return query_row_of(a, Q, row); };
   if (tid < a.Rs) {
     const float m = reinterpret_cast<const float*>(a.words + (size_t)u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)];
-    s_r[tid] = make_float2(-m, tid < a.R ? weight_of(a, a.zsum[(size_t)u * a.Rs + tid]) : 0.f);
+    s_r[tid] = make_float2(-m, tid < a.R ? weight_of(a, u, tid) : 0.f);
   }
 #pragma unroll 1
   for (int part = part0; part < jobs; part += kSiftParts) {

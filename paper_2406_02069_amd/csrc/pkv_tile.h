@@ -66,15 +66,20 @@ __device__ __forceinline__ float transpose_sum(const f32x16& t, int lane) {
 // ... of a product whose rows are keys: the key (of the tile's 32) whose sum arrives in a lane.
 __device__ __forceinline__ int transpose_key(int lane) { return (lane & 24) + 4 * (lane >> 5) + ((lane & 6) >> 1); }
 
-// Sums of exponentials as integers, so that the order in which they are added does not show.
-constexpr float kSumUnits = 0x1p30f;   // to the 1
-constexpr float kSumLimit = 0x1p13f;   // of an item's sum (256 of them stay below bit 52)
+// Sums of exponentials as integers, so that the order in which they are added does not show; large ones in further words.
+constexpr float kSumUnits = 0x1p30f, kSumUnits2 = 0x1p11f, kSumUnits3 = 0x1p-19f, kSumUnits4 = 0x1p-49f;  // to the 1
+constexpr float kSumLimit = 0x1p13f, kSumLimit2 = 0x1p43f, kSumLimit3 = 0x1p73f, kSumLimit4 = 0x1p103f;   // of an item's sum (256 of them stay below bit 52)
 __device__ __forceinline__ u64 fixed_point(float z, float scale) {
   const float y = rintf(z * scale);
   const float hi = floorf(y * 0x1p-32f);
   return (u64)(uint32_t)hi << 32 | (uint32_t)__builtin_fmaf(hi, -0x1p32f, y);
 }
 __device__ __forceinline__ float as_float(u64 w) { return __builtin_fmaf((float)(uint32_t)(w >> 32), 0x1p32f, (float)(uint32_t)w); }
+// The sum of all words (first: the one of small sums, as a float).
+__device__ __forceinline__ float sum_of_words(float first, u64 b2, u64 b3, u64 b4) {
+  const float z = __builtin_fmaf(as_float(b2), 1.f / kSumUnits2, first * (1.f / kSumUnits));
+  return __builtin_fmaf(as_float(b4), 1.f / kSumUnits4, __builtin_fmaf(as_float(b3), 1.f / kSumUnits3, z));
+}
 
 }  // namespace
 }  // namespace pkv

@@ -186,3 +186,29 @@ def test_many_heads_of_128_items(B, Hkv, tried):
         for i in range(3):
             assert torch.equal(call.outputs[0][i][b:b + 1], alone[i])
     assert (call.outputs[0][3] == k).all()
+
+
+@pytest.mark.parametrize("d,G,alpha", [(128, 4, 32), (128, 5, 40), (64, 4, 21)])
+def test_large_sums_are_held(d, G, alpha):
+    """Keys that one query sees above all others (a needle), by 2^20, 2^53, 2^78: the sums go to further words, the heads are not
+    handed on for them, and the kept sets are those of the kernel that scores every key."""
+    N, k, unit = 16500, alpha + 60, 1.4426950408889634 / d ** 0.5
+    print("sift large sums", d, G, alpha, flush=True)
+    data = [list(_inputs(1, G, 8, d, N, alpha, seed=20 + l)) for l in range(3)]
+    for (Q, K, V), above in zip(data, (20, 53, 78)):
+        for g in range(8):
+            q = Q[0, g * G:(g + 1) * G].float().reshape(-1, d)
+            row = q[alpha + 5 + g]
+            own = row - q.mean(0)  # what it does not share with the others
+            top = (K[0, g].float() @ row).max().item() * unit
+            K[0, g, 2000 + 1500 * g] = ((above + top) / ((row @ own).item() * unit) * own).to(torch.bfloat16)
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, [k] * 3, AVG, 5)
+    print(flags[:, 0], flush=True)
+    # every layer is tried; a head may be handed on all the same (the strongest keys are seen by many other queries, too)
+    assert (4 * (flags & 1).sum(-1) <= 8).all() and ((flags & 2) != 0).sum() <= 3
+    full, _ = _run(Qs, Ks, Vs, [k] * 3, AVG, 5, scores=True)
+    for l in range(3):
+        _same(call.outputs[l], full.outputs[l])
+    a, b = (torch.stack(binding.attention_recall(c)).cpu().numpy() for c in (call, full))
+    assert np.abs(a - b).max() <= 1e-5
