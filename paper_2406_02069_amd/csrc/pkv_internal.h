@@ -194,7 +194,7 @@ struct SiftArgs {
   float* omega;               // [units][Rs] estimated weights of the rows: 1 / (G z)
   unsigned long long* zsum;   // [units][Rs] their sums, as the other kernel's words hold them (bit 63: large ones in further words; 62: beyond those)
   unsigned long long* zlarge; // [units][3][Rs] the further words
-  int32_t* flags;             // [layer slot][B][Hkv] bit 0: not worth it; bit 1: not scored exactly
+  int32_t* flags;             // [layer slot][B][Hkv] bit 0: objects; bit 1: not scored exactly; bit 2: too few take part
   float* window;              // [units][Rs] sums of the rows over the window keys
   int32_t* done;              // [units] jobs done
   int32_t* total;             // [units] keys listed
@@ -210,13 +210,13 @@ struct SiftArgs {
   int32_t sample_tiles;       // of 32 keys, per wave (8 waves): 2 or 4
   int32_t sample_shift;       // log2 of the sample's runs of eight keys
   int32_t min_share;          // keys of a prefix per key to keep, at least
+  int32_t min_items;          // of a launch that are worth it
   uint32_t alpha_magic, bh_magic, hkv_magic;  // as LagArgs
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;
 };
 hipError_t launch_score_sift(const SiftArgs& a, bool clear_err, hipStream_t s);
-// Whether the heads' flags of a (layer, sequence) have it sifted: a quarter of the heads at most object.  And whether its
-// scores are there then.
+// Whether the heads' flags of a (layer, sequence) have it sifted: a quarter of the heads at most object.
 __device__ __forceinline__ bool sift_takes(const int32_t* flags, int Hkv) {
   int bad = 0;
   for (int g0 = 0; g0 < Hkv; g0 += 8) {
@@ -228,8 +228,14 @@ __device__ __forceinline__ bool sift_takes(const int32_t* flags, int Hkv) {
   }
   return 4 * bad <= Hkv;
 }
-__device__ __forceinline__ bool sift_done(const int32_t* flags, int Hkv) {
-  int bad = 0, failed = 0;
+// And behind the sifting kernels: whether head g's scores are there; how many heads of the sequence are left to score, and the
+// k-th of those.
+constexpr int32_t kSiftLeft = 2 | 4;
+__device__ __forceinline__ bool sift_done(const int32_t* flags, int Hkv, int g) {
+  return (flags[g] & kSiftLeft) == 0 && sift_takes(flags, Hkv);
+}
+__device__ __forceinline__ int sift_left(const int32_t* flags, int Hkv) {
+  int bad = 0, left = 0;
   for (int g0 = 0; g0 < Hkv; g0 += 8) {
     int f[8];
 #pragma unroll
@@ -237,10 +243,17 @@ __device__ __forceinline__ bool sift_done(const int32_t* flags, int Hkv) {
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
       bad += g0 + g < Hkv ? f[g] & 1 : 0;
-      failed |= f[g] & 2;
+      left += g0 + g < Hkv && (f[g] & kSiftLeft) != 0 ? 1 : 0;
     }
   }
-  return 4 * bad <= Hkv && failed == 0;
+  return 4 * bad <= Hkv ? left : Hkv;
+}
+__device__ __forceinline__ int sift_left_at(const int32_t* flags, int Hkv, int left, int k) {
+  if (left == Hkv) return k;
+  int g = 0;
+  for (; g < Hkv; ++g)
+    if ((flags[g] & kSiftLeft) != 0 && k-- == 0) break;
+  return g;
 }
 
 // ---- scoring in two streaming launches for many query rows, over many layers (pkv_sweep.hip) ----
@@ -283,7 +296,7 @@ struct SelectBatchArgs {
   int32_t nrb;         // partial score arrays to add per layer
   float inv_G;         // factor applied to the sum of the partials
   const int32_t* err;  // error word of the scoring kernel (non-zero: a wait was given up), or null
-  const int32_t* flags;  // [layer][B][Hkv] of the sifting kernels: where they scored a sequence, its kept positions are there; or null
+  const int32_t* flags;  // [layer][B][Hkv] of the sifting kernels: where they scored a head, its kept positions are there; or null
   int32_t listed;      // a launch before this one has listed the candidates of long prefixes
 };
 
@@ -351,7 +364,7 @@ struct RecallArgs {
   const int32_t* seq_lens;
   int32_t B, Hkv, N, alpha, nrb;
   float inv_G;         // factor applied to the sum of the partials
-  const int32_t* flags;  // [layer][B][Hkv] of the sifting kernels, first layer of this launch: where they scored a sequence,
+  const int32_t* flags;  // [layer][B][Hkv] of the sifting kernels, first layer of this launch: where they scored a head,
                          // the sum over all keys lies behind its scores; or null
 };
 

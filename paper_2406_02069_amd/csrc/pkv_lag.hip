@@ -147,11 +147,16 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
     __syncthreads();
   } else {
     // A round is one item per workgroup.  Units that may lie in two rounds are dealt one after the other; behind them each
-    // sequence of others starts a round of its own, as many units to a round as fit.  (All of them one after the other, 4
+    // sequence of others starts a round of its own, as many units to a round as fit.  Heads that are scored take no part.  (All of them one after the other, 4
     // sequences of 0.8 .. 1 of 64k keys x 2 layers: 96 rows 497 -> 432 us, 128 rows 500 -> 446, 256 rows 680 -> 586.)
     int* pre = reinterpret_cast<int*>(smem);  // [E + 1] before (layer, sequence) e: items of the former, rounds of the latter << 20
     const int E = a.L * a.B;
     int* wsum = pre + kStreamUnits + 1;
+    auto flags_of = [&](int e) {
+      const int l = e / a.B;
+      return a.flags + ((size_t)a.layer[l].slot * a.B + (e - l * a.B)) * a.Hkv;
+    };
+    auto heads = [&](int e) { return a.flags ? sift_left(flags_of(e), a.Hkv) : a.Hkv; };
     auto length = [&](int b) {
       int n = a.N;
       if (a.seq_lens) {
@@ -166,13 +171,12 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
       int c = 0;
       if (e < E) {
         const int l = e / a.B, n = length(e - l * a.B), parts = (n + KI - 1) / KI;
-        // (whole sequence kept: no scores needed; or they are there)
-        const int32_t* flags = a.flags ? a.flags + ((size_t)a.layer[l].slot * a.B + (e - l * a.B)) * a.Hkv : nullptr;
-        if (a.layer[l].k_l < n && (!flags || !sift_done(flags, a.Hkv))) {
-          if (lag_unit_straddles(parts, MODE)) c = a.Hkv * parts;
+        if (a.layer[l].k_l < n) {  // (whole sequence kept: no scores needed)
+          const int left = heads(e);
+          if (lag_unit_straddles(parts, MODE)) c = left * parts;
           else {
             const int q = kStreamGrid / parts;  // (the host admits no unit of more items than workgroups)
-            c = ((a.Hkv + q - 1) / q) << 20;
+            c = ((left + q - 1) / q) << 20;
           }
         }
       }
@@ -211,14 +215,15 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
           else hi = mid;
         }
         const int rem = j - at(lo), n = length(lo % a.B), parts = (n + KI - 1) / KI;
-        const int at_unit = is_short ? rem : w, k = at_unit / parts;
+        const int at_unit = is_short ? rem : w, k = at_unit / parts, left = heads(lo);
         int g = k;
         mine = true;
         if (!is_short) {
           const int q = kStreamGrid / parts;
           g += rem * q;
-          mine = k < q && g < a.Hkv;
+          mine = k < q && g < left;
         }
+        if (mine && left < a.Hkv) g = sift_left_at(flags_of(lo), a.Hkv, left, g);
         it = make_uint2((uint32_t)(lo * a.Hkv + g), (uint32_t)(at_unit - k * parts) << 20 | (uint32_t)n);
       }
     }

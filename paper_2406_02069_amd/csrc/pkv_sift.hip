@@ -10,9 +10,9 @@
 // are, all below, and the selection finds the kept set among all of them.  tau is a guess (from the largest estimates, less what
 // the weights differ); whether it was low enough is checked, never assumed.
 //
-// Handed on to the lagging one-pass kernel, which scores all keys of a sequence: heads whose estimates are no use (seen in the sample
-// beforehand: the cut lies where keys are many, as with queries that have no common direction), whose sums do not fit, whose list
-// does not fit an eighth of the keys, or that fail the check.  Sums and scores come about exactly as in that kernel (same
+// Handed on to the lagging one-pass kernel, which scores all keys: sequences with heads whose estimates are no use (seen in the
+// sample beforehand: the cut lies where keys are many, as with queries that have no common direction), the whole launch where few
+// are left then, and single heads whose sums fit no word, whose list does not fit an eighth of the keys, or that fail the check.  Sums and scores come about exactly as in that kernel (same
 // references, same order of additions), so that the kept sets are the same to the bit whoever scores.
 //
 // Four launches: sift_prepare_kernel (references, weights o_r from 512 or 1024 keys: the median of eight groups' sums, so that a rare
@@ -368,7 +368,13 @@ __device__ __forceinline__ bool first_pass(const SiftArgs& a, Pass& p, int* wsum
       }
     }
     if (round == 0) {
-      if (run == 0) return false;
+      if (run < a.min_items) {  // (the same in all workgroups): the launches behind this one cost more than is gained
+        for (int u = (int)blockIdx.x * kT + tid; u < a.L * a.B * a.Hkv; u += (int)gridDim.x * kT) {
+          const Unit x = unit_of(a, u);
+          a.flags[(size_t)a.layer[x.l].slot * a.B * a.Hkv + (size_t)x.b * a.Hkv + x.g] |= 4;  // (others may read it now, but bit 0 only)
+        }
+        return false;
+      }
       lo = (int)((int64_t)blockIdx.x * run / gridDim.x);
       hi = (int)((int64_t)(blockIdx.x + 1) * run / gridDim.x);
     }
@@ -884,7 +890,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = blockIdx.x;
   const Unit p = unit_of(a, u);
-  if (a.layer[p.l].k_l >= p.n || !sift_takes(flags_of(a, p.l, p.b), a.Hkv)) return;
+  if (a.layer[p.l].k_l >= p.n || (flags_of(a, p.l, p.b)[p.g] & 4) != 0 || !sift_takes(flags_of(a, p.l, p.b), a.Hkv)) return;
   const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
   const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
   float* raw = a.raw + place * a.N;
@@ -894,7 +900,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   const bool is_avg = a.pool == PKV_POOL_AVG;
   const int r = a.pool == PKV_POOL_NONE ? 0 : (a.pool_w - 1) / 2;
   const float inv_w = 1.f / (float)a.pool_w;
-  // no list: the kernel behind the next one scores the sequence
+  // no list: the kernel behind the next one scores the head
   auto fail = [&]() {
     if (tid == 0) a.flags[place] |= 2;
   };

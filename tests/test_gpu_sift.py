@@ -212,3 +212,73 @@ def test_large_sums_are_held(d, G, alpha):
         _same(call.outputs[l], full.outputs[l])
     a, b = (torch.stack(binding.attention_recall(c)).cpu().numpy() for c in (call, full))
     assert np.abs(a - b).max() <= 1e-5
+
+
+def _scored_again(call, flags):
+    """Per unit of the call's scoring layers: whether the kernel that scores every key has added sums of it."""
+    d, L = call.descs[0], len(flags)
+    need = binding.load().pkv_workspace_bytes(call.descs, call.L)
+    at = need - binding.scoring_route(d, call.L)[2]
+    groups = -(-(d.Hq // d.Hkv * d.alpha) // 64)
+    words = call.workspace[at:at + L * d.B * d.Hkv * groups * 2048].view(torch.int64).view(L, d.B, d.Hkv, groups, 8, 32)
+    return (words[..., :8] != 0).flatten(3).any(-1).cpu().numpy()  # (eight rows' sums, further words, references, maxima)
+
+
+def test_a_head_that_fails_is_handed_on_alone():
+    alpha, G, N, k = 32, 4, 32768, 100
+    data = [list(_inputs(1, G, 8, 128, N, alpha, seed=70 + l)) for l in range(2)]
+    data[1][1][0, 3, 7001] = 4 * data[1][0][0, 13, 5]           # one head's normalisers are far above their estimates
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, [k] * 2, MAX, 7)
+    print(flags[:, 0], flush=True)
+    want = np.zeros((2, 1, 8), bool)
+    want[1, 0, 3] = True
+    assert np.array_equal(flags != 0, want) and np.array_equal(_scored_again(call, flags), want)
+    full, _ = _run(Qs, Ks, Vs, [k] * 2, MAX, 7, scores=True)
+    for l in range(2):
+        _same(call.outputs[l], full.outputs[l])
+    a, b = (torch.stack(binding.attention_recall(c)).cpu().numpy() for c in (call, full))
+    assert np.abs(a - b).max() <= 1e-5
+
+
+@pytest.mark.parametrize("B,N,G,d", [(3, 20000, 4, 64), (2, 65536, 4, 64), (1, 131072, 4, 128), (3, 16500, 9, 128)])
+def test_some_heads_are_handed_on(B, N, G, d):
+    """Single heads of several sequences, of units that are dealt one after the other and of units with rounds of their own (128 and
+    256 items), of an odd number of heads, beside a layer of which all are handed on."""
+    alpha, k, Hkv = 32, 100, 5
+    print("sift some heads", B, N, G, d, flush=True)
+    data = [list(_inputs(B, G, Hkv, d, N, alpha, seed=80 + l)) for l in range(3)]
+    bad = [(l, b, g) for l in (0, 2) for b in range(B) for g in range(Hkv) if (l + b + g) % 3 == 0 and b != 1]
+    for l, b, g in bad:
+        data[l][1][b, g, 4001 + g] = 6 * data[l][0][b, g * G + 1, 5]
+    data[1][0] = torch.randn_like(data[1][0].float()).to(torch.bfloat16)
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, [k] * 3, MAX, 7)
+    print(flags.tolist(), flush=True)
+    for l, b, g in bad:
+        assert flags[l, b, g] & 2
+    assert not _sifted(flags)[1].any() and ((flags[[0, 2]] & 3) == 0).sum() >= 10 * B - len(bad) - 2
+    full, _ = _run(Qs, Ks, Vs, [k] * 3, MAX, 7, scores=True)
+    for l in range(3):
+        _same(call.outputs[l], full.outputs[l])
+
+
+def test_too_few_take_part():
+    """4.5 million keys in the call, 1.5 million of heads that would be sifted: nothing is, and every key is scored."""
+    alpha, G, N, k = 32, 4, 16384, 100
+    data = [list(_inputs(1, G, 8, 128, N, alpha, seed=90 + l)) for l in range(3)]
+    for l in (0, 1):
+        data[l][0] = torch.randn_like(data[l][0].float()).to(torch.bfloat16)
+    Qs, Ks, Vs = ([data[l % 3][i] for l in range(36)] for i in range(3))
+    call = binding.LayersCall(Qs, Ks, Vs, [k] * 36, MAX, 7)
+    call.run()
+    torch.cuda.synchronize()
+    flags = call.workspace[8:8 + 4 * 36 * 8].view(torch.int32).cpu().numpy().reshape(36, 1, 8)
+    print(flags[:3, 0], flush=True)
+    assert (flags & 4).all() and not (flags & 2).any() and _scored_again(call, flags).all()
+    full = binding.LayersCall(Qs, Ks, Vs, [k] * 36, MAX, 7, want_scores=True)
+    full.run()
+    for l in range(36):
+        _same(call.outputs[l], full.outputs[l])
+    for a, b in zip(binding.attention_recall(call), binding.attention_recall(full)):
+        assert torch.equal(a, b)
