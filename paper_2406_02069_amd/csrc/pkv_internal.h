@@ -165,7 +165,11 @@ constexpr int kSiftJob = 256;         // keys scored exactly by a workgroup
 // ... of a unit, at most: an eighth of its keys
 __host__ __device__ constexpr int sift_list(int N) { return N / 8 / kSiftJob * kSiftJob; }
 constexpr int kSiftMinKeys = 4096;    // of a prefix
-// Estimates are no use where more than 16 of 256 sampled keys lie between half the cut's estimate and the cut.  Whole calls of 32
+// Estimates are no use where the scores of 63 keys spread by less than kSiftSpread binades (standard deviation; 0.18 without a common
+// direction, 0.35 at a strength of 0.2, 0.48 at 0.3, 0.63 at 0.4, 0.8 at 0.5, 1.2 at 0.8, 1.8 at 1.2; keys with channels of unequal
+// scales, LogNormal(0, 1), 0.4 .. 1.2 without one), which is seen first.
+constexpr float kSiftSpread = 0.45f;
+// And where more than 16 of 256 sampled keys lie between half the cut's estimate and the cut.  Whole calls of 32
 // layers x 8 heads x 32k keys, 128 rows, us, with 12 and with 16 (where nothing is tried: 705), by the strength of the queries' common
 // direction (the rest: 0.9): 1.0 568 and 555, 0.9 582 and 553, 0.8 620 and 557, 0.7 685 and 596, 0.6 695 and 645, 0.5 788 and 728, 0.4
 // 706 and 751 (two layers in vain; with 20 837), 0.2 706 and 677.

@@ -121,7 +121,23 @@ __device__ __forceinline__ f32x16 product(const bf16x8 (&k)[KS], const u32x4* s_
   return x;
 }
 
+// Sums over the lower 32 lanes and over all of them (the same in all lanes).
+__device__ __forceinline__ float2 wave_sums(float v) {
+#define PKV_DPP_ADD(ctrl, rows) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xF, false))
+  PKV_DPP_ADD(0x111, 0xF);  // as wave_max_lane63
+  PKV_DPP_ADD(0x112, 0xF);
+  PKV_DPP_ADD(0x114, 0xF);
+  PKV_DPP_ADD(0x118, 0xF);
+  PKV_DPP_ADD(0x142, 0xA);
+  PKV_DPP_ADD(0x143, 0xC);
+#undef PKV_DPP_ADD
+  return make_float2(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)));
+}
+
 // ---- estimates of the normalisers of 128 rows of a unit; with its first rows, whether it is worth it ----
+// Where it is not, most is seen from 64 keys, and the sample's multiplications are left out: 32 layers x 8 heads x 32k keys, 128 rows
+// without a common direction, which the one-pass kernel takes in 662 us, 692 -> 679 us; 24 layers, 512 rows, 1466 -> 1370 of 1330 (this
+// kernel's work there costs the next one 70 us more than its own 35); 80 layers 4600 -> 4546 of 4493.
 // What bounds it: latencies, and the address units, which take a fragment's 32 rows one by one.  So queries and the keys that
 // several waves multiply come through LDS (256 units of 128 rows 31 -> 26 us, 640 of 512 rows 154 -> 98, against 64 rows per
 // workgroup and every key as fragments from memory).
@@ -170,9 +186,9 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   qb.commit(s_q);
   __syncthreads();
   const int half = wave & 1, rt = wave >> 1;  // of the reference and window keys: the tile; of the rows
-  f32x16 xw;  // logits of the wave's window keys
+  f32x16 x, xw;  // logits of the wave's keys of the references and of the window
   if (rt < ntile) {
-    const f32x16 x = product_of<KS>(s_k, 32 * half + l32, s_q, 32 * rt + l32, hf);
+    x = product_of<KS>(s_k, 32 * half + l32, s_q, 32 * rt + l32, hf);
     float m = x[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) m = fmaxf(m, x[v]);
@@ -198,6 +214,34 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     for (int v = 0; v < 16; ++v) y += mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(xw[v], a.kappa, nm));
     y = both_halves<false>(y);
     if (hf == 0) s_win[half][32 * rt + l32] = y;
+    // Hopeless ones are seen from the references' keys, before the sample is looked at: the scores of 31 or 32 of them, key 0 not
+    // counted, with weights from themselves, spread little.
+    y = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      x[v] = fast_exp2(__builtin_fmaf(x[v], a.kappa, nm));
+      y += v == 0 && half == 0 && hf == 0 ? 0.f : x[v];
+    }
+    const float o = row0 + 32 * rt + l32 < a.R ? __builtin_amdgcn_rcpf(both_halves<false>(y)) : 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[v] *= o;
+    s_score[64 * rt + 32 * half + transpose_key(lane)] = transpose_sum(x, lane);
+  }
+  __syncthreads();
+  {
+    float e = 0.f;
+    for (int i = 0; i < ntile; ++i) e += s_score[64 * i + lane];
+    const float y = lane == 0 ? 0.f : fast_log2(fmaxf(e, 0x1p-100f));
+    const float2 sum = wave_sums(y);
+    const float off = lane == 0 ? 0.f : y - (lane < 32 ? sum.x * (1.f / 31.f) : (sum.y - sum.x) * (1.f / 32.f));
+    // (a block that is not the unit's first does not decide; that it leaves is rarer, and void weights have the head handed on)
+    const float least = row0 == 0 ? kSiftSpread : 0.75f * kSiftSpread;
+    const bool skip = (a.scored[p.l >> 5] >> (p.l & 31) & 1) != 0 || npre < kSiftMinKeys || (int64_t)kk * a.min_share > npre;
+    if (skip || !(wave_sums(off * off).y >= 61.f * least * least)) {  // (the same in all waves)
+      if (tid < rows) a.omega[(size_t)u * a.Rs + row0 + tid] = 0.f;
+      if (row0 == 0 && tid == 0) *flag = 1;
+      return;
+    }
   }
   float z[kBlockTiles] = {};
 #pragma unroll 1
@@ -287,8 +331,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     int near = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) near += __popcll(__ballot(__uint_as_float(v[j]) >= __uint_as_float(cut) * kSiftNear));
-    const bool skip = (a.scored[p.l >> 5] >> (p.l & 31) & 1) != 0 || npre < kSiftMinKeys || (int64_t)kk * a.min_share > npre || near > at + kSiftMaxNear;
-    if (lane == 0) *flag = skip ? 1 : 0;
+    if (lane == 0) *flag = near > at + kSiftMaxNear ? 1 : 0;
   }
 }
 
@@ -872,8 +915,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_many_kernel(const SiftArgs a
 
 // ---- the keys that can be kept ----
 // The row's weight 1 / (G z), the other kernel's to the bit; 0 where its sum is not usable.
-__device__ __forceinline__ float weight_of(const SiftArgs& a, int u, int row) {
-  const u64 w = a.zsum[(size_t)u * a.Rs + row];
+__device__ __forceinline__ float weight_of(const SiftArgs& a, int u, int row, u64 w) {
   if (__builtin_expect((w & kZLarge) != 0 && (w & kZBad) == 0, 0)) {
     const u64* large = a.zlarge + (size_t)u * 3 * a.Rs + row;
     return __builtin_amdgcn_rcpf(sum_of_words(as_float(w & ~kZLarge), large[0], large[a.Rs], large[2 * a.Rs])) * a.inv_G;
@@ -906,7 +948,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   };
 
   // rows: the largest and the mean ratio of the weight to its estimate
-  const float weight = tid < a.R ? weight_of(a, u, tid) : 0.f;
+  const u64 word = tid < a.R ? a.zsum[(size_t)u * a.Rs + tid] : 0ull;
   const float omega = tid < a.R ? a.omega[(size_t)u * a.Rs + tid] : 1.f;
   const float row_window = tid < a.R ? a.window[(size_t)u * a.Rs + tid] : 0.f;
   // the pooled score of the middle one, M scores on each side at hand
@@ -1007,7 +1049,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
     for (int i = tid; i < ngroup4; i += NT) note(i, pooled4(std::integral_constant<int, 2>{}, 4 * i));
   }
   {
-    const float ratio = tid < a.R ? weight / omega : 0.f;
+    const float weight = tid < a.R ? weight_of(a, u, tid, word) : 0.f, ratio = weight / omega;
     float mx = ratio, sm = ratio, wn = row_window * weight;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -1036,7 +1078,10 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
     anybad += s_red[2][w];
     window += s_red[3][w];
   }
-  mean /= (float)a.R;
+  auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+  rmax = uniform(rmax);
+  window = uniform(window);
+  mean = uniform(mean / (float)a.R);
   if (anybad != 0.f) {
     fail();
     return;
@@ -1178,7 +1223,7 @@ __global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a, int
   auto row_at = [&](int row) { return query_row_of(a, Q, row); };
   if (tid < a.Rs) {
     const float m = reinterpret_cast<const float*>(a.words + (size_t)u * a.groups * (kLagGroupBytes / 8))[lag_half_word(kLagRefs, tid)];
-    s_r[tid] = make_float2(-m, tid < a.R ? weight_of(a, u, tid) : 0.f);
+    s_r[tid] = make_float2(-m, tid < a.R ? weight_of(a, u, tid, a.zsum[(size_t)u * a.Rs + tid]) : 0.f);
   }
 #pragma unroll 1
   for (int part = part0; part < jobs; part += kSiftParts) {

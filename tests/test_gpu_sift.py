@@ -282,3 +282,18 @@ def test_too_few_take_part():
         _same(call.outputs[l], full.outputs[l])
     for a, b in zip(binding.attention_recall(call), binding.attention_recall(full)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("G,alpha,d", [(4, 32, 128), (4, 21, 64), (10, 40, 128)])
+def test_hopeless_head_among_others(G, alpha, d):
+    """Two heads of eight whose queries have no common direction: the sequence is tried, those two have no estimates and are handed on."""
+    N, k = 16500, alpha + 60
+    print("sift hopeless heads", G, alpha, d, flush=True)
+    Q, K, V = _inputs(1, G, 8, d, N, alpha, seed=G + alpha)
+    for g in (2, 7):
+        Q[0, g * G:(g + 1) * G] = torch.randn_like(Q[0, g * G:(g + 1) * G].float()).to(torch.bfloat16)
+    call, flags = _run([Q], [K], [V], [k], MAX, 7)
+    print(flags[0, 0], flush=True)
+    assert flags[0, 0].tolist() == [0, 0, 3, 0, 0, 0, 0, 3]
+    full, _ = _run([Q], [K], [V], [k], MAX, 7, scores=True)
+    _same(call.outputs[0], full.outputs[0])
