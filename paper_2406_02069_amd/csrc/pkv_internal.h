@@ -178,6 +178,12 @@ constexpr int kSiftMaxNear = 16;
 // The guess of tau: the estimate that kSiftRank times the groups that the kept keys are thought to fill reach, times what the mean
 // ratio of weight to estimate is below the largest, times kSiftSlack (0.95 and 1: one head in a hundred fails the check).
 constexpr float kSiftSlack = 0.9f, kSiftRank = 1.2f;
+// Less by kSiftApart binades per unit of the ratios' relative deviation from kSiftApartFrom on, where the rows' weights lie apart, as
+// they do with key channels of unequal scales.  32 layers x 8 heads x 32k keys, 128 rows, average and max pooling, and 24 layers, 512
+// rows, max, us, without estimates, without this and with it: scales LogNormal(0, 0.6) 675, 941, 590; 675, 1042, 590; 1326, 2297, 1137;
+// LogNormal(0, 0.95) 697, 1205, 747; 699, 1203, 809; 1471, 2481, 1587; LogNormal(0, 1.1) 856, 1354, 1050; 857, 1349, 1147; 1564, 2547, 2120
+// (of the heads 2 %, 25 % and 60 % are handed on; 3 from 0.12 on: 594, 589, 1140; 779, 832, 1600; 8 from 0.15 on: 598, 597, 1137; 737, 775, 1628).
+constexpr float kSiftApart = 5.f, kSiftApartFrom = 0.15f;
 constexpr int kSiftMaxPoolW = 17;
 
 // (two where they fit the LDS beside the queries)

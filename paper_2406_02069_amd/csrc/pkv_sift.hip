@@ -927,7 +927,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   extern __shared__ uint32_t smem_u[];  // [N / 8] the largest of every four, upper 16 bits | [N / 32] a bit per key
   __shared__ __attribute__((aligned(16))) uint32_t hist[HIST];
   __shared__ uint32_t scan[2 * NW], sel[4];
-  __shared__ float s_red[4][NW];
+  __shared__ float s_red[5][NW];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = blockIdx.x;
@@ -1050,11 +1050,12 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   }
   {
     const float weight = tid < a.R ? weight_of(a, u, tid, word) : 0.f, ratio = weight / omega;
-    float mx = ratio, sm = ratio, wn = row_window * weight;
+    float mx = ratio, sm = ratio, sq = ratio * ratio, wn = row_window * weight;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       mx = fmaxf(mx, __shfl_xor(mx, o));
       sm += __shfl_xor(sm, o);
+      sq += __shfl_xor(sq, o);
       wn += __shfl_xor(wn, o);
     }
     const bool bad = __any(tid < a.R && !(ratio > 0.f && ratio < INFINITY));
@@ -1066,22 +1067,25 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
       s_red[1][wave] = sm;
       s_red[2][wave] = bad ? 1.f : 0.f;
       s_red[3][wave] = wn;
+      s_red[4][wave] = sq;
       scan[wave] = m;
     }
   }
   __syncthreads();
-  float rmax = 1.f, mean = 0.f, anybad = 0.f, window = 0.f;
+  float rmax = 1.f, mean = 0.f, square = 0.f, anybad = 0.f, window = 0.f;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     rmax = fmaxf(rmax, s_red[0][w]);
     mean += s_red[1][w];
     anybad += s_red[2][w];
     window += s_red[3][w];
+    square += s_red[4][w];
   }
   auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
   rmax = uniform(rmax);
   window = uniform(window);
   mean = uniform(mean / (float)a.R);
+  const float apart = uniform(__builtin_sqrtf(fmaxf(square / (float)a.R - mean * mean, 0.f)) / mean);
   if (anybad != 0.f) {
     fail();
     return;
@@ -1113,7 +1117,24 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
       }
     }
     const float edge = __uint_as_float(bins.lower_edge(__builtin_amdgcn_readfirstlane(sel[0])));
-    const float tau = edge * fminf(1.f, kSiftSlack * mean / rmax);
+    // (less where the ratios lie apart, as far as there is room for what is listed then: about four keys per group)
+    float slack = kSiftSlack;
+    for (float less = fminf(kSiftApart * fmaxf(apart - kSiftApartFrom, 0.f), 4.f); less > 0.f; less = less > 0.25f ? less * (1.f / 3.f) : 0.f) {
+      const float lower = kSiftSlack * fast_exp2(-less);
+      const uint32_t low16 = __float_as_uint(edge * fminf(1.f, lower * mean / rmax)) >> 16;
+      uint32_t cnt = 0u, groups;
+      for (int i = tid; i < ngroup4; i += NT) cnt += gmax[i] >= low16 ? 1u : 0u;
+      cnt = wave_inclusive_sum(cnt);
+      if (lane == 63) scan[wave] = cnt;
+      __syncthreads();
+      (void)sum_before(scan, wave, groups);
+      __syncthreads();
+      if (4u * groups <= (uint32_t)sift_list(a.N)) {  // (uniform)
+        slack = lower;
+        break;
+      }
+    }
+    const float tau = edge * fminf(1.f, slack * mean / rmax);
     bound = tau * rmax * (1.f + 0x1p-9f);
     if (!(tau > 0x1p-60f) || !(bound < 0x1p100f)) {
       fail();

@@ -297,3 +297,26 @@ def test_hopeless_head_among_others(G, alpha, d):
     assert flags[0, 0].tolist() == [0, 0, 3, 0, 0, 0, 0, 3]
     full, _ = _run([Q], [K], [V], [k], MAX, 7, scores=True)
     _same(call.outputs[0], full.outputs[0])
+
+
+@pytest.mark.parametrize("pool,pw,strength,scale", [(AVG, 5, 1.2, 0.8), (MAX, 7, 1.2, 0.8)])
+def test_most_heads_pass(pool, pw, strength, scale):
+    """Key channels of unequal scales (LogNormal(0, scale)), which set the rows' weights apart from their estimates, and queries with a weak
+    common direction: most heads pass their check, and all kept sets are those of the kernel that scores every key."""
+    alpha, G, N, L = 32, 4, 32768, 4
+    print("sift most heads", pool, pw, strength, scale, flush=True)
+    data = []
+    for l in range(L):
+        Q, K, V = _inputs(1, G, 8, 128, N, alpha, seed=110 + l)
+        g = torch.Generator(device=DEV).manual_seed(7 + l)
+        base = torch.randn(1, 8, 1, 1, 128, generator=g, device=DEV)
+        Q = (strength * base + 0.9 * torch.randn(1, 8, G, alpha, 128, generator=g, device=DEV)).reshape(Q.shape).to(torch.bfloat16)
+        K *= torch.exp(scale * torch.randn(1, 8, 1, 128, generator=g, device=DEV)).to(torch.bfloat16)
+        data.append((Q, K, V))
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, [alpha + 96] * L, pool, pw)
+    print(flags[:, 0], flush=True)
+    assert (4 * (flags & 1).sum(-1) <= 8).all() and ((flags & 2) != 0).sum() <= 8 * L // 3
+    full, _ = _run(Qs, Ks, Vs, [alpha + 96] * L, pool, pw, scores=True)
+    for l in range(L):
+        _same(call.outputs[l], full.outputs[l])
