@@ -499,6 +499,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         // (so that the list fits an eighth of the keys: it holds about 4 keys per key to keep, with average pooling 2.5 + w)
         fa.min_share = fa.pool == PKV_POOL_AVG ? 27 + 11 * d.pool_w : 43;
         fa.min_items = (int32_t)((plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal) / 4 * 3 / kLagKeys);
+        fa.max_near = fa.pool == PKV_POOL_AVG ? kSiftMaxNearAvg : kSiftMaxNear;
         fa.alpha_magic = alpha_magic;
         fa.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;
         fa.hkv_magic = 0xFFFFFFFFu / (uint32_t)d.Hkv;

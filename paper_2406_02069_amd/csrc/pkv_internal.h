@@ -169,12 +169,15 @@ constexpr int kSiftMinKeys = 4096;    // of a prefix
 // direction, 0.35 at a strength of 0.2, 0.48 at 0.3, 0.63 at 0.4, 0.8 at 0.5, 1.2 at 0.8, 1.8 at 1.2; keys with channels of unequal
 // scales, LogNormal(0, 1), 0.4 .. 1.2 without one), which is seen first.
 constexpr float kSiftSpread = 0.45f;
-// And where more than 16 of 256 sampled keys lie between half the cut's estimate and the cut.  Whole calls of 32
-// layers x 8 heads x 32k keys, 128 rows, us, with 12 and with 16 (where nothing is tried: 705), by the strength of the queries' common
-// direction (the rest: 0.9): 1.0 568 and 555, 0.9 582 and 553, 0.8 620 and 557, 0.7 685 and 596, 0.6 695 and 645, 0.5 788 and 728, 0.4
-// 706 and 751 (two layers in vain; with 20 837), 0.2 706 and 677.
+// And where more than so many of 256 sampled keys lie between half the cut's estimate and the cut (with average pooling the lists are
+// longer).  Whole calls of 32k keys x 8 heads, us, without estimates and with at most 16, 32, 64 and 128 (average pooling 16, 24, 32 and
+// 48), by the strength of the queries' common direction (the rest: 0.9):
+//   32 layers, 128 rows, max: 0.3 678, 699, 700, 696, 716; 0.4 682, 700, 697, 594, 589; 0.5 681, 703, 613, 580, 578; 0.7 681, 641, 548, 546, 544
+//   24 layers, 512 rows, max: 0.3 1375, 1458, 1449, 1577, 1552; 0.4 1373, 1466, 1294, 1177, 1176; 0.5 1378, 1467, 1109, 1108, 1109
+//   32 layers, 128 rows, average: 0.4 680, 705, 703, 703, 829; 0.5 677, 704, 714, 680, 662; 0.6 683, 703, 645, 611, 612; 0.7 679, 645, 595, 597, 595
+//   24 layers, 512 rows, average: 0.4 1370, 1521, 1515, 1817, 1928; 0.5 1377, 1506, 1443, 1375, 1357; 0.6 1360, 1357, 1230, 1209, 1211
 constexpr float kSiftNear = 0.5f;
-constexpr int kSiftMaxNear = 16;
+constexpr int kSiftMaxNear = 48, kSiftMaxNearAvg = 24;
 // The guess of tau: the estimate that kSiftRank times the groups that the kept keys are thought to fill reach, times what the mean
 // ratio of weight to estimate is below the largest, times kSiftSlack (0.95 and 1: one head in a hundred fails the check).
 constexpr float kSiftSlack = 0.9f, kSiftRank = 1.2f;
@@ -221,6 +224,7 @@ struct SiftArgs {
   int32_t sample_shift;       // log2 of the sample's runs of eight keys
   int32_t min_share;          // keys of a prefix per key to keep, at least
   int32_t min_items;          // of a launch that are worth it
+  int32_t max_near;           // of the sampled keys near the cut
   uint32_t alpha_magic, bh_magic, hkv_magic;  // as LagArgs
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;

@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     int near = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) near += __popcll(__ballot(__uint_as_float(v[j]) >= __uint_as_float(cut) * kSiftNear));
-    if (lane == 0) *flag = near > at + kSiftMaxNear ? 1 : 0;
+    if (lane == 0) *flag = near > at + a.max_near ? 1 : 0;
   }
 }
 

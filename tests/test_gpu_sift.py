@@ -299,7 +299,7 @@ def test_hopeless_head_among_others(G, alpha, d):
     _same(call.outputs[0], full.outputs[0])
 
 
-@pytest.mark.parametrize("pool,pw,strength,scale", [(AVG, 5, 1.2, 0.8), (MAX, 7, 1.2, 0.8)])
+@pytest.mark.parametrize("pool,pw,strength,scale", [(AVG, 5, 1.2, 0.8), (MAX, 7, 1.2, 0.8), (MAX, 7, 0.6, 0.0), (AVG, 5, 0.7, 0.0)])
 def test_most_heads_pass(pool, pw, strength, scale):
     """Key channels of unequal scales (LogNormal(0, scale)), which set the rows' weights apart from their estimates, and queries with a weak
     common direction: most heads pass their check, and all kept sets are those of the kernel that scores every key."""
