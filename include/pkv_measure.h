@@ -106,7 +106,7 @@ int pkv_probe_read(const void* buf, size_t bytes, uint32_t* sink,
  * kernel_id      written: PKV_KERNEL_SCORE_STREAM, _LAG, _SWEEP, _RESIDENT, or
  *                _ACCUM for the per-layer kernels; with PKV_ROUTE_KEPT also
  *                _SIFT, which _LAG follows for what it does not take.
- * scratch_bytes  written: bytes of statistics that a launch addresses.
+ * scratch_bytes  written: bytes of statistics that the call's launches address.
  * scratch_room   written: bytes of the workspace region that holds them.
  * Returns PKV_OK, PKV_ERR_INVALID_ARG or PKV_ERR_UNSUPPORTED.
  */

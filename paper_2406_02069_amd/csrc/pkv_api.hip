@@ -1151,9 +1151,11 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t variant, in
   if (!plan.resident_ok || (desc->flags & PKV_FLAG_STREAM_SCORING)) return PKV_OK;
   const LagPlan gp = lag_plan(plan, *desc, lse_mode, ragged);
   if (gp.layers > 0) {
-    *kernel_id = PKV_KERNEL_SCORE_LAG;
-    if ((variant & PKV_ROUTE_KEPT) != 0 && sift_plan(plan, *desc, lse_mode, ragged, desc->k_l < desc->N ? L : 0).Rs > 0) *kernel_id = PKV_KERNEL_SCORE_SIFT;
-    *scratch_bytes = (size_t)std::min(L, gp.layers) * plan.BH * gp.unit_bytes();
+    // (the words of all layers lie there at once, whatever the launches; with the sifting kernels' sums, weights and lists behind them)
+    const SiftPlan fp = sift_plan(plan, *desc, lse_mode, ragged, desc->k_l < desc->N ? L : 0);
+    const bool sift = (variant & PKV_ROUTE_KEPT) != 0 && fp.Rs > 0;
+    *kernel_id = sift ? PKV_KERNEL_SCORE_SIFT : PKV_KERNEL_SCORE_LAG;
+    *scratch_bytes = (size_t)L * plan.BH * (sift ? fp.unit_bytes(desc->N) : gp.unit_bytes());
     return PKV_OK;
   }
   const SweepPlan wp = sweep_plan(plan, *desc, lse_mode);

@@ -381,3 +381,30 @@ def test_sifting_only_where_what_it_hands_on_fits_a_launch():
                         assert N < 65025 or rounds(B, Hkv, N) <= 254, (B, Hkv, N, R)
     assert sifted > 10000
     assert binding.scoring_route(_shape(1, 32, 8, 128, 32768, 32), 32)[0] == "score_lag"  # (scores of every key are asked for)
+
+
+def test_statistics_of_the_sifting_kernels_fit_the_workspace():
+    # sums, weights and lists of all layers lie behind one another, behind the one-pass kernel's words (2 KB and 0.5 KB per 64 rows), in the
+    # 4 bytes per key that hold the pooled scores later on
+    taken = {}
+    for Hkv, G, alpha in ((8, 4, 32), (8, 4, 17), (8, 8, 64), (1, 5, 40), (3, 9, 57), (32, 16, 32)):
+        R = G * alpha
+        groups, rows = -(-R // 64), -(-R // 64) * 64
+        for d in (64, 128):
+            for B in (1, 3):
+                for N in (16383, 16384, 16385, 20001, 32768, 45056, 65536, 131072, 131073 + alpha):
+                    for L in (1, 2, 32, 33, 95, 96, 97, 126):
+                        desc = _shape(B, G * Hkv, Hkv, d, N, alpha)
+                        kernel, used, room = binding.scoring_route(desc, L, kept_only=True)
+                        assert used <= room == -(-4 * L * B * Hkv * N // 256) * 256, (B, Hkv, G, alpha, N, L, kernel, used, room)
+                        units = L * B * Hkv
+                        if kernel == "score_lag":
+                            assert used == units * groups * 2560
+                        if kernel == "score_sift":
+                            # sums in four words, weights, sums over the window; positions of an eighth of the keys, three words
+                            assert used == units * (groups * 2560 + rows * 40 + N // 8 // 256 * 256 * 4 + 12)
+                            assert R >= 65 and N >= 16384 and units * N >= (3 << 20 if R > 128 else 4 << 20)
+                        taken[kernel] = taken.get(kernel, 0) + 1
+                        assert binding.scoring_route(desc, L)[0] != "score_sift"
+                        assert binding.scoring_route(desc, L, lse_supplied=True, kept_only=True)[0] != "score_sift"
+    assert taken["score_sift"] > 200 and taken["score_lag"] > 200
