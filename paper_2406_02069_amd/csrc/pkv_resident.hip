@@ -52,6 +52,7 @@
 #include <type_traits>
 
 #include "pkv_internal.h"
+#include "pkv_lds.h"
 
 namespace pkv {
 namespace {
@@ -115,17 +116,6 @@ __device__ __forceinline__ u64 split3(float c) {
 __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+v"(v));
   return v;
-}
-
-// Workgroup barrier that orders LDS traffic only.  A full __syncthreads() carries fences over global memory as
-// well, and the waits the compiler builds for them include, since memory operations retire in order, every key
-// load requested before: exactly the loads that are meant to stay in flight across the barrier.  (Neither kind
-// of barrier waits for the acknowledgement of outstanding global stores: where another workgroup is told that
-// data is ready, the storing waves wait for vmcnt(0) themselves.)
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ void st64(u64* p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }

@@ -51,6 +51,7 @@ __device__ __forceinline__ int fresh(int v) {
   return v;
 }
 
+// Number of set bits of m below this lane.
 __device__ __forceinline__ uint32_t bits_below(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }

@@ -71,7 +71,6 @@ __device__ __forceinline__ uint32_t sum_before(const uint32_t* per_wave, int wav
   return wave > 0 ? incl : 0u;
 }
 
-// Number of set bits of m below this lane.
 // The bin in which the count over ascending bins reaches kk: sel[0] = bin, sel[1] = count before it, sel[2] = count in it
 // (untouched if there is none).  Returns the count over all bins.  Thread t owns bins 2t, 2t + 1 and leaves them cleared.
 // Every thread returns after the answer is there.  (Bins 0 .. HIST - 1, `scan` holds NW entries.)

@@ -483,7 +483,7 @@ __global__ __launch_bounds__(kT, 2) void score_sift_few_kernel(const SiftArgs a)
   float* s_end = s_z + 2 * kW * F::ROWS;                                 // [kW][ROWS] a wave's sums behind a unit's end
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    u32x4* s_k = smem + wave * 2 * F::TILE;  // [2][32] keys, slot s of key i at s ^ (i % SEG) (bank-free)
+  u32x4* s_k = smem + wave * 2 * F::TILE;  // [2][32] keys, slot s of key i at s ^ (i % SEG) (bank-free)
   const uint32_t s_k_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_k);
 
   Pass cur;

@@ -47,6 +47,7 @@
 #include <type_traits>
 
 #include "pkv_internal.h"
+#include "pkv_lds.h"
 
 namespace pkv {
 namespace {
@@ -71,11 +72,6 @@ __device__ __forceinline__ bf16x8 as_frag(u32x4 u) { return __builtin_bit_cast(b
 __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+v"(v));
   return v;
-}
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 // LDS traffic of one wave to its own region needs ordering only inside the wave.
 __device__ __forceinline__ void wave_lds_fence() {
