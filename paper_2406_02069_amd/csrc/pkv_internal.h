@@ -246,7 +246,8 @@ __device__ __forceinline__ bool sift_takes(const int32_t* flags, int Hkv) {
 // k-th of those.
 constexpr int32_t kSiftLeft = 2 | 4;
 __device__ __forceinline__ bool sift_done(const int32_t* flags, int Hkv, int g) {
-  return (flags[g] & kSiftLeft) == 0 && sift_takes(flags, Hkv);
+  const int32_t own = flags[g];  // (under way together with the others)
+  return sift_takes(flags, Hkv) && (own & kSiftLeft) == 0;
 }
 __device__ __forceinline__ int sift_left(const int32_t* flags, int Hkv) {
   int bad = 0, left = 0;

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   }
   kb.commit(s_k);
   qb.commit(s_q);
-  __syncthreads();
+  lds_barrier();
   const int half = wave & 1, rt = wave >> 1;  // of the reference and window keys: the tile; of the rows
   f32x16 x, xw;  // logits of the wave's keys of the references and of the window
   if (rt < ntile) {
@@ -199,13 +199,13 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     }
     xw = product_of<KS>(s_k, 64 + 32 * half + l32, s_q, 32 * rt + l32, hf);
   }
-  __syncthreads();
+  lds_barrier();
   if (tid < rows) {
     const float m = fmaxf(s_part[0][tid], s_part[1][tid]);
     s_m[tid] = m;
     reinterpret_cast<float*>(words)[lag_half_word(kLagRefs, tid)] = m;
   }
-  __syncthreads();
+  lds_barrier();
   if (rt < ntile) {
     const int lim = min(row0 + 32 * rt + l32, a.R - 1) % a.alpha - 32 * half - 4 * hf;  // last window key the lane's query sees
     const float nm = -s_m[32 * rt + l32];
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     for (int v = 0; v < 16; ++v) x[v] *= o;
     s_score[64 * rt + 32 * half + transpose_key(lane)] = transpose_sum(x, lane);
   }
-  __syncthreads();
+  lds_barrier();
   {
     float e = 0.f;
     for (int i = 0; i < ntile; ++i) e += s_score[64 * i + lane];
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     const float y = both_halves<false>(z[q]);
     if (hf == 0) s_part[wave][32 * q + l32] = y;
   }
-  __syncthreads();
+  lds_barrier();
   if (tid < rows) {
     // half the sum of the two middle ones of the groups: a rare large key does not count
     float v[kW], mid = 0.f;
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     for (int i = 0; i < 3; ++i) a.zlarge[((size_t)u * 3 + i) * a.Rs + row0 + tid] = 0;
   }
   if (row0 != 0) return;
-  __syncthreads();
+  lds_barrier();
   // estimated scores (of these rows) of a part of the sample without key 0: a sink's is far above the others, is kept in any case, and
   // as the cut said that few keys lie near it (80 layers x 32k keys, 512 rows without a common direction, a sink: tried in vain, 4.5 ms
   // became 8.4; now 4.8)
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     for (int v = 0; v < 16; ++v) t[v] = __builtin_fmaf(o, fast_exp2(__builtin_fmaf(x[v], a.kappa, nm)), t[v]);
   }
   s_score[32 * wave + transpose_key(lane)] = transpose_sum(t, lane);
-  __syncthreads();
+  lds_barrier();
   if (wave == 0) {
     // the cut's place in it, and how many of its keys lie near the cut or above
     uint32_t v[4];
@@ -932,7 +932,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = blockIdx.x;
   const Unit p = unit_of(a, u);
-  if (a.layer[p.l].k_l >= p.n || (flags_of(a, p.l, p.b)[p.g] & 4) != 0 || !sift_takes(flags_of(a, p.l, p.b), a.Hkv)) return;
+  if (a.layer[p.l].k_l >= p.n || !sift_done(flags_of(a, p.l, p.b), a.Hkv, p.g)) return;  // (bit 1 comes from here, and from behind here)
   const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
   const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
   float* raw = a.raw + place * a.N;
@@ -1050,14 +1050,9 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   }
   {
     const float weight = tid < a.R ? weight_of(a, u, tid, word) : 0.f, ratio = weight / omega;
-    float mx = ratio, sm = ratio, sq = ratio * ratio, wn = row_window * weight;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      mx = fmaxf(mx, __shfl_xor(mx, o));
-      sm += __shfl_xor(sm, o);
-      sq += __shfl_xor(sq, o);
-      wn += __shfl_xor(wn, o);
-    }
+    // (a ratio that is not a number has the largest bits of all; it is seen below)
+    const float mx = __int_as_float(__builtin_amdgcn_readlane((int)wave_max_lane63(__float_as_uint(ratio)), 63));
+    const float sm = wave_sums(ratio).y, sq = wave_sums(ratio * ratio).y, wn = wave_sums(row_window * weight).y;
     const bool bad = __any(tid < a.R && !(ratio > 0.f && ratio < INFINITY));
     kmax = row_max_lane15(kmax);
     const uint32_t m = min(min((uint32_t)__builtin_amdgcn_readlane((int)kmax, 15), (uint32_t)__builtin_amdgcn_readlane((int)kmax, 31)),
