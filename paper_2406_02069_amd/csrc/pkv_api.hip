@@ -345,13 +345,13 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
 
 // How the sifting kernels serve a call whose shape the lagging kernel takes: padded rows (0: they do not).  The two give the
 // same kept sets to the bit (the scores that decide them are the same to the bit), so that here the number of layers may count.
-// Where the lines lie, whole calls, before -> with these kernels, us: five launches instead of two cost about 100 us where
-//   keys are few, and a key costs less by a quarter at 128 rows and a fifth at 512.  32 layers of 8 heads x 32k keys, 128 rows
-//   673 -> 545; x 128k 3325 -> 1870; 80 layers x 32k, 512 rows 4390 -> 3500.  128 rows, 4 million keys of 32k 356 -> 302, of 16k 337 ->
+// Where the lines lie, whole calls, before -> with these kernels, us: five launches instead of two before the selection cost about
+//   100 us where keys are few, and a key costs less by a quarter at 128 rows and a fifth at 512.  32 layers of 8 heads x 32k keys, 128
+//   rows 677 -> 542; x 128k 3246 -> 1850; 80 layers x 32k, 512 rows 4418 -> 3500.  128 rows, 4 million keys of 32k 356 -> 302, of 16k 337 ->
 //   316, of 128k 458 -> 316; 3 million 272 -> 249, 259 -> 259; 2 million 193 -> 194, 181 -> 194, 258 -> 214; 1 million 106 -> 125.
 //   512 rows, of 32k keys, 3 million 700 -> 593, 2 million 480 -> 418, 1 million 250 -> 241; 256 rows, 4 million 522 -> 456, 2 million
-//   284 -> 271, 1 million 153 -> 173.  Uncorrelated queries (32 layers x 32k, 128 rows), whose layers are all handed on: 670 -> 705, and
-//   as much more at fewer keys, so that the lines lie where the gain is a sixth.
+//   284 -> 271, 1 million 153 -> 173.  Queries without a common direction (32 layers x 32k, 128 rows), whose heads are all handed on:
+//   662 -> 677, and as much more at fewer keys, so that the lines lie where the gain is a sixth.
 // The statistics, lists and jobs lie where the pooled scores lie later on, behind the words of the lagging kernel.
 constexpr int kSiftMinRows = 65;     // (64 rows: K's read binds either way)
 constexpr int kSiftMinLen = 16384;
@@ -499,7 +499,7 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         // (so that the list fits an eighth of the keys: it holds about 4 keys per key to keep, with average pooling 2.5 + w)
         fa.min_share = fa.pool == PKV_POOL_AVG ? 27 + 11 * d.pool_w : 43;
         fa.min_items = (int32_t)((plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal) / 4 * 3 / kLagKeys);
-        fa.max_near = fa.pool == PKV_POOL_AVG ? kSiftMaxNearAvg : kSiftMaxNear;
+        fa.min_spread = fa.pool == PKV_POOL_AVG ? kSiftSpreadAvg : kSiftSpread;
         fa.alpha_magic = alpha_magic;
         fa.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;
         fa.hkv_magic = 0xFFFFFFFFu / (uint32_t)d.Hkv;

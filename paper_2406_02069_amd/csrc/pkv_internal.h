@@ -165,27 +165,28 @@ constexpr int kSiftJob = 256;         // keys scored exactly by a workgroup
 // ... of a unit, at most: an eighth of its keys
 __host__ __device__ constexpr int sift_list(int N) { return N / 8 / kSiftJob * kSiftJob; }
 constexpr int kSiftMinKeys = 4096;    // of a prefix
-// Estimates are no use where the scores of 63 keys spread by less than kSiftSpread binades (standard deviation; 0.18 without a common
-// direction, 0.35 at a strength of 0.2, 0.48 at 0.3, 0.63 at 0.4, 0.8 at 0.5, 1.2 at 0.8, 1.8 at 1.2; keys with channels of unequal
-// scales, LogNormal(0, 1), 0.4 .. 1.2 without one), which is seen first.
-constexpr float kSiftSpread = 0.45f;
-// And where more than so many of 256 sampled keys lie between half the cut's estimate and the cut (with average pooling the lists are
-// longer).  Whole calls of 32k keys x 8 heads, us, without estimates and with at most 16, 32, 64 and 128 (average pooling 16, 24, 32 and
-// 48), by the strength of the queries' common direction (the rest: 0.9):
-//   32 layers, 128 rows, max: 0.3 678, 699, 700, 696, 716; 0.4 682, 700, 697, 594, 589; 0.5 681, 703, 613, 580, 578; 0.7 681, 641, 548, 546, 544
-//   24 layers, 512 rows, max: 0.3 1375, 1458, 1449, 1577, 1552; 0.4 1373, 1466, 1294, 1177, 1176; 0.5 1378, 1467, 1109, 1108, 1109
-//   32 layers, 128 rows, average: 0.4 680, 705, 703, 703, 829; 0.5 677, 704, 714, 680, 662; 0.6 683, 703, 645, 611, 612; 0.7 679, 645, 595, 597, 595
-//   24 layers, 512 rows, average: 0.4 1370, 1521, 1515, 1817, 1928; 0.5 1377, 1506, 1443, 1375, 1357; 0.6 1360, 1357, 1230, 1209, 1211
-constexpr float kSiftNear = 0.5f;
-constexpr int kSiftMaxNear = 48, kSiftMaxNearAvg = 24;
+// Estimates are no use where the scores of 63 keys spread by less than kSiftSpread binades (standard deviation; with average pooling,
+// whose lists are longer, kSiftSpreadAvg): about 0.18 without a common direction of the queries, 0.35 at a strength of 0.2 (the rest:
+// 0.9), 0.48 at 0.3, 0.63 at 0.4, 0.8 at 0.5, 1.2 at 0.8, 1.8 at 1.2.  Whole calls of 8 heads x 32k keys, us, without estimates and with them from
+// this spread on:
+//   24 layers, 512 rows, max, 0.36, 0.42, 0.5 and 0.58: 0.25 1317, 1530, 1342, 1342, -; 0.3 1314, 1228, 1273, 1356, 1341; 0.35 1325, 1117, 1144,
+//     1193, 1346; 0.4 1328, -, 1069, 1122, 1197.  Window 13: 0.25 1331, 1594, 1352, 1348; 0.3 1326, 1306, 1354, 1357; no pooling: 0.25 1311, 1154, 1345, 1341
+//   32 layers, 128 rows, max, likewise: 0.25 675, 678, 693, 699, -; 0.3 680, 609, 632, 694, 692; 0.35 671, 588, 583, 611, 690
+//   24 layers, 512 rows, average, 0.62, 0.7 and 0.78: 0.4 1311, 1360, 1359, 1354; 0.45 1311, 1485, 1358, 1358; 0.5 1318, 1285, 1319, 1359; 0.6 1325,
+//     1140, 1151, 1187
+//   32 layers, 128 rows, average: 0.4 672, 702, 695, 692; 0.45 683, 716, 696, 697; 0.5 680, 649, 661, 696; 0.6 677, 591, 596, 604
+// The spread is seen before the sample is multiplied, so that heads without a common direction cost little more than their references.
+// (A count of 256 sampled keys near the cut told the strengths apart worse, and later.)
+constexpr float kSiftSpread = 0.42f, kSiftSpreadAvg = 0.7f;
 // The guess of tau: the estimate that kSiftRank times the groups that the kept keys are thought to fill reach, times what the mean
 // ratio of weight to estimate is below the largest, times kSiftSlack (0.95 and 1: one head in a hundred fails the check).
 constexpr float kSiftSlack = 0.9f, kSiftRank = 1.2f;
 // Less by kSiftApart binades per unit of the ratios' relative deviation from kSiftApartFrom on, where the rows' weights lie apart, as
 // they do with key channels of unequal scales.  32 layers x 8 heads x 32k keys, 128 rows, average and max pooling, and 24 layers, 512
-// rows, max, us, without estimates, without this and with it: scales LogNormal(0, 0.6) 675, 941, 590; 675, 1042, 590; 1326, 2297, 1137;
-// LogNormal(0, 0.95) 697, 1205, 747; 699, 1203, 809; 1471, 2481, 1587; LogNormal(0, 1.1) 856, 1354, 1050; 857, 1349, 1147; 1564, 2547, 2120
-// (of the heads 2 %, 25 % and 60 % are handed on; 3 from 0.12 on: 594, 589, 1140; 779, 832, 1600; 8 from 0.15 on: 598, 597, 1137; 737, 775, 1628).
+// rows, max, us, without estimates, without this (and a failing head handing on its sequence) and with it: scales LogNormal(0, 0.6) 675,
+// 941, 583; 675, 1042, 588; 1323, 2297, 1117; LogNormal(0, 0.95) 697, 1205, 738; 699, 1203, 791; 1470, 2481, 1567; LogNormal(0, 1.1) 856, 1354,
+// 1008; 857, 1349, 1100; 1563, 2547, 2061 (of the heads 3 %, 25 % and 55 % are handed on: that the rows' weights lie apart so far is seen
+// only behind the pass.  3 from 0.12 on: 594, 589, 1140; 779, 832, 1600; 8 from 0.15 on: 598, 597, 1137; 737, 775, 1628).
 constexpr float kSiftApart = 5.f, kSiftApartFrom = 0.15f;
 constexpr int kSiftMaxPoolW = 17;
 
@@ -207,7 +208,7 @@ struct SiftArgs {
   float* omega;               // [units][Rs] estimated weights of the rows: 1 / (G z)
   unsigned long long* zsum;   // [units][Rs] their sums, as the other kernel's words hold them (bit 63: large ones in further words; 62: beyond those)
   unsigned long long* zlarge; // [units][3][Rs] the further words
-  int32_t* flags;             // [layer slot][B][Hkv] bit 0: objects; bit 1: not scored exactly; bit 2: too few take part
+  int32_t* flags;             // [layer slot][B][Hkv] 0: scored, or kept whole; else bits of kSiftLeft: left to the lagging kernel
   float* window;              // [units][Rs] sums of the rows over the window keys
   int32_t* done;              // [units] jobs done
   int32_t* total;             // [units] keys listed
@@ -224,52 +225,33 @@ struct SiftArgs {
   int32_t sample_shift;       // log2 of the sample's runs of eight keys
   int32_t min_share;          // keys of a prefix per key to keep, at least
   int32_t min_items;          // of a launch that are worth it
-  int32_t max_near;           // of the sampled keys near the cut
+  float min_spread;           // of the scores of some keys
   uint32_t alpha_magic, bh_magic, hkv_magic;  // as LagArgs
   int64_t q_sb, q_sh, q_st, kv_sb, kv_sh, kv_st;
   float kappa, inv_G;
 };
 hipError_t launch_score_sift(const SiftArgs& a, bool clear_err, hipStream_t s);
-// Whether the heads' flags of a (layer, sequence) have it sifted: a quarter of the heads at most object.
-__device__ __forceinline__ bool sift_takes(const int32_t* flags, int Hkv) {
-  int bad = 0;
+// How many heads of a (layer, sequence) have none of the bits set, and the k-th of them; how many have one, and the k-th of those.
+template <bool SET>
+__device__ __forceinline__ int sift_heads(const int32_t* flags, int Hkv, int32_t bits) {
+  int n = 0;
   for (int g0 = 0; g0 < Hkv; g0 += 8) {
     int f[8];
 #pragma unroll
     for (int g = 0; g < 8; ++g) f[g] = flags[g0 + g < Hkv ? g0 + g : 0];
 #pragma unroll
-    for (int g = 0; g < 8; ++g) bad += g0 + g < Hkv ? f[g] & 1 : 0;
+    for (int g = 0; g < 8; ++g) n += g0 + g < Hkv && ((f[g] & bits) != 0) == SET ? 1 : 0;
   }
-  return 4 * bad <= Hkv;
+  return n;
 }
-// And behind the sifting kernels: whether head g's scores are there; how many heads of the sequence are left to score, and the
-// k-th of those.
-constexpr int32_t kSiftLeft = 2 | 4;
-__device__ __forceinline__ bool sift_done(const int32_t* flags, int Hkv, int g) {
-  const int32_t own = flags[g];  // (under way together with the others)
-  return sift_takes(flags, Hkv) && (own & kSiftLeft) == 0;
-}
-__device__ __forceinline__ int sift_left(const int32_t* flags, int Hkv) {
-  int bad = 0, left = 0;
-  for (int g0 = 0; g0 < Hkv; g0 += 8) {
-    int f[8];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) f[g] = flags[g0 + g < Hkv ? g0 + g : 0];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      bad += g0 + g < Hkv ? f[g] & 1 : 0;
-      left += g0 + g < Hkv && (f[g] & kSiftLeft) != 0 ? 1 : 0;
-    }
-  }
-  return 4 * bad <= Hkv ? left : Hkv;
-}
-__device__ __forceinline__ int sift_left_at(const int32_t* flags, int Hkv, int left, int k) {
-  if (left == Hkv) return k;
+template <bool SET>
+__device__ __forceinline__ int sift_head(const int32_t* flags, int Hkv, int32_t bits, int k) {
   int g = 0;
   for (; g < Hkv; ++g)
-    if ((flags[g] & kSiftLeft) != 0 && k-- == 0) break;
+    if (((flags[g] & bits) != 0) == SET && k-- == 0) break;
   return g;
 }
+constexpr int32_t kSiftObjects = 1, kSiftFailed = 2, kSiftTooFew = 4, kSiftLeft = 7;
 
 // ---- scoring in two streaming launches for many query rows, over many layers (pkv_sweep.hip) ----
 constexpr int kSweepGrid = 256;     // workgroups, one per compute unit

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
       const int l = e / a.B;
       return a.flags + ((size_t)a.layer[l].slot * a.B + (e - l * a.B)) * a.Hkv;
     };
-    auto heads = [&](int e) { return a.flags ? sift_left(flags_of(e), a.Hkv) : a.Hkv; };
+    auto heads = [&](int e) { return a.flags ? sift_heads<true>(flags_of(e), a.Hkv, kSiftLeft) : a.Hkv; };
     auto length = [&](int b) {
       int n = a.N;
       if (a.seq_lens) {
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kT, 2) void score_lag_kernel(const LagArgs a) {
           g += rem * q;
           mine = k < q && g < left;
         }
-        if (mine && left < a.Hkv) g = sift_left_at(flags_of(lo), a.Hkv, left, g);
+        if (mine && left < a.Hkv) g = sift_head<true>(flags_of(lo), a.Hkv, kSiftLeft, g);
         it = make_uint2((uint32_t)(lo * a.Hkv + g), (uint32_t)(at_unit - k * parts) << 20 | (uint32_t)n);
       }
     }
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(256) void lag_prepare_kernel(const LagArgs a, int c
   u64* words = a.words + (size_t)blockIdx.x * 256;
   if ((tid & 31) < kRefs || (tid & 31) >= kMax) words[tid] = 0;
   if (a.words4 && tid < 64) a.words4[(size_t)blockIdx.x * 64 + tid] = 0;
-  if (a.flags && h == 0 && tid == 0) a.flags[(size_t)a.layer[l].slot * BH + bg] = 1;  // (not sifted)
+  if (a.flags && h == 0 && tid == 0) a.flags[(size_t)a.layer[l].slot * BH + bg] = kSiftObjects;  // (not sifted)
   int n = a.N;
   if (a.seq_lens) {
     n = a.seq_lens[b];

@@ -817,7 +817,7 @@ __global__ __launch_bounds__(kStretchThreads, 4) void select_stretch_kernel(cons
     n = n < 0 ? 0 : (n > a.N ? a.N : n);
   }
   if (ly.k_l >= n) return;
-  if (a.flags && sift_done(a.flags + (size_t)l * BH + (size_t)(bg / a.Hkv) * a.Hkv, a.Hkv, bg % a.Hkv)) return;  // (the kept set is there)
+  if (a.flags && a.flags[(size_t)l * BH + bg] == 0) return;  // (the kept set is there)
   const int npre = n - a.alpha, kk = ly.k_l - a.alpha;
   const Stretches st = stretches(npre, kk, a.listed != 0, ly.write_pooled != 0);
   if ((int)blockIdx.x >= st.count) return;
@@ -1146,7 +1146,7 @@ __global__ __launch_bounds__(NT, PMAX <= 16 ? 8 : 4) void pool_select_batch_kern
     if (fuse_gather) gather_unit(ga, gl, b, g, [&](int j) { return j < n ? j : -1; });
     return;
   }
-  if (a.flags && sift_done(a.flags + (size_t)l * BH + (size_t)b * a.Hkv, a.Hkv, g)) {  // the kept set is there
+  if (a.flags && a.flags[(size_t)l * BH + bg] == 0) {  // the kept set is there
     if (fuse_gather) gather_unit(ga, gl, b, g, [&](int j) { return idx[j]; });
     return;
   }
@@ -1261,7 +1261,7 @@ __global__ __launch_bounds__(256) void recall_kernel(const RecallArgs a) {
   float all = 0.f, kept = 0.f;
   if (ly.k_l < n) {
     const int npre = n - a.alpha, kk = ly.k_l - a.alpha;
-    const bool sifted = a.flags && sift_done(a.flags + (size_t)blockIdx.y * BH + (size_t)b * a.Hkv, a.Hkv, bg - b * a.Hkv);
+    const bool sifted = a.flags && a.flags[(size_t)blockIdx.y * BH + bg] == 0;
     for (int p = 0; p < a.nrb; ++p) {
       const float* row = a.raw + (((size_t)blockIdx.y * a.nrb + p) * BH + bg) * a.N;
       if (sifted) all = threadIdx.x == 0 ? row[npre] : 0.f;

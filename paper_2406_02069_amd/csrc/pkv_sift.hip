@@ -10,9 +10,9 @@
 // are, all below, and the selection finds the kept set among all of them.  tau is a guess (from the largest estimates, less what
 // the weights differ); whether it was low enough is checked, never assumed.
 //
-// Handed on to the lagging one-pass kernel, which scores all keys: sequences with heads whose estimates are no use (seen in the
-// sample beforehand: the cut lies where keys are many, as with queries that have no common direction), the whole launch where few
-// are left then, and single heads whose sums fit no word, whose list does not fit an eighth of the keys, or that fail the check.  Sums and scores come about exactly as in that kernel (same
+// Handed on to the lagging one-pass kernel, which scores all keys: heads whose estimates are no use (seen beforehand: scores spread
+// little where queries have no common direction), all of a launch where these are many, heads whose sums fit no word, whose list
+// does not fit an eighth of the keys, or that fail the check.  Sums and scores come about exactly as in that kernel (same
 // references, same order of additions), so that the kept sets are the same to the bit whoever scores.
 //
 // Four launches: sift_prepare_kernel (references, weights o_r from 512 or 1024 keys: the median of eight groups' sums, so that a rare
@@ -26,10 +26,11 @@
 // of items of equal length; no workgroup waits for another.
 //
 // What bounds it: vector instructions and HBM, and the clock the chip holds under this load, at 128 rows (32 layers x 8 heads x 32k
-// keys 412 us, 5.2 TB/s, at 2.1 GHz; the lagging kernel 620), power at 512 rows (80 layers 3.25 ms at 1.8 GHz; 4.3: two key tiles per
+// keys 432 us, 5.0 TB/s, in the median of 60 launches behind one another, 425 at the least; 470 .. 480 in shorter series; the lagging
+// kernel 622 .. 655), power at 512 rows (80 layers 3.2 ms at 1.8 GHz; 4.3: two key tiles per
 // query fragment, sixteen waves, or products and exponentials of two waves in turn by barriers change the clock, 1.80 .. 1.94 GHz, and
 // the time to 3.2 .. 3.5).  A launch begins with 12 us until the first product.  The kernels around it are chains of latencies:
-// 31, 26 and 38 us for 256 heads of 32k keys (the selection kernel, which takes 27 otherwise, is left with 10).
+// 27, 25 and 33 us for 256 heads of 32k keys (the selection kernel, which takes 27 otherwise, is left with 11).
 #include <type_traits>
 
 #include "pkv_internal.h"
@@ -135,9 +136,9 @@ __device__ __forceinline__ float2 wave_sums(float v) {
 }
 
 // ---- estimates of the normalisers of 128 rows of a unit; with its first rows, whether it is worth it ----
-// Where it is not, most is seen from 64 keys, and the sample's multiplications are left out: 32 layers x 8 heads x 32k keys, 128 rows
-// without a common direction, which the one-pass kernel takes in 662 us, 692 -> 679 us; 24 layers, 512 rows, 1466 -> 1370 of 1330 (this
-// kernel's work there costs the next one 70 us more than its own 35); 80 layers 4600 -> 4546 of 4493.
+// Where it is not, that is seen from the 64 keys of the references, and the sample's multiplications are left out (31 -> 14 us): 32
+// layers x 8 heads x 32k keys, 128 rows without a common direction, which the one-pass kernel takes in 662 us, 692 -> 677 us; 24 layers,
+// 512 rows, 1466 -> 1347 of 1332; 80 layers 4565 -> 4541 of 4503.
 // What bounds it: latencies, and the address units, which take a fragment's 32 rows one by one.  So queries and the keys that
 // several waves multiply come through LDS (256 units of 128 rows 31 -> 26 us, 640 of 512 rows 154 -> 98, against 64 rows per
 // workgroup and every key as fragments from memory).
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   constexpr int KS = D / 16;
   using QB = RowBlock<D, kBlockRows>;
   __shared__ u32x4 s_q[QB::SLOTS], s_k[QB::SLOTS];  // queries; 64 keys for the references and 64 of the window
-  __shared__ float s_m[kBlockRows], s_x0[kBlockRows], s_o[kBlockRows], s_part[kW][kBlockRows], s_win[2][kBlockRows], s_score[32 * kW];
+  __shared__ float s_m[kBlockRows], s_x0[kBlockRows], s_part[kW][kBlockRows], s_win[2][kBlockRows], s_score[64 * kBlockTiles];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blocks = (a.Rs + kBlockRows - 1) / kBlockRows, u = blockIdx.x / blocks, row0 = kBlockRows * (blockIdx.x - u * blocks);
@@ -235,13 +236,14 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     const float2 sum = wave_sums(y);
     const float off = lane == 0 ? 0.f : y - (lane < 32 ? sum.x * (1.f / 31.f) : (sum.y - sum.x) * (1.f / 32.f));
     // (a block that is not the unit's first does not decide; that it leaves is rarer, and void weights have the head handed on)
-    const float least = row0 == 0 ? kSiftSpread : 0.75f * kSiftSpread;
+    const float least = row0 == 0 ? a.min_spread : 0.75f * a.min_spread;
     const bool skip = (a.scored[p.l >> 5] >> (p.l & 31) & 1) != 0 || npre < kSiftMinKeys || (int64_t)kk * a.min_share > npre;
     if (skip || !(wave_sums(off * off).y >= 61.f * least * least)) {  // (the same in all waves)
       if (tid < rows) a.omega[(size_t)u * a.Rs + row0 + tid] = 0.f;
-      if (row0 == 0 && tid == 0) *flag = 1;
+      if (row0 == 0 && tid == 0) *flag = kSiftObjects;
       return;
     }
+    if (row0 == 0 && tid == 0) *flag = 0;
   }
   float z[kBlockTiles] = {};
 #pragma unroll 1
@@ -290,48 +292,10 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     const float sum = __builtin_fmaf(mid, (float)(npre - 1) / (float)(64 * a.sample_tiles), fast_exp2(s_x0[tid] - m)) + window;
     a.window[(size_t)u * a.Rs + row0 + tid] = window;
     const float o = row0 + tid < a.R ? a.inv_G / sum : 0.f;
-    s_o[tid] = o;
     a.omega[(size_t)u * a.Rs + row0 + tid] = o;
     a.zsum[(size_t)u * a.Rs + row0 + tid] = 0;
 #pragma unroll
     for (int i = 0; i < 3; ++i) a.zlarge[((size_t)u * 3 + i) * a.Rs + row0 + tid] = 0;
-  }
-  if (row0 != 0) return;
-  lds_barrier();
-  // estimated scores (of these rows) of a part of the sample without key 0: a sink's is far above the others, is kept in any case, and
-  // as the cut said that few keys lie near it (80 layers x 32k keys, 512 rows without a common direction, a sink: tried in vain, 4.5 ms
-  // became 8.4; now 4.8)
-  f32x16 t = {};
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const float nm = -s_m[32 * q + l32], o = s_o[32 * q + l32];
-    const f32x16 x = product(kf[1], s_q, 32 * q + l32, hf);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) t[v] = __builtin_fmaf(o, fast_exp2(__builtin_fmaf(x[v], a.kappa, nm)), t[v]);
-  }
-  s_score[32 * wave + transpose_key(lane)] = transpose_sum(t, lane);
-  lds_barrier();
-  if (wave == 0) {
-    // the cut's place in it, and how many of its keys lie near the cut or above
-    uint32_t v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = __float_as_uint(s_score[64 * j + lane]);
-    const int at = (int)((int64_t)32 * kW * kk / npre);
-    uint32_t cut = 0x7FFFFFFFu;
-    for (int above = 0; above <= at;) {  // the next smaller score, until enough have been passed (each round passes one at least)
-      uint32_t m = 0u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) m = max(m, v[j] < cut ? v[j] : 0u);
-      m = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_lane63(m), 63);
-      if (m == 0u) break;
-      cut = m;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) above += __popcll(__ballot(v[j] == cut));
-    }
-    int near = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) near += __popcll(__ballot(__uint_as_float(v[j]) >= __uint_as_float(cut) * kSiftNear));
-    if (lane == 0) *flag = near > at + a.max_near ? 1 : 0;
   }
 }
 
@@ -350,7 +314,7 @@ __device__ __forceinline__ bool open_unit(const SiftArgs& a, Pass& p, bool known
   const Unit x = unit_of(a, p.u);
   p.n = x.n;
   p.K = keys_of(a, x);
-  return known || (a.layer[x.l].k_l < x.n && sift_takes(flags_of(a, x.l, x.b), a.Hkv));
+  return known || (a.layer[x.l].k_l < x.n && (flags_of(a, x.l, x.b)[x.g] & kSiftObjects) == 0);
 }
 // The pass after p, of KEYS keys; false if there is none (p is then a pass over the unit's first key alone).
 template <int KEYS>
@@ -370,51 +334,55 @@ __device__ __forceinline__ bool advance(const SiftArgs& a, Pass& p) {
   }
   return true;
 }
-// The workgroup's first pass; false if it has none.  wsum: kW + 2 words of LDS, read before the next barrier.
+// The workgroup's first pass; false if it has none.  wsum: 2 kW + 2 words of LDS, read before the next barrier.
 __device__ __forceinline__ bool first_pass(const SiftArgs& a, Pass& p, int* wsum) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // wsum: [kW] sums of the waves, [kW], [kW + 1] the first item's place
+  // wsum: [kW] sums of the waves, [kW], [kW + 1] the first item's place; [kW] sums of the waves over all that is to be scored
+  int* const wall = wsum + kW + 2;
   const int E = a.L * a.B;
   int lo = 0, hi = 0, u0 = 0, c0 = 0;
   int c = 0, parts = 0, before = 0;
   for (int round = 0; round < 2; ++round) {  // how many items there are; then who owns the first one
-    int run = 0;
+    int run = 0, all = 0;
     for (int e0 = 0; e0 < E; e0 += kT) {
       const int e = e0 + tid;
       if (round == 0 || E > kT) {  // (else the first round's are still there)
         c = parts = 0;
         if (e < E) {
           const int l = e / a.B, b = e - l * a.B, n = valid_length(a, b);
-          parts = a.layer[l].k_l < n && sift_takes(flags_of(a, l, b), a.Hkv) ? (n + kLagKeys - 1) / kLagKeys : 0;
-          c = a.Hkv * parts;
+          parts = a.layer[l].k_l < n ? (n + kLagKeys - 1) / kLagKeys : 0;
+          c = sift_heads<false>(flags_of(a, l, b), a.Hkv, kSiftObjects) * parts;
         }
-        int v = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int x = __shfl_up(v, o);
-          if (lane >= o) v += x;
-        }
+        const int v = (int)wave_inclusive_sum((uint32_t)c), y = (int)wave_inclusive_sum((uint32_t)(a.Hkv * parts));
         lds_barrier();
-        if (lane == 63) wsum[wave] = v;
+        if (lane == 63) {
+          wsum[wave] = v;
+          wall[wave] = y;
+        }
         lds_barrier();
         before = run + v - c;
 #pragma unroll
         for (int w = 0; w < kW; ++w) {
           before += w < wave ? wsum[w] : 0;
           run += wsum[w];
+          all += wall[w];
         }
       }
       if (round == 1 && lo >= before && lo < before + c) {
-        const int rem = lo - before, g = rem / parts;
-        wsum[kW] = e * a.Hkv + g;
-        wsum[kW + 1] = rem - g * parts;
+        const int rem = lo - before, k = rem / parts, l = e / a.B;
+        wsum[kW] = e * a.Hkv + sift_head<false>(flags_of(a, l, e - l * a.B), a.Hkv, kSiftObjects, k);
+        wsum[kW + 1] = rem - k * parts;
       }
     }
     if (round == 0) {
-      if (run < a.min_items) {  // (the same in all workgroups): the launches behind this one cost more than is gained
+      // Where little takes part (the same in all workgroups) the launches behind this one cost more than is gained, and heads that
+      // barely take part gain little.  1 .. 5 heads of 8 without a common direction, 32 layers x 32k keys, 128 rows, max pooling, us: without
+      // estimates 678, with them whatever takes part 567, 591, 613, 653, 663, handed on altogether 690; 24 layers, 512 rows 1316: 1085, 1159,
+      // 1219, 1281, 1382 and 1345.  Average pooling, a common direction of 0.45 (half of the heads take part): 675: 724, 697; 1320: 1531, 1404.
+      if (run < a.min_items || 2 * run < all) {
         for (int u = (int)blockIdx.x * kT + tid; u < a.L * a.B * a.Hkv; u += (int)gridDim.x * kT) {
           const Unit x = unit_of(a, u);
-          a.flags[(size_t)a.layer[x.l].slot * a.B * a.Hkv + (size_t)x.b * a.Hkv + x.g] |= 4;  // (others may read it now, but bit 0 only)
+          a.flags[(size_t)a.layer[x.l].slot * a.B * a.Hkv + (size_t)x.b * a.Hkv + x.g] |= kSiftTooFew;  // (others may read it now, but another bit)
         }
         return false;
       }
@@ -458,8 +426,8 @@ __device__ __forceinline__ void add_sum(const SiftArgs& a, int u, int row, u64 s
 // 65 to 128 rows: they lie in the registers of every wave as matrix operands (but for the last row tile's, for which there are none
 // left), and K comes through LDS.  A wave requests its tile two passes ahead, whole rows at a time and past the registers, and reads
 // each fragment once, behind the last product that needs its predecessor.  Against queries in LDS and keys requested as operands a
-// pass reads 16 KB of LDS per wave instead of 32 and has 390 vector instructions instead of 508: 32 layers x 8 heads x 32k keys 450 ->
-// 412 us, x 128k 1853 -> 1700.
+// pass reads 16 KB of LDS per wave instead of 32 and has a fifth fewer vector instructions (407 are counted for 32 keys x 128 rows): both
+// in one series, 32 layers x 8 heads x 32k keys 450 -> 412 us, x 128k 1853 -> 1700.
 template <int D>
 struct FewRows {
   static constexpr int ROWS = 128, TILES = ROWS / 32;
@@ -932,7 +900,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = blockIdx.x;
   const Unit p = unit_of(a, u);
-  if (a.layer[p.l].k_l >= p.n || !sift_done(flags_of(a, p.l, p.b), a.Hkv, p.g)) return;  // (bit 1 comes from here, and from behind here)
+  if (a.layer[p.l].k_l >= p.n || flags_of(a, p.l, p.b)[p.g] != 0) return;
   const int npre = p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
   const size_t place = (size_t)a.layer[p.l].slot * a.B * a.Hkv + (size_t)p.b * a.Hkv + p.g;
   float* raw = a.raw + place * a.N;
@@ -944,7 +912,7 @@ __global__ __launch_bounds__(NT, 8) void sift_list_kernel(const SiftArgs a) {
   const float inv_w = 1.f / (float)a.pool_w;
   // no list: the kernel behind the next one scores the head
   auto fail = [&]() {
-    if (tid == 0) a.flags[place] |= 2;
+    if (tid == 0) a.flags[place] = kSiftFailed;
   };
 
   // rows: the largest and the mean ratio of the weight to its estimate
@@ -1370,7 +1338,7 @@ __global__ __launch_bounds__(kT, 4) void sift_exact_kernel(const SiftArgs a, int
 #pragma unroll
     for (int w = 0; w < kW; ++w) bad |= s_scan[kW + w];
     if (bad != 0u) {
-      if (tid == 0) a.flags[place] |= 2;
+      if (tid == 0) a.flags[place] = kSiftFailed;
       return;  // (no part of the unit is left)
     }
     // ---- the kk-th largest of them: bins of equal width between the smallest and the largest, as long as more than 64 are in its bin ----
