@@ -146,8 +146,8 @@ template <int D>
 __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, int clear_err) {
   constexpr int KS = D / 16;
   using QB = RowBlock<D, kBlockRows>;
-  __shared__ u32x4 s_q[QB::SLOTS], s_k[QB::SLOTS];  // queries; 64 keys for the references and 64 of the window
-  __shared__ float s_m[kBlockRows], s_x0[kBlockRows], s_part[kW][kBlockRows], s_win[2][kBlockRows], s_score[64 * kBlockTiles];
+  __shared__ u32x4 s_q[QB::SLOTS], s_k[QB::SLOTS];  // queries; 64 keys for the references and 64 of the window, then the first 64
+  __shared__ float s_m[kBlockRows], s_part[kW][kBlockRows], s_win[2][kBlockRows], s_first[2][kBlockRows], s_score[64 * kBlockTiles];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blocks = (a.Rs + kBlockRows - 1) / kBlockRows, u = blockIdx.x / blocks, row0 = kBlockRows * (blockIdx.x - u * blocks);
@@ -160,6 +160,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   const uint16_t* K = keys_of(a, p);
   bf16x8 kf[2][KS];
   QB qb, kb;
+  RowBlock<D, 64> fb;
   // The sample: wave w's group of keys is spread evenly over the prefix in runs of eight neighbours, four to a tile.
   auto sample = [&](int tile, bf16x8 (&f)[KS]) {
     const uint32_t run = (uint32_t)((4 * tile + (l32 >> 3)) * kW + wave);
@@ -169,6 +170,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     // references: the largest logit of 64 keys, eight neighbours each at eight places, key 0 among them
     kb.request(0, [&](int i) { return K + (size_t)(i < 64 ? min((int)((uint32_t)npre * (uint32_t)(i >> 3) >> 3) + (i & 7), npre - 1) : min(npre + i - 64, p.n - 1)) * a.kv_st; });
     qb.request(row0, [&](int row) { return query_row_of(a, Q, row); });
+    fb.request(0, [&](int i) { return K + (size_t)min(i, npre - 1) * a.kv_st; });
     sample(0, kf[0]);
     sample(1, kf[1]);
   }
@@ -194,13 +196,11 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
 #pragma unroll
     for (int v = 1; v < 16; ++v) m = fmaxf(m, x[v]);
     m = both_halves<true>(m) * a.kappa;
-    if (hf == 0) {
-      s_part[half][32 * rt + l32] = m;
-      if (half == 0) s_x0[32 * rt + l32] = x[0] * a.kappa;
-    }
+    if (hf == 0) s_part[half][32 * rt + l32] = m;
     xw = product_of<KS>(s_k, 64 + 32 * half + l32, s_q, 32 * rt + l32, hf);
   }
   lds_barrier();
+  fb.commit(s_k);
   if (tid < rows) {
     const float m = fmaxf(s_part[0][tid], s_part[1][tid]);
     s_m[tid] = m;
@@ -215,13 +215,13 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     for (int v = 0; v < 16; ++v) y += mrow0(v) > lim ? 0.f : fast_exp2(__builtin_fmaf(xw[v], a.kappa, nm));
     y = both_halves<false>(y);
     if (hf == 0) s_win[half][32 * rt + l32] = y;
-    // Hopeless ones are seen from the references' keys, before the sample is looked at: the scores of 31 or 32 of them, key 0 not
-    // counted, with weights from themselves, spread little.
+    // Hopeless ones are seen from the references' keys, before the sample is looked at: the scores of 24 or 32 of them, with weights
+    // from themselves, spread little.  (The first eight, where sinks lie, do not count.)
     y = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       x[v] = fast_exp2(__builtin_fmaf(x[v], a.kappa, nm));
-      y += v == 0 && half == 0 && hf == 0 ? 0.f : x[v];
+      y += v < 4 && half == 0 ? 0.f : x[v];
     }
     const float o = row0 + 32 * rt + l32 < a.R ? __builtin_amdgcn_rcpf(both_halves<false>(y)) : 0.f;
 #pragma unroll
@@ -232,18 +232,32 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   {
     float e = 0.f;
     for (int i = 0; i < ntile; ++i) e += s_score[64 * i + lane];
-    const float y = lane == 0 ? 0.f : fast_log2(fmaxf(e, 0x1p-100f));
+    const float y = lane < 8 ? 0.f : fast_log2(fmaxf(e, 0x1p-100f));
     const float2 sum = wave_sums(y);
-    const float off = lane == 0 ? 0.f : y - (lane < 32 ? sum.x * (1.f / 31.f) : (sum.y - sum.x) * (1.f / 32.f));
+    const float off = lane < 8 ? 0.f : y - (lane < 32 ? sum.x * (1.f / 24.f) : (sum.y - sum.x) * (1.f / 32.f));
     // (a block that is not the unit's first does not decide; that it leaves is rarer, and void weights have the head handed on)
     const float least = row0 == 0 ? a.min_spread : 0.75f * a.min_spread;
     const bool skip = (a.scored[p.l >> 5] >> (p.l & 31) & 1) != 0 || npre < kSiftMinKeys || (int64_t)kk * a.min_share > npre;
-    if (skip || !(wave_sums(off * off).y >= 61.f * least * least)) {  // (the same in all waves)
+    if (skip || !(wave_sums(off * off).y >= 54.f * least * least)) {  // (the same in all waves)
       if (tid < rows) a.omega[(size_t)u * a.Rs + row0 + tid] = 0.f;
       if (row0 == 0 && tid == 0) *flag = kSiftObjects;
       return;
     }
     if (row0 == 0 && tid == 0) *flag = 0;
+  }
+  if (rt < ntile) {
+    // the first 64 keys, which count themselves: sinks lie there, and the sample would miss them (one at key 20 that all rows see, 32
+    // layers x 8 heads x 32k keys, 128 rows: every head's weights lay apart, and the call took 1190 us instead of 690)
+    const float nm = -s_m[32 * rt + l32];
+    float y0 = 0.f, y1 = 0.f;
+    x = product_of<KS>(s_k, 32 * half + l32, s_q, 32 * rt + l32, hf);
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      y0 += fast_exp2(__builtin_fmaf(x[v], a.kappa, nm));
+      y1 += fast_exp2(__builtin_fmaf(x[v + 1], a.kappa, nm));
+    }
+    y0 = both_halves<false>(y0 + y1);
+    if (hf == 0) s_first[half][32 * rt + l32] = y0;
   }
   float z[kBlockTiles] = {};
 #pragma unroll 1
@@ -287,9 +301,8 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
       for (int x = 0; x < kW; ++x) rank += (v[x] < v[w] || (v[x] == v[w] && x < w)) ? 1 : 0;
       if (rank == kW / 2 - 1 || rank == kW / 2) mid += v[w];
     }
-    const float m = s_m[tid];
     const float window = s_win[0][tid] + s_win[1][tid];
-    const float sum = __builtin_fmaf(mid, (float)(npre - 1) / (float)(64 * a.sample_tiles), fast_exp2(s_x0[tid] - m)) + window;
+    const float sum = __builtin_fmaf(mid, (float)(npre - 64) / (float)(64 * a.sample_tiles), s_first[0][tid] + s_first[1][tid]) + window;
     a.window[(size_t)u * a.Rs + row0 + tid] = window;
     const float o = row0 + tid < a.R ? a.inv_G / sum : 0.f;
     a.omega[(size_t)u * a.Rs + row0 + tid] = o;

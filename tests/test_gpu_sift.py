@@ -444,3 +444,24 @@ def test_heads_object_one_by_one(flat, taken):
     full, _ = _run(Qs, Ks, Vs, [k] * L, MAX, 7, scores=True)
     for l in range(L):
         _same(call.outputs[l], full.outputs[l])
+
+
+@pytest.mark.parametrize("at", [3, 20, 63])
+@pytest.mark.parametrize("d,G,alpha,pool,pw", [(128, 4, 32, AVG, 5), (64, 6, 32, MAX, 7)])
+def test_second_sink(at, d, G, alpha, pool, pw):
+    """A key among the first 64 that all queries see far above the others: it counts in the weights, and heads pass their check; queries
+    without a common direction are seen to have none all the same."""
+    N, k = 32768, alpha + 60
+    print("sift second sink", at, d, G, pool, flush=True)
+    data = [list(_inputs(1, G, 8, d, N, alpha, seed=170 + l)) for l in range(2)]
+    data[1][0] = torch.randn_like(data[1][0].float()).to(torch.bfloat16)
+    for l, (Q, K, V) in enumerate(data):
+        q = Q[0].float().view(8, G * alpha, d)
+        K[0, :, at] = ((2.0 if l == 0 else 0.5 * G * alpha) * q.mean(1)).to(torch.bfloat16)
+    Qs, Ks, Vs = ([x[i] for x in data] for i in range(3))
+    call, flags = _run(Qs, Ks, Vs, [k] * 2, pool, pw)
+    print(flags[:, 0].tolist(), flush=True)
+    assert (flags[0] & 3 == 0).all() and (flags[1] & 1 != 0).all()
+    full, _ = _run(Qs, Ks, Vs, [k] * 2, pool, pw, scores=True)
+    for l in range(2):
+        _same(call.outputs[l], full.outputs[l])
