@@ -15,8 +15,8 @@
 // does not fit an eighth of the keys, or that fail the check.  Sums and scores come about exactly as in that kernel (same
 // references, same order of additions), so that the kept sets are the same to the bit whoever scores.
 //
-// Four launches: sift_prepare_kernel (references, weights o_r from 512 or 1024 keys: the median of eight groups' sums, so that a rare
-// large key does not spoil them), score_sift_few_kernel or score_sift_many_kernel (the pass over K), sift_list_kernel (a workgroup per head: tau and the list),
+// Four launches: sift_prepare_kernel (references, weights o_r from the first 64 keys and 512 or 1024 others: the median of eight groups'
+// sums, so that a rare large key does not spoil them), score_sift_few_kernel or score_sift_many_kernel (the pass over K), sift_list_kernel (a workgroup per head: tau and the list),
 // sift_exact_kernel (256 listed keys at a time; the last workgroup of a head makes the check and selects the kept set among the few
 // places that reach the bound, so that the selection kernel only copies their rows).
 //
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   }
   if (rt < ntile) {
     // the first 64 keys, which count themselves: sinks lie there, and the sample would miss them (one at key 20 that all rows see, 32
-    // layers x 8 heads x 32k keys, 128 rows: every head's weights lay apart, and the call took 1190 us instead of 690)
+    // layers x 8 heads x 32k keys, 128 rows: the weights of every head lay apart, and the call took 1245 us, now 542; this takes 2)
     const float nm = -s_m[32 * rt + l32];
     float y0 = 0.f, y1 = 0.f;
     x = product_of<KS>(s_k, 32 * half + l32, s_q, 32 * rt + l32, hf);
