@@ -356,16 +356,26 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
 constexpr int kSiftMinRows = 65;     // (64 rows: K's read binds either way)
 constexpr int kSiftMinLen = 16384;
 constexpr int64_t kSiftMinTotal = 4 << 20, kSiftMinTotalMany = 3 << 20;  // keys of a call; with more than 128 rows
+// Layers that keep many of their keys are left to the lagging kernel (their lists would not fit an eighth of the keys: they hold about 4
+//   keys per key to keep, with average pooling 2.5 + w), and where what is left of a call is less than the line, with more than 128 rows
+//   than half of it, so is the call: 20 layers x 31k keys, 128 rows, 6 layers left, 614 us, tried in vain 638; 7 sequences x 8 layers x 22k, 3
+//   layers left 804, sifted 838; 36 layers x 43k, 256 rows, 15 layers left 1900, sifted 1711; 2 x 8 x 42k, 140 rows, 3.5 left 620, 590.
+static int sift_min_share(const pkv_layer_desc& d) { return d.pool == PKV_POOL_AVG && d.pool_w > 1 ? 27 + 11 * d.pool_w : 43; }
+static bool sift_layer(const pkv_layer_desc& d) {
+  return d.k_l < d.N && (int64_t)(d.k_l - d.alpha) * sift_min_share(d) <= d.N - d.alpha;
+}
 struct SiftPlan {
   int Rs;
   LagPlan rest;  // of the sequences that are handed on: any of them, so they are dealt as with sequence lengths
   // the other kernel's words; sums in four words, estimates, sums over the window; list and three words about it
   size_t unit_bytes(int N) const { return rest.unit_bytes() + (size_t)Rs * 40 + sift_list(N) * 4 + 12; }
 };
-static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged, int scoring_layers) {
+// scoring, fit: layers that are not kept whole; those of them that may be sifted
+static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode, bool ragged, int scoring, int fit) {
   const SiftPlan none = {0, {0, 0, 0, false}};
   if (d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return none;
-  if ((int64_t)scoring_layers * plan.BH * d.N < (plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal)) return none;
+  const int64_t line = plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal;
+  if ((int64_t)scoring * plan.BH * d.N < line || (int64_t)fit * plan.BH * d.N < (plan.R > 128 ? line / 2 : line)) return none;
   // (Dealing takes whole rounds for units of 128 items and more, so that a layer of many of them can be too much for a launch
   // although it is not when all units are taken in order: 448 heads of 65 536 keys.)
   const SiftPlan p = {(plan.R + 63) / 64 * 64, lag_plan(plan, d, lse_mode, ragged, true)};
@@ -439,14 +449,16 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
     unsigned long long* const words = reinterpret_cast<unsigned long long*>(pooled_ws);
     const size_t unit_words = (size_t)gp.groups * (kLagGroupBytes / 8), unit_words4 = (size_t)gp.groups * (kLagGroupBytes4 / 8);
     const uint32_t alpha_magic = (65536u + (uint32_t)d.alpha - 1) / (uint32_t)d.alpha;
-    int32_t scoring = 0, unscored = 0;  // layers that take part; those of them without scores_out
+    int32_t scoring = 0, fit = 0, unscored = 0;  // layers that take part; that may be sifted; those of them without scores_out
     for (int32_t l = 0; l < L; ++l) {
       if (descs[l].k_l >= d.N) continue;
       ++scoring;
-      unscored += ptrs[l].scores_out ? 0 : 1;
+      fit += sift_layer(descs[l]) ? 1 : 0;
+      unscored += sift_layer(descs[l]) && !ptrs[l].scores_out ? 1 : 0;
     }
-    const SiftPlan may = sift_plan(plan, d, lse_mode, seq_lens != nullptr, scoring);
-    const bool sift = may.Rs > 0 && unscored > 0;
+    // (whether there are flags in the workspace has to be seen without scores_out, too: for the recall)
+    const SiftPlan may = sift_plan(plan, d, lse_mode, seq_lens != nullptr, scoring, fit);
+    const bool sift = may.Rs > 0 && sift_plan(plan, d, lse_mode, seq_lens != nullptr, scoring, unscored).Rs > 0;
     unsigned long long* const words4 = words + scoring * plan.BH * unit_words;
     int32_t* const flags = reinterpret_cast<int32_t*>(ws + plan.off_cnt) + 2;
     if (sift) {
@@ -496,9 +508,8 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         fa.zbufs = sift_zbufs(may.Rs);
         fa.sample_tiles = fa.pool == PKV_POOL_AVG ? 4 : 2;  // (its lists are longer)
         fa.sample_shift = fa.sample_tiles == 4 ? 7 : 6;
-        // (so that the list fits an eighth of the keys: it holds about 4 keys per key to keep, with average pooling 2.5 + w)
-        fa.min_share = fa.pool == PKV_POOL_AVG ? 27 + 11 * d.pool_w : 43;
-        fa.min_items = (int32_t)((plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal) / 4 * 3 / kLagKeys);
+        fa.min_share = sift_min_share(d);
+        fa.min_items = (int32_t)((plan.R > 128 ? kSiftMinTotalMany / 2 : kSiftMinTotal / 4 * 3) / kLagKeys);
         fa.min_spread = fa.pool == PKV_POOL_AVG ? kSiftSpreadAvg : kSiftSpread;
         fa.alpha_magic = alpha_magic;
         fa.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;
@@ -1097,9 +1108,12 @@ int pkv_attention_recall(int32_t L, const pkv_layer_desc* descs, int32_t lse_sup
   const bool resident = use_resident(plan, lse_supplied != 0, d.flags);
   const int nrb = resident ? 1 : plan.nrb;
   const float* raw = reinterpret_cast<const float*>(static_cast<const char*>(workspace) + plan.off_raw);
-  int32_t scoring = 0;
-  for (int32_t l = 0; l < L; ++l) scoring += descs[l].k_l < d.N ? 1 : 0;
-  const bool sifted = resident && sift_plan(plan, d, lse_supplied != 0, seq_lens != nullptr, scoring).Rs > 0;
+  int32_t scoring = 0, fit = 0;
+  for (int32_t l = 0; l < L; ++l) {
+    scoring += descs[l].k_l < d.N ? 1 : 0;
+    fit += sift_layer(descs[l]) ? 1 : 0;
+  }
+  const bool sifted = resident && sift_plan(plan, d, lse_supplied != 0, seq_lens != nullptr, scoring, fit).Rs > 0;
   const int32_t* flags = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + plan.off_cnt) + 2;
   for (int32_t l0 = 0; l0 < L; l0 += kBatchMaxLayers) {
     const int32_t nl = L - l0 < kBatchMaxLayers ? L - l0 : kBatchMaxLayers;
@@ -1152,7 +1166,7 @@ int pkv_scoring_route(const pkv_layer_desc* desc, int32_t L, int32_t variant, in
   const LagPlan gp = lag_plan(plan, *desc, lse_mode, ragged);
   if (gp.layers > 0) {
     // (the words of all layers lie there at once, whatever the launches; with the sifting kernels' sums, weights and lists behind them)
-    const SiftPlan fp = sift_plan(plan, *desc, lse_mode, ragged, desc->k_l < desc->N ? L : 0);
+    const SiftPlan fp = sift_plan(plan, *desc, lse_mode, ragged, L, sift_layer(*desc) ? L : 0);
     const bool sift = (variant & PKV_ROUTE_KEPT) != 0 && fp.Rs > 0;
     *kernel_id = sift ? PKV_KERNEL_SCORE_SIFT : PKV_KERNEL_SCORE_LAG;
     *scratch_bytes = (size_t)L * plan.BH * (sift ? fp.unit_bytes(desc->N) : gp.unit_bytes());

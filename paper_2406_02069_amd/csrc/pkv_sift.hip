@@ -59,6 +59,11 @@ __device__ __forceinline__ Unit unit_of(const SiftArgs& a, int u) {
   const int BH = a.B * a.Hkv, l = (int)((u64)(uint32_t)(u + 1) * a.bh_magic >> 32), bg = u - l * BH, b = (int)((u64)(uint32_t)(bg + 1) * a.hkv_magic >> 32);
   return {l, b, bg - b * a.Hkv, valid_length(a, b)};
 }
+// Whether the heads of a (layer, sequence) of length n are asked at all: not where scores are wanted or many of the keys are kept.
+__device__ __forceinline__ bool asked(const SiftArgs& a, int l, int n) {
+  const int npre = n - a.alpha, kk = a.layer[l].k_l - a.alpha;
+  return (a.scored[l >> 5] >> (l & 31) & 1) == 0 && npre >= kSiftMinKeys && (int64_t)kk * a.min_share <= npre;
+}
 __device__ __forceinline__ const int32_t* flags_of(const SiftArgs& a, int l, int b) {
   return a.flags + (size_t)a.layer[l].slot * a.B * a.Hkv + (size_t)b * a.Hkv;
 }
@@ -155,7 +160,8 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
   if (blockIdx.x == 0 && tid == 0 && clear_err) a.err[0] = a.err[1] = 0;
   const Unit p = unit_of(a, u);
   const bool whole = a.layer[p.l].k_l >= p.n;
-  const int npre = whole ? 1 : p.n - a.alpha, kk = a.layer[p.l].k_l - a.alpha;
+  const int npre = whole ? 1 : p.n - a.alpha;
+  const bool ask = !whole && asked(a, p.l, p.n);
   const uint16_t* Q = queries_of(a, p);
   const uint16_t* K = keys_of(a, p);
   bf16x8 kf[2][KS];
@@ -237,8 +243,7 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     const float off = lane < 8 ? 0.f : y - (lane < 32 ? sum.x * (1.f / 24.f) : (sum.y - sum.x) * (1.f / 32.f));
     // (a block that is not the unit's first does not decide; that it leaves is rarer, and void weights have the head handed on)
     const float least = row0 == 0 ? a.min_spread : 0.75f * a.min_spread;
-    const bool skip = (a.scored[p.l >> 5] >> (p.l & 31) & 1) != 0 || npre < kSiftMinKeys || (int64_t)kk * a.min_share > npre;
-    if (skip || !(wave_sums(off * off).y >= 54.f * least * least)) {  // (the same in all waves)
+    if (!ask || !(wave_sums(off * off).y >= 54.f * least * least)) {  // (the same in all waves)
       if (tid < rows) a.omega[(size_t)u * a.Rs + row0 + tid] = 0.f;
       if (row0 == 0 && tid == 0) *flag = kSiftObjects;
       return;
@@ -350,7 +355,7 @@ __device__ __forceinline__ bool advance(const SiftArgs& a, Pass& p) {
 // The workgroup's first pass; false if it has none.  wsum: 2 kW + 2 words of LDS, read before the next barrier.
 __device__ __forceinline__ bool first_pass(const SiftArgs& a, Pass& p, int* wsum) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // wsum: [kW] sums of the waves, [kW], [kW + 1] the first item's place; [kW] sums of the waves over all that is to be scored
+  // wsum: [kW] sums of the waves, [kW], [kW + 1] the first item's place; [kW] sums of the waves over all that were asked
   int* const wall = wsum + kW + 2;
   const int E = a.L * a.B;
   int lo = 0, hi = 0, u0 = 0, c0 = 0;
@@ -360,13 +365,15 @@ __device__ __forceinline__ bool first_pass(const SiftArgs& a, Pass& p, int* wsum
     for (int e0 = 0; e0 < E; e0 += kT) {
       const int e = e0 + tid;
       if (round == 0 || E > kT) {  // (else the first round's are still there)
+        int items = 0;
         c = parts = 0;
         if (e < E) {
           const int l = e / a.B, b = e - l * a.B, n = valid_length(a, b);
           parts = a.layer[l].k_l < n ? (n + kLagKeys - 1) / kLagKeys : 0;
           c = sift_heads<false>(flags_of(a, l, b), a.Hkv, kSiftObjects) * parts;
+          items = asked(a, l, n) ? a.Hkv * parts : 0;
         }
-        const int v = (int)wave_inclusive_sum((uint32_t)c), y = (int)wave_inclusive_sum((uint32_t)(a.Hkv * parts));
+        const int v = (int)wave_inclusive_sum((uint32_t)c), y = (int)wave_inclusive_sum((uint32_t)items);
         lds_barrier();
         if (lane == 63) {
           wsum[wave] = v;

@@ -380,6 +380,11 @@ def test_sifting_only_where_what_it_hands_on_fits_a_launch():
                         sifted += 1
                         assert N < 65025 or rounds(B, Hkv, N) <= 254, (B, Hkv, N, R)
     assert sifted > 10000
+    # not where more than a 43rd of the keys is kept, with average pooling fewer
+    for k, pool, pool_w, kernel in ((760, 1, 7, "score_sift"), (762, 1, 7, "score_lag"), (399, 2, 5, "score_sift"), (400, 2, 5, "score_lag")):
+        desc = _shape(1, 32, 8, 128, 32768, 32)
+        desc.k_l, desc.pool, desc.pool_w = 32 + k, pool, pool_w
+        assert binding.scoring_route(desc, 32, kept_only=True)[0] == kernel
     assert binding.scoring_route(_shape(1, 32, 8, 128, 32768, 32), 32)[0] == "score_lag"  # (scores of every key are asked for)
 
 

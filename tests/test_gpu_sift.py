@@ -465,3 +465,31 @@ def test_second_sink(at, d, G, alpha, pool, pw):
     full, _ = _run(Qs, Ks, Vs, [k] * 2, pool, pw, scores=True)
     for l in range(2):
         _same(call.outputs[l], full.outputs[l])
+
+
+@pytest.mark.parametrize("fit,taken", [(13, True), (11, False)])
+def test_layers_that_keep_many(fit, taken):
+    """30 layers of 8 x 16k keys, most of which keep more than a 43rd of their keys: the others are sifted from 1.5 million keys on, those
+    are not asked."""
+    alpha, G, N, L = 32, 6, 16384, 30
+    data = [_inputs(1, G, 8, 64, N, alpha, seed=190 + l) for l in range(2)]
+    Qs, Ks, Vs = ([data[l % 2][i] for l in range(L)] for i in range(3))
+    ks = [alpha + (380 if l % 2 == 0 and l // 2 < fit else 381) for l in range(L)]   # 380 * 43 <= 16352 < 381 * 43
+    print("sift large budgets", fit, flush=True)
+    calls = []
+    for scores in (False, True):
+        call = binding.LayersCall(Qs, Ks, Vs, ks, MAX, 7, want_scores=scores)
+        events = binding.HipEvents(5 * L + 1)
+        ids = [binding.KERNEL_NAMES[i] for i in binding.run_profiled(call, events)] if not scores else call.run()
+        torch.cuda.synchronize()
+        events.close()
+        assert scores or ("score_sift" in ids) == taken
+        calls.append(call)
+    if taken:
+        flags = calls[0].workspace[8:8 + 4 * L * 8].view(torch.int32).cpu().numpy().reshape(L, 1, 8)
+        want = np.array([0 if k == alpha + 380 else 1 for k in ks])[:, None, None] + np.zeros((1, 1, 8), np.int64)
+        assert np.array_equal(flags, want) and np.array_equal(_scored_again(calls[0], flags), want != 0)
+    for l in range(L):
+        _same(calls[0].outputs[l], calls[1].outputs[l])
+    for a, b in zip(*(binding.attention_recall(c) for c in calls)):
+        assert (a - b).abs().max().item() <= 1e-5
