@@ -141,9 +141,8 @@ __device__ __forceinline__ float2 wave_sums(float v) {
 }
 
 // ---- estimates of the normalisers of 128 rows of a unit; with its first rows, whether it is worth it ----
-// Where it is not, that is seen from the 64 keys of the references, and the sample's multiplications are left out (31 -> 14 us): 32
-// layers x 8 heads x 32k keys, 128 rows without a common direction, which the one-pass kernel takes in 662 us, 692 -> 677 us; 24 layers,
-// 512 rows, 1466 -> 1347 of 1332; 80 layers 4565 -> 4541 of 4503.
+// Where it is not, that is seen from the 64 keys of the references, and the sample is left out (256 units of 128 rows 31 -> 10 us).  It is
+// requested behind that: in front of it, it held the references' keys up and cost more than its latency does here (29 -> 26 us where it is used).
 // What bounds it: latencies, and the address units, which take a fragment's 32 rows one by one.  So queries and the keys that
 // several waves multiply come through LDS (256 units of 128 rows 31 -> 26 us, 640 of 512 rows 154 -> 98, against 64 rows per
 // workgroup and every key as fragments from memory).
@@ -177,8 +176,6 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     kb.request(0, [&](int i) { return K + (size_t)(i < 64 ? min((int)((uint32_t)npre * (uint32_t)(i >> 3) >> 3) + (i & 7), npre - 1) : min(npre + i - 64, p.n - 1)) * a.kv_st; });
     qb.request(row0, [&](int row) { return query_row_of(a, Q, row); });
     fb.request(0, [&](int i) { return K + (size_t)min(i, npre - 1) * a.kv_st; });
-    sample(0, kf[0]);
-    sample(1, kf[1]);
   }
   // the words of the kernel that takes the other sequences
   const size_t group0 = (size_t)u * a.groups + row0 / 64;
@@ -250,6 +247,8 @@ __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, i
     }
     if (row0 == 0 && tid == 0) *flag = 0;
   }
+  sample(0, kf[0]);
+  sample(1, kf[1]);
   if (rt < ntile) {
     // the first 64 keys, which count themselves: sinks lie there, and the sample would miss them (one at key 20 that all rows see, 32
     // layers x 8 heads x 32k keys, 128 rows: the weights of every head lay apart, and the call took 1245 us, now 542; this takes 2)
