@@ -351,7 +351,7 @@ static LagPlan lag_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mode
 //   316, of 128k 458 -> 316; 3 million 272 -> 249, 259 -> 259; 2 million 193 -> 194, 181 -> 194, 258 -> 214; 1 million 106 -> 125.
 //   512 rows, of 32k keys, 3 million 700 -> 593, 2 million 480 -> 418, 1 million 250 -> 241; 256 rows, 4 million 522 -> 456, 2 million
 //   284 -> 271, 1 million 153 -> 173.  Queries without a common direction (32 layers x 32k, 128 rows), whose heads are all handed on:
-//   662 -> 677, and as much more at fewer keys, so that the lines lie where the gain is a sixth.
+//   662 -> 670, and as much more at fewer keys, so that the lines lie where the gain is a sixth.
 // The statistics, lists and jobs lie where the pooled scores lie later on, behind the words of the lagging kernel.
 constexpr int kSiftMinRows = 65;     // (64 rows: K's read binds either way)
 constexpr int kSiftMinLen = 16384;

@@ -30,7 +30,7 @@
 // kernel 622 .. 655), power at 512 rows (80 layers 3.2 ms at 1.8 GHz; 4.3: two key tiles per
 // query fragment, sixteen waves, or products and exponentials of two waves in turn by barriers change the clock, 1.80 .. 1.94 GHz, and
 // the time to 3.2 .. 3.5).  A launch begins with 12 us until the first product.  The kernels around it are chains of latencies:
-// 27, 25 and 33 us for 256 heads of 32k keys (the selection kernel, which takes 27 otherwise, is left with 11).
+// 26, 26 and 33 us for 256 heads of 32k keys (the selection kernel, which takes 27 otherwise, is left with 11).
 #include <type_traits>
 
 #include "pkv_internal.h"
@@ -144,8 +144,8 @@ __device__ __forceinline__ float2 wave_sums(float v) {
 // Where it is not, that is seen from the 64 keys of the references, and the sample is left out (256 units of 128 rows 31 -> 10 us).  It is
 // requested behind that: in front of it, it held the references' keys up and cost more than its latency does here (29 -> 26 us where it is used).
 // What bounds it: latencies, and the address units, which take a fragment's 32 rows one by one.  So queries and the keys that
-// several waves multiply come through LDS (256 units of 128 rows 31 -> 26 us, 640 of 512 rows 154 -> 98, against 64 rows per
-// workgroup and every key as fragments from memory).
+// several waves multiply come through LDS (256 units of 128 rows 31 -> 26 us, 640 of 512 rows 154 -> 98 when this was made, 111 with the
+// first 64 keys and the question, against 64 rows per workgroup and every key as fragments from memory).
 template <int D>
 __global__ __launch_bounds__(kT, 4) void sift_prepare_kernel(const SiftArgs a, int clear_err) {
   constexpr int KS = D / 16;
