@@ -357,9 +357,12 @@ constexpr int kSiftMinRows = 65;     // (64 rows: K's read binds either way)
 constexpr int kSiftMinLen = 16384;
 constexpr int64_t kSiftMinTotal = 4 << 20, kSiftMinTotalMany = 3 << 20;  // keys of a call; with more than 128 rows
 // Layers that keep many of their keys are left to the lagging kernel (their lists would not fit an eighth of the keys: they hold about 4
-//   keys per key to keep, with average pooling 2.5 + w), and where what is left of a call is less than the line, with more than 128 rows
-//   than half of it, so is the call: 20 layers x 31k keys, 128 rows, 6 layers left, 614 us, tried in vain 638; 7 sequences x 8 layers x 22k, 3
-//   layers left 804, sifted 838; 36 layers x 43k, 256 rows, 15 layers left 1900, sifted 1711; 2 x 8 x 42k, 140 rows, 3.5 left 620, 590.
+//   keys per key to keep, with average pooling 2.5 + w), and where what is left of a call is less than half of the line, so is the call.
+//   Without estimates -> with them, us: 128 rows, one to six sequences, 3.4 million keys left of 9 million 1076 -> 969, 2.6 of 8 959 -> 888, 3.3 of
+//   4.6 (64 numbers a key) 396 -> 320, 2.4 of 4.8 514 -> 532, 1.5 of 5.5 541 -> 589, 1.1 of 5.4 658 -> 675; 20 layers x 31k keys, 6 layers
+//   left, 614 -> 638; 256 rows, 15 of 36 layers x 43k 1900 -> 1711, 1.4 million of 8 1133 -> 1109, 0.9 of 5 643 -> 654.  Sequence lengths are not
+//   known here, and a batch with keys that it does not count is tried in vain more easily: half of the longest to the longest, 128 rows, 3.7
+//   million 709 -> 662, 442 -> 408, 3.2 million of 52k 465 -> 419, of 17k 841 -> 860, 2.5 million 334 -> 354, so three quarters of the line there.
 static int sift_min_share(const pkv_layer_desc& d) { return d.pool == PKV_POOL_AVG && d.pool_w > 1 ? 27 + 11 * d.pool_w : 43; }
 static bool sift_layer(const pkv_layer_desc& d) {
   return d.k_l < d.N && (int64_t)(d.k_l - d.alpha) * sift_min_share(d) <= d.N - d.alpha;
@@ -375,7 +378,7 @@ static SiftPlan sift_plan(const Plan& plan, const pkv_layer_desc& d, bool lse_mo
   const SiftPlan none = {0, {0, 0, 0, false}};
   if (d.flags != 0 || plan.R < kSiftMinRows || d.N < kSiftMinLen || d.N - d.alpha > kSiftMaxKeys || d.pool_w > kSiftMaxPoolW) return none;
   const int64_t line = plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal;
-  if ((int64_t)scoring * plan.BH * d.N < line || (int64_t)fit * plan.BH * d.N < (plan.R > 128 ? line / 2 : line)) return none;
+  if ((int64_t)scoring * plan.BH * d.N < line || (int64_t)fit * plan.BH * d.N < (plan.R > 128 || !ragged ? line / 2 : line / 4 * 3)) return none;
   // (Dealing takes whole rounds for units of 128 items and more, so that a layer of many of them can be too much for a launch
   // although it is not when all units are taken in order: 448 heads of 65 536 keys.)
   const SiftPlan p = {(plan.R + 63) / 64 * 64, lag_plan(plan, d, lse_mode, ragged, true)};
@@ -509,7 +512,8 @@ static int run_layers(int32_t L, const pkv_layer_desc* descs, const Plan& plan, 
         fa.sample_tiles = fa.pool == PKV_POOL_AVG ? 4 : 2;  // (its lists are longer)
         fa.sample_shift = fa.sample_tiles == 4 ? 7 : 6;
         fa.min_share = sift_min_share(d);
-        fa.min_items = (int32_t)((plan.R > 128 ? kSiftMinTotalMany / 2 : kSiftMinTotal / 4 * 3) / kLagKeys);
+        // (an eighth below half of the line, so that a call just above it has room for heads that object)
+        fa.min_items = (int32_t)((plan.R > 128 ? kSiftMinTotalMany : kSiftMinTotal) / 16 * 7 / kLagKeys);
         fa.min_spread = fa.pool == PKV_POOL_AVG ? kSiftSpreadAvg : kSiftSpread;
         fa.alpha_magic = alpha_magic;
         fa.bh_magic = 0xFFFFFFFFu / (uint32_t)plan.BH;

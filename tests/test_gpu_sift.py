@@ -467,18 +467,20 @@ def test_second_sink(at, d, G, alpha, pool, pw):
         _same(call.outputs[l], full.outputs[l])
 
 
-@pytest.mark.parametrize("fit,taken", [(13, True), (11, False)])
-def test_layers_that_keep_many(fit, taken):
-    """30 layers of 8 x 16k keys, most of which keep more than a 43rd of their keys: the others are sifted from 1.5 million keys on, those
-    are not asked."""
-    alpha, G, N, L = 32, 6, 16384, 30
+@pytest.mark.parametrize("G,fit,taken,ragged", [(6, 12, True, False), (6, 11, False, False), (4, 16, True, False), (4, 15, False, False),
+                                                (4, 24, True, True), (4, 23, False, True)])
+def test_layers_that_keep_many(G, fit, taken, ragged):
+    """Layers of 8 x 16k keys, most of which keep more than a 43rd of their keys: the others are sifted from 1.5 million keys on with more than
+    128 rows, from 2 million with 128, with sequence lengths from 3 million, those are not asked."""
+    alpha, N, L = 32, 16384, 2 * fit + 8
+    lens = torch.full((1,), N, dtype=torch.int32, device="cuda") if ragged else None
     data = [_inputs(1, G, 8, 64, N, alpha, seed=190 + l) for l in range(2)]
     Qs, Ks, Vs = ([data[l % 2][i] for l in range(L)] for i in range(3))
     ks = [alpha + (380 if l % 2 == 0 and l // 2 < fit else 381) for l in range(L)]   # 380 * 43 <= 16352 < 381 * 43
-    print("sift large budgets", fit, flush=True)
+    print("sift large budgets", G, fit, ragged, flush=True)
     calls = []
     for scores in (False, True):
-        call = binding.LayersCall(Qs, Ks, Vs, ks, MAX, 7, want_scores=scores)
+        call = binding.LayersCall(Qs, Ks, Vs, ks, MAX, 7, seq_lens=lens, want_scores=scores)
         events = binding.HipEvents(5 * L + 1)
         ids = [binding.KERNEL_NAMES[i] for i in binding.run_profiled(call, events)] if not scores else call.run()
         torch.cuda.synchronize()
